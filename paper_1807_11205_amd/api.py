@@ -186,10 +186,17 @@ def _ws(ws: Optional[torch.Tensor]):
     return ws.data_ptr(), ws.numel() * ws.element_size()
 
 
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)   # the current stream's handle without a Stream object
+_get_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream(stream):
+    """A hipStream_t as the integer ctypes passes on; None is torch's current stream."""
     if stream is None:
+        if _raw_stream is not None and _get_device is not None:
+            return _raw_stream(_get_device())
         stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 def jz_version() -> int:
@@ -214,37 +221,53 @@ def jz_bn_workspace_bytes(rows: int, channels: int) -> int:
     return n.value
 
 
-def jz_bn_relu_fwd(rows, channels, x16, gamma, beta, eps, relu, y16, save_mean, save_invstd, ws, stream=None):
-    """y16 = [relu](gamma * (x16 - mean) * invstd + beta) with the mini-batch statistics, which are written to save_*."""
+def bind_bn_relu_fwd(rows, channels, x16, gamma, beta, eps, relu, y16, save_mean, save_invstd, ws) -> "BoundCall":
+    """jz_bn_relu_fwd with its arguments checked and marshalled once (see BoundCall)."""
     h, f = torch.float16, torch.float32
     wp, wn = _ws(ws)
-    _check(lib().jz_bn_relu_fwd(rows, channels, _dev_ptr(x16, h, rows * channels, "x16"), _dev_ptr(gamma, f, channels, "gamma"),
-                                _dev_ptr(beta, f, channels, "beta"), float(eps), int(bool(relu)),
-                                _dev_ptr(y16, h, rows * channels, "y16"), _dev_ptr(save_mean, f, channels, "save_mean"),
-                                _dev_ptr(save_invstd, f, channels, "save_invstd"), wp, wn, _stream(stream)), "jz_bn_relu_fwd")
+    args = (rows, channels, _dev_ptr(x16, h, rows * channels, "x16"), _dev_ptr(gamma, f, channels, "gamma"), _dev_ptr(beta, f,
+            channels, "beta"), float(eps), int(bool(relu)), _dev_ptr(y16, h, rows * channels, "y16"), _dev_ptr(save_mean, f,
+            channels, "save_mean"), _dev_ptr(save_invstd, f, channels, "save_invstd"), wp, wn)
+    return BoundCall(lib().jz_bn_relu_fwd, args, "jz_bn_relu_fwd", (x16, gamma, beta, y16, save_mean, save_invstd, ws))
+
+
+def jz_bn_relu_fwd(rows, channels, x16, gamma, beta, eps, relu, y16, save_mean, save_invstd, ws, stream=None):
+    """y16 = [relu](gamma * (x16 - mean) * invstd + beta) with the mini-batch statistics, which are written to save_*."""
+    bind_bn_relu_fwd(rows, channels, x16, gamma, beta, eps, relu, y16, save_mean, save_invstd, ws)(stream)
+
+
+def bind_bn_relu_bwd(rows, channels, x16, y16, dy16, gamma, save_mean, save_invstd, relu, dx16, dgamma16, dbeta16, ws) -> "BoundCall":
+    """jz_bn_relu_bwd with its arguments checked and marshalled once (see BoundCall)."""
+    h, f = torch.float16, torch.float32
+    wp, wn = _ws(ws)
+    args = (rows, channels, _dev_ptr(x16, h, rows * channels, "x16"), _dev_ptr(y16, h, rows * channels, "y16"), _dev_ptr(dy16,
+            h, rows * channels, "dy16"), _dev_ptr(gamma, f, channels, "gamma"), _dev_ptr(save_mean, f, channels, "save_mean"),
+            _dev_ptr(save_invstd, f, channels, "save_invstd"), int(bool(relu)), _dev_ptr(dx16, h, rows * channels, "dx16"),
+            _dev_ptr(dgamma16, h, channels, "dgamma16"), _dev_ptr(dbeta16, h, channels, "dbeta16"), wp, wn)
+    return BoundCall(lib().jz_bn_relu_bwd, args, "jz_bn_relu_bwd", (x16, y16, dy16, gamma, save_mean, save_invstd, dx16, dgamma16, dbeta16, ws))
 
 
 def jz_bn_relu_bwd(rows, channels, x16, y16, dy16, gamma, save_mean, save_invstd, relu, dx16, dgamma16, dbeta16, ws, stream=None):
     """dx16, dgamma16, dbeta16 of the layer above; y16 (the forward output) is the ReLU mask and may be None without ReLU."""
-    h, f = torch.float16, torch.float32
+    bind_bn_relu_bwd(rows, channels, x16, y16, dy16, gamma, save_mean, save_invstd, relu, dx16, dgamma16, dbeta16, ws)(stream)
+
+
+def bind_bn_bwd_block_end(rows, channels, x16, y_out16, dya16, dyb16, gamma, save_mean, save_invstd, g16, dx16, dgamma16, dbeta16, ws) -> "BoundCall":
+    """jz_bn_bwd_block_end with its arguments checked and marshalled once (see BoundCall)."""
+    h, f, n = torch.float16, torch.float32, rows * channels
     wp, wn = _ws(ws)
-    _check(lib().jz_bn_relu_bwd(rows, channels, _dev_ptr(x16, h, rows * channels, "x16"), _dev_ptr(y16, h, rows * channels, "y16"),
-                                _dev_ptr(dy16, h, rows * channels, "dy16"), _dev_ptr(gamma, f, channels, "gamma"),
-                                _dev_ptr(save_mean, f, channels, "save_mean"), _dev_ptr(save_invstd, f, channels, "save_invstd"),
-                                int(bool(relu)), _dev_ptr(dx16, h, rows * channels, "dx16"), _dev_ptr(dgamma16, h, channels, "dgamma16"),
-                                _dev_ptr(dbeta16, h, channels, "dbeta16"), wp, wn, _stream(stream)), "jz_bn_relu_bwd")
+    args = (rows, channels, _dev_ptr(x16, h, n, "x16"), _dev_ptr(y_out16, h, n, "y_out16"), _dev_ptr(dya16, h, n, "dya16"),
+            _dev_ptr(dyb16, h, n, "dyb16"), _dev_ptr(gamma, f, channels, "gamma"), _dev_ptr(save_mean, f, channels,
+            "save_mean"), _dev_ptr(save_invstd, f, channels, "save_invstd"), _dev_ptr(g16, h, n, "g16"), _dev_ptr(dx16, h, n,
+            "dx16"), _dev_ptr(dgamma16, h, channels, "dgamma16"), _dev_ptr(dbeta16, h, channels, "dbeta16"), wp, wn)
+    return BoundCall(lib().jz_bn_bwd_block_end, args, "jz_bn_bwd_block_end",
+                     (x16, y_out16, dya16, dyb16, gamma, save_mean, save_invstd, g16, dx16, dgamma16, dbeta16, ws))
 
 
 def jz_bn_bwd_block_end(rows, channels, x16, y_out16, dya16, dyb16, gamma, save_mean, save_invstd, g16, dx16, dgamma16, dbeta16, ws,
                         stream=None):
     """g16 = relu-masked (dya16 [+ dyb16]); dx16, dgamma16, dbeta16 = batch-norm backward (no ReLU) of dy = g16."""
-    h, f, n = torch.float16, torch.float32, rows * channels
-    wp, wn = _ws(ws)
-    _check(lib().jz_bn_bwd_block_end(rows, channels, _dev_ptr(x16, h, n, "x16"), _dev_ptr(y_out16, h, n, "y_out16"),
-                                     _dev_ptr(dya16, h, n, "dya16"), _dev_ptr(dyb16, h, n, "dyb16"), _dev_ptr(gamma, f, channels, "gamma"),
-                                     _dev_ptr(save_mean, f, channels, "save_mean"), _dev_ptr(save_invstd, f, channels, "save_invstd"),
-                                     _dev_ptr(g16, h, n, "g16"), _dev_ptr(dx16, h, n, "dx16"), _dev_ptr(dgamma16, h, channels, "dgamma16"),
-                                     _dev_ptr(dbeta16, h, channels, "dbeta16"), wp, wn, _stream(stream)), "jz_bn_bwd_block_end")
+    bind_bn_bwd_block_end(rows, channels, x16, y_out16, dya16, dyb16, gamma, save_mean, save_invstd, g16, dx16, dgamma16, dbeta16, ws)(stream)
 
 
 def jz_conv2d_tune_set(op: int, desc: jz_conv_desc, tile_m: int, tile_n: int, k_tile: int, wavefronts: int, ring: int, splits: int):
@@ -354,7 +377,7 @@ class BoundCall:
 
     def __call__(self, stream=None):
         st = self.fn(*self.args, _stream(stream))
-        if st != JZ_OK:
+        if st:      # JZ_OK is 0
             raise JzError(st, self.where)
 
 
@@ -628,18 +651,23 @@ def jz_conv2d_bn_relu_fwd_workspace_bytes(desc: jz_conv_desc) -> int:
     return n.value
 
 
-def jz_conv2d_bn_relu_fwd(desc, x16, w16, gamma, beta, eps, relu, conv_out16, y16, save_mean, save_invstd, ws, residual16=None,
-                          stream=None):
-    """y16 = [relu](bn(conv(x16, w16)) [+ residual16]); conv_out16 receives the convolution output."""
+def bind_conv2d_bn_relu_fwd(desc, x16, w16, gamma, beta, eps, relu, conv_out16, y16, save_mean, save_invstd, ws, residual16=None) -> "BoundCall":
+    """jz_conv2d_bn_relu_fwd with its arguments checked and marshalled once (see BoundCall)."""
     d, h, f = desc, torch.float16, torch.float32
     n_out = d.N * d.P * d.Q * d.K
     wp, wn = _ws(ws)
-    _check(lib().jz_conv2d_bn_relu_fwd(ctypes.byref(d), _dev_ptr(x16, h, d.N * d.H * d.W * d.C, "x16"),
-                                       _dev_ptr(w16, h, d.K * d.R * d.S * d.C, "w16"), _dev_ptr(gamma, f, d.K, "gamma"),
-                                       _dev_ptr(beta, f, d.K, "beta"), float(eps), _dev_ptr(residual16, h, n_out, "residual16"),
-                                       int(bool(relu)), _dev_ptr(conv_out16, h, n_out, "conv_out16"),
-                                       _dev_ptr(y16, h, n_out, "y16"), _dev_ptr(save_mean, f, d.K, "save_mean"),
-                                       _dev_ptr(save_invstd, f, d.K, "save_invstd"), wp, wn, _stream(stream)), "jz_conv2d_bn_relu_fwd")
+    args = (ctypes.byref(d), _dev_ptr(x16, h, d.N * d.H * d.W * d.C, "x16"), _dev_ptr(w16, h, d.K * d.R * d.S * d.C, "w16"),
+            _dev_ptr(gamma, f, d.K, "gamma"), _dev_ptr(beta, f, d.K, "beta"), float(eps), _dev_ptr(residual16, h, n_out,
+            "residual16"), int(bool(relu)), _dev_ptr(conv_out16, h, n_out, "conv_out16"), _dev_ptr(y16, h, n_out, "y16"),
+            _dev_ptr(save_mean, f, d.K, "save_mean"), _dev_ptr(save_invstd, f, d.K, "save_invstd"), wp, wn)
+    return BoundCall(lib().jz_conv2d_bn_relu_fwd, args, "jz_conv2d_bn_relu_fwd",
+                     (desc, x16, w16, gamma, beta, conv_out16, y16, save_mean, save_invstd, ws, residual16))
+
+
+def jz_conv2d_bn_relu_fwd(desc, x16, w16, gamma, beta, eps, relu, conv_out16, y16, save_mean, save_invstd, ws, residual16=None,
+                          stream=None):
+    """y16 = [relu](bn(conv(x16, w16)) [+ residual16]); conv_out16 receives the convolution output."""
+    bind_conv2d_bn_relu_fwd(desc, x16, w16, gamma, beta, eps, relu, conv_out16, y16, save_mean, save_invstd, ws, residual16)(stream)
 
 
 def jz_conv2d_bwd_data_bn_relu_bwd_workspace_bytes(desc: jz_conv_desc) -> int:
@@ -649,34 +677,46 @@ def jz_conv2d_bwd_data_bn_relu_bwd_workspace_bytes(desc: jz_conv_desc) -> int:
     return n.value
 
 
+def bind_conv2d_bwd_data_bn_relu_bwd(desc, dy16, w16, bn_x16, bn_y16, gamma, save_mean, save_invstd, dz16, bn_dx16, dgamma16, dbeta16,
+                                     ws) -> "BoundCall":
+    """jz_conv2d_bwd_data_bn_relu_bwd with its arguments checked and marshalled once (see BoundCall)."""
+    d, h, f = desc, torch.float16, torch.float32
+    n_in, C = d.N * d.H * d.W * d.C, d.C
+    wp, wn = _ws(ws)
+    args = (ctypes.byref(d), _dev_ptr(dy16, h, d.N * d.P * d.Q * d.K, "dy16"), _dev_ptr(w16, h, d.K * d.R * d.S * d.C, "w16"),
+            _dev_ptr(bn_x16, h, n_in, "bn_x16"), _dev_ptr(bn_y16, h, n_in, "bn_y16"), _dev_ptr(gamma, f, C, "gamma"),
+            _dev_ptr(save_mean, f, C, "save_mean"), _dev_ptr(save_invstd, f, C, "save_invstd"), _dev_ptr(dz16, h, n_in, "dz16"),
+            _dev_ptr(bn_dx16, h, n_in, "bn_dx16"), _dev_ptr(dgamma16, h, C, "dgamma16"), _dev_ptr(dbeta16, h, C, "dbeta16"), wp,
+            wn)
+    return BoundCall(lib().jz_conv2d_bwd_data_bn_relu_bwd, args, "jz_conv2d_bwd_data_bn_relu_bwd",
+                     (desc, dy16, w16, bn_x16, bn_y16, gamma, save_mean, save_invstd, dz16, bn_dx16, dgamma16, dbeta16, ws))
+
+
 def jz_conv2d_bwd_data_bn_relu_bwd(desc, dy16, w16, bn_x16, bn_y16, gamma, save_mean, save_invstd, dz16, bn_dx16, dgamma16, dbeta16, ws,
                                    stream=None):
     """dz16 = bwd_data(dy16, w16); bn_dx16, dgamma16, dbeta16 = backward of the batch norm + ReLU (input bn_x16, output
     bn_y16 = this convolution's forward input) for the incoming gradient dz16."""
+    bind_conv2d_bwd_data_bn_relu_bwd(desc, dy16, w16, bn_x16, bn_y16, gamma, save_mean, save_invstd, dz16, bn_dx16, dgamma16, dbeta16, ws)(stream)
+
+
+def bind_conv2d_bwd_data_block_end_bwd(desc, dy16, w16, dyb16, bn_x16, y_out16, gamma, save_mean, save_invstd, g16, bn_dx16, dgamma16, dbeta16,
+                                     ws) -> "BoundCall":
+    """jz_conv2d_bwd_data_block_end_bwd with its arguments checked and marshalled once (see BoundCall)."""
     d, h, f = desc, torch.float16, torch.float32
     n_in, C = d.N * d.H * d.W * d.C, d.C
     wp, wn = _ws(ws)
-    _check(lib().jz_conv2d_bwd_data_bn_relu_bwd(ctypes.byref(d), _dev_ptr(dy16, h, d.N * d.P * d.Q * d.K, "dy16"),
-                                                _dev_ptr(w16, h, d.K * d.R * d.S * d.C, "w16"), _dev_ptr(bn_x16, h, n_in, "bn_x16"),
-                                                _dev_ptr(bn_y16, h, n_in, "bn_y16"), _dev_ptr(gamma, f, C, "gamma"),
-                                                _dev_ptr(save_mean, f, C, "save_mean"), _dev_ptr(save_invstd, f, C, "save_invstd"),
-                                                _dev_ptr(dz16, h, n_in, "dz16"), _dev_ptr(bn_dx16, h, n_in, "bn_dx16"),
-                                                _dev_ptr(dgamma16, h, C, "dgamma16"), _dev_ptr(dbeta16, h, C, "dbeta16"), wp, wn,
-                                                _stream(stream)), "jz_conv2d_bwd_data_bn_relu_bwd")
+    args = (ctypes.byref(d), _dev_ptr(dy16, h, d.N * d.P * d.Q * d.K, "dy16"), _dev_ptr(w16, h, d.K * d.R * d.S * d.C, "w16"),
+            _dev_ptr(dyb16, h, n_in, "dyb16"), _dev_ptr(bn_x16, h, n_in, "bn_x16"), _dev_ptr(y_out16, h, n_in, "y_out16"),
+            _dev_ptr(gamma, f, C, "gamma"), _dev_ptr(save_mean, f, C, "save_mean"), _dev_ptr(save_invstd, f, C, "save_invstd"),
+            _dev_ptr(g16, h, n_in, "g16"), _dev_ptr(bn_dx16, h, n_in, "bn_dx16"), _dev_ptr(dgamma16, h, C, "dgamma16"),
+            _dev_ptr(dbeta16, h, C, "dbeta16"), wp, wn)
+    return BoundCall(lib().jz_conv2d_bwd_data_block_end_bwd, args, "jz_conv2d_bwd_data_block_end_bwd",
+                     (desc, dy16, w16, dyb16, bn_x16, y_out16, gamma, save_mean, save_invstd, g16, bn_dx16, dgamma16, dbeta16, ws))
 
 
 def jz_conv2d_bwd_data_block_end_bwd(desc, dy16, w16, dyb16, bn_x16, y_out16, gamma, save_mean, save_invstd, g16, bn_dx16, dgamma16, dbeta16,
                                      ws, stream=None):
     """g16 = relu-masked (bwd_data(dy16, w16) [+ dyb16]) by y_out16 > 0; bn_dx16, dgamma16, dbeta16 = batch-norm backward
     (no ReLU, input bn_x16) of dy = g16."""
-    d, h, f = desc, torch.float16, torch.float32
-    n_in, C = d.N * d.H * d.W * d.C, d.C
-    wp, wn = _ws(ws)
-    _check(lib().jz_conv2d_bwd_data_block_end_bwd(ctypes.byref(d), _dev_ptr(dy16, h, d.N * d.P * d.Q * d.K, "dy16"),
-                                                  _dev_ptr(w16, h, d.K * d.R * d.S * d.C, "w16"), _dev_ptr(dyb16, h, n_in, "dyb16"),
-                                                  _dev_ptr(bn_x16, h, n_in, "bn_x16"), _dev_ptr(y_out16, h, n_in, "y_out16"),
-                                                  _dev_ptr(gamma, f, C, "gamma"), _dev_ptr(save_mean, f, C, "save_mean"),
-                                                  _dev_ptr(save_invstd, f, C, "save_invstd"), _dev_ptr(g16, h, n_in, "g16"),
-                                                  _dev_ptr(bn_dx16, h, n_in, "bn_dx16"), _dev_ptr(dgamma16, h, C, "dgamma16"),
-                                                  _dev_ptr(dbeta16, h, C, "dbeta16"), wp, wn, _stream(stream)),
-           "jz_conv2d_bwd_data_block_end_bwd")
+    bind_conv2d_bwd_data_block_end_bwd(desc, dy16, w16, dyb16, bn_x16, y_out16, gamma, save_mean, save_invstd, g16, bn_dx16, dgamma16,
+                                       dbeta16, ws)(stream)

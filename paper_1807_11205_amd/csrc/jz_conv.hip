@@ -7,7 +7,9 @@
 // translation unit per operation (jz_conv_fwd.hip, ...).
 #include <stdio.h>
 #include <stdlib.h>
+#include <string.h>
 
+#include <atomic>
 #include <mutex>
 #include <type_traits>
 #include <vector>
@@ -354,6 +356,7 @@ const Tuned kTuned[] = {
 std::mutex g_tune_mutex;
 std::vector<Tuned> g_tune_rt;
 bool g_use_table = true;
+std::atomic<unsigned> g_tune_generation{1};  // changes whenever one of the above does: plans made before are stale
 
 bool same_key(const Tuned& x, const Tuned& y) {
   return x.op == y.op && x.M == y.M && x.N == y.N && x.K == y.K && x.taps == y.taps && x.scatter == y.scatter;
@@ -502,7 +505,7 @@ void plan_text(const Plan& pl, char* buf, size_t n) {
            a.sc_on ? ", scatter epilogue" : pl.classes ? ", one launch per parity class of the stride" : pl.gen ? ", per-load tap arithmetic" : "");
 }
 
-int make_plan(int op, const jz_conv_desc* d, Plan* pl) {
+int compute_plan(int op, const jz_conv_desc* d, Plan* pl) {
   if (!d) return JZ_ERR_NULL;
   if (op != JZ_FWD && op != JZ_BWD_DATA && op != JZ_BWD_WEIGHT) return JZ_ERR_UNSUPPORTED;
   if (d->N <= 0 || d->H <= 0 || d->W <= 0 || d->C <= 0 || d->K <= 0 || d->R <= 0 || d->S <= 0 || d->stride_h <= 0 ||
@@ -623,9 +626,59 @@ int make_plan(int op, const jz_conv_desc* d, Plan* pl) {
   return JZ_OK;
 }
 
-// One parity class (ca, cb) of a strided multi-tap backward-data layer as a plan of its own (see make_plan).  base: the
+// Plans of the shapes this thread has used lately.  A plan depends on the operation, the descriptor and the tuning state
+// only; making one (table search, then the cost model over every variant and split count) takes 5-10 us of host time,
+// which is more than the launch itself and what a sequence of short layers was bound by (ResNet-50 at batch 8, 64 x 64
+// images: 2.9 ms of host time per step against 2.1 ms of kernels).  Fixed size (256 entries, four probes, ~150 KB per
+// thread that launches convolutions), so it cannot grow; a miss overwrites the first probe's entry.
+struct PlanCacheEntry {
+  unsigned generation = 0;  // 0: empty
+  int op = 0, rc = 0, ca = 0, cb = 0;
+  jz_conv_desc d{};
+  size_t w_elems = 0;  // parity-class plans only
+  Plan pl;
+};
+constexpr unsigned kPlanCacheSize = 256, kPlanCacheProbes = 4;
+
+// The entry for the key (created by `fill` on a miss); ca = cb = -1 for a layer's own plan.  Valid until the thread's
+// next look-up.
+template <class F>
+const PlanCacheEntry& cached_plan(int op, const jz_conv_desc& d, int ca, int cb, F&& fill) {
+  thread_local std::vector<PlanCacheEntry> cache(kPlanCacheSize);
+  unsigned h = 2166136261u;
+  const int key[14] = {op, ca, cb, d.N, d.H, d.W, d.C, d.K, d.R, d.S, d.stride_h, d.stride_w, d.pad_h, d.pad_w};
+  for (int v : key) h = (h ^ (unsigned)v) * 16777619u;
+  h ^= h >> 15;
+  const unsigned gen = g_tune_generation.load(std::memory_order_acquire);
+  for (unsigned i = 0; i < kPlanCacheProbes; ++i) {
+    const PlanCacheEntry& e = cache[(h + i) % kPlanCacheSize];
+    if (e.generation == gen && e.op == op && e.ca == ca && e.cb == cb && memcmp(&e.d, &d, sizeof d) == 0) return e;
+  }
+  unsigned slot = h % kPlanCacheSize;
+  for (unsigned i = 0; i < kPlanCacheProbes; ++i)
+    if (cache[(h + i) % kPlanCacheSize].generation != gen) {
+      slot = (h + i) % kPlanCacheSize;
+      break;
+    }
+  PlanCacheEntry e;
+  e.op = op; e.ca = ca; e.cb = cb;
+  e.d = d;
+  fill(e);
+  e.generation = gen;
+  cache[slot] = e;
+  return cache[slot];
+}
+
+int make_plan(int op, const jz_conv_desc* d, Plan* pl) {
+  if (!d) return JZ_ERR_NULL;
+  const PlanCacheEntry& e = cached_plan(op, *d, -1, -1, [&](PlanCacheEntry& n) { n.rc = compute_plan(op, d, &n.pl); });
+  *pl = e.pl;
+  return e.rc;
+}
+
+// One parity class (ca, cb) of a strided multi-tap backward-data layer as a plan of its own (see compute_plan).  base: the
 // layer's plan; w_off: where this class's packed filter starts in the workspace (elements); false: the class has no pixels.
-bool make_class_plan(const jz_conv_desc* d, const Plan& base, int ca, int cb, Plan* pl, size_t* w_elems) {
+bool compute_class_plan(const jz_conv_desc* d, const Plan& base, int ca, int cb, Plan* pl, size_t* w_elems) {
   const int sh = d->stride_h, sw = d->stride_w;
   const int P = out_dim(d->H, d->pad_h, d->R, sh), Q = out_dim(d->W, d->pad_w, d->S, sw);
   const int Ha = (d->H - ca + sh - 1) / sh, Wb = (d->W - cb + sw - 1) / sw;     // pixels h = ca + sh i, w = cb + sw l
@@ -654,6 +707,15 @@ bool make_class_plan(const jz_conv_desc* d, const Plan& base, int ca, int cb, Pl
   pl->part_offset = 0;
   pl->ws_bytes = 0;
   return true;
+}
+
+bool make_class_plan(const jz_conv_desc* d, const Plan& base, int ca, int cb, Plan* pl, size_t* w_elems) {
+  const PlanCacheEntry& e = cached_plan(JZ_BWD_DATA, *d, ca, cb, [&](PlanCacheEntry& n) {
+    n.rc = compute_class_plan(d, base, ca, cb, &n.pl, &n.w_elems) ? 1 : 0;
+  });
+  *w_elems = e.w_elems;
+  if (e.rc) *pl = e.pl;
+  return e.rc != 0;
 }
 
 // class filters: wp[class][k][j][i][c] = w[k][r0 + sh j][s0 + sw i][c], classes in (ca, cb) row-major order
@@ -907,6 +969,7 @@ extern "C" int jz_conv2d_tune_set(int op, const jz_conv_desc* desc, int tile_m, 
         keys.push_back(Tuned{1, a.M, a.N, a.Kred, a.g.R * a.g.S, a.sc_on, tile_m, tile_n, k_tile, wavefronts, ring, 1});
       }
     std::lock_guard<std::mutex> lock(g_tune_mutex);
+    g_tune_generation.fetch_add(1);
     for (const Tuned& t : keys) {
       bool found = false;
       for (Tuned& e : g_tune_rt)
@@ -924,6 +987,7 @@ extern "C" int jz_conv2d_tune_set(int op, const jz_conv_desc* desc, int tile_m, 
   const Tuned t{op == JZ_FWD ? 0 : op == JZ_BWD_DATA ? 1 : 2, a.M, a.N, a.Kred, a.g.R * a.g.S, a.sc_on,
                 tile_m, tile_n, k_tile, wavefronts, ring, splits};
   std::lock_guard<std::mutex> lock(g_tune_mutex);
+  g_tune_generation.fetch_add(1);
   for (Tuned& e : g_tune_rt)
     if (same_key(e, t)) {
       e = t;
@@ -935,6 +999,7 @@ extern "C" int jz_conv2d_tune_set(int op, const jz_conv_desc* desc, int tile_m, 
 
 extern "C" int jz_conv2d_tune_clear(void) {
   std::lock_guard<std::mutex> lock(g_tune_mutex);
+  g_tune_generation.fetch_add(1);
   g_tune_rt.clear();
   g_use_table = true;
   return JZ_OK;
@@ -942,6 +1007,7 @@ extern "C" int jz_conv2d_tune_clear(void) {
 
 extern "C" int jz_conv2d_tune_use_table(int on) {
   std::lock_guard<std::mutex> lock(g_tune_mutex);
+  g_tune_generation.fetch_add(1);
   g_use_table = on != 0;
   return JZ_OK;
 }

@@ -24,11 +24,11 @@ BN_EPS = 1e-5
 class Op:
     """One library call of the step: what it is, the tensors it reads and writes, and the launch itself."""
 
-    __slots__ = ("kind", "name", "params", "ins", "outs", "call", "side_call", "lane", "joins_side")
+    __slots__ = ("kind", "name", "params", "ins", "outs", "call", "bind", "lane", "joins_side")
 
-    def __init__(self, kind, name, params, ins, outs, call, side_call=None):
+    def __init__(self, kind, name, params, ins, outs, call=None, bind=None):
         self.kind, self.name, self.params, self.ins, self.outs, self.call = kind, name, params, ins, outs, call
-        self.side_call = side_call      # workspace -> the same launch bound to that workspace, for a side stream
+        self.bind = bind                # workspace -> the launch with its arguments marshalled once, bound to that workspace
         self.lane = "main"              # "side": a weight gradient, "proj": the projection-shortcut branch (both may run on a side stream)
         self.joins_side = False         # reads what the side stream's projection branch wrote: waits for it
 
@@ -87,7 +87,6 @@ class ResNet50Chain:
         self.loss = torch.zeros(self.N, dtype=f, device=dev)
 
         self._ws_bytes = 16
-        self._pending_ws = []
         self.fwd_ops: List[Op] = []
         self.bwd_ops: List[Op] = []
         self._build()
@@ -102,8 +101,11 @@ class ResNet50Chain:
         self.side_ws = []               # one workspace per side stream, made on first use
         self._side_calls = {}
         self._events = {}
-        for bind in self._pending_ws:
-            bind(self.ws)
+        # the launches' arguments are checked and marshalled once, here: doing that on every call was most of the host time of
+        # a step whose layers are short
+        for op in self.fwd_ops + self.bwd_ops:
+            if op.bind is not None:
+                op.call = op.bind(self.ws)
         self.trace = self.fwd_ops + self.bwd_ops + [self._lars_op()]
 
     # ---- buffers and parameter views --------------------------------------------------------------------------------
@@ -115,12 +117,6 @@ class ResNet50Chain:
         return buf[self.offsets[i]:self.offsets[i + 1]]
 
     # ---- op constructors ---------------------------------------------------------------------------------------------
-    def _later(self, make):
-        """Calls that need the shared workspace are bound once its size is known."""
-        box = {}
-        self._pending_ws.append(lambda ws: box.__setitem__("call", make(ws)))
-        return lambda stream=None: box["call"](stream)
-
     def _conv(self, op, cs, a, b, out, name):
         d = api.conv_desc(self.N, cs.H, cs.H, cs.C, cs.K, cs.R, cs.R, cs.stride, cs.pad)
         self._ws_bytes = max(self._ws_bytes, api.jz_conv2d_workspace_bytes(op, d))
@@ -129,7 +125,7 @@ class ResNet50Chain:
         if op == api.JZ_BWD_WEIGHT and self.presummed and self.flags[self.index[name + ".w"]] & api.JZ_PARAM_GRAD_PRESUMMED:
             sink = api.jz_lars_sumsq_sink(self.ps, self.lars_ws, self.index[name + ".w"])
             bind = lambda ws: api.bind_conv2d_bwd_weight_sumsq(d, a, b, out, sink, ws)
-        o = Op(kind, name, dict(desc=d), [a, b], [out], self._later(bind), bind)
+        o = Op(kind, name, dict(desc=d), [a, b], [out], bind=bind)
         if op == api.JZ_BWD_WEIGHT:
             o.lane = "side"
         return o
@@ -142,7 +138,7 @@ class ResNet50Chain:
         if mode == api.JZ_BWD_WEIGHT and self.presummed and self.flags[self.index[name + ".w"]] & api.JZ_PARAM_GRAD_PRESUMMED:
             sink = api.jz_lars_sumsq_sink(self.ps, self.lars_ws, self.index[name + ".w"])
             bind = lambda ws: api.bind_gemm_fc_bwd_weight_sumsq(B, I, O, a, b, out, sink, ws)
-        o = Op(kind, name, dict(B=B, I=I, O=O), [a, b], [out], self._later(bind), bind)
+        o = Op(kind, name, dict(B=B, I=I, O=O), [a, b], [out], bind=bind)
         if mode == api.JZ_BWD_WEIGHT:
             o.lane = "side"
         return o
@@ -152,9 +148,8 @@ class ResNet50Chain:
         gamma, beta = self._param(self.master, cs.name + ".gamma"), self._param(self.master, cs.name + ".beta")
         mean, invstd = self._buf(C, torch.float32), self._buf(C, torch.float32)
         self._ws_bytes = max(self._ws_bytes, api.jz_bn_workspace_bytes(rows, C))
-        run = lambda ws, stream: api.jz_bn_relu_fwd(rows, C, x, gamma, beta, BN_EPS, relu, y, mean, invstd, ws, stream)
         return Op("bn_fwd", name, dict(rows=rows, C=C, relu=relu, eps=BN_EPS), [x, gamma, beta], [y, mean, invstd],
-                  lambda stream=None: run(self.ws, stream), lambda ws: (lambda stream=None: run(ws, stream))), mean, invstd
+                  bind=lambda ws: api.bind_bn_relu_fwd(rows, C, x, gamma, beta, BN_EPS, relu, y, mean, invstd, ws)), mean, invstd
 
     def _conv_bn_fwd(self, cs, x, w, c, y, relu, residual=None):
         d = api.conv_desc(self.N, cs.H, cs.H, cs.C, cs.K, cs.R, cs.R, cs.stride, cs.pad)
@@ -162,10 +157,9 @@ class ResNet50Chain:
         gamma, beta = self._param(self.master, cs.name + ".gamma"), self._param(self.master, cs.name + ".beta")
         mean, invstd = self._buf(C, torch.float32), self._buf(C, torch.float32)
         self._ws_bytes = max(self._ws_bytes, api.jz_conv2d_bn_relu_fwd_workspace_bytes(d))
-        run = lambda ws, stream: api.jz_conv2d_bn_relu_fwd(d, x, w, gamma, beta, BN_EPS, relu, c, y, mean, invstd, ws, residual, stream)
         return Op("conv_bn_fwd", cs.name, dict(desc=d, rows=rows, C=C, relu=relu, eps=BN_EPS), [x, w, gamma, beta, residual],
-                  [c, y, mean, invstd], lambda stream=None: run(self.ws, stream),
-                  lambda ws: (lambda stream=None: run(ws, stream))), mean, invstd
+                  [c, y, mean, invstd],
+                  bind=lambda ws: api.bind_conv2d_bn_relu_fwd(d, x, w, gamma, beta, BN_EPS, relu, c, y, mean, invstd, ws, residual)), mean, invstd
 
     def _block_end(self, cs, x, mean, invstd, dx, end, name):
         """ReLU gradient of the block output (one or two incoming contributions, named in `end`) and the batch-norm
@@ -174,9 +168,9 @@ class ResNet50Chain:
         gamma = self._param(self.master, cs.name + ".gamma")
         dgamma, dbeta = self._param(self.grad, cs.name + ".gamma"), self._param(self.grad, cs.name + ".beta")
         op = Op("bn_bwd_block_end", name, dict(rows=rows, C=C), [x, end["out"], end["dya"], end["dyb"], gamma, mean, invstd],
-                [end["g"], dx, dgamma, dbeta], None)
-        op.call = lambda stream=None: api.jz_bn_bwd_block_end(rows, C, x, end["out"], end["dya"], end["dyb"], gamma, mean, invstd, end["g"],
-                                                              dx, dgamma, dbeta, self.ws, stream)
+                [end["g"], dx, dgamma, dbeta],
+                bind=lambda ws: api.bind_bn_bwd_block_end(rows, C, x, end["out"], end["dya"], end["dyb"], gamma, mean, invstd, end["g"],
+                                                          dx, dgamma, dbeta, ws))
         end["op"] = op
         return op
 
@@ -184,10 +178,8 @@ class ResNet50Chain:
         rows, C = self.N * cs.P * cs.P, cs.K
         gamma = self._param(self.master, cs.name + ".gamma")
         dgamma, dbeta = self._param(self.grad, cs.name + ".gamma"), self._param(self.grad, cs.name + ".beta")
-        run = lambda ws, stream: api.jz_bn_relu_bwd(rows, C, x, y if relu else None, dy, gamma, mean, invstd, relu, dx, dgamma, dbeta,
-                                                    ws, stream)
         return Op("bn_bwd", name, dict(rows=rows, C=C, relu=relu), [x, y, dy, gamma, mean, invstd], [dx, dgamma, dbeta],
-                  lambda stream=None: run(self.ws, stream), lambda ws: (lambda stream=None: run(ws, stream)))
+                  bind=lambda ws: api.bind_bn_relu_bwd(rows, C, x, y if relu else None, dy, gamma, mean, invstd, relu, dx, dgamma, dbeta, ws))
 
     def _fuse_bwd_pairs(self, seg):
         """A backward-data convolution directly followed by the batch-norm (+ ReLU) backward that reads its output becomes
@@ -203,10 +195,9 @@ class ResNet50Chain:
                 x, y, dz, gamma, mean, invstd = b.ins
                 dx, dgamma, dbeta = b.outs
                 self._ws_bytes = max(self._ws_bytes, api.jz_conv2d_bwd_data_bn_relu_bwd_workspace_bytes(d))
-                run = lambda stream=None, t=(d, dy, w, x, y, gamma, mean, invstd, dz, dx, dgamma, dbeta): \
-                    api.jz_conv2d_bwd_data_bn_relu_bwd(*t, self.ws, stream)
+                bind = lambda ws, t=(d, dy, w, x, y, gamma, mean, invstd, dz, dx, dgamma, dbeta): api.bind_conv2d_bwd_data_bn_relu_bwd(*t, ws)
                 op = Op("conv_bwd_data_bn_bwd", a.name + " + " + b.name, dict(desc=d, rows=b.params["rows"], C=b.params["C"]),
-                        [dy, w, x, y, gamma, mean, invstd], [dz, dx, dgamma, dbeta], run)
+                        [dy, w, x, y, gamma, mean, invstd], [dz, dx, dgamma, dbeta], bind=bind)
                 op.joins_side = a.joins_side or b.joins_side
                 out.append(op)
                 i += 2
@@ -219,10 +210,10 @@ class ResNet50Chain:
                 x, y_out, _, dyb, gamma, mean, invstd = b.ins
                 g, dx, dgamma, dbeta = b.outs
                 self._ws_bytes = max(self._ws_bytes, api.jz_conv2d_bwd_data_bn_relu_bwd_workspace_bytes(d))
-                run = lambda stream=None, t=(d, dy, w, dyb, x, y_out, gamma, mean, invstd, g, dx, dgamma, dbeta): \
-                    api.jz_conv2d_bwd_data_block_end_bwd(*t, self.ws, stream)
+                bind = lambda ws, t=(d, dy, w, dyb, x, y_out, gamma, mean, invstd, g, dx, dgamma, dbeta): \
+                    api.bind_conv2d_bwd_data_block_end_bwd(*t, ws)
                 op = Op("conv_bwd_data_block_end", a.name + " + " + b.name, dict(desc=d, rows=b.params["rows"], C=b.params["C"]),
-                        [dy, w, dyb, x, y_out, gamma, mean, invstd], [g, dx, dgamma, dbeta], run)
+                        [dy, w, dyb, x, y_out, gamma, mean, invstd], [g, dx, dgamma, dbeta], bind=bind)
                 op.joins_side = a.joins_side or b.joins_side
                 out.append(op)
                 i += 2
@@ -308,7 +299,7 @@ class ResNet50Chain:
                 if self.block_end:     # ... and the ReLU gradient in the statistics pass of branch c's backward
                     seg = back_c[:1] + back_p + back_c[1:] + back_b + back_a
                 else:
-                    op = Op("relu_bwd", nm + ".add", {}, [out, dout, None], [ds], None)
+                    op = Op("relu_bwd", nm + ".add", {}, [out, dout, None], [ds])
                     op.call = lambda stream=None, e=end, y=out: (
                         api.jz_relu_bwd_sum(y, e["dya"], e["dyb"], e["g"], stream) if e["dyb"] is not None
                         else api.jz_relu_bwd(y, e["dya"], e["g"], stream))
@@ -380,13 +371,15 @@ class ResNet50Chain:
         says the main stream has produced what it reads), and an op that reads the projection branch's output first
         waits for the side streams.  which: "fwd" or "bwd" (keys of the pre-created events)."""
         if side is None:
+            handle = api._stream(stream)
             for op in ops:
-                op.call(stream)
+                op.call(handle)
             return
         sides = list(side) if isinstance(side, (list, tuple)) else [side]
         while len(self.side_ws) < len(sides):
             self.side_ws.append(torch.zeros(self._ws_bytes, dtype=torch.uint8, device=self.device))
         main = stream if stream is not None else torch.cuda.current_stream()
+        handle, side_handles = api._stream(main), [api._stream(s_) for s_ in sides]
 
         def event(key):
             ev = self._events.get(key)
@@ -403,7 +396,7 @@ class ResNet50Chain:
                             ev = event((which, "join", i, j))
                             ev.record(s_)
                             main.wait_event(ev)
-                op.call(main)
+                op.call(handle)
                 continue
             # weight gradients go round-robin; the projection branches (their weight gradients included) stay in order
             # on the first side stream
@@ -413,11 +406,11 @@ class ResNet50Chain:
                 k += 1
             call = self._side_calls.get((which, i, j))
             if call is None:
-                call = self._side_calls[(which, i, j)] = op.side_call(self.side_ws[j])
+                call = self._side_calls[(which, i, j)] = op.bind(self.side_ws[j])
             ev = event((which, i))
             ev.record(main)                 # what this op reads has just been produced on the main stream
             sides[j].wait_event(ev)
-            call(sides[j])
+            call(side_handles[j])
             dirty[j] = True
         for j, s_ in enumerate(sides):
             if dirty[j]:
