@@ -89,6 +89,39 @@ __global__ __launch_bounds__(128) void pad_to_c4(const unsigned short* __restric
   }
 }
 
+// Channel counts that are not multiples of 8: rows of C halves copied to rows of C8 (zeros behind), `real` of `rows` rows
+// present in the source (the others are all zero: a filter's missing output channels).  Two tensors per launch
+// (blockIdx.y); one 16-byte chunk of the copy per thread and pass.  A pass over the operands, memory-bound.
+struct WidenArgs {
+  const unsigned short* src[2];
+  unsigned short* dst[2];
+  long long chunks[2], real_rows[2];
+  int C[2];
+  jz::FastDiv d_cpr[2];
+};
+__global__ __launch_bounds__(256) void widen_channels(WidenArgs a) {
+  const int t = blockIdx.y;
+  const unsigned cpr = a.d_cpr[t].d;
+  const int C = a.C[t];
+  for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < a.chunks[t]; i += (long long)gridDim.x * 256) {
+    const unsigned row = jz::fd_div((unsigned)i, a.d_cpr[t]);  // at most 2^30 / 8 chunks
+    const int c0 = (int)((unsigned)i - row * cpr) * 8;
+    unsigned short v[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = row < a.real_rows[t] && c0 + e < C ? a.src[t][(size_t)row * C + c0 + e] : (unsigned short)0;
+    *reinterpret_cast<uint4*>(a.dst[t] + i * 8) = make_uint4((unsigned)v[0] | ((unsigned)v[1] << 16), (unsigned)v[2] | ((unsigned)v[3] << 16),
+                                                             (unsigned)v[4] | ((unsigned)v[5] << 16), (unsigned)v[6] | ((unsigned)v[7] << 16));
+  }
+}
+// the way back: dst[row][0..C) = src[row][0..C) of rows C8 long
+__global__ __launch_bounds__(256) void narrow_channels(const unsigned short* __restrict__ src, unsigned short* __restrict__ dst,
+                                                       long long n, jz::FastDiv d_c, int C8) {
+  for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < n; i += (long long)gridDim.x * 256) {
+    const unsigned row = jz::fd_div((unsigned)i, d_c);
+    dst[i] = src[(size_t)row * C8 + ((unsigned)i - row * d_c.d)];
+  }
+}
+
 // dwp[K][R][KT] -> dw[K][R][S][C]
 __global__ __launch_bounds__(256) void unpack_filter_c4(const unsigned short* __restrict__ dwp, unsigned short* __restrict__ dw,
                                                         int K, int R, int S, int C, int KT) {
@@ -376,7 +409,7 @@ void choose_tiling(Plan* pl, bool bk64_ok, int forced_bk) {
   if (pl->fast && (!forced_bk || pl->packed)) {
     const Tuned key{oi, a.M, a.N, a.Kred, a.g.R * a.g.S, a.sc_on, 0, 0, 0, 0, 0, 0};
     auto usable = [&](const Tuned& t) {
-      if (pl->gen && (t.waves != 4 || t.bk != 32 || t.nst != 4)) return false;  // the only kernels of that mode
+      if ((pl->gen || pl->flat) && (t.waves != 4 || t.bk != 32 || t.nst != 4 || t.BM > 128 || t.BN > 128)) return false;  // the only kernels of those modes
       return same_key(t, key) && (forced_bk ? t.bk == forced_bk : (t.bk == 32 || bk64_ok));
     };
     bool use_table;
@@ -407,7 +440,7 @@ void choose_tiling(Plan* pl, bool bk64_ok, int forced_bk) {
   } else {
     for (const Variant& v : kVariants) {
       if (!pl->fast && &v != &kVariants[0]) break;
-      if ((forced_bk || pl->gen) && (v.waves != 4 || v.bk != 32)) continue;  // those kernels exist as 4-wavefront variants only
+      if ((forced_bk || pl->gen || pl->flat) && (v.waves != 4 || v.bk != 32)) continue;  // those kernels exist as 4-wavefront variants only
       if (!forced_bk && v.bk == 64 && !bk64_ok) continue;
       if (v.nst == 3 && v.bk == 32) continue;  // short rings: from the table of measured choices or on request only
       if (v.waves == 8 && v.BM == 128 && v.bk == 32) continue;  // likewise (the model has no fit for it)
@@ -492,6 +525,10 @@ bool stem_fwd_setup(const Plan& pl, const jz_conv_desc* d, StemArgs* sa) {
 
 void plan_text(const Plan& pl, char* buf, size_t n) {
   const GemmArgs& a = pl.args;
+  if (pl.widen) {
+    snprintf(buf, n, "op %d M %d N %d K %d: run as %d -> %d channels on zero-extended copies", pl.op, a.M, a.N, a.Kred, pl.wide.C, pl.wide.K);
+    return;
+  }
   if (pl.stem) {
     const int mb = 128 * stem_fwd_tm(a.N / 32);
     snprintf(buf, n, "op %d M %d N %d K %d: patch kernel, %d pixels x %d channels per block, %d blocks per image, filter resident in LDS, "
@@ -502,8 +539,18 @@ void plan_text(const Plan& pl, char* buf, size_t n) {
            a.N, a.Kred, pl.fast ? "vector" : "element-wise", pl.BM, pl.BN, pl.bk, pl.fast ? pl.waves : 4,
            pl.fast ? pl.nst : 2, a.tiles_m, a.tiles_n,
            a.splits, a.kt_per_split, pl.packed ? ", 4-channel padded copy" : "",
-           a.sc_on ? ", scatter epilogue" : pl.classes ? ", one launch per parity class of the stride" : pl.gen ? ", per-load tap arithmetic" : "");
+           pl.flat ? (pl.classes ? ", flattened taps, one launch per residue of the stride" : ", flattened taps")
+           : a.sc_on ? ", scatter epilogue" : pl.classes ? ", one launch per parity class of the stride" : pl.gen ? ", per-load tap arithmetic" : "");
 }
+
+// whether strided multi-tap backward-data can run as one unit-stride launch per parity class: every class has a tap, and
+// at most 32 of them (the masks)
+bool has_classes(const jz_conv_desc* d) {
+  return (d->stride_h > 1 || d->stride_w > 1) && d->R >= d->stride_h && d->S >= d->stride_w && d->stride_h * d->stride_w <= kMaxClasses &&
+         ((d->R + d->stride_h - 1) / d->stride_h) * ((d->S + d->stride_w - 1) / d->stride_w) <= 32;
+}
+
+void plan_widened(int op, const jz_conv_desc* d, Plan* pl);
 
 int compute_plan(int op, const jz_conv_desc* d, Plan* pl) {
   if (!d) return JZ_ERR_NULL;
@@ -539,13 +586,18 @@ int compute_plan(int op, const jz_conv_desc* d, Plan* pl) {
   if (op == JZ_FWD) {
     a.M = d->N * P * Q; a.N = d->K; a.Kred = d->R * d->S * d->C;
     g.IH = d->H; g.IW = d->W; g.IC = d->C; g.OH = P; g.OW = Q;
-    pl->fast = d->C % bk == 0 || (one_tap && d->C % 8 == 0);
+    pl->flat = d->C % bk != 0 && d->C % 8 == 0 && !one_tap && d->R * d->S <= 32;
+    pl->fast = d->C % bk == 0 || (one_tap && d->C % 8 == 0) || pl->flat;
     bk64_ok = d->C % 64 == 0 || (one_tap && d->C % 8 == 0);
     pl->bytesA = 2 * nx; pl->bytesB = 2 * nw; pl->bytesD = 2 * ny;
   } else if (op == JZ_BWD_DATA) {
     a.M = d->N * d->H * d->W; a.N = d->C; a.Kred = d->R * d->S * d->K;
     g.IH = P; g.IW = Q; g.IC = d->K; g.OH = d->H; g.OW = d->W;
-    pl->fast = (d->K % bk == 0 || (one_tap && d->K % 8 == 0)) && d->C % 8 == 0;
+    // strided multi-tap layers only through their parity classes (each a unit-stride problem); the per-load variant for the
+    // others walks whole k tiles inside one tap
+    pl->flat = d->K % bk != 0 && d->K % 8 == 0 && d->C % 8 == 0 && !one_tap &&
+               (d->stride_h > 1 || d->stride_w > 1 ? has_classes(d) : d->R * d->S <= 32);
+    pl->fast = ((d->K % bk == 0 || (one_tap && d->K % 8 == 0)) && d->C % 8 == 0) || pl->flat;
     bk64_ok = d->K % 64 == 0 || (one_tap && d->K % 8 == 0);
     pl->bytesA = 2 * ny; pl->bytesB = 2 * nw; pl->bytesD = 2 * nx;
   } else {
@@ -619,11 +671,45 @@ int compute_plan(int op, const jz_conv_desc* d, Plan* pl) {
   // on the dy grid with the filter's taps of that class: sh * sw launches of the mask kernels that together do the
   // useful multiply-adds only (the per-load variant fetches and masks every tap for every pixel: sh * sw times the work).
   // Every class needs a tap (R >= sh, S >= sw); the class filters are packed into the workspace by one small launch.
-  pl->classes = pl->gen && op == JZ_BWD_DATA && (d->stride_h > 1 || d->stride_w > 1) && d->R >= d->stride_h &&
-                d->S >= d->stride_w && d->stride_h * d->stride_w <= kMaxClasses &&
-                ((d->R + d->stride_h - 1) / d->stride_h) * ((d->S + d->stride_w - 1) / d->stride_w) <= 32;
+  pl->classes = pl->gen && op == JZ_BWD_DATA && has_classes(d);
   if (pl->classes) pl->ws_bytes = up256((size_t)nw * 2);
+  pl->element_ws_bytes = pl->ws_bytes;
+  if (!pl->fast) plan_widened(op, d, pl);
   return JZ_OK;
+}
+
+// Channel counts that are not multiples of 8 leave nothing to load 16 bytes at a time, and the element-wise kernel is 5-20
+// times slower than the vector kernels.  Where rounding the counts up adds at most half to the multiply-adds, the layer
+// runs on zero-extended copies instead (memory-bound passes over the operands and the result).  Below that (5 -> 3
+// channels would become 8 -> 8) the element-wise kernel stays.
+void plan_widened(int op, const jz_conv_desc* d, Plan* pl) {
+  const int C8 = (d->C + 7) & ~7, K8 = (d->K + 7) & ~7;
+  jz_conv_desc w = *d;
+  w.C = C8;
+  if (op != JZ_FWD) w.K = K8;  // forward takes any number of output channels
+  if (w.C == d->C && w.K == d->K) return;
+  if ((double)w.C * w.K > 1.5 * d->C * d->K) return;
+  Plan in;
+  if (compute_plan(op, &w, &in) != JZ_OK || !in.fast) return;
+  const size_t npix = (size_t)d->N * d->H * d->W, nout = pl->bytesD / 2;
+  const size_t ny = op == JZ_FWD ? nout : (pl->bytesA / 2) / d->K * w.K, nx = npix * w.C, nw = (size_t)w.K * d->R * d->S * w.C;
+  const bool x_wide = w.C != d->C, y_wide = w.K != d->K, w_wide = x_wide || y_wide;
+  if (op == JZ_FWD) {
+    pl->wide_a_bytes = x_wide ? up256(nx * 2) : 0;
+    pl->wide_b_bytes = w_wide ? up256(nw * 2) : 0;
+  } else if (op == JZ_BWD_DATA) {
+    pl->wide_a_bytes = y_wide ? up256(ny * 2) : 0;
+    pl->wide_b_bytes = w_wide ? up256(nw * 2) : 0;
+    pl->wide_d_bytes = x_wide ? up256(nx * 2) : 0;
+  } else {
+    pl->wide_a_bytes = y_wide ? up256(ny * 2) : 0;
+    pl->wide_b_bytes = x_wide ? up256(nx * 2) : 0;
+    pl->wide_d_bytes = w_wide ? up256(nw * 2) : 0;
+  }
+  pl->widen = true;
+  pl->wide = w;
+  const size_t need = pl->wide_a_bytes + pl->wide_b_bytes + pl->wide_d_bytes + in.ws_bytes;
+  if (need > pl->ws_bytes) pl->ws_bytes = need;
 }
 
 // Plans of the shapes this thread has used lately.  A plan depends on the operation, the descriptor and the tuning state
@@ -748,13 +834,16 @@ __global__ __launch_bounds__(256) void pack_class_filters(const unsigned short* 
 
 // a forward plan whose kernel can leave the per-tile column sums: the ring kernels (their LDS holds the sums), no split
 bool plan_leaves_stats(const Plan& pl) {
-  return pl.op == JZ_FWD && pl.fast && pl.args.splits == 1;
+  return pl.op == JZ_FWD && pl.fast && !pl.flat && pl.args.splits == 1;
 }
 // a backward-data plan whose kernel can leave the sums of a batch-norm backward: the ring kernels with masks, no split,
 // no scatter epilogue, whole 16-byte pieces of a row
 bool plan_leaves_bwd_stats(const Plan& pl) {
-  return pl.op == JZ_BWD_DATA && pl.fast && !pl.gen && pl.args.splits == 1 && !pl.args.sc_on && (pl.args.N & 7) == 0;
+  return pl.op == JZ_BWD_DATA && pl.fast && !pl.gen && !pl.flat && pl.args.splits == 1 && !pl.args.sc_on && (pl.args.N & 7) == 0;
 }
+
+int run_widened(int op, const jz_conv_desc* d, const Plan& pl, const void* A, const void* B, void* D, void* ws, size_t ws_bytes,
+                void* stream, const jz::SumsqSink* sink);
 
 // A, B in the kernel's order: FWD (x, w), BWD_DATA (dy, w), BWD_WEIGHT (dy, x)
 int run(int op, const jz_conv_desc* d, const void* A, const void* B, void* D, void* ws, size_t ws_bytes, void* stream,
@@ -769,11 +858,16 @@ int run(int op, const jz_conv_desc* d, const void* A, const void* B, void* D, vo
   if (!A || !B || !D) return JZ_ERR_NULL;
   if (!aligned16(A) || !aligned16(B) || !aligned16(D) || (ws && !aligned16(ws))) return JZ_ERR_ALIGN;
   if (overlaps(D, pl.bytesD, A, pl.bytesA) || overlaps(D, pl.bytesD, B, pl.bytesB)) return JZ_ERR_ALIAS;
+  if (pl.widen && (!ws || ws_bytes < pl.ws_bytes)) {  // no room for the copies: the element-wise kernel
+    pl.widen = false;
+    pl.ws_bytes = pl.element_ws_bytes;
+  }
   if (pl.ws_bytes > 0 && (!ws || ws_bytes < pl.ws_bytes)) return JZ_ERR_WORKSPACE;
   if (pl.ws_bytes > 0 && (overlaps(ws, pl.ws_bytes, A, pl.bytesA) || overlaps(ws, pl.ws_bytes, B, pl.bytesB) ||
                           overlaps(ws, pl.ws_bytes, D, pl.bytesD)))
     return JZ_ERR_ALIAS;
   hipStream_t st = static_cast<hipStream_t>(stream);
+  if (pl.widen) return run_widened(op, d, pl, A, B, D, ws, ws_bytes, stream, sink);
   if (pl.classes) {  // strided multi-tap backward-data: pack the class filters, then one unit-stride launch per class
     unsigned short* wp = static_cast<unsigned short*>(ws);
     const long long nwl = (long long)d->K * d->R * d->S * d->C;
@@ -884,6 +978,60 @@ int run(int op, const jz_conv_desc* d, const void* A, const void* B, void* D, vo
   return rc;
 }
 
+// a layer with channel counts that are not multiples of 8 on zero-extended copies (plan_widened)
+int run_widened(int op, const jz_conv_desc* d, const Plan& pl, const void* A, const void* B, void* D, void* ws, size_t ws_bytes,
+                void* stream, const jz::SumsqSink* sink) {
+  const jz_conv_desc& w = pl.wide;
+  const int RS = d->R * d->S;
+  char* base = static_cast<char*>(ws);
+  char* const inner_ws = base + pl.wide_a_bytes + pl.wide_b_bytes + pl.wide_d_bytes;
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  const long long npix = (long long)d->N * d->H * d->W;
+  const long long nout = (long long)d->N * out_dim(d->H, d->pad_h, d->R, d->stride_h) * out_dim(d->W, d->pad_w, d->S, d->stride_w);
+  WidenArgs wa{};
+  int nt = 0;
+  long long most = 0;
+  auto copy = [&](const void* src, char* dst, long long rows, long long real_rows, int c, int c8) {
+    wa.src[nt] = static_cast<const unsigned short*>(src);
+    wa.dst[nt] = reinterpret_cast<unsigned short*>(dst);
+    wa.chunks[nt] = rows * (c8 / 8);
+    wa.real_rows[nt] = real_rows;
+    wa.C[nt] = c;
+    wa.d_cpr[nt] = make_fastdiv((unsigned)(c8 / 8));
+    if (wa.chunks[nt] > most) most = wa.chunks[nt];
+    ++nt;
+  };
+  const void* a2 = A;
+  const void* b2 = B;
+  if (pl.wide_a_bytes) {
+    a2 = base;
+    if (op == JZ_FWD) copy(A, base, npix, npix, d->C, w.C);
+    else copy(A, base, nout, nout, d->K, w.K);
+  }
+  if (pl.wide_b_bytes) {
+    char* const p = base + pl.wide_a_bytes;
+    b2 = p;
+    if (op == JZ_BWD_WEIGHT) copy(B, p, npix, npix, d->C, w.C);
+    else copy(B, p, (long long)w.K * RS, (long long)d->K * RS, d->C, w.C);
+  }
+  void* d2 = pl.wide_d_bytes ? base + pl.wide_a_bytes + pl.wide_b_bytes : static_cast<char*>(D);
+  int rc = JZ_OK;
+  if (nt > 0) {
+    const long long blocks = (most + 255) / 256;
+    hipLaunchKernelGGL(widen_channels, dim3((unsigned)(blocks < 4096 ? blocks : 4096), (unsigned)nt), dim3(256), 0, st, wa);
+    if ((rc = jz::launch_status()) != JZ_OK) return rc;
+  }
+  const size_t used = (size_t)(inner_ws - base);
+  rc = run(op, &w, a2, b2, d2, ws_bytes > used ? inner_ws : nullptr, ws_bytes - used, stream, nullptr, 0, pl.wide_d_bytes ? nullptr : sink);
+  if (rc != JZ_OK || !pl.wide_d_bytes) return rc;
+  const long long n = op == JZ_BWD_DATA ? npix * d->C : (long long)d->K * RS * d->C;
+  const long long blocks = (n + 255) / 256;
+  hipLaunchKernelGGL(narrow_channels, dim3((unsigned)(blocks < 8192 ? blocks : 8192)), dim3(256), 0, st, static_cast<const unsigned short*>(d2),
+                     static_cast<unsigned short*>(D), n, make_fastdiv((unsigned)d->C), w.C);
+  if ((rc = jz::launch_status()) != JZ_OK) return rc;
+  return sink ? jz::sumsq_half_launch(static_cast<const unsigned short*>(D), n, *sink, st) : JZ_OK;
+}
+
 int fc_desc(int mode, int batch, int in_features, int out_features, jz_conv_desc* d) {
   if (mode != JZ_FWD && mode != JZ_BWD_DATA && mode != JZ_BWD_WEIGHT) return JZ_ERR_UNSUPPORTED;
   if (batch <= 0 || in_features <= 0 || out_features <= 0) return JZ_ERR_SHAPE;
@@ -979,7 +1127,7 @@ extern "C" int jz_conv2d_tune_set(int op, const jz_conv_desc* desc, int tile_m, 
     return JZ_OK;
   }
   // per-load tap arithmetic exists for the four basic 4-wavefront tiles, 32 deep, four-stage ring
-  if (pl.gen && (v->waves != 4 || v->bk != 32 || v->nst != 4 || v->BM > 128 || v->BN > 128)) return JZ_ERR_UNSUPPORTED;
+  if ((pl.gen || pl.flat) && (v->waves != 4 || v->bk != 32 || v->nst != 4 || v->BM > 128 || v->BN > 128)) return JZ_ERR_UNSUPPORTED;
   // the small-channel path runs the 4-wavefront kernels of the four basic tiles at its own k tile depth only
   if (pl.packed && (v->waves != 4 || v->BM > 128 || v->BN > 128 || k_tile != pl.bk || (ring == 3 && k_tile != 32)))
     return JZ_ERR_UNSUPPORTED;
@@ -1055,7 +1203,7 @@ extern "C" int jz_conv2d_bwd_weight_sumsq(const jz_conv_desc* desc, const void* 
   int rc = make_plan(JZ_BWD_WEIGHT, desc, &pl);
   if (rc != JZ_OK) return rc;
   jz::SumsqSink sk;
-  if ((rc = check_sink(sink, dw16, pl.bytesD, ws, pl.ws_bytes, &sk)) != JZ_OK) return rc;
+  if ((rc = check_sink(sink, dw16, pl.bytesD, ws, ws_bytes < pl.ws_bytes ? ws_bytes : pl.ws_bytes, &sk)) != JZ_OK) return rc;
   return run(JZ_BWD_WEIGHT, desc, dy16, x16, dw16, ws, ws_bytes, hip_stream, nullptr, 0, &sk);
 }
 
@@ -1094,7 +1242,7 @@ extern "C" int jz_conv2d_bwd_weight_static(const jz_conv_desc* desc, const void*
   Plan pl;
   int rc = make_plan(JZ_BWD_WEIGHT, desc, &pl);
   if (rc != JZ_OK) return rc;
-  if (pl.ws_bytes > kStaticScratchBytes) return JZ_ERR_WORKSPACE;  // the layer needs more scratch than the array holds
+  if ((pl.widen ? pl.element_ws_bytes : pl.ws_bytes) > kStaticScratchBytes) return JZ_ERR_WORKSPACE;  // the layer needs more scratch than the array holds
   void* ws = nullptr;
   if (pl.ws_bytes > 0 && (rc = static_scratch(&ws)) != JZ_OK) return rc;
   return run(JZ_BWD_WEIGHT, desc, dy16, x16, dw16, ws, ws ? kStaticScratchBytes : 0, hip_stream);  // A = dy, B = x

@@ -13,8 +13,16 @@ struct Plan {
   bool fast = false;    // vector (16-byte) operand access possible
   bool packed = false;  // small-channel layer run on a 4-channel padded copy
   bool gen = false;     // gather with per-load tap arithmetic (more than 32 taps, strided multi-tap backward-data)
+  bool flat = false;    // reduction over the flattened (tap, channel) index: channel counts that are not multiples of the k tile
   bool classes = false; // strided multi-tap backward-data as one unit-stride launch per parity class of the stride
   bool stem = false;    // packed forward layer that runs on the patch kernel (jz_conv_stem.hip) unless column sums are asked for
+  // widened channels: the layer runs as `wide` (channel counts rounded up to 8) on zero-extended copies of its operands in
+  // the workspace, the result is copied back without the extra channels; ws_bytes covers it, element_ws_bytes is what
+  // the element-wise kernel (which this plan also describes) needs and all a caller's smaller workspace has to hold
+  bool widen = false;
+  jz_conv_desc wide{};
+  size_t wide_a_bytes = 0, wide_b_bytes = 0, wide_d_bytes = 0;  // the copies (0: that operand is used where it is)
+  size_t element_ws_bytes = 0;
   bool rt_forced = false;  // the variant comes from jz_conv2d_tune_set (the patch kernel then steps aside)
   int BM = 128, BN = 128;
   int bk = 64;  // k tile depth of the kernel that will run

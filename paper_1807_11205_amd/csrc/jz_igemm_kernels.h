@@ -462,7 +462,7 @@ int launch_one(const GemmArgs& a, hipStream_t st) {
   return jz::launch_status();
 }
 
-template <int OP, int BM, int BN, int TBK, int NST, bool MASKA = false, int WGM = 2, int WGN = 2, bool GEN = false>
+template <int OP, int BM, int BN, int TBK, int NST, bool MASKA = false, int WGM = 2, int WGN = 2, bool GEN = false, bool FLAT = false>
 int launch_dma(const GemmArgs& a, hipStream_t st) {
   constexpr size_t ring_bytes = (size_t)NST * (BM + BN) * 2 * TBK;
   constexpr size_t epi_bytes = (size_t)BM / dma_epass(BM, BN) * (BN + 8) * sizeof(unsigned short);
@@ -470,13 +470,13 @@ int launch_dma(const GemmArgs& a, hipStream_t st) {
   static_assert(smem <= 160 * 1024, "more LDS than a compute unit has");
   static bool attr_set = false;
   if (!attr_set) {
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(&igemm_dma_kernel<OP, BM, BN, TBK, NST, MASKA, WGM, WGN, GEN>),
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(&igemm_dma_kernel<OP, BM, BN, TBK, NST, MASKA, WGM, WGN, GEN, FLAT>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) != hipSuccess)
       return JZ_ERR_LAUNCH;
     attr_set = true;
   }
   unsigned grid = (unsigned)a.tiles_m * (unsigned)a.tiles_n * (unsigned)a.splits;
-  hipLaunchKernelGGL((igemm_dma_kernel<OP, BM, BN, TBK, NST, MASKA, WGM, WGN, GEN>), dim3(grid), dim3(64 * WGM * WGN), smem, st, a);
+  hipLaunchKernelGGL((igemm_dma_kernel<OP, BM, BN, TBK, NST, MASKA, WGM, WGN, GEN, FLAT>), dim3(grid), dim3(64 * WGM * WGN), smem, st, a);
   return jz::launch_status();
 }
 
@@ -485,9 +485,9 @@ int launch_op(const Plan& pl, hipStream_t st) {
   const GemmArgs& a = pl.args;
   constexpr bool IS_FWD = OP == OP_FWD || OP == OP_FWD_STATS;
   if constexpr (OP == OP_FWD_STATS) {
-    if (!pl.fast) return JZ_ERR_UNSUPPORTED;  // only the ring kernels come in this form
+    if (!pl.fast || pl.flat) return JZ_ERR_UNSUPPORTED;  // only the ring kernels come in this form
   } else if constexpr (OP == OP_BWD_DATA_STATS || OP == OP_BWD_DATA_BLOCK_END) {
-    if (!pl.fast || pl.gen || a.sc_on || a.splits != 1 || (a.N & 7) != 0) return JZ_ERR_UNSUPPORTED;
+    if (!pl.fast || pl.gen || pl.flat || a.sc_on || a.splits != 1 || (a.N & 7) != 0) return JZ_ERR_UNSUPPORTED;
   } else {
     if (!pl.fast) return launch_one<OP, 128, 128>(a, st);
   }
@@ -516,6 +516,14 @@ int launch_op(const Plan& pl, hipStream_t st) {
       if (pl.BM == 128 && pl.BN == 64) return launch_dma<OP, 128, 64, 32, 4, false, 2, 2, true>(a, st);
       if (pl.BM == 64 && pl.BN == 128) return launch_dma<OP, 64, 128, 32, 4, false, 2, 2, true>(a, st);
       return launch_dma<OP, 64, 64, 32, 4, false, 2, 2, true>(a, st);
+    }
+  }
+  if constexpr (OP == OP_FWD || OP == OP_BWD_DATA) {
+    if (pl.flat) {  // flattened (tap, channel) reduction: the same four tiles
+      if (pl.BM == 128 && pl.BN == 128) return launch_dma<OP, 128, 128, 32, 4, false, 2, 2, false, true>(a, st);
+      if (pl.BM == 128 && pl.BN == 64) return launch_dma<OP, 128, 64, 32, 4, false, 2, 2, false, true>(a, st);
+      if (pl.BM == 64 && pl.BN == 128) return launch_dma<OP, 64, 128, 32, 4, false, 2, 2, false, true>(a, st);
+      return launch_dma<OP, 64, 64, 32, 4, false, 2, 2, false, true>(a, st);
     }
   }
   // large tiles, one workgroup of 8 wavefronts per compute unit with (nearly) the whole LDS as its ring
