@@ -5,15 +5,21 @@
 // result is narrowed to fp16 for the next forward pass.  The whole thing is HBM-bound (20 bytes per
 // parameter must move), so it is organised as three stream-ordered launches over a fused flat buffer:
 //
-//   lars_reduce    one workgroup per chunk (<= LARS_CH elements inside one tensor): fp64 partial sums of
-//                  g16^2 (and of w^2, unless the workspace still holds them from the previous update) and a
-//                  non-finite flag, stored per chunk (no atomics => deterministic)
-//   lars_finalize  one workgroup per tensor: adds that tensor's chunk partials in index order, forms
-//                  lr*rho_t, ORs the chunk flags
+//   lars_reduce    per chunk (<= LARS_CH elements inside one tensor): the fp64 sum of g16^2 (and of w^2, unless the
+//                  workspace still holds it from the previous update), not finite when a gradient is not, stored per
+//                  chunk (no atomics => deterministic).  It runs at about 3 TB/s because the update in front of it left
+//                  the last-level cache full of lines that have to be written out first (a persistent form that requests
+//                  the next chunk ahead is no faster)
+//   lars_finalize  one workgroup per tensor: adds that tensor's chunk sums in a fixed order, forms lr*rho_t.  A thread
+//                  requests ten sums at once; 1024 threads when a tensor has more chunks than 256 threads take in one
+//                  round (a 38 M-element tensor has 9216: 57 us with 256 threads and a sum per wavefront, 8 us now)
 //   lars_update    one workgroup per chunk, walking the buffer in the opposite direction so that the
 //                  tail the reduce pass touched last is still in the last-level cache; skips everything
 //                  when any tensor raised the flag.  While writing w it accumulates the chunk's sum of w^2,
 //                  which the next update's reduce pass then need not read w for.
+//
+// A set of at most LARS_SMALL_CHUNKS chunks is one launch of one workgroup (lars_small): three launches are 13 us of
+// latency whatever they do.
 //
 // When the kernels that produce the gradients also leave each tensor's sum of squares (jz_sumsq.h), the first two
 // launches have nothing left to do at update time and the update is one launch ("presummed"):
@@ -39,7 +45,10 @@ namespace {
 #endif
 constexpr int LARS_CH = JZ_LARS_CH;  // elements per chunk; a multiple of 2048 (8 per thread and pass)
 constexpr int LARS_THREADS = 256;
-constexpr int LARS_WAVES = LARS_THREADS / 64;  // every wavefront of a chunk keeps its own partial sums
+constexpr int LARS_WAVES = LARS_THREADS / 64;
+constexpr int LARS_FIN_BATCH = 10;       // chunk sums a thread of the finalize kernel requests together
+constexpr int LARS_SMALL_CHUNKS = 4;     // largest set lars_small takes: one chunk per group of threads (18 chunks: 37 us) ...
+constexpr int LARS_SMALL_T = 64;         // ... and this many tensors
 constexpr uint64_t LARS_MAGIC = 0x4a5a4c4152533031ull;  // "JZLARS01"
 
 // Everything a workgroup needs to know about its chunk in one 16-byte record: a kernel's first loads then depend on
@@ -52,10 +61,11 @@ struct ChunkRec {
 
 struct Layout {
   int64_t T = 0, P = 0, n_chunks = 0;
+  int64_t most_chunks = 0;  // of one tensor
   size_t off_header = 0, off_offsets = 0, off_chunk_begin = 0, off_flags = 0, off_chunk_tensor = 0, off_chunk_rec = 0;
   size_t off_state = 0;
   size_t static_bytes = 0;  // everything up to here is written by prepare
-  size_t off_psum_w = 0, off_psum_g = 0, off_pflag = 0, off_coef = 0, off_tflag = 0;
+  size_t off_psum_w = 0, off_psum_g = 0, off_coef = 0, off_tflag = 0;
   size_t off_gsum = 0, off_gflag = 0, off_wsum = 0, total = 0;  // presummed path: gradient sinks, their flags, sum of w^2
 };
 
@@ -73,7 +83,9 @@ int make_layout(const jz_param_set* ps, Layout* L) {
       int64_t n = ps->offsets[t + 1] - ps->offsets[t];
       if (n < 0) return JZ_ERR_SHAPE;
       if (n >= (int64_t(1) << 31)) return JZ_ERR_UNSUPPORTED;
-      chunks += (n + LARS_CH - 1) / LARS_CH;
+      const int64_t nc = (n + LARS_CH - 1) / LARS_CH;
+      chunks += nc;
+      if (nc > L->most_chunks) L->most_chunks = nc;
     }
     L->P = ps->offsets[L->T];
   }
@@ -88,10 +100,9 @@ int make_layout(const jz_param_set* ps, Layout* L) {
   L->off_chunk_rec = o;     o = up256(o + sizeof(ChunkRec) * (chunks ? chunks : 1));
   L->off_state = o;         o = up256(o + 64);
   L->static_bytes = o;
-  const size_t parts = (size_t)(chunks ? chunks : 1) * LARS_WAVES;
-  L->off_psum_w = o;        o = up256(o + sizeof(double) * parts);
+  const size_t parts = (size_t)(chunks ? chunks : 1);
+  L->off_psum_w = o;        o = up256(o + sizeof(double) * parts * LARS_WAVES);
   L->off_psum_g = o;        o = up256(o + sizeof(double) * parts);
-  L->off_pflag = o;         o = up256(o + sizeof(int) * parts);
   L->off_coef = o;          o = up256(o + sizeof(float) * (L->T ? L->T : 1));
   L->off_tflag = o;         o = up256(o + sizeof(int) * (L->T ? L->T : 1));
   L->off_gsum = o;          o = up256(o + jz::kSumsqSinkBytes * (L->T ? L->T : 1));
@@ -145,6 +156,12 @@ bool is_prepared(void* ws, uint64_t sum) {
   return false;
 }
 
+// a chunk's sum of w^2 from its wavefronts' sums
+__device__ __forceinline__ double chunk_sumsq_w(const double* __restrict__ psum_w, int c) {
+  const double2 a = *reinterpret_cast<const double2*>(psum_w + (size_t)c * LARS_WAVES), b = *reinterpret_cast<const double2*>(psum_w + (size_t)c * LARS_WAVES + 2);
+  return ((a.x + a.y) + b.x) + b.y;
+}
+
 struct Tables {
   const uint64_t* header;
   const int64_t* offsets;
@@ -154,9 +171,8 @@ struct Tables {
   const ChunkRec* chunk_rec;
   int* state;    // [0]: 1 when psum_w holds the sums of squares of the current master weights; [1], [2]: 1/S and S as
                  // float bits when the loss scale lives on the device (written by a launch before the update)
-  double* psum_w;  // [n_chunks][LARS_WAVES] partial sums of w^2: one per wavefront, so that no kernel needs a barrier
-  double* psum_g;  // same for the (loss-scaled) gradient
-  int* pflag;      // same: non-finite gradient seen
+  double* psum_w;  // [n_chunks][LARS_WAVES] sums of w^2, one per wavefront: the update kernel then ends without a barrier
+  double* psum_g;  // [n_chunks] sums of the squared (loss-scaled) gradients; Inf / NaN: a gradient of the chunk is not finite
   float* coef;  // lr * rho_t
   int* tflag;
   unsigned long long* gsum;  // [T][kSumsqSubs * kSumsqSubStride]: gradient sum-of-squares sinks
@@ -181,14 +197,27 @@ __device__ __forceinline__ unsigned short float_to_half_bits(float f) {
   return h;
 }
 
-// Sum over the workgroup in a fixed order: lanes by shuffle tree, then the four waves left to right.
-__device__ __forceinline__ double block_sum(double v, double* lds4) {
+// Sum over a workgroup of NW wavefronts in a fixed order: lanes by shuffle tree, then the wavefronts left to right.
+template <int NW>
+__device__ __forceinline__ double block_sum(double v, double* lds) {
   for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
   int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   __syncthreads();
-  if (lane == 0) lds4[wv] = v;
+  if (lane == 0) lds[wv] = v;
   __syncthreads();
-  return ((lds4[0] + lds4[1]) + lds4[2]) + lds4[3];
+  double t = lds[0];
+#pragma unroll
+  for (int i = 1; i < NW; ++i) t += lds[i];
+  return t;
+}
+
+// Workgroup barrier for data exchanged through LDS: unlike __syncthreads() it does not wait for the global stores in flight.
+__device__ __forceinline__ void lds_barrier() {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+#endif
 }
 
 // Sum over the 64 lanes of a wavefront by a fixed shuffle tree; the total ends up in lane 0.
@@ -250,9 +279,9 @@ __device__ __forceinline__ void chunk_body(int64_t s, int64_t e, int64_t* b0, in
   *b1 = a + ((e - a) & ~int64_t(7));
 }
 
-// One thread's share of a chunk's sum of w^2, in the order lars_reduce and lars_update add it (the 8-element groups in
-// turn, then at most one head / tail element).
-__device__ __forceinline__ double chunk_thread_sumsq_w(const ChunkRec& rec, const float* __restrict__ w) {
+// One thread's share (tid of LARS_THREADS) of a chunk's sum of w^2, in the order lars_update adds it (the 8-element groups
+// in turn, then at most one head / tail element).
+__device__ __forceinline__ double chunk_thread_sumsq_w(const ChunkRec& rec, const float* __restrict__ w, int tid) {
   int t;
   int64_t s, e, b0, b1;
   chunk_range(rec, &t, &s, &e);
@@ -260,7 +289,7 @@ __device__ __forceinline__ double chunk_thread_sumsq_w(const ChunkRec& rec, cons
   double sw = 0.0;
 #pragma unroll
   for (int k = 0; k < LARS_IT; ++k) {
-    int64_t i = b0 + (int64_t)(k * LARS_THREADS + threadIdx.x) * 8;
+    int64_t i = b0 + (int64_t)(k * LARS_THREADS + tid) * 8;
     if (i < b1) {
       const float4 a = *reinterpret_cast<const float4*>(w + i), b = *reinterpret_cast<const float4*>(w + i + 4);
       const float wv[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
@@ -269,7 +298,7 @@ __device__ __forceinline__ double chunk_thread_sumsq_w(const ChunkRec& rec, cons
     }
   }
   int64_t nh = b0 - s, nt = e - b1;
-  int64_t k = threadIdx.x;
+  int64_t k = tid;
   if (k < nh + nt) {
     int64_t i = (k < nh) ? s + k : b1 + (k - nh);
     sw = fma((double)w[i], (double)w[i], sw);
@@ -277,118 +306,106 @@ __device__ __forceinline__ double chunk_thread_sumsq_w(const ChunkRec& rec, cons
   return sw;
 }
 
-__global__ __launch_bounds__(LARS_THREADS) void lars_reduce(Tables tb, const float* __restrict__ w,
-                                                            const unsigned short* __restrict__ g16) {
-  const int c = blockIdx.x;
-  const ChunkRec rec = tb.chunk_rec[c];  // requested together with the header: garbage if the header is, but then unused
-  const bool have_w = tb.state[0] != 0;  // written by the previous update, i.e. by an earlier launch
-  if (!table_ok(tb)) return;
+// A thread's gradients of one chunk: its 8-element groups (zero where the chunk has none) and at most one head / tail element.
+struct ChunkGrads {
+  uint4 q[LARS_IT];
+  unsigned short edge;
+};
+__device__ __forceinline__ ChunkGrads load_chunk_grads(const ChunkRec& rec, const unsigned short* __restrict__ g16, int tid) {
+  ChunkGrads r;
   int t;
   int64_t s, e, b0, b1;
   chunk_range(rec, &t, &s, &e);
   chunk_body(s, e, &b0, &b1);
-  double sw = 0.0, sg = 0.0;
-  int bad = 0;
-  uint4 gq[LARS_IT];
-  float4 w0[LARS_IT], w1[LARS_IT];
 #pragma unroll
   for (int k = 0; k < LARS_IT; ++k) {
-    int64_t i = b0 + (int64_t)(k * LARS_THREADS + threadIdx.x) * 8;
-    gq[k] = make_uint4(0, 0, 0, 0);
-    w0[k] = w1[k] = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (i < b1) {
-      gq[k] = *reinterpret_cast<const uint4*>(g16 + i);
-      if (!have_w) {
-        w0[k] = *reinterpret_cast<const float4*>(w + i);
-        w1[k] = *reinterpret_cast<const float4*>(w + i + 4);
-      }
-    }
+    const int64_t i = b0 + (int64_t)(k * LARS_THREADS + tid) * 8;
+    r.q[k] = make_uint4(0, 0, 0, 0);
+    if (i < b1) r.q[k] = *reinterpret_cast<const uint4*>(g16 + i);
   }
+  const int64_t nh = b0 - s, nt = e - b1, k = tid;
+  r.edge = k < nh + nt ? g16[k < nh ? s + k : b1 + (k - nh)] : (unsigned short)0;
+  return r;
+}
+// Its sum of squares; not finite when one of them is not (the sum of finite halves' squares cannot overflow in FP64), so
+// nothing has to be tested per element: the pass is bound by vector arithmetic (13 instructions per element: 3.1 TB/s).
+// The square of a half is exact in FP32 (22 bits), the sum is FP64.
+__device__ __forceinline__ double chunk_thread_sumsq_g(const ChunkGrads& r) {
+  double sg = 0.0;
 #pragma unroll
-  for (int k = 0; k < LARS_IT; ++k) {  // zeros of the groups beyond b1 add nothing
-    float wv[8] = {w0[k].x, w0[k].y, w0[k].z, w0[k].w, w1[k].x, w1[k].y, w1[k].z, w1[k].w};
-    unsigned gw[4] = {gq[k].x, gq[k].y, gq[k].z, gq[k].w};
+  for (int k = 0; k < LARS_IT; ++k) {
+    const unsigned gw[4] = {r.q[k].x, r.q[k].y, r.q[k].z, r.q[k].w};
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-      unsigned short hb = (unsigned short)(gw[j >> 1] >> ((j & 1) * 16));
-      bad |= half_nonfinite(hb);
-      double gd = (double)half_bits_to_float(hb);
-      sg = fma(gd, gd, sg);
-    }
-    if (!have_w) {
-#pragma unroll
-      for (int j = 0; j < 8; ++j) sw = fma((double)wv[j], (double)wv[j], sw);
+      const float g = half_bits_to_float((unsigned short)(gw[j >> 1] >> ((j & 1) * 16)));
+      sg += (double)(g * g);
     }
   }
-  {  // head and tail, at most 7 elements each
-    int64_t nh = b0 - s, nt = e - b1;
-    int64_t k = threadIdx.x;
-    if (k < nh + nt) {
-      int64_t i = (k < nh) ? s + k : b1 + (k - nh);
-      unsigned short hb = g16[i];
-      bad |= half_nonfinite(hb);
-      double wd = have_w ? 0.0 : (double)w[i], gd = (double)half_bits_to_float(hb);
-      sw = fma(wd, wd, sw);
-      sg = fma(gd, gd, sg);
-    }
-  }
-  sw = wave_sum(sw);
-  sg = wave_sum(sg);
-  bad = __any(bad);
+  const float g = half_bits_to_float(r.edge);
+  return sg + (double)(g * g);
+}
+__device__ __forceinline__ bool sum_overflowed(double sg) { return !(sg <= 1.7e308); }  // Inf or NaN
+
+__global__ __launch_bounds__(LARS_THREADS) void lars_reduce(Tables tb, const float* __restrict__ w,
+                                                            const unsigned short* __restrict__ g16) {
+  __shared__ double red[LARS_WAVES];
+  const int c = blockIdx.x;
+  const ChunkRec rec = tb.chunk_rec[c];  // requested together with the header: garbage if the header is, but then unused
+  const bool have_w = tb.state[0] != 0;  // written by the previous update, i.e. by an earlier launch
+  if (!table_ok(tb)) return;
+  const double sg = wave_sum(chunk_thread_sumsq_g(load_chunk_grads(rec, g16, threadIdx.x)));
+  const double sw = have_w ? 0.0 : wave_sum(chunk_thread_sumsq_w(rec, w, threadIdx.x));
   if ((threadIdx.x & 63) == 0) {
-    const int slot = c * LARS_WAVES + (threadIdx.x >> 6);
-    if (!have_w) tb.psum_w[slot] = sw;
-    tb.psum_g[slot] = sg;
-    tb.pflag[slot] = bad ? 1 : 0;
+    red[threadIdx.x >> 6] = sg;
+    if (!have_w) tb.psum_w[(size_t)c * LARS_WAVES + (threadIdx.x >> 6)] = sw;
   }
+  lds_barrier();
+  if (threadIdx.x == 0) tb.psum_g[c] = ((red[0] + red[1]) + red[2]) + red[3];
+}
+
+// gamma rho_t of Eq. 1 on the un-scaled gradient
+__device__ __forceinline__ float lars_rate(int flags, double sw, double sg, float lr, float eta, float loss_scale) {
+  double rho = 1.0;
+  if ((flags & JZ_PARAM_LARS) && sw > 0.0 && sg > 0.0) rho = (double)eta * sqrt(sw) / (sqrt(sg) / (double)loss_scale);
+  return (float)((double)lr * rho);
 }
 
 // scale_dev != nullptr: the loss scale lives on the device (dynamic loss scaling) and replaces the argument
-__global__ __launch_bounds__(LARS_THREADS) void lars_finalize(Tables tb, float lr, float eta, float loss_scale,
-                                                              const float* __restrict__ scale_dev) {
-  __shared__ double red[4];
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void lars_finalize(Tables tb, float lr, float eta, float loss_scale,
+                                                         const float* __restrict__ scale_dev) {
+  __shared__ double red[THREADS / 64];
   if (scale_dev) loss_scale = *scale_dev;
   if (!table_ok(tb)) return;
   const int t = blockIdx.x;
   // the update kernel adjusts the device-resident scale itself, so its workgroups take 1/S from here instead
   if (scale_dev && t == 0 && threadIdx.x == 0) tb.state[1] = __float_as_int(1.0f / loss_scale);
-  const int c0 = tb.chunk_begin[t] * LARS_WAVES, c1 = tb.chunk_begin[t + 1] * LARS_WAVES;
+  const int c0 = tb.chunk_begin[t], c1 = tb.chunk_begin[t + 1];
   double sw = 0.0, sg = 0.0;
-  int bad = 0;
-  // a thread's first FIN_PRE partials are requested together (the largest ResNet-50 tensor has 9 per thread): one
-  // memory round trip instead of one per partial; the additions keep their order
-  constexpr int FIN_PRE = 10;
-  double pw[FIN_PRE], pg[FIN_PRE];
-  int pf[FIN_PRE];
+  constexpr int U = LARS_FIN_BATCH;
+  for (int c = c0 + (int)threadIdx.x; c < c1; c += U * THREADS) {
+    double pw[U], pg[U];
 #pragma unroll
-  for (int j = 0; j < FIN_PRE; ++j) {
-    const int c = c0 + (int)threadIdx.x + j * LARS_THREADS;
-    pw[j] = 0.0; pg[j] = 0.0; pf[j] = 0;
-    if (c < c1) { pw[j] = tb.psum_w[c]; pg[j] = tb.psum_g[c]; pf[j] = tb.pflag[c]; }
-  }
+    for (int j = 0; j < U; ++j) {
+      const int cj = c + j * THREADS;
+      pw[j] = 0.0; pg[j] = 0.0;
+      if (cj < c1) { pw[j] = chunk_sumsq_w(tb.psum_w, cj); pg[j] = tb.psum_g[cj]; }
+    }
 #pragma unroll
-  for (int j = 0; j < FIN_PRE; ++j) { sw += pw[j]; sg += pg[j]; bad |= pf[j]; }
-  for (int c = c0 + (int)threadIdx.x + FIN_PRE * LARS_THREADS; c < c1; c += LARS_THREADS) {
-    sw += tb.psum_w[c];
-    sg += tb.psum_g[c];
-    bad |= tb.pflag[c];
+    for (int j = 0; j < U; ++j) { sw += pw[j]; sg += pg[j]; }
   }
-  sw = block_sum(sw, red);
-  sg = block_sum(sg, red);
-  bad = __syncthreads_or(bad);
+  sw = block_sum<THREADS / 64>(sw, red);
+  sg = block_sum<THREADS / 64>(sg, red);
   if (threadIdx.x == 0) {
-    double rho = 1.0;
-    if ((tb.flags[t] & JZ_PARAM_LARS) && sw > 0.0 && sg > 0.0)
-      rho = (double)eta * sqrt(sw) / (sqrt(sg) / (double)loss_scale);  // Eq. 1 on the un-scaled gradient
-    tb.coef[t] = (float)((double)lr * rho);
-    tb.tflag[t] = bad ? 1 : 0;
+    tb.coef[t] = lars_rate(tb.flags[t], sw, sg, lr, eta, loss_scale);
+    tb.tflag[t] = sum_overflowed(sg) ? 1 : 0;
   }
 }
 
 // Start of a step on the presummed path, one workgroup per tensor (see the top of the file).
 __global__ __launch_bounds__(LARS_THREADS) void lars_begin(Tables tb, const float* __restrict__ w,
                                                            const float* __restrict__ scale_dev) {
-  __shared__ double red[4];
+  __shared__ double red[LARS_WAVES];
   if (!table_ok(tb)) return;
   const int t = blockIdx.x;
   const bool have_w = tb.state[0] != 0;  // written by an earlier launch
@@ -400,18 +417,20 @@ __global__ __launch_bounds__(LARS_THREADS) void lars_begin(Tables tb, const floa
     tb.state[1] = __float_as_int(1.0f / S);
     tb.state[2] = __float_as_int(S);
   }
-  const int c0 = tb.chunk_begin[t] * LARS_WAVES, c1 = tb.chunk_begin[t + 1] * LARS_WAVES;
+  int c0 = tb.chunk_begin[t], c1 = tb.chunk_begin[t + 1];
   if (!have_w) {
     // Fresh workspace: leave in psum_w what lars_reduce would (same elements per thread, same order), chunk by chunk, so
     // that the sum below is the same bits whether the partial sums were carried or are recomputed here.  One workgroup
     // per tensor makes this slow for large tensors; it runs once per jz_lars_prepare.
-    for (int c = tb.chunk_begin[t]; c < tb.chunk_begin[t + 1]; ++c) {
-      const double p = wave_sum(chunk_thread_sumsq_w(tb.chunk_rec[c], w));
-      if ((threadIdx.x & 63) == 0) tb.psum_w[c * LARS_WAVES + (threadIdx.x >> 6)] = p;
+    for (int c = c0; c < c1; ++c) {
+      const double p = wave_sum(chunk_thread_sumsq_w(tb.chunk_rec[c], w, threadIdx.x));
+      if ((threadIdx.x & 63) == 0) tb.psum_w[(size_t)c * LARS_WAVES + (threadIdx.x >> 6)] = p;
     }
     __threadfence_block();
     __syncthreads();
   }
+  c0 *= LARS_WAVES;
+  c1 *= LARS_WAVES;
   // Loads that go past the compute unit's own cache: in the fresh case a partial sum written above may share a cache
   // line with a neighbouring tensor's, which another workgroup on this compute unit may have pulled in before the write.
   double sw = 0.0;
@@ -433,7 +452,7 @@ __global__ __launch_bounds__(LARS_THREADS) void lars_begin(Tables tb, const floa
       sw += __longlong_as_double((long long)__hip_atomic_load(reinterpret_cast<const unsigned long long*>(tb.psum_w + c),
                                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
   }
-  sw = block_sum(sw, red);
+  sw = block_sum<LARS_WAVES>(sw, red);
   if (threadIdx.x == 0) tb.wsum[t] = sw;
 }
 
@@ -503,6 +522,69 @@ __device__ __forceinline__ void lars_step(float& w, float& v, unsigned short gbi
   w16 = float_to_half_bits(wn);                 // cast back for the next forward pass
 }
 
+// One thread's share (tid of LARS_THREADS) of a chunk's update; returns its share of the sum of squares of the new weights.
+__device__ __forceinline__ double update_chunk(const ChunkRec& rec, int tid, float* __restrict__ w, float* __restrict__ v,
+                                               const unsigned short* __restrict__ g16, unsigned short* __restrict__ w16, float coef,
+                                               float lam, float m, float inv_s) {
+  int t;
+  int64_t s, e, b0, b1;
+  chunk_range(rec, &t, &s, &e);
+  chunk_body(s, e, &b0, &b1);
+  float4 w0[LARS_IT], w1[LARS_IT], v0[LARS_IT], v1[LARS_IT];
+  uint4 gq[LARS_IT];
+#pragma unroll
+  for (int k = 0; k < LARS_IT; ++k) {  // every load of the chunk is in flight before the first use
+    int64_t i = b0 + (int64_t)(k * LARS_THREADS + tid) * 8;
+    if (i < b1) {
+      gq[k] = load_stream_u4(g16 + i);
+      w0[k] = load_stream_f4(w + i);
+      w1[k] = load_stream_f4(w + i + 4);
+      v0[k] = load_stream_f4(v + i);
+      v1[k] = load_stream_f4(v + i + 4);
+    }
+  }
+  double sw = 0.0;  // sum of squares of the new weights, in the order lars_reduce would add them
+#pragma unroll
+  for (int k = 0; k < LARS_IT; ++k) {
+    int64_t i = b0 + (int64_t)(k * LARS_THREADS + tid) * 8;
+    if (i < b1) {
+      float wv[8] = {w0[k].x, w0[k].y, w0[k].z, w0[k].w, w1[k].x, w1[k].y, w1[k].z, w1[k].w};
+      float vv[8] = {v0[k].x, v0[k].y, v0[k].z, v0[k].w, v1[k].x, v1[k].y, v1[k].z, v1[k].w};
+      unsigned gw[4] = {gq[k].x, gq[k].y, gq[k].z, gq[k].w};
+      unsigned ow[4];
+#pragma unroll
+      for (int j = 0; j < 8; j += 2) {
+        unsigned short h0, h1;
+        lars_step(wv[j], vv[j], (unsigned short)(gw[j >> 1] & 0xffffu), coef, lam, m, inv_s, h0);
+        lars_step(wv[j + 1], vv[j + 1], (unsigned short)(gw[j >> 1] >> 16), coef, lam, m, inv_s, h1);
+        ow[j >> 1] = (unsigned)h0 | ((unsigned)h1 << 16);
+      }
+#pragma unroll
+      for (int j = 0; j < 8; ++j) sw = fma((double)wv[j], (double)wv[j], sw);
+      store_stream_f4(w + i, wv[0], wv[1], wv[2], wv[3]);
+      store_stream_f4(w + i + 4, wv[4], wv[5], wv[6], wv[7]);
+      store_stream_f4(v + i, vv[0], vv[1], vv[2], vv[3]);
+      store_stream_f4(v + i + 4, vv[4], vv[5], vv[6], vv[7]);
+      store_stream_u4(w16 + i, ow[0], ow[1], ow[2], ow[3]);
+    }
+  }
+  {
+    int64_t nh = b0 - s, nt = e - b1;
+    int64_t k = tid;
+    if (k < nh + nt) {
+      int64_t i = (k < nh) ? s + k : b1 + (k - nh);
+      float wi = w[i], vi = v[i];
+      unsigned short h;
+      lars_step(wi, vi, g16[i], coef, lam, m, inv_s, h);
+      w[i] = wi;
+      v[i] = vi;
+      w16[i] = h;
+      sw = fma((double)wi, (double)wi, sw);
+    }
+  }
+  return sw;
+}
+
 // PRE: the presummed path -- no lars_finalize ran; every wavefront forms its tensor's lr*rho_t itself (lr, eta and, for a
 // fixed loss scale, S come as arguments) and the overflow flags are those of the sinks.
 template <bool PRE>
@@ -519,7 +601,7 @@ __global__ __launch_bounds__(LARS_THREADS) void lars_update(Tables tb, float* __
   // tables is used before the header has been checked
   const int cidx = (int)blockIdx.x < tb.n_chunks ? tb.n_chunks - 1 - (int)blockIdx.x : 0;
   const ChunkRec rec = tb.n_chunks > 0 ? tb.chunk_rec[cidx] : ChunkRec{0, 0, 0};
-  int f = 0;  // every wavefront looks at all tensor flags itself: no barrier anywhere in this kernel
+  int f = 0;  // every wavefront looks at all tensor flags itself
   for (int t = threadIdx.x & 63; t < tb.T; t += 64) f |= PRE ? tb.gflag[t] : tb.tflag[t];
   // PRE: this lane's share of the tensor's gradient sink (the tensor index is garbage if the header is: clamp it)
   // the first wavefront reads the sink (one quadruple per lane) and hands the total to the others through LDS
@@ -550,11 +632,7 @@ __global__ __launch_bounds__(LARS_THREADS) void lars_update(Tables tb, float* __
   }
   if (f) return;  // overflow under loss scaling: the step is skipped as a whole
   if ((int)blockIdx.x >= tb.n_chunks) return;
-  const int c = cidx;
-  int t;
-  int64_t s, e, b0, b1;
-  chunk_range(rec, &t, &s, &e);
-  chunk_body(s, e, &b0, &b1);
+  const int c = cidx, t = rec.tensor;
   float coef;
   if (PRE) {
     if (threadIdx.x < 64) {  // integer sums: the order does not matter
@@ -565,69 +643,74 @@ __global__ __launch_bounds__(LARS_THREADS) void lars_update(Tables tb, float* __
       if (threadIdx.x == 63) sg_shared = jz::sumsq_value(d0, d1, d2, d3);
     }
     __syncthreads();  // every wavefront of the workgroup is here: the returns above depend on nothing wave-specific
-    const double sg = sg_shared;
-    double rho = 1.0;
-    if ((tb.flags[t] & JZ_PARAM_LARS) && sw_t > 0.0 && sg > 0.0)
-      rho = (double)eta * sqrt(sw_t) / (sqrt(sg) / (double)loss_scale);  // Eq. 1 on the un-scaled gradient
-    coef = (float)((double)lr * rho);
+    coef = lars_rate(tb.flags[t], sw_t, sg_shared, lr, eta, loss_scale);
   } else {
     coef = tb.coef[t];
   }
   const float lam = (tb.flags[t] & JZ_PARAM_WEIGHT_DECAY) ? wd : 0.0f;
-  float4 w0[LARS_IT], w1[LARS_IT], v0[LARS_IT], v1[LARS_IT];
-  uint4 gq[LARS_IT];
-#pragma unroll
-  for (int k = 0; k < LARS_IT; ++k) {  // every load of the chunk is in flight before the first use
-    int64_t i = b0 + (int64_t)(k * LARS_THREADS + threadIdx.x) * 8;
-    if (i < b1) {
-      gq[k] = load_stream_u4(g16 + i);
-      w0[k] = load_stream_f4(w + i);
-      w1[k] = load_stream_f4(w + i + 4);
-      v0[k] = load_stream_f4(v + i);
-      v1[k] = load_stream_f4(v + i + 4);
+  const double sw = wave_sum(update_chunk(rec, threadIdx.x, w, v, g16, w16, coef, lam, m, inv_s));
+  if ((threadIdx.x & 63) == 0) tb.psum_w[(size_t)c * LARS_WAVES + (threadIdx.x >> 6)] = sw;
+}
+
+// The whole update of a small set in one launch of one workgroup: four groups of LARS_THREADS threads take the chunks in
+// turn, the sums meet in LDS.  The same sums in the same order as the three launches.  What bounds it is three dependent
+// round trips to memory (records, gradients, weights) and what one compute unit can move.
+__global__ __launch_bounds__(1024) void lars_small(Tables tb, float* __restrict__ w, float* __restrict__ v,
+                                                   const unsigned short* __restrict__ g16, unsigned short* __restrict__ w16, float m,
+                                                   float wd, float inv_s, int* __restrict__ found_inf, DynScale dyn, float lr, float eta,
+                                                   float loss_scale) {
+  __shared__ double pg[LARS_SMALL_CHUNKS][LARS_WAVES], pw[LARS_SMALL_CHUNKS][LARS_WAVES];
+  __shared__ float coef[LARS_SMALL_T];
+  __shared__ int overflow;
+  const int group = threadIdx.x / LARS_THREADS, tid = threadIdx.x % LARS_THREADS;
+  const bool have_w = tb.state[0] != 0;
+  if (dyn.st) {
+    loss_scale = dyn.st->scale;
+    inv_s = 1.0f / loss_scale;
+  }
+  if (!table_ok(tb)) {
+    if (threadIdx.x == 0) *found_inf = -1;
+    return;
+  }
+  if (threadIdx.x == 0) overflow = 0;
+  for (int c = group; c < tb.n_chunks; c += 1024 / LARS_THREADS) {
+    const ChunkRec rec = tb.chunk_rec[c];
+    const double sg = wave_sum(chunk_thread_sumsq_g(load_chunk_grads(rec, g16, tid)));
+    const double sw = have_w ? 0.0 : wave_sum(chunk_thread_sumsq_w(rec, w, tid));
+    if ((tid & 63) == 0) {
+      pg[c][tid >> 6] = sg;
+      pw[c][tid >> 6] = sw;
+      if (!have_w) tb.psum_w[(size_t)c * LARS_WAVES + (tid >> 6)] = sw;  // what a skipped update leaves
     }
   }
-  double sw = 0.0;  // sum of squares of the new weights, in the order lars_reduce would add them
-#pragma unroll
-  for (int k = 0; k < LARS_IT; ++k) {
-    int64_t i = b0 + (int64_t)(k * LARS_THREADS + threadIdx.x) * 8;
-    if (i < b1) {
-      float wv[8] = {w0[k].x, w0[k].y, w0[k].z, w0[k].w, w1[k].x, w1[k].y, w1[k].z, w1[k].w};
-      float vv[8] = {v0[k].x, v0[k].y, v0[k].z, v0[k].w, v1[k].x, v1[k].y, v1[k].z, v1[k].w};
-      unsigned gw[4] = {gq[k].x, gq[k].y, gq[k].z, gq[k].w};
-      unsigned ow[4];
-#pragma unroll
-      for (int j = 0; j < 8; j += 2) {
-        unsigned short h0, h1;
-        lars_step(wv[j], vv[j], (unsigned short)(gw[j >> 1] & 0xffffu), coef, lam, m, inv_s, h0);
-        lars_step(wv[j + 1], vv[j + 1], (unsigned short)(gw[j >> 1] >> 16), coef, lam, m, inv_s, h1);
-        ow[j >> 1] = (unsigned)h0 | ((unsigned)h1 << 16);
-      }
-#pragma unroll
-      for (int j = 0; j < 8; ++j) sw = fma((double)wv[j], (double)wv[j], sw);
-      store_stream_f4(w + i, wv[0], wv[1], wv[2], wv[3]);
-      store_stream_f4(w + i + 4, wv[4], wv[5], wv[6], wv[7]);
-      store_stream_f4(v + i, vv[0], vv[1], vv[2], vv[3]);
-      store_stream_f4(v + i + 4, vv[4], vv[5], vv[6], vv[7]);
-      store_stream_u4(w16 + i, ow[0], ow[1], ow[2], ow[3]);
+  __syncthreads();
+  if ((int)threadIdx.x < tb.T) {
+    const int t = threadIdx.x;
+    double sw = 0.0, sg = 0.0;
+    for (int c = tb.chunk_begin[t]; c < tb.chunk_begin[t + 1]; ++c) {
+      double cw;
+      if (have_w) cw = chunk_sumsq_w(tb.psum_w, c);
+      else cw = ((pw[c][0] + pw[c][1]) + pw[c][2]) + pw[c][3];
+      sw += cw;
+      sg += ((pg[c][0] + pg[c][1]) + pg[c][2]) + pg[c][3];
     }
+    coef[t] = lars_rate(tb.flags[t], sw, sg, lr, eta, loss_scale);
+    if (sum_overflowed(sg)) overflow = 1;
   }
-  {
-    int64_t nh = b0 - s, nt = e - b1;
-    int64_t k = threadIdx.x;
-    if (k < nh + nt) {
-      int64_t i = (k < nh) ? s + k : b1 + (k - nh);
-      float wi = w[i], vi = v[i];
-      unsigned short h;
-      lars_step(wi, vi, g16[i], coef, lam, m, inv_s, h);
-      w[i] = wi;
-      v[i] = vi;
-      w16[i] = h;
-      sw = fma((double)wi, (double)wi, sw);
-    }
+  __syncthreads();
+  const int f = overflow;
+  if (threadIdx.x == 0) {
+    *found_inf = f;
+    tb.state[0] = 1;
+    if (dyn.st) loss_scale_step(dyn, f);  // every thread has read the scale
   }
-  sw = wave_sum(sw);
-  if ((threadIdx.x & 63) == 0) tb.psum_w[c * LARS_WAVES + (threadIdx.x >> 6)] = sw;
+  if (f) return;
+  for (int c = group; c < tb.n_chunks; c += 1024 / LARS_THREADS) {
+    const ChunkRec rec = tb.chunk_rec[c];
+    const float lam = (tb.flags[rec.tensor] & JZ_PARAM_WEIGHT_DECAY) ? wd : 0.0f;
+    const double sw = wave_sum(update_chunk(rec, tid, w, v, g16, w16, coef[rec.tensor], lam, m, inv_s));
+    if ((tid & 63) == 0) tb.psum_w[(size_t)c * LARS_WAVES + (tid >> 6)] = sw;
+  }
 }
 
 __global__ void loss_scale_init(jz_loss_scale_state* __restrict__ st, float scale) {
@@ -649,7 +732,6 @@ Tables make_tables(const Layout& L, void* ws, uint64_t sum) {
   tb.state = reinterpret_cast<int*>(b + L.off_state);
   tb.psum_w = reinterpret_cast<double*>(b + L.off_psum_w);
   tb.psum_g = reinterpret_cast<double*>(b + L.off_psum_g);
-  tb.pflag = reinterpret_cast<int*>(b + L.off_pflag);
   tb.coef = reinterpret_cast<float*>(b + L.off_coef);
   tb.tflag = reinterpret_cast<int*>(b + L.off_tflag);
   tb.gsum = reinterpret_cast<unsigned long long*>(b + L.off_gsum);
@@ -774,10 +856,19 @@ int lars_run(const jz_param_set* ps, const jz_lars_hparams* hp, const jz_loss_sc
                        state ? 1.0f : hp->loss_scale);
     return jz::launch_status();
   }
+  if (L.n_chunks <= LARS_SMALL_CHUNKS && L.T <= LARS_SMALL_T) {
+    hipLaunchKernelGGL(lars_small, dim3(1), dim3(1024), 0, st, tb, ps->master_w, ps->momentum, g16,
+                       static_cast<unsigned short*>(ps->weight16), hp->momentum, hp->weight_decay, state ? 1.0f : 1.0f / hp->loss_scale,
+                       found_inf_dev, dyn, hp->lr, hp->trust_coef, state ? 1.0f : hp->loss_scale);
+    return jz::launch_status();
+  }
   if (L.n_chunks > 0)
     hipLaunchKernelGGL(lars_reduce, dim3((unsigned)L.n_chunks), dim3(LARS_THREADS), 0, st, tb, ps->master_w, g16);
-  if (L.T > 0)
-    hipLaunchKernelGGL(lars_finalize, dim3((unsigned)L.T), dim3(LARS_THREADS), 0, st, tb, hp->lr, hp->trust_coef,
+  if (L.T > 0 && L.most_chunks <= 256 * LARS_FIN_BATCH)
+    hipLaunchKernelGGL(lars_finalize<256>, dim3((unsigned)L.T), dim3(256), 0, st, tb, hp->lr, hp->trust_coef,
+                       state ? 1.0f : hp->loss_scale, scale_dev);
+  else if (L.T > 0)
+    hipLaunchKernelGGL(lars_finalize<1024>, dim3((unsigned)L.T), dim3(1024), 0, st, tb, hp->lr, hp->trust_coef,
                        state ? 1.0f : hp->loss_scale, scale_dev);
   // at least one workgroup so that the flag is always written
   hipLaunchKernelGGL(lars_update<false>, dim3((unsigned)(L.n_chunks > 0 ? L.n_chunks : 1)), dim3(LARS_THREADS), 0, st, tb,
