@@ -4,20 +4,27 @@
 //
 //   D[m][n] = sum_k A(m,k) * B(n,k), every product and sum in FP32 on v_mfma_f32_32x32x2_f32.
 //
-// One kernel family, built for the 157 TFLOP/s matrix peak of FP32 (a sixteenth of the FP16 one), where the operand
-// traffic per flop is small: a workgroup of 4 wavefronts (2 x 2) owns a BM x BN output tile, walks the reduction in
+// Channel counts that are multiples of 4 run on the LDS-direct kernel of jz_f32_dma.h (strided multi-tap backward-data as one
+// unit-stride launch per residue of the stride, strided 1x1 backward-data with a scattering epilogue); other counts run on
+// it through copies with the channels rounded up to 4, where that adds at most half to the work (3-channel stems).
+//
+// What is left (a filter smaller than its stride in backward-data; 1 or 2 channels) runs on igemm_f32_kernel below: a workgroup of 4 wavefronts (2 x 2) owns a BM x BN output tile, walks the reduction in
 // tiles of 16, and stages operands global -> registers -> LDS, double buffered.  Both tiles sit in LDS as
 // [k][row] (row contiguous), so an MFMA operand (lane l: row l % 32, k l / 32) is one conflict-free 4-byte read per
 // lane.  Operands that are contiguous along the reduction in memory (x / dy gathered per pixel, the forward filter) are
 // fetched as 4 consecutive k of one row and written to LDS as 4 scalars; operands contiguous along their own row index
 // (the filter in backward-data, dy and x in backward-weight) as 4 consecutive rows of one k, one 16-byte write.  With
-// channel counts that are not multiples of 4 the same kernel fetches element by element (VEC = false).
-//
-// Addressing is the plain index definition of each operation, bounds-checked per fetched vector; a strided
-// backward-data runs over every input pixel and finds the structural zeros by the divisibility test (no compact
-// form as in the FP16 path).  Split reductions (backward-weight) leave FP32 partial sums in the workspace, added in
+// channel counts that are not multiples of 4 the same kernel fetches element by element (VEC = false).  Addressing is the
+// plain index definition of each operation, bounds-checked per fetched vector.  Split reductions (backward-weight) leave FP32 partial sums in the workspace, added in
 // index order by splitk_reduce_f32: deterministic.
 #include <hip/hip_runtime.h>
+
+#include <math.h>
+
+#include <algorithm>
+#include <atomic>
+#include <type_traits>
+#include <vector>
 
 #include "jz_igemm.h"
 #include "jz_internal.h"
@@ -38,7 +45,18 @@ struct F32Args {
   int M, N, Kred;
   int nkt, kt_per_split, splits, tiles_m, tiles_n;
   ConvGeom g;
+  // the LDS-direct kernel's: descriptor bounds, tile decomposition, where tap (r, s) of the launch sits among the w_taps taps
+  // of a filter (backward-data), and the scatter of strided backward-data as in GemmArgs
+  unsigned bytesA, bytesB;
+  FastDiv d_tiles_mn, d_tiles_n;
+  int w_taps, w_tap0, w_tap_r, w_tap_s;
+  int bw_same;    // backward-weight, unit stride, output grid = input grid: x is read at a constant pixel distance per tap
+  int bw_linear;  // backward-weight of a 1x1 unit-stride unpadded layer: x is a plain [Kred][IC] matrix
+  int sc_on, sc_H, sc_W, sc_sh, sc_sw, sc_oh, sc_ow, sc_fill;
 };
+
+#include "jz_lds_dma.h"
+#include "jz_f32_dma.h"
 
 // Address of the gathered tensor's element for pixel `pix` of the (n, OH, OW) grid at filter tap `tap`, channel c, or
 // nullptr when the tap falls outside the image (or, backward-data, when no output pixel reads the input pixel through it).
@@ -230,22 +248,200 @@ __global__ __launch_bounds__(F_THREADS) void igemm_f32_kernel(F32Args a) {
   }
 }
 
-// D[i] = sum_s part[s][i], splits added in index order
-__global__ __launch_bounds__(256) void splitk_reduce_f32(const float* __restrict__ part, float* __restrict__ out, long long MN, int splits) {
-  const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (i >= MN) return;
-  float s = 0.0f;
-  for (int k = 0; k < splits; ++k) s += part[(size_t)k * MN + i];
-  out[i] = s;
+// D[i] = sum_s part[s][i].  A workgroup owns 256 / G groups of four consecutive outputs and G = 2^lg lanes per group: lane g
+// adds splits g, g + G, ... in that order, four loads in flight, then the lane sums are added in lane order (deterministic:
+// the order depends on splits and G only).  One thread per output that walked through all splits one load at a time took
+// 11 us per launch of the ResNet-50 step.
+__global__ __launch_bounds__(256) void splitk_reduce_f32(const float* __restrict__ part, float* __restrict__ out, long long MN, int splits, int lg) {
+  __shared__ float4 red[256];
+  const int G = 1 << lg, Q = 256 >> lg;
+  const int q = threadIdx.x & (Q - 1), lane = threadIdx.x >> (8 - lg);
+  const long long i = ((long long)blockIdx.x * Q + q) * 4;
+  const bool full = i + 3 < MN && (MN & 3) == 0;  // every split's slab starts on a 16-byte boundary
+  float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (full) {
+    int k = lane;
+    for (; k + 3 * G < splits; k += 4 * G) {
+      float4 t[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) t[u] = *reinterpret_cast<const float4*>(part + (size_t)(k + u * G) * MN + i);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) { s.x += t[u].x; s.y += t[u].y; s.z += t[u].z; s.w += t[u].w; }
+    }
+    for (; k < splits; k += G) {
+      const float4 t = *reinterpret_cast<const float4*>(part + (size_t)k * MN + i);
+      s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w;
+    }
+  } else if (i < MN) {
+    float v[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int k = lane; k < splits; k += G)
+      for (int e = 0; e < 4 && i + e < MN; ++e) v[e] += part[(size_t)k * MN + i + e];
+    s = make_float4(v[0], v[1], v[2], v[3]);
+  }
+  if (G > 1) {
+    red[threadIdx.x] = s;
+    __syncthreads();
+    if (lane != 0) return;
+    for (int l = 1; l < G; ++l) {
+      const float4 t = red[l * Q + q];
+      s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w;
+    }
+  }
+  if (full) {
+    *reinterpret_cast<float4*>(out + i) = s;
+  } else {
+    const float v[4] = {s.x, s.y, s.z, s.w};
+    for (int e = 0; e < 4 && i + e < MN; ++e) out[i + e] = v[e];
+  }
+}
+
+// Channel counts that are not multiples of 4: rows of C floats copied to rows of C4 (zeros behind), `real` of the rows
+// present in the source; two tensors per launch (blockIdx.y), one 16-byte chunk per thread and pass.  And the way back.
+struct WidenF32 {
+  const float* src[2];
+  float* dst[2];
+  long long chunks[2], real_rows[2];
+  int C[2];
+  FastDiv d_cpr[2];
+};
+__global__ __launch_bounds__(256) void widen_channels_f32(WidenF32 a) {
+  const int t = blockIdx.y, C = a.C[t];
+  for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < a.chunks[t]; i += (long long)gridDim.x * 256) {
+    const unsigned row = fd_div((unsigned)i, a.d_cpr[t]);
+    const int c0 = (int)((unsigned)i - row * a.d_cpr[t].d) * 4;
+    float v[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = row < a.real_rows[t] && c0 + e < C ? a.src[t][(size_t)row * C + c0 + e] : 0.f;
+    *reinterpret_cast<float4*>(a.dst[t] + i * 4) = make_float4(v[0], v[1], v[2], v[3]);
+  }
+}
+__global__ __launch_bounds__(256) void narrow_channels_f32(const float* __restrict__ src, float* __restrict__ dst, long long n, FastDiv d_c, int C4) {
+  for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < n; i += (long long)gridDim.x * 256) {
+    const unsigned row = fd_div((unsigned)i, d_c);
+    dst[i] = src[(size_t)row * C4 + ((unsigned)i - row * d_c.d)];
+  }
 }
 
 struct PlanF32 {
   int op = 0;
   bool vec = false;
-  int tile = 128;
+  bool dma = false;      // the LDS-direct kernel
+  bool gen = false;      // ... with per-lane tap arithmetic
+  bool classes = false;  // strided multi-tap backward-data: one launch per residue of the stride (class_args_f32)
+  bool widen = false;    // channels rounded up to 4 on copies: `wide` is the layer that runs
+  int BM = 128, BN = 128;
   F32Args args{};
   size_t ws_bytes = 0, bytesA = 0, bytesB = 0, bytesD = 0;
+  jz_conv_desc wide{};
+  size_t wide_a = 0, wide_b = 0, wide_d = 0;  // bytes of the copies (0: that operand is used where it is)
+  size_t plain_ws_bytes = 0;                  // what the same layer needs without them
 };
+
+size_t up256f(size_t x) { return (x + 255) & ~size_t(255); }
+
+void finish_geometry_f32(ConvGeom& g) {
+  g.tap_rep = 0;
+  if (g.R * g.S <= 32)
+    for (int r = 0; r < g.R; ++r) g.tap_rep |= 1u << (r * g.S);
+  g.row_pitch = g.IW * g.IC; g.pix_step = g.IC; g.s_step = g.IC;
+  g.d_ohow = make_fastdiv((unsigned)(g.OH * g.OW));
+  g.d_ow = make_fastdiv((unsigned)g.OW);
+  g.d_ic = make_fastdiv((unsigned)g.IC);
+  g.d_s = make_fastdiv((unsigned)g.S);
+  g.d_sh = make_fastdiv((unsigned)g.sh);
+  g.d_sw = make_fastdiv((unsigned)g.sw);
+}
+
+// whether the gathered operand needs the kernel's per-lane tap arithmetic: a k tile must lie inside one tap, the masks hold 32
+// taps, and descriptor plus padding margin must stay below the out-of-range mark
+bool needs_gen_f32(const PlanF32& pl) {
+  const ConvGeom& g = pl.args.g;
+  if (pl.op == JZ_BWD_WEIGHT) return false;
+  const long long margin = 4ll * g.IC * ((long long)(pl.op == JZ_FWD ? g.ph : g.R - 1) * g.IW + (pl.op == JZ_FWD ? g.pw : g.S - 1));
+  return g.IC % FD_BK != 0 || g.R * g.S > 32 || (long long)pl.bytesA + margin >= 0xfffffff0ll;
+}
+
+// Tile and split of the LDS-direct kernel.  The vector ALU bounds it, so a launch takes (workgroups a compute unit gets) x (k
+// tiles) x (time of a k tile), but not less than one workgroup alone takes per tile, when nothing covers its waits; plus
+// prologues and epilogues, plus, when the reduction is split, writing and re-reading the partial sums and a second launch.
+// The times are microseconds measured on ResNet-50 layers at batch 64 with each tile forced; the gathered x of
+// backward-weight costs vector instructions of its own.
+void choose_tiling_f32(PlanF32* pl, bool may_split, bool fixed_tile = false) {
+  struct Tile { int bm, bn; double us, alone, us_bw, alone_bw; };
+  static const Tile tiles[] = {{128, 128, 0.98, 1.05, 1.25, 1.40}, {128, 64, 0.49, 0.60, 0.55, 0.75}, {64, 128, 0.48, 0.60, 0.57, 0.80},
+                               {64, 64, 0.23, 0.36, 0.29, 0.48}};
+  F32Args& a = pl->args;
+  a.nkt = (a.Kred + FD_BK - 1) / FD_BK;
+  const bool gather = pl->op == JZ_BWD_WEIGHT && !a.bw_linear;
+  double best = 1e30;
+  int bsp = 1;
+  for (const Tile& t : tiles) {
+    if (fixed_tile && (t.bm != pl->BM || t.bn != pl->BN)) continue;
+    const long long tm = (a.M + t.bm - 1) / t.bm, tn = (a.N + t.bn - 1) / t.bn;
+    for (int sp = 1; sp <= 512; sp = sp < 8 ? sp + 1 : sp + sp / 4) {
+      if (sp > 1 && (!may_split || a.nkt / sp < 8)) break;
+      const int kps = (a.nkt + sp - 1) / sp, real = (a.nkt + kps - 1) / kps;
+      const double w = (double)(tm * tn * real) / 256.0;
+      const double n = w <= 4.0 ? ceil(w) : w + 0.5;  // many small rounds even out
+      double per = n * (gather ? t.us_bw : t.us);
+      const double alone = gather ? t.alone_bw : t.alone;
+      if (per < alone) per = alone;
+      double us = 5.0 + kps * per + n;
+      if (real > 1) us += 4.0 + 2.0 * real * (double)a.M * a.N * 4.0 / 4.0e6;
+      if (us < best) { best = us; pl->BM = t.bm; pl->BN = t.bn; bsp = sp; }
+    }
+  }
+  a.tiles_m = (a.M + pl->BM - 1) / pl->BM;
+  a.tiles_n = (a.N + pl->BN - 1) / pl->BN;
+  a.kt_per_split = (a.nkt + bsp - 1) / bsp;
+  a.splits = (a.nkt + a.kt_per_split - 1) / a.kt_per_split;
+  a.d_tiles_mn = make_fastdiv((unsigned)(a.tiles_m * a.tiles_n));
+  a.d_tiles_n = make_fastdiv((unsigned)a.tiles_n);
+}
+
+// One residue (ca, cb) of the stride of a strided multi-tap backward-data layer: the input pixels h = ca + sh i, w = cb + sw l
+// meet the taps r = r0 + sh j, s = s0 + sw k only, at dy row i + (ca + ph) / sh - j: a unit-stride layer over those taps.
+// false: no such pixel.
+bool class_args_f32(const jz_conv_desc* d, const PlanF32& base, int ca, int cb, PlanF32* pl) {
+  const int sh = d->stride_h, sw = d->stride_w;
+  const int Ha = (d->H - ca + sh - 1) / sh, Wb = (d->W - cb + sw - 1) / sw;
+  if (Ha <= 0 || Wb <= 0) return false;
+  const int r0 = (ca + d->pad_h) % sh, s0 = (cb + d->pad_w) % sw;
+  *pl = base;
+  F32Args& a = pl->args;
+  ConvGeom& g = a.g;
+  g.R = (d->R - r0 + sh - 1) / sh; g.S = (d->S - s0 + sw - 1) / sw;
+  g.OH = Ha; g.OW = Wb; g.sh = g.sw = 1;
+  g.ph = (ca + d->pad_h) / sh; g.pw = (cb + d->pad_w) / sw;
+  finish_geometry_f32(g);
+  a.M = d->N * Ha * Wb; a.Kred = g.R * g.S * d->K;
+  a.w_tap0 = r0 * d->S + s0; a.w_tap_r = sh * d->S; a.w_tap_s = sw;
+  a.sc_on = 1; a.sc_H = d->H; a.sc_W = d->W; a.sc_sh = sh; a.sc_sw = sw; a.sc_oh = ca; a.sc_ow = cb; a.sc_fill = 0;
+  choose_tiling_f32(pl, false, true);  // one tile for all residues: the layer's
+  return true;
+}
+
+int make_plan_f32(int op, const jz_conv_desc* d, PlanF32* pl);
+
+// Channels rounded up to 4 on copies, when that adds at most half to the multiply-adds.
+void plan_widened_f32(int op, const jz_conv_desc* d, PlanF32* pl) {
+  jz_conv_desc w = *d;
+  w.C = (d->C + 3) & ~3;
+  if (op != JZ_FWD) w.K = (d->K + 3) & ~3;  // forward takes any number of output channels
+  if ((w.C == d->C && w.K == d->K) || (double)w.C * w.K > 1.5 * d->C * d->K) return;
+  PlanF32 in;
+  if (make_plan_f32(op, &w, &in) != JZ_OK || !in.dma) return;
+  const bool x_wide = w.C != d->C, y_wide = w.K != d->K;
+  const size_t nx = up256f((size_t)d->N * d->H * d->W * w.C * 4), nw = up256f((size_t)w.K * d->R * d->S * w.C * 4);
+  const size_t ny = op == JZ_FWD ? 0 : up256f(pl->bytesA / d->K * w.K);
+  if (op == JZ_FWD) { pl->wide_a = x_wide ? nx : 0; pl->wide_b = nw; }
+  else if (op == JZ_BWD_DATA) { pl->wide_a = y_wide ? ny : 0; pl->wide_b = nw; pl->wide_d = x_wide ? nx : 0; }
+  else { pl->wide_a = y_wide ? ny : 0; pl->wide_b = x_wide ? nx : 0; pl->wide_d = nw; }
+  pl->widen = true;
+  pl->wide = w;
+  const size_t need = pl->wide_a + pl->wide_b + pl->wide_d + in.ws_bytes;
+  if (need > pl->ws_bytes) pl->ws_bytes = need;
+}
 
 int out_dim(int in, int pad, int f, int st) { return (in + 2 * pad - f) / st + 1; }
 
@@ -284,42 +480,115 @@ int make_plan_f32(int op, const jz_conv_desc* d, PlanF32* pl) {
     pl->vec = d->K % 4 == 0 && d->C % 4 == 0;
     pl->bytesA = 4 * ny; pl->bytesB = 4 * nx; pl->bytesD = 4 * nw;  // A = dy, B = x
   }
-  g.row_pitch = g.IW * g.IC; g.pix_step = g.IC; g.s_step = g.IC;
-  g.d_ohow = make_fastdiv((unsigned)(g.OH * g.OW));
-  g.d_ow = make_fastdiv((unsigned)g.OW);
-  g.d_ic = make_fastdiv((unsigned)g.IC);
-  g.d_s = make_fastdiv((unsigned)g.S);
-  g.d_sh = make_fastdiv((unsigned)g.sh);
-  g.d_sw = make_fastdiv((unsigned)g.sw);
+  const bool strided = d->stride_h > 1 || d->stride_w > 1;
+  a.bytesA = (unsigned)pl->bytesA;
+  a.bytesB = (unsigned)pl->bytesB;
+  a.w_taps = d->R * d->S; a.w_tap0 = 0; a.w_tap_r = d->S; a.w_tap_s = 1;
+  a.sc_on = 0; a.sc_H = a.sc_W = 0; a.sc_sh = a.sc_sw = 1; a.sc_oh = a.sc_ow = 0; a.sc_fill = 0;
+  const bool single_tap = d->R == 1 && d->S == 1;
+  pl->dma = pl->vec && (op != JZ_BWD_DATA || !strided || single_tap || (d->R >= d->stride_h && d->S >= d->stride_w));
+  pl->classes = pl->dma && op == JZ_BWD_DATA && strided && !single_tap;
+  if (pl->dma && op == JZ_BWD_DATA && strided && single_tap) {
+    // only the input pixels (p sh, q sw) receive gradient: the GEMM runs over the output pixels, its epilogue scatters
+    a.M = d->N * P * Q;
+    g.OH = P; g.OW = Q; g.sh = g.sw = 1;
+    a.sc_on = 1; a.sc_H = d->H; a.sc_W = d->W; a.sc_sh = d->stride_h; a.sc_sw = d->stride_w; a.sc_fill = 1;
+  }
+  finish_geometry_f32(g);
+  a.bw_same = op == JZ_BWD_WEIGHT && !single_tap && !strided && P == d->H && Q == d->W &&
+              (long long)pl->bytesB + 4ll * d->C * ((long long)d->pad_h * d->W + d->pad_w) < 0xfffffff0ll;
+  a.bw_linear = op == JZ_BWD_WEIGHT && single_tap && !strided && d->pad_h == 0 && d->pad_w == 0;
+  if (pl->dma) {
+    pl->gen = needs_gen_f32(*pl);
+    if (pl->classes) {  // every input pixel meets one residue's taps only
+      const int all = a.Kred;
+      a.Kred = all / (d->stride_h * d->stride_w) + 1;
+      choose_tiling_f32(pl, false);
+      a.Kred = all;
+      a.splits = 1;
+    } else {
+      choose_tiling_f32(pl, !a.sc_on);
+    }
+    pl->ws_bytes = a.splits > 1 ? (size_t)a.splits * a.M * a.N * sizeof(float) : 0;
+    pl->plain_ws_bytes = pl->ws_bytes;
+    return JZ_OK;
+  }
   // Tile and split: 128 x 128 tiles where they give the chip (256 compute units, two workgroups each) enough
   // workgroups, else 64 x 64; then split the reduction until about 512 workgroups exist, never shorter than 8 k tiles.
   a.nkt = (a.Kred + F_BK - 1) / F_BK;
   auto tiles = [&](int t) { return (long long)((a.M + t - 1) / t) * ((a.N + t - 1) / t); };
-  pl->tile = tiles(128) >= 384 ? 128 : 64;
-  a.tiles_m = (a.M + pl->tile - 1) / pl->tile;
-  a.tiles_n = (a.N + pl->tile - 1) / pl->tile;
-  long long want = 512 / tiles(pl->tile);
+  pl->BM = pl->BN = tiles(128) >= 384 ? 128 : 64;
+  a.tiles_m = (a.M + pl->BM - 1) / pl->BM;
+  a.tiles_n = (a.N + pl->BM - 1) / pl->BM;
+  long long want = 512 / tiles(pl->BM);
   if (want > a.nkt / 8) want = a.nkt / 8;
   if (want > 256) want = 256;
   if (want < 1) want = 1;
   a.kt_per_split = (int)((a.nkt + want - 1) / want);
   a.splits = (a.nkt + a.kt_per_split - 1) / a.kt_per_split;
   pl->ws_bytes = a.splits > 1 ? (size_t)a.splits * a.M * a.N * sizeof(float) : 0;
+  pl->plain_ws_bytes = pl->ws_bytes;
+  plan_widened_f32(op, d, pl);
   return JZ_OK;
 }
 
-template <int OP>
-void launch_f32(const PlanF32& pl, hipStream_t st) {
-  const F32Args& a = pl.args;
-  const dim3 grid((unsigned)a.tiles_m * (unsigned)a.tiles_n * (unsigned)a.splits), block(F_THREADS);
-  if (pl.tile == 128) {
-    if (pl.vec) hipLaunchKernelGGL((igemm_f32_kernel<OP, true, 128, 128>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((igemm_f32_kernel<OP, false, 128, 128>), grid, block, 0, st, a);
-  } else {
-    if (pl.vec) hipLaunchKernelGGL((igemm_f32_kernel<OP, true, 64, 64>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((igemm_f32_kernel<OP, false, 64, 64>), grid, block, 0, st, a);
+template <int OP, int BM, int BN, bool GEN>
+int launch_f32_dma(const F32Args& a, hipStream_t st) {
+  constexpr size_t smem = (size_t)FD_NST * (BM + BN) * FD_BK * 4;
+  static std::atomic<bool> attr_set{false};  // per instantiation; setting it twice is harmless
+  if (!attr_set.load(std::memory_order_relaxed)) {
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(&f32_dma_kernel<OP, BM, BN, GEN>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)smem) != hipSuccess)
+      return JZ_ERR_LAUNCH;
+    attr_set.store(true, std::memory_order_relaxed);
   }
+  hipLaunchKernelGGL((f32_dma_kernel<OP, BM, BN, GEN>), dim3((unsigned)a.tiles_m * (unsigned)a.tiles_n * (unsigned)a.splits), dim3(256), smem, st, a);
+  return jz::launch_status();
 }
+
+template <int BM, int BN, bool GEN>
+int launch_f32_set(const F32Set& set, hipStream_t st) {
+  constexpr size_t smem = (size_t)FD_NST * (BM + BN) * FD_BK * 4;
+  static std::atomic<bool> attr_set{false};
+  if (!attr_set.load(std::memory_order_relaxed)) {
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(&f32_dma_set_kernel<BM, BN, GEN>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)smem) != hipSuccess)
+      return JZ_ERR_LAUNCH;
+    attr_set.store(true, std::memory_order_relaxed);
+  }
+  hipLaunchKernelGGL((f32_dma_set_kernel<BM, BN, GEN>), dim3(set.first[FD_MAX_SET]), dim3(256), smem, st, set);
+  return jz::launch_status();
+}
+
+template <int OP>
+int launch_f32(const PlanF32& pl, hipStream_t st) {
+  const F32Args& a = pl.args;
+  if (pl.dma) {
+    if constexpr (OP != OP_BWD_WEIGHT)
+      if (pl.gen) {
+        if (pl.BM == 128 && pl.BN == 128) return launch_f32_dma<OP, 128, 128, true>(a, st);
+        if (pl.BM == 128) return launch_f32_dma<OP, 128, 64, true>(a, st);
+        if (pl.BN == 128) return launch_f32_dma<OP, 64, 128, true>(a, st);
+        return launch_f32_dma<OP, 64, 64, true>(a, st);
+      }
+    if (pl.BM == 128 && pl.BN == 128) return launch_f32_dma<OP, 128, 128, false>(a, st);
+    if (pl.BM == 128) return launch_f32_dma<OP, 128, 64, false>(a, st);
+    if (pl.BN == 128) return launch_f32_dma<OP, 64, 128, false>(a, st);
+    return launch_f32_dma<OP, 64, 64, false>(a, st);
+  }
+  const dim3 grid((unsigned)a.tiles_m * (unsigned)a.tiles_n * (unsigned)a.splits), block(F_THREADS);
+  if constexpr (OP == OP_BWD_DATA)
+    if (pl.vec) {  // a filter smaller than its stride
+      if (pl.BM == 128) hipLaunchKernelGGL((igemm_f32_kernel<OP, true, 128, 128>), grid, block, 0, st, a);
+      else hipLaunchKernelGGL((igemm_f32_kernel<OP, true, 64, 64>), grid, block, 0, st, a);
+      return jz::launch_status();
+    }
+  if (pl.BM == 128) hipLaunchKernelGGL((igemm_f32_kernel<OP, false, 128, 128>), grid, block, 0, st, a);
+  else hipLaunchKernelGGL((igemm_f32_kernel<OP, false, 64, 64>), grid, block, 0, st, a);
+  return jz::launch_status();
+}
+
+int run_widened_f32(int op, const jz_conv_desc* d, const PlanF32& pl, const void* A, const void* B, void* D, void* ws, size_t ws_bytes, void* stream);
 
 // A, B in the kernel's order: FWD (x, w), BWD_DATA (dy, w), BWD_WEIGHT (dy, x)
 int run_f32(int op, const jz_conv_desc* d, const void* A, const void* B, void* D, void* ws, size_t ws_bytes, void* stream) {
@@ -329,26 +598,107 @@ int run_f32(int op, const jz_conv_desc* d, const void* A, const void* B, void* D
   if (!A || !B || !D) return JZ_ERR_NULL;
   if (!aligned16(A) || !aligned16(B) || !aligned16(D) || (ws && !aligned16(ws))) return JZ_ERR_ALIGN;
   if (overlaps(D, pl.bytesD, A, pl.bytesA) || overlaps(D, pl.bytesD, B, pl.bytesB)) return JZ_ERR_ALIAS;
+  if (pl.widen && (!ws || ws_bytes < pl.ws_bytes)) {  // no room for the copies
+    pl.widen = false;
+    pl.ws_bytes = pl.plain_ws_bytes;
+  }
   if (pl.ws_bytes > 0 && (!ws || ws_bytes < pl.ws_bytes)) return JZ_ERR_WORKSPACE;
   if (pl.ws_bytes > 0 && (overlaps(ws, pl.ws_bytes, A, pl.bytesA) || overlaps(ws, pl.ws_bytes, B, pl.bytesB) ||
                           overlaps(ws, pl.ws_bytes, D, pl.bytesD)))
     return JZ_ERR_ALIAS;
+  if (pl.widen) return run_widened_f32(op, d, pl, A, B, D, ws, ws_bytes, stream);
   hipStream_t st = static_cast<hipStream_t>(stream);
   F32Args& a = pl.args;
   a.A = static_cast<const float*>(A);
   a.B = static_cast<const float*>(B);
   a.D = static_cast<float*>(D);
   a.Dpart = static_cast<float*>(ws);
-  if (op == JZ_FWD) launch_f32<OP_FWD>(pl, st);
-  else if (op == JZ_BWD_DATA) launch_f32<OP_BWD_DATA>(pl, st);
-  else launch_f32<OP_BWD_WEIGHT>(pl, st);
-  if ((rc = jz::launch_status()) != JZ_OK) return rc;
+  if (pl.classes) {
+    // residues in launches of at most FD_MAX_SET, those with the most taps (the last ones to start would end last) first
+    std::vector<PlanF32> cps;
+    for (int ca = 0; ca < d->stride_h; ++ca)
+      for (int cb = 0; cb < d->stride_w; ++cb) {
+        PlanF32 cp;
+        if (class_args_f32(d, pl, ca, cb, &cp)) cps.push_back(cp);
+      }
+    std::stable_sort(cps.begin(), cps.end(), [](const PlanF32& x, const PlanF32& y) { return x.args.Kred > y.args.Kred; });
+    for (size_t i = 0; i < cps.size() && rc == JZ_OK; i += FD_MAX_SET) {
+      F32Set set{};
+      for (int k = 0; k < FD_MAX_SET; ++k) {
+        const size_t at = i + k < cps.size() ? i + k : cps.size() - 1;
+        set.c[k] = cps[at].args;
+        set.first[k + 1] = set.first[k] + (i + k < cps.size() ? (unsigned)(set.c[k].tiles_m * set.c[k].tiles_n) : 0u);
+      }
+      const int v = (pl.gen ? 4 : 0) + (pl.BM == 128 ? 2 : 0) + (pl.BN == 128 ? 1 : 0);
+      rc = v == 0 ? launch_f32_set<64, 64, false>(set, st) : v == 1 ? launch_f32_set<64, 128, false>(set, st)
+         : v == 2 ? launch_f32_set<128, 64, false>(set, st) : v == 3 ? launch_f32_set<128, 128, false>(set, st)
+         : v == 4 ? launch_f32_set<64, 64, true>(set, st) : v == 5 ? launch_f32_set<64, 128, true>(set, st)
+         : v == 6 ? launch_f32_set<128, 64, true>(set, st) : launch_f32_set<128, 128, true>(set, st);
+    }
+    return rc;
+  }
+  if (op == JZ_FWD) rc = launch_f32<OP_FWD>(pl, st);
+  else if (op == JZ_BWD_DATA) rc = launch_f32<OP_BWD_DATA>(pl, st);
+  else rc = launch_f32<OP_BWD_WEIGHT>(pl, st);
+  if (rc != JZ_OK) return rc;
   if (a.splits > 1) {
-    const long long MN = (long long)a.M * a.N;
-    hipLaunchKernelGGL(splitk_reduce_f32, dim3((unsigned)((MN + 255) / 256)), dim3(256), 0, st, (const float*)a.Dpart, a.D, MN, a.splits);
+    const long long MN = (long long)a.M * a.N, groups = (MN + 3) / 4;
+    int lg = 0;  // lanes per output group: enough workgroups to cover the chip first, then shorten each thread's chain
+    while (lg < 5 && (2 << lg) <= a.splits && (groups + (256 >> lg) - 1) / (256 >> lg) < 1024) ++lg;
+    hipLaunchKernelGGL(splitk_reduce_f32, dim3((unsigned)((groups + (256 >> lg) - 1) / (256 >> lg))), dim3(256), 0, st,
+                       (const float*)a.Dpart, a.D, MN, a.splits, lg);
     rc = jz::launch_status();
   }
   return rc;
+}
+
+int run_widened_f32(int op, const jz_conv_desc* d, const PlanF32& pl, const void* A, const void* B, void* D, void* ws, size_t ws_bytes,
+                    void* stream) {
+  const jz_conv_desc& w = pl.wide;
+  const long long RS = (long long)d->R * d->S, npix = (long long)d->N * d->H * d->W;
+  const long long nout = (long long)d->N * out_dim(d->H, d->pad_h, d->R, d->stride_h) * out_dim(d->W, d->pad_w, d->S, d->stride_w);
+  char* const base = static_cast<char*>(ws);
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  WidenF32 wa{};
+  int nt = 0;
+  long long most = 0;
+  auto copy = [&](const void* src, char* dst, long long rows, long long real_rows, int c, int c4) {
+    wa.src[nt] = static_cast<const float*>(src);
+    wa.dst[nt] = reinterpret_cast<float*>(dst);
+    wa.chunks[nt] = rows * (c4 / 4);
+    wa.real_rows[nt] = real_rows;
+    wa.C[nt] = c;
+    wa.d_cpr[nt] = make_fastdiv((unsigned)(c4 / 4));
+    if (wa.chunks[nt] > most) most = wa.chunks[nt];
+    ++nt;
+  };
+  const void* a2 = A;
+  const void* b2 = B;
+  if (pl.wide_a) {
+    a2 = base;
+    if (op == JZ_FWD) copy(A, base, npix, npix, d->C, w.C);
+    else copy(A, base, nout, nout, d->K, w.K);
+  }
+  if (pl.wide_b) {
+    b2 = base + pl.wide_a;
+    if (op == JZ_BWD_WEIGHT) copy(B, base + pl.wide_a, npix, npix, d->C, w.C);
+    else copy(B, base + pl.wide_a, w.K * RS, d->K * RS, d->C, w.C);
+  }
+  int rc = JZ_OK;
+  if (nt > 0) {
+    const long long blocks = (most + 255) / 256;
+    hipLaunchKernelGGL(widen_channels_f32, dim3((unsigned)(blocks < 8192 ? blocks : 8192), (unsigned)nt), dim3(256), 0, st, wa);
+    if ((rc = jz::launch_status()) != JZ_OK) return rc;
+  }
+  const size_t used = pl.wide_a + pl.wide_b + pl.wide_d;
+  void* const d2 = pl.wide_d ? base + pl.wide_a + pl.wide_b : D;
+  rc = run_f32(op, &w, a2, b2, d2, ws_bytes > used ? base + used : nullptr, ws_bytes - used, stream);
+  if (rc != JZ_OK || !pl.wide_d) return rc;
+  const long long n = op == JZ_BWD_DATA ? npix * d->C : (long long)d->K * RS * d->C;
+  const long long blocks = (n + 255) / 256;
+  hipLaunchKernelGGL(narrow_channels_f32, dim3((unsigned)(blocks < 8192 ? blocks : 8192)), dim3(256), 0, st, static_cast<const float*>(d2),
+                     static_cast<float*>(D), n, make_fastdiv((unsigned)d->C), w.C);
+  return jz::launch_status();
 }
 
 int fc_desc_f32(int mode, int batch, int in_features, int out_features, jz_conv_desc* d) {

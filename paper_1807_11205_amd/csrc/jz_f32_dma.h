@@ -1,0 +1,470 @@
+// FP32 implicit GEMM with LDS-direct loads for channel counts that are multiples of 4 (included by jz_conv_f32.hip inside its
+// anonymous namespace; the table in jz_igemm.h says what A, B, m, n, k are in each operation).
+//
+// What bounds it: the vector ALU.  The FP32 MFMAs run on it (their 157 TFLOP/s are the packed FP32 rate), so unlike beside FP16
+// MFMAs every other vector instruction of the loop takes matrix time: a first version with plain per-load tap arithmetic,
+// 60-80 vector instructions per k tile, stood at 115-126 TFLOP/s on a large GEMM.  Hence:
+//   * operands go from memory to LDS directly, requested NST tiles ahead, one barrier per tile;
+//   * a load's address is a per-lane offset that never changes plus a scalar offset (tap, channel block): one
+//     v_bfe_i32 + one v_or per gathered load (bit mask of the row's invalid taps, an out-of-range offset delivers zeros),
+//     none for the others (the last tile of a backward-weight reduction, whose rows can lie beyond the tensors, is the one
+//     that compares: scalar offsets take no part in the descriptor's range check);
+//   * the loop is unrolled over the ring's stages, so that LDS addresses are a register plus a constant.
+// GEN = true keeps per-lane tap arithmetic, for channel counts that are not multiples of the k tile (the reduction then runs
+// over the flattened (tap, channel) index) and more than 32 taps.
+// The MFMA is the 16x16x4 form: in a loop of nothing else it reaches 152-154 TFLOP/s whatever the occupancy, the 32x32x2
+// form 141 with one wavefront per SIMD, 151 with two and 124 with four.
+//
+// Reduction order inside a tile.  An MFMA multiplies four k, lanes 16 q .. 16 q + 15 hold the q-th.  Which four does not
+// matter as long as both operands agree, so step j of a tile takes k = 4 q + j: a lane's four steps are then four
+// consecutive k, one ds_read_b128 of a k-contiguous operand ("KC": rows of 16 floats in LDS, 16-byte chunk c of row r at
+// position c ^ ((r >> 2) & 3), conflict-free for the writes and the reads).  An operand that is contiguous along its own
+// m / n index ("MC") sits in LDS as [k][rows] and is read one float per lane and step; chunk c of k-row k is at position
+// c ^ 4 ((k >> 2) & 3), so that the four 64-byte pieces a read takes from rows j, 4 + j, 8 + j, 12 + j lie in different banks.
+#pragma once
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+template <int OFF>
+__device__ __forceinline__ f32x4 lds_read_f4(unsigned addr) {
+  f32x4 v = {};
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(OFF));
+#endif
+  return v;
+}
+template <int OFF>
+__device__ __forceinline__ float lds_read_f1(unsigned addr) {
+  float v = 0.f;
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("ds_read_b32 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(OFF));
+#endif
+  return v;
+}
+
+// the k lowest bits, k in [0, 32]
+__device__ __forceinline__ unsigned low_taps(int k) { return k >= 32 ? 0xffffffffu : (1u << k) - 1u; }
+__device__ __forceinline__ int clamp_taps(int x, int hi) { return x < 0 ? 0 : (x > hi ? hi : x); }
+
+constexpr int FD_BK = 16;   // floats per k tile: a KC row is 64 bytes
+constexpr int FD_NST = 4;   // ring stages
+
+// the workgroup with number `block` of the `blocks` that the launch `a` consists of
+template <int OP, int BM, int BN, bool GEN>
+__device__ __forceinline__ void f32_dma_body(const F32Args& a, unsigned block, unsigned blocks) {
+  static_assert(!GEN || OP != OP_BWD_WEIGHT, "backward-weight has one form");
+  constexpr bool A_KC = OP != OP_BWD_WEIGHT, B_KC = OP == OP_FWD;
+  constexpr int TM = BM / 32, TN = BN / 32;   // 16x16 MFMA tiles per wavefront (2 x 2 wavefronts)
+  constexpr int RB = FD_BK * 4;               // bytes per row of a KC tile
+  constexpr int A_BYTES = BM * RB, B_BYTES = BN * RB, STAGE = A_BYTES + B_BYTES;
+  constexpr int LA = A_BYTES / 4096, LB = B_BYTES / 4096, LPT = LA + LB;  // LDS-direct loads per thread and tile
+  static_assert(LA >= 1 && LB >= 1, "tile too small for 256 loaders");
+  extern __shared__ __align__(16) float lds_f[];
+  lds_byte* const ldsb = (lds_byte*)lds_f;
+  const unsigned lds_base = (unsigned)(uintptr_t)JZ_LDS_PTR(lds_f);
+  const ConvGeom& g = a.g;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+
+  unsigned L = xcd_remap(block, blocks);
+  const unsigned tiles_mn = (unsigned)(a.tiles_m * a.tiles_n);
+  const int split = (int)fd_div(L, a.d_tiles_mn);
+  L -= (unsigned)split * tiles_mn;
+  const unsigned trow = fd_div(L, a.d_tiles_n);
+  const int m0 = (int)trow * BM, n0 = (int)(L - trow * (unsigned)a.tiles_n) * BN;
+  const int kt_begin = split * a.kt_per_split;
+  const int kt_end = kt_begin + a.kt_per_split < a.nkt ? kt_begin + a.kt_per_split : a.nkt;
+  const int nk = kt_end - kt_begin;
+
+  constexpr unsigned OOB = 0xffffffffu;
+  // in-range taps of a gathered row can start before the tensor (padding): the descriptor's base is moved down by that much
+  unsigned biasA = 0;
+  if (!GEN && OP == OP_FWD) biasA = (unsigned)(g.ph * g.row_pitch + g.pw * g.IC) * 4u;
+  if (!GEN && OP == OP_BWD_DATA) biasA = (unsigned)((g.R - 1) * g.row_pitch + (g.S - 1) * g.IC) * 4u;
+  const __amdgpu_buffer_rsrc_t rsrcA =
+      __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)a.A - biasA), 0, (int)(a.bytesA + biasA), 0x00020000);
+  // backward-weight of a layer whose output grid is its input grid (bw_same): pixel j at a tap is pixel j + constant of x, so the
+  // offset is linear in j as for a plain matrix and only the image borders need the pixel's coordinates
+  const unsigned biasB = OP == OP_BWD_WEIGHT && a.bw_same ? (unsigned)(g.ph * g.row_pitch + g.pw * g.IC) * 4u : 0u;
+  const __amdgpu_buffer_rsrc_t rsrcB =
+      __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)a.B - biasB), 0, (int)(a.bytesB + biasB), 0x00020000);
+
+  // ---- loader geometry: one load of a wavefront fills 1 KB ----------------------------------------
+  // KC: 16 rows x 4 chunks; load ii of wavefront w covers rows (4 ii + w) 16 + lane / 4.  The swizzle is the same for every ii.
+  const int kc_row = wave * 16 + lane / 4;
+  const int kc_chunk = (lane & 3) ^ ((kc_row >> 2) & 3);
+  // MC with ROWS mn: ROWS / 4 chunks per k-row
+  auto mc_k = [&](int rows, int ii) { return ((4 * ii + wave) * 64 + lane) / (rows / 4); };
+  auto mc_col = [&](int rows, int ii) { return ((lane % (rows / 4)) ^ (4 * ((mc_k(rows, ii) >> 2) & 3))) * 4; };
+
+  // ---- per-lane loader state ------------------------------------------------------------------------
+  // vA / vB: the part of a load's byte offset that does not change over the k loop (OOB: the row or column does not exist);
+  // invA: bit t set when filter tap t reads outside the image for this row (all bits for rows beyond M)
+  unsigned vA[LA], invA[LA], vB[LB];
+  int gh[LA], gw[LA];  // GEN: source coordinates of tap (0, 0)
+  (void)invA; (void)gh; (void)gw;
+  if constexpr (A_KC) {
+    const unsigned full = low_taps(g.S);
+#pragma unroll
+    for (int ii = 0; ii < LA; ++ii) {
+      const int m = m0 + 64 * ii + kc_row;
+      gh[ii] = -(1 << 28); gw[ii] = 0; vA[ii] = 0; invA[ii] = OOB;
+      if (m < a.M) {
+        const unsigned n = fd_div((unsigned)m, g.d_ohow);
+        const unsigned rem = (unsigned)m - n * (unsigned)(g.OH * g.OW);
+        const int oh = (int)fd_div(rem, g.d_ow), ow = (int)rem - oh * g.OW;
+        const int h0 = OP == OP_FWD ? oh * g.sh - g.ph : oh + g.ph, w0 = OP == OP_FWD ? ow * g.sw - g.pw : ow + g.pw;
+        gh[ii] = h0; gw[ii] = w0;
+        vA[ii] = (unsigned)(((int)n * g.IH + h0) * g.IW + w0) * (unsigned)g.IC;
+        if constexpr (!GEN) {
+          vA[ii] = (vA[ii] + (unsigned)kc_chunk * 4u) * 4u + (OP == OP_FWD ? biasA : 0u);
+          // along one axis the taps outside are a run at the start and a run at the end of the filter (backward-data: the
+          // other way round); the column mask is copied into every filter row's slot by one multiplication
+          const int lo_w = OP == OP_FWD ? -w0 : w0 - g.IW + 1, hi_w = OP == OP_FWD ? g.IW - w0 : w0 + 1;
+          const int lo_h = OP == OP_FWD ? -h0 : h0 - g.IH + 1, hi_h = OP == OP_FWD ? g.IH - h0 : h0 + 1;
+          const unsigned cm = low_taps(clamp_taps(lo_w, g.S)) | (full & ~low_taps(clamp_taps(hi_w, g.S)));
+          invA[ii] = cm * g.tap_rep | low_taps(clamp_taps(lo_h, g.R) * g.S) |
+                     (low_taps(g.R * g.S) & ~low_taps(clamp_taps(hi_h, g.R) * g.S));
+        }
+      }
+    }
+  } else {
+#pragma unroll
+    for (int ii = 0; ii < LA; ++ii) {
+      const int mm = m0 + mc_col(BM, ii);
+      vA[ii] = mm < a.M ? (unsigned)(mc_k(BM, ii) * a.M + mm) * 4u : OOB;
+    }
+  }
+  // backward-weight, gathered x: the filter tap of the lane's columns, and per load the row, the column and the byte offset
+  // of its pixel, advanced by 16 pixels per tile with one carry per digit
+  int bw_r[LB], bw_s[LB], xp[LB], xq[LB], bw_tp = 0, bw_tq = 0;
+  unsigned xoff[LB], bw_dv = 0, bw_k1 = 0, bw_k2 = 0;
+  (void)bw_r; (void)bw_s; (void)xp; (void)xq; (void)xoff; (void)bw_tp; (void)bw_tq; (void)bw_dv; (void)bw_k1; (void)bw_k2;
+  if constexpr (OP == OP_FWD) {
+#pragma unroll
+    for (int ii = 0; ii < LB; ++ii) {
+      const int nn = n0 + 64 * ii + kc_row;
+      vB[ii] = nn < a.N ? (unsigned)(nn * a.Kred + kc_chunk * 4) * 4u : OOB;
+    }
+  } else if constexpr (OP == OP_BWD_DATA) {
+#pragma unroll
+    for (int ii = 0; ii < LB; ++ii) {
+      const int nn = n0 + mc_col(BN, ii);
+      vB[ii] = nn < a.N ? (unsigned)nn * 4u + (GEN ? 0u : (unsigned)(mc_k(BN, ii) * a.w_taps) * (unsigned)a.N * 4u) : OOB;
+    }
+  } else {
+    const unsigned Pn = (unsigned)(g.IH * g.row_pitch) * 4u, Ph = (unsigned)(g.sh * g.row_pitch) * 4u, Pw = (unsigned)(g.sw * g.IC) * 4u;
+    const unsigned ta = fd_div((unsigned)FD_BK, g.d_ohow), trem = (unsigned)FD_BK - ta * (unsigned)(g.OH * g.OW);
+    bw_tp = (int)fd_div(trem, g.d_ow);
+    bw_tq = (int)trem - bw_tp * g.OW;
+    bw_dv = ta * Pn + (unsigned)bw_tp * Ph + (unsigned)bw_tq * Pw;
+    bw_k1 = Ph - (unsigned)g.OW * Pw;
+    bw_k2 = Pn - (unsigned)g.OH * Ph;
+#pragma unroll
+    for (int ii = 0; ii < LB; ++ii) {
+      const int nn = n0 + mc_col(BN, ii);
+      bw_r[ii] = -(1 << 28); bw_s[ii] = 0;
+      vB[ii] = nn < a.N ? (unsigned)(mc_k(BN, ii) * g.IC + nn) * 4u : OOB;  // 1x1, unit stride, unpadded: a plain matrix
+      int ch = 0;
+      if (nn < a.N) {
+        const unsigned tap = fd_div((unsigned)nn, g.d_ic), r = fd_div(tap, g.d_s);
+        ch = nn - (int)tap * g.IC;
+        bw_r[ii] = (int)r - g.ph;
+        bw_s[ii] = (int)(tap - r * (unsigned)g.S) - g.pw;
+      }
+      const unsigned j = (unsigned)(kt_begin * FD_BK + mc_k(BN, ii));
+      const unsigned n = fd_div(j, g.d_ohow), rem = j - n * (unsigned)(g.OH * g.OW);
+      const unsigned pp = fd_div(rem, g.d_ow);
+      xp[ii] = (int)pp;
+      xq[ii] = (int)(rem - pp * (unsigned)g.OW);
+      if (a.bw_same) {
+        // xp, xq: the source row and column (wrapping at the grid's size plus the tap's shift)
+        if (nn < a.N)
+          vB[ii] = (unsigned)((mc_k(BN, ii) + bw_r[ii] * g.IW + bw_s[ii]) * g.IC + ch) * 4u + biasB;
+        xp[ii] += bw_r[ii];
+        xq[ii] += bw_s[ii];
+      }
+      xoff[ii] = ((n * (unsigned)g.IH + pp * (unsigned)g.sh + (unsigned)bw_r[ii]) * (unsigned)g.row_pitch +
+                  ((unsigned)(xq[ii] * g.sw) + (unsigned)bw_s[ii]) * (unsigned)g.IC + (unsigned)ch) * 4u;
+    }
+  }
+
+  struct TileCtx {
+    unsigned k0;
+    unsigned tap, soffA, soffB;  // the same for the whole wavefront (the tile lies inside one tap)
+    int r, s;                    // GEN, per lane: the tap of the lane's chunk (negated for backward-data) ...
+    unsigned loff;               // ... the element offset it adds ...
+    bool in;                     // ... and whether the chunk lies inside the reduction
+    bool tail;                   // backward-weight, wave-uniform: some rows of the tile lie beyond the reduction
+  };
+  auto tile_ctx = [&](int kt) {
+    TileCtx c{};
+    c.k0 = (unsigned)(kt * FD_BK);
+    if constexpr (OP == OP_BWD_WEIGHT) {
+      c.soffA = c.k0 * (unsigned)a.M * 4u;
+      c.soffB = c.k0 * (unsigned)g.IC * 4u;
+      c.tail = c.k0 + FD_BK > (unsigned)a.Kred;
+    } else if constexpr (!GEN) {
+      c.tap = fd_div(c.k0, g.d_ic);
+      const unsigned ch = c.k0 - c.tap * (unsigned)g.IC;
+      const unsigned r = fd_div(c.tap, g.d_s), s = c.tap - r * (unsigned)g.S;
+      if constexpr (OP == OP_FWD) {
+        c.soffA = (r * (unsigned)g.row_pitch + s * (unsigned)g.IC + ch) * 4u;
+        c.soffB = c.k0 * 4u;
+      } else {
+        c.soffA = (((unsigned)g.R - 1u - r) * (unsigned)g.row_pitch + ((unsigned)g.S - 1u - s) * (unsigned)g.IC + ch) * 4u;
+        c.soffB = (ch * (unsigned)a.w_taps + (unsigned)a.w_tap0 + r * (unsigned)a.w_tap_r + s * (unsigned)a.w_tap_s) * (unsigned)a.N * 4u;
+      }
+    } else {
+      const unsigned kq = c.k0 + (unsigned)kc_chunk * 4u;
+      const unsigned tap = fd_div(kq, g.d_ic), ch = kq - tap * (unsigned)g.IC;
+      const int r = (int)fd_div(tap, g.d_s), s = (int)tap - r * g.S;
+      c.r = OP == OP_FWD ? r : -r;
+      c.s = OP == OP_FWD ? s : -s;
+      c.loff = (unsigned)((c.r * g.IW + c.s) * g.IC) + ch;
+      c.in = kq < (unsigned)a.Kred;
+      c.soffB = c.k0 * 4u;
+    }
+    return c;
+  };
+  auto issue_load = [&](const TileCtx& c, int st, auto l_tag) {
+    constexpr int Lx = decltype(l_tag)::value;
+    lds_byte* const dst = ldsb + st * STAGE + (Lx < LA ? 0 : A_BYTES) + (4 * (Lx < LA ? Lx : Lx - LA) + wave) * 1024;
+    if constexpr (Lx < LA) {
+      constexpr int ii = Lx;
+      if constexpr (A_KC && GEN) {
+        const bool ok = c.in && (unsigned)(gh[ii] + c.r) < (unsigned)g.IH && (unsigned)(gw[ii] + c.s) < (unsigned)g.IW;
+        jz_dma16(rsrcA, dst, ok ? (vA[ii] + c.loff) * 4u : OOB);
+      } else if constexpr (A_KC) {
+        const unsigned bad = (unsigned)__builtin_amdgcn_sbfe(invA[ii], c.tap, 1);  // 0 / -1
+        jz_dma16s(rsrcA, dst, vA[ii] | bad, c.soffA);
+      } else if (c.tail) {
+        jz_dma16s(rsrcA, dst, c.k0 + (unsigned)mc_k(BM, ii) < (unsigned)a.Kred ? vA[ii] : OOB, c.soffA);
+      } else {
+        jz_dma16s(rsrcA, dst, vA[ii], c.soffA);
+      }
+    } else {
+      constexpr int ii = Lx - LA;
+      if constexpr (OP == OP_FWD && GEN) {
+        jz_dma16s(rsrcB, dst, c.in ? vB[ii] : OOB, c.soffB);
+      } else if constexpr (OP == OP_BWD_DATA && GEN) {
+        // row k is filter w[ko][tap][.]; a strided layer's launch covers the taps of one residue of the stride
+        const unsigned kk = c.k0 + (unsigned)mc_k(BN, ii);
+        const unsigned tap = fd_div(kk, g.d_ic), ko = kk - tap * (unsigned)g.IC;
+        const unsigned r = fd_div(tap, g.d_s), s = tap - r * (unsigned)g.S;
+        const unsigned row = ko * (unsigned)a.w_taps + (unsigned)a.w_tap0 + r * (unsigned)a.w_tap_r + s * (unsigned)a.w_tap_s;
+        jz_dma16(rsrcB, dst, kk < (unsigned)a.Kred && vB[ii] != OOB ? vB[ii] + row * (unsigned)a.N * 4u : OOB);
+      } else if constexpr (OP != OP_BWD_WEIGHT) {
+        jz_dma16s(rsrcB, dst, vB[ii], c.soffB);
+      } else if (a.bw_linear) {
+        if (c.tail) jz_dma16s(rsrcB, dst, c.k0 + (unsigned)mc_k(BN, ii) < (unsigned)a.Kred ? vB[ii] : OOB, c.soffB);
+        else jz_dma16s(rsrcB, dst, vB[ii], c.soffB);
+      } else if (a.bw_same) {
+        bool ok = (unsigned)xp[ii] < (unsigned)g.IH && (unsigned)xq[ii] < (unsigned)g.IW;
+        if (c.tail) ok = ok && c.k0 + (unsigned)mc_k(BN, ii) < (unsigned)a.Kred;
+        jz_dma16s(rsrcB, dst, ok ? vB[ii] : OOB, c.soffB);
+        xq[ii] += bw_tq;
+        const bool c1 = xq[ii] >= g.OW + bw_s[ii];
+        xq[ii] -= c1 ? g.OW : 0;
+        xp[ii] += bw_tp + (c1 ? 1 : 0);
+        xp[ii] -= xp[ii] >= g.OH + bw_r[ii] ? g.OH : 0;
+      } else {
+        const int ih = __mul24(xp[ii], g.sh) + bw_r[ii], iw = __mul24(xq[ii], g.sw) + bw_s[ii];
+        bool ok = (unsigned)ih < (unsigned)g.IH && (unsigned)iw < (unsigned)g.IW;
+        if (c.tail) ok = ok && c.k0 + (unsigned)mc_k(BN, ii) < (unsigned)a.Kred;
+        jz_dma16(rsrcB, dst, ok ? xoff[ii] : OOB);
+        xq[ii] += bw_tq;
+        const bool c1 = xq[ii] >= g.OW;
+        xq[ii] -= c1 ? g.OW : 0;
+        xp[ii] += bw_tp + (c1 ? 1 : 0);
+        const bool c2 = xp[ii] >= g.OH;
+        xp[ii] -= c2 ? g.OH : 0;
+        xoff[ii] += bw_dv + (c1 ? bw_k1 : 0u) + (c2 ? bw_k2 : 0u);
+      }
+    }
+  };
+
+#pragma unroll
+  for (int s = 0; s < FD_NST; ++s)
+    if (s < nk) {
+      const TileCtx c = tile_ctx(kt_begin + s);
+      static_for<0, LPT>([&](auto l) { issue_load(c, s, l); });
+    }
+  sched_fence();
+
+  // ---- MFMA operand addresses -----------------------------------------------------------------------
+  const int r15 = lane & 15, q4l = lane >> 4;
+  // KC: row base + r15, chunk q at its swizzled place; 16-row sub-tiles are 16 RB bytes apart and share the swizzle.
+  // MC: k-row 4 q + j, column base + r15: the swizzle moves whole groups of four chunks (16 columns), i.e. sub-tile t of a
+  // wavefront sits where sub-tile t ^ q would: one address per sub-tile.
+  unsigned adA[A_KC ? 1 : TM], adB[B_KC ? 1 : TN];
+  if constexpr (A_KC) {
+    adA[0] = lds_base + (unsigned)((wm * (BM / 2) + r15) * RB + ((q4l ^ ((r15 >> 2) & 3)) * 16));
+  } else {
+#pragma unroll
+    for (int t = 0; t < TM; ++t) adA[t] = lds_base + (unsigned)((4 * q4l * BM + (((wm * (BM / 2)) / 16 + t) ^ q4l) * 16 + r15) * 4);
+  }
+  if constexpr (B_KC) {
+    adB[0] = lds_base + (unsigned)(A_BYTES + (wn * (BN / 2) + r15) * RB + ((q4l ^ ((r15 >> 2) & 3)) * 16));
+  } else {
+#pragma unroll
+    for (int t = 0; t < TN; ++t) adB[t] = lds_base + (unsigned)(A_BYTES + (4 * q4l * BN + (((wn * (BN / 2)) / 16 + t) ^ q4l) * 16 + r15) * 4);
+  }
+
+  f32x4 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.0f;
+
+  f32x4 fa0[TM], fb0[TN], fa1[TM], fb1[TN];  // operands of one tile each
+  auto read_tile = [&](auto st_tag, f32x4 (&va)[TM], f32x4 (&vb)[TN]) {
+    constexpr int SO = decltype(st_tag)::value * STAGE;  // fits the instruction's 16-bit offset
+    static_assert(FD_NST * STAGE <= 65536, "stage offsets are immediates");
+    static_for<0, TM>([&](auto t_tag) {
+      constexpr int T = decltype(t_tag)::value;
+      if constexpr (A_KC) {
+        va[T] = lds_read_f4<SO + 16 * T * RB>(adA[0]);
+      } else {
+        static_for<0, 4>([&](auto j_tag) {
+          constexpr int J = decltype(j_tag)::value;
+          va[T][J] = lds_read_f1<SO + J * BM * 4>(adA[A_KC ? 0 : T]);
+        });
+      }
+    });
+    static_for<0, TN>([&](auto t_tag) {
+      constexpr int T = decltype(t_tag)::value;
+      if constexpr (B_KC) {
+        vb[T] = lds_read_f4<SO + 16 * T * RB>(adB[0]);
+      } else {
+        static_for<0, 4>([&](auto j_tag) {
+          constexpr int J = decltype(j_tag)::value;
+          vb[T][J] = lds_read_f1<SO + J * BN * 4>(adB[B_KC ? 0 : T]);
+        });
+      }
+    });
+  };
+  auto wait_tiles = [&](int younger) {  // until at most `younger` later tiles are in flight
+    if (younger >= 2) wait_vmcnt<2 * LPT>();
+    else if (younger == 1) wait_vmcnt<LPT>();
+    else wait_vmcnt<0>();
+  };
+
+  // One iteration multiplies tile i, whose operands were requested from LDS during tile i - 1.  Once they have arrived, tile
+  // i + 1 has landed and every wavefront is at the barrier, stage i % NST is free: the next tile's operands are requested
+  // from LDS and tile i + NST from memory between the MFMAs.
+  static_assert(FD_NST == 4, "wait_tiles counts two younger tiles");
+  auto iteration = [&](int i, auto st_tag, f32x4 (&va)[TM], f32x4 (&vb)[TN], f32x4 (&na)[TM], f32x4 (&nb)[TN]) {
+    constexpr int ST = decltype(st_tag)::value;  // i % NST
+    const bool more = i + FD_NST < nk;
+    const TileCtx c = tile_ctx(kt_begin + i + FD_NST);  // unused when there is no such tile
+    lds_wait<0>();
+#pragma unroll
+    for (int t = 0; t < TM; ++t) lds_pin(va[t]);
+#pragma unroll
+    for (int t = 0; t < TN; ++t) lds_pin(vb[t]);
+    if (i + 1 < nk) {
+      wait_tiles(nk - 2 - i);
+      __builtin_amdgcn_s_barrier();
+      read_tile(std::integral_constant<int, (ST + 1) % FD_NST>{}, na, nb);
+    }
+    sched_fence();
+    static_for<0, 4>([&](auto j_tag) {
+      constexpr int J = decltype(j_tag)::value;
+#pragma unroll
+      for (int x = 0; x < TM; ++x)
+#pragma unroll
+        for (int y = 0; y < TN; ++y)
+          // n operand in the first slot: each lane then owns 4 consecutive n for one m (row = lane % 16)
+          acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x4f32(vb[y][J], va[x][J], acc[x][y], 0, 0, 0);
+      if (more)
+        static_for<0, LPT>([&](auto l_tag) {
+          if constexpr (decltype(l_tag)::value * 4 / LPT == J) issue_load(c, ST, l_tag);
+        });
+      sched_fence();
+    });
+  };
+  if (nk > 0) {
+    if (nk >= 4) wait_vmcnt<3 * LPT>();
+    else wait_tiles(nk - 1);
+    __builtin_amdgcn_s_barrier();
+    read_tile(std::integral_constant<int, 0>{}, fa0, fb0);
+  }
+  for (int i = 0; i < nk; i += FD_NST) {
+    iteration(i, std::integral_constant<int, 0>{}, fa0, fb0, fa1, fb1);
+    if (i + 1 < nk) iteration(i + 1, std::integral_constant<int, 1>{}, fa1, fb1, fa0, fb0);
+    if (i + 2 < nk) iteration(i + 2, std::integral_constant<int, 2>{}, fa0, fb0, fa1, fb1);
+    if (i + 3 < nk) iteration(i + 3, std::integral_constant<int, 3>{}, fa1, fb1, fa0, fb0);
+  }
+  __syncthreads();  // the epilogue stages the tile in the ring
+
+  // accumulator register r of tile (x,y): m = wrow + 16 x + lane % 16, n = wcol + 16 y + 4 (lane / 16) + r.
+  // Half of the tile's rows at a time (those of one wm) go through LDS, so that a store instruction writes whole row pieces.
+  float* const out = a.splits > 1 ? a.Dpart + (size_t)split * a.M * a.N : a.D;
+  const bool scatter = a.sc_on && a.splits == 1;
+  constexpr int LDF = BN + 4, RH = BM / 2, FCH = BN / 4, RPP = 256 / FCH;
+  static_assert(RH * LDF * 4 <= FD_NST * STAGE, "the staged half tile has to fit the ring");
+  const bool vec = (a.N & 3) == 0;
+  const int fch = tid % FCH, frow = tid / FCH;
+#pragma unroll
+  for (int ps = 0; ps < 2; ++ps) {
+    if (ps > 0) __syncthreads();
+    if (wm == ps) {
+#pragma unroll
+      for (int x = 0; x < TM; ++x)
+#pragma unroll
+        for (int y = 0; y < TN; ++y)
+          *reinterpret_cast<float4*>(lds_f + (16 * x + r15) * LDF + wn * (BN / 2) + 16 * y + 4 * q4l) =
+              make_float4(acc[x][y][0], acc[x][y][1], acc[x][y][2], acc[x][y][3]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < RH / RPP; ++i) {
+      const int row = frow + RPP * i, m = m0 + ps * RH + row, n = n0 + fch * 4;
+      if (m >= a.M || n >= a.N) continue;
+      size_t drow = (size_t)m;
+      if (scatter) {  // row m = (n, p, q) of the strided grid goes to input pixel (n, p sh + oh, q sw + ow)
+        const unsigned img = fd_div((unsigned)m, g.d_ohow);
+        const unsigned rem = (unsigned)m - img * (unsigned)(g.OH * g.OW);
+        const unsigned p = fd_div(rem, g.d_ow), q = rem - p * (unsigned)g.OW;
+        drow = ((size_t)img * a.sc_H + p * a.sc_sh + a.sc_oh) * a.sc_W + q * a.sc_sw + a.sc_ow;
+        // strided single tap: no output pixel reads the other pixels of this cell, their gradient is zero
+        for (int i2 = 0; a.sc_fill && i2 < a.sc_sh; ++i2)
+          for (int j2 = 0; j2 < a.sc_sw; ++j2) {
+            if ((i2 | j2) == 0 || (int)(p * a.sc_sh) + i2 >= a.sc_H || (int)(q * a.sc_sw) + j2 >= a.sc_W) continue;
+            *reinterpret_cast<float4*>(out + (drow + (size_t)i2 * a.sc_W + j2) * a.N + n) = make_float4(0.f, 0.f, 0.f, 0.f);
+          }
+      }
+      const float4 v = *reinterpret_cast<const float4*>(lds_f + row * LDF + fch * 4);
+      float* dst = out + drow * a.N + n;
+      if (vec) {
+        *reinterpret_cast<float4*>(dst) = v;
+      } else {
+        const float e[4] = {v.x, v.y, v.z, v.w};
+        for (int k = 0; k < 4 && n + k < a.N; ++k) dst[k] = e[k];
+      }
+    }
+  }
+}
+
+template <int OP, int BM, int BN, bool GEN>
+__global__ __launch_bounds__(256) void f32_dma_kernel(F32Args a) {
+  f32_dma_body<OP, BM, BN, GEN>(a, blockIdx.x, gridDim.x);
+}
+
+// Several launches in one: the residues of the stride of a strided backward-data layer, each of which alone fills a part of
+// the chip (ResNet-50 v1.5 at batch 20, 3x3 512 -> 512 on 14x14: 128 workgroups each).
+constexpr int FD_MAX_SET = 4;
+struct F32Set {
+  F32Args c[FD_MAX_SET];
+  unsigned first[FD_MAX_SET + 1];  // workgroup numbers of member k: first[k] .. first[k + 1] - 1
+};
+template <int BM, int BN, bool GEN>
+__global__ __launch_bounds__(256) void f32_dma_set_kernel(F32Set s) {
+  int k = 0;
+  while (k + 1 < FD_MAX_SET && blockIdx.x >= s.first[k + 1]) ++k;
+  f32_dma_body<OP_BWD_DATA, BM, BN, GEN>(s.c[k], blockIdx.x - s.first[k], s.first[k + 1] - s.first[k]);
+}

@@ -13,19 +13,13 @@ typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
+#include "jz_lds_dma.h"
+
 constexpr int THREADS = 256;
 constexpr int BK = 64;
 constexpr int LDK = BK + 8;  // LDS row pitch in halves
 constexpr int KCH = BK / 8;  // 16-byte chunks per tile row
 constexpr int LOADERS = 128; // threads per operand
-
-__device__ __forceinline__ unsigned xcd_remap(unsigned bid, unsigned nb) {
-  // consecutive workgroup ids land on different XCDs (each with its own L2); give every XCD one
-  // contiguous run of tiles instead so that neighbouring tiles share their operand rows in L2
-  const unsigned X = 8;
-  unsigned q = nb / X, rem = nb % X, xcd = bid % X, local = bid / X;
-  return xcd * q + (xcd < rem ? xcd : rem) + local;
-}
 
 // ---------------------------------------------------------------------------------------------
 // element-wise (generic) operand access: the plain index definitions, every bound checked
