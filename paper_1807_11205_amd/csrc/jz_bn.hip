@@ -24,6 +24,8 @@ namespace {
 constexpr int BN_THREADS = 256;
 constexpr int BN_MAX_C = 2048;       // C / 8 lanes of a row have to fit one workgroup
 constexpr int BN_TARGET_SLABS = 512;   // two per compute unit
+constexpr int BN_MERGE_SLABS = 64;     // most partial sums per channel that an apply pass adds up itself (ResNet-50 at batch 64: 64 is
+                                       // even with none, 128 costs 1 %, 512 costs 4 %; small steps have fewer anyway)
 constexpr int BN_FIN_C = 8;            // channels a finalize workgroup handles (32 contiguous bytes of every slab's sums);
                                        // its 256 / 8 = 32 lanes per channel share the slabs
 
@@ -261,6 +263,21 @@ __device__ __forceinline__ bool bn_slab_totals(const float* __restrict__ part, i
   return true;
 }
 
+// mean and 1 / sqrt(var + eps) of one channel (written where the pointers are not null) and y = a x + b
+__device__ __forceinline__ void bn_fwd_coef(double s, double q, double inv_rows, float eps, float gamma, float beta, float* save_mean,
+                                            float* save_invstd, float* coef, int pitch) {
+  const double m = s * inv_rows;
+  double var = q * inv_rows - m * m;
+  if (var < 0.0) var = 0.0;
+  const double is = 1.0 / sqrt(var + (double)eps);
+  const float mf = (float)m, isf = (float)is;
+  if (save_mean) *save_mean = mf;
+  if (save_invstd) *save_invstd = isf;
+  const float a = gamma * isf;
+  coef[0] = a;
+  coef[pitch] = beta - mf * a;
+}
+
 __global__ __launch_bounds__(BN_THREADS) void bn_fwd_final(const float* __restrict__ part, int slabs, int C, double inv_rows,
                                                           float eps, const float* __restrict__ gamma,
                                                           const float* __restrict__ beta, float* __restrict__ save_mean,
@@ -268,16 +285,7 @@ __global__ __launch_bounds__(BN_THREADS) void bn_fwd_final(const float* __restri
   const int c = blockIdx.x * BN_FIN_C + threadIdx.x % BN_FIN_C;
   double s, q;
   if (!bn_slab_totals(part, slabs, C, c, s, q)) return;
-  const double m = s * inv_rows;
-  double var = q * inv_rows - m * m;
-  if (var < 0.0) var = 0.0;
-  const double is = 1.0 / sqrt(var + (double)eps);
-  const float mf = (float)m, isf = (float)is;
-  save_mean[c] = mf;
-  save_invstd[c] = isf;
-  const float a = gamma[c] * isf;
-  coef[c] = a;
-  coef[C + c] = beta[c] - mf * a;
+  bn_fwd_coef(s, q, inv_rows, eps, gamma[c], beta[c], save_mean + c, save_invstd + c, coef + c, C);
 }
 
 // RES: a residual tensor is added in front of the ReLU (the end of a bottleneck block)
@@ -307,6 +315,20 @@ __global__ __launch_bounds__(BN_THREADS) void bn_apply(const uint4* __restrict__
   }
 }
 
+// the parameter gradients of one channel (written where the pointers are not null) and its dx = a (g - dbeta/M - x^ dgamma/M),
+// x^ = (x - mean) invstd, as a g + P x + Q
+__device__ __forceinline__ void bn_bwd_coef(double sb, double sg, double inv_rows, float gamma, float mean, float invstd,
+                                            unsigned short* dgamma16, unsigned short* dbeta16, float* coef, int pitch) {
+  _Float16 hg = (_Float16)(float)sg, hb = (_Float16)(float)sb;
+  if (dgamma16) __builtin_memcpy(dgamma16, &hg, 2);
+  if (dbeta16) __builtin_memcpy(dbeta16, &hb, 2);
+  const double a = (double)gamma * (double)invstd;
+  const double t = a * (sg * inv_rows) * (double)invstd;
+  coef[0] = (float)a;
+  coef[pitch] = (float)(-t);
+  coef[2 * pitch] = (float)(t * (double)mean - a * (sb * inv_rows));
+}
+
 __global__ __launch_bounds__(BN_THREADS) void bn_bwd_final(const float* __restrict__ part, int slabs, int C, double inv_rows,
                                                           const float* __restrict__ gamma, const float* __restrict__ mean,
                                                           const float* __restrict__ invstd, unsigned short* __restrict__ dgamma16,
@@ -314,18 +336,7 @@ __global__ __launch_bounds__(BN_THREADS) void bn_bwd_final(const float* __restri
   const int c = blockIdx.x * BN_FIN_C + threadIdx.x % BN_FIN_C;
   double sb, sg;
   if (!bn_slab_totals(part, slabs, C, c, sb, sg)) return;
-  _Float16 hg = (_Float16)(float)sg, hb = (_Float16)(float)sb;
-  unsigned short ug, ub;
-  __builtin_memcpy(&ug, &hg, 2);
-  __builtin_memcpy(&ub, &hb, 2);
-  dgamma16[c] = ug;
-  dbeta16[c] = ub;
-  // dx = a (g - dbeta/M - x^ dgamma/M) with x^ = (x - mean) invstd, as dx = a g + P x + Q
-  const double a = (double)gamma[c] * (double)invstd[c];
-  const double t = a * (sg * inv_rows) * (double)invstd[c];
-  coef[c] = (float)a;
-  coef[C + c] = (float)(-t);
-  coef[2 * C + c] = (float)(t * (double)mean[c] - a * (sb * inv_rows));
+  bn_bwd_coef(sb, sg, inv_rows, gamma[c], mean[c], invstd[c], dgamma16 + c, dbeta16 + c, coef + c, C);
 }
 
 __device__ __forceinline__ void load8(const float* p, float (&f)[8]) {
@@ -359,10 +370,230 @@ __global__ __launch_bounds__(BN_THREADS) void bn_bwd_apply(const uint4* __restri
   }
 }
 
+// ---- apply passes that finish the statistics themselves ----------------------------------------------------------------------
+// With few partial sums per channel (BN_MERGE_SLABS) the launch between the statistics and the apply pass does nothing but cost
+// its 4-5 us: here a workgroup owns 64 channels and a range of rows, adds up the partial sums of its channels (a few tens of KB
+// out of L2, while its first rows are on their way) and goes on.  The first workgroup of a channel range also writes what the
+// finalize kernel would.
+constexpr int BM_CH = 64;    // channels of a workgroup: one 128-byte line of every row
+constexpr int BM_ROWS = 32;  // rows one pass of a workgroup covers
+constexpr int BM_U = 4;      // passes whose loads are in flight together
+
+// the two sums of channel first + tid (tid < 64), FP64: four lanes per channel take every fourth slab, then added in lane order
+__device__ __forceinline__ bool bn_merged_totals(const float* __restrict__ part, int slabs, int C, int first, double& s, double& q) {
+  __shared__ double red[2][BN_THREADS];
+  const int c = first + (threadIdx.x & (BM_CH - 1)), j = threadIdx.x / BM_CH;
+  s = q = 0.0;
+  if (c < C)
+    for (int k = j; k < slabs; k += 32) {  // eight slabs' sums requested together, added in slab order
+      float a[8], b[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int ku = k + 4 * u < slabs ? k + 4 * u : k;
+        a[u] = part[((size_t)ku * 2) * C + c];
+        b[u] = part[((size_t)ku * 2 + 1) * C + c];
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (k + 4 * u < slabs) {
+          s += (double)a[u];
+          q += (double)b[u];
+        }
+    }
+  red[0][threadIdx.x] = s;
+  red[1][threadIdx.x] = q;
+  __syncthreads();
+  if (j != 0 || c >= C) return false;
+  for (int l = 1; l < 4; ++l) {
+    s += red[0][l * BM_CH + threadIdx.x];
+    q += red[1][l * BM_CH + threadIdx.x];
+  }
+  return true;
+}
+
+template <int RES>
+__global__ __launch_bounds__(BN_THREADS) void bn_apply_merged(const uint4* __restrict__ x, const uint4* __restrict__ res, uint4* __restrict__ y,
+                                                             int64_t rows, int rows_per_wg, int C, const float* __restrict__ part, int slabs,
+                                                             double inv_rows, float eps, int relu, const float* __restrict__ gamma,
+                                                             const float* __restrict__ beta, float* __restrict__ save_mean,
+                                                             float* __restrict__ save_invstd) {
+  __shared__ __align__(16) float coef[2][BM_CH];
+  const int cpr = C / 8, first = blockIdx.x * BM_CH;
+  const int chunk = blockIdx.x * (BM_CH / 8) + (threadIdx.x & 7), rsub = threadIdx.x / 8;
+  const bool live = chunk < cpr;
+  const int64_t r0 = (int64_t)blockIdx.y * rows_per_wg, r1 = r0 + rows_per_wg < rows ? r0 + rows_per_wg : rows;
+  uint4 q[BM_U], e[BM_U];
+  auto fetch = [&](int64_t r) {
+#pragma unroll
+    for (int u = 0; u < BM_U; ++u) {
+      const int64_t ru = r + u * BM_ROWS;
+      if (live && ru < r1) {
+        q[u] = x[(size_t)ru * cpr + chunk];
+        if (RES) e[u] = res[(size_t)ru * cpr + chunk];
+      }
+    }
+  };
+  fetch(r0 + rsub);
+  double s, sq;
+  if (bn_merged_totals(part, slabs, C, first, s, sq)) {
+    const int c = first + threadIdx.x;
+    const bool writer = blockIdx.y == 0;
+    bn_fwd_coef(s, sq, inv_rows, eps, gamma[c], beta[c], writer ? save_mean + c : nullptr, writer ? save_invstd + c : nullptr,
+                &coef[0][threadIdx.x], BM_CH);
+  }
+  __syncthreads();
+  float a[8], b[8];
+  load8(&coef[0][(threadIdx.x & 7) * 8], a);
+  load8(&coef[1][(threadIdx.x & 7) * 8], b);
+  for (int64_t r = r0 + rsub; r < r1; r += BM_U * BM_ROWS) {
+    uint4 o[BM_U];
+#pragma unroll
+    for (int u = 0; u < BM_U; ++u) {
+      float v[8], rv[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      unpack8(q[u], v);
+      if (RES) unpack8(e[u], rv);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        float z = v[k] * a[k] + b[k];
+        if (RES) z += rv[k];
+        v[k] = (relu && !(z > 0.f)) ? 0.f : z;
+      }
+      o[u] = pack8(v);
+    }
+    fetch(r + BM_U * BM_ROWS);
+#pragma unroll
+    for (int u = 0; u < BM_U; ++u) {
+      const int64_t ru = r + u * BM_ROWS;
+      if (live && ru < r1) y[(size_t)ru * cpr + chunk] = o[u];
+    }
+  }
+}
+
+__global__ __launch_bounds__(BN_THREADS) void bn_bwd_apply_merged(const uint4* __restrict__ x, const uint4* __restrict__ y,
+                                                                 const uint4* __restrict__ dy, uint4* __restrict__ dx, int64_t rows,
+                                                                 int rows_per_wg, int C, const float* __restrict__ part, int slabs,
+                                                                 double inv_rows, int relu, const float* __restrict__ gamma,
+                                                                 const float* __restrict__ mean, const float* __restrict__ invstd,
+                                                                 unsigned short* __restrict__ dgamma16, unsigned short* __restrict__ dbeta16) {
+  __shared__ __align__(16) float coef[3][BM_CH];
+  const int cpr = C / 8, first = blockIdx.x * BM_CH;
+  const int chunk = blockIdx.x * (BM_CH / 8) + (threadIdx.x & 7), rsub = threadIdx.x / 8;
+  const bool live = chunk < cpr;
+  const int64_t r0 = (int64_t)blockIdx.y * rows_per_wg, r1 = r0 + rows_per_wg < rows ? r0 + rows_per_wg : rows;
+  uint4 qx[BM_U], qd[BM_U], qy[BM_U];
+  auto fetch = [&](int64_t r) {
+#pragma unroll
+    for (int u = 0; u < BM_U; ++u) {
+      const int64_t ru = r + u * BM_ROWS;
+      if (live && ru < r1) {
+        const size_t i = (size_t)ru * cpr + chunk;
+        qx[u] = x[i];
+        qd[u] = dy[i];
+        if (relu) qy[u] = y[i];
+      }
+    }
+  };
+  fetch(r0 + rsub);
+  double sb, sg;
+  if (bn_merged_totals(part, slabs, C, first, sb, sg)) {
+    const int c = first + threadIdx.x;
+    const bool writer = blockIdx.y == 0;
+    bn_bwd_coef(sb, sg, inv_rows, gamma[c], mean[c], invstd[c], writer ? dgamma16 + c : nullptr, writer ? dbeta16 + c : nullptr,
+                &coef[0][threadIdx.x], BM_CH);
+  }
+  __syncthreads();
+  float a[8], pc[8], qc[8];
+  load8(&coef[0][(threadIdx.x & 7) * 8], a);
+  load8(&coef[1][(threadIdx.x & 7) * 8], pc);
+  load8(&coef[2][(threadIdx.x & 7) * 8], qc);
+  for (int64_t r = r0 + rsub; r < r1; r += BM_U * BM_ROWS) {
+    uint4 o[BM_U];
+#pragma unroll
+    for (int u = 0; u < BM_U; ++u) {
+      float xv[8], gv[8], out[8];
+      unpack8(qx[u], xv);
+      unpack8(qd[u], gv);
+      if (relu) {
+        float yv[8];
+        unpack8(qy[u], yv);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) gv[k] = yv[k] > 0.f ? gv[k] : 0.f;
+      }
+#pragma unroll
+      for (int k = 0; k < 8; ++k) out[k] = a[k] * gv[k] + (pc[k] * xv[k] + qc[k]);
+      o[u] = pack8(out);
+    }
+    fetch(r + BM_U * BM_ROWS);
+#pragma unroll
+    for (int u = 0; u < BM_U; ++u) {
+      const int64_t ru = r + u * BM_ROWS;
+      if (live && ru < r1) dx[(size_t)ru * cpr + chunk] = o[u];
+    }
+  }
+}
+
+// grid of a merged apply pass: about 2048 workgroups, at least one pass each
+dim3 merged_grid(int64_t rows, int C, int* rows_per_wg) {
+  const int64_t groups = (C + BM_CH - 1) / BM_CH;
+  int64_t per = (rows * groups + 2047) / 2048;
+  per = (per + BM_ROWS - 1) / BM_ROWS * BM_ROWS;
+  *rows_per_wg = (int)per;
+  return dim3((unsigned)groups, (unsigned)((rows + per - 1) / per));
+}
+
 unsigned apply_grid(int64_t n_chunks) {
   int64_t b = (n_chunks + BN_THREADS - 1) / BN_THREADS;
   const int64_t cap = 256 * 16;  // 16 workgroups per compute unit, grid-stride beyond that
   return (unsigned)(b < cap ? b : cap);
+}
+
+// what follows the partial sums of the forward pass: totals, saved statistics, y = [relu](a x + b [+ res])
+int launch_fwd_rest(const float* part, int slabs, float* coef, int64_t rows, int C, float eps, int relu, const float* gamma, const float* beta,
+                    const uint4* x, const uint4* res, uint4* y, float* save_mean, float* save_invstd, hipStream_t st) {
+  const double inv_rows = 1.0 / (double)rows;
+  if (slabs <= BN_MERGE_SLABS) {
+    int per;
+    const dim3 grid = merged_grid(rows, C, &per);
+    if (res)
+      hipLaunchKernelGGL(bn_apply_merged<1>, grid, dim3(BN_THREADS), 0, st, x, res, y, rows, per, C, part, slabs, inv_rows, eps, relu, gamma, beta,
+                         save_mean, save_invstd);
+    else
+      hipLaunchKernelGGL(bn_apply_merged<0>, grid, dim3(BN_THREADS), 0, st, x, res, y, rows, per, C, part, slabs, inv_rows, eps, relu, gamma, beta,
+                         save_mean, save_invstd);
+    return jz::launch_status();
+  }
+  hipLaunchKernelGGL(bn_fwd_final, dim3((unsigned)((C + BN_FIN_C - 1) / BN_FIN_C)), dim3(BN_THREADS), 0, st, part, slabs, C, inv_rows, eps, gamma,
+                     beta, save_mean, save_invstd, coef);
+  int rc = jz::launch_status();
+  if (rc != JZ_OK) return rc;
+  const int64_t n_chunks = rows * (C / 8);
+  if (res)
+    hipLaunchKernelGGL(bn_apply<1>, dim3(apply_grid(n_chunks)), dim3(BN_THREADS), 0, st, x, res, y, coef, n_chunks, C, C / 8, relu);
+  else
+    hipLaunchKernelGGL(bn_apply<0>, dim3(apply_grid(n_chunks)), dim3(BN_THREADS), 0, st, x, res, y, coef, n_chunks, C, C / 8, relu);
+  return jz::launch_status();
+}
+
+// the same for the backward pass: parameter gradients, dx from g = dy (masked by y > 0 when relu)
+int launch_bwd_rest(const float* part, int slabs, float* coef, int64_t rows, int C, int relu, const float* gamma, const float* mean,
+                    const float* invstd, const uint4* x, const uint4* y, const uint4* dy, uint4* dx, void* dgamma16, void* dbeta16, hipStream_t st) {
+  const double inv_rows = 1.0 / (double)rows;
+  unsigned short* dg = static_cast<unsigned short*>(dgamma16);
+  unsigned short* db = static_cast<unsigned short*>(dbeta16);
+  if (slabs <= BN_MERGE_SLABS) {
+    int per;
+    const dim3 grid = merged_grid(rows, C, &per);
+    hipLaunchKernelGGL(bn_bwd_apply_merged, grid, dim3(BN_THREADS), 0, st, x, y, dy, dx, rows, per, C, part, slabs, inv_rows, relu, gamma, mean,
+                       invstd, dg, db);
+    return jz::launch_status();
+  }
+  hipLaunchKernelGGL(bn_bwd_final, dim3((unsigned)((C + BN_FIN_C - 1) / BN_FIN_C)), dim3(BN_THREADS), 0, st, part, slabs, C, inv_rows, gamma, mean,
+                     invstd, dg, db, coef);
+  int rc = jz::launch_status();
+  if (rc != JZ_OK) return rc;
+  const int64_t n_chunks = rows * (C / 8);
+  hipLaunchKernelGGL(bn_bwd_apply, dim3(apply_grid(n_chunks)), dim3(BN_THREADS), 0, st, x, y, dy, dx, coef, n_chunks, C, C / 8, relu);
+  return jz::launch_status();
 }
 
 }  // namespace
@@ -400,13 +631,8 @@ extern "C" int jz_bn_relu_fwd(int64_t rows, int channels, const void* x16, const
   hipLaunchKernelGGL(bn_stats<0>, dim3((unsigned)(p.slabs * p.csplit)), dim3(BN_THREADS), 0, st, x, nullptr, nullptr, nullptr, nullptr,
                      part, rows, channels, p.cpr, p.rpp, p.rows_per_slab, 0, p.csplit);
   if ((rc = jz::launch_status()) != JZ_OK) return rc;
-  hipLaunchKernelGGL(bn_fwd_final, dim3((unsigned)((channels + BN_FIN_C - 1) / BN_FIN_C)), dim3(BN_THREADS), 0, st, part,
-                     p.slabs, channels, 1.0 / (double)rows, eps, gamma, beta, save_mean, save_invstd, coef);
-  if ((rc = jz::launch_status()) != JZ_OK) return rc;
-  const int64_t n_chunks = rows * p.cpr;
-  hipLaunchKernelGGL(bn_apply<0>, dim3(apply_grid(n_chunks)), dim3(BN_THREADS), 0, st, x, nullptr, static_cast<uint4*>(y16), coef,
-                     n_chunks, channels, p.cpr, relu ? 1 : 0);
-  return jz::launch_status();
+  return launch_fwd_rest(part, p.slabs, coef, rows, channels, eps, relu ? 1 : 0, gamma, beta, x, nullptr, static_cast<uint4*>(y16), save_mean,
+                         save_invstd, st);
 }
 
 extern "C" int jz_bn_relu_bwd(int64_t rows, int channels, const void* x16, const void* y16, const void* dy16,
@@ -436,14 +662,8 @@ extern "C" int jz_bn_relu_bwd(int64_t rows, int channels, const void* x16, const
   hipLaunchKernelGGL(bn_stats<1>, dim3((unsigned)(p.slabs * p.csplit)), dim3(BN_THREADS), 0, st, x, y, dy, save_mean, save_invstd, part, rows,
                      channels, p.cpr, p.rpp, p.rows_per_slab, relu ? 1 : 0, p.csplit);
   if ((rc = jz::launch_status()) != JZ_OK) return rc;
-  hipLaunchKernelGGL(bn_bwd_final, dim3((unsigned)((channels + BN_FIN_C - 1) / BN_FIN_C)), dim3(BN_THREADS), 0, st, part,
-                     p.slabs, channels, 1.0 / (double)rows, gamma, save_mean, save_invstd, static_cast<unsigned short*>(dgamma16),
-                     static_cast<unsigned short*>(dbeta16), coef);
-  if ((rc = jz::launch_status()) != JZ_OK) return rc;
-  const int64_t n_chunks = rows * p.cpr;
-  hipLaunchKernelGGL(bn_bwd_apply, dim3(apply_grid(n_chunks)), dim3(BN_THREADS), 0, st, x, y, dy, static_cast<uint4*>(dx16), coef,
-                     n_chunks, channels, p.cpr, relu ? 1 : 0);
-  return jz::launch_status();
+  return launch_bwd_rest(part, p.slabs, coef, rows, channels, relu ? 1 : 0, gamma, save_mean, save_invstd, x, y, dy, static_cast<uint4*>(dx16),
+                         dgamma16, dbeta16, st);
 }
 
 extern "C" int jz_bn_bwd_block_end(int64_t rows, int channels, const void* x16, const void* y_out16, const void* dya16,
@@ -476,14 +696,8 @@ extern "C" int jz_bn_bwd_block_end(int64_t rows, int channels, const void* x16, 
                      static_cast<const uint4*>(dya16), save_mean, save_invstd, part, rows, channels, p.cpr, p.rpp, p.rows_per_slab, 0,
                      p.csplit, static_cast<const uint4*>(dyb16), static_cast<uint4*>(g16));
   if ((rc = jz::launch_status()) != JZ_OK) return rc;
-  hipLaunchKernelGGL(bn_bwd_final, dim3((unsigned)((channels + BN_FIN_C - 1) / BN_FIN_C)), dim3(BN_THREADS), 0, st, part,
-                     p.slabs, channels, 1.0 / (double)rows, gamma, save_mean, save_invstd, static_cast<unsigned short*>(dgamma16),
-                     static_cast<unsigned short*>(dbeta16), coef);
-  if ((rc = jz::launch_status()) != JZ_OK) return rc;
-  const int64_t n_chunks = rows * p.cpr;
-  hipLaunchKernelGGL(bn_bwd_apply, dim3(apply_grid(n_chunks)), dim3(BN_THREADS), 0, st, x, nullptr, static_cast<const uint4*>(g16),
-                     static_cast<uint4*>(dx16), coef, n_chunks, channels, p.cpr, 0);
-  return jz::launch_status();
+  return launch_bwd_rest(part, p.slabs, coef, rows, channels, 0, gamma, save_mean, save_invstd, x, nullptr, static_cast<const uint4*>(g16),
+                         static_cast<uint4*>(dx16), dgamma16, dbeta16, st);
 }
 
 // ---- convolution + batch normalization (+ ReLU), forward, with the statistics taken in the convolution's epilogue ----
@@ -562,17 +776,8 @@ extern "C" int jz_conv2d_bn_relu_fwd(const jz_conv_desc* desc, const void* x16, 
                        part, rows, C, p.bn.cpr, p.bn.rpp, p.bn.rows_per_slab, 0, p.bn.csplit);
     if ((rc = jz::launch_status()) != JZ_OK) return rc;
   }
-  hipLaunchKernelGGL(bn_fwd_final, dim3((unsigned)((C + BN_FIN_C - 1) / BN_FIN_C)), dim3(BN_THREADS), 0, st, part, slabs, C,
-                     1.0 / (double)rows, eps, gamma, beta, save_mean, save_invstd, coef);
-  if ((rc = jz::launch_status()) != JZ_OK) return rc;
-  const int64_t n_chunks = rows * p.bn.cpr;
-  if (residual16)
-    hipLaunchKernelGGL(bn_apply<1>, dim3(apply_grid(n_chunks)), dim3(BN_THREADS), 0, st, c, static_cast<const uint4*>(residual16),
-                       static_cast<uint4*>(y16), coef, n_chunks, C, p.bn.cpr, relu ? 1 : 0);
-  else
-    hipLaunchKernelGGL(bn_apply<0>, dim3(apply_grid(n_chunks)), dim3(BN_THREADS), 0, st, c, nullptr, static_cast<uint4*>(y16), coef,
-                       n_chunks, C, p.bn.cpr, relu ? 1 : 0);
-  return jz::launch_status();
+  return launch_fwd_rest(part, slabs, coef, rows, C, eps, relu ? 1 : 0, gamma, beta, c, static_cast<const uint4*>(residual16),
+                         static_cast<uint4*>(y16), save_mean, save_invstd, st);
 }
 
 // ---- backward-data of a convolution + the backward pass of the batch normalization + ReLU that produced its input ----
@@ -671,14 +876,8 @@ static int conv_bwd_data_bn_bwd(const jz_conv_desc* desc, const void* dy16, cons
                          rows, C, p.bn.cpr, p.bn.rpp, p.bn.rows_per_slab, 1, p.bn.csplit);
     if ((rc = jz::launch_status()) != JZ_OK) return rc;
   }
-  hipLaunchKernelGGL(bn_bwd_final, dim3((unsigned)((C + BN_FIN_C - 1) / BN_FIN_C)), dim3(BN_THREADS), 0, st, part, slabs, C,
-                     1.0 / (double)rows, gamma, save_mean, save_invstd, static_cast<unsigned short*>(dgamma16),
-                     static_cast<unsigned short*>(dbeta16), coef);
-  if ((rc = jz::launch_status()) != JZ_OK) return rc;
-  const int64_t n_chunks = rows * p.bn.cpr;
-  hipLaunchKernelGGL(bn_bwd_apply, dim3(apply_grid(n_chunks)), dim3(BN_THREADS), 0, st, x, block_end ? nullptr : y, dz,
-                     static_cast<uint4*>(bn_dx16), coef, n_chunks, C, p.bn.cpr, block_end ? 0 : 1);
-  return jz::launch_status();
+  return launch_bwd_rest(part, slabs, coef, rows, C, block_end ? 0 : 1, gamma, save_mean, save_invstd, x, block_end ? nullptr : y, dz,
+                         static_cast<uint4*>(bn_dx16), dgamma16, dbeta16, st);
 }
 
 extern "C" int jz_conv2d_bwd_data_bn_relu_bwd(const jz_conv_desc* desc, const void* dy16, const void* w16, const void* bn_x16,
