@@ -292,6 +292,103 @@ __global__ __launch_bounds__(256) void splitk_reduce_sumsq(const float* __restri
   jz::sumsq_block_flush(sq, bad, sink, blockIdx.x, wsum);
 }
 
+// splitk_reduce for a convolution with a batch normalization behind it (MODE 0) or underneath it (MODE 1, 2): the kernel that
+// adds the partial sums and rounds also takes the per-channel sums that the normalization's statistics pass would, over
+// slabs of rows_per_slab rows, laid out as that pass's and the convolution epilogue's: stats[slab][2][N].
+//   MODE 0: sums of the stored value and of its square.   MODE 1: of g and g x^, g = the stored value where y > 0, else 0,
+//   x^ = (c - mean) invstd.   MODE 2: what is stored is g = RNE16(value [+ add]) where y > 0, else 0; sums of g and g x^.
+// A reduction is split where a layer has too few output tiles, i.e. in short layers, for which a launch costs as much as
+// the work: at 8 images of 64 x 64 the reduction (3.1 us) and the statistics pass behind it (3.8-5.7 us) were bound by
+// their start-up and the latency of a few loads; together they take 3.4-3.9 us, and ResNet-50's step went from 1.85 to
+// 1.66 ms (45 launches fewer).  A workgroup owns 64 columns; a thread 4 of them (one 16-byte load per split, eight in
+// flight) in every 16th row.
+constexpr int RS_COLS = 64, RS_ROWS = 16;
+template <int MODE>
+__global__ __launch_bounds__(256) void splitk_reduce_stats(const float* __restrict__ part, unsigned short* __restrict__ out, int M, int N,
+                                                           int splits, int G, int rows_per_slab, const unsigned short* __restrict__ y,
+                                                           const unsigned short* __restrict__ c, const unsigned short* __restrict__ add,
+                                                           const float* __restrict__ mean, const float* __restrict__ invstd,
+                                                           float* __restrict__ stats) {
+  __shared__ float4 red[2][RS_ROWS][RS_COLS / 4];
+  const int q = threadIdx.x % (RS_COLS / 4), rsub = threadIdx.x / (RS_COLS / 4);
+  const int n = blockIdx.x * RS_COLS + q * 4;
+  const bool live = n < N;  // N is a multiple of 8
+  const size_t MN = (size_t)M * N;
+  const int r1 = (int)(blockIdx.y + 1) * rows_per_slab < M ? (int)(blockIdx.y + 1) * rows_per_slab : M;
+  float s0[4] = {0.f, 0.f, 0.f, 0.f}, s1[4] = {0.f, 0.f, 0.f, 0.f};
+  float4 mu = make_float4(0.f, 0.f, 0.f, 0.f), is = mu;
+  if (MODE >= 1 && live) {
+    mu = *reinterpret_cast<const float4*>(mean + n);
+    is = *reinterpret_cast<const float4*>(invstd + n);
+  }
+  const float muv[4] = {mu.x, mu.y, mu.z, mu.w}, isv[4] = {is.x, is.y, is.z, is.w};
+  auto half_at = [](const uint2& v, int e) {
+    const unsigned short b = (unsigned short)((e < 2 ? v.x : v.y) >> ((e & 1) * 16));
+    _Float16 h;
+    __builtin_memcpy(&h, &b, 2);
+    return (float)h;
+  };
+  for (int r = blockIdx.y * rows_per_slab + rsub; live && r < r1; r += RS_ROWS) {
+    const size_t i = (size_t)r * N + n;
+    uint2 yq = make_uint2(0u, 0u), cq = yq, aq = yq;
+    if (MODE >= 1) {
+      yq = *reinterpret_cast<const uint2*>(y + i);
+      cq = *reinterpret_cast<const uint2*>(c + i);
+      if (MODE == 2 && add) aq = *reinterpret_cast<const uint2*>(add + i);
+    }
+    float v[4] = {0.f, 0.f, 0.f, 0.f}, lane[4] = {0.f, 0.f, 0.f, 0.f};
+    // splitk_reduce's order, hence its bits: splits g, g + G, g + 2G, ... for lane g, then the lanes
+    for (int k = 0, g = 0; g < G;) {
+      float4 t[8];
+      int ends = 0;  // bit u: load u is its lane's last
+      int n8 = 0;
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        t[u] = *reinterpret_cast<const float4*>(part + (size_t)(g < G ? k : 0) * MN + i);
+        if (g < G) {
+          ++n8;
+          k += G;
+          if (k >= splits) { ends |= 1 << u; k = ++g; }
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (u < n8) {
+          lane[0] += t[u].x; lane[1] += t[u].y; lane[2] += t[u].z; lane[3] += t[u].w;
+          if (ends >> u & 1)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) { v[e] += lane[e]; lane[e] = 0.f; }
+        }
+    }
+    _Float16 h[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      h[e] = (_Float16)v[e];
+      if (MODE == 2) {
+        h[e] = (_Float16)((float)h[e] + half_at(aq, e));  // exact in FP32, rounded once
+        if (!(half_at(yq, e) > 0.f)) h[e] = (_Float16)0.f;
+      }
+      const float g = MODE == 1 && !(half_at(yq, e) > 0.f) ? 0.f : (float)h[e];
+      s0[e] += g;
+      s1[e] += MODE == 0 ? g * g : g * ((half_at(cq, e) - muv[e]) * isv[e]);
+    }
+    uint2 pk;
+    __builtin_memcpy(&pk, h, 8);
+    *reinterpret_cast<uint2*>(out + i) = pk;
+  }
+  red[0][rsub][q] = make_float4(s0[0], s0[1], s0[2], s0[3]);
+  red[1][rsub][q] = make_float4(s1[0], s1[1], s1[2], s1[3]);
+  __syncthreads();
+  if (threadIdx.x < 2 * RS_COLS) {  // a thread per column and kind of sum, rows in order
+    const int kind = threadIdx.x / RS_COLS, col = threadIdx.x % RS_COLS;
+    const float* src = reinterpret_cast<const float*>(red[kind]) + col;
+    float t = 0.f;
+#pragma unroll
+    for (int r = 0; r < RS_ROWS; ++r) t += src[r * RS_COLS];
+    if (blockIdx.x * RS_COLS + col < (unsigned)N) stats[((size_t)blockIdx.y * 2 + kind) * N + blockIdx.x * RS_COLS + col] = t;
+  }
+}
+
 // sum of squares of n FP16 values into a sink (gradients whose producing kernel has no fused form)
 __global__ __launch_bounds__(256) void sumsq_half(const unsigned short* __restrict__ g16, long long n, jz::SumsqSink sink) {
   __shared__ unsigned long long wsum[5];
@@ -832,15 +929,33 @@ __global__ __launch_bounds__(256) void pack_class_filters(const unsigned short* 
   }
 }
 
-// a forward plan whose kernel can leave the per-tile column sums: the ring kernels (their LDS holds the sums), no split
+// slabs of rows whose sums a split reduction leaves (splitk_reduce_stats): at most 64, so that the normalization's apply pass
+// can add them up itself, unless that would leave fewer than two workgroups per compute unit
+int reduce_slab_rows(const GemmArgs& a) {
+  const int passes = (a.M + RS_ROWS - 1) / RS_ROWS, cols = (a.N + RS_COLS - 1) / RS_COLS;
+  const int slabs = cols < 8 ? 512 / cols : 64;
+  return (passes + slabs - 1) / slabs * RS_ROWS;
+}
+int reduce_slabs(const GemmArgs& a) {
+  const int rows = reduce_slab_rows(a);
+  return (a.M + rows - 1) / rows;
+}
+// a split reduction that can leave the column sums: one over a whole [M][N] result, whole 16-byte pieces of its rows
+bool split_leaves_stats(const Plan& pl) { return pl.args.splits > 1 && !pl.widen && !pl.packed && !pl.args.sc_on && (pl.args.N & 7) == 0; }
+
+// a forward plan whose kernel can leave the per-tile column sums: the ring kernels (their LDS holds the sums), or the
+// reduction behind a split one
 bool plan_leaves_stats(const Plan& pl) {
-  return pl.op == JZ_FWD && pl.fast && !pl.flat && pl.args.splits == 1;
+  return pl.op == JZ_FWD && ((pl.fast && !pl.flat && pl.args.splits == 1) || split_leaves_stats(pl));
 }
-// a backward-data plan whose kernel can leave the sums of a batch-norm backward: the ring kernels with masks, no split,
-// no scatter epilogue, whole 16-byte pieces of a row
+// a backward-data plan whose kernel can leave the sums of a batch-norm backward: the ring kernels with masks and
+// no scatter epilogue, whole 16-byte pieces of a row, or the reduction behind a split one
 bool plan_leaves_bwd_stats(const Plan& pl) {
-  return pl.op == JZ_BWD_DATA && pl.fast && !pl.gen && !pl.flat && pl.args.splits == 1 && !pl.args.sc_on && (pl.args.N & 7) == 0;
+  return pl.op == JZ_BWD_DATA && !pl.classes &&
+         ((pl.fast && !pl.gen && !pl.flat && pl.args.splits == 1 && !pl.args.sc_on && (pl.args.N & 7) == 0) || split_leaves_stats(pl));
 }
+// row groups of those sums: row tiles, or slabs of the reduction
+int stats_groups(const Plan& pl) { return pl.args.splits > 1 ? reduce_slabs(pl.args) : pl.args.tiles_m; }
 
 int run_widened(int op, const jz_conv_desc* d, const Plan& pl, const void* A, const void* B, void* D, void* ws, size_t ws_bytes,
                 void* stream, const jz::SumsqSink* sink);
@@ -854,7 +969,7 @@ int run(int op, const jz_conv_desc* d, const void* A, const void* B, void* D, vo
   // the caller sized the buffer of the column sums from an earlier plan: it has to be this plan (the run-time tuning table
   // may have been changed in between)
   if (stats && !(op == JZ_BWD_DATA ? plan_leaves_bwd_stats(pl) && bn != nullptr : plan_leaves_stats(pl))) return JZ_ERR_UNSUPPORTED;
-  if (stats && pl.args.tiles_m != stats_tiles_m) return JZ_ERR_UNSUPPORTED;
+  if (stats && stats_groups(pl) != stats_tiles_m) return JZ_ERR_UNSUPPORTED;
   if (!A || !B || !D) return JZ_ERR_NULL;
   if (!aligned16(A) || !aligned16(B) || !aligned16(D) || (ws && !aligned16(ws))) return JZ_ERR_ALIGN;
   if (overlaps(D, pl.bytesD, A, pl.bytesA) || overlaps(D, pl.bytesD, B, pl.bytesB)) return JZ_ERR_ALIAS;
@@ -943,15 +1058,30 @@ int run(int op, const jz_conv_desc* d, const void* A, const void* B, void* D, vo
     }
     if ((rc = jz::launch_status()) != JZ_OK) return rc;
   }
-  if (op == JZ_FWD) rc = stats ? launch_fwd_stats(pl, st) : launch_fwd(pl, st);
-  else if (op == JZ_BWD_DATA) rc = !stats ? launch_bwd_data(pl, st) : bn->block_end ? launch_bwd_data_block_end(pl, st) : launch_bwd_data_stats(pl, st);
+  const bool epilogue_stats = stats && a.splits == 1;
+  if (op == JZ_FWD) rc = epilogue_stats ? launch_fwd_stats(pl, st) : launch_fwd(pl, st);
+  else if (op == JZ_BWD_DATA) rc = !epilogue_stats ? launch_bwd_data(pl, st) : bn->block_end ? launch_bwd_data_block_end(pl, st) : launch_bwd_data_stats(pl, st);
   else rc = launch_bwd_weight(pl, st);
   if (rc != JZ_OK) return rc;
+  int lg = 0;
+  if (a.splits > 1) {  // split lanes per output group: enough workgroups to cover the chip first, then shorten each thread's chain
+    const long long MN = (long long)a.M * a.N;
+    while (lg < 5 && (2 << lg) <= a.splits && ((MN + 3) / 4 + (256 >> lg) - 1) / (256 >> lg) < 1024) ++lg;
+  }
+  if (a.splits > 1 && stats) {
+    const dim3 grid((unsigned)((a.N + RS_COLS - 1) / RS_COLS), (unsigned)reduce_slabs(a));
+    const int mode = op == JZ_FWD ? 0 : bn->block_end ? 2 : 1;
+    auto go = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, a.Dpart, a.D16, a.M, a.N, a.splits, 1 << lg, reduce_slab_rows(a), a.st_y, a.st_c, a.st_add,
+                         a.st_mean, a.st_invstd, stats);
+    };
+    if (mode == 0) go(splitk_reduce_stats<0>);
+    else if (mode == 1) go(splitk_reduce_stats<1>);
+    else go(splitk_reduce_stats<2>);
+    return jz::launch_status();
+  }
   if (a.splits > 1) {
     long long MN = (long long)a.M * a.N;
-    // split lanes per output group: enough workgroups to cover the chip first, then shorten each thread's chain
-    int lg = 0;
-    while (lg < 5 && (2 << lg) <= a.splits && ((MN + 3) / 4 + (256 >> lg) - 1) / (256 >> lg) < 1024) ++lg;
     const long long per_block = 256 >> lg;
     unsigned blocks = (unsigned)(((MN + 3) / 4 + per_block - 1) / per_block);
     // small-channel backward-weight: the reduction writes the real filter entries straight into dw
@@ -1048,7 +1178,7 @@ int jz::conv_fwd_stats_plan(const jz_conv_desc* d, size_t* conv_ws_bytes, int* t
   int rc = make_plan(JZ_FWD, d, &pl);
   if (rc != JZ_OK) return rc;
   *conv_ws_bytes = pl.ws_bytes;
-  *tiles_m = plan_leaves_stats(pl) ? pl.args.tiles_m : 0;
+  *tiles_m = plan_leaves_stats(pl) ? stats_groups(pl) : 0;
   return JZ_OK;
 }
 int jz::conv_fwd_run(const jz_conv_desc* d, const void* x, const void* w, void* y, void* ws, size_t ws_bytes, float* stats,
@@ -1060,7 +1190,7 @@ int jz::conv_bwd_data_stats_plan(const jz_conv_desc* d, size_t* conv_ws_bytes, i
   int rc = make_plan(JZ_BWD_DATA, d, &pl);
   if (rc != JZ_OK) return rc;
   *conv_ws_bytes = pl.ws_bytes;
-  *tiles_m = plan_leaves_bwd_stats(pl) ? pl.args.tiles_m : 0;
+  *tiles_m = plan_leaves_bwd_stats(pl) ? stats_groups(pl) : 0;
   return JZ_OK;
 }
 int jz::conv_bwd_data_run(const jz_conv_desc* d, const void* dy, const void* w, void* dx, void* ws, size_t ws_bytes, float* stats,

@@ -17,8 +17,8 @@ inline bool overlaps(const void* a, size_t na, const void* b, size_t nb) {
 }
 
 // Forward convolution for the fused convolution + batch normalization entry point.  conv_fwd_stats_plan: the workspace
-// the convolution needs and, when its kernel can leave per-tile column sums of y and y^2, the number of row tiles (else
-// 0).  conv_fwd_run with stats != nullptr (only after a plan that said so) writes them as [tiles_m][2][K] floats; it
+// the convolution needs and, when its kernel (or its split reduction) can leave column sums of y and y^2 over groups of
+// rows (its row tiles, or slabs of the reduction), the number of groups (else 0).  conv_fwd_run with stats != nullptr (only after a plan that said so) writes them as [tiles_m][2][K] floats; it
 // returns JZ_ERR_UNSUPPORTED, before anything is launched, if the plan no longer has stats_tiles_m row tiles.
 int conv_fwd_stats_plan(const jz_conv_desc* d, size_t* conv_ws_bytes, int* tiles_m);
 int conv_fwd_run(const jz_conv_desc* d, const void* x, const void* w, void* y, void* ws, size_t ws_bytes, float* stats,
@@ -26,7 +26,7 @@ int conv_fwd_run(const jz_conv_desc* d, const void* x, const void* w, void* y, v
 
 // Backward-data convolution for the fused "backward-data + batch-norm backward" entry point (jz_bn.hip): the layer whose
 // output (after batch normalization + ReLU) was this convolution's input.  conv_bwd_data_stats_plan: the convolution's
-// workspace and, when its kernel can leave per-tile sums of g and g x^ (g = dx where y > 0), the number of row tiles (else 0);
+// workspace and, when its kernel or split reduction can leave sums of g and g x^ (g = dx where y > 0) over groups of rows, their number (else 0);
 // conv_bwd_data_run with stats != nullptr (only after a plan that said so) writes them as [tiles_m][2][C] floats.
 struct BnBwdOperands {
   const void* x16;      // the normalization's input  [N,H,W,C] of the convolution's input shape
