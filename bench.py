@@ -22,7 +22,7 @@ import time
 import numpy as np
 import torch
 
-from paper_1807_11205_amd import api, inputs, shapes
+from paper_1807_11205_amd import api, inputs, shapes, tune
 
 FP16_MFMA_PEAK_TFLOPS = 2500.0   # MI355X dense fp16 matrix peak
 FP32_MFMA_PEAK_TFLOPS = 157.3    # MI355X dense fp32 matrix peak
@@ -439,6 +439,9 @@ def alexnet_workload(args):
     """bench.py --workload alexnet: times AlexNetStep.  One JSON line; no LARS phase (the configuration names none)."""
     B = args.batch
     n_side = max(0, min(args.streams, 4) - 1)
+    if n_side > 1:   # weight gradients on two side streams: launches that leave room for each other
+        tune.share_chip([api.conv_desc(B, c.H, c.H, c.C, c.K, c.R, c.R, c.stride, c.pad) for c in shapes.alexnet_convs()] +
+                        [api.conv_desc(B, 1, 1, f.I, f.O, 1, 1) for f in shapes.ALEXNET_FCS])
     wl = AlexNetStep(B, n_side)
     layers, flops, prog = wl.layers, wl.flops, wl.prog
     rows = None
@@ -773,6 +776,9 @@ def main():
     if args.workload == "chain":
         chain_workload(args)
         return
+    if args.streams > 2 and args.dtype == "f16":   # weight gradients on two side streams: launches that leave room for each other
+        tune.share_chip([api.conv_desc(args.batch, c.H, c.H, c.C, c.K, c.R, c.R, c.stride, c.pad) for c in shapes.resnet50_convs(args.variant)] +
+                        [api.conv_desc(args.batch, 1, 1, shapes.RESNET50_FC.I, shapes.RESNET50_FC.O, 1, 1)])
     wl = ResNet50Step(batch=args.batch, dtype=args.dtype, lars_path=args.lars_path, sumsq_from=args.sumsq_from, variant=args.variant)
 
     # loss-scale back-off: halve S until the weight gradients stay inside fp16 and the update is not skipped

@@ -79,6 +79,27 @@ def model_layers(model):
     return BATCH, layers
 
 
+def share_chip(descs):
+    """Make backward-weight of these layers use the split counts recorded for a step whose weight gradients run on two side
+    streams beside the rest of the backward pass.  Alone, a launch is fastest when it fills the chip, and that is what the
+    planner chooses; three streams side by side want a half to a quarter of the splits (the batch-64 step: 3.40 ms against
+    3.53).  Process-wide, through jz_conv2d_tune_set, like any recorded choice.  Returns the number of layers it found."""
+    import glob
+    from . import api
+    rows = {}
+    for path in sorted(glob.glob(os.path.join(PKG, "csrc", "jz_tuned*.inc"))):
+        for m in re.finditer(r"^\{2, (\d+), (\d+), (\d+), (\d+), 0, (\d+), (\d+), (\d+), (\d+), (\d+), (\d+)\}", open(path).read(), re.M):
+            v = tuple(int(g) for g in m.groups())
+            rows.setdefault(v[:4], v[4:])
+    found = 0
+    for d in descs:
+        row = rows.get((d.K, d.R * d.S * d.C, d.N * d.P * d.Q, d.R * d.S))
+        if row:
+            api.jz_conv2d_tune_set(api.JZ_BWD_WEIGHT, d, *row)
+            found += 1
+    return found
+
+
 def sweep(path, variants=VARIANTS, model="resnet50"):
     import torch
     from . import api
