@@ -38,10 +38,10 @@ class ResNet50Chain:
                  policy=None, device="cuda:0", fused=True, block_end=True, proj_side=False, presummed=True, bwd_stats=True):
         """fused: forward convolution + batch normalization as one call (statistics in the convolution's epilogue)
         instead of two.  bwd_stats (with fused): a backward-data convolution and the batch-norm backward that consumes its
-        output as one call (the statistics of that backward in the convolution's epilogue).  presummed: the weight-gradient GEMMs whose reduction is split leave their gradient's sum of squares
-        in the optimiser's workspace (from inside the kernel that adds the partial sums), the remaining tensors' sums are
-        taken by one launch behind the last gradient of the backward pass, and the update is one launch (else: the update's
-        own reduce pass reads every gradient again, three launches)."""
+        output as one call (the statistics of that backward in the convolution's epilogue).  presummed: the gradients' sums of squares are taken by one launch
+        behind the last gradient of the backward pass, and the update is one launch with the weights' norms carried (else: the
+        update's own reduce pass, three launches).  Taking the sums inside the weight-gradient GEMMs' split reductions instead
+        makes those launches (47 of them) 2 us longer each, where one pass over all gradients takes 15-25 us."""
         self.presummed = bool(presummed)
         self.N, self.image, self.device, self.fused = int(batch), int(image), torch.device(device), bool(fused)
         self.block_end = bool(block_end) and self.fused
@@ -60,14 +60,6 @@ class ResNet50Chain:
         self.offsets = [int(o) for o in host.offsets]
         self.flags = [int(x) for x in host.flags]
         self.index = {name: i for i, (name, _, _, _) in enumerate(self.tensors)}
-        if self.presummed:      # filters whose weight-gradient reduction is split: their producer supplies the sum of squares
-            for cs in self.convs:
-                d = api.conv_desc(self.N, cs.H, cs.H, cs.C, cs.K, cs.R, cs.R, cs.stride, cs.pad)
-                if ", 1 splits" not in api.jz_conv2d_describe_plan(api.JZ_BWD_WEIGHT, d):
-                    self.flags[self.index[cs.name + ".w"]] |= api.JZ_PARAM_GRAD_PRESUMMED
-            d = api.conv_desc(self.N, 1, 1, self.fc.I, self.fc.O, 1, 1)
-            if ", 1 splits" not in api.jz_conv2d_describe_plan(api.JZ_BWD_WEIGHT, d):
-                self.flags[self.index["fc.w"]] |= api.JZ_PARAM_GRAD_PRESUMMED
         self.master = torch.from_numpy(host.master_w).to(dev)
         self.momentum = torch.zeros_like(self.master)
         self.w16 = self.master.to(h)
@@ -92,7 +84,7 @@ class ResNet50Chain:
         self._build()
         if self.presummed:
             # first launch of a step: clear the gradient sinks, add up the carried sums of squares of the weights, note the
-            # loss scale; last launch of the backward pass: the tensors no GEMM produces (batch-norm scale / shift, bias)
+            # loss scale; last launch of the backward pass: every tensor's gradient
             self.fwd_ops.insert(0, Op("lars_begin", "begin", {}, [], [],
                                       lambda stream=None: api.jz_lars_begin_step(self.ps, self.lars_ws, self.ls_state, stream)))
             self.bwd_ops.append(Op("lars_grad_sumsq", "rest", {}, [self.grad], [],
@@ -122,9 +114,6 @@ class ResNet50Chain:
         self._ws_bytes = max(self._ws_bytes, api.jz_conv2d_workspace_bytes(op, d))
         kind = {api.JZ_FWD: "conv_fwd", api.JZ_BWD_DATA: "conv_bwd_data", api.JZ_BWD_WEIGHT: "conv_bwd_weight"}[op]
         bind = lambda ws: api.bind_conv2d(op, d, a, b, out, ws)
-        if op == api.JZ_BWD_WEIGHT and self.presummed and self.flags[self.index[name + ".w"]] & api.JZ_PARAM_GRAD_PRESUMMED:
-            sink = api.jz_lars_sumsq_sink(self.ps, self.lars_ws, self.index[name + ".w"])
-            bind = lambda ws: api.bind_conv2d_bwd_weight_sumsq(d, a, b, out, sink, ws)
         o = Op(kind, name, dict(desc=d), [a, b], [out], bind=bind)
         if op == api.JZ_BWD_WEIGHT:
             o.lane = "side"
@@ -135,9 +124,6 @@ class ResNet50Chain:
         self._ws_bytes = max(self._ws_bytes, api.jz_gemm_fc_workspace_bytes(mode, B, I, O))
         kind = {api.JZ_FWD: "fc_fwd", api.JZ_BWD_DATA: "fc_bwd_data", api.JZ_BWD_WEIGHT: "fc_bwd_weight"}[mode]
         bind = lambda ws: api.bind_gemm_fc(mode, B, I, O, a, b, out, ws)
-        if mode == api.JZ_BWD_WEIGHT and self.presummed and self.flags[self.index[name + ".w"]] & api.JZ_PARAM_GRAD_PRESUMMED:
-            sink = api.jz_lars_sumsq_sink(self.ps, self.lars_ws, self.index[name + ".w"])
-            bind = lambda ws: api.bind_gemm_fc_bwd_weight_sumsq(B, I, O, a, b, out, sink, ws)
         o = Op(kind, name, dict(B=B, I=I, O=O), [a, b], [out], bind=bind)
         if mode == api.JZ_BWD_WEIGHT:
             o.lane = "side"
