@@ -40,15 +40,16 @@ constexpr int F_BK = 16;  // reduction elements per tile
 struct F32Args {
   const float* A;
   const float* B;
-  float* D;      // [M][N], written when splits == 1
-  float* Dpart;  // [splits][M][N]
+  float* D;      // [M][N], written where the reduction is not split
+  float* Dpart;  // [splits][rows][N], the rows whose reduction is split
   int M, N, Kred;
   int nkt, kt_per_split, splits, tiles_m, tiles_n;
   ConvGeom g;
   // the LDS-direct kernel's: descriptor bounds, tile decomposition, where tap (r, s) of the launch sits among the w_taps taps
   // of a filter (backward-data), and the scatter of strided backward-data as in GemmArgs
   unsigned bytesA, bytesB;
-  FastDiv d_tiles_mn, d_tiles_n;
+  int full_rows;  // rows of tiles whose reduction is not split (all of them: splits == 1)
+  FastDiv d_tiles_mn, d_tiles_n;  // d_tiles_mn: the tiles of the other rows
   int w_taps, w_tap0, w_tap_r, w_tap_s;
   int bw_same;    // backward-weight, unit stride, output grid = input grid: x is read at a constant pixel distance per tap
   int bw_linear;  // backward-weight of a 1x1 unit-stride unpadded layer: x is a plain [Kred][IC] matrix
@@ -361,41 +362,63 @@ bool needs_gen_f32(const PlanF32& pl) {
   return g.IC % FD_BK != 0 || g.R * g.S > 32 || (long long)pl.bytesA + margin >= 0xfffffff0ll;
 }
 
-// Tile and split of the LDS-direct kernel.  The vector ALU bounds it, so a launch takes (workgroups a compute unit gets) x (k
-// tiles) x (time of a k tile), but not less than one workgroup alone takes per tile, when nothing covers its waits; plus
-// prologues and epilogues, plus, when the reduction is split, writing and re-reading the partial sums and a second launch.
-// The times are microseconds measured on ResNet-50 layers at batch 64 with each tile forced; the gathered x of
-// backward-weight costs vector instructions of its own.
+// Tile and split of the LDS-direct kernel, by a cost model in microseconds.  A compute unit works through its share of the
+// workgroups, `resident` of them at a time; the vector ALU (which the FP32 matrix instructions share) bounds it at `thr` a k
+// tile, a workgroup whose waits nothing covers takes `lat`, and the operands have to come from memory once: the launch takes
+// the fourth-power norm of the three.  A split adds a second launch and re-reading the partial sums.
+// Which part of the reduction is split: all of it, or only the rows of tiles that would start the last, unfilled round of
+// workgroups (full_rows rows of tiles are then computed whole).  Batch 64 makes 98 * 2^n tiles, 784 for most layers of
+// ResNet-50: four rounds of 256 instead of 3.06 (14 x 14, 256 -> 256, 3x3: 135 -> 118 us forward, 139 -> 124 backward-data).
+// The constants (forward, backward-data, backward-weight with plain and with gathered x) are least-squares fits to timings of
+// every tile and split on 660 operations: ResNet-50 of both kinds and AlexNet at batch sizes from 2 to 64, random layers.  On a
+// quarter of them left out of the fit the choices were 0.7-1.9 % slower than the best.
 void choose_tiling_f32(PlanF32* pl, bool may_split, bool fixed_tile = false) {
-  struct Tile { int bm, bn; double us, alone, us_bw, alone_bw; };
-  static const Tile tiles[] = {{128, 128, 0.98, 1.05, 1.25, 1.40}, {128, 64, 0.49, 0.60, 0.55, 0.75}, {64, 128, 0.48, 0.60, 0.57, 0.80},
-                               {64, 64, 0.23, 0.36, 0.29, 0.48}};
+  struct Tile { int bm, bn, resident; double lat[4], thr[4], prologue[4], own[4]; };
+  static const Tile tiles[] = {
+      {128, 128, 2, {0.935, 1.023, 1.020, 1.181}, {0.889, 0.919, 0.907, 1.065}, {1.798, 1.665, 2.516, 2.486}, {2.607, 2.429, 2.484, 0.813}},
+      {128, 64, 3, {0.513, 0.615, 0.604, 0.685}, {0.461, 0.464, 0.488, 0.532}, {0.137, 0.147, 0.335, 0.128}, {1.206, 1.280, 0.974, 0.474}},
+      {64, 128, 3, {0.489, 0.579, 0.630, 0.800}, {0.456, 0.476, 0.494, 0.565}, {0.159, 0.239, 0.687, 0.228}, {1.199, 1.092, 0.988, 0.657}},
+      {64, 64, 5, {0.283, 0.342, 0.352, 0.421}, {0.235, 0.246, 0.255, 0.288}, {0.037, 0.039, 0.043, 0.030}, {0.512, 0.548, 0.429, 0.187}}};
+  static const double fixed[] = {4.76, 4.82, 5.10, 5.64}, reduce_launch[] = {3.38, 3.81, 3.59, 4.01}, reduce_byte[] = {0.187, 0.169, 0.160, 0.208},
+                      byte[] = {0.135, 0.127, 0.135, 0.230};  // per megabyte
   F32Args& a = pl->args;
   a.nkt = (a.Kred + FD_BK - 1) / FD_BK;
-  const bool gather = pl->op == JZ_BWD_WEIGHT && !a.bw_linear;
+  const int c = pl->op == JZ_FWD ? 0 : pl->op == JZ_BWD_DATA ? 1 : a.bw_linear ? 2 : 3;
+  const double in = 1e-6 * ((double)std::min<long long>(pl->bytesA, 4ll * a.M * a.Kred) + (double)std::min<long long>(pl->bytesB, 4ll * a.N * a.Kred));
+  auto p4 = [](double x) { return (x * x) * (x * x); };
+  auto rounds = [](double w) { return w <= 4.0 ? ceil(w) : w + 0.5; };  // many small rounds even out
   double best = 1e30;
-  int bsp = 1;
+  int bsp = 1, bfull = 0;
   for (const Tile& t : tiles) {
     if (fixed_tile && (t.bm != pl->BM || t.bn != pl->BN)) continue;
-    const long long tm = (a.M + t.bm - 1) / t.bm, tn = (a.N + t.bn - 1) / t.bn;
+    const long long tm = (a.M + t.bm - 1) / t.bm, tn = (a.N + t.bn - 1) / t.bn, slots = 256 * t.resident;
     for (int sp = 1; sp <= 512; sp = sp < 8 ? sp + 1 : sp + sp / 4) {
       if (sp > 1 && (!may_split || a.nkt / sp < 8)) break;
       const int kps = (a.nkt + sp - 1) / sp, real = (a.nkt + kps - 1) / kps;
-      const double w = (double)(tm * tn * real) / 256.0;
-      const double n = w <= 4.0 ? ceil(w) : w + 0.5;  // many small rounds even out
-      double per = n * (gather ? t.us_bw : t.us);
-      const double alone = gather ? t.alone_bw : t.alone;
-      if (per < alone) per = alone;
-      double us = 5.0 + kps * per + n;
-      if (real > 1) us += 4.0 + 2.0 * real * (double)a.M * a.N * 4.0 / 4.0e6;
-      if (us < best) { best = us; pl->BM = t.bm; pl->BN = t.bn; bsp = sp; }
+      // full rows of tiles: none (all of them without a split), or as many as fill whole rounds
+      const long long round_rows = tm * tn / 256 * 256 / tn;
+      for (int tail = 0; tail < 2; ++tail) {
+        if (tail && (sp == 1 || round_rows == 0 || round_rows >= tm)) break;
+        const long long full = sp == 1 ? tm : tail ? round_rows : 0, wf = full * tn, ws = (tm - full) * tn * real;
+        const double n1 = tail ? ceil(wf / 256.0) : rounds(wf / 256.0), n2 = tail ? ceil(ws / 256.0) : rounds(ws / 256.0);
+        const double t_thr = n1 * (t.own[c] + t.thr[c] * a.nkt) + n2 * (t.own[c] + t.thr[c] * kps);
+        const long long l1 = (wf + slots - 1) / slots, l2 = wf > 0 ? (wf + ws + slots - 1) / slots - l1 : (ws + slots - 1) / slots;
+        const double t_lat = l1 * (t.prologue[c] + t.lat[c] * a.nkt) + l2 * (t.prologue[c] + t.lat[c] * kps);
+        const double out = 4e-6 * a.M * a.N, part = sp > 1 ? 4e-6 * real * (double)(a.M - full * t.bm) * a.N : 0.0;
+        const double t_mem = byte[c] * (in + part + (full > 0 ? out : 0.0));
+        double time = fixed[c] + sqrt(sqrt(p4(t_thr) + p4(t_lat) + p4(t_mem)));
+        if (sp > 1) time += reduce_launch[c] + reduce_byte[c] * part;
+        if (time < best) { best = time; pl->BM = t.bm; pl->BN = t.bn; bsp = sp; bfull = (int)full; }
+      }
     }
   }
   a.tiles_m = (a.M + pl->BM - 1) / pl->BM;
   a.tiles_n = (a.N + pl->BN - 1) / pl->BN;
   a.kt_per_split = (a.nkt + bsp - 1) / bsp;
   a.splits = (a.nkt + a.kt_per_split - 1) / a.kt_per_split;
-  a.d_tiles_mn = make_fastdiv((unsigned)(a.tiles_m * a.tiles_n));
+  a.full_rows = a.splits > 1 ? bfull : a.tiles_m;
+  const int tail_tiles = (a.tiles_m - a.full_rows) * a.tiles_n;
+  a.d_tiles_mn = make_fastdiv((unsigned)(tail_tiles > 0 ? tail_tiles : 1));
   a.d_tiles_n = make_fastdiv((unsigned)a.tiles_n);
 }
 
@@ -509,10 +532,11 @@ int make_plan_f32(int op, const jz_conv_desc* d, PlanF32* pl) {
     } else {
       choose_tiling_f32(pl, !a.sc_on);
     }
-    pl->ws_bytes = a.splits > 1 ? (size_t)a.splits * a.M * a.N * sizeof(float) : 0;
+    pl->ws_bytes = a.splits > 1 ? (size_t)a.splits * (a.M - a.full_rows * pl->BM) * a.N * sizeof(float) : 0;
     pl->plain_ws_bytes = pl->ws_bytes;
     return JZ_OK;
   }
+  a.full_rows = 0;
   // Tile and split: 128 x 128 tiles where they give the chip (256 compute units, two workgroups each) enough
   // workgroups, else 64 x 64; then split the reduction until about 512 workgroups exist, never shorter than 8 k tiles.
   a.nkt = (a.Kred + F_BK - 1) / F_BK;
@@ -542,7 +566,7 @@ int launch_f32_dma(const F32Args& a, hipStream_t st) {
       return JZ_ERR_LAUNCH;
     attr_set.store(true, std::memory_order_relaxed);
   }
-  hipLaunchKernelGGL((f32_dma_kernel<OP, BM, BN, GEN>), dim3((unsigned)a.tiles_m * (unsigned)a.tiles_n * (unsigned)a.splits), dim3(256), smem, st, a);
+  hipLaunchKernelGGL((f32_dma_kernel<OP, BM, BN, GEN>), dim3((unsigned)(a.full_rows + (a.tiles_m - a.full_rows) * a.splits) * (unsigned)a.tiles_n), dim3(256), smem, st, a);
   return jz::launch_status();
 }
 
@@ -642,11 +666,11 @@ int run_f32(int op, const jz_conv_desc* d, const void* A, const void* B, void* D
   else rc = launch_f32<OP_BWD_WEIGHT>(pl, st);
   if (rc != JZ_OK) return rc;
   if (a.splits > 1) {
-    const long long MN = (long long)a.M * a.N, groups = (MN + 3) / 4;
+    const long long first = (long long)a.full_rows * pl.BM * a.N, MN = (long long)a.M * a.N - first, groups = (MN + 3) / 4;
     int lg = 0;  // lanes per output group: enough workgroups to cover the chip first, then shorten each thread's chain
     while (lg < 5 && (2 << lg) <= a.splits && (groups + (256 >> lg) - 1) / (256 >> lg) < 1024) ++lg;
     hipLaunchKernelGGL(splitk_reduce_f32, dim3((unsigned)((groups + (256 >> lg) - 1) / (256 >> lg))), dim3(256), 0, st,
-                       (const float*)a.Dpart, a.D, MN, a.splits, lg);
+                       (const float*)a.Dpart, a.D + first, MN, a.splits, lg);
     rc = jz::launch_status();
   }
   return rc;

@@ -67,14 +67,16 @@ __device__ __forceinline__ void f32_dma_body(const F32Args& a, unsigned block, u
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
 
-  unsigned L = xcd_remap(block, blocks);
-  const unsigned tiles_mn = (unsigned)(a.tiles_m * a.tiles_n);
-  const int split = (int)fd_div(L, a.d_tiles_mn);
-  L -= (unsigned)split * tiles_mn;
+  // the first full_rows rows of tiles are computed whole, one workgroup each; the rest by `splits` workgroups a tile
+  const unsigned full = (unsigned)(a.full_rows * a.tiles_n);
+  const bool whole = block < full;
+  unsigned L = whole ? xcd_remap(block, full) : xcd_remap(block - full, blocks - full);
+  const int split = whole ? 0 : (int)fd_div(L, a.d_tiles_mn);
+  L -= (unsigned)split * (unsigned)((a.tiles_m - a.full_rows) * a.tiles_n);
   const unsigned trow = fd_div(L, a.d_tiles_n);
-  const int m0 = (int)trow * BM, n0 = (int)(L - trow * (unsigned)a.tiles_n) * BN;
+  const int m0 = ((int)trow + (whole ? 0 : a.full_rows)) * BM, n0 = (int)(L - trow * (unsigned)a.tiles_n) * BN;
   const int kt_begin = split * a.kt_per_split;
-  const int kt_end = kt_begin + a.kt_per_split < a.nkt ? kt_begin + a.kt_per_split : a.nkt;
+  const int kt_end = !whole && kt_begin + a.kt_per_split < a.nkt ? kt_begin + a.kt_per_split : a.nkt;
   const int nk = kt_end - kt_begin;
 
   constexpr unsigned OOB = 0xffffffffu;
@@ -403,8 +405,8 @@ __device__ __forceinline__ void f32_dma_body(const F32Args& a, unsigned block, u
 
   // accumulator register r of tile (x,y): m = wrow + 16 x + lane % 16, n = wcol + 16 y + 4 (lane / 16) + r.
   // Half of the tile's rows at a time (those of one wm) go through LDS, so that a store instruction writes whole row pieces.
-  float* const out = a.splits > 1 ? a.Dpart + (size_t)split * a.M * a.N : a.D;
-  const bool scatter = a.sc_on && a.splits == 1;
+  const int part_row = a.full_rows * BM;  // row 0 of the partial sums
+  float* const out = whole ? a.D : a.Dpart + (size_t)split * (a.M - part_row) * a.N;
   constexpr int LDF = BN + 4, RH = BM / 2, FCH = BN / 4, RPP = 256 / FCH;
   static_assert(RH * LDF * 4 <= FD_NST * STAGE, "the staged half tile has to fit the ring");
   const bool vec = (a.N & 3) == 0;
@@ -425,8 +427,8 @@ __device__ __forceinline__ void f32_dma_body(const F32Args& a, unsigned block, u
     for (int i = 0; i < RH / RPP; ++i) {
       const int row = frow + RPP * i, m = m0 + ps * RH + row, n = n0 + fch * 4;
       if (m >= a.M || n >= a.N) continue;
-      size_t drow = (size_t)m;
-      if (scatter) {  // row m = (n, p, q) of the strided grid goes to input pixel (n, p sh + oh, q sw + ow)
+      size_t drow = (size_t)(whole ? m : m - part_row);
+      if (a.sc_on) {  // row m = (n, p, q) of the strided grid goes to input pixel (n, p sh + oh, q sw + ow)
         const unsigned img = fd_div((unsigned)m, g.d_ohow);
         const unsigned rem = (unsigned)m - img * (unsigned)(g.OH * g.OW);
         const unsigned p = fd_div(rem, g.d_ow), q = rem - p * (unsigned)g.OW;
