@@ -499,7 +499,18 @@ bool same_key(const Tuned& x, const Tuned& y) {
 }
 
 // bk64_ok: the 64-deep k tile is usable for this layer; forced_bk: the k tile depth is fixed (register path, packed mode)
-void choose_tiling(Plan* pl, bool bk64_ok, int forced_bk) {
+void set_tiles(Plan* pl, int splits) {
+  GemmArgs& a = pl->args;
+  a.nkt = (a.Kred + pl->bk - 1) / pl->bk;
+  a.tiles_m = (a.M + pl->BM - 1) / pl->BM;
+  a.tiles_n = (a.N + pl->BN - 1) / pl->BN;
+  a.kt_per_split = (a.nkt + splits - 1) / splits;
+  a.splits = (a.nkt + a.kt_per_split - 1) / a.kt_per_split;  // drop empty splits
+  a.d_tiles_mn = make_fastdiv((unsigned)(a.tiles_m * a.tiles_n));
+  a.d_tiles_n = make_fastdiv((unsigned)a.tiles_n);
+}
+
+void choose_tiling(Plan* pl, bool bk64_ok, int forced_bk, bool tables = true) {
   GemmArgs& a = pl->args;
   static const int split_opts[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64, 96, 128, 192, 256, 384, 512};
   const int oi = pl->op == JZ_FWD ? 0 : pl->op == JZ_BWD_DATA ? 1 : 2;
@@ -509,7 +520,7 @@ void choose_tiling(Plan* pl, bool bk64_ok, int forced_bk) {
   if (!pl->fast) forced_bk = BK;  // the element-wise kernel: one shape (the first variant's), 64-deep tiles, ~8x slower
   const Tuned* hit = nullptr;
   Tuned rt_hit{};
-  if (pl->fast && (!forced_bk || pl->packed)) {
+  if (tables && pl->fast && (!forced_bk || pl->packed)) {
     const Tuned key{oi, a.M, a.N, a.Kred, a.g.R * a.g.S, a.sc_on, 0, 0, 0, 0, 0, 0};
     auto usable = [&](const Tuned& t) {
       if ((pl->gen || pl->flat) && (t.waves != 4 || t.bk != 32 || t.nst != 4 || t.BM > 128 || t.BN > 128)) return false;  // the only kernels of those modes
@@ -588,13 +599,8 @@ void choose_tiling(Plan* pl, bool bk64_ok, int forced_bk) {
     pl->waves = bv->waves;
     pl->nst = bv->nst;
   }
-  a.nkt = (a.Kred + pl->bk - 1) / pl->bk;
-  a.tiles_m = (a.M + pl->BM - 1) / pl->BM;
-  a.tiles_n = (a.N + pl->BN - 1) / pl->BN;
-  a.kt_per_split = (a.nkt + bS - 1) / bS;
-  a.splits = (a.nkt + a.kt_per_split - 1) / a.kt_per_split;  // drop empty splits
-  a.d_tiles_mn = make_fastdiv((unsigned)(a.tiles_m * a.tiles_n));
-  a.d_tiles_n = make_fastdiv((unsigned)a.tiles_n);
+  pl->tuned = hit != nullptr;
+  set_tiles(pl, bS);
 }
 
 void finish_geometry(ConvGeom& g) {
@@ -662,8 +668,8 @@ void plan_text(const Plan& pl, char* buf, size_t n) {
            a.N, a.Kred, pl.fast ? "vector" : "element-wise", pl.BM, pl.BN, pl.bk, pl.fast ? pl.waves : 4,
            pl.fast ? pl.nst : 2, a.tiles_m, a.tiles_n,
            a.splits, a.kt_per_split, pl.packed ? ", 4-channel padded copy" : "",
-           pl.flat ? (pl.classes ? ", flattened taps, one launch per residue of the stride" : ", flattened taps")
-           : a.sc_on ? ", scatter epilogue" : pl.classes ? ", one launch per parity class of the stride" : pl.gen ? ", per-load tap arithmetic" : "");
+           pl.flat ? (pl.classes ? ", flattened taps, the residues of the stride in one launch" : ", flattened taps")
+           : a.sc_on ? ", scatter epilogue" : pl.classes ? ", the parity classes of the stride in one launch" : pl.gen ? ", per-load tap arithmetic" : "");
 }
 
 // whether strided multi-tap backward-data can run as one unit-stride launch per parity class: every class has a tap, and
@@ -730,6 +736,7 @@ int compute_plan(int op, const jz_conv_desc* d, Plan* pl) {
     pl->bytesA = 2 * ny; pl->bytesB = 2 * nx; pl->bytesD = 2 * nw;  // A = dy, B = x
   }
   a.sc_on = 0; a.sc_H = a.sc_W = 0; a.sc_sh = a.sc_sw = 1; a.sc_oh = a.sc_ow = 0; a.sc_fill = 0;
+  a.w_taps = d->R * d->S; a.w_tap0 = 0; a.w_tap_r = d->S; a.w_tap_s = 1;
   g.always_mask = 0;
   a.bw_linear = (op == JZ_BWD_WEIGHT && d->R == 1 && d->S == 1 && d->stride_h == 1 && d->stride_w == 1 && d->pad_h == 0 &&
                  d->pad_w == 0) ? 1 : 0;
@@ -791,9 +798,11 @@ int compute_plan(int op, const jz_conv_desc* d, Plan* pl) {
   pl->ws_bytes = pl->part_offset + part;
   // Strided multi-tap backward-data: input pixel (h, w) only meets the taps r = (h + ph) mod sh (+ sh, + 2 sh, ...) and
   // likewise along w, so the pixels of one parity class (h mod sh, w mod sw) form a unit-stride backward-data problem
-  // on the dy grid with the filter's taps of that class: sh * sw launches of the mask kernels that together do the
-  // useful multiply-adds only (the per-load variant fetches and masks every tap for every pixel: sh * sw times the work).
-  // Every class needs a tap (R >= sh, S >= sw); the class filters are packed into the workspace by one small launch.
+  // on the dy grid with the filter's taps of that class.  Together they do the useful multiply-adds only (the per-load
+  // variant fetches and masks every tap for every pixel: sh * sw times the work), and they run as one launch out of the
+  // filter where it lies.  Packing each class's filter into the workspace and one launch per class took five launches:
+  // 128, 256 and 512 channels at batch 24: 35, 43 and 68 us, now 17, 21 and 23.  Every class needs a tap (R >= sh, S >= sw).  The workspace size stays
+  // the filter's, although nothing is kept there any more: callers have sized theirs by it.
   pl->classes = pl->gen && op == JZ_BWD_DATA && has_classes(d);
   if (pl->classes) pl->ws_bytes = up256((size_t)nw * 2);
   pl->element_ws_bytes = pl->ws_bytes;
@@ -844,7 +853,6 @@ struct PlanCacheEntry {
   unsigned generation = 0;  // 0: empty
   int op = 0, rc = 0, ca = 0, cb = 0;
   jz_conv_desc d{};
-  size_t w_elems = 0;  // parity-class plans only
   Plan pl;
 };
 constexpr unsigned kPlanCacheSize = 256, kPlanCacheProbes = 4;
@@ -886,14 +894,13 @@ int make_plan(int op, const jz_conv_desc* d, Plan* pl) {
 }
 
 // One parity class (ca, cb) of a strided multi-tap backward-data layer as a plan of its own (see compute_plan).  base: the
-// layer's plan; w_off: where this class's packed filter starts in the workspace (elements); false: the class has no pixels.
-bool compute_class_plan(const jz_conv_desc* d, const Plan& base, int ca, int cb, Plan* pl, size_t* w_elems) {
+// layer's plan; false: the class has no pixels.
+bool compute_class_plan(const jz_conv_desc* d, const Plan& base, int ca, int cb, Plan* pl) {
   const int sh = d->stride_h, sw = d->stride_w;
   const int P = out_dim(d->H, d->pad_h, d->R, sh), Q = out_dim(d->W, d->pad_w, d->S, sw);
   const int Ha = (d->H - ca + sh - 1) / sh, Wb = (d->W - cb + sw - 1) / sw;     // pixels h = ca + sh i, w = cb + sw l
   const int r0 = (ca + d->pad_h) % sh, s0 = (cb + d->pad_w) % sw;               // first tap of the class
   const int Ra = (d->R - r0 + sh - 1) / sh, Sb = (d->S - s0 + sw - 1) / sw;     // taps r0 + sh j, s0 + sw i
-  *w_elems = (size_t)d->K * Ra * Sb * d->C;
   if (Ha <= 0 || Wb <= 0) return false;
   *pl = base;
   pl->gen = false;
@@ -907,52 +914,32 @@ bool compute_class_plan(const jz_conv_desc* d, const Plan& base, int ca, int cb,
   g.row_pitch = Q * d->K; g.pix_step = d->K; g.s_step = d->K;
   g.kvalid = 0;
   g.always_mask = 1;   // the class grid and the dy grid are not tied by the usual size formula
+  a.w_tap0 = r0 * d->S + s0; a.w_tap_r = sh * d->S; a.w_tap_s = sw;   // its taps among the filter's
   a.sc_on = 1; a.sc_H = d->H; a.sc_W = d->W; a.sc_sh = sh; a.sc_sw = sw; a.sc_oh = ca; a.sc_ow = cb; a.sc_fill = 0;
   a.bw_linear = 0;
   finish_geometry(g);
-  pl->bytesB = *w_elems * 2;
   pl->bk = 32;
   choose_tiling(pl, d->K % 64 == 0, 0);
+  if (!pl->tuned) {  // the classes run in one launch: one variant, chosen for all pixels and a class's share of the taps
+    Plan all = *pl;
+    all.args.M = d->N * d->H * d->W;
+    all.args.Kred = (d->R * d->S * d->K + sh * sw - 1) / (sh * sw);
+    all.args.g.R = d->R; all.args.g.S = d->S;
+    choose_tiling(&all, d->K % 64 == 0, 0, false);
+    pl->BM = all.BM; pl->BN = all.BN; pl->bk = all.bk; pl->waves = all.waves; pl->nst = all.nst;
+    set_tiles(pl, 1);
+  }
   pl->part_offset = 0;
   pl->ws_bytes = 0;
   return true;
 }
 
-bool make_class_plan(const jz_conv_desc* d, const Plan& base, int ca, int cb, Plan* pl, size_t* w_elems) {
+bool make_class_plan(const jz_conv_desc* d, const Plan& base, int ca, int cb, Plan* pl) {
   const PlanCacheEntry& e = cached_plan(JZ_BWD_DATA, *d, ca, cb, [&](PlanCacheEntry& n) {
-    n.rc = compute_class_plan(d, base, ca, cb, &n.pl, &n.w_elems) ? 1 : 0;
+    n.rc = compute_class_plan(d, base, ca, cb, &n.pl) ? 1 : 0;
   });
-  *w_elems = e.w_elems;
   if (e.rc) *pl = e.pl;
   return e.rc != 0;
-}
-
-// class filters: wp[class][k][j][i][c] = w[k][r0 + sh j][s0 + sw i][c], classes in (ca, cb) row-major order
-__global__ __launch_bounds__(256) void pack_class_filters(const unsigned short* __restrict__ w, unsigned short* __restrict__ wp,
-                                                          int K, int R, int S, int C, int sh, int sw, int ph, int pw) {
-  const long long n = (long long)K * R * S * C;
-  for (long long idx = (long long)blockIdx.x * 256 + threadIdx.x; idx < n; idx += (long long)gridDim.x * 256) {
-    const int c = (int)(idx % C);
-    long long t = idx / C;
-    const int s_ = (int)(t % S); t /= S;
-    const int r = (int)(t % R);
-    const int k = (int)(t / R);
-    // the class this tap belongs to: r = (ca + ph) mod sh  <=>  ca = (r - ph) mod sh
-    const int ca = ((r - ph) % sh + sh) % sh, cb = ((s_ - pw) % sw + sw) % sw;
-    const int r0 = (ca + ph) % sh, s0 = (cb + pw) % sw;
-    const int j = (r - r0) / sh, i = (s_ - s0) / sw;
-    // offset of the class: the filters of all classes before it
-    long long off = 0;
-    for (int a2 = 0; a2 < sh; ++a2)
-      for (int b2 = 0; b2 < sw; ++b2) {
-        if (a2 * sw + b2 >= ca * sw + cb) break;
-        const int rr = (a2 + ph) % sh, ss = (b2 + pw) % sw;
-        off += (long long)K * ((R - rr + sh - 1) / sh) * ((S - ss + sw - 1) / sw) * C;
-      }
-    const int Ra = (R - r0 + sh - 1) / sh, Sb = (S - s0 + sw - 1) / sw;
-    (void)Ra;
-    wp[off + (((long long)k * ((R - r0 + sh - 1) / sh) + j) * Sb + i) * C + c] = w[idx];
-  }
 }
 
 // slabs of rows whose sums a split reduction leaves (splitk_reduce_stats): at most 64, so that the normalization's apply pass
@@ -1009,34 +996,49 @@ int run(int op, const jz_conv_desc* d, const void* A, const void* B, void* D, vo
     return JZ_ERR_ALIAS;
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (pl.widen) return run_widened(op, d, pl, A, B, D, ws, ws_bytes, stream, sink);
-  if (pl.classes) {  // strided multi-tap backward-data: pack the class filters, then one unit-stride launch per class
-    unsigned short* wp = static_cast<unsigned short*>(ws);
-    const long long nwl = (long long)d->K * d->R * d->S * d->C;
-    const unsigned pgrid = (unsigned)((nwl + 255) / 256 < 2048 ? (nwl + 255) / 256 : 2048);
-    hipLaunchKernelGGL(pack_class_filters, dim3(pgrid), dim3(256), 0, st, static_cast<const unsigned short*>(B), wp, d->K, d->R, d->S,
-                       d->C, d->stride_h, d->stride_w, d->pad_h, d->pad_w);
-    if ((rc = jz::launch_status()) != JZ_OK) return rc;
-    size_t w_off = 0;
+  if (pl.classes) {
+    // strided multi-tap backward-data: the classes of one variant in launches of up to kGemmSet, those with the most taps first
+    // (the last workgroups to start are then the shortest)
+    Plan cps[kMaxClasses];
+    int n = 0;
     for (int ca = 0; ca < d->stride_h; ++ca)
-      for (int cb = 0; cb < d->stride_w; ++cb) {
-        Plan cp;
-        size_t w_elems = 0;
-        const bool any = make_class_plan(d, pl, ca, cb, &cp, &w_elems);
-        if (any) {
-          GemmArgs& c = cp.args;
+      for (int cb = 0; cb < d->stride_w; ++cb)
+        if (make_class_plan(d, pl, ca, cb, &cps[n])) {
+          GemmArgs& c = cps[n++].args;
           c.A = static_cast<const unsigned short*>(A);
-          c.B = wp + w_off;
+          c.B = static_cast<const unsigned short*>(B);
           c.D16 = static_cast<unsigned short*>(D);
           c.bytesA = (unsigned)pl.bytesA;
-          c.bytesB = (unsigned)(w_elems * 2);
+          c.bytesB = (unsigned)pl.bytesB;
           c.Dpart = nullptr;
           c.stats = nullptr;
           c.st_y = c.st_c = c.st_add = nullptr;
           c.st_mean = c.st_invstd = nullptr;
-          if ((rc = launch_bwd_data(cp, st)) != JZ_OK) return rc;
         }
-        w_off += w_elems;
+    int order[kMaxClasses];
+    for (int i = 0; i < n; ++i) order[i] = i;
+    std::stable_sort(order, order + n, [&](int x, int y) { return cps[x].args.Kred > cps[y].args.Kred; });
+    bool done[kMaxClasses] = {};
+    for (int i = 0; i < n; ++i) {
+      if (done[i]) continue;
+      const Plan& first = cps[order[i]];
+      GemmSet set;
+      int k = 0;
+      set.first[0] = 0;
+      for (int j = i; j < n && k < kGemmSet; ++j) {
+        const Plan& c = cps[order[j]];
+        if (done[j] || c.BM != first.BM || c.BN != first.BN || c.bk != first.bk || c.waves != first.waves || c.nst != first.nst) continue;
+        done[j] = true;
+        set.g[k] = c.args;
+        set.first[k + 1] = set.first[k] + (unsigned)c.args.tiles_m * (unsigned)c.args.tiles_n;
+        ++k;
       }
+      for (; k < kGemmSet; ++k) {
+        set.g[k] = set.g[0];
+        set.first[k + 1] = set.first[k];
+      }
+      if ((rc = launch_bwd_data(first, st, &set)) != JZ_OK) return rc;
+    }
     return JZ_OK;
   }
   GemmArgs& a = pl.args;
@@ -1240,8 +1242,7 @@ extern "C" int jz_conv2d_describe_plan(int op, const jz_conv_desc* desc, char* t
   if (rc != JZ_OK) return rc;
   if (pl.classes) {  // the launches of the parity classes: the first class stands for all (same filter shape up to a tap row / column)
     Plan cp;
-    size_t w_elems;
-    if (make_class_plan(desc, pl, 0, 0, &cp, &w_elems)) {
+    if (make_class_plan(desc, pl, 0, 0, &cp)) {
       cp.classes = true;
       cp.args.sc_on = 0;
       plan_text(cp, text, text_bytes);
@@ -1267,8 +1268,7 @@ extern "C" int jz_conv2d_tune_set(int op, const jz_conv_desc* desc, int tile_m, 
     for (int ca = 0; ca < desc->stride_h; ++ca)
       for (int cb = 0; cb < desc->stride_w; ++cb) {
         Plan cp;
-        size_t w_elems;
-        if (!make_class_plan(desc, pl, ca, cb, &cp, &w_elems)) continue;
+        if (!make_class_plan(desc, pl, ca, cb, &cp)) continue;
         const GemmArgs& a = cp.args;
         keys.push_back(Tuned{1, a.M, a.N, a.Kred, a.g.R * a.g.S, a.sc_on, tile_m, tile_n, k_tile, wavefronts, ring, 1});
       }

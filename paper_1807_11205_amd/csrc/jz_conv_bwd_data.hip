@@ -2,4 +2,4 @@
 // the operations compile in parallel).
 #include "jz_igemm_kernels.h"
 
-int jz::launch_bwd_data(const Plan& pl, hipStream_t st) { return launch_op<OP_BWD_DATA>(pl, st); }
+int jz::launch_bwd_data(const Plan& pl, hipStream_t st, const GemmSet* set) { return launch_op<OP_BWD_DATA>(pl, st, set); }

@@ -14,7 +14,7 @@ struct Plan {
   bool packed = false;  // small-channel layer run on a 4-channel padded copy
   bool gen = false;     // gather with per-load tap arithmetic (more than 32 taps, strided multi-tap backward-data)
   bool flat = false;    // reduction over the flattened (tap, channel) index: channel counts that are not multiples of the k tile
-  bool classes = false; // strided multi-tap backward-data as one unit-stride launch per parity class of the stride
+  bool classes = false; // strided multi-tap backward-data as one unit-stride problem per parity class of the stride
   bool stem = false;    // packed forward layer that runs on the patch kernel (jz_conv_stem.hip) unless column sums are asked for
   // widened channels: the layer runs as `wide` (channel counts rounded up to 8) on zero-extended copies of its operands in
   // the workspace, the result is copied back without the extra channels; ws_bytes covers it, element_ws_bytes is what
@@ -23,6 +23,7 @@ struct Plan {
   jz_conv_desc wide{};
   size_t wide_a_bytes = 0, wide_b_bytes = 0, wide_d_bytes = 0;  // the copies (0: that operand is used where it is)
   size_t element_ws_bytes = 0;
+  bool tuned = false;      // the variant comes from a table or from jz_conv2d_tune_set
   bool rt_forced = false;  // the variant comes from jz_conv2d_tune_set (the patch kernel then steps aside)
   int BM = 128, BN = 128;
   int bk = 64;  // k tile depth of the kernel that will run
@@ -58,7 +59,7 @@ int launch_fwd(const Plan& pl, hipStream_t st);
 int launch_fwd_stats(const Plan& pl, hipStream_t st);  // forward that also leaves per-tile column sums
 int launch_bwd_data_stats(const Plan& pl, hipStream_t st);  // backward-data that also leaves batch-norm backward sums
 int launch_bwd_data_block_end(const Plan& pl, hipStream_t st);  // ... of the block-end gradient it forms from its tile
-int launch_bwd_data(const Plan& pl, hipStream_t st);
+int launch_bwd_data(const Plan& pl, hipStream_t st, const GemmSet* set = nullptr);  // set: these GEMMs instead of the plan's own
 int launch_bwd_weight(const Plan& pl, hipStream_t st);
 
 }  // namespace jz

@@ -85,7 +85,16 @@ struct GemmArgs {
   int sc_on, sc_H, sc_W, sc_sh, sc_sw, sc_oh, sc_ow, sc_fill;
   // backward-weight of a 1x1 unit-stride unpadded layer: reduction row j (a pixel) of x starts at j * IC, no gather
   int bw_linear;
+  // backward-data: tap (r, s) of the launch is tap w_tap0 + r w_tap_r + s w_tap_s of the w_taps taps of a filter (a parity
+  // class of a stride has a subset of them)
+  int w_taps, w_tap0, w_tap_r, w_tap_s;
   ConvGeom g;
+};
+
+constexpr int kGemmSet = 4;
+struct GemmSet {
+  GemmArgs g[kGemmSet];
+  unsigned first[kGemmSet + 1];  // workgroup numbers of member k: first[k] .. first[k + 1] - 1
 };
 
 }  // namespace jz

@@ -79,7 +79,7 @@ __device__ __forceinline__ unsigned low_bits(int k) { return k >= 32 ? 0xfffffff
 __device__ __forceinline__ int clamp_to(int x, int hi) { return x < 0 ? 0 : (x > hi ? hi : x); }
 
 template <int OP_ARG, int BM, int BN, int TBK, int NST, bool MASKA = false, int WGM = 2, int WGN = 2, bool GEN = false, bool FLAT = false>
-__global__ __launch_bounds__(64 * WGM * WGN) void igemm_dma_kernel(GemmArgs a) {
+__device__ __forceinline__ void igemm_dma_body(const GemmArgs& a, unsigned block, unsigned blocks) {
   // the forward kernel with column sums in its epilogue (1), the backward-data kernel with batch-norm backward sums (2),
   // the same with the gradient of a residual block's end formed from the tile first (3)
   constexpr int STATS = OP_ARG == OP_FWD_STATS ? 1 : (OP_ARG == OP_BWD_DATA_STATS ? 2 : (OP_ARG == OP_BWD_DATA_BLOCK_END ? 3 : 0));
@@ -112,7 +112,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void igemm_dma_kernel(GemmArgs a) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WGN, wn = wave % WGN;
 
-  unsigned L = xcd_remap(blockIdx.x, gridDim.x);
+  unsigned L = xcd_remap(block, blocks);
   const int tiles_mn = a.tiles_m * a.tiles_n;
   const int split = (int)fd_div(L, a.d_tiles_mn);
   L -= (unsigned)split * (unsigned)tiles_mn;
@@ -265,7 +265,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void igemm_dma_kernel(GemmArgs a) {
     for (int ii = 0; ii < LB; ++ii) {
       int k = mc_k(BN, ii);
       int nn = n0 + mc_chunk(BN, k) * 8;
-      vB[ii] = nn < a.N ? (FLAT ? (unsigned)nn * 2u : (unsigned)((k * g.R * g.S) * a.N + nn) * 2u) : OOB;  // + (c0 * R * S + tap) * N * 2 per tile
+      vB[ii] = nn < a.N ? (FLAT ? (unsigned)nn * 2u : (unsigned)((k * a.w_taps) * a.N + nn) * 2u) : OOB;  // + (c0 * w_taps + tap) * N * 2 per tile
     }
   } else {
     // x gathered: this lane's 8 columns (tap, c..c+7) are the same for every load (k & 7 does not depend on ii)
@@ -353,7 +353,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void igemm_dma_kernel(GemmArgs a) {
       } else {
         c.soffA = (unsigned)((g.R - 1 - c.r) * g.row_pitch + (g.S - 1 - c.s) * g.pix_step + c.c0) * 2u;
       }
-      c.soffB = OP == OP_FWD ? (unsigned)c.k0 * 2u : (unsigned)((c.c0 * g.R * g.S + (int)c.tap) * a.N) * 2u;
+      c.soffB = OP == OP_FWD ? (unsigned)c.k0 * 2u
+                             : (unsigned)((c.c0 * a.w_taps + a.w_tap0 + c.r * a.w_tap_r + c.s * a.w_tap_s) * a.N) * 2u;
       c.rag = c.c0 + kc_chunk * 8 < g.IC ? 0u : OOB;
     } else {
       c.soffA = (unsigned)(c.k0 * a.M) * 2u;
@@ -401,7 +402,9 @@ __global__ __launch_bounds__(64 * WGM * WGN) void igemm_dma_kernel(GemmArgs a) {
           // row k of the tile is filter w[ko][tap][.]; (tap, ko) from the flattened index
           const unsigned kk = (unsigned)(c.k0 + mc_k(BN, ii));
           const unsigned tap = fd_div(kk, g.d_ic), ko = kk - tap * (unsigned)g.IC;
-          const unsigned off = (ko * (unsigned)(g.R * g.S) + tap) * (unsigned)a.N * 2u;
+          const unsigned r = fd_div(tap, g.d_s), sx = tap - r * (unsigned)g.S;
+          const unsigned wt = (unsigned)a.w_tap0 + r * (unsigned)a.w_tap_r + sx * (unsigned)a.w_tap_s;
+          const unsigned off = (ko * (unsigned)a.w_taps + wt) * (unsigned)a.N * 2u;
           jz_dma16(rsrcB, dst, kk < (unsigned)a.Kred && vB[ii] != OOB ? vB[ii] + off : OOB);
         } else if constexpr (OP == OP_BWD_DATA) {
           const bool ok = c.c0 + mc_k(BN, ii) < g.IC;
@@ -649,4 +652,18 @@ __global__ __launch_bounds__(64 * WGM * WGN) void igemm_dma_kernel(GemmArgs a) {
   constexpr int ring_bytes = NST * STAGE, epi_bytes = BM / dma_epass(BM, BN) * (BN + 8) * 2;
   igemm_epilogue_impl<BM, BN, TM, TN, NT, dma_epass(BM, BN), (ring_bytes > epi_bytes ? ring_bytes : epi_bytes), STATS>(
       a, acc, lds, m0, n0, split, tid, lane, wm * WTM, wn * WTN);
+}
+
+template <int OP, int BM, int BN, int TBK, int NST, bool MASKA = false, int WGM = 2, int WGN = 2, bool GEN = false, bool FLAT = false>
+__global__ __launch_bounds__(64 * WGM * WGN) void igemm_dma_kernel(GemmArgs a) {
+  igemm_dma_body<OP, BM, BN, TBK, NST, MASKA, WGM, WGN, GEN, FLAT>(a, blockIdx.x, gridDim.x);
+}
+
+// Several GEMMs of one variant in one launch: the parity classes of a strided backward-data layer, each of which alone is a
+// short launch that fills a part of the chip.
+template <int OP, int BM, int BN, int TBK, int NST, int WGM, int WGN, bool FLAT>
+__global__ __launch_bounds__(64 * WGM * WGN) void igemm_dma_set_kernel(GemmSet s) {
+  int k = 0;
+  while (k + 1 < kGemmSet && blockIdx.x >= s.first[k + 1]) ++k;
+  igemm_dma_body<OP, BM, BN, TBK, NST, false, WGM, WGN, false, FLAT>(s.g[k], blockIdx.x - s.first[k], s.first[k + 1] - s.first[k]);
 }

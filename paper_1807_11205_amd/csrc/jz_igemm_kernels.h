@@ -457,7 +457,7 @@ int launch_one(const GemmArgs& a, hipStream_t st) {
 }
 
 template <int OP, int BM, int BN, int TBK, int NST, bool MASKA = false, int WGM = 2, int WGN = 2, bool GEN = false, bool FLAT = false>
-int launch_dma(const GemmArgs& a, hipStream_t st) {
+int launch_dma(const GemmArgs& a, hipStream_t st, const GemmSet* set = nullptr) {
   constexpr size_t ring_bytes = (size_t)NST * (BM + BN) * 2 * TBK;
   constexpr size_t epi_bytes = (size_t)BM / dma_epass(BM, BN) * (BN + 8) * sizeof(unsigned short);
   constexpr size_t smem = ring_bytes > epi_bytes ? ring_bytes : epi_bytes;
@@ -469,13 +469,26 @@ int launch_dma(const GemmArgs& a, hipStream_t st) {
       return JZ_ERR_LAUNCH;
     attr_set = true;
   }
+  if constexpr (OP == OP_BWD_DATA && !GEN && !MASKA) {
+    if (set) {
+      static bool set_attr = false;
+      if (!set_attr) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void*>(&igemm_dma_set_kernel<OP, BM, BN, TBK, NST, WGM, WGN, FLAT>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) != hipSuccess)
+          return JZ_ERR_LAUNCH;
+        set_attr = true;
+      }
+      hipLaunchKernelGGL((igemm_dma_set_kernel<OP, BM, BN, TBK, NST, WGM, WGN, FLAT>), dim3(set->first[kGemmSet]), dim3(64 * WGM * WGN), smem, st, *set);
+      return jz::launch_status();
+    }
+  }
   unsigned grid = (unsigned)a.tiles_m * (unsigned)a.tiles_n * (unsigned)a.splits;
   hipLaunchKernelGGL((igemm_dma_kernel<OP, BM, BN, TBK, NST, MASKA, WGM, WGN, GEN, FLAT>), dim3(grid), dim3(64 * WGM * WGN), smem, st, a);
   return jz::launch_status();
 }
 
 template <int OP>
-int launch_op(const Plan& pl, hipStream_t st) {
+int launch_op(const Plan& pl, hipStream_t st, const GemmSet* set = nullptr) {
   const GemmArgs& a = pl.args;
   constexpr bool IS_FWD = OP == OP_FWD || OP == OP_FWD_STATS;
   if constexpr (OP == OP_FWD_STATS) {
@@ -514,36 +527,36 @@ int launch_op(const Plan& pl, hipStream_t st) {
   }
   if constexpr (OP == OP_FWD || OP == OP_BWD_DATA) {
     if (pl.flat) {  // flattened (tap, channel) reduction: the same four tiles
-      if (pl.BM == 128 && pl.BN == 128) return launch_dma<OP, 128, 128, 32, 4, false, 2, 2, false, true>(a, st);
-      if (pl.BM == 128 && pl.BN == 64) return launch_dma<OP, 128, 64, 32, 4, false, 2, 2, false, true>(a, st);
-      if (pl.BM == 64 && pl.BN == 128) return launch_dma<OP, 64, 128, 32, 4, false, 2, 2, false, true>(a, st);
-      return launch_dma<OP, 64, 64, 32, 4, false, 2, 2, false, true>(a, st);
+      if (pl.BM == 128 && pl.BN == 128) return launch_dma<OP, 128, 128, 32, 4, false, 2, 2, false, true>(a, st, set);
+      if (pl.BM == 128 && pl.BN == 64) return launch_dma<OP, 128, 64, 32, 4, false, 2, 2, false, true>(a, st, set);
+      if (pl.BM == 64 && pl.BN == 128) return launch_dma<OP, 64, 128, 32, 4, false, 2, 2, false, true>(a, st, set);
+      return launch_dma<OP, 64, 64, 32, 4, false, 2, 2, false, true>(a, st, set);
     }
   }
   // large tiles, one workgroup of 8 wavefronts per compute unit with (nearly) the whole LDS as its ring
-  if (pl.BM == 256 && pl.BN == 256 && pl.bk == 32) return launch_dma<OP, 256, 256, 32, 4, false, 2, 4>(a, st);  // 2x4 wavefronts of 128x64
-  if (pl.BM == 256 && pl.BN == 128 && pl.bk == 64) return launch_dma<OP, 256, 128, 64, 3, false, 4, 2>(a, st);
-  if (pl.BM == 128 && pl.BN == 128 && pl.bk == 64 && pl.waves == 8) return launch_dma<OP, 128, 128, 64, 4, false, 4, 2>(a, st);
-  if (pl.BM == 256 && pl.BN == 128 && pl.bk == 32 && pl.nst == 3) return launch_dma<OP, 256, 128, 32, 3, false, 4, 2>(a, st);
-  if (pl.BM == 256 && pl.BN == 128 && pl.bk == 32) return launch_dma<OP, 256, 128, 32, 4, false, 4, 2>(a, st);  // 4x2 wavefronts of 64x64
-  if (pl.BM == 128 && pl.BN == 128 && pl.bk == 32 && pl.waves == 8 && pl.nst == 3) return launch_dma<OP, 128, 128, 32, 3, false, 4, 2>(a, st);
-  if (pl.BM == 128 && pl.BN == 128 && pl.bk == 32 && pl.waves == 8) return launch_dma<OP, 128, 128, 32, 4, false, 4, 2>(a, st);
+  if (pl.BM == 256 && pl.BN == 256 && pl.bk == 32) return launch_dma<OP, 256, 256, 32, 4, false, 2, 4>(a, st, set);  // 2x4 wavefronts of 128x64
+  if (pl.BM == 256 && pl.BN == 128 && pl.bk == 64) return launch_dma<OP, 256, 128, 64, 3, false, 4, 2>(a, st, set);
+  if (pl.BM == 128 && pl.BN == 128 && pl.bk == 64 && pl.waves == 8) return launch_dma<OP, 128, 128, 64, 4, false, 4, 2>(a, st, set);
+  if (pl.BM == 256 && pl.BN == 128 && pl.bk == 32 && pl.nst == 3) return launch_dma<OP, 256, 128, 32, 3, false, 4, 2>(a, st, set);
+  if (pl.BM == 256 && pl.BN == 128 && pl.bk == 32) return launch_dma<OP, 256, 128, 32, 4, false, 4, 2>(a, st, set);  // 4x2 wavefronts of 64x64
+  if (pl.BM == 128 && pl.BN == 128 && pl.bk == 32 && pl.waves == 8 && pl.nst == 3) return launch_dma<OP, 128, 128, 32, 3, false, 4, 2>(a, st, set);
+  if (pl.BM == 128 && pl.BN == 128 && pl.bk == 32 && pl.waves == 8) return launch_dma<OP, 128, 128, 32, 4, false, 4, 2>(a, st, set);
   if (pl.bk == 64) {
-    if (pl.BM == 128 && pl.BN == 128) return launch_dma<OP, 128, 128, 64, 4>(a, st);
-    if (pl.BM == 128 && pl.BN == 64) return launch_dma<OP, 128, 64, 64, 4>(a, st);
-    if (pl.BM == 64 && pl.BN == 128) return launch_dma<OP, 64, 128, 64, 4>(a, st);
-    return launch_dma<OP, 64, 64, 64, 4>(a, st);
+    if (pl.BM == 128 && pl.BN == 128) return launch_dma<OP, 128, 128, 64, 4>(a, st, set);
+    if (pl.BM == 128 && pl.BN == 64) return launch_dma<OP, 128, 64, 64, 4>(a, st, set);
+    if (pl.BM == 64 && pl.BN == 128) return launch_dma<OP, 64, 128, 64, 4>(a, st, set);
+    return launch_dma<OP, 64, 64, 64, 4>(a, st, set);
   }
   if (pl.nst == 3) {
-    if (pl.BM == 128 && pl.BN == 128) return launch_dma<OP, 128, 128, 32, 3>(a, st);
-    if (pl.BM == 128 && pl.BN == 64) return launch_dma<OP, 128, 64, 32, 3>(a, st);
-    if (pl.BM == 64 && pl.BN == 128) return launch_dma<OP, 64, 128, 32, 3>(a, st);
-    return launch_dma<OP, 64, 64, 32, 3>(a, st);
+    if (pl.BM == 128 && pl.BN == 128) return launch_dma<OP, 128, 128, 32, 3>(a, st, set);
+    if (pl.BM == 128 && pl.BN == 64) return launch_dma<OP, 128, 64, 32, 3>(a, st, set);
+    if (pl.BM == 64 && pl.BN == 128) return launch_dma<OP, 64, 128, 32, 3>(a, st, set);
+    return launch_dma<OP, 64, 64, 32, 3>(a, st, set);
   }
-  if (pl.BM == 128 && pl.BN == 128) return launch_dma<OP, 128, 128, 32, 4>(a, st);
-  if (pl.BM == 128 && pl.BN == 64) return launch_dma<OP, 128, 64, 32, 4>(a, st);
-  if (pl.BM == 64 && pl.BN == 128) return launch_dma<OP, 64, 128, 32, 4>(a, st);
-  return launch_dma<OP, 64, 64, 32, 4>(a, st);
+  if (pl.BM == 128 && pl.BN == 128) return launch_dma<OP, 128, 128, 32, 4>(a, st, set);
+  if (pl.BM == 128 && pl.BN == 64) return launch_dma<OP, 128, 64, 32, 4>(a, st, set);
+  if (pl.BM == 64 && pl.BN == 128) return launch_dma<OP, 64, 128, 32, 4>(a, st, set);
+  return launch_dma<OP, 64, 64, 32, 4>(a, st, set);
 }
 
 }  // namespace
