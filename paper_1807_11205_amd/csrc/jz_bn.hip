@@ -100,6 +100,17 @@ __device__ __forceinline__ uint4 pack8(const float (&f)[8]) {
   return make_uint4(w[0], w[1], w[2], w[3]);
 }
 
+// A result of the passes over large tensors goes out with the non-temporal hint: written back while the pass that makes it
+// reads out of the last-level cache and memory is idle, instead of during the next pass, which does read from memory and
+// slowed down to 3.3-4.3 TB/s beside the write-back.  ResNet-50's 53 layers forward and backward, batch 64: 3.52 -> 3.17 ms
+// (statistics passes 1.66 -> 1.35 ms, the apply passes the same); the training step, where a convolution reads the result
+// next, is neither faster nor slower.
+__device__ __forceinline__ void store_streaming(uint4* p, const uint4& v) {
+  typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
+  const u32x4_t t = {v.x, v.y, v.z, v.w};
+  __builtin_nontemporal_store(t, reinterpret_cast<u32x4_t*>(p));
+}
+
 // Sums over a slab of rows, for the 8 channels of each lane: s0 and s1 are whatever `term` produces per element.
 // The rpp lanes that share a channel chunk (one per row of a pass) are then added in row order through LDS, and the
 // slab's 2 x C sums are stored.  MODE 0: (x, x^2).  MODE 1: (g, g x^) with g = dy [* (y > 0)].  MODE 2: the end of a
@@ -311,7 +322,7 @@ __global__ __launch_bounds__(BN_THREADS) void bn_apply(const uint4* __restrict__
       if (RES) z += rv[e];
       v[e] = (relu && !(z > 0.f)) ? 0.f : z;
     }
-    y[i] = pack8(v);
+    store_streaming(y + i, pack8(v));
   }
 }
 
@@ -366,7 +377,7 @@ __global__ __launch_bounds__(BN_THREADS) void bn_bwd_apply(const uint4* __restri
     }
 #pragma unroll
     for (int e = 0; e < 8; ++e) out[e] = a[e] * gv[e] + (pc[e] * xv[e] + qc[e]);
-    dx[i] = pack8(out);
+    store_streaming(dx + i, pack8(out));
   }
 }
 
