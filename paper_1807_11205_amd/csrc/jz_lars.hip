@@ -234,41 +234,27 @@ __device__ __forceinline__ void chunk_range(const ChunkRec& r, int* t_out, int64
 
 constexpr int LARS_IT = LARS_CH / (LARS_THREADS * 8);  // 8-element groups per thread and chunk
 
-// 16-byte accesses of the update pass.  Non-temporal variants (JZ_LARS_NT) were measured slower on MI355X (the
-// last-level cache then no longer serves the gradient the reduce pass just read), so plain accesses are the default.
+// 16-byte accesses of the update pass.  What it writes (w, v, the FP16 copy: 20 of 28 bytes an element) goes out with the
+// non-temporal hint, or dirty lines of it are still being written back while the next pass reads: one update of ResNet-50
+// 114 -> 109 us, AlexNet 274 -> 262 us.  The gradient, which the reduce pass has just read, is in the last-level cache: plain
+// loads.  So is a part of the state when it fits there (204 MB for ResNet-50: 93 us for updates in a row, 108 with the hint);
+// state that does not fit only displaces the gradient and is read with the hint (STREAM; AlexNet 261 -> 253 us).
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ float4 load_stream_f4(const float* p) {
-#ifndef JZ_LARS_NT
-  return *reinterpret_cast<const float4*>(p);
-#else
+constexpr int64_t LARS_STREAM_ELEMENTS = (256ll << 20) / 8;  // 8 bytes of state an element against 256 MiB of last-level cache
+template <bool STREAM>
+__device__ __forceinline__ float4 load_state_f4(const float* p) {
+  if constexpr (!STREAM) return *reinterpret_cast<const float4*>(p);
   f32x4_t t = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(p));
   return make_float4(t.x, t.y, t.z, t.w);
-#endif
-}
-__device__ __forceinline__ uint4 load_stream_u4(const unsigned short* p) {
-#ifndef JZ_LARS_NT
-  return *reinterpret_cast<const uint4*>(p);
-#else
-  u32x4_t t = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(p));
-  return make_uint4(t.x, t.y, t.z, t.w);
-#endif
 }
 __device__ __forceinline__ void store_stream_f4(float* p, float a, float b, float c, float d) {
-#ifndef JZ_LARS_NT
-  *reinterpret_cast<float4*>(p) = make_float4(a, b, c, d);
-#else
   f32x4_t t = {a, b, c, d};
   __builtin_nontemporal_store(t, reinterpret_cast<f32x4_t*>(p));
-#endif
 }
 __device__ __forceinline__ void store_stream_u4(unsigned short* p, unsigned a, unsigned b, unsigned c, unsigned d) {
-#ifndef JZ_LARS_NT
-  *reinterpret_cast<uint4*>(p) = make_uint4(a, b, c, d);
-#else
   u32x4_t t = {a, b, c, d};
   __builtin_nontemporal_store(t, reinterpret_cast<u32x4_t*>(p));
-#endif
 }
 
 // the 8-aligned body [b0,b1) of a chunk [s,e); the rest is at most 7 head and 7 tail elements
@@ -523,6 +509,7 @@ __device__ __forceinline__ void lars_step(float& w, float& v, unsigned short gbi
 }
 
 // One thread's share (tid of LARS_THREADS) of a chunk's update; returns its share of the sum of squares of the new weights.
+template <bool STREAM>
 __device__ __forceinline__ double update_chunk(const ChunkRec& rec, int tid, float* __restrict__ w, float* __restrict__ v,
                                                const unsigned short* __restrict__ g16, unsigned short* __restrict__ w16, float coef,
                                                float lam, float m, float inv_s) {
@@ -536,11 +523,11 @@ __device__ __forceinline__ double update_chunk(const ChunkRec& rec, int tid, flo
   for (int k = 0; k < LARS_IT; ++k) {  // every load of the chunk is in flight before the first use
     int64_t i = b0 + (int64_t)(k * LARS_THREADS + tid) * 8;
     if (i < b1) {
-      gq[k] = load_stream_u4(g16 + i);
-      w0[k] = load_stream_f4(w + i);
-      w1[k] = load_stream_f4(w + i + 4);
-      v0[k] = load_stream_f4(v + i);
-      v1[k] = load_stream_f4(v + i + 4);
+      gq[k] = *reinterpret_cast<const uint4*>(g16 + i);
+      w0[k] = load_state_f4<STREAM>(w + i);
+      w1[k] = load_state_f4<STREAM>(w + i + 4);
+      v0[k] = load_state_f4<STREAM>(v + i);
+      v1[k] = load_state_f4<STREAM>(v + i + 4);
     }
   }
   double sw = 0.0;  // sum of squares of the new weights, in the order lars_reduce would add them
@@ -587,7 +574,7 @@ __device__ __forceinline__ double update_chunk(const ChunkRec& rec, int tid, flo
 
 // PRE: the presummed path -- no lars_finalize ran; every wavefront forms its tensor's lr*rho_t itself (lr, eta and, for a
 // fixed loss scale, S come as arguments) and the overflow flags are those of the sinks.
-template <bool PRE>
+template <bool PRE, bool STREAM>
 __global__ __launch_bounds__(LARS_THREADS) void lars_update(Tables tb, float* __restrict__ w, float* __restrict__ v,
                                                             const unsigned short* __restrict__ g16,
                                                             unsigned short* __restrict__ w16, float m, float wd,
@@ -648,7 +635,7 @@ __global__ __launch_bounds__(LARS_THREADS) void lars_update(Tables tb, float* __
     coef = tb.coef[t];
   }
   const float lam = (tb.flags[t] & JZ_PARAM_WEIGHT_DECAY) ? wd : 0.0f;
-  const double sw = wave_sum(update_chunk(rec, threadIdx.x, w, v, g16, w16, coef, lam, m, inv_s));
+  const double sw = wave_sum(update_chunk<STREAM>(rec, threadIdx.x, w, v, g16, w16, coef, lam, m, inv_s));
   if ((threadIdx.x & 63) == 0) tb.psum_w[(size_t)c * LARS_WAVES + (threadIdx.x >> 6)] = sw;
 }
 
@@ -708,7 +695,7 @@ __global__ __launch_bounds__(1024) void lars_small(Tables tb, float* __restrict_
   for (int c = group; c < tb.n_chunks; c += 1024 / LARS_THREADS) {
     const ChunkRec rec = tb.chunk_rec[c];
     const float lam = (tb.flags[rec.tensor] & JZ_PARAM_WEIGHT_DECAY) ? wd : 0.0f;
-    const double sw = wave_sum(update_chunk(rec, tid, w, v, g16, w16, coef[rec.tensor], lam, m, inv_s));
+    const double sw = wave_sum(update_chunk<false>(rec, tid, w, v, g16, w16, coef[rec.tensor], lam, m, inv_s));
     if ((tid & 63) == 0) tb.psum_w[(size_t)c * LARS_WAVES + (tid >> 6)] = sw;
   }
 }
@@ -850,8 +837,8 @@ int lars_run(const jz_param_set* ps, const jz_lars_hparams* hp, const jz_loss_sc
   if (state) dyn = DynScale{state, pol->growth_factor, pol->backoff_factor, pol->growth_interval, pol->min_scale, pol->max_scale};
   if (presummed) {
     set_begun(ws, false, nullptr);
-    hipLaunchKernelGGL(lars_update<true>, dim3((unsigned)(L.n_chunks > 0 ? L.n_chunks : 1)), dim3(LARS_THREADS), 0, st, tb,
-                       ps->master_w, ps->momentum, g16, static_cast<unsigned short*>(ps->weight16), hp->momentum,
+    hipLaunchKernelGGL((L.P > LARS_STREAM_ELEMENTS ? lars_update<true, true> : lars_update<true, false>),
+                       dim3((unsigned)(L.n_chunks > 0 ? L.n_chunks : 1)), dim3(LARS_THREADS), 0, st, tb, ps->master_w, ps->momentum, g16, static_cast<unsigned short*>(ps->weight16), hp->momentum,
                        hp->weight_decay, state ? 1.0f : 1.0f / hp->loss_scale, found_inf_dev, dyn, hp->lr, hp->trust_coef,
                        state ? 1.0f : hp->loss_scale);
     return jz::launch_status();
@@ -871,8 +858,8 @@ int lars_run(const jz_param_set* ps, const jz_lars_hparams* hp, const jz_loss_sc
     hipLaunchKernelGGL(lars_finalize<1024>, dim3((unsigned)L.T), dim3(1024), 0, st, tb, hp->lr, hp->trust_coef,
                        state ? 1.0f : hp->loss_scale, scale_dev);
   // at least one workgroup so that the flag is always written
-  hipLaunchKernelGGL(lars_update<false>, dim3((unsigned)(L.n_chunks > 0 ? L.n_chunks : 1)), dim3(LARS_THREADS), 0, st, tb,
-                     ps->master_w, ps->momentum, g16, static_cast<unsigned short*>(ps->weight16), hp->momentum,
+  hipLaunchKernelGGL((L.P > LARS_STREAM_ELEMENTS ? lars_update<false, true> : lars_update<false, false>),
+                     dim3((unsigned)(L.n_chunks > 0 ? L.n_chunks : 1)), dim3(LARS_THREADS), 0, st, tb, ps->master_w, ps->momentum, g16, static_cast<unsigned short*>(ps->weight16), hp->momentum,
                      hp->weight_decay, state ? 1.0f : 1.0f / hp->loss_scale, found_inf_dev, dyn, 0.0f, 0.0f, 1.0f);
   return jz::launch_status();
 }
