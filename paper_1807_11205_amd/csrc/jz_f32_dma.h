@@ -442,7 +442,11 @@ __device__ __forceinline__ void f32_dma_body(const F32Args& a, unsigned block, u
       }
       const float4 v = *reinterpret_cast<const float4*>(lds_f + row * LDF + fch * 4);
       float* dst = out + drow * a.N + n;
-      if (vec) {
+      if (vec && whole) {  // non-temporal: written back at once, not while the next launch reads (partial sums are read at once)
+        typedef float f32x4_t __attribute__((ext_vector_type(4)));
+        const f32x4_t t = {v.x, v.y, v.z, v.w};
+        __builtin_nontemporal_store(t, reinterpret_cast<f32x4_t*>(dst));
+      } else if (vec) {
         *reinterpret_cast<float4*>(dst) = v;
       } else {
         const float e[4] = {v.x, v.y, v.z, v.w};
