@@ -19,7 +19,8 @@
 //                  which the next update's reduce pass then need not read w for.
 //
 // A set of at most LARS_SMALL_CHUNKS chunks is one launch of one workgroup (lars_small): three launches are 13 us of
-// latency whatever they do.
+// latency whatever they do.  Up to LARS_MERGED_CHUNKS chunks there are two: every workgroup of the update adds up its tensor's
+// chunk sums itself (lars_update<LARS_MERGED>), which costs it less than the finalize launch costs the stream.
 //
 // When the kernels that produce the gradients also leave each tensor's sum of squares (jz_sumsq.h), the first two
 // launches have nothing left to do at update time and the update is one launch ("presummed"):
@@ -28,7 +29,7 @@
 //                    (or, for a fresh workspace, squares the tensor itself), clears the tensor's gradient sink
 //   lars_grad_sumsq  the reduce pass for the tensors no other kernel covers (batch-norm scale / shift, bias), any time
 //                    after their gradients exist
-//   lars_update<true>  every wavefront forms lr*rho_t of its chunk's tensor itself from the sink and the sum lars_begin
+//   lars_update<LARS_PRE>  every wavefront forms lr*rho_t of its chunk's tensor itself from the sink and the sum lars_begin
 //                    left; otherwise the same kernel
 #include <hip/hip_runtime.h>
 
@@ -49,6 +50,10 @@ constexpr int LARS_WAVES = LARS_THREADS / 64;
 constexpr int LARS_FIN_BATCH = 10;       // chunk sums a thread of the finalize kernel requests together
 constexpr int LARS_SMALL_CHUNKS = 4;     // largest set lars_small takes: one chunk per group of threads (18 chunks: 37 us) ...
 constexpr int LARS_SMALL_T = 64;         // ... and this many tensors
+// Largest set whose update works out its rates itself: a chunk's sums for every thread.  Saves the finalize launch (3.0-4.6 us)
+// where a launch costs as much as the work: the three passes and the update of one 3x3 layer 32.7 -> 30.9 us, of a block 181 -> 176.
+constexpr int LARS_MERGED_CHUNKS = LARS_THREADS;
+enum { LARS_PLAIN = 0, LARS_PRE = 1, LARS_MERGED = 2 };  // where lars_update takes a tensor's rate from
 constexpr uint64_t LARS_MAGIC = 0x4a5a4c4152533031ull;  // "JZLARS01"
 
 // Everything a workgroup needs to know about its chunk in one 16-byte record: a kernel's first loads then depend on
@@ -66,7 +71,7 @@ struct Layout {
   size_t off_state = 0;
   size_t static_bytes = 0;  // everything up to here is written by prepare
   size_t off_psum_w = 0, off_psum_g = 0, off_coef = 0, off_tflag = 0;
-  size_t off_gsum = 0, off_gflag = 0, off_wsum = 0, total = 0;  // presummed path: gradient sinks, their flags, sum of w^2
+  size_t off_gsum = 0, off_gflag = 0, off_wsum = 0, off_psum_w_before = 0, total = 0;  // presummed path: gradient sinks, their flags, sum of w^2
 };
 
 size_t up256(size_t x) { return (x + 255) & ~size_t(255); }
@@ -108,6 +113,7 @@ int make_layout(const jz_param_set* ps, Layout* L) {
   L->off_gsum = o;          o = up256(o + jz::kSumsqSinkBytes * (L->T ? L->T : 1));
   L->off_gflag = o;         o = up256(o + sizeof(int) * (L->T ? L->T : 1));
   L->off_wsum = o;          o = up256(o + sizeof(double) * (L->T ? L->T : 1));
+  L->off_psum_w_before = o; o = up256(o + (L->n_chunks <= LARS_MERGED_CHUNKS ? sizeof(double) * LARS_WAVES * L->n_chunks : 0));
   L->total = o;
   return JZ_OK;
 }
@@ -178,6 +184,7 @@ struct Tables {
   unsigned long long* gsum;  // [T][kSumsqSubs * kSumsqSubStride]: gradient sum-of-squares sinks
   int* gflag;                // [T]: non-finite gradient reported to the sink
   double* wsum;              // [T]: sum of squares of the master weights, written by lars_begin
+  double* psum_w_before;     // psum_w as the update found it (sets of at most LARS_MERGED_CHUNKS chunks)
   int T, n_chunks;
   uint64_t checksum;
 };
@@ -332,18 +339,29 @@ __device__ __forceinline__ double chunk_thread_sumsq_g(const ChunkGrads& r) {
 }
 __device__ __forceinline__ bool sum_overflowed(double sg) { return !(sg <= 1.7e308); }  // Inf or NaN
 
+// MERGED: the update works out the rates itself (lars_update<LARS_MERGED>): it also finds the weights' sums where it does not
+// overwrite them, and the device-resident loss scale where it does not adjust it.
+template <bool MERGED>
 __global__ __launch_bounds__(LARS_THREADS) void lars_reduce(Tables tb, const float* __restrict__ w,
-                                                            const unsigned short* __restrict__ g16) {
+                                                            const unsigned short* __restrict__ g16, const float* __restrict__ scale_dev) {
   __shared__ double red[LARS_WAVES];
   const int c = blockIdx.x;
   const ChunkRec rec = tb.chunk_rec[c];  // requested together with the header: garbage if the header is, but then unused
   const bool have_w = tb.state[0] != 0;  // written by the previous update, i.e. by an earlier launch
   if (!table_ok(tb)) return;
   const double sg = wave_sum(chunk_thread_sumsq_g(load_chunk_grads(rec, g16, threadIdx.x)));
-  const double sw = have_w ? 0.0 : wave_sum(chunk_thread_sumsq_w(rec, w, threadIdx.x));
+  double sw = have_w ? 0.0 : wave_sum(chunk_thread_sumsq_w(rec, w, threadIdx.x));
   if ((threadIdx.x & 63) == 0) {
     red[threadIdx.x >> 6] = sg;
-    if (!have_w) tb.psum_w[(size_t)c * LARS_WAVES + (threadIdx.x >> 6)] = sw;
+    double* const pw = tb.psum_w + (size_t)c * LARS_WAVES + (threadIdx.x >> 6);
+    if (!have_w) *pw = sw;
+    else if (MERGED) sw = *pw;
+    if (MERGED) tb.psum_w_before[(size_t)c * LARS_WAVES + (threadIdx.x >> 6)] = sw;
+  }
+  if (MERGED && scale_dev && c == 0 && threadIdx.x == 0) {
+    const float scale = *scale_dev;
+    tb.state[1] = __float_as_int(1.0f / scale);
+    tb.state[2] = __float_as_int(scale);
   }
   lds_barrier();
   if (threadIdx.x == 0) tb.psum_g[c] = ((red[0] + red[1]) + red[2]) + red[3];
@@ -574,22 +592,36 @@ __device__ __forceinline__ double update_chunk(const ChunkRec& rec, int tid, flo
 
 // PRE: the presummed path -- no lars_finalize ran; every wavefront forms its tensor's lr*rho_t itself (lr, eta and, for a
 // fixed loss scale, S come as arguments) and the overflow flags are those of the sinks.
-template <bool PRE, bool STREAM>
+template <int MODE, bool STREAM>
 __global__ __launch_bounds__(LARS_THREADS) void lars_update(Tables tb, float* __restrict__ w, float* __restrict__ v,
                                                             const unsigned short* __restrict__ g16,
                                                             unsigned short* __restrict__ w16, float m, float wd,
                                                             float inv_s, int* __restrict__ found_inf, DynScale dyn,
                                                             float lr, float eta, float loss_scale) {
-  if (dyn.st) {  // written by lars_finalize / lars_begin (not used when there is no tensor)
+  constexpr bool PRE = MODE == LARS_PRE;
+  if (dyn.st) {  // written by lars_finalize / lars_begin / lars_reduce (not used when there is no tensor)
     inv_s = __int_as_float(tb.state[1]);
-    if (PRE) loss_scale = __int_as_float(tb.state[2]);
+    if (MODE != LARS_PLAIN) loss_scale = __int_as_float(tb.state[2]);
   }
   // the header, this workgroup's chunk record and the tensor flags are requested together; nothing read through the
   // tables is used before the header has been checked
   const int cidx = (int)blockIdx.x < tb.n_chunks ? tb.n_chunks - 1 - (int)blockIdx.x : 0;
   const ChunkRec rec = tb.n_chunks > 0 ? tb.chunk_rec[cidx] : ChunkRec{0, 0, 0};
   int f = 0;  // every wavefront looks at all tensor flags itself
-  for (int t = threadIdx.x & 63; t < tb.T; t += 64) f |= PRE ? tb.gflag[t] : tb.tflag[t];
+  double mw = 0.0, mg = 0.0;
+  __shared__ double red[LARS_WAVES];
+  if constexpr (MODE == LARS_MERGED) {  // a chunk per thread: is any gradient not finite, and what the chunk adds to its tensor's sums
+    const int i = threadIdx.x;
+    if (i < tb.n_chunks) {
+      const double g = tb.psum_g[i];
+      const int ti = tb.chunk_tensor[i];
+      f = sum_overflowed(g) ? 1 : 0;
+      if (ti == rec.tensor) { mg = g; mw = chunk_sumsq_w(tb.psum_w_before, i); }
+    }
+    f = __syncthreads_or(f);
+  } else {
+    for (int t = threadIdx.x & 63; t < tb.T; t += 64) f |= PRE ? tb.gflag[t] : tb.tflag[t];
+  }
   // PRE: this lane's share of the tensor's gradient sink (the tensor index is garbage if the header is: clamp it)
   // the first wavefront reads the sink (one quadruple per lane) and hands the total to the others through LDS
   __shared__ double sg_shared;
@@ -631,6 +663,10 @@ __global__ __launch_bounds__(LARS_THREADS) void lars_update(Tables tb, float* __
     }
     __syncthreads();  // every wavefront of the workgroup is here: the returns above depend on nothing wave-specific
     coef = lars_rate(tb.flags[t], sw_t, sg_shared, lr, eta, loss_scale);
+  } else if (MODE == LARS_MERGED) {
+    mw = block_sum<LARS_WAVES>(mw, red);
+    mg = block_sum<LARS_WAVES>(mg, red);
+    coef = lars_rate(tb.flags[t], mw, mg, lr, eta, loss_scale);
   } else {
     coef = tb.coef[t];
   }
@@ -724,6 +760,7 @@ Tables make_tables(const Layout& L, void* ws, uint64_t sum) {
   tb.gsum = reinterpret_cast<unsigned long long*>(b + L.off_gsum);
   tb.gflag = reinterpret_cast<int*>(b + L.off_gflag);
   tb.wsum = reinterpret_cast<double*>(b + L.off_wsum);
+  tb.psum_w_before = reinterpret_cast<double*>(b + L.off_psum_w_before);
   tb.T = (int)L.T;
   tb.n_chunks = (int)L.n_chunks;
   tb.checksum = sum;
@@ -837,7 +874,7 @@ int lars_run(const jz_param_set* ps, const jz_lars_hparams* hp, const jz_loss_sc
   if (state) dyn = DynScale{state, pol->growth_factor, pol->backoff_factor, pol->growth_interval, pol->min_scale, pol->max_scale};
   if (presummed) {
     set_begun(ws, false, nullptr);
-    hipLaunchKernelGGL((L.P > LARS_STREAM_ELEMENTS ? lars_update<true, true> : lars_update<true, false>),
+    hipLaunchKernelGGL((L.P > LARS_STREAM_ELEMENTS ? lars_update<LARS_PRE, true> : lars_update<LARS_PRE, false>),
                        dim3((unsigned)(L.n_chunks > 0 ? L.n_chunks : 1)), dim3(LARS_THREADS), 0, st, tb, ps->master_w, ps->momentum, g16, static_cast<unsigned short*>(ps->weight16), hp->momentum,
                        hp->weight_decay, state ? 1.0f : 1.0f / hp->loss_scale, found_inf_dev, dyn, hp->lr, hp->trust_coef,
                        state ? 1.0f : hp->loss_scale);
@@ -849,8 +886,15 @@ int lars_run(const jz_param_set* ps, const jz_lars_hparams* hp, const jz_loss_sc
                        found_inf_dev, dyn, hp->lr, hp->trust_coef, state ? 1.0f : hp->loss_scale);
     return jz::launch_status();
   }
+  if (L.n_chunks > 0 && L.n_chunks <= LARS_MERGED_CHUNKS) {
+    hipLaunchKernelGGL(lars_reduce<true>, dim3((unsigned)L.n_chunks), dim3(LARS_THREADS), 0, st, tb, ps->master_w, g16, scale_dev);
+    hipLaunchKernelGGL((lars_update<LARS_MERGED, false>), dim3((unsigned)L.n_chunks), dim3(LARS_THREADS), 0, st, tb, ps->master_w,
+                       ps->momentum, g16, static_cast<unsigned short*>(ps->weight16), hp->momentum, hp->weight_decay,
+                       state ? 1.0f : 1.0f / hp->loss_scale, found_inf_dev, dyn, hp->lr, hp->trust_coef, state ? 1.0f : hp->loss_scale);
+    return jz::launch_status();
+  }
   if (L.n_chunks > 0)
-    hipLaunchKernelGGL(lars_reduce, dim3((unsigned)L.n_chunks), dim3(LARS_THREADS), 0, st, tb, ps->master_w, g16);
+    hipLaunchKernelGGL(lars_reduce<false>, dim3((unsigned)L.n_chunks), dim3(LARS_THREADS), 0, st, tb, ps->master_w, g16, nullptr);
   if (L.T > 0 && L.most_chunks <= 256 * LARS_FIN_BATCH)
     hipLaunchKernelGGL(lars_finalize<256>, dim3((unsigned)L.T), dim3(256), 0, st, tb, hp->lr, hp->trust_coef,
                        state ? 1.0f : hp->loss_scale, scale_dev);
@@ -858,7 +902,7 @@ int lars_run(const jz_param_set* ps, const jz_lars_hparams* hp, const jz_loss_sc
     hipLaunchKernelGGL(lars_finalize<1024>, dim3((unsigned)L.T), dim3(1024), 0, st, tb, hp->lr, hp->trust_coef,
                        state ? 1.0f : hp->loss_scale, scale_dev);
   // at least one workgroup so that the flag is always written
-  hipLaunchKernelGGL((L.P > LARS_STREAM_ELEMENTS ? lars_update<false, true> : lars_update<false, false>),
+  hipLaunchKernelGGL((L.P > LARS_STREAM_ELEMENTS ? lars_update<LARS_PLAIN, true> : lars_update<LARS_PLAIN, false>),
                      dim3((unsigned)(L.n_chunks > 0 ? L.n_chunks : 1)), dim3(LARS_THREADS), 0, st, tb, ps->master_w, ps->momentum, g16, static_cast<unsigned short*>(ps->weight16), hp->momentum,
                      hp->weight_decay, state ? 1.0f : 1.0f / hp->loss_scale, found_inf_dev, dyn, 0.0f, 0.0f, 1.0f);
   return jz::launch_status();
