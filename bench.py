@@ -762,9 +762,6 @@ def main():
         sys.exit(2)
     api.lib()
     torch.cuda.set_device(0)
-    if args.plans_digest:
-        print(plans_digest(ResNet50Step(batch=args.batch or 64)))
-        return
     if args.batch is None:
         args.batch = 128 if args.workload == "alexnet" else 64
     if args.workload == "alexnet":
@@ -780,6 +777,9 @@ def main():
         tune.share_chip([api.conv_desc(args.batch, c.H, c.H, c.C, c.K, c.R, c.R, c.stride, c.pad) for c in shapes.resnet50_convs(args.variant)] +
                         [api.conv_desc(args.batch, 1, 1, shapes.RESNET50_FC.I, shapes.RESNET50_FC.O, 1, 1)])
     wl = ResNet50Step(batch=args.batch, dtype=args.dtype, lars_path=args.lars_path, sumsq_from=args.sumsq_from, variant=args.variant)
+    if args.plans_digest:
+        print(plans_digest(wl))
+        return
 
     # loss-scale back-off: halve S until the weight gradients stay inside fp16 and the update is not skipped
     for _ in range(12):
