@@ -142,8 +142,8 @@ int jz_gemm_fc_bwd_weight_sumsq(int batch, int in_features, int out_features, co
  * FP32 storage, FP32 products and sums (v_mfma_f32_32x32x2_f32), no rounding to FP16 anywhere: same definitions, same
  * layouts (NHWC / KRSC / NPQK), same GEMM view, same conventions and status codes as the FP16 entry points above, with
  * float tensors (DEVICE, 16-byte aligned).  Split reductions leave FP32 partial sums in `ws` and are added in index
- * order (deterministic).  Meant as the baseline the mixed-precision path is compared with: one kernel family sized
- * for the FP32 matrix peak, no table of tuned variants. */
+ * order (deterministic).  Kernels sized for the FP32 matrix peak, chosen by a cost model; no table of tuned variants
+ * and no tuning hook. */
 int jz_conv2d_f32_workspace_bytes(int op, const jz_conv_desc* desc, size_t* bytes);
 int jz_conv2d_fwd_f32(const jz_conv_desc* desc, const float* x32, const float* w32, float* y32, void* ws, size_t ws_bytes,
                       void* hip_stream);
@@ -404,9 +404,9 @@ int jz_conv2d_describe_plan(int op, const jz_conv_desc* desc, char* text, size_t
  * choices and of the cost model; nothing else overrides the planner (the library reads no environment variables).
  * The variant must be one the library has (jz_conv2d_describe_plan shows the names: e.g. 128x128 tile, k tile 64,
  * 8 wavefronts, ring 4), else JZ_ERR_UNSUPPORTED; shapes that gather with per-load tap arithmetic take the four
- * 4-wavefront tiles, 32 deep, ring 4; a strided multi-tap backward-data layer, which runs as one launch per parity
- * class of its stride, takes the variant for every one of those launches (never split); shapes on the element-wise
- * kernel cannot be tuned (JZ_ERR_UNSUPPORTED).
+ * 4-wavefront tiles, 32 deep, ring 4; a strided multi-tap backward-data layer, whose parity classes (the residues of its
+ * stride) run side by side in one launch, takes the variant for every one of them (never split); shapes on the
+ * element-wise kernel cannot be tuned (JZ_ERR_UNSUPPORTED).
  * Results never depend on the choice beyond the summation order of the reduction.
  * jz_conv2d_tune_use_table(0) makes the planner skip its built-in table of measured choices (cost model only),
  * jz_conv2d_tune_use_table(1) restores it.  jz_conv2d_tune_clear forgets every recorded choice and restores the
