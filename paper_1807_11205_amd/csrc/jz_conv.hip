@@ -36,58 +36,85 @@ constexpr int BK = 64;  // k tile depth of the element-wise kernel
 // (w'[k][r][4 s + c], zeros elsewhere); for backward-weight the GEMM produces dw' in that layout and the real
 // entries are copied out.
 
-// One launch does both copies.  Slices z < N of the grid: a workgroup of 128 threads covers 256 padded pixels of the
-// PAD_ROWS image rows (z, PAD_ROWS y ...), two pixels per thread and row (one 16-byte store; Wp is even).  Slice z = N (present when wp != nullptr) repacks the
-// filter: w[K][R][S][C] -> wp[K][R][KT] with wp[k][r][4 s + c] = w[k][r][s][c], zero elsewhere.
-constexpr int PAD_ROWS = 4;
-__global__ __launch_bounds__(128) void pad_to_c4(const unsigned short* __restrict__ x, unsigned short* __restrict__ xp,
-                                                 int N, int H, int W, int C, int Hp, int Wp, int ph, int pw,
-                                                 const unsigned short* __restrict__ w, unsigned short* __restrict__ wp,
-                                                 int K, int R, int S, int KT, int chunk_major) {
-  const int z = blockIdx.z;
-  if (z == N) {
-    const int total = K * R * KT;
-    const int stride = gridDim.x * gridDim.y * 128;
-    for (int i = (blockIdx.y * gridDim.x + blockIdx.x) * 128 + threadIdx.x; i < total; i += stride) {
-      int j = i % KT, kr = i / KT;
-      int s = j >> 2, c = j & 3;
-      // chunk_major (the patch kernel's layout): wq[r][j / 8][k][j % 8], 16-byte chunks of one filter row side by side per k
-      const int k = kr / R, r = kr - k * R;
-      const int dst = chunk_major ? ((r * (KT / 8) + (j >> 3)) * K + k) * 8 + (j & 7) : i;
-      wp[dst] = (s < S && c < C) ? w[((size_t)kr * S + s) * C + c] : (unsigned short)0;
-    }
+// One launch does both copies.  A workgroup writes PAD_PAIRS consecutive pixel pairs of one image of xp (a pair is one
+// 16-byte store; Wp is even).  Padding only adds pixels, so the image pixels among them are one contiguous run of x,
+// which comes in through LDS in whole aligned 16-byte chunks whatever C and the row length are, all loads of a thread
+// in flight together.  Bound by memory; 2-byte loads straight from x (a 3-channel row starts on any even byte) kept the
+// load units busy instead: 227 x 227 x 3 x 128 (92 MB moved) took 26 us that way, 6.5 us more than this; 512 pairs
+// measure the same.  The workgroups behind the images' (present when w != nullptr) repack the filter: w[K][R][S][C] ->
+// wp[K][R][KT] with wp[k][r][4 s + c] = w[k][r][s][c], zero elsewhere.
+constexpr int PAD_PAIRS = 1024, PAD_THREADS = 256;
+struct PadArgs {
+  const unsigned short *x, *w;
+  unsigned short *xp, *wp;
+  int N, H, W, C, Hp, Wp, ph, pw;
+  int K, R, S, KT, chunk_major;
+  unsigned pairs, groups;  // pixel pairs per image of xp, workgroups per image
+  FastDiv d_row;           // Wp / 2
+};
+__global__ __launch_bounds__(PAD_THREADS) void pad_to_c4(PadArgs a) {
+  const int z = blockIdx.x / a.groups, C = a.C;
+  if (z >= a.N) {
+    const int i = (blockIdx.x - a.N * a.groups) * PAD_THREADS + threadIdx.x;
+    if (i >= a.K * a.R * a.KT) return;
+    int j = i % a.KT, kr = i / a.KT;
+    int s = j >> 2, c = j & 3;
+    // chunk_major (the patch kernel's layout): wq[r][j / 8][k][j % 8], 16-byte chunks of one filter row side by side per k
+    const int k = kr / a.R, r = kr - k * a.R;
+    const int dst = a.chunk_major ? ((r * (a.KT / 8) + (j >> 3)) * a.K + k) * 8 + (j & 7) : i;
+    a.wp[dst] = (s < a.S && c < C) ? a.w[((size_t)kr * a.S + s) * C + c] : (unsigned short)0;
     return;
   }
-  // PAD_ROWS image rows per workgroup: every load of a thread's rows is in flight before the first store
-  const int wp0 = 2 * (blockIdx.x * 128 + threadIdx.x);
-  if (wp0 >= Wp) return;
-  unsigned short v[PAD_ROWS][8];
+  constexpr int CHUNKS = PAD_PAIRS + 2;  // 2 PAD_PAIRS pixels of up to 4 halves, and a partial chunk at each end
+  __shared__ __align__(16) unsigned short in[CHUNKS * 8];
+  const unsigned q0 = (blockIdx.x - z * a.groups) * PAD_PAIRS, q1 = min(q0 + PAD_PAIRS, a.pairs);
+  auto before = [&](unsigned q) {  // pixels of the image in front of padded pair q
+    const int hp = (int)fd_div(q, a.d_row), wi = 2 * (int)(q - hp * a.d_row.d) - a.pw, h = hp - a.ph;
+    return h < 0 ? 0 : h >= a.H ? a.H * a.W : h * a.W + min(max(wi, 0), a.W);
+  };
+  const size_t image = (size_t)z * a.H * a.W * C, total = (size_t)a.N * a.H * a.W * C;
+  const int first = before(q0);
+  const size_t g0 = image + (size_t)first * C, g1 = image + (size_t)before(q1) * C, a0 = g0 & ~(size_t)7;
+  constexpr int ITERS = (CHUNKS + PAD_THREADS - 1) / PAD_THREADS;
+  uint4 t[ITERS];
 #pragma unroll
-  for (int rr = 0; rr < PAD_ROWS; ++rr) {
-    const int hp = blockIdx.y * PAD_ROWS + rr;
-    const int h = hp - ph;
+  for (int i = 0; i < ITERS; ++i) {
+    const size_t g = a0 + 8 * (size_t)(i * PAD_THREADS + threadIdx.x);
+    if (g + 8 <= total) {
+      if (g < g1) t[i] = *reinterpret_cast<const uint4*>(a.x + g);
+    } else if (g < g1) {  // the last chunk of x where x does not end on a 16-byte boundary
+      unsigned short e[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) v[rr][e] = 0;
-    if (hp < Hp && (unsigned)h < (unsigned)H) {
-      const unsigned short* row = x + ((size_t)z * H + h) * W * C;
-#pragma unroll
-      for (int p = 0; p < 2; ++p) {
-        const int wi = wp0 + p - pw;
-        if ((unsigned)wi < (unsigned)W) {
-#pragma unroll
-          for (int c = 0; c < 4; ++c)
-            if (c < C) v[rr][4 * p + c] = row[(size_t)wi * C + c];
-        }
-      }
+      for (int k = 0; k < 8; ++k) e[k] = g + k < total ? a.x[g + k] : (unsigned short)0;
+      t[i] = make_uint4((unsigned)e[0] | ((unsigned)e[1] << 16), (unsigned)e[2] | ((unsigned)e[3] << 16),
+                        (unsigned)e[4] | ((unsigned)e[5] << 16), (unsigned)e[6] | ((unsigned)e[7] << 16));
     }
   }
 #pragma unroll
-  for (int rr = 0; rr < PAD_ROWS; ++rr) {
-    const int hp = blockIdx.y * PAD_ROWS + rr;
-    if (hp >= Hp) break;
-    uint4 pk = make_uint4((unsigned)v[rr][0] | ((unsigned)v[rr][1] << 16), (unsigned)v[rr][2] | ((unsigned)v[rr][3] << 16),
-                          (unsigned)v[rr][4] | ((unsigned)v[rr][5] << 16), (unsigned)v[rr][6] | ((unsigned)v[rr][7] << 16));
-    *reinterpret_cast<uint4*>(xp + (((size_t)z * Hp + hp) * Wp + wp0) * 4) = pk;
+  for (int i = 0; i < ITERS; ++i) {
+    const int c = i * PAD_THREADS + threadIdx.x;
+    if (a0 + 8 * (size_t)c < g1) *reinterpret_cast<uint4*>(&in[8 * c]) = t[i];
+  }
+  __syncthreads();
+  const int lead = (int)(g0 - a0) - first * C;  // in[lead + C * pixel]: a pixel of the image
+#pragma unroll
+  for (int i = 0; i < PAD_PAIRS / PAD_THREADS; ++i) {
+    const unsigned q = q0 + i * PAD_THREADS + threadIdx.x;
+    if (q >= q1) break;
+    const int hp = (int)fd_div(q, a.d_row), wi = 2 * (int)(q - hp * a.d_row.d) - a.pw, h = hp - a.ph;
+    unsigned v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    if ((unsigned)h < (unsigned)a.H) {
+#pragma unroll
+      for (int p = 0; p < 2; ++p)
+        if ((unsigned)(wi + p) < (unsigned)a.W) {
+          const unsigned short* px = &in[lead + C * (h * a.W + wi + p)];
+#pragma unroll
+          for (int c = 0; c < 4; ++c)
+            if (c < C) v[4 * p + c] = px[c];
+        }
+    }
+    *reinterpret_cast<uint4*>(a.xp + ((size_t)z * a.pairs + q) * 8) =
+        make_uint4(v[0] | (v[1] << 16), v[2] | (v[3] << 16), v[4] | (v[5] << 16), v[6] | (v[7] << 16));
   }
 }
 
@@ -762,7 +789,7 @@ int compute_plan(int op, const jz_conv_desc* d, Plan* pl) {
     if (Wp < (Q - 1) * d->stride_w + KT / 4) Wp = (Q - 1) * d->stride_w + KT / 4;
     Wp = (Wp + 1) & ~1;  // rows stay 16-byte aligned
     const long long nxp = (long long)d->N * Hp * Wp * 4;
-    if (nxp <= lim && Hp <= 65535 && d->N < 65535) {  // the copy kernel's grid is (columns, Hp, N + 1)
+    if (nxp <= lim && Hp <= 65535 && d->N < 65535) {
       pl->packed = true;
       pl->fast = true;
       pl->Hp = Hp; pl->Wp = Wp; pl->KT = KT;
@@ -1066,9 +1093,11 @@ int run(int op, const jz_conv_desc* d, const void* A, const void* B, void* D, vo
     const unsigned short* wsrc = op == JZ_FWD ? static_cast<const unsigned short*>(B) : nullptr;
     StemArgs sa;
     const bool stem = pl.stem && !stats && stem_fwd_setup(pl, d, &sa);
-    hipLaunchKernelGGL(pad_to_c4, dim3((unsigned)((pl.Wp / 2 + 127) / 128), (unsigned)((pl.Hp + PAD_ROWS - 1) / PAD_ROWS), (unsigned)(d->N + (wsrc ? 1 : 0))),
-                       dim3(128), 0, st, x, xp, d->N, d->H, d->W, d->C, pl.Hp, pl.Wp, d->pad_h, d->pad_w, wsrc,
-                       wsrc ? wp : nullptr, d->K, d->R, d->S, stem ? sa.NKS * 16 : pl.KT, stem ? 1 : 0);
+    PadArgs pa{x, wsrc, xp, wp, d->N, d->H, d->W, d->C, pl.Hp, pl.Wp, d->pad_h, d->pad_w, d->K, d->R, d->S,
+               stem ? sa.NKS * 16 : pl.KT, stem ? 1 : 0, (unsigned)pl.Hp * (pl.Wp / 2), 0, make_fastdiv(pl.Wp / 2)};
+    pa.groups = (pa.pairs + PAD_PAIRS - 1) / PAD_PAIRS;
+    const unsigned wgroups = wsrc ? ((unsigned)(pa.K * pa.R * pa.KT) + PAD_THREADS - 1) / PAD_THREADS : 0;
+    hipLaunchKernelGGL(pad_to_c4, dim3(pa.groups * (unsigned)d->N + wgroups), dim3(PAD_THREADS), 0, st, pa);
     if (stem) {
       if ((rc = jz::launch_status()) != JZ_OK) return rc;
       sa.xp = xp;
