@@ -762,6 +762,9 @@ int compute_plan(int op, const jz_conv_desc* d, Plan* pl) {
     pl->fast = d->K % 8 == 0 && d->C % 8 == 0;
     pl->bytesA = 2 * ny; pl->bytesB = 2 * nx; pl->bytesD = 2 * nw;  // A = dy, B = x
   }
+  // a grid of one row or column never steps: the kernels' sums of coordinates and strides then stay far below 2^31
+  if (op != JZ_BWD_DATA && P == 1) g.sh = 1;
+  if (op != JZ_BWD_DATA && Q == 1) g.sw = 1;
   a.sc_on = 0; a.sc_H = a.sc_W = 0; a.sc_sh = a.sc_sw = 1; a.sc_oh = a.sc_ow = 0; a.sc_fill = 0;
   a.w_taps = d->R * d->S; a.w_tap0 = 0; a.w_tap_r = d->S; a.w_tap_s = 1;
   g.always_mask = 0;

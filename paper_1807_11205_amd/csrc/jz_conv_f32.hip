@@ -503,6 +503,9 @@ int make_plan_f32(int op, const jz_conv_desc* d, PlanF32* pl) {
     pl->vec = d->K % 4 == 0 && d->C % 4 == 0;
     pl->bytesA = 4 * ny; pl->bytesB = 4 * nx; pl->bytesD = 4 * nw;  // A = dy, B = x
   }
+  // a grid of one row or column never steps: the kernels' sums of coordinates and strides then stay far below 2^31
+  if (op != JZ_BWD_DATA && P == 1) g.sh = 1;
+  if (op != JZ_BWD_DATA && Q == 1) g.sw = 1;
   const bool strided = d->stride_h > 1 || d->stride_w > 1;
   a.bytesA = (unsigned)pl->bytesA;
   a.bytesB = (unsigned)pl->bytesB;

@@ -138,11 +138,14 @@ __device__ __forceinline__ void f32_dma_body(const F32Args& a, unsigned block, u
       vA[ii] = mm < a.M ? (unsigned)(mc_k(BM, ii) * a.M + mm) * 4u : OOB;
     }
   }
-  // backward-weight, gathered x: the filter tap of the lane's columns, and per load the row, the column and the byte offset
-  // of its pixel, advanced by 16 pixels per tile with one carry per digit
-  int bw_r[LB], bw_s[LB], xp[LB], xq[LB], bw_tp = 0, bw_tq = 0;
+  // backward-weight, gathered x: per load the row, the column and the byte offset of the input pixel at the lane's tap,
+  // advanced by 16 output pixels per tile with one carry per digit.  The digits are kept as input coordinates (times the
+  // stride, plus the tap): no multiplication in the loop, and exact for every size (a 24-bit product is not: grids and strides
+  // reach beyond 2^23).  xp_end, xq_end: where they wrap.
+  int xp[LB], xq[LB], xp_end[LB], xq_end[LB], bw_tp = 0, bw_tp1 = 0, bw_tq = 0;
+  const int bw_rows = g.OH * g.sh, bw_cols = g.OW * g.sw;
   unsigned xoff[LB], bw_dv = 0, bw_k1 = 0, bw_k2 = 0;
-  (void)bw_r; (void)bw_s; (void)xp; (void)xq; (void)xoff; (void)bw_tp; (void)bw_tq; (void)bw_dv; (void)bw_k1; (void)bw_k2;
+  (void)xp; (void)xq; (void)xp_end; (void)xq_end; (void)xoff; (void)bw_tp; (void)bw_tp1; (void)bw_tq; (void)bw_dv; (void)bw_k1; (void)bw_k2;
   if constexpr (OP == OP_FWD) {
 #pragma unroll
     for (int ii = 0; ii < LB; ++ii) {
@@ -158,37 +161,35 @@ __device__ __forceinline__ void f32_dma_body(const F32Args& a, unsigned block, u
   } else {
     const unsigned Pn = (unsigned)(g.IH * g.row_pitch) * 4u, Ph = (unsigned)(g.sh * g.row_pitch) * 4u, Pw = (unsigned)(g.sw * g.IC) * 4u;
     const unsigned ta = fd_div((unsigned)FD_BK, g.d_ohow), trem = (unsigned)FD_BK - ta * (unsigned)(g.OH * g.OW);
-    bw_tp = (int)fd_div(trem, g.d_ow);
-    bw_tq = (int)trem - bw_tp * g.OW;
-    bw_dv = ta * Pn + (unsigned)bw_tp * Ph + (unsigned)bw_tq * Pw;
+    const unsigned tp = fd_div(trem, g.d_ow), tq = trem - tp * (unsigned)g.OW;
+    bw_tp = (int)tp * g.sh;
+    bw_tp1 = bw_tp + g.sh;
+    bw_tq = (int)tq * g.sw;
+    bw_dv = ta * Pn + tp * Ph + tq * Pw;
     bw_k1 = Ph - (unsigned)g.OW * Pw;
     bw_k2 = Pn - (unsigned)g.OH * Ph;
 #pragma unroll
     for (int ii = 0; ii < LB; ++ii) {
       const int nn = n0 + mc_col(BN, ii);
-      bw_r[ii] = -(1 << 28); bw_s[ii] = 0;
+      int r0 = -(1 << 30), s0 = 0;  // a column that does not exist lies outside every image
       vB[ii] = nn < a.N ? (unsigned)(mc_k(BN, ii) * g.IC + nn) * 4u : OOB;  // 1x1, unit stride, unpadded: a plain matrix
       int ch = 0;
       if (nn < a.N) {
         const unsigned tap = fd_div((unsigned)nn, g.d_ic), r = fd_div(tap, g.d_s);
         ch = nn - (int)tap * g.IC;
-        bw_r[ii] = (int)r - g.ph;
-        bw_s[ii] = (int)(tap - r * (unsigned)g.S) - g.pw;
+        r0 = (int)r - g.ph;
+        s0 = (int)(tap - r * (unsigned)g.S) - g.pw;
       }
       const unsigned j = (unsigned)(kt_begin * FD_BK + mc_k(BN, ii));
       const unsigned n = fd_div(j, g.d_ohow), rem = j - n * (unsigned)(g.OH * g.OW);
       const unsigned pp = fd_div(rem, g.d_ow);
-      xp[ii] = (int)pp;
-      xq[ii] = (int)(rem - pp * (unsigned)g.OW);
-      if (a.bw_same) {
-        // xp, xq: the source row and column (wrapping at the grid's size plus the tap's shift)
-        if (nn < a.N)
-          vB[ii] = (unsigned)((mc_k(BN, ii) + bw_r[ii] * g.IW + bw_s[ii]) * g.IC + ch) * 4u + biasB;
-        xp[ii] += bw_r[ii];
-        xq[ii] += bw_s[ii];
-      }
-      xoff[ii] = ((n * (unsigned)g.IH + pp * (unsigned)g.sh + (unsigned)bw_r[ii]) * (unsigned)g.row_pitch +
-                  ((unsigned)(xq[ii] * g.sw) + (unsigned)bw_s[ii]) * (unsigned)g.IC + (unsigned)ch) * 4u;
+      const unsigned qq = rem - pp * (unsigned)g.OW;
+      xp[ii] = (int)pp * g.sh + r0;
+      xq[ii] = (int)qq * g.sw + s0;
+      xp_end[ii] = bw_rows + r0;
+      xq_end[ii] = bw_cols + s0;
+      if (a.bw_same && nn < a.N) vB[ii] = (unsigned)((mc_k(BN, ii) + r0 * g.IW + s0) * g.IC + ch) * 4u + biasB;
+      xoff[ii] = ((n * (unsigned)g.IH + (unsigned)xp[ii]) * (unsigned)g.row_pitch + (unsigned)xq[ii] * (unsigned)g.IC + (unsigned)ch) * 4u;
     }
   }
 
@@ -262,27 +263,26 @@ __device__ __forceinline__ void f32_dma_body(const F32Args& a, unsigned block, u
       } else if (a.bw_linear) {
         if (c.tail) jz_dma16s(rsrcB, dst, c.k0 + (unsigned)mc_k(BN, ii) < (unsigned)a.Kred ? vB[ii] : OOB, c.soffB);
         else jz_dma16s(rsrcB, dst, vB[ii], c.soffB);
-      } else if (a.bw_same) {
+      } else {
         bool ok = (unsigned)xp[ii] < (unsigned)g.IH && (unsigned)xq[ii] < (unsigned)g.IW;
         if (c.tail) ok = ok && c.k0 + (unsigned)mc_k(BN, ii) < (unsigned)a.Kred;
-        jz_dma16s(rsrcB, dst, ok ? vB[ii] : OOB, c.soffB);
-        xq[ii] += bw_tq;
-        const bool c1 = xq[ii] >= g.OW + bw_s[ii];
-        xq[ii] -= c1 ? g.OW : 0;
-        xp[ii] += bw_tp + (c1 ? 1 : 0);
-        xp[ii] -= xp[ii] >= g.OH + bw_r[ii] ? g.OH : 0;
-      } else {
-        const int ih = __mul24(xp[ii], g.sh) + bw_r[ii], iw = __mul24(xq[ii], g.sw) + bw_s[ii];
-        bool ok = (unsigned)ih < (unsigned)g.IH && (unsigned)iw < (unsigned)g.IW;
-        if (c.tail) ok = ok && c.k0 + (unsigned)mc_k(BN, ii) < (unsigned)a.Kred;
-        jz_dma16(rsrcB, dst, ok ? xoff[ii] : OOB);
-        xq[ii] += bw_tq;
-        const bool c1 = xq[ii] >= g.OW;
-        xq[ii] -= c1 ? g.OW : 0;
-        xp[ii] += bw_tp + (c1 ? 1 : 0);
-        const bool c2 = xp[ii] >= g.OH;
-        xp[ii] -= c2 ? g.OH : 0;
-        xoff[ii] += bw_dv + (c1 ? bw_k1 : 0u) + (c2 ? bw_k2 : 0u);
+        auto advance = [&](bool& c1, bool& c2) {
+          xq[ii] += bw_tq;
+          c1 = xq[ii] >= xq_end[ii];
+          xq[ii] -= c1 ? bw_cols : 0;
+          xp[ii] += c1 ? bw_tp1 : bw_tp;
+          c2 = xp[ii] >= xp_end[ii];
+          xp[ii] -= c2 ? bw_rows : 0;
+        };
+        bool c1, c2;
+        if (a.bw_same) {
+          jz_dma16s(rsrcB, dst, ok ? vB[ii] : OOB, c.soffB);
+          advance(c1, c2);
+        } else {
+          jz_dma16(rsrcB, dst, ok ? xoff[ii] : OOB);
+          advance(c1, c2);
+          xoff[ii] += bw_dv + (c1 ? bw_k1 : 0u) + (c2 ? bw_k2 : 0u);
+        }
       }
     }
   };

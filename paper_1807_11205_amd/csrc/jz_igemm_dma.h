@@ -199,6 +199,9 @@ __device__ __forceinline__ void igemm_dma_body(const GemmArgs& a, unsigned block
     const unsigned Ph = (unsigned)(shh * g.row_pitch) * 2u;
     const unsigned Pw = (unsigned)(sww * g.pix_step) * 2u;
     const unsigned dV = sa * Pn + (unsigned)sb * Ph + (unsigned)sc * Pw;
+    // the digits are kept times the stride, as source coordinates: multiplying them for the masks would need the full 32-bit
+    // product (grids reach beyond 2^23), a quarter-rate instruction per row and axis
+    const int rows = g.OH * shh, cols = g.OW * sww, row_step = sb * shh, row_step1 = row_step + shh, col_step = sc * sww;
     const unsigned k1 = Ph - (unsigned)g.OW * Pw;               // a carry out of the column digit
     const unsigned k2 = Pn - (unsigned)g.OH * Ph;               // a carry out of the row digit
     // a single unpadded tap is always inside, and so is every tap of a forward pass without padding
@@ -209,23 +212,23 @@ __device__ __forceinline__ void igemm_dma_body(const GemmArgs& a, unsigned block
     int m = m0 + kc_row;
     const unsigned n0img = fd_div((unsigned)m, g.d_ohow);
     const unsigned rem = (unsigned)m - n0img * (unsigned)(g.OH * g.OW);
-    int oh = (int)fd_div(rem, g.d_ow);
-    int ow = (int)rem - oh * g.OW;
+    const int oh0 = (int)fd_div(rem, g.d_ow);
+    int oh = oh0 * shh, ow = ((int)rem - oh0 * g.OW) * sww;
     // offset of the pixel the per-tile scalar offset counts from: tap (0,0) for forward, tap (R-1,S-1) for
     // backward-data; forward adds the descriptor margin, which makes it non-negative
     // (FLAT: the lane's chunk is part of the per-tile offset)
-    unsigned v = (unsigned)(((int)n0img * g.IH + oh * shh + offh) * g.row_pitch + (ow * sww + offw) * g.pix_step + (FLAT ? 0 : kc_chunk * 8)) * 2u +
+    unsigned v = (unsigned)(((int)n0img * g.IH + oh + offh) * g.row_pitch + (ow + offw) * g.pix_step + (FLAT ? 0 : kc_chunk * 8)) * 2u +
                  (OP == OP_FWD ? biasA : 0u);
 #pragma unroll
     for (int ii = 0; ii < LA; ++ii) {
       if (ii > 0) {
         m += (int)STR;
-        ow += sc;
-        const bool c1 = ow >= g.OW;
-        ow -= c1 ? g.OW : 0;
-        oh += sb + (c1 ? 1 : 0);
-        const bool c2 = oh >= g.OH;
-        oh -= c2 ? g.OH : 0;
+        ow += col_step;
+        const bool c1 = ow >= cols;
+        ow -= c1 ? cols : 0;
+        oh += c1 ? row_step1 : row_step;
+        const bool c2 = oh >= rows;
+        oh -= c2 ? rows : 0;
         v += dV + (c1 ? k1 : 0u) + (c2 ? k2 : 0u);
       }
       vA[ii] = 0; invA[ii] = OOB;
@@ -237,7 +240,7 @@ __device__ __forceinline__ void igemm_dma_body(const GemmArgs& a, unsigned block
           // position p0 + dir t is below 0 for the first `lo` taps and at or beyond the size from tap `hi` on
           // (dir = -1: the other way round).  Columns give a mask cm of S bits that is copied into every row's slot by
           // one multiplication (tap_rep has bit r S set for every r); rows that are outside fill their whole slots.
-          const int ih0 = __mul24(oh, shh) + offh, iw0 = __mul24(ow, sww) + offw;
+          const int ih0 = oh + offh, iw0 = ow + offw;
           const int lo_w = dir > 0 ? -iw0 : iw0 - g.IW + 1, hi_w = dir > 0 ? g.IW - iw0 : iw0 + 1;
           const int lo_h = dir > 0 ? -ih0 : ih0 - g.IH + 1, hi_h = dir > 0 ? g.IH - ih0 : ih0 + 1;
           const unsigned cm = low_bits(clamp_to(lo_w, g.S)) | (full & ~low_bits(clamp_to(hi_w, g.S)));
@@ -247,12 +250,13 @@ __device__ __forceinline__ void igemm_dma_body(const GemmArgs& a, unsigned block
       }
     }
   }
-  int sb1 = 0, sb2 = 0, sbc = 0;
-  (void)sb1; (void)sb2; (void)sbc;
-  // backward-weight, gathered x: per load the pixel's row and column and the byte offset of its tap, advanced per tile
-  int xp[LB], xq[LB], bw_tp = 0, bw_tq = 0;
+  // backward-weight, gathered x: per load the row, the column and the byte offset of the input pixel at this lane's tap,
+  // advanced per tile; the digits are input coordinates (times the stride, plus the tap), which wrap at xp_end, xq_end: no
+  // multiplication in the k loop, exact for every size
+  int xp[LB], xq[LB], xp_end = 0, xq_end = 0, bw_tp = 0, bw_tp1 = 0, bw_tq = 0;
+  const int bw_rows = g.OH * g.sh, bw_cols = g.OW * g.sw;
   unsigned xoff[LB], bw_dv = 0, bw_k1 = 0, bw_k2 = 0;
-  (void)xp; (void)xq; (void)xoff; (void)bw_tp; (void)bw_tq; (void)bw_dv; (void)bw_k1; (void)bw_k2;
+  (void)xp; (void)xq; (void)xp_end; (void)xq_end; (void)xoff; (void)bw_tp; (void)bw_tp1; (void)bw_tq; (void)bw_dv; (void)bw_k1; (void)bw_k2;
   if (OP == OP_FWD) {
 #pragma unroll
     for (int ii = 0; ii < LB; ++ii) {
@@ -270,15 +274,13 @@ __device__ __forceinline__ void igemm_dma_body(const GemmArgs& a, unsigned block
   } else {
     // x gathered: this lane's 8 columns (tap, c..c+7) are the same for every load (k & 7 does not depend on ii)
     int nn = n0 + mc_chunk(BN, mc_k(BN, 0)) * 8;
+    int sb1 = -(1 << 30), sb2 = 0, sbc = 0;  // columns that do not exist lie outside every image
     if (nn < a.N) {
       unsigned tap = fd_div((unsigned)nn, g.d_ic);
       unsigned r = fd_div(tap, g.d_s);
       sbc = nn - (int)tap * g.IC;
       sb1 = (int)r - g.ph;
       sb2 = (int)(tap - r * g.S) - g.pw;
-    } else {
-      sb1 = -(1 << 28);
-      sb2 = -(1 << 28);
     }
     // 1x1, unit stride, no padding: pixel j of x is row j of a plain [Kred][IC] matrix, so the load needs no pixel
     // arithmetic at all (per-lane offset fixed, per-tile offset scalar)
@@ -291,11 +293,15 @@ __device__ __forceinline__ void igemm_dma_body(const GemmArgs& a, unsigned block
     if (!a.bw_linear) {
       const unsigned ta = fd_div((unsigned)TBK, g.d_ohow);
       const unsigned trem = (unsigned)TBK - ta * (unsigned)(g.OH * g.OW);
-      bw_tp = (int)fd_div(trem, g.d_ow);
-      bw_tq = (int)trem - bw_tp * g.OW;
+      const unsigned tp = fd_div(trem, g.d_ow), tq = trem - tp * (unsigned)g.OW;
+      bw_tp = (int)tp * g.sh;
+      bw_tp1 = bw_tp + g.sh;
+      bw_tq = (int)tq * g.sw;
+      xp_end = bw_rows + sb1;
+      xq_end = bw_cols + sb2;
       const unsigned Pn = (unsigned)(g.IH * g.row_pitch) * 2u, Ph = (unsigned)(g.sh * g.row_pitch) * 2u,
                      Pw = (unsigned)(g.sw * g.pix_step) * 2u;
-      bw_dv = ta * Pn + (unsigned)bw_tp * Ph + (unsigned)bw_tq * Pw;
+      bw_dv = ta * Pn + tp * Ph + tq * Pw;
       bw_k1 = Ph - (unsigned)g.OW * Pw;
       bw_k2 = Pn - (unsigned)g.OH * Ph;
 #pragma unroll
@@ -304,10 +310,9 @@ __device__ __forceinline__ void igemm_dma_body(const GemmArgs& a, unsigned block
         const unsigned n = fd_div(j, g.d_ohow);
         const unsigned rem = j - n * (unsigned)(g.OH * g.OW);
         const unsigned pp = fd_div(rem, g.d_ow);
-        xp[ii] = (int)pp;
-        xq[ii] = (int)(rem - pp * (unsigned)g.OW);
-        xoff[ii] = ((n * (unsigned)g.IH + pp * (unsigned)g.sh + (unsigned)sb1) * (unsigned)g.row_pitch +
-                    ((unsigned)(xq[ii] * g.sw) + (unsigned)sb2) * (unsigned)g.pix_step + (unsigned)sbc) * 2u;
+        xp[ii] = (int)pp * g.sh + sb1;
+        xq[ii] = (int)(rem - pp * (unsigned)g.OW) * g.sw + sb2;
+        xoff[ii] = ((n * (unsigned)g.IH + (unsigned)xp[ii]) * (unsigned)g.row_pitch + (unsigned)xq[ii] * (unsigned)g.pix_step + (unsigned)sbc) * 2u;
       }
     }
     // dy[(n,p,q)][k_out], chunk = 8 consecutive k_out: row j = k0 + k of the tile at (mm + j M) * 2
@@ -413,16 +418,15 @@ __device__ __forceinline__ void igemm_dma_body(const GemmArgs& a, unsigned block
           const bool ok = c.k0 + mc_k(BN, ii) < a.Kred;
           jz_dma16s(rsrcB, dst, ok ? vB[ii] : OOB, c.soffB);
         } else {  // x at this lane's tap for output pixel j = k0 + k-row
-          const int ih = __mul24(xp[ii], g.sh) + sb1, iw = __mul24(xq[ii], g.sw) + sb2;
-          const bool ok = c.k0 + mc_k(BN, ii) < a.Kred && (unsigned)ih < (unsigned)g.IH && (unsigned)iw < (unsigned)g.IW;
+          const bool ok = c.k0 + mc_k(BN, ii) < a.Kred && (unsigned)xp[ii] < (unsigned)g.IH && (unsigned)xq[ii] < (unsigned)g.IW;
           jz_dma16(rsrcB, dst, ok ? xoff[ii] : OOB);
           // on to the pixel of the next tile
           xq[ii] += bw_tq;
-          const bool c1 = xq[ii] >= g.OW;
-          xq[ii] -= c1 ? g.OW : 0;
-          xp[ii] += bw_tp + (c1 ? 1 : 0);
-          const bool c2 = xp[ii] >= g.OH;
-          xp[ii] -= c2 ? g.OH : 0;
+          const bool c1 = xq[ii] >= xq_end;
+          xq[ii] -= c1 ? bw_cols : 0;
+          xp[ii] += c1 ? bw_tp1 : bw_tp;
+          const bool c2 = xp[ii] >= xp_end;
+          xp[ii] -= c2 ? bw_rows : 0;
           xoff[ii] += bw_dv + (c1 ? bw_k1 : 0u) + (c2 ? bw_k2 : 0u);
         }
       }
