@@ -371,8 +371,8 @@ bool needs_gen_f32(const PlanF32& pl) {
 // ResNet-50: four rounds of 256 instead of 3.06 (14 x 14, 256 -> 256, 3x3: 135 -> 118 us forward, 139 -> 124 backward-data).
 // The constants (forward, backward-data, backward-weight with plain and with gathered x) are least-squares fits to timings of
 // every tile and split on 660 operations: ResNet-50 of both kinds and AlexNet at batch sizes from 2 to 64, random layers.  On a
-// quarter of them left out of the fit the choices were 0.7-1.9 % slower than the best.
-void choose_tiling_f32(PlanF32* pl, bool may_split, bool fixed_tile = false) {
+// quarter of them left out of the fit the choices were 0.7-1.9 % slower than the best.  limit: bytes of partial sums.
+void choose_tiling_f32(PlanF32* pl, bool may_split, bool fixed_tile = false, size_t limit = 0) {
   struct Tile { int bm, bn, resident; double lat[4], thr[4], prologue[4], own[4]; };
   static const Tile tiles[] = {
       {128, 128, 2, {0.935, 1.023, 1.020, 1.181}, {0.889, 0.919, 0.907, 1.065}, {1.798, 1.665, 2.516, 2.486}, {2.607, 2.429, 2.484, 0.813}},
@@ -405,6 +405,7 @@ void choose_tiling_f32(PlanF32* pl, bool may_split, bool fixed_tile = false) {
         const long long l1 = (wf + slots - 1) / slots, l2 = wf > 0 ? (wf + ws + slots - 1) / slots - l1 : (ws + slots - 1) / slots;
         const double t_lat = l1 * (t.prologue[c] + t.lat[c] * a.nkt) + l2 * (t.prologue[c] + t.lat[c] * kps);
         const double out = 4e-6 * a.M * a.N, part = sp > 1 ? 4e-6 * real * (double)(a.M - full * t.bm) * a.N : 0.0;
+        if (1e6 * part > (double)limit) continue;
         const double t_mem = byte[c] * (in + part + (full > 0 ? out : 0.0));
         double time = fixed[c] + sqrt(sqrt(p4(t_thr) + p4(t_lat) + p4(t_mem)));
         if (sp > 1) time += reduce_launch[c] + reduce_byte[c] * part;
@@ -444,7 +445,7 @@ bool class_args_f32(const jz_conv_desc* d, const PlanF32& base, int ca, int cb, 
   return true;
 }
 
-int make_plan_f32(int op, const jz_conv_desc* d, PlanF32* pl);
+int make_plan_f32(int op, const jz_conv_desc* d, PlanF32* pl, size_t limit = kPartialSumLimit);
 
 // Channels rounded up to 4 on copies, when that adds at most half to the multiply-adds.
 void plan_widened_f32(int op, const jz_conv_desc* d, PlanF32* pl) {
@@ -468,7 +469,7 @@ void plan_widened_f32(int op, const jz_conv_desc* d, PlanF32* pl) {
 
 int out_dim(int in, int pad, int f, int st) { return (in + 2 * pad - f) / st + 1; }
 
-int make_plan_f32(int op, const jz_conv_desc* d, PlanF32* pl) {
+int make_plan_f32(int op, const jz_conv_desc* d, PlanF32* pl, size_t limit) {
   if (!d) return JZ_ERR_NULL;
   if (op != JZ_FWD && op != JZ_BWD_DATA && op != JZ_BWD_WEIGHT) return JZ_ERR_UNSUPPORTED;
   if (d->N <= 0 || d->H <= 0 || d->W <= 0 || d->C <= 0 || d->K <= 0 || d->R <= 0 || d->S <= 0 || d->stride_h <= 0 ||
@@ -533,7 +534,7 @@ int make_plan_f32(int op, const jz_conv_desc* d, PlanF32* pl) {
       a.Kred = all;
       a.splits = 1;
     } else {
-      choose_tiling_f32(pl, !a.sc_on);
+      choose_tiling_f32(pl, !a.sc_on, false, limit);
     }
     pl->ws_bytes = a.splits > 1 ? (size_t)a.splits * (a.M - a.full_rows * pl->BM) * a.N * sizeof(float) : 0;
     pl->plain_ws_bytes = pl->ws_bytes;
@@ -550,6 +551,7 @@ int make_plan_f32(int op, const jz_conv_desc* d, PlanF32* pl) {
   long long want = 512 / tiles(pl->BM);
   if (want > a.nkt / 8) want = a.nkt / 8;
   if (want > 256) want = 256;
+  want = std::min(want, (long long)(limit / ((size_t)a.M * a.N * sizeof(float))));
   if (want < 1) want = 1;
   a.kt_per_split = (int)((a.nkt + want - 1) / want);
   a.splits = (a.nkt + a.kt_per_split - 1) / a.kt_per_split;
@@ -629,7 +631,16 @@ int run_f32(int op, const jz_conv_desc* d, const void* A, const void* B, void* D
     pl.widen = false;
     pl.ws_bytes = pl.plain_ws_bytes;
   }
-  if (pl.ws_bytes > 0 && (!ws || ws_bytes < pl.ws_bytes)) return JZ_ERR_WORKSPACE;
+  const size_t room = ws ? ws_bytes : 0;
+  if (room < pl.ws_bytes) {  // fewer splits
+    pl = PlanF32{};
+    if ((rc = make_plan_f32(op, d, &pl, room)) != JZ_OK) return rc;
+    if (pl.widen) {
+      pl.widen = false;
+      pl.ws_bytes = pl.plain_ws_bytes;
+    }
+    if (room < pl.ws_bytes || !runs_with_fewer_splits(op, pl.args.M, pl.args.N, pl.args.splits)) return JZ_ERR_WORKSPACE;
+  }
   if (pl.ws_bytes > 0 && (overlaps(ws, pl.ws_bytes, A, pl.bytesA) || overlaps(ws, pl.ws_bytes, B, pl.bytesB) ||
                           overlaps(ws, pl.ws_bytes, D, pl.bytesD)))
     return JZ_ERR_ALIAS;

@@ -42,6 +42,17 @@ int conv_bwd_data_stats_plan(const jz_conv_desc* d, size_t* conv_ws_bytes, int* 
 int conv_bwd_data_run(const jz_conv_desc* d, const void* dy, const void* w, void* dx, void* ws, size_t ws_bytes, float* stats,
                       int stats_tiles_m, const BnBwdOperands* bn, void* stream);
 
+// Splitting a reduction is a matter of speed.  A plan's partial sums take at most kPartialSumLimit bytes, the size of the
+// last-level cache: more of them would be written to memory and read back, and lie outside what the cost models were fitted to.
+// A caller with less workspace than the plan asks for gets fewer splits: a forward or backward-data layer always runs, without
+// any if need be; a weight gradient, whose reduction runs over all pixels, if 64 x 64 tiles times the splits that fit still are
+// kFewSplitsGrid workgroups, one per compute unit (else it is refused, JZ_ERR_WORKSPACE).
+constexpr size_t kPartialSumLimit = size_t(256) << 20;
+constexpr long long kFewSplitsGrid = 256;
+inline bool runs_with_fewer_splits(int op, int M, int N, int splits) {
+  return op != JZ_BWD_WEIGHT || (long long)((M + 63) / 64) * ((N + 63) / 64) * splits >= kFewSplitsGrid;
+}
+
 inline int launch_status() { return hipGetLastError() == hipSuccess ? JZ_OK : JZ_ERR_LAUNCH; }
 
 }  // namespace jz
