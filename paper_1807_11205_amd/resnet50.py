@@ -30,7 +30,7 @@ class Op:
         self.kind, self.name, self.params, self.ins, self.outs, self.call = kind, name, params, ins, outs, call
         self.bind = bind                # workspace -> the launch with its arguments marshalled once, bound to that workspace
         self.lane = "main"              # "side": a weight gradient, "proj": the projection-shortcut branch (both may run on a side stream)
-        self.joins_side = False         # reads what the side stream's projection branch wrote: waits for it
+        self.joins_side = False         # reads what side streams wrote (the projection branch, weight gradients): waits for it
 
 
 class ResNet50Chain:
@@ -87,8 +87,10 @@ class ResNet50Chain:
             # loss scale; last launch of the backward pass: every tensor's gradient
             self.fwd_ops.insert(0, Op("lars_begin", "begin", {}, [], [],
                                       lambda stream=None: api.jz_lars_begin_step(self.ps, self.lars_ws, self.ls_state, stream)))
+            # (joins_side: the gradients include those that the weight-gradient launches write on side streams)
             self.bwd_ops.append(Op("lars_grad_sumsq", "rest", {}, [self.grad], [],
                                    lambda stream=None: api.jz_lars_grad_sumsq(self.ps, 0, self.ps.T, self.lars_ws, stream)))
+            self.bwd_ops[-1].joins_side = True
         self.ws = torch.zeros(self._ws_bytes, dtype=torch.uint8, device=dev)
         self.side_ws = []               # one workspace per side stream, made on first use
         self._side_calls = {}
@@ -354,8 +356,8 @@ class ResNet50Chain:
     # ---- running -----------------------------------------------------------------------------------------------------
     def _run(self, ops, stream, side, which):
         """Launches ops in order; with side streams, those of lane "side" go there round-robin (each after an event that
-        says the main stream has produced what it reads), and an op that reads the projection branch's output first
-        waits for the side streams.  which: "fwd" or "bwd" (keys of the pre-created events)."""
+        says the main stream has produced what it reads), and an op that reads what side streams write (the projection
+        branch's output, all gradients) first waits for them.  which: "fwd" or "bwd" (keys of the pre-created events)."""
         if side is None:
             handle = api._stream(stream)
             for op in ops:
@@ -382,6 +384,7 @@ class ResNet50Chain:
                             ev = event((which, "join", i, j))
                             ev.record(s_)
                             main.wait_event(ev)
+                            dirty[j] = False
                 op.call(handle)
                 continue
             # weight gradients go round-robin; the projection branches (their weight gradients included) stay in order
