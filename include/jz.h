@@ -63,7 +63,11 @@ typedef struct {
   int pad_h, pad_w;
 } jz_conv_desc;
 
-/* Scratch bytes `op` (JZ_FWD / JZ_BWD_DATA / JZ_BWD_WEIGHT) needs for this layer. */
+/* Scratch bytes `op` (JZ_FWD / JZ_BWD_DATA / JZ_BWD_WEIGHT) wants for this layer: partial sums of a split reduction (at most
+ * 256 MiB unless jz_conv2d_tune_set asked for more), the padded copy of a layer with up to 4 channels, zero-extended copies
+ * of a layer with other channel counts that are not multiples of 8.  With less, a call does without the zero-extended copies
+ * and with as many splits as fit: forward and backward-data always, a weight gradient while its tiles times those splits
+ * fill the chip (256 tiles of 64 x 64).  Otherwise, and without room for a padded copy: JZ_ERR_WORKSPACE. */
 int jz_conv2d_workspace_bytes(int op, const jz_conv_desc* desc, size_t* bytes);
 
 /* Forward pass of one layer (Section 4.1: forward propagation in FP16, FP32 accumulate):
@@ -79,7 +83,8 @@ int jz_conv2d_fwd(const jz_conv_desc* desc, const void* x16, const void* w16, vo
  *                        of dy[n,p,q,k] * w[k,r,s,c] ),
  * input pixels no output reads get 0.
  * dy16: in [N,P,Q,K] fp16 (loss-scaled); w16: in [K,R,S,C]; dx16: out [N,H,W,C] fp16, fully overwritten.
- * A strided layer with a filter of more than one tap needs workspace (a repacked copy of the filter). */
+ * A strided layer with more than one tap and a multiple of 32 output channels asks for workspace of its filter's size, but
+ * stores nothing there. */
 int jz_conv2d_bwd_data(const jz_conv_desc* desc, const void* dy16, const void* w16, void* dx16, void* ws,
                        size_t ws_bytes, void* hip_stream);
 
@@ -116,9 +121,9 @@ int jz_conv2d_bwd_weight_sumsq(const jz_conv_desc* desc, const void* x16, const 
  * loops, harnesses that forbid hipMalloc) and therefore have no workspace to pass: same kernels, same bits, with the
  * scratch (split-K partial sums, the padded copy of a small-channel layer) in a fixed array of
  * JZ_STATIC_SCRATCH_BYTES inside the library.  Every GPU the library runs on holds its own copy of that array for the
- * life of the process.  Calls nothing that allocates.  JZ_ERR_WORKSPACE when the layer needs more scratch than the
- * array holds (jz_conv2d_workspace_bytes(JZ_BWD_WEIGHT, ...) says how much); other status codes as
- * jz_conv2d_bwd_weight.  All calls on one GPU share the array: calls that may overlap in time on one GPU (different
+ * life of the process.  Calls nothing that allocates.  A layer that wants more than the array holds runs, or is refused
+ * with JZ_ERR_WORKSPACE, as jz_conv2d_bwd_weight with a workspace of the array's size (its bits are then those of that
+ * call); other status codes as jz_conv2d_bwd_weight.  All calls on one GPU share the array: calls that may overlap in time on one GPU (different
  * streams, different threads) race on it and must be ordered by the caller; nothing in it needs clearing between
  * calls (every byte that is read was written by the same call). */
 #define JZ_STATIC_SCRATCH_BYTES (64u << 20)

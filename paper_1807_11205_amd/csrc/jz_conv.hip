@@ -593,7 +593,7 @@ void choose_tiling(Plan* pl, bool bk64_ok, int forced_bk, bool tables = true) {
   auto try_variant = [&](const Variant& v, int vbk) {
     const int nkt = (a.Kred + vbk - 1) / vbk;
     for (int sp : split_opts) {
-      if (sp > 1 && (nkt / sp < 4 || a.sc_on)) break;  // the scatter lives in the fp16 epilogue
+      if (sp > 1 && (nkt / sp < 4 || a.sc_on || 4.0 * sp * a.M * a.N > (double)pl->part_limit)) break;  // the scatter lives in the fp16 epilogue
       const double t = cost(v, vbk, sp);
       if (t < best) { best = t; bv = &v; bS = sp; }
     }
@@ -604,14 +604,16 @@ void choose_tiling(Plan* pl, bool bk64_ok, int forced_bk, bool tables = true) {
     bS = hit->splits;
     const int nkt_h = (a.Kred + hit->bk - 1) / hit->bk;
     if (bS > 1 && (nkt_h / bS < 4 || a.sc_on)) bS = 1;  // the same admissibility rules as the search below
+    const bool too_much = bS > 1 && !pl->rt_forced && 4.0 * bS * a.M * a.N > (double)pl->part_limit;
+    if (too_much) bS = 1;
     // backward-weight: most of the table's split counts were chosen for launches that share the chip with two other streams
     // (fewer splits, hence fewer workgroups and partial sums); a launch of its own wants the chip filled.  The tile is kept,
     // and so is the split where the model does not see a twelfth in changing it: batch 64 (chosen in company) 1.78 -> 1.32 ms
     // for the 52 layers, batch 32 (measured alone) keeps its splits.
-    if (oi == 2 && !pl->rt_forced && !pl->packed)
+    if ((oi == 2 && !pl->rt_forced && !pl->packed) || too_much)
       for (const Variant& v : kVariants)
         if (v.BM == hit->BM && v.BN == hit->BN && v.bk == hit->bk && v.waves == hit->waves && v.nst == hit->nst) {
-          best = (11.0 / 12.0) * cost(v, v.bk, bS);
+          best = (too_much ? 1.0 : 11.0 / 12.0) * cost(v, v.bk, bS);
           try_variant(v, v.bk);
         }
   } else {
@@ -708,7 +710,8 @@ bool has_classes(const jz_conv_desc* d) {
 
 void plan_widened(int op, const jz_conv_desc* d, Plan* pl);
 
-int compute_plan(int op, const jz_conv_desc* d, Plan* pl) {
+// limit: bytes that the partial sums of a split reduction may take
+int compute_plan(int op, const jz_conv_desc* d, Plan* pl, size_t limit = kPartialSumLimit) {
   if (!d) return JZ_ERR_NULL;
   if (op != JZ_FWD && op != JZ_BWD_DATA && op != JZ_BWD_WEIGHT) return JZ_ERR_UNSUPPORTED;
   if (d->N <= 0 || d->H <= 0 || d->W <= 0 || d->C <= 0 || d->K <= 0 || d->R <= 0 || d->S <= 0 || d->stride_h <= 0 ||
@@ -730,6 +733,7 @@ int compute_plan(int op, const jz_conv_desc* d, Plan* pl) {
   GemmArgs& a = pl->args;
   ConvGeom& g = a.g;
   pl->op = op;
+  pl->part_limit = limit;
   // k tile depth for the applicability checks: the LDS-direct kernels come 32 and 64 deep (chosen by the planner when
   // the layer allows both; 32 lets two workgroups share a compute unit)
   int bk = 32;
@@ -831,10 +835,11 @@ int compute_plan(int op, const jz_conv_desc* d, Plan* pl) {
   // on the dy grid with the filter's taps of that class.  Together they do the useful multiply-adds only (the per-load
   // variant fetches and masks every tap for every pixel: sh * sw times the work), and they run as one launch out of the
   // filter where it lies.  Packing each class's filter into the workspace and one launch per class took five launches:
-  // 128, 256 and 512 channels at batch 24: 35, 43 and 68 us, now 17, 21 and 23.  Every class needs a tap (R >= sh, S >= sw).  The workspace size stays
-  // the filter's, although nothing is kept there any more: callers have sized theirs by it.
+  // 128, 256 and 512 channels at batch 24: 35, 43 and 68 us, now 17, 21 and 23.  Every class needs a tap (R >= sh, S >= sw).
+  // Nothing is kept in a workspace.  Layers with whole k tiles per tap ask for the filter's size all the same, as they always
+  // have; the flattened ones, which never did, do not.
   pl->classes = pl->gen && op == JZ_BWD_DATA && has_classes(d);
-  if (pl->classes) pl->ws_bytes = up256((size_t)nw * 2);
+  if (pl->classes) pl->ws_bytes = pl->flat ? 0 : up256((size_t)nw * 2);
   pl->element_ws_bytes = pl->ws_bytes;
   if (!pl->fast) plan_widened(op, d, pl);
   return JZ_OK;
@@ -882,6 +887,7 @@ void plan_widened(int op, const jz_conv_desc* d, Plan* pl) {
 struct PlanCacheEntry {
   unsigned generation = 0;  // 0: empty
   int op = 0, rc = 0, ca = 0, cb = 0;
+  size_t limit = 0;
   jz_conv_desc d{};
   Plan pl;
 };
@@ -890,16 +896,16 @@ constexpr unsigned kPlanCacheSize = 256, kPlanCacheProbes = 4;
 // The entry for the key (created by `fill` on a miss); ca = cb = -1 for a layer's own plan.  Valid until the thread's
 // next look-up.
 template <class F>
-const PlanCacheEntry& cached_plan(int op, const jz_conv_desc& d, int ca, int cb, F&& fill) {
+const PlanCacheEntry& cached_plan(int op, const jz_conv_desc& d, int ca, int cb, size_t limit, F&& fill) {
   thread_local std::vector<PlanCacheEntry> cache(kPlanCacheSize);
   unsigned h = 2166136261u;
-  const int key[14] = {op, ca, cb, d.N, d.H, d.W, d.C, d.K, d.R, d.S, d.stride_h, d.stride_w, d.pad_h, d.pad_w};
+  const int key[15] = {op, ca, cb, (int)(limit >> 4), d.N, d.H, d.W, d.C, d.K, d.R, d.S, d.stride_h, d.stride_w, d.pad_h, d.pad_w};
   for (int v : key) h = (h ^ (unsigned)v) * 16777619u;
   h ^= h >> 15;
   const unsigned gen = g_tune_generation.load(std::memory_order_acquire);
   for (unsigned i = 0; i < kPlanCacheProbes; ++i) {
     const PlanCacheEntry& e = cache[(h + i) % kPlanCacheSize];
-    if (e.generation == gen && e.op == op && e.ca == ca && e.cb == cb && memcmp(&e.d, &d, sizeof d) == 0) return e;
+    if (e.generation == gen && e.op == op && e.ca == ca && e.cb == cb && e.limit == limit && memcmp(&e.d, &d, sizeof d) == 0) return e;
   }
   unsigned slot = h % kPlanCacheSize;
   for (unsigned i = 0; i < kPlanCacheProbes; ++i)
@@ -908,7 +914,7 @@ const PlanCacheEntry& cached_plan(int op, const jz_conv_desc& d, int ca, int cb,
       break;
     }
   PlanCacheEntry e;
-  e.op = op; e.ca = ca; e.cb = cb;
+  e.op = op; e.ca = ca; e.cb = cb; e.limit = limit;
   e.d = d;
   fill(e);
   e.generation = gen;
@@ -916,9 +922,9 @@ const PlanCacheEntry& cached_plan(int op, const jz_conv_desc& d, int ca, int cb,
   return cache[slot];
 }
 
-int make_plan(int op, const jz_conv_desc* d, Plan* pl) {
+int make_plan(int op, const jz_conv_desc* d, Plan* pl, size_t limit = kPartialSumLimit) {
   if (!d) return JZ_ERR_NULL;
-  const PlanCacheEntry& e = cached_plan(op, *d, -1, -1, [&](PlanCacheEntry& n) { n.rc = compute_plan(op, d, &n.pl); });
+  const PlanCacheEntry& e = cached_plan(op, *d, -1, -1, limit, [&](PlanCacheEntry& n) { n.rc = compute_plan(op, d, &n.pl, limit); });
   *pl = e.pl;
   return e.rc;
 }
@@ -965,7 +971,7 @@ bool compute_class_plan(const jz_conv_desc* d, const Plan& base, int ca, int cb,
 }
 
 bool make_class_plan(const jz_conv_desc* d, const Plan& base, int ca, int cb, Plan* pl) {
-  const PlanCacheEntry& e = cached_plan(JZ_BWD_DATA, *d, ca, cb, [&](PlanCacheEntry& n) {
+  const PlanCacheEntry& e = cached_plan(JZ_BWD_DATA, *d, ca, cb, 0, [&](PlanCacheEntry& n) {
     n.rc = compute_class_plan(d, base, ca, cb, &n.pl) ? 1 : 0;
   });
   if (e.rc) *pl = e.pl;
@@ -1020,7 +1026,16 @@ int run(int op, const jz_conv_desc* d, const void* A, const void* B, void* D, vo
     pl.widen = false;
     pl.ws_bytes = pl.element_ws_bytes;
   }
-  if (pl.ws_bytes > 0 && (!ws || ws_bytes < pl.ws_bytes)) return JZ_ERR_WORKSPACE;
+  const size_t room = ws ? ws_bytes : 0;
+  if (room < pl.ws_bytes && !stats && !pl.rt_forced) {  // fewer splits (a choice made by hand runs as it was made, or not at all)
+    if ((rc = make_plan(op, d, &pl, room > pl.part_offset ? room - pl.part_offset : 0)) != JZ_OK) return rc;
+    if (pl.widen) {
+      pl.widen = false;
+      pl.ws_bytes = pl.element_ws_bytes;
+    }
+    if (!runs_with_fewer_splits(op, pl.args.M, pl.args.N, pl.args.splits)) return JZ_ERR_WORKSPACE;
+  }
+  if (room < pl.ws_bytes) return JZ_ERR_WORKSPACE;
   if (pl.ws_bytes > 0 && (overlaps(ws, pl.ws_bytes, A, pl.bytesA) || overlaps(ws, pl.ws_bytes, B, pl.bytesB) ||
                           overlaps(ws, pl.ws_bytes, D, pl.bytesD)))
     return JZ_ERR_ALIAS;
@@ -1430,7 +1445,6 @@ extern "C" int jz_conv2d_bwd_weight_static(const jz_conv_desc* desc, const void*
   Plan pl;
   int rc = make_plan(JZ_BWD_WEIGHT, desc, &pl);
   if (rc != JZ_OK) return rc;
-  if ((pl.widen ? pl.element_ws_bytes : pl.ws_bytes) > kStaticScratchBytes) return JZ_ERR_WORKSPACE;  // the layer needs more scratch than the array holds
   void* ws = nullptr;
   if (pl.ws_bytes > 0 && (rc = static_scratch(&ws)) != JZ_OK) return rc;
   return run(JZ_BWD_WEIGHT, desc, dy16, x16, dw16, ws, ws ? kStaticScratchBytes : 0, hip_stream);  // A = dy, B = x

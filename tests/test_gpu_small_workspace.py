@@ -58,6 +58,55 @@ def test_single_precision_weight_gradient_that_would_leave_the_chip_idle_is_refu
     d = jz.conv_desc(16, 20, 20, 8, 8, 3, 3, 1, 1)         # one tile
     need = jz.jz_conv2d_f32_workspace_bytes(jz.JZ_BWD_WEIGHT, d)
     A = 0x10000000                                         # refused before anything is launched
+    assert need > 16
     for room in (0, need - 16):
         assert jz.lib().jz_conv2d_bwd_weight_f32(ctypes.byref(d), A, A + (1 << 28), A + (1 << 29), A + (1 << 30) if room else None, room,
                                                  None) == jz.JZ_ERR_WORKSPACE
+
+
+def call_f16(jz, op, d, a, b, out_shape, room):  # noqa: F811
+    import jzt
+    out = torch.full(out_shape, float("nan"), dtype=torch.float16, device="cuda")
+    jz.bind_conv2d(op, d, jzt.to_dev(a), jzt.to_dev(b), out, torch.empty(room, dtype=torch.uint8, device="cuda") if room else None)()
+    torch.cuda.synchronize()
+    return out.cpu().numpy()
+
+
+@pytest.mark.parametrize("part", [0.0, 0.5, 0.99])
+def test_half_precision(jz, part):  # noqa: F811
+    import jzt
+    for cfg, ops in ((FEW_TILES, (jz.JZ_FWD, jz.JZ_BWD_DATA)), (WIDE_FILTER, (jz.JZ_BWD_WEIGHT,))):
+        N, H, C, K, R = cfg
+        od, x, w, dy = operands(*cfg, np.float16)
+        d = jz.conv_desc(N, H, H, C, K, R, R, 1, R // 2)
+        for op, a, b, shape, fn in ((jz.JZ_FWD, x, w, (N, H, H, K), oracle.conv_fwd), (jz.JZ_BWD_DATA, dy, w, (N, H, H, C), oracle.conv_bwd_data),
+                                    (jz.JZ_BWD_WEIGHT, x, dy, (K, R, R, C), oracle.conv_bwd_weight)):
+            if op in ops:
+                need = jz.jz_conv2d_workspace_bytes(op, d)
+                assert need > 0, "the case has to split"
+                jzt.check_half_output(call_f16(jz, op, d, a, b, shape, int(part * need) & ~15), fn(od, a, b), 1e-3, "op %d" % op)
+
+
+def test_strided_backward_data_without_a_workspace(jz):  # noqa: F811
+    import jzt
+    od, d = oracle.conv_desc(2, 16, 15, 40, 24, 3, 3, (2, 2), (1, 1)), jz.conv_desc(2, 16, 15, 40, 24, 3, 3, 2, 1)
+    rng = inputs.rng_for(94)
+    w, dy = inputs.he_normal_f32(rng, (24, 3, 3, 40), 360).astype(np.float16), inputs.normal_f16(rng, (2, od.P, od.Q, 24))
+    jzt.check_half_output(call_f16(jz, jz.JZ_BWD_DATA, d, dy, w, (2, 16, 15, 40), 0), oracle.conv_bwd_data(od, dy, w), 1e-3, "bwd_data")
+
+
+def test_static_scratch_holds_fewer_splits_of_a_layer_that_wants_more(jz):  # noqa: F811
+    """1360 -> 72 channels, 5 x 5, 54 x 54 pixels: the plan wants more than the array's 64 MiB.  FP64 products per tap on the GPU;
+    one FP16 rounding of FP32 sums, 1e-3."""
+    N, H, C, K, R = 4, 54, 1360, 72, 5
+    d = jz.conv_desc(N, H, H, C, K, R, R, 1, 2)
+    assert jz.jz_conv2d_workspace_bytes(jz.JZ_BWD_WEIGHT, d) > jz.JZ_STATIC_SCRATCH_BYTES
+    g = torch.Generator(device="cuda").manual_seed(1)
+    x, dy = (torch.randn(N, H, H, c, generator=g, device="cuda").half() for c in (C, K))
+    dw = torch.full((K, R, R, C), float("nan"), dtype=torch.float16, device="cuda")
+    jz.jz_conv2d_bwd_weight_static(d, x, dy, dw)
+    xp = torch.nn.functional.pad(x.double(), (0, 0, 2, 2, 2, 2))
+    dy64 = dy.double().reshape(-1, K).t().contiguous()
+    want = torch.stack([torch.stack([dy64 @ xp[:, r:r + H, s:s + H].reshape(-1, C) for s in range(R)], 1) for r in range(R)], 1)
+    err = ((dw.double() - want).norm() / want.norm()).item()
+    assert err < 1e-3, err

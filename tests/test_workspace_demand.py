@@ -31,3 +31,16 @@ def test_partial_sums_of_single_precision_layers_are_bounded(jz):
                     d = jz.conv_desc(N, c.H, c.H, c.C, c.K, c.R, c.R, c.stride, c.pad)
                     for op in (jz.JZ_FWD, jz.JZ_BWD_DATA, jz.JZ_BWD_WEIGHT):
                         assert jz.jz_conv2d_f32_workspace_bytes(op, d) <= 256 * MB
+
+
+def test_partial_sums_of_half_precision_layers_are_bounded(jz):
+    for N, H, C, K, R, st in LONG:
+        C, K = C // 8 * 8, K // 8 * 8
+        d = jz.conv_desc(N, H, H, C, K, R, R, st, R // 2)
+        for op in (jz.JZ_FWD, jz.JZ_BWD_DATA, jz.JZ_BWD_WEIGHT):
+            assert jz.jz_conv2d_workspace_bytes(op, d) <= 256 * MB, (N, H, C, K, R, st, op)
+
+
+def test_strided_backward_data_of_ragged_channels_asks_for_no_workspace(jz):
+    for N, H, W, C, K, R, S, st, pad in ((2, 16, 15, 40, 24, 3, 3, 2, 1), (1, 20, 20, 8, 200, 7, 4, (3, 2), (2, 1))):
+        assert jz.jz_conv2d_workspace_bytes(jz.JZ_BWD_DATA, jz.conv_desc(N, H, W, C, K, R, S, st, pad)) == 0
