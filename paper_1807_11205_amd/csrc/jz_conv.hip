@@ -17,6 +17,7 @@
 #include <vector>
 
 #include "jz_conv_plan.h"
+#include "jz_plan_cache.h"
 #include "jz_sumsq.h"
 
 namespace {
@@ -879,54 +880,10 @@ void plan_widened(int op, const jz_conv_desc* d, Plan* pl) {
   if (need > pl->ws_bytes) pl->ws_bytes = need;
 }
 
-// Plans of the shapes this thread has used lately.  A plan depends on the operation, the descriptor and the tuning state
-// only; making one (table search, then the cost model over every variant and split count) takes 5-10 us of host time,
-// which is more than the launch itself and what a sequence of short layers was bound by (ResNet-50 at batch 8, 64 x 64
-// images: 2.9 ms of host time per step against 2.1 ms of kernels).  Fixed size (256 entries, four probes, ~150 KB per
-// thread that launches convolutions), so it cannot grow; a miss overwrites the first probe's entry.
-struct PlanCacheEntry {
-  unsigned generation = 0;  // 0: empty
-  int op = 0, rc = 0, ca = 0, cb = 0;
-  size_t limit = 0;
-  jz_conv_desc d{};
-  Plan pl;
-};
-constexpr unsigned kPlanCacheSize = 256, kPlanCacheProbes = 4;
-
-// The entry for the key (created by `fill` on a miss); ca = cb = -1 for a layer's own plan.  Valid until the thread's
-// next look-up.
-template <class F>
-const PlanCacheEntry& cached_plan(int op, const jz_conv_desc& d, int ca, int cb, size_t limit, F&& fill) {
-  thread_local std::vector<PlanCacheEntry> cache(kPlanCacheSize);
-  unsigned h = 2166136261u;
-  const int key[15] = {op, ca, cb, (int)(limit >> 4), d.N, d.H, d.W, d.C, d.K, d.R, d.S, d.stride_h, d.stride_w, d.pad_h, d.pad_w};
-  for (int v : key) h = (h ^ (unsigned)v) * 16777619u;
-  h ^= h >> 15;
-  const unsigned gen = g_tune_generation.load(std::memory_order_acquire);
-  for (unsigned i = 0; i < kPlanCacheProbes; ++i) {
-    const PlanCacheEntry& e = cache[(h + i) % kPlanCacheSize];
-    if (e.generation == gen && e.op == op && e.ca == ca && e.cb == cb && e.limit == limit && memcmp(&e.d, &d, sizeof d) == 0) return e;
-  }
-  unsigned slot = h % kPlanCacheSize;
-  for (unsigned i = 0; i < kPlanCacheProbes; ++i)
-    if (cache[(h + i) % kPlanCacheSize].generation != gen) {
-      slot = (h + i) % kPlanCacheSize;
-      break;
-    }
-  PlanCacheEntry e;
-  e.op = op; e.ca = ca; e.cb = cb; e.limit = limit;
-  e.d = d;
-  fill(e);
-  e.generation = gen;
-  cache[slot] = e;
-  return cache[slot];
-}
-
 int make_plan(int op, const jz_conv_desc* d, Plan* pl, size_t limit = kPartialSumLimit) {
   if (!d) return JZ_ERR_NULL;
-  const PlanCacheEntry& e = cached_plan(op, *d, -1, -1, limit, [&](PlanCacheEntry& n) { n.rc = compute_plan(op, d, &n.pl, limit); });
-  *pl = e.pl;
-  return e.rc;
+  return cached_plan(g_tune_generation.load(std::memory_order_acquire), PlanKey{op, -1, -1, limit, *d}, pl,
+                     [&](Plan* p) { return compute_plan(op, d, p, limit); });
 }
 
 // One parity class (ca, cb) of a strided multi-tap backward-data layer as a plan of its own (see compute_plan).  base: the
@@ -971,11 +928,8 @@ bool compute_class_plan(const jz_conv_desc* d, const Plan& base, int ca, int cb,
 }
 
 bool make_class_plan(const jz_conv_desc* d, const Plan& base, int ca, int cb, Plan* pl) {
-  const PlanCacheEntry& e = cached_plan(JZ_BWD_DATA, *d, ca, cb, 0, [&](PlanCacheEntry& n) {
-    n.rc = compute_class_plan(d, base, ca, cb, &n.pl) ? 1 : 0;
-  });
-  if (e.rc) *pl = e.pl;
-  return e.rc != 0;
+  return cached_plan(g_tune_generation.load(std::memory_order_acquire), PlanKey{JZ_BWD_DATA, ca, cb, 0, *d}, pl,
+                     [&](Plan* p) { return compute_class_plan(d, base, ca, cb, p) ? 1 : 0; }) != 0;
 }
 
 // slabs of rows whose sums a split reduction leaves (splitk_reduce_stats): at most 64, so that the normalization's apply pass

@@ -24,10 +24,10 @@
 #include <algorithm>
 #include <atomic>
 #include <type_traits>
-#include <vector>
 
 #include "jz_igemm.h"
 #include "jz_internal.h"
+#include "jz_plan_cache.h"
 
 namespace {
 using namespace jz;
@@ -433,6 +433,8 @@ bool class_args_f32(const jz_conv_desc* d, const PlanF32& base, int ca, int cb, 
   const int r0 = (ca + d->pad_h) % sh, s0 = (cb + d->pad_w) % sw;
   *pl = base;
   F32Args& a = pl->args;
+  a.A = a.B = nullptr;
+  a.D = a.Dpart = nullptr;
   ConvGeom& g = a.g;
   g.R = (d->R - r0 + sh - 1) / sh; g.S = (d->S - s0 + sw - 1) / sw;
   g.OH = Ha; g.OW = Wb; g.sh = g.sw = 1;
@@ -445,7 +447,7 @@ bool class_args_f32(const jz_conv_desc* d, const PlanF32& base, int ca, int cb, 
   return true;
 }
 
-int make_plan_f32(int op, const jz_conv_desc* d, PlanF32* pl, size_t limit = kPartialSumLimit);
+int compute_plan_f32(int op, const jz_conv_desc* d, PlanF32* pl, size_t limit);
 
 // Channels rounded up to 4 on copies, when that adds at most half to the multiply-adds.
 void plan_widened_f32(int op, const jz_conv_desc* d, PlanF32* pl) {
@@ -454,7 +456,7 @@ void plan_widened_f32(int op, const jz_conv_desc* d, PlanF32* pl) {
   if (op != JZ_FWD) w.K = (d->K + 3) & ~3;  // forward takes any number of output channels
   if ((w.C == d->C && w.K == d->K) || (double)w.C * w.K > 1.5 * d->C * d->K) return;
   PlanF32 in;
-  if (make_plan_f32(op, &w, &in) != JZ_OK || !in.dma) return;
+  if (compute_plan_f32(op, &w, &in, kPartialSumLimit) != JZ_OK || !in.dma) return;
   const bool x_wide = w.C != d->C, y_wide = w.K != d->K;
   const size_t nx = up256f((size_t)d->N * d->H * d->W * w.C * 4), nw = up256f((size_t)w.K * d->R * d->S * w.C * 4);
   const size_t ny = op == JZ_FWD ? 0 : up256f(pl->bytesA / d->K * w.K);
@@ -469,7 +471,7 @@ void plan_widened_f32(int op, const jz_conv_desc* d, PlanF32* pl) {
 
 int out_dim(int in, int pad, int f, int st) { return (in + 2 * pad - f) / st + 1; }
 
-int make_plan_f32(int op, const jz_conv_desc* d, PlanF32* pl, size_t limit) {
+int compute_plan_f32(int op, const jz_conv_desc* d, PlanF32* pl, size_t limit) {
   if (!d) return JZ_ERR_NULL;
   if (op != JZ_FWD && op != JZ_BWD_DATA && op != JZ_BWD_WEIGHT) return JZ_ERR_UNSUPPORTED;
   if (d->N <= 0 || d->H <= 0 || d->W <= 0 || d->C <= 0 || d->K <= 0 || d->R <= 0 || d->S <= 0 || d->stride_h <= 0 ||
@@ -561,6 +563,17 @@ int make_plan_f32(int op, const jz_conv_desc* d, PlanF32* pl, size_t limit) {
   return JZ_OK;
 }
 
+int make_plan_f32(int op, const jz_conv_desc* d, PlanF32* pl, size_t limit = kPartialSumLimit) {
+  if (!d) return JZ_ERR_NULL;
+  return cached_plan(1, PlanKey{op, -1, -1, limit, *d}, pl, [&](PlanF32* p) { return compute_plan_f32(op, d, p, limit); });
+}
+// residues of larger strides are planned anew by every call: they would fill the table
+constexpr int kKeptResidues = 16;
+bool make_class_plan_f32(const jz_conv_desc* d, const PlanF32& base, int ca, int cb, PlanF32* pl) {
+  if ((long long)d->stride_h * d->stride_w > kKeptResidues) return class_args_f32(d, base, ca, cb, pl);
+  return cached_plan(1, PlanKey{JZ_BWD_DATA, ca, cb, 0, *d}, pl, [&](PlanF32* p) { return class_args_f32(d, base, ca, cb, p) ? 1 : 0; }) != 0;
+}
+
 template <int OP, int BM, int BN, bool GEN>
 int launch_f32_dma(const F32Args& a, hipStream_t st) {
   constexpr size_t smem = (size_t)FD_NST * (BM + BN) * FD_BK * 4;
@@ -633,7 +646,6 @@ int run_f32(int op, const jz_conv_desc* d, const void* A, const void* B, void* D
   }
   const size_t room = ws ? ws_bytes : 0;
   if (room < pl.ws_bytes) {  // fewer splits
-    pl = PlanF32{};
     if ((rc = make_plan_f32(op, d, &pl, room)) != JZ_OK) return rc;
     if (pl.widen) {
       pl.widen = false;
@@ -652,28 +664,39 @@ int run_f32(int op, const jz_conv_desc* d, const void* A, const void* B, void* D
   a.D = static_cast<float*>(D);
   a.Dpart = static_cast<float*>(ws);
   if (pl.classes) {
-    // residues in launches of at most FD_MAX_SET, those with the most taps (the last ones to start would end last) first
-    std::vector<PlanF32> cps;
-    for (int ca = 0; ca < d->stride_h; ++ca)
-      for (int cb = 0; cb < d->stride_w; ++cb) {
-        PlanF32 cp;
-        if (class_args_f32(d, pl, ca, cb, &cp)) cps.push_back(cp);
+    // residues in launches of at most FD_MAX_SET, those with the most taps (the last ones to start would end last) first: along
+    // an axis they have ceil(R / stride) taps or one less
+    F32Set set{};
+    int k = 0;
+    auto flush = [&] {
+      for (int j = k; j < FD_MAX_SET; ++j) {
+        set.c[j] = set.c[0];
+        set.first[j + 1] = set.first[j];
       }
-    std::stable_sort(cps.begin(), cps.end(), [](const PlanF32& x, const PlanF32& y) { return x.args.Kred > y.args.Kred; });
-    for (size_t i = 0; i < cps.size() && rc == JZ_OK; i += FD_MAX_SET) {
-      F32Set set{};
-      for (int k = 0; k < FD_MAX_SET; ++k) {
-        const size_t at = i + k < cps.size() ? i + k : cps.size() - 1;
-        set.c[k] = cps[at].args;
-        set.first[k + 1] = set.first[k] + (i + k < cps.size() ? (unsigned)(set.c[k].tiles_m * set.c[k].tiles_n) : 0u);
-      }
+      k = 0;
       const int v = (pl.gen ? 4 : 0) + (pl.BM == 128 ? 2 : 0) + (pl.BN == 128 ? 1 : 0);
-      rc = v == 0 ? launch_f32_set<64, 64, false>(set, st) : v == 1 ? launch_f32_set<64, 128, false>(set, st)
-         : v == 2 ? launch_f32_set<128, 64, false>(set, st) : v == 3 ? launch_f32_set<128, 128, false>(set, st)
-         : v == 4 ? launch_f32_set<64, 64, true>(set, st) : v == 5 ? launch_f32_set<64, 128, true>(set, st)
-         : v == 6 ? launch_f32_set<128, 64, true>(set, st) : launch_f32_set<128, 128, true>(set, st);
-    }
-    return rc;
+      return v == 0 ? launch_f32_set<64, 64, false>(set, st) : v == 1 ? launch_f32_set<64, 128, false>(set, st)
+           : v == 2 ? launch_f32_set<128, 64, false>(set, st) : v == 3 ? launch_f32_set<128, 128, false>(set, st)
+           : v == 4 ? launch_f32_set<64, 64, true>(set, st) : v == 5 ? launch_f32_set<64, 128, true>(set, st)
+           : v == 6 ? launch_f32_set<128, 64, true>(set, st) : launch_f32_set<128, 128, true>(set, st);
+    };
+    const int Rm = (d->R + d->stride_h - 1) / d->stride_h, Sm = (d->S + d->stride_w - 1) / d->stride_w;
+    const bool rows_first = (Rm - 1) * Sm >= Rm * (Sm - 1);
+    const int taps[4][2] = {{Rm, Sm}, {rows_first ? Rm - 1 : Rm, rows_first ? Sm : Sm - 1}, {rows_first ? Rm : Rm - 1, rows_first ? Sm - 1 : Sm}, {Rm - 1, Sm - 1}};
+    for (const auto& t : taps)
+      for (int ca = 0; ca < d->stride_h; ++ca) {
+        if ((d->R - (ca + d->pad_h) % d->stride_h + d->stride_h - 1) / d->stride_h != t[0]) continue;
+        for (int cb = 0; cb < d->stride_w; ++cb) {
+          PlanF32 cp;
+          if ((d->S - (cb + d->pad_w) % d->stride_w + d->stride_w - 1) / d->stride_w != t[1] || !make_class_plan_f32(d, pl, ca, cb, &cp)) continue;
+          F32Args& c = set.c[k];
+          c = cp.args;
+          c.A = a.A; c.B = a.B; c.D = a.D; c.Dpart = nullptr;
+          set.first[k + 1] = set.first[k] + (unsigned)(c.tiles_m * c.tiles_n);
+          if (++k == FD_MAX_SET && (rc = flush()) != JZ_OK) return rc;
+        }
+      }
+    return k > 0 ? flush() : JZ_OK;
   }
   if (op == JZ_FWD) rc = launch_f32<OP_FWD>(pl, st);
   else if (op == JZ_BWD_DATA) rc = launch_f32<OP_BWD_DATA>(pl, st);
