@@ -22,7 +22,6 @@
 #include <math.h>
 
 #include <algorithm>
-#include <atomic>
 #include <type_traits>
 
 #include "jz_igemm.h"
@@ -577,13 +576,8 @@ bool make_class_plan_f32(const jz_conv_desc* d, const PlanF32& base, int ca, int
 template <int OP, int BM, int BN, bool GEN>
 int launch_f32_dma(const F32Args& a, hipStream_t st) {
   constexpr size_t smem = (size_t)FD_NST * (BM + BN) * FD_BK * 4;
-  static std::atomic<bool> attr_set{false};  // per instantiation; setting it twice is harmless
-  if (!attr_set.load(std::memory_order_relaxed)) {
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(&f32_dma_kernel<OP, BM, BN, GEN>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)smem) != hipSuccess)
-      return JZ_ERR_LAUNCH;
-    attr_set.store(true, std::memory_order_relaxed);
-  }
+  static std::atomic<bool> lds_set{false};
+  if (!allow_lds(reinterpret_cast<const void*>(&f32_dma_kernel<OP, BM, BN, GEN>), smem, lds_set)) return JZ_ERR_LAUNCH;
   hipLaunchKernelGGL((f32_dma_kernel<OP, BM, BN, GEN>), dim3((unsigned)(a.full_rows + (a.tiles_m - a.full_rows) * a.splits) * (unsigned)a.tiles_n), dim3(256), smem, st, a);
   return jz::launch_status();
 }
@@ -591,13 +585,8 @@ int launch_f32_dma(const F32Args& a, hipStream_t st) {
 template <int BM, int BN, bool GEN>
 int launch_f32_set(const F32Set& set, hipStream_t st) {
   constexpr size_t smem = (size_t)FD_NST * (BM + BN) * FD_BK * 4;
-  static std::atomic<bool> attr_set{false};
-  if (!attr_set.load(std::memory_order_relaxed)) {
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(&f32_dma_set_kernel<BM, BN, GEN>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)smem) != hipSuccess)
-      return JZ_ERR_LAUNCH;
-    attr_set.store(true, std::memory_order_relaxed);
-  }
+  static std::atomic<bool> lds_set{false};
+  if (!allow_lds(reinterpret_cast<const void*>(&f32_dma_set_kernel<BM, BN, GEN>), smem, lds_set)) return JZ_ERR_LAUNCH;
   hipLaunchKernelGGL((f32_dma_set_kernel<BM, BN, GEN>), dim3(set.first[FD_MAX_SET]), dim3(256), smem, st, set);
   return jz::launch_status();
 }

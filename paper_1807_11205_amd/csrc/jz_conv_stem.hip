@@ -160,13 +160,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
 
 template <int NT, int TM, int NKS, int WPE>
 int launch_stem(const StemArgs& a, hipStream_t st) {
-  static bool attr_set = false;
-  if (!attr_set) {
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(&stem_fwd_kernel<NT, TM, NKS, WPE>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            160 * 1024) != hipSuccess)
-      return JZ_ERR_LAUNCH;
-    attr_set = true;
-  }
+  static std::atomic<bool> lds_set{false};
+  if (!jz::allow_lds(reinterpret_cast<const void*>(&stem_fwd_kernel<NT, TM, NKS, WPE>), 160 * 1024, lds_set)) return JZ_ERR_LAUNCH;
   hipLaunchKernelGGL((stem_fwd_kernel<NT, TM, NKS, WPE>), dim3((unsigned)a.grid), dim3(256), a.lds_w_bytes + a.lds_p_bytes, st, a);
   return jz::launch_status();
 }

@@ -452,13 +452,8 @@ int launch_one(const GemmArgs& a, hipStream_t st) {
   constexpr size_t tile_bytes = 2 * (size_t)(BM + BN) * LDK * sizeof(unsigned short);
   constexpr size_t epi_bytes = (size_t)BM * (BN + 8) * sizeof(unsigned short);
   constexpr size_t smem = tile_bytes > epi_bytes ? tile_bytes : epi_bytes;
-  static bool attr_set = false;  // per instantiation; setting it twice is harmless
-  if (!attr_set) {
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(&igemm_kernel<OP, BM, BN>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) != hipSuccess)
-      return JZ_ERR_LAUNCH;
-    attr_set = true;
-  }
+  static std::atomic<bool> lds_set{false};
+  if (!jz::allow_lds(reinterpret_cast<const void*>(&igemm_kernel<OP, BM, BN>), smem, lds_set)) return JZ_ERR_LAUNCH;
   unsigned grid = (unsigned)a.tiles_m * (unsigned)a.tiles_n * (unsigned)a.splits;
   hipLaunchKernelGGL((igemm_kernel<OP, BM, BN>), dim3(grid), dim3(THREADS), smem, st, a);
   return jz::launch_status();
@@ -470,22 +465,12 @@ int launch_dma(const GemmArgs& a, hipStream_t st, const GemmSet* set = nullptr) 
   constexpr size_t epi_bytes = (size_t)BM / dma_epass(BM, BN) * (BN + 8) * sizeof(unsigned short);
   constexpr size_t smem = ring_bytes > epi_bytes ? ring_bytes : epi_bytes;
   static_assert(smem <= 160 * 1024, "more LDS than a compute unit has");
-  static bool attr_set = false;
-  if (!attr_set) {
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(&igemm_dma_kernel<OP, BM, BN, TBK, NST, MASKA, WGM, WGN, GEN, FLAT>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) != hipSuccess)
-      return JZ_ERR_LAUNCH;
-    attr_set = true;
-  }
+  static std::atomic<bool> lds_set{false};
+  if (!jz::allow_lds(reinterpret_cast<const void*>(&igemm_dma_kernel<OP, BM, BN, TBK, NST, MASKA, WGM, WGN, GEN, FLAT>), smem, lds_set)) return JZ_ERR_LAUNCH;
   if constexpr (OP == OP_BWD_DATA && !GEN && !MASKA) {
     if (set) {
-      static bool set_attr = false;
-      if (!set_attr) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void*>(&igemm_dma_set_kernel<OP, BM, BN, TBK, NST, WGM, WGN, FLAT>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) != hipSuccess)
-          return JZ_ERR_LAUNCH;
-        set_attr = true;
-      }
+      static std::atomic<bool> set_lds_set{false};
+      if (!jz::allow_lds(reinterpret_cast<const void*>(&igemm_dma_set_kernel<OP, BM, BN, TBK, NST, WGM, WGN, FLAT>), smem, set_lds_set)) return JZ_ERR_LAUNCH;
       hipLaunchKernelGGL((igemm_dma_set_kernel<OP, BM, BN, TBK, NST, WGM, WGN, FLAT>), dim3(set->first[kGemmSet]), dim3(64 * WGM * WGN), smem, st, *set);
       return jz::launch_status();
     }

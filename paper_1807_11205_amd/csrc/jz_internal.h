@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
+
 #include "jz.h"
 
 namespace jz {
@@ -52,6 +54,15 @@ constexpr size_t kPartialSumLimit = size_t(256) << 20;
 constexpr long long kFewSplitsGrid = 256;
 inline bool runs_with_fewer_splits(int op, int M, int N, int splits) {
   return op != JZ_BWD_WEIGHT || (long long)((M + 63) / 64) * ((N + 63) / 64) * splits >= kFewSplitsGrid;
+}
+
+// Lets a kernel use `bytes` of dynamic LDS, at its first launch.  done: one per kernel, shared by all threads (setting the
+// attribute twice is harmless).
+inline bool allow_lds(const void* kernel, size_t bytes, std::atomic<bool>& done) {
+  if (done.load(std::memory_order_relaxed)) return true;
+  if (hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) != hipSuccess) return false;
+  done.store(true, std::memory_order_relaxed);
+  return true;
 }
 
 inline int launch_status() { return hipGetLastError() == hipSuccess ? JZ_OK : JZ_ERR_LAUNCH; }
