@@ -22,7 +22,7 @@ import time
 import numpy as np
 import torch
 
-from paper_1807_11205_amd import api, inputs, shapes, tune
+from paper_1807_11205_amd import api, inputs, shapes
 
 FP16_MFMA_PEAK_TFLOPS = 2500.0   # MI355X dense fp16 matrix peak
 FP32_MFMA_PEAK_TFLOPS = 157.3    # MI355X dense fp32 matrix peak
@@ -36,7 +36,7 @@ class ResNet50Step:
     """All device buffers of one ResNet-50 N=batch step and the launch sequence."""
 
     def __init__(self, batch=64, loss_scale=1024.0, seed=180711205, variant="v1", device="cuda:0", dtype="f16", lars_path="presummed",
-                 sumsq_from="split"):
+                 sumsq_from="split", beside=False):
         """dtype "f32": the single-precision variant of the GEMM phase (float32 activations, filters = the master weights,
         float32 weight gradients in a buffer of their own; the LARS update still runs on the fp16 gradient buffer).
         lars_path "presummed": the update is one launch (jz_lars_mp_update_presummed).  The gradient sums of squares it needs
@@ -45,8 +45,10 @@ class ResNet50Step:
         registers there); every other tensor (unsplit filters, batch-norm scale / shift, bias) is covered by one
         jz_lars_grad_sumsq launch behind the last backward-data launch, beside the last backward-weight launches.
         "all": every backward-weight launch leaves its sum (unsplit ones through a separate pass over the gradient).
-        "three_launches": plain backward-weight, jz_lars_mp_update."""
+        "three_launches": plain backward-weight, jz_lars_mp_update.
+        beside: weight gradients on side streams split their reductions for a part of the chip (jz_conv2d_bwd_weight_beside)."""
         self.f32 = dtype == "f32"
+        self.beside = bool(beside) and not self.f32
         self.presummed = lars_path == "presummed" and not self.f32
         self.sumsq_from = sumsq_from
         self.N = batch
@@ -98,7 +100,7 @@ class ResNet50Step:
                      y=torch.empty(batch * cs.P * cs.P * cs.K, dtype=h, device=device),
                      dx=None if cs.first else torch.empty(batch * cs.H * cs.H * cs.C, dtype=h, device=device),
                      w=wsrc[a:b], dw=gdst[a:b], calls={})
-            for op in (api.JZ_FWD, api.JZ_BWD_DATA, api.JZ_BWD_WEIGHT):
+            for op in (api.JZ_FWD, api.JZ_BWD_DATA, api.JZ_BWD_WEIGHT) + ((api.JZ_BWD_WEIGHT | api.JZ_BESIDE,) if self.beside else ()):
                 ws_bytes = max(ws_bytes, ws_conv(op, d))
             self.flops += 2 * cs.macs(batch) * (2 if cs.first else 3)
             self.layers.append(L)
@@ -110,6 +112,8 @@ class ResNet50Step:
                                 w=wsrc[a:b], dw=gdst[a:b], calls={}))
         for op in (api.JZ_FWD, api.JZ_BWD_DATA, api.JZ_BWD_WEIGHT):
             ws_bytes = max(ws_bytes, ws_fc(op, B, I, O))
+        if self.beside:
+            ws_bytes = max(ws_bytes, api.jz_conv2d_workspace_bytes(api.JZ_BWD_WEIGHT | api.JZ_BESIDE, api.conv_desc(B, 1, 1, I, O, 1, 1)))
         self.flops += 2 * self.fc.macs(batch) * 3
         self.ws = torch.empty(max(ws_bytes, 16), dtype=torch.uint8, device=device)
         self.side_ws = [torch.empty(max(ws_bytes, 16), dtype=torch.uint8, device=device) for _ in range(3)]
@@ -117,7 +121,7 @@ class ResNet50Step:
         if self.presummed:
             for L in self.layers:
                 d = L["d"] if L["kind"] == "conv" else api.conv_desc(B, 1, 1, I, O, 1, 1)
-                split = ", 1 splits" not in api.jz_conv2d_describe_plan(api.JZ_BWD_WEIGHT, d)
+                split = ", 1 splits" not in api.jz_conv2d_describe_plan(self.weight_op(), d)
                 L["sumsq"] = self.sumsq_from == "all" or (self.sumsq_from == "split" and split)
                 if L["sumsq"]:
                     self.flags[L["tensor"]] |= api.JZ_PARAM_GRAD_PRESUMMED
@@ -132,12 +136,20 @@ class ResNet50Step:
         hp = inputs.HPARAMS
         return api.lars_hparams(hp["lr"], hp["momentum"], hp["weight_decay"], hp["trust_coef"], self.loss_scale)
 
+    def weight_op(self):
+        """What the weight gradients on side streams are planned as."""
+        return api.JZ_BWD_WEIGHT | api.JZ_BESIDE if self.beside else api.JZ_BWD_WEIGHT
+
     def _bound(self, L, op, ws):
         """The layer's forward / backward-data / backward-weight call with its arguments marshalled once."""
         B, I, O = self.N, self.fc.I, self.fc.O
         key = (op, ws.data_ptr())
         if key not in L["calls"]:
-            if self.presummed and op == api.JZ_BWD_WEIGHT and L.get("sumsq"):
+            if op == api.JZ_BWD_WEIGHT | api.JZ_BESIDE:
+                d = L["d"] if L["kind"] == "conv" else api.conv_desc(B, 1, 1, I, O, 1, 1)
+                sink = api.jz_lars_sumsq_sink(self.ps, self.lars_ws, L["tensor"]) if self.presummed and L.get("sumsq") else None
+                L["calls"][key] = api.bind_conv2d_bwd_weight_beside(d, L["x"], L["dy"], L["dw"], ws, sink)
+            elif self.presummed and op == api.JZ_BWD_WEIGHT and L.get("sumsq"):
                 sink = api.jz_lars_sumsq_sink(self.ps, self.lars_ws, L["tensor"])
                 if L["kind"] == "conv":
                     L["calls"][key] = api.bind_conv2d_bwd_weight_sumsq(L["d"], L["x"], L["dy"], L["dw"], sink, ws)
@@ -209,7 +221,7 @@ class ResNet50Step:
         unsplit_done = {}
         for k, L in enumerate(reversed(self.layers)):
             si = 1 + k % n_side
-            prog += [("wait", ready, si), ("launch", self._bound(L, api.JZ_BWD_WEIGHT, self.side_ws[si - 1]), si)]
+            prog += [("wait", ready, si), ("launch", self._bound(L, self.weight_op(), self.side_ws[si - 1]), si)]
             if self.presummed and not L.get("sumsq"):
                 unsplit_done[si] = len(prog)                    # the last launch on this side stream that `rest` reads from
             if not L.get("first"):
@@ -372,7 +384,7 @@ class AlexNetStep:
     """configs[3]: the AlexNet-shaped layers (five convolutions, ungrouped, and the three FC GEMMs) at N = 128, forward,
     backward-data and backward-weight of every layer on independent seeded N(0,1) inputs, He-normal weights.  Same launch
     scheme as the ResNet-50 step: forward and the backward-data chain in network order on one stream, backward-weight
-    round-robin on the side streams.  ws_bytes: size of each stream's workspace (default: what the current plans need;
+    round-robin on the side streams, splitting for a part of the chip if there are several.  ws_bytes: size of each stream's workspace (default: what the current plans need;
     a tuning run that tries other split counts passes more)."""
 
     def __init__(self, batch=128, n_side=2, ws_bytes=None):
@@ -382,19 +394,21 @@ class AlexNetStep:
         gen.manual_seed(7)
         randn = lambda n, std=1.0: (torch.randn(n, generator=gen, device=dev) * std).to(h)
         layers, flops, need = [], 0, 0
+        self.weight_op = api.JZ_BWD_WEIGHT | api.JZ_BESIDE if n_side > 1 else api.JZ_BWD_WEIGHT
         for cs in shapes.alexnet_convs():
             d = api.conv_desc(B, cs.H, cs.H, cs.C, cs.K, cs.R, cs.R, cs.stride, cs.pad)
             nx, ny, nw = B * cs.H * cs.H * cs.C, B * cs.P * cs.P * cs.K, cs.K * cs.R * cs.R * cs.C
             layers.append(dict(kind="conv", name=cs.name, d=d, first=cs.first, x=randn(nx), dy=randn(ny),
                                w=randn(nw, float(np.sqrt(2.0 / (cs.R * cs.R * cs.C)))), y=torch.empty(ny, dtype=h, device=dev),
                                dx=None if cs.first else torch.empty(nx, dtype=h, device=dev), dw=torch.empty(nw, dtype=h, device=dev)))
-            need = max([need] + [api.jz_conv2d_workspace_bytes(op, d) for op in (api.JZ_FWD, api.JZ_BWD_DATA, api.JZ_BWD_WEIGHT)])
+            need = max([need] + [api.jz_conv2d_workspace_bytes(op, d) for op in (api.JZ_FWD, api.JZ_BWD_DATA, api.JZ_BWD_WEIGHT, self.weight_op)])
             flops += 2 * cs.macs(B) * (2 if cs.first else 3)
         for fc in shapes.ALEXNET_FCS:
             layers.append(dict(kind="fc", name=fc.name, I=fc.I, O=fc.O, first=False, x=randn(B * fc.I), dy=randn(B * fc.O),
                                w=randn(fc.I * fc.O, float(np.sqrt(2.0 / fc.I))), y=torch.empty(B * fc.O, dtype=h, device=dev),
                                dx=torch.empty(B * fc.I, dtype=h, device=dev), dw=torch.empty(fc.I * fc.O, dtype=h, device=dev)))
-            need = max([need] + [api.jz_gemm_fc_workspace_bytes(op, B, fc.I, fc.O) for op in (api.JZ_FWD, api.JZ_BWD_DATA, api.JZ_BWD_WEIGHT)])
+            d = api.conv_desc(B, 1, 1, fc.I, fc.O, 1, 1)
+            need = max([need] + [api.jz_conv2d_workspace_bytes(op, d) for op in (api.JZ_FWD, api.JZ_BWD_DATA, api.JZ_BWD_WEIGHT, self.weight_op)])
             flops += 2 * fc.macs(B) * 3
         self.layers, self.flops = layers, flops
         self.wss = [torch.empty(max(ws_bytes or need, 16), dtype=torch.uint8, device=dev) for _ in range(n_side + 1)]
@@ -405,7 +419,7 @@ class AlexNetStep:
             si = 1 + k % n_side if n_side else 0
             if n_side:
                 prog.append(("wait", ready, si))
-            prog.append(("launch", self.bound(L, api.JZ_BWD_WEIGHT, self.wss[si]), si))
+            prog.append(("launch", self.bound(L, self.weight_op, self.wss[si]), si))
             if not L["first"]:
                 prog.append(("launch", self.bound(L, api.JZ_BWD_DATA, self.wss[0]), 0))
                 if n_side:
@@ -417,6 +431,9 @@ class AlexNetStep:
         self.prog = prog
 
     def bound(self, L, op, ws):
+        if op == api.JZ_BWD_WEIGHT | api.JZ_BESIDE:
+            d = L["d"] if L["kind"] == "conv" else api.conv_desc(self.N, 1, 1, L["I"], L["O"], 1, 1)
+            return api.bind_conv2d_bwd_weight_beside(d, L["x"], L["dy"], L["dw"], ws)
         if L["kind"] == "conv":
             a, b, o = {api.JZ_FWD: ("x", "w", "y"), api.JZ_BWD_DATA: ("dy", "w", "dx"), api.JZ_BWD_WEIGHT: ("x", "dy", "dw")}[op]
             return api.bind_conv2d(op, L["d"], L[a], L[b], L[o], ws)
@@ -439,9 +456,6 @@ def alexnet_workload(args):
     """bench.py --workload alexnet: times AlexNetStep.  One JSON line; no LARS phase (the configuration names none)."""
     B = args.batch
     n_side = max(0, min(args.streams, 4) - 1)
-    if n_side > 1:   # weight gradients on two side streams: launches that leave room for each other
-        tune.share_chip([api.conv_desc(B, c.H, c.H, c.C, c.K, c.R, c.R, c.stride, c.pad) for c in shapes.alexnet_convs()] +
-                        [api.conv_desc(B, 1, 1, f.I, f.O, 1, 1) for f in shapes.ALEXNET_FCS])
     wl = AlexNetStep(B, n_side)
     layers, flops, prog = wl.layers, wl.flops, wl.prog
     rows = None
@@ -674,7 +688,8 @@ def time_steps(wl, stream, side, steps, warmup, graph=0):
 
 def plans_digest(wl):
     """A fingerprint of how the library would run every launch of the step (kernel variant, tiles, splits per layer and
-    op): a traffic figure measured under one set of plans says nothing about another."""
+    op; weight gradients as they run on the side streams): a traffic figure measured under one set of plans says nothing
+    about another."""
     import hashlib
     hsh = hashlib.sha256()
     B, I, O = wl.N, wl.fc.I, wl.fc.O
@@ -683,7 +698,7 @@ def plans_digest(wl):
             if L.get("first") and op == api.JZ_BWD_DATA:
                 continue
             d = L["d"] if L["kind"] == "conv" else api.conv_desc(B, 1, 1, I, O, 1, 1)
-            hsh.update(api.jz_conv2d_describe_plan(op, d).encode())
+            hsh.update(api.jz_conv2d_describe_plan(wl.weight_op() if op == api.JZ_BWD_WEIGHT else op, d).encode())
     return hsh.hexdigest()[:16]
 
 
@@ -773,10 +788,8 @@ def main():
     if args.workload == "chain":
         chain_workload(args)
         return
-    if args.streams > 2 and args.dtype == "f16":   # weight gradients on two side streams: launches that leave room for each other
-        tune.share_chip([api.conv_desc(args.batch, c.H, c.H, c.C, c.K, c.R, c.R, c.stride, c.pad) for c in shapes.resnet50_convs(args.variant)] +
-                        [api.conv_desc(args.batch, 1, 1, shapes.RESNET50_FC.I, shapes.RESNET50_FC.O, 1, 1)])
-    wl = ResNet50Step(batch=args.batch, dtype=args.dtype, lars_path=args.lars_path, sumsq_from=args.sumsq_from, variant=args.variant)
+    beside = args.streams > 2     # weight gradients on two side streams: launches that leave room for each other
+    wl = ResNet50Step(batch=args.batch, dtype=args.dtype, lars_path=args.lars_path, sumsq_from=args.sumsq_from, variant=args.variant, beside=beside)
     if args.plans_digest:
         print(plans_digest(wl))
         return
@@ -849,7 +862,7 @@ def main():
     if wl.presummed and not args.no_alt:
         # the same step with the other update path (plain backward-weight launches, three-launch update), a run of its own:
         # what the one-launch update costs the GEMM phase and what it saves behind it
-        wl3 = ResNet50Step(batch=args.batch, loss_scale=wl.loss_scale, lars_path="three_launches", variant=args.variant)   # the scale after back-off
+        wl3 = ResNet50Step(batch=args.batch, loss_scale=wl.loss_scale, lars_path="three_launches", variant=args.variant, beside=beside)   # the scale after back-off
         if args.dynamic_loss_scale:
             wl3.use_dynamic_loss_scale()
         t3 = time_steps(wl3, stream, side, args.steps, args.warmup)

@@ -54,6 +54,8 @@ enum {
 };
 
 enum { JZ_FWD = 0, JZ_BWD_DATA = 1, JZ_BWD_WEIGHT = 2 };
+/* JZ_BWD_WEIGHT | JZ_BESIDE in jz_conv2d_workspace_bytes and jz_conv2d_describe_plan: jz_conv2d_bwd_weight_beside */
+enum { JZ_BESIDE = 16 };
 
 /* One convolution layer: x[N,H,W,C] (*) w[K,R,S,C] -> y[N,P,Q,K]. */
 typedef struct {
@@ -116,6 +118,15 @@ typedef struct {
 } jz_sumsq_sink;
 int jz_conv2d_bwd_weight_sumsq(const jz_conv_desc* desc, const void* x16, const void* dy16, void* dw16, void* ws,
                                size_t ws_bytes, const jz_sumsq_sink* sink, void* hip_stream);
+
+/* jz_conv2d_bwd_weight for a launch that runs beside others on streams of their own, as the weight gradients of a training step
+ * do beside the backward-data chain.  Alone a weight gradient is fastest when the splits of its reduction fill the chip; beside
+ * other work it then only takes compute units from it, and writes more partial sums.  This call splits for half of the chip
+ * (or as recorded for the layer by a tuning run inside such a step).  Same sums, in another order where the splits differ.
+ * Workspace: jz_conv2d_workspace_bytes(JZ_BWD_WEIGHT | JZ_BESIDE, ...).  sink: as in jz_conv2d_bwd_weight_sumsq, or NULL.  A
+ * fully connected layer is the 1x1 convolution {batch, 1, 1, in_features, out_features, 1, 1, 1, 1, 0, 0}. */
+int jz_conv2d_bwd_weight_beside(const jz_conv_desc* desc, const void* x16, const void* dy16, void* dw16, void* ws,
+                                size_t ws_bytes, const jz_sumsq_sink* sink, void* hip_stream);
 
 /* jz_conv2d_bwd_weight for callers that cannot allocate device memory (code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc) and therefore have no workspace to pass: same kernels, same bits, with the

@@ -17,11 +17,12 @@ JZ_OK = 0
 JZ_ERR_NULL, JZ_ERR_SHAPE, JZ_ERR_UNSUPPORTED, JZ_ERR_WORKSPACE = -1, -2, -3, -4
 JZ_ERR_ALIGN, JZ_ERR_ALIAS, JZ_ERR_LAUNCH, JZ_ERR_NOT_PREPARED = -5, -6, -7, -8
 JZ_FWD, JZ_BWD_DATA, JZ_BWD_WEIGHT = 0, 1, 2
+JZ_BESIDE = 16
 JZ_PARAM_WEIGHT_DECAY, JZ_PARAM_LARS, JZ_PARAM_GRAD_PRESUMMED = 1, 2, 4
 
 EXPORTS = [
     "jz_conv2d_workspace_bytes", "jz_conv2d_describe_plan", "jz_conv2d_tune_set", "jz_conv2d_tune_use_table", "jz_conv2d_tune_clear", "jz_conv2d_fwd", "jz_conv2d_bwd_data", "jz_conv2d_bwd_weight", "jz_conv2d_bwd_weight_static",
-    "jz_conv2d_bwd_weight_sumsq", "jz_gemm_fc_workspace_bytes", "jz_gemm_fc", "jz_gemm_fc_bwd_weight_sumsq",
+    "jz_conv2d_bwd_weight_sumsq", "jz_conv2d_bwd_weight_beside", "jz_gemm_fc_workspace_bytes", "jz_gemm_fc", "jz_gemm_fc_bwd_weight_sumsq",
     "jz_conv2d_f32_workspace_bytes", "jz_conv2d_fwd_f32", "jz_conv2d_bwd_data_f32", "jz_conv2d_bwd_weight_f32",
     "jz_gemm_fc_f32_workspace_bytes", "jz_gemm_fc_f32",
     "jz_lars_workspace_bytes", "jz_lars_prepare", "jz_lars_mp_update", "jz_loss_scale_init", "jz_lars_mp_update_dyn",
@@ -102,6 +103,7 @@ def lib() -> ctypes.CDLL:
         L.jz_conv2d_bwd_weight_static.argtypes = [dp, vp, vp, vp, vp]
         sk = ctypes.POINTER(jz_sumsq_sink)
         L.jz_conv2d_bwd_weight_sumsq.argtypes = [dp, vp, vp, vp, vp, sz, sk, vp]
+        L.jz_conv2d_bwd_weight_beside.argtypes = [dp, vp, vp, vp, vp, sz, sk, vp]
         L.jz_gemm_fc_bwd_weight_sumsq.argtypes = [ci, ci, ci, vp, vp, vp, vp, sz, sk, vp]
         L.jz_conv2d_f32_workspace_bytes.argtypes = [ci, dp, ctypes.POINTER(sz)]
         for name in ("jz_conv2d_fwd_f32", "jz_conv2d_bwd_data_f32", "jz_conv2d_bwd_weight_f32"):
@@ -529,6 +531,15 @@ def bind_conv2d_bwd_weight_sumsq(desc, x16, dy16, dw16, sink: jz_sumsq_sink, ws=
     args = (ctypes.byref(d), _dev_ptr(x16, h, d.N * d.H * d.W * d.C, "x16"), _dev_ptr(dy16, h, d.N * d.P * d.Q * d.K, "dy16"),
             _dev_ptr(dw16, h, d.K * d.R * d.S * d.C, "dw16"), wp, wn, ctypes.byref(sink))
     return BoundCall(lib().jz_conv2d_bwd_weight_sumsq, args, "jz_conv2d_bwd_weight_sumsq", (d, x16, dy16, dw16, ws, sink))
+
+
+def bind_conv2d_bwd_weight_beside(desc, x16, dy16, dw16, ws=None, sink: Optional[jz_sumsq_sink] = None) -> BoundCall:
+    """Pre-marshalled jz_conv2d_bwd_weight_beside: a weight gradient that shares the chip with other streams' work."""
+    d, h = desc, torch.float16
+    wp, wn = _ws(ws)
+    args = (ctypes.byref(d), _dev_ptr(x16, h, d.N * d.H * d.W * d.C, "x16"), _dev_ptr(dy16, h, d.N * d.P * d.Q * d.K, "dy16"),
+            _dev_ptr(dw16, h, d.K * d.R * d.S * d.C, "dw16"), wp, wn, ctypes.byref(sink) if sink is not None else None)
+    return BoundCall(lib().jz_conv2d_bwd_weight_beside, args, "jz_conv2d_bwd_weight_beside", (d, x16, dy16, dw16, ws, sink))
 
 
 def bind_gemm_fc_bwd_weight_sumsq(batch, in_features, out_features, dy16, x16, dw16, sink: jz_sumsq_sink, ws=None) -> BoundCall:

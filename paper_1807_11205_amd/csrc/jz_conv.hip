@@ -446,6 +446,13 @@ __global__ __launch_bounds__(256) void sumsq_half(const unsigned short* __restri
 int out_dim(int in, int pad, int f, int st) { return (in + 2 * pad - f) / st + 1; }
 size_t up256(size_t x) { return (x + 255) & ~size_t(255); }
 
+// Compute units that a launch's workgroups are counted against: the chip's, or half of them for a weight gradient beside other
+// streams' work.  GEMMs of a ResNet-50 step, weight gradients on two side streams, none of the layers recorded: batch 48, 63 and
+// 100 take 3.00, 3.53 and 4.85 ms planned for the whole chip, 2.92, 3.43 and 4.74 for half of it, 2.99, 3.55 and 5.06 where at
+// most 128 workgroups are allowed instead.  (Batch 64, recorded choices: 3.40 ms against 3.53 planned alone.  With one side
+// stream beside a chained step it makes no difference, 6.36 ms at batch 64: such a step keeps the plans of a single stream.)
+constexpr int kUnits = 256, kUnitsBeside = 128;
+
 // Pick the kernel variant (output tile, k tile depth, wavefronts per workgroup) and the split of the reduction with a
 // cost model, in microseconds.  A compute unit works through n = ceil(workgroups / 256) workgroups, `resident` of them
 // at a time, each over kps k tiles; what it can be bound by, and the time as their (fourth-power) norm:
@@ -576,6 +583,7 @@ void choose_tiling(Plan* pl, bool bk64_ok, int forced_bk, bool tables = true) {
   const double megabytes_in = 1e-6 * ((double)std::min<long long>(pl->bytesA, 2ll * a.M * a.Kred) +
                                       (double)std::min<long long>(pl->bytesB, 2ll * a.N * a.Kred));
   const CostGlobals& cg = kCost[oi];
+  const int units = pl->beside ? kUnitsBeside : kUnits;
   // variant v with sp splits (v.bk may differ from the k tile that runs: vbk)
   auto cost = [&](const Variant& v, int vbk, int sp) {
     const int nkt = (a.Kred + vbk - 1) / vbk, kps = (nkt + sp - 1) / sp;
@@ -583,8 +591,8 @@ void choose_tiling(Plan* pl, bool bk64_ok, int forced_bk, bool tables = true) {
     const long long blocks = tiles * ((nkt + kps - 1) / kps);
     const double loop = kps * (vbk / (double)v.bk) * (a.g.R * a.g.S > 1 ? cg.taps : 1.0) * (pl->fast ? 1.0 : 8.0);
     const double out = 1e-6 * (double)a.M * a.N;
-    const double t_lat = (double)((blocks + 256 * v.resident - 1) / (256 * v.resident)) * (v.prologue[oi] + v.lat[oi] * loop);
-    const double t_thr = (double)((blocks + 255) / 256) * (v.own[oi] + v.thr[oi] * loop);
+    const double t_lat = (double)((blocks + units * v.resident - 1) / (units * v.resident)) * (v.prologue[oi] + v.lat[oi] * loop);
+    const double t_thr = (double)((blocks + units - 1) / units) * (v.own[oi] + v.thr[oi] * loop);
     const double t_mem = cg.byte * (megabytes_in + (sp > 1 ? 4.0 * sp : 2.0) * out);
     auto p4 = [](double x) { return (x * x) * (x * x); };
     return cg.fixed + std::sqrt(std::sqrt(p4(t_lat) + p4(t_thr) + p4(t_mem))) +
@@ -608,10 +616,10 @@ void choose_tiling(Plan* pl, bool bk64_ok, int forced_bk, bool tables = true) {
     const bool too_much = bS > 1 && !pl->rt_forced && 4.0 * bS * a.M * a.N > (double)pl->part_limit;
     if (too_much) bS = 1;
     // backward-weight: most of the table's split counts were chosen for launches that share the chip with two other streams
-    // (fewer splits, hence fewer workgroups and partial sums); a launch of its own wants the chip filled.  The tile is kept,
+    // (fewer splits, hence fewer workgroups and partial sums) and stay for such launches; one of its own wants the chip filled.  The tile is kept,
     // and so is the split where the model does not see a twelfth in changing it: batch 64 (chosen in company) 1.78 -> 1.32 ms
     // for the 52 layers, batch 32 (measured alone) keeps its splits.
-    if ((oi == 2 && !pl->rt_forced && !pl->packed) || too_much)
+    if ((oi == 2 && !pl->rt_forced && !pl->packed && !pl->beside) || too_much)
       for (const Variant& v : kVariants)
         if (v.BM == hit->BM && v.BN == hit->BN && v.bk == hit->bk && v.waves == hit->waves && v.nst == hit->nst) {
           best = (too_much ? 1.0 : 11.0 / 12.0) * cost(v, v.bk, bS);
@@ -694,12 +702,13 @@ void plan_text(const Plan& pl, char* buf, size_t n) {
              "4 wavefronts, 4-channel padded copy", pl.op, a.M, a.N, a.Kred, mb, a.N, (a.g.OH * a.g.OW + mb - 1) / mb);
     return;
   }
-  snprintf(buf, n, "op %d M %d N %d K %d: %s tile %dx%dx%d, %d wavefronts, ring %d, %d x %d tiles, %d splits of %d k tiles%s%s", pl.op, a.M,
+  snprintf(buf, n, "op %d M %d N %d K %d: %s tile %dx%dx%d, %d wavefronts, ring %d, %d x %d tiles, %d splits of %d k tiles%s%s%s", pl.op, a.M,
            a.N, a.Kred, pl.fast ? "vector" : "element-wise", pl.BM, pl.BN, pl.bk, pl.fast ? pl.waves : 4,
            pl.fast ? pl.nst : 2, a.tiles_m, a.tiles_n,
            a.splits, a.kt_per_split, pl.packed ? ", 4-channel padded copy" : "",
            pl.flat ? (pl.classes ? ", flattened taps, the residues of the stride in one launch" : ", flattened taps")
-           : a.sc_on ? ", scatter epilogue" : pl.classes ? ", the parity classes of the stride in one launch" : pl.gen ? ", per-load tap arithmetic" : "");
+           : a.sc_on ? ", scatter epilogue" : pl.classes ? ", the parity classes of the stride in one launch" : pl.gen ? ", per-load tap arithmetic" : "",
+           pl.tuned ? ", recorded choice" : "");
 }
 
 // whether strided multi-tap backward-data can run as one unit-stride launch per parity class: every class has a tap, and
@@ -714,6 +723,8 @@ void plan_widened(int op, const jz_conv_desc* d, Plan* pl);
 // limit: bytes that the partial sums of a split reduction may take
 int compute_plan(int op, const jz_conv_desc* d, Plan* pl, size_t limit = kPartialSumLimit) {
   if (!d) return JZ_ERR_NULL;
+  pl->beside = op == (JZ_BWD_WEIGHT | JZ_BESIDE);
+  if (pl->beside) op = JZ_BWD_WEIGHT;
   if (op != JZ_FWD && op != JZ_BWD_DATA && op != JZ_BWD_WEIGHT) return JZ_ERR_UNSUPPORTED;
   if (d->N <= 0 || d->H <= 0 || d->W <= 0 || d->C <= 0 || d->K <= 0 || d->R <= 0 || d->S <= 0 || d->stride_h <= 0 ||
       d->stride_w <= 0 || d->pad_h < 0 || d->pad_w < 0)
@@ -858,7 +869,7 @@ void plan_widened(int op, const jz_conv_desc* d, Plan* pl) {
   if (w.C == d->C && w.K == d->K) return;
   if ((double)w.C * w.K > 1.5 * d->C * d->K) return;
   Plan in;
-  if (compute_plan(op, &w, &in) != JZ_OK || !in.fast) return;
+  if (compute_plan(pl->beside ? op | JZ_BESIDE : op, &w, &in) != JZ_OK || !in.fast) return;
   const size_t npix = (size_t)d->N * d->H * d->W, nout = pl->bytesD / 2;
   const size_t ny = op == JZ_FWD ? nout : (pl->bytesA / 2) / d->K * w.K, nx = npix * w.C, nw = (size_t)w.K * d->R * d->S * w.C;
   const bool x_wide = w.C != d->C, y_wide = w.K != d->K, w_wide = x_wide || y_wide;
@@ -964,11 +975,14 @@ int run_widened(int op, const jz_conv_desc* d, const Plan& pl, const void* A, co
                 void* stream, const jz::SumsqSink* sink);
 
 // A, B in the kernel's order: FWD (x, w), BWD_DATA (dy, w), BWD_WEIGHT (dy, x)
+// op may be JZ_BWD_WEIGHT | JZ_BESIDE
 int run(int op, const jz_conv_desc* d, const void* A, const void* B, void* D, void* ws, size_t ws_bytes, void* stream,
         float* stats = nullptr, int stats_tiles_m = 0, const jz::SumsqSink* sink = nullptr, const jz::BnBwdOperands* bn = nullptr) {
   Plan pl;
-  int rc = make_plan(op, d, &pl);
+  const int plan_op = op;
+  int rc = make_plan(plan_op, d, &pl);
   if (rc != JZ_OK) return rc;
+  op = pl.op;
   // the caller sized the buffer of the column sums from an earlier plan: it has to be this plan (the run-time tuning table
   // may have been changed in between)
   if (stats && !(op == JZ_BWD_DATA ? plan_leaves_bwd_stats(pl) && bn != nullptr : plan_leaves_stats(pl))) return JZ_ERR_UNSUPPORTED;
@@ -982,7 +996,7 @@ int run(int op, const jz_conv_desc* d, const void* A, const void* B, void* D, vo
   }
   const size_t room = ws ? ws_bytes : 0;
   if (room < pl.ws_bytes && !stats && !pl.rt_forced) {  // fewer splits (a choice made by hand runs as it was made, or not at all)
-    if ((rc = make_plan(op, d, &pl, room > pl.part_offset ? room - pl.part_offset : 0)) != JZ_OK) return rc;
+    if ((rc = make_plan(plan_op, d, &pl, room > pl.part_offset ? room - pl.part_offset : 0)) != JZ_OK) return rc;
     if (pl.widen) {
       pl.widen = false;
       pl.ws_bytes = pl.element_ws_bytes;
@@ -1181,7 +1195,7 @@ int run_widened(int op, const jz_conv_desc* d, const Plan& pl, const void* A, co
     if ((rc = jz::launch_status()) != JZ_OK) return rc;
   }
   const size_t used = (size_t)(inner_ws - base);
-  rc = run(op, &w, a2, b2, d2, ws_bytes > used ? inner_ws : nullptr, ws_bytes - used, stream, nullptr, 0, pl.wide_d_bytes ? nullptr : sink);
+  rc = run(pl.beside ? op | JZ_BESIDE : op, &w, a2, b2, d2, ws_bytes > used ? inner_ws : nullptr, ws_bytes - used, stream, nullptr, 0, pl.wide_d_bytes ? nullptr : sink);
   if (rc != JZ_OK || !pl.wide_d_bytes) return rc;
   const long long n = op == JZ_BWD_DATA ? npix * d->C : (long long)d->K * RS * d->C;
   const long long blocks = (n + 255) / 256;
@@ -1362,6 +1376,18 @@ extern "C" int jz_conv2d_bwd_weight_sumsq(const jz_conv_desc* desc, const void* 
   jz::SumsqSink sk;
   if ((rc = check_sink(sink, dw16, pl.bytesD, ws, ws_bytes < pl.ws_bytes ? ws_bytes : pl.ws_bytes, &sk)) != JZ_OK) return rc;
   return run(JZ_BWD_WEIGHT, desc, dy16, x16, dw16, ws, ws_bytes, hip_stream, nullptr, 0, &sk);
+}
+
+extern "C" int jz_conv2d_bwd_weight_beside(const jz_conv_desc* desc, const void* x16, const void* dy16, void* dw16, void* ws,
+                                           size_t ws_bytes, const jz_sumsq_sink* sink, void* hip_stream) {
+  const int op = JZ_BWD_WEIGHT | JZ_BESIDE;
+  if (!sink) return run(op, desc, dy16, x16, dw16, ws, ws_bytes, hip_stream);
+  Plan pl;
+  int rc = make_plan(op, desc, &pl);
+  if (rc != JZ_OK) return rc;
+  jz::SumsqSink sk;
+  if ((rc = check_sink(sink, dw16, pl.bytesD, ws, ws_bytes < pl.ws_bytes ? ws_bytes : pl.ws_bytes, &sk)) != JZ_OK) return rc;
+  return run(op, desc, dy16, x16, dw16, ws, ws_bytes, hip_stream, nullptr, 0, &sk);
 }
 
 // ---- backward-weight without a caller workspace ---------------------------------------------------------------

@@ -32,6 +32,7 @@ struct Plan {
   size_t ws_bytes = 0;       // total workspace
   size_t part_offset = 0;    // where the split-K partial sums start inside it
   size_t part_limit = kPartialSumLimit;  // bytes they may take
+  bool beside = false;       // weight gradient that runs beside other streams' work: its split leaves part of the chip free
   size_t bytesA = 0, bytesB = 0, bytesD = 0;  // caller's operand sizes in bytes, for the overlap checks
   // packed mode
   int Hp = 0, Wp = 0, KT = 0;

@@ -79,23 +79,22 @@ def model_layers(model):
     return BATCH, layers
 
 
+def plan_choice(text):
+    """(tile m, tile n, k tile, wavefronts, ring, splits) of a jz_conv2d_describe_plan text"""
+    m = re.search(r"tile (\d+)x(\d+)x(\d+), (\d+) wavefronts, ring (\d+), \d+ x \d+ tiles, (\d+) splits", text)
+    return tuple(int(v) for v in m.groups())
+
+
 def share_chip(descs):
-    """Make backward-weight of these layers use the split counts recorded for a step whose weight gradients run on two side
-    streams beside the rest of the backward pass.  Alone, a launch is fastest when it fills the chip, and that is what the
-    planner chooses; three streams side by side want a half to a quarter of the splits (the batch-64 step: 3.40 ms against
-    3.53).  Process-wide, through jz_conv2d_tune_set, like any recorded choice.  Returns the number of layers it found."""
-    import glob
+    """For tuning runs: make every backward-weight call of these layers use the recorded choice of jz_conv2d_bwd_weight_beside, where there
+    is one.  Process-wide, through jz_conv2d_tune_set (jz_conv2d_tune_clear takes it back); a program whose weight gradients run
+    on side streams calls jz_conv2d_bwd_weight_beside instead.  Returns the number of layers it found."""
     from . import api
-    rows = {}
-    for path in sorted(glob.glob(os.path.join(PKG, "csrc", "jz_tuned*.inc"))):
-        for m in re.finditer(r"^\{2, (\d+), (\d+), (\d+), (\d+), 0, (\d+), (\d+), (\d+), (\d+), (\d+), (\d+)\}", open(path).read(), re.M):
-            v = tuple(int(g) for g in m.groups())
-            rows.setdefault(v[:4], v[4:])
     found = 0
     for d in descs:
-        row = rows.get((d.K, d.R * d.S * d.C, d.N * d.P * d.Q, d.R * d.S))
-        if row:
-            api.jz_conv2d_tune_set(api.JZ_BWD_WEIGHT, d, *row)
+        text = api.jz_conv2d_describe_plan(api.JZ_BWD_WEIGHT | api.JZ_BESIDE, d)
+        if "recorded choice" in text:
+            api.jz_conv2d_tune_set(api.JZ_BWD_WEIGHT, d, *plan_choice(text))
             found += 1
     return found
 
@@ -213,7 +212,7 @@ def in_place(recs, steps=100, top=3, gain=0.001, passes=2, n_side=2, model="resn
         wl = bench.AlexNetStep(batch, n_side, ws_bytes=big)                 # room for any split count
     else:
         batch = BATCH
-        wl = bench.ResNet50Step(batch=BATCH, variant=VARIANT)
+        wl = bench.ResNet50Step(batch=BATCH, variant=VARIANT, beside=n_side > 1)
         wl.ws = torch.empty(big, dtype=torch.uint8, device="cuda:0")
         wl.side_ws = [torch.empty(big, dtype=torch.uint8, device="cuda:0") for _ in range(3)]
         for _ in range(12):                                                 # the loss-scale back-off of bench.py
@@ -277,9 +276,9 @@ def in_place(recs, steps=100, top=3, gain=0.001, passes=2, n_side=2, model="resn
                      "64064.32.4.4/256"))
     work.sort(key=lambda w: -w[0])
 
-    def current(d, op):                                                     # what the library would run now, as a key
-        m = re.search(r"tile (\d+)x(\d+)x(\d+), (\d+) wavefronts, ring (\d+), \d+ x \d+ tiles, (\d+) splits", api.jz_conv2d_describe_plan(op, d))
-        bm, bn, bk, wv, nst, sp = (int(v) for v in m.groups())
+    def current(d, op):                                                     # what the step would run now, as a key
+        beside = api.JZ_BESIDE if op == api.JZ_BWD_WEIGHT and n_side > 1 else 0
+        bm, bn, bk, wv, nst, sp = plan_choice(api.jz_conv2d_describe_plan(op | beside, d))
         return "%d.%d.%d.%d/%d" % (bm * 1000 + bn, bk, wv, nst, sp)
 
     choice = {}
