@@ -381,7 +381,7 @@ def per_layer_report(wl, iters=20, out_path=None, peak=FP16_MFMA_PEAK_TFLOPS):
 
 
 class AlexNetStep:
-    """configs[3]: the AlexNet-shaped layers (five convolutions, ungrouped, and the three FC GEMMs) at N = 128, forward,
+    """The AlexNet-shaped layers (five convolutions, ungrouped, and the three FC GEMMs) at N = 128, forward,
     backward-data and backward-weight of every layer on independent seeded N(0,1) inputs, He-normal weights.  Same launch
     scheme as the ResNet-50 step: forward and the backward-data chain in network order on one stream, backward-weight
     round-robin on the side streams, splitting for a part of the chip if there are several.  ws_bytes: size of each stream's workspace (default: what the current plans need;
@@ -486,9 +486,9 @@ def alexnet_workload(args):
         "metric": "AlexNet-shaped layers N=%d fp16 fwd+bwd images/s" % B, "value": B / (ms * 1e-3), "unit": "images/s", "n_gpus": 1,
         "steps": args.steps, "warmup": args.warmup, "ms_per_step": ms, "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
         "dtype": "f16 storage, f32 accumulate", "data": "synthetic",
-        "config": {"workload": "configs[3]: AlexNet-shaped layers (5 convs ungrouped + 3 FC), fwd + bwd_data + bwd_weight per layer on "
+        "config": {"workload": "AlexNet-shaped layers (5 convs ungrouped + 3 FC), fwd + bwd_data + bwd_weight per layer on "
                                "independent seeded N(0,1) inputs", "batch": B, "launch": "eager", "streams": args.streams},
-        "roofline": {"kernel": "igemm_kernel (all %d conv/FC launches of a step)" % n_launch, "bound": "mfma", "achieved": tflops,
+        "roofline": {"kernel": "igemm_dma_kernel (all %d conv/FC launches of a step)" % n_launch, "bound": "mfma", "achieved": tflops,
                      "peak": FP16_MFMA_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": tflops / FP16_MFMA_PEAK_TFLOPS, "traffic": None,
                      "flop_per_step": flops}}
     if rows is not None:
@@ -729,7 +729,7 @@ def main():
     ap.add_argument("--warmup", type=int, default=20)
     ap.add_argument("--batch", type=int, default=None, help="default: 64 (resnet50), 128 (alexnet)")
     ap.add_argument("--workload", default="resnet50", choices=("resnet50", "alexnet", "bn", "chain"),
-                    help="resnet50: the full step the headline metric is quoted on; alexnet: the AlexNet-shaped layers of configs[3]; "
+                    help="resnet50: the full step the headline metric is quoted on; alexnet: the AlexNet-shaped layers (five convolutions, three FC); "
                          "bn: the batch-normalization + ReLU layers of ResNet-50 (not part of the headline step); chain: a complete chained "
                          "ResNet-50 training step with every layer between the convolutions (not the headline step either)")
     ap.add_argument("--no-cpu-baseline", action="store_true")
@@ -832,15 +832,15 @@ def main():
         "dtype": "f32 storage, f32 accumulate (LARS as in the mixed-precision step)" if wl.f32 else
                  "f16 storage, f32 accumulate (LARS in f32, norms f64)",
         "data": "synthetic",
-        "config": {"workload": "configs[4]: ResNet-50 %s, 53 convs + FC, fwd + bwd_data + bwd_weight per layer on "
+        "config": {"workload": "ResNet-50 %s, 53 convs + FC, fwd + bwd_data + bwd_weight per layer on "
                                "independent seeded N(0,1) inputs, then fused LARS over 161 tensors / 25,557,032 params" % args.variant,
                    "batch": args.batch, "loss_scale_after_back_off": wl.loss_scale, "loss_scale_control": "device" if args.dynamic_loss_scale else "fixed", "launch": "hip graph" if args.graph else "eager", "streams": args.streams},
         "ms_per_step_stats": {"gpu_mean": t["step_ms_mean"], "gpu_median": t["step_ms_median"], "gpu_min": t["step_ms_min"],
                               "note": "per-step HIP-event times (GEMM phase + LARS) over the timed steps; ms_per_step is host wall clock / steps"},
         "pct_fp16_mfma_peak": 100.0 * (wl.flops / (ms_per_step * 1e-3) / 1e12) / FP16_MFMA_PEAK_TFLOPS,
-        "roofline": {"kernel": "%s (all %d conv/FC launches of a step)" % ("igemm_f32_kernel" if wl.f32 else "igemm_dma_kernel", n_gemm),
+        "roofline": {"kernel": "%s (all %d conv/FC launches of a step)" % ("f32_dma_kernel" if wl.f32 else "igemm_dma_kernel", n_gemm),
                      "bound": "mfma", "achieved": tflops, "peak": peak, "unit": "TFLOP/s", "frac": tflops / peak,
-                     "peak_note": ("dense FP32 MFMA: 256 CU x 4 SIMD x 64 flop/clk (v_mfma_f32_32x32x2_f32) x 2.4 GHz = 157.3 TFLOP/s" if wl.f32 else
+                     "peak_note": ("dense FP32 MFMA: 256 CU x 4 SIMD x 64 flop/clk (v_mfma_f32_16x16x4_f32) x 2.4 GHz = 157.3 TFLOP/s" if wl.f32 else
                                    "dense FP16 MFMA, the published 2.5 PFLOP/s: 256 CU x 4 SIMD x 1024 flop/clk (v_mfma_f32_32x32x16_f16) x 2.4 GHz = 2.52; "
                                    "a loop of nothing but MFMAs sustains 1.94 on this chip (effective clock 1.85 GHz)"),
                      "traffic": traffic["bytes"] if traffic else None,

@@ -2,21 +2,24 @@
 // gfx950: the single-precision side of the paper's FP32-versus-mixed-precision throughput comparison (Jia et al. 2018,
 // Section 5.4, Table 9).  Same operations, layouts and GEMM view as the FP16 path (jz_igemm.h):
 //
-//   D[m][n] = sum_k A(m,k) * B(n,k), every product and sum in FP32 on v_mfma_f32_32x32x2_f32.
+//   D[m][n] = sum_k A(m,k) * B(n,k), every product and sum in FP32 on the FP32 matrix instructions.
 //
 // Channel counts that are multiples of 4 run on the LDS-direct kernel of jz_f32_dma.h (strided multi-tap backward-data as one
 // unit-stride launch per residue of the stride, strided 1x1 backward-data with a scattering epilogue); other counts run on
 // it through copies with the channels rounded up to 4, where that adds at most half to the work (3-channel stems).
 //
-// What is left (a filter smaller than its stride in backward-data; 1 or 2 channels) runs on igemm_f32_kernel below: a workgroup of 4 wavefronts (2 x 2) owns a BM x BN output tile, walks the reduction in
-// tiles of 16, and stages operands global -> registers -> LDS, double buffered.  Both tiles sit in LDS as
-// [k][row] (row contiguous), so an MFMA operand (lane l: row l % 32, k l / 32) is one conflict-free 4-byte read per
+// What is left (a filter smaller than its stride in backward-data; 1 or 2 channels; callers without room for the copies) runs on
+// igemm_f32_kernel below: a workgroup of 4 wavefronts (2 x 2) owns a BM x BN output tile, walks the reduction in
+// tiles of 16 with v_mfma_f32_32x32x2_f32, and stages operands global -> registers -> LDS, double buffered.  Both tiles sit in
+// LDS as [k][row] (row contiguous), so an MFMA operand (lane l: row l % 32, k l / 32) is one conflict-free 4-byte read per
 // lane.  Operands that are contiguous along the reduction in memory (x / dy gathered per pixel, the forward filter) are
 // fetched as 4 consecutive k of one row and written to LDS as 4 scalars; operands contiguous along their own row index
 // (the filter in backward-data, dy and x in backward-weight) as 4 consecutive rows of one k, one 16-byte write.  With
 // channel counts that are not multiples of 4 the same kernel fetches element by element (VEC = false).  Addressing is the
-// plain index definition of each operation, bounds-checked per fetched vector.  Split reductions (backward-weight) leave FP32 partial sums in the workspace, added in
-// index order by splitk_reduce_f32: deterministic.
+// plain index definition of each operation, bounds-checked per fetched vector.
+//
+// Split reductions (any operation with too few output tiles for the chip) leave FP32 partial sums in the workspace, added in a
+// fixed order by splitk_reduce_f32: deterministic.
 #include <hip/hip_runtime.h>
 
 #include <math.h>

@@ -291,8 +291,8 @@ __device__ __forceinline__ void igemm_epilogue_impl(const GemmArgs& a, f32x16 (&
       if (nvec) {
         if constexpr (STATS == 0) {
           // Non-temporal: the next launch of a plain sequence of layers reads other tensors, and would share memory with the
-          // write-back of this result (ResNet-50 at batch 64 3.92 -> 3.80 ms, a bottleneck block at batch 32 179 -> 163 us).  The
-          // normalization behind a fused call (STATS) reads the result at once: there the hint costs the training step 1 %.
+          // write-back of this result (without and with the hint: ResNet-50's GEMMs at batch 64 and their update 3.97 and 3.85 ms,
+          // a bottleneck block at batch 32 195 and 179 us).  The normalization behind a fused call (STATS) reads the result at once: there the hint costs the training step 1 %.
           const u32x4 v = *reinterpret_cast<const u32x4*>(src);
           __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(dst));
         } else {

@@ -242,8 +242,9 @@ __device__ __forceinline__ void chunk_range(const ChunkRec& r, int* t_out, int64
 constexpr int LARS_IT = LARS_CH / (LARS_THREADS * 8);  // 8-element groups per thread and chunk
 
 // 16-byte accesses of the update pass.  What it writes (w, v, the FP16 copy: 20 of 28 bytes an element) goes out with the
-// non-temporal hint, or dirty lines of it are still being written back while the next pass reads: one update of ResNet-50
-// 114 -> 109 us, AlexNet 274 -> 262 us.  The gradient, which the reduce pass has just read, is in the last-level cache: plain
+// non-temporal hint, or dirty lines of it are still being written back while the next pass reads: ResNet-50 113 -> 109 us,
+// AlexNet 279 -> 260 us for updates one behind the other; an update of a state that was just written (133, 325 us) gains
+// nothing.  The gradient, which the reduce pass has just read, is in the last-level cache: plain
 // loads.  So is a part of the state when it fits there (204 MB for ResNet-50: 93 us for updates in a row, 108 with the hint);
 // state that does not fit only displaces the gradient and is read with the hint (STREAM; AlexNet 261 -> 253 us).
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
