@@ -273,8 +273,8 @@ class ResNet50Step:
         api.jz_loss_scale_init(self.ls_state, self.loss_scale)
         self.programs = {}   # jz_lars_begin_step takes the state
 
-    def step(self):
-        self.run_gemms()
+    def step(self, sides=()):
+        self.run_gemms(sides)
         self.run_lars()
 
     def halve_loss_scale(self):
@@ -558,7 +558,7 @@ def chain_workload(args):
     launches, the weight-gradient GEMMs on a side stream (--streams 1: everything on one), the same fixed synthetic
     batch every step."""
     from paper_1807_11205_amd import resnet50
-    net = resnet50.ResNet50Chain(batch=args.batch, image=224, initial_loss_scale=65536.0,
+    net = resnet50.ResNet50Chain(batch=args.batch, image=args.image, initial_loss_scale=65536.0,
                                  policy=dict(growth_interval=1 << 30, max_scale=2.0 ** 24), fused=not args.unfused,
                                  block_end=not args.no_block_end, bwd_stats=not args.no_bwd_stats)
     skipped = 0
@@ -595,7 +595,7 @@ def chain_workload(args):
         "n_gpus": 1, "steps": args.steps, "warmup": args.warmup, "ms_per_step": ms, "higher_is_better": True, "scaling": "weak",
         "vs_baseline": None, "dtype": "f16 storage, f32 accumulate, f32 master weights", "data": "synthetic",
         "config": {"workload": "ResNet-50 v1 chained step: conv + batch norm + ReLU + pooling + residual adds + classifier + "
-                               "softmax loss gradient, backward, LARS with dynamic loss scale", "batch": args.batch, "image": 224,
+                               "softmax loss gradient, backward, LARS with dynamic loss scale", "batch": args.batch, "image": args.image,
                    "launch": "eager", "streams": 1 + (len(side) if side else 0), "launches_per_step": len(net.trace), "launches_by_kind": kinds,
                    "conv_bn_forward": "one call, statistics in the convolution epilogue" if net.fused else "two calls",
                    "loss_scale": api.loss_scale_state(net.ls_state)[0], "steps_skipped_while_the_scale_settled": skipped,
@@ -754,6 +754,7 @@ def main():
     ap.add_argument("--streams", type=int, default=3, help="1: everything in order on one stream; n > 1: n-1 side streams "
                     "for the projection shortcuts (forward) and the backward-weight launches (at most 4)")
     ap.add_argument("--graph", type=int, default=0, help="replay the step from a HIP graph (1) or launch eagerly (0); eager launches measured faster here")
+    ap.add_argument("--image", type=int, default=224, help="chain workload: image size (a multiple of 32)")
     ap.add_argument("--no-block-end", action="store_true", help="chain workload: ReLU gradient and batch-norm backward at a block's end as two calls")
     ap.add_argument("--no-bwd-stats", action="store_true",
                     help="chain workload: backward-data convolution and the batch-norm backward underneath it as two calls")
@@ -794,9 +795,11 @@ def main():
         print(plans_digest(wl))
         return
 
+    stream = torch.cuda.Stream()
+    side = [torch.cuda.Stream() for _ in range(max(0, min(args.streams, 4) - 1))]
     # loss-scale back-off: halve S until the weight gradients stay inside fp16 and the update is not skipped
     for _ in range(12):
-        wl.step()
+        wl.step(side)
         torch.cuda.synchronize()
         if int(wl.found_inf.item()) == 0:
             break
@@ -811,8 +814,6 @@ def main():
         rows = per_layer_report(wl, out_path=args.per_layer_file, peak=FP32_MFMA_PEAK_TFLOPS if wl.f32 else FP16_MFMA_PEAK_TFLOPS)
         wl.reset_state()
 
-    stream = torch.cuda.Stream()
-    side = [torch.cuda.Stream() for _ in range(max(0, min(args.streams, 4) - 1))]
     t = time_steps(wl, stream, side, args.steps, args.warmup, graph=args.graph)
     gemm_ms, lars_ms, ms_per_step = t["gemm_ms"], t["lars_ms"], t["wall_ms"]
     n_gemm = sum(3 if not L.get("first") else 2 for L in wl.layers)
