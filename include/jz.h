@@ -157,7 +157,7 @@ int jz_gemm_fc_bwd_weight_sumsq(int batch, int in_features, int out_features, co
  * mixed-precision throughput comparison) --------------------------------------------------------------------------
  * FP32 storage, FP32 products and sums (v_mfma_f32_16x16x4_f32), no rounding to FP16 anywhere: same definitions, same
  * layouts (NHWC / KRSC / NPQK), same GEMM view, same conventions and status codes as the FP16 entry points above, with
- * float tensors (DEVICE, 16-byte aligned).  Split reductions leave FP32 partial sums in `ws` and are added in index
+ * float tensors (DEVICE, 16-byte aligned).  Split reductions leave FP32 partial sums in `ws` that are added in a fixed
  * order (deterministic); they take at most 256 MiB.  With less workspace than reported a call runs with fewer splits: forward
  * and backward-data always (with none in no workspace at all), a weight gradient while its tiles times the splits that fit
  * fill the chip (256 tiles of 64 x 64), else JZ_ERR_WORKSPACE.  Kernels sized for the FP32 matrix peak, chosen by a cost
