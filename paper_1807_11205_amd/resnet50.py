@@ -365,7 +365,10 @@ class ResNet50Chain:
             return
         sides = list(side) if isinstance(side, (list, tuple)) else [side]
         while len(self.side_ws) < len(sides):
-            self.side_ws.append(torch.zeros(self._ws_bytes, dtype=torch.uint8, device=self.device))
+            # made on the current stream, which may be neither the step's nor the side stream: what it still does with this memory
+            # (the last use of a freed tensor) comes first
+            self.side_ws.append(torch.empty(self._ws_bytes, dtype=torch.uint8, device=self.device))
+            sides[len(self.side_ws) - 1].wait_stream(torch.cuda.current_stream())
         main = stream if stream is not None else torch.cuda.current_stream()
         handle, side_handles = api._stream(main), [api._stream(s_) for s_ in sides]
 
