@@ -1273,6 +1273,7 @@ extern "C" int jz_conv2d_tune_set(int op, const jz_conv_desc* desc, int tile_m, 
   Plan pl;
   int rc = make_plan(op, desc, &pl);
   if (rc != JZ_OK) return rc;
+  if (pl.beside) return JZ_ERR_UNSUPPORTED;  // a recorded choice is for both kinds of call
   if (!pl.fast || splits < 1) return JZ_ERR_UNSUPPORTED;  // the element-wise path has one kernel shape
   const Variant* v = nullptr;
   for (const Variant& c : kVariants)

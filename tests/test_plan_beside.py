@@ -47,6 +47,8 @@ def test_the_flag_belongs_to_the_weight_gradient(jz):  # noqa: F811
     d = jz.conv_desc(64, 56, 56, 64, 64, 3, 3, 1, 1)
     for op in (jz.JZ_FWD, jz.JZ_BWD_DATA):
         assert jz.lib().jz_conv2d_workspace_bytes(op | jz.JZ_BESIDE, ctypes.byref(d), ctypes.byref(n)) == jz.JZ_ERR_UNSUPPORTED
+    assert jz.lib().jz_conv2d_tune_set(jz.JZ_BWD_WEIGHT | jz.JZ_BESIDE, ctypes.byref(d), 64, 64, 32, 4, 4, 1) == jz.JZ_ERR_UNSUPPORTED
+    assert jz.lib().jz_gemm_fc(jz.JZ_BWD_WEIGHT | jz.JZ_BESIDE, 4, 8, 8, None, None, None, None, 0, None) == jz.JZ_ERR_UNSUPPORTED
     A = 0x10000000
     assert jz.lib().jz_conv2d_bwd_weight_beside(ctypes.byref(d), None, A, A + (1 << 20), None, 0, None, None) == jz.JZ_ERR_NULL
     assert jz.lib().jz_conv2d_bwd_weight_beside(ctypes.byref(d), A, A + (1 << 28), A + (1 << 29), None, 0, None, None) == jz.JZ_ERR_WORKSPACE
