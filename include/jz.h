@@ -394,11 +394,13 @@ int jz_softmax_xent_bwd(int rows, int classes, const void* z16, const int* label
  *   gamma, beta, save_mean, save_invstd: DEVICE FP32 [channels] (master precision), 16-byte aligned
  *   dgamma16, dbeta16: DEVICE FP16 [channels]: the parameter gradients as the optimizer's FP16 gradient buffer takes them
  *                      (they carry whatever loss scale dy16 carries)
- *   ws: DEVICE workspace of jz_bn_workspace_bytes(rows, channels) bytes (per-slab partial sums and per-channel
- *       coefficients); contents need not survive between the forward and the backward call
+ *   ws: DEVICE workspace of jz_bn_workspace_bytes(rows, channels) bytes (per-slab partial sums, per-channel
+ *       coefficients and, backward, one bit per element for the ReLU's mask; without room for those bits the backward call
+ *       reads y16 twice); contents need not survive between the forward and the backward call
  * jz_bn_relu_fwd: y = gamma * (x - mean) * invstd + beta, then max(., 0) when relu != 0, rounded once to FP16; writes the
  *   statistics it used (invstd = 1 / sqrt(var + eps)) to save_mean / save_invstd.  Sums are FP32 within a slab of rows
- *   and FP64 across slabs, in an order that depends only on (rows, channels): results are deterministic.
+ *   and FP64 across slabs, in an order that depends only on (rows, channels) as long as the workspace has the size above:
+ *   results are deterministic.
  * jz_bn_relu_bwd: with g = dy (relu == 0) or dy where y16 > 0 and 0 elsewhere (relu != 0; y16 is the forward output):
  *   dbeta = sum g, dgamma = sum g * x^, dx = gamma * invstd * (g - dbeta / rows - x^ * dgamma / rows).  y16 may be NULL
  *   when relu == 0.

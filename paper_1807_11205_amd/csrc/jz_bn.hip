@@ -12,20 +12,35 @@
 //             bn_bwd_final  dbeta = sum g, dgamma = sum g x^ (FP16 copies for the optimizer's gradient buffer)
 //             bn_bwd_apply  dx = gamma invstd (g - dbeta/M - x^ dgamma/M), evaluated as a g + P x + Q per channel
 //
+// Where there is room in the workspace the backward statistics leave the ReLU's mask as bits for the apply pass, which then
+// reads x, dy and 1/16 of y's bytes instead of y (bn_bwd_apply_masked).  Where the partial sums are few the apply pass adds them
+// up itself (*_merged).
+//
 // A lane always handles 8 consecutive channels (one 16-byte access); the C/8 lanes of a row sit side by side, so a
 // wavefront reads whole rows contiguously.  Results are deterministic: the order of every sum depends only on
 // (rows, C).
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
 
 #include "jz_internal.h"
 
 namespace {
 
 constexpr int BN_THREADS = 256;
+constexpr int BN_BWD_ROWS = 4;         // rows of a lane whose loads are in flight together in the backward passes
 constexpr int BN_MAX_C = 2048;       // C / 8 lanes of a row have to fit one workgroup
 constexpr int BN_TARGET_SLABS = 512;   // two per compute unit
 constexpr int BN_MERGE_SLABS = 64;     // most partial sums per channel that an apply pass adds up itself (ResNet-50 at batch 64: 64 is
                                        // even with none, 128 costs 1 %, 512 costs 4 %; small steps have fewer anyway)
+// Forward tensors between these sizes: slabs shared by workgroups of 64 channels and up, so that at most 128 partial sums per
+// channel are left, and an apply pass of about 512 workgroups of 512 threads that adds them up (12544 x 256: 14.4 us in three
+// launches, 10.9 in two; x 1024: 21.6 and 18.2; 50176 x 512, 51 MB: 33.6 and 31-34).  Above (100 MB) the 128-byte pieces of rows cost
+// the statistics what the launch costs (57.2 and 57-60 us); below, 2048 workgroups of 256 threads are better (8 x 64 x 64
+// training step 1.62 and 1.65 ms).  Backward it does not pay: its statistics read three tensors (3136 x 512: 13.6 us in three
+// launches, 16.1 in two).
+constexpr int BN_MERGE_SLABS_WIDE = 128;
+constexpr int64_t BN_WIDE_BYTES = 4 << 20, BN_FEW_SLABS_BYTES = 64 << 20;
 constexpr int BN_FIN_C = 8;            // channels a finalize workgroup handles (32 contiguous bytes of every slab's sums);
                                        // its 256 / 8 = 32 lanes per channel share the slabs
 
@@ -39,9 +54,11 @@ struct BnPlan {
   int64_t rows_per_slab = 0; // a multiple of rpp
   int slabs = 0;
   size_t off_part = 0, off_coef = 0, total = 0;  // workspace: [slabs][2][C] float partial sums, [4][C] float coefficients
+  int mask_iters = 0;        // words of it a lane of the statistics pass has
+  size_t mask_bytes = 0;     // behind them, if there is room: one bit per element, the backward pass's ReLU mask
 };
 
-int make_bn_plan(int64_t rows, int channels, BnPlan* p) {
+int make_bn_plan(int64_t rows, int channels, bool forward, BnPlan* p) {
   if (rows <= 0 || channels <= 0) return JZ_ERR_SHAPE;
   if (channels % 8 != 0 || channels > BN_MAX_C) return JZ_ERR_UNSUPPORTED;
   if (rows * (int64_t)channels >= (int64_t(1) << 40)) return JZ_ERR_UNSUPPORTED;
@@ -52,13 +69,15 @@ int make_bn_plan(int64_t rows, int channels, BnPlan* p) {
   // slabs, so that the partial sums stay small beside the tensor.  A wide tensor with few rows would then leave most of
   // the chip idle (2048 channels x 3136 rows: 49 slabs), so its slabs are shared by csplit workgroups that take a range
   // of at least 32 chunks (512 contiguous bytes of a row) each: more workgroups, the same number of partial sums.
+  const bool merge = forward && rows * channels * 2 <= BN_FEW_SLABS_BYTES && rows * channels * 2 >= BN_WIDE_BYTES;
   for (int cs = 1;; cs *= 2) {
     const int cpr_l = p->cpr / cs;
     p->csplit = cs;
     p->rpp = BN_THREADS / cpr_l;
+    const int target = merge ? BN_TARGET_SLABS / cs : BN_TARGET_SLABS;
     // fewer passes per workgroup (16, 8, 4) until at least 256 workgroups exist
-    for (int min_passes = 16; min_passes >= 4; min_passes /= 2) {
-      int64_t per = (rows + BN_TARGET_SLABS - 1) / BN_TARGET_SLABS;
+    for (int min_passes = 16; min_passes >= (merge ? 2 : 4); min_passes /= 2) {
+      int64_t per = (rows + target - 1) / target;
       if (per < min_passes * (int64_t)p->rpp) per = min_passes * (int64_t)p->rpp;
       if (per < 32) per = 32;
       per = (per + p->rpp - 1) / p->rpp * p->rpp;
@@ -66,11 +85,18 @@ int make_bn_plan(int64_t rows, int channels, BnPlan* p) {
       p->slabs = (int)((rows + per - 1) / per);
       if ((int64_t)p->slabs * cs >= 256) break;
     }
-    if ((int64_t)p->slabs * cs >= 256 || cs == 8 || cpr_l % 2 != 0 || cpr_l / 2 < 32) break;
+    const bool full = (int64_t)p->slabs * cs >= 256;
+    if (merge) {
+      if ((full && p->slabs <= BN_MERGE_SLABS_WIDE) || cpr_l % 2 != 0 || cpr_l / 2 < 8) break;
+    } else if (full || cs == 8 || cpr_l % 2 != 0 || cpr_l / 2 < 32) {
+      break;
+    }
   }
   p->off_part = 0;
   p->off_coef = up256((size_t)p->slabs * 2 * channels * sizeof(float));
   p->total = p->off_coef + up256((size_t)4 * channels * sizeof(float));
+  p->mask_iters = (int)((p->rows_per_slab + BN_BWD_ROWS * (int64_t)p->rpp - 1) / (BN_BWD_ROWS * (int64_t)p->rpp));
+  p->mask_bytes = (size_t)p->slabs * p->csplit * p->mask_iters * BN_THREADS * 4;
   return JZ_OK;
 }
 
@@ -85,6 +111,11 @@ __device__ __forceinline__ void unpack8(const uint4& v, float (&f)[8]) {
     f[2 * i] = (float)lo;
     f[2 * i + 1] = (float)hi;
   }
+}
+
+__device__ __forceinline__ void load8(const float* p, float (&f)[8]) {
+  const float4 t0 = reinterpret_cast<const float4*>(p)[0], t1 = reinterpret_cast<const float4*>(p)[1];
+  f[0] = t0.x; f[1] = t0.y; f[2] = t0.z; f[3] = t0.w; f[4] = t1.x; f[5] = t1.y; f[6] = t1.z; f[7] = t1.w;
 }
 
 __device__ __forceinline__ uint4 pack8(const float (&f)[8]) {
@@ -111,125 +142,153 @@ __device__ __forceinline__ void store_streaming(uint4* p, const uint4& v) {
   __builtin_nontemporal_store(t, reinterpret_cast<u32x4_t*>(p));
 }
 
-// Sums over a slab of rows, for the 8 channels of each lane: s0 and s1 are whatever `term` produces per element.
-// The rpp lanes that share a channel chunk (one per row of a pass) are then added in row order through LDS, and the
-// slab's 2 x C sums are stored.  MODE 0: (x, x^2).  MODE 1: (g, g x^) with g = dy [* (y > 0)].  MODE 2: the end of a
+// Sums over a slab of rows, for the 8 channels of each lane: s0 and s1 are whatever the mode produces per element.
+// The rpp lanes that share a channel chunk (one per row of a pass) are then added through LDS, and the
+// slab's 2 x C sums are stored.  ST_SUM: (x, x^2).  ST_GRAD: (g, g x^) with g = dy.  ST_RELU: ... with g = dy where y > 0, else 0.
+// ST_MASK: the same, and the bits y > 0 are left for the apply pass.  ST_END: the end of a
 // residual block: g = RNE16(dy [+ dy2]) where y > 0, else 0, is formed here, written to g_out for the other consumers of
-// that gradient, and summed as in MODE 1 (the sums see the rounded g, as a pass over g_out would).
+// that gradient, and summed (the sums see the rounded g, as a pass over g_out would).
+enum { ST_SUM, ST_GRAD, ST_RELU, ST_MASK, ST_END };
+struct BnStatsArgs {
+  const uint4 *x, *y, *dy, *dy2;
+  uint4* g_out;
+  unsigned* mask;
+  const float *mean, *invstd;
+  float* part;
+  int64_t rows, rows_per_slab;
+  int C, cpr, rpp, csplit, mask_iters;
+};
 template <int MODE>
-__global__ __launch_bounds__(BN_THREADS) void bn_stats(const uint4* __restrict__ x, const uint4* __restrict__ y,
-                                                      const uint4* __restrict__ dy, const float* __restrict__ mean,
-                                                      const float* __restrict__ invstd, float* __restrict__ part, int64_t rows,
-                                                      int C, int cpr, int rpp, int64_t rows_per_slab, int relu, int csplit,
-                                                      const uint4* __restrict__ dy2 = nullptr, uint4* __restrict__ g_out = nullptr) {
-  __shared__ float red[2][BN_THREADS][8];
-  const int tid = threadIdx.x;
-  const int cpr_l = cpr / csplit;  // chunks of a row this workgroup handles: [cfirst, cfirst + cpr_l)
-  const int slab = blockIdx.x / csplit, cfirst = (blockIdx.x % csplit) * cpr_l;
+__global__ __launch_bounds__(BN_THREADS) void bn_stats(BnStatsArgs a) {
+  __shared__ __align__(16) float red[2][BN_THREADS][8];
+  constexpr bool GRAD = MODE != ST_SUM, NEEDS_Y = MODE == ST_RELU || MODE == ST_MASK || MODE == ST_END;
+  const int tid = threadIdx.x, cpr = a.cpr, rpp = a.rpp, C = a.C;
+  const int cpr_l = cpr / a.csplit;  // chunks of a row this workgroup handles: [cfirst, cfirst + cpr_l)
+  const int slab = blockIdx.x / a.csplit, cfirst = (blockIdx.x % a.csplit) * cpr_l;
   const int chunk_l = tid % cpr_l, rsub = tid / cpr_l;
   const int chunk = cfirst + chunk_l;
-  const int64_t r0 = (int64_t)slab * rows_per_slab;
-  int64_t r1 = r0 + rows_per_slab;
-  if (r1 > rows) r1 = rows;
+  const int64_t r0 = (int64_t)slab * a.rows_per_slab;
+  const int64_t r1 = r0 + a.rows_per_slab < a.rows ? r0 + a.rows_per_slab : a.rows;
   float s0[8], s1[8], mu[8], is[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     s0[e] = 0.f; s1[e] = 0.f; mu[e] = 0.f; is[e] = 0.f;
   }
-  if (MODE >= 1 && rsub < rpp) {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      mu[e] = mean[chunk * 8 + e];
-      is[e] = invstd[chunk * 8 + e];
-    }
+  if (GRAD && rsub < rpp) {
+    load8(a.mean + chunk * 8, mu);
+    load8(a.invstd + chunk * 8, is);
   }
-  // U rows of a lane are requested together (the loop is bound by memory latency otherwise)
-  constexpr int U = MODE == 0 ? 8 : 4;
-  for (int64_t r = r0 + rsub; rsub < rpp && r < r1; r += (int64_t)U * rpp) {
+  unsigned held = 0, *word = nullptr;  // ST_MASK: the bits of the rows before, and where they go
+  unsigned* next_word = MODE == ST_MASK ? a.mask + (size_t)blockIdx.x * a.mask_iters * BN_THREADS + tid : nullptr;
+  // U rows of a lane are requested together (the loop is bound by memory latency otherwise); rows beyond the slab add nothing
+  // (x = 0 and g = 0 contribute zero to every sum)
+  constexpr int U = MODE == ST_SUM ? 8 : BN_BWD_ROWS;
+  auto group = [&](int64_t r, auto whole_tag) {
+    constexpr bool WHOLE = decltype(whole_tag)::value;
     uint4 qx[U], qd[U], qy[U], qe[U];
-    const uint4 zero = make_uint4(0u, 0u, 0u, 0u);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int64_t ru = r + (int64_t)u * rpp;
-      const bool in = ru < r1;
-      const size_t idx = (size_t)(in ? ru : r) * cpr + chunk;
-      qx[u] = x[idx];
-      if (MODE >= 1) {
-        qd[u] = dy[idx];
-        qy[u] = (relu || MODE == 2) ? y[idx] : zero;
-      }
-      if (MODE == 2) qe[u] = dy2 ? dy2[idx] : zero;
-      if (!in) {            // rows beyond the slab add nothing (x = 0 and g = 0 contribute zero to every sum)
-        qx[u] = zero;
-        if (MODE >= 1) qd[u] = zero;
-        if (MODE == 2) qe[u] = zero;
+      const size_t idx = (size_t)ru * cpr + chunk;
+      if constexpr (!WHOLE) qx[u] = qd[u] = qy[u] = qe[u] = make_uint4(0u, 0u, 0u, 0u);
+      if (WHOLE || ru < r1) {
+        qx[u] = a.x[idx];
+        if constexpr (GRAD) qd[u] = a.dy[idx];
+        if constexpr (NEEDS_Y) qy[u] = a.y[idx];
+        if constexpr (MODE == ST_END)
+          if (a.dy2) qe[u] = a.dy2[idx];
       }
     }
-    if (MODE == 2) {        // form g, keep it as this row's dy, and store it
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        float a[8], b[8], m[8];
-        unpack8(qd[u], a);
-        unpack8(qe[u], b);
-        unpack8(qy[u], m);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) a[e] += b[e];  // exact in FP32; pack8 rounds once
-        uint4 gq = pack8(a);
-        unsigned gw[4] = {gq.x, gq.y, gq.z, gq.w};
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-          gw[k] = (m[2 * k] > 0.f ? (gw[k] & 0xffffu) : 0u) | (m[2 * k + 1] > 0.f ? (gw[k] & 0xffff0000u) : 0u);
-        qd[u] = make_uint4(gw[0], gw[1], gw[2], gw[3]);
-        const int64_t ru = r + (int64_t)u * rpp;
-        if (ru < r1) g_out[(size_t)ru * cpr + chunk] = qd[u];
-      }
+    if constexpr (MODE == ST_MASK) {
+      // the word of the group before goes out behind this group's loads: a wait for loads behind it would wait for the store too
+      if (word) __builtin_nontemporal_store(held, word);
+      word = next_word;
+      next_word += BN_THREADS;
+      held = 0;
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       float xv[8];
       unpack8(qx[u], xv);
-      if (MODE == 0) {
+      if constexpr (MODE == ST_SUM) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
           s0[e] += xv[e];
           s1[e] += xv[e] * xv[e];
         }
-      } else {
-        float gv[8];
-        unpack8(qd[u], gv);
-        if (MODE == 1 && relu) {
-          float yv[8];
-          unpack8(qy[u], yv);
+        continue;
+      }
+      float gv[8], yv[8];
+      unpack8(qd[u], gv);
+      if constexpr (NEEDS_Y) unpack8(qy[u], yv);
+      if constexpr (MODE == ST_END) {  // form g and store it
+        if (a.dy2) {
+          float ev[8];
+          unpack8(qe[u], ev);
 #pragma unroll
-          for (int e = 0; e < 8; ++e) gv[e] = yv[e] > 0.f ? gv[e] : 0.f;
+          for (int e = 0; e < 8; ++e) gv[e] += ev[e];  // exact in FP32; pack8 rounds once
         }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) gv[e] = yv[e] > 0.f ? gv[e] : 0.f;
+        const uint4 g = pack8(gv);
+        unpack8(g, gv);
+        const int64_t ru = r + (int64_t)u * rpp;
+        if (WHOLE || ru < r1) a.g_out[(size_t)ru * cpr + chunk] = g;
+      } else if constexpr (NEEDS_Y) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          s0[e] += gv[e];
-          s1[e] += gv[e] * ((xv[e] - mu[e]) * is[e]);
+          const bool on = yv[e] > 0.f;
+          gv[e] = on ? gv[e] : 0.f;
+          if constexpr (MODE == ST_MASK) held |= on ? 1u << (8 * u + e) : 0u;
         }
       }
-    }
-  }
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    red[0][tid][e] = s0[e];
-    red[1][tid][e] = s1[e];
-  }
-  __syncthreads();
-  if (rsub == 0) {
-    for (int j = 1; j < rpp; ++j)
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        s0[e] += red[0][j * cpr_l + chunk_l][e];
-        s1[e] += red[1][j * cpr_l + chunk_l][e];
+        s0[e] += gv[e];
+        s1[e] += gv[e] * ((xv[e] - mu[e]) * is[e]);
       }
-    float* p0 = part + ((size_t)slab * 2) * C + chunk * 8;
-    float* p1 = p0 + C;
-    *reinterpret_cast<float4*>(p0) = make_float4(s0[0], s0[1], s0[2], s0[3]);
-    *reinterpret_cast<float4*>(p0 + 4) = make_float4(s0[4], s0[5], s0[6], s0[7]);
-    *reinterpret_cast<float4*>(p1) = make_float4(s1[0], s1[1], s1[2], s1[3]);
-    *reinterpret_cast<float4*>(p1 + 4) = make_float4(s1[4], s1[5], s1[6], s1[7]);
+    }
+  };
+  if (rsub < rpp) {
+    int64_t r = r0 + rsub;
+    for (; r + (int64_t)(U - 1) * rpp < r1; r += (int64_t)U * rpp) group(r, std::true_type{});
+    if (r < r1) group(r, std::false_type{});
+  }
+  if (MODE == ST_MASK && word) __builtin_nontemporal_store(held, word);
+  // the rows' sums are added by all threads: each takes a channel's sum, of a part of the rows where there are fewer sums than
+  // threads (the lanes of one row adding up the others': 8.7 instead of 7.5 us for 200704 x 64)
+  const int ch = 8 * cpr_l, sums = 2 * ch;  // red[0] and red[1] are [rows of a pass][ch]
+  float* const r0s = &red[0][0][0];
+  float* const r1s = &red[1][0][0];
+#pragma unroll
+  for (int e = 0; e < 8; e += 4) {
+    *reinterpret_cast<float4*>(&red[0][tid][e]) = make_float4(s0[e], s0[e + 1], s0[e + 2], s0[e + 3]);
+    *reinterpret_cast<float4*>(&red[1][tid][e]) = make_float4(s1[e], s1[e + 1], s1[e + 2], s1[e + 3]);
+  }
+  __syncthreads();
+  float* const out = a.part + (size_t)slab * 2 * C + cfirst * 8;
+  if (sums >= BN_THREADS) {
+    for (int i = tid; i < sums; i += BN_THREADS) {
+      const float* p = i < ch ? r0s + i : r1s + (i - ch);
+      float t = 0.f;
+      for (int j = 0; j < rpp; ++j) t += p[j * ch];
+      out[i < ch ? i : C + i - ch] = t;
+    }
+    return;
+  }
+  const int parts = BN_THREADS / sums, i = tid % sums, first = tid / sums;
+  float t = 0.f;
+  if (first < parts) {
+    const float* p = i < ch ? r0s + i : r1s + (i - ch);
+    for (int j = first; j < rpp; j += parts) t += p[j * ch];
+  }
+  __syncthreads();
+  if (first < parts) r0s[first * sums + i] = t;
+  __syncthreads();
+  if (tid < sums) {
+    t = 0.f;
+    for (int k = 0; k < parts; ++k) t += r0s[k * sums + tid];
+    out[tid < ch ? tid : C + tid - ch] = t;
   }
 }
 
@@ -350,11 +409,6 @@ __global__ __launch_bounds__(BN_THREADS) void bn_bwd_final(const float* __restri
   bn_bwd_coef(sb, sg, inv_rows, gamma[c], mean[c], invstd[c], dgamma16 + c, dbeta16 + c, coef + c, C);
 }
 
-__device__ __forceinline__ void load8(const float* p, float (&f)[8]) {
-  const float4 t0 = reinterpret_cast<const float4*>(p)[0], t1 = reinterpret_cast<const float4*>(p)[1];
-  f[0] = t0.x; f[1] = t0.y; f[2] = t0.z; f[3] = t0.w; f[4] = t1.x; f[5] = t1.y; f[6] = t1.z; f[7] = t1.w;
-}
-
 __global__ __launch_bounds__(BN_THREADS) void bn_bwd_apply(const uint4* __restrict__ x, const uint4* __restrict__ y,
                                                           const uint4* __restrict__ dy, uint4* __restrict__ dx,
                                                           const float* __restrict__ coef, int64_t n_chunks, int C, int cpr, int relu) {
@@ -381,32 +435,92 @@ __global__ __launch_bounds__(BN_THREADS) void bn_bwd_apply(const uint4* __restri
   }
 }
 
+// The same with the ReLU's mask out of the words that the statistics pass left, by the workgroups, lanes and rows of that pass:
+// a quarter of the reads less.  802816 x 64 (103 MB a tensor): statistics 56 -> 63 us for writing the words, apply pass 63 -> 52;
+// ResNet-50's 53 layers at batch 64: 920 -> 970 and 888 -> 710 us.  A byte per 16 bytes of y at its place in the tensor, which any
+// mapping could read, cost the statistics 145 us; the words with the non-temporal hint cost the apply passes 50.
+__global__ __launch_bounds__(BN_THREADS) void bn_bwd_apply_masked(const uint4* __restrict__ x, const uint4* __restrict__ dy, uint4* __restrict__ dx,
+                                                                 const float* __restrict__ coef, const unsigned* __restrict__ mask,
+                                                                 int64_t rows, int C, int cpr, int rpp, int64_t rows_per_slab, int csplit) {
+  constexpr int U = BN_BWD_ROWS;
+  const int cpr_l = cpr / csplit, slab = blockIdx.x / csplit, rsub = threadIdx.x / cpr_l;
+  const int chunk = (blockIdx.x % csplit) * cpr_l + threadIdx.x % cpr_l;
+  const int64_t r0 = (int64_t)slab * rows_per_slab, r1 = r0 + rows_per_slab < rows ? r0 + rows_per_slab : rows;
+  if (rsub >= rpp) return;
+  mask += (size_t)blockIdx.x * ((rows_per_slab + U * rpp - 1) / (U * rpp)) * BN_THREADS + threadIdx.x;
+  float a[8], pc[8], qc[8];
+  load8(coef + chunk * 8, a);
+  load8(coef + C + chunk * 8, pc);
+  load8(coef + 2 * C + chunk * 8, qc);
+  uint4 qx[U], qd[U];
+  unsigned w = 0;
+  auto fetch = [&](int64_t r) {
+    if (r < r1) {
+      w = *mask;
+      mask += BN_THREADS;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t ru = r + (int64_t)u * rpp;
+      if (ru < r1) {
+        qx[u] = x[(size_t)ru * cpr + chunk];
+        qd[u] = dy[(size_t)ru * cpr + chunk];
+      }
+    }
+  };
+  fetch(r0 + rsub);
+  for (int64_t r = r0 + rsub; r < r1; r += (int64_t)U * rpp) {
+    uint4 o[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      float xv[8], gv[8], out[8];
+      unpack8(qx[u], xv);
+      unpack8(qd[u], gv);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float g = (w >> (8 * u + e)) & 1u ? gv[e] : 0.f;
+        out[e] = a[e] * g + (pc[e] * xv[e] + qc[e]);
+      }
+      o[u] = pack8(out);
+    }
+    fetch(r + (int64_t)U * rpp);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t ru = r + (int64_t)u * rpp;
+      if (ru < r1) store_streaming(dx + (size_t)ru * cpr + chunk, o[u]);
+    }
+  }
+}
+
 // ---- apply passes that finish the statistics themselves ----------------------------------------------------------------------
 // With few partial sums per channel (BN_MERGE_SLABS) the launch between the statistics and the apply pass does nothing but cost
 // its 4-5 us: here a workgroup owns 64 channels and a range of rows, adds up the partial sums of its channels (a few tens of KB
 // out of L2, while its first rows are on their way) and goes on.  The first workgroup of a channel range also writes what the
 // finalize kernel would.
 constexpr int BM_CH = 64;    // channels of a workgroup: one 128-byte line of every row
-constexpr int BM_ROWS = 32;  // rows one pass of a workgroup covers
+constexpr int BM_ROWS = BN_THREADS / (BM_CH / 8);  // rows one pass of a workgroup covers
 constexpr int BM_U = 4;      // passes whose loads are in flight together
 
-// the two sums of channel first + tid (tid < 64), FP64: four lanes per channel take every fourth slab, then added in lane order
+// the two sums of channel first + tid (tid < 64), FP64: T / 64 lanes per channel take every (T / 64)-th slab, then added in lane
+// order
+template <int T>
 __device__ __forceinline__ bool bn_merged_totals(const float* __restrict__ part, int slabs, int C, int first, double& s, double& q) {
-  __shared__ double red[2][BN_THREADS];
+  constexpr int LANES = T / BM_CH;
+  __shared__ double red[2][T];
   const int c = first + (threadIdx.x & (BM_CH - 1)), j = threadIdx.x / BM_CH;
   s = q = 0.0;
   if (c < C)
-    for (int k = j; k < slabs; k += 32) {  // eight slabs' sums requested together, added in slab order
+    for (int k = j; k < slabs; k += 8 * LANES) {  // eight slabs' sums requested together, added in slab order
       float a[8], b[8];
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
-        const int ku = k + 4 * u < slabs ? k + 4 * u : k;
+        const int ku = k + LANES * u < slabs ? k + LANES * u : k;
         a[u] = part[((size_t)ku * 2) * C + c];
         b[u] = part[((size_t)ku * 2 + 1) * C + c];
       }
 #pragma unroll
       for (int u = 0; u < 8; ++u)
-        if (k + 4 * u < slabs) {
+        if (k + LANES * u < slabs) {
           s += (double)a[u];
           q += (double)b[u];
         }
@@ -415,19 +529,20 @@ __device__ __forceinline__ bool bn_merged_totals(const float* __restrict__ part,
   red[1][threadIdx.x] = q;
   __syncthreads();
   if (j != 0 || c >= C) return false;
-  for (int l = 1; l < 4; ++l) {
+  for (int l = 1; l < LANES; ++l) {
     s += red[0][l * BM_CH + threadIdx.x];
     q += red[1][l * BM_CH + threadIdx.x];
   }
   return true;
 }
 
-template <int RES>
-__global__ __launch_bounds__(BN_THREADS) void bn_apply_merged(const uint4* __restrict__ x, const uint4* __restrict__ res, uint4* __restrict__ y,
+template <int RES, int T>
+__global__ __launch_bounds__(T) void bn_apply_merged(const uint4* __restrict__ x, const uint4* __restrict__ res, uint4* __restrict__ y,
                                                              int64_t rows, int rows_per_wg, int C, const float* __restrict__ part, int slabs,
                                                              double inv_rows, float eps, int relu, const float* __restrict__ gamma,
                                                              const float* __restrict__ beta, float* __restrict__ save_mean,
                                                              float* __restrict__ save_invstd) {
+  constexpr int ROWS = T / (BM_CH / 8);  // rows one pass covers
   __shared__ __align__(16) float coef[2][BM_CH];
   const int cpr = C / 8, first = blockIdx.x * BM_CH;
   const int chunk = blockIdx.x * (BM_CH / 8) + (threadIdx.x & 7), rsub = threadIdx.x / 8;
@@ -437,7 +552,7 @@ __global__ __launch_bounds__(BN_THREADS) void bn_apply_merged(const uint4* __res
   auto fetch = [&](int64_t r) {
 #pragma unroll
     for (int u = 0; u < BM_U; ++u) {
-      const int64_t ru = r + u * BM_ROWS;
+      const int64_t ru = r + u * ROWS;
       if (live && ru < r1) {
         q[u] = x[(size_t)ru * cpr + chunk];
         if (RES) e[u] = res[(size_t)ru * cpr + chunk];
@@ -446,7 +561,7 @@ __global__ __launch_bounds__(BN_THREADS) void bn_apply_merged(const uint4* __res
   };
   fetch(r0 + rsub);
   double s, sq;
-  if (bn_merged_totals(part, slabs, C, first, s, sq)) {
+  if (bn_merged_totals<T>(part, slabs, C, first, s, sq)) {
     const int c = first + threadIdx.x;
     const bool writer = blockIdx.y == 0;
     bn_fwd_coef(s, sq, inv_rows, eps, gamma[c], beta[c], writer ? save_mean + c : nullptr, writer ? save_invstd + c : nullptr,
@@ -456,7 +571,7 @@ __global__ __launch_bounds__(BN_THREADS) void bn_apply_merged(const uint4* __res
   float a[8], b[8];
   load8(&coef[0][(threadIdx.x & 7) * 8], a);
   load8(&coef[1][(threadIdx.x & 7) * 8], b);
-  for (int64_t r = r0 + rsub; r < r1; r += BM_U * BM_ROWS) {
+  for (int64_t r = r0 + rsub; r < r1; r += BM_U * ROWS) {
     uint4 o[BM_U];
 #pragma unroll
     for (int u = 0; u < BM_U; ++u) {
@@ -471,11 +586,13 @@ __global__ __launch_bounds__(BN_THREADS) void bn_apply_merged(const uint4* __res
       }
       o[u] = pack8(v);
     }
-    fetch(r + BM_U * BM_ROWS);
+    fetch(r + BM_U * ROWS);
 #pragma unroll
     for (int u = 0; u < BM_U; ++u) {
-      const int64_t ru = r + u * BM_ROWS;
-      if (live && ru < r1) y[(size_t)ru * cpr + chunk] = o[u];
+      const int64_t ru = r + u * ROWS;
+      if (!live || ru >= r1) continue;
+      if (T == BN_THREADS) y[(size_t)ru * cpr + chunk] = o[u];
+      else store_streaming(y + (size_t)ru * cpr + chunk, o[u]);
     }
   }
 }
@@ -506,7 +623,7 @@ __global__ __launch_bounds__(BN_THREADS) void bn_bwd_apply_merged(const uint4* _
   };
   fetch(r0 + rsub);
   double sb, sg;
-  if (bn_merged_totals(part, slabs, C, first, sb, sg)) {
+  if (bn_merged_totals<BN_THREADS>(part, slabs, C, first, sb, sg)) {
     const int c = first + threadIdx.x;
     const bool writer = blockIdx.y == 0;
     bn_bwd_coef(sb, sg, inv_rows, gamma[c], mean[c], invstd[c], writer ? dgamma16 + c : nullptr, writer ? dbeta16 + c : nullptr,
@@ -543,11 +660,11 @@ __global__ __launch_bounds__(BN_THREADS) void bn_bwd_apply_merged(const uint4* _
   }
 }
 
-// grid of a merged apply pass: about 2048 workgroups, at least one pass each
-dim3 merged_grid(int64_t rows, int C, int* rows_per_wg) {
+// grid of a merged apply pass: about `wgs` workgroups, at least one pass of `pass` rows each
+dim3 merged_grid(int64_t rows, int C, int pass, int wgs, int* rows_per_wg) {
   const int64_t groups = (C + BM_CH - 1) / BM_CH;
-  int64_t per = (rows * groups + 2047) / 2048;
-  per = (per + BM_ROWS - 1) / BM_ROWS * BM_ROWS;
+  int64_t per = (rows * groups + wgs - 1) / wgs;
+  per = (per + pass - 1) / pass * pass;
   *rows_per_wg = (int)per;
   return dim3((unsigned)groups, (unsigned)((rows + per - 1) / per));
 }
@@ -558,21 +675,30 @@ unsigned apply_grid(int64_t n_chunks) {
   return (unsigned)(b < cap ? b : cap);
 }
 
+template <int MODE>
+int launch_stats(const BnPlan& p, float* part, BnStatsArgs a, hipStream_t st) {
+  a.part = part;
+  a.rows = p.rows; a.rows_per_slab = p.rows_per_slab;
+  a.C = p.C; a.cpr = p.cpr; a.rpp = p.rpp; a.csplit = p.csplit; a.mask_iters = p.mask_iters;
+  hipLaunchKernelGGL(bn_stats<MODE>, dim3((unsigned)(p.slabs * p.csplit)), dim3(BN_THREADS), 0, st, a);
+  return jz::launch_status();
+}
+
 // what follows the partial sums of the forward pass: totals, saved statistics, y = [relu](a x + b [+ res])
 int launch_fwd_rest(const float* part, int slabs, float* coef, int64_t rows, int C, float eps, int relu, const float* gamma, const float* beta,
                     const uint4* x, const uint4* res, uint4* y, float* save_mean, float* save_invstd, hipStream_t st) {
   const double inv_rows = 1.0 / (double)rows;
-  if (slabs <= BN_MERGE_SLABS) {
+  auto merged = [&](auto kernel, int threads, int wgs) {
     int per;
-    const dim3 grid = merged_grid(rows, C, &per);
-    if (res)
-      hipLaunchKernelGGL(bn_apply_merged<1>, grid, dim3(BN_THREADS), 0, st, x, res, y, rows, per, C, part, slabs, inv_rows, eps, relu, gamma, beta,
-                         save_mean, save_invstd);
-    else
-      hipLaunchKernelGGL(bn_apply_merged<0>, grid, dim3(BN_THREADS), 0, st, x, res, y, rows, per, C, part, slabs, inv_rows, eps, relu, gamma, beta,
-                         save_mean, save_invstd);
+    const dim3 grid = merged_grid(rows, C, threads / (BM_CH / 8), wgs, &per);
+    hipLaunchKernelGGL(kernel, grid, dim3((unsigned)threads), 0, st, x, res, y, rows, per, C, part, slabs, inv_rows, eps, relu, gamma, beta, save_mean,
+                       save_invstd);
     return jz::launch_status();
-  }
+  };
+  const int64_t nb = rows * C * 2;
+  if (slabs <= BN_MERGE_SLABS_WIDE && nb >= BN_WIDE_BYTES && nb <= BN_FEW_SLABS_BYTES)
+    return res ? merged(bn_apply_merged<1, 512>, 512, 512) : merged(bn_apply_merged<0, 512>, 512, 512);
+  if (slabs <= BN_MERGE_SLABS) return res ? merged(bn_apply_merged<1, BN_THREADS>, BN_THREADS, 2048) : merged(bn_apply_merged<0, BN_THREADS>, BN_THREADS, 2048);
   hipLaunchKernelGGL(bn_fwd_final, dim3((unsigned)((C + BN_FIN_C - 1) / BN_FIN_C)), dim3(BN_THREADS), 0, st, part, slabs, C, inv_rows, eps, gamma,
                      beta, save_mean, save_invstd, coef);
   int rc = jz::launch_status();
@@ -587,13 +713,14 @@ int launch_fwd_rest(const float* part, int slabs, float* coef, int64_t rows, int
 
 // the same for the backward pass: parameter gradients, dx from g = dy (masked by y > 0 when relu)
 int launch_bwd_rest(const float* part, int slabs, float* coef, int64_t rows, int C, int relu, const float* gamma, const float* mean,
-                    const float* invstd, const uint4* x, const uint4* y, const uint4* dy, uint4* dx, void* dgamma16, void* dbeta16, hipStream_t st) {
+                    const float* invstd, const uint4* x, const uint4* y, const uint4* dy, uint4* dx, void* dgamma16, void* dbeta16, hipStream_t st,
+                    const unsigned* mask = nullptr, const BnPlan* p = nullptr) {
   const double inv_rows = 1.0 / (double)rows;
   unsigned short* dg = static_cast<unsigned short*>(dgamma16);
   unsigned short* db = static_cast<unsigned short*>(dbeta16);
   if (slabs <= BN_MERGE_SLABS) {
     int per;
-    const dim3 grid = merged_grid(rows, C, &per);
+    const dim3 grid = merged_grid(rows, C, BM_ROWS, 2048, &per);
     hipLaunchKernelGGL(bn_bwd_apply_merged, grid, dim3(BN_THREADS), 0, st, x, y, dy, dx, rows, per, C, part, slabs, inv_rows, relu, gamma, mean,
                        invstd, dg, db);
     return jz::launch_status();
@@ -603,7 +730,11 @@ int launch_bwd_rest(const float* part, int slabs, float* coef, int64_t rows, int
   int rc = jz::launch_status();
   if (rc != JZ_OK) return rc;
   const int64_t n_chunks = rows * (C / 8);
-  hipLaunchKernelGGL(bn_bwd_apply, dim3(apply_grid(n_chunks)), dim3(BN_THREADS), 0, st, x, y, dy, dx, coef, n_chunks, C, C / 8, relu);
+  if (mask)
+    hipLaunchKernelGGL(bn_bwd_apply_masked, dim3((unsigned)(p->slabs * p->csplit)), dim3(BN_THREADS), 0, st, x, dy, dx, coef, mask, rows, C, p->cpr,
+                       p->rpp, p->rows_per_slab, p->csplit);
+  else
+    hipLaunchKernelGGL(bn_bwd_apply, dim3(apply_grid(n_chunks)), dim3(BN_THREADS), 0, st, x, y, dy, dx, coef, n_chunks, C, C / 8, relu);
   return jz::launch_status();
 }
 
@@ -611,10 +742,11 @@ int launch_bwd_rest(const float* part, int slabs, float* coef, int64_t rows, int
 
 extern "C" int jz_bn_workspace_bytes(int64_t rows, int channels, size_t* bytes) {
   if (!bytes) return JZ_ERR_NULL;
-  BnPlan p;
-  int rc = make_bn_plan(rows, channels, &p);
+  BnPlan f, b;
+  int rc = make_bn_plan(rows, channels, true, &f);
   if (rc != JZ_OK) return rc;
-  *bytes = p.total;
+  make_bn_plan(rows, channels, false, &b);
+  *bytes = f.total > b.total + b.mask_bytes ? f.total : b.total + b.mask_bytes;
   return JZ_OK;
 }
 
@@ -622,7 +754,8 @@ extern "C" int jz_bn_relu_fwd(int64_t rows, int channels, const void* x16, const
                               int relu, void* y16, float* save_mean, float* save_invstd, void* ws, size_t ws_bytes,
                               void* hip_stream) {
   BnPlan p;
-  int rc = make_bn_plan(rows, channels, &p);
+  int rc = make_bn_plan(rows, channels, true, &p);
+  if (rc == JZ_OK && ws_bytes < p.total) rc = make_bn_plan(rows, channels, false, &p);
   if (rc != JZ_OK) return rc;
   if (!(eps >= 0.f)) return JZ_ERR_SHAPE;
   if (!x16 || !gamma || !beta || !y16 || !save_mean || !save_invstd) return JZ_ERR_NULL;
@@ -639,9 +772,7 @@ extern "C" int jz_bn_relu_fwd(int64_t rows, int channels, const void* x16, const
   float* part = reinterpret_cast<float*>(static_cast<char*>(ws) + p.off_part);
   float* coef = reinterpret_cast<float*>(static_cast<char*>(ws) + p.off_coef);
   const uint4* x = static_cast<const uint4*>(x16);
-  hipLaunchKernelGGL(bn_stats<0>, dim3((unsigned)(p.slabs * p.csplit)), dim3(BN_THREADS), 0, st, x, nullptr, nullptr, nullptr, nullptr,
-                     part, rows, channels, p.cpr, p.rpp, p.rows_per_slab, 0, p.csplit);
-  if ((rc = jz::launch_status()) != JZ_OK) return rc;
+  if ((rc = launch_stats<ST_SUM>(p, part, {.x = x}, st)) != JZ_OK) return rc;
   return launch_fwd_rest(part, p.slabs, coef, rows, channels, eps, relu ? 1 : 0, gamma, beta, x, nullptr, static_cast<uint4*>(y16), save_mean,
                          save_invstd, st);
 }
@@ -650,13 +781,15 @@ extern "C" int jz_bn_relu_bwd(int64_t rows, int channels, const void* x16, const
                               const float* gamma, const float* save_mean, const float* save_invstd, int relu, void* dx16,
                               void* dgamma16, void* dbeta16, void* ws, size_t ws_bytes, void* hip_stream) {
   BnPlan p;
-  int rc = make_bn_plan(rows, channels, &p);
+  int rc = make_bn_plan(rows, channels, false, &p);
   if (rc != JZ_OK) return rc;
   if (!x16 || !dy16 || !gamma || !save_mean || !save_invstd || !dx16 || !dgamma16 || !dbeta16 || (relu && !y16)) return JZ_ERR_NULL;
   if (!ws || ws_bytes < p.total) return JZ_ERR_WORKSPACE;
   if (!jz::aligned16(x16) || !jz::aligned16(dy16) || !jz::aligned16(dx16) || !jz::aligned16(ws) || (relu && !jz::aligned16(y16)) ||
       !jz::aligned16(gamma) || !jz::aligned16(save_mean) || !jz::aligned16(save_invstd))
     return JZ_ERR_ALIGN;
+  const bool keep_mask = relu && p.slabs > BN_MERGE_SLABS && ws_bytes >= p.total + p.mask_bytes;
+  if (keep_mask) p.total += p.mask_bytes;
   const size_t nb = (size_t)rows * channels * 2, nh = (size_t)channels * 2;
   if (jz::overlaps(dx16, nb, x16, nb) || jz::overlaps(dx16, nb, dy16, nb) || (relu && jz::overlaps(dx16, nb, y16, nb)) ||
       jz::overlaps(ws, p.total, x16, nb) || jz::overlaps(ws, p.total, dy16, nb) || jz::overlaps(ws, p.total, dx16, nb) ||
@@ -667,21 +800,22 @@ extern "C" int jz_bn_relu_bwd(int64_t rows, int channels, const void* x16, const
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   float* part = reinterpret_cast<float*>(static_cast<char*>(ws) + p.off_part);
   float* coef = reinterpret_cast<float*>(static_cast<char*>(ws) + p.off_coef);
+  unsigned* mask = keep_mask ? reinterpret_cast<unsigned*>(static_cast<char*>(ws) + p.total - p.mask_bytes) : nullptr;
   const uint4* x = static_cast<const uint4*>(x16);
   const uint4* y = static_cast<const uint4*>(y16);
   const uint4* dy = static_cast<const uint4*>(dy16);
-  hipLaunchKernelGGL(bn_stats<1>, dim3((unsigned)(p.slabs * p.csplit)), dim3(BN_THREADS), 0, st, x, y, dy, save_mean, save_invstd, part, rows,
-                     channels, p.cpr, p.rpp, p.rows_per_slab, relu ? 1 : 0, p.csplit);
-  if ((rc = jz::launch_status()) != JZ_OK) return rc;
+  const BnStatsArgs in{.x = x, .y = y, .dy = dy, .mask = mask, .mean = save_mean, .invstd = save_invstd};
+  rc = !relu ? launch_stats<ST_GRAD>(p, part, in, st) : mask ? launch_stats<ST_MASK>(p, part, in, st) : launch_stats<ST_RELU>(p, part, in, st);
+  if (rc != JZ_OK) return rc;
   return launch_bwd_rest(part, p.slabs, coef, rows, channels, relu ? 1 : 0, gamma, save_mean, save_invstd, x, y, dy, static_cast<uint4*>(dx16),
-                         dgamma16, dbeta16, st);
+                         dgamma16, dbeta16, st, mask, &p);
 }
 
 extern "C" int jz_bn_bwd_block_end(int64_t rows, int channels, const void* x16, const void* y_out16, const void* dya16,
                                    const void* dyb16, const float* gamma, const float* save_mean, const float* save_invstd,
                                    void* g16, void* dx16, void* dgamma16, void* dbeta16, void* ws, size_t ws_bytes, void* hip_stream) {
   BnPlan p;
-  int rc = make_bn_plan(rows, channels, &p);
+  int rc = make_bn_plan(rows, channels, false, &p);
   if (rc != JZ_OK) return rc;
   if (!x16 || !y_out16 || !dya16 || !gamma || !save_mean || !save_invstd || !g16 || !dx16 || !dgamma16 || !dbeta16) return JZ_ERR_NULL;
   if (!ws || ws_bytes < p.total) return JZ_ERR_WORKSPACE;
@@ -703,10 +837,10 @@ extern "C" int jz_bn_bwd_block_end(int64_t rows, int channels, const void* x16, 
   float* part = reinterpret_cast<float*>(static_cast<char*>(ws) + p.off_part);
   float* coef = reinterpret_cast<float*>(static_cast<char*>(ws) + p.off_coef);
   const uint4* x = static_cast<const uint4*>(x16);
-  hipLaunchKernelGGL(bn_stats<2>, dim3((unsigned)(p.slabs * p.csplit)), dim3(BN_THREADS), 0, st, x, static_cast<const uint4*>(y_out16),
-                     static_cast<const uint4*>(dya16), save_mean, save_invstd, part, rows, channels, p.cpr, p.rpp, p.rows_per_slab, 0,
-                     p.csplit, static_cast<const uint4*>(dyb16), static_cast<uint4*>(g16));
-  if ((rc = jz::launch_status()) != JZ_OK) return rc;
+  rc = launch_stats<ST_END>(p, part, {.x = x, .y = static_cast<const uint4*>(y_out16), .dy = static_cast<const uint4*>(dya16),
+                                      .dy2 = static_cast<const uint4*>(dyb16), .g_out = static_cast<uint4*>(g16), .mean = save_mean,
+                                      .invstd = save_invstd}, st);
+  if (rc != JZ_OK) return rc;
   return launch_bwd_rest(part, p.slabs, coef, rows, channels, 0, gamma, save_mean, save_invstd, x, nullptr, static_cast<const uint4*>(g16),
                          static_cast<uint4*>(dx16), dgamma16, dbeta16, st);
 }
@@ -725,7 +859,7 @@ int make_conv_bn_plan(const jz_conv_desc* d, ConvBnPlan* p) {
   int rc = jz::conv_fwd_stats_plan(d, &p->conv_ws, &p->tiles_m);
   if (rc != JZ_OK) return rc;
   const int P = (d->H + 2 * d->pad_h - d->R) / d->stride_h + 1, Q = (d->W + 2 * d->pad_w - d->S) / d->stride_w + 1;
-  rc = make_bn_plan((int64_t)d->N * P * Q, d->K, &p->bn);
+  rc = make_bn_plan((int64_t)d->N * P * Q, d->K, false, &p->bn);
   if (rc != JZ_OK) return rc;
   const int slabs = p->tiles_m > p->bn.slabs ? p->tiles_m : p->bn.slabs;
   p->off_bn = up256(p->conv_ws);
@@ -783,9 +917,7 @@ extern "C" int jz_conv2d_bn_relu_fwd(const jz_conv_desc* desc, const void* x16, 
   int slabs = p.tiles_m;
   if (slabs == 0) {  // this convolution kernel cannot leave the sums: one more pass over its output
     slabs = p.bn.slabs;
-    hipLaunchKernelGGL(bn_stats<0>, dim3((unsigned)(slabs * p.bn.csplit)), dim3(BN_THREADS), 0, st, c, nullptr, nullptr, nullptr, nullptr,
-                       part, rows, C, p.bn.cpr, p.bn.rpp, p.bn.rows_per_slab, 0, p.bn.csplit);
-    if ((rc = jz::launch_status()) != JZ_OK) return rc;
+    if ((rc = launch_stats<ST_SUM>(p.bn, part, {.x = c}, st)) != JZ_OK) return rc;
   }
   return launch_fwd_rest(part, slabs, coef, rows, C, eps, relu ? 1 : 0, gamma, beta, c, static_cast<const uint4*>(residual16),
                          static_cast<uint4*>(y16), save_mean, save_invstd, st);
@@ -807,7 +939,7 @@ struct ConvBnBwdPlan {
 int make_conv_bn_bwd_plan(const jz_conv_desc* d, ConvBnBwdPlan* p) {
   int rc = jz::conv_bwd_data_stats_plan(d, &p->conv_ws, &p->tiles_m);
   if (rc != JZ_OK) return rc;
-  rc = make_bn_plan((int64_t)d->N * d->H * d->W, d->C, &p->bn);
+  rc = make_bn_plan((int64_t)d->N * d->H * d->W, d->C, false, &p->bn);
   if (rc != JZ_OK) return rc;
   const int slabs = p->tiles_m > p->bn.slabs ? p->tiles_m : p->bn.slabs;
   p->off_bn = up256(p->conv_ws);
@@ -878,14 +1010,11 @@ static int conv_bwd_data_bn_bwd(const jz_conv_desc* desc, const void* dy16, cons
   int slabs = p.tiles_m;
   if (slabs == 0) {  // this convolution kernel cannot leave the sums: the statistics pass, which then also forms g in place
     slabs = p.bn.slabs;
-    if (block_end)
-      hipLaunchKernelGGL(bn_stats<2>, dim3((unsigned)(slabs * p.bn.csplit)), dim3(BN_THREADS), 0, st, x, y, dz, save_mean, save_invstd, part,
-                         rows, C, p.bn.cpr, p.bn.rpp, p.bn.rows_per_slab, 0, p.bn.csplit, static_cast<const uint4*>(add16),
-                         static_cast<uint4*>(out16));
-    else
-      hipLaunchKernelGGL(bn_stats<1>, dim3((unsigned)(slabs * p.bn.csplit)), dim3(BN_THREADS), 0, st, x, y, dz, save_mean, save_invstd, part,
-                         rows, C, p.bn.cpr, p.bn.rpp, p.bn.rows_per_slab, 1, p.bn.csplit);
-    if ((rc = jz::launch_status()) != JZ_OK) return rc;
+    BnStatsArgs in{.x = x, .y = y, .dy = dz, .mean = save_mean, .invstd = save_invstd};
+    in.dy2 = static_cast<const uint4*>(add16);
+    in.g_out = static_cast<uint4*>(out16);
+    rc = block_end ? launch_stats<ST_END>(p.bn, part, in, st) : launch_stats<ST_RELU>(p.bn, part, in, st);
+    if (rc != JZ_OK) return rc;
   }
   return launch_bwd_rest(part, slabs, coef, rows, C, block_end ? 0 : 1, gamma, save_mean, save_invstd, x, block_end ? nullptr : y, dz,
                          static_cast<uint4*>(bn_dx16), dgamma16, dbeta16, st);

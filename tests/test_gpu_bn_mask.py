@@ -1,0 +1,41 @@
+"""Batch normalization, the routes that depend on the workspace and on the tensor's size: the ReLU mask kept as bits between the
+backward passes against the pass that reads y again, and forward statistics with few, shared slabs against those of a
+workspace that holds the other plan only."""
+import numpy as np
+import pytest
+import torch
+
+import jzt
+from test_gpu_bn import _inputs, _run, jz  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+# rows, channels: one word a lane and less, rows that end inside a group, several workgroups a slab, idle lanes
+SHAPES = [(4160, 256), (12544, 72), (12545, 128), (3136, 2048), (3139, 1024), (70001, 8), (8192 + 3, 264)]
+
+
+@pytest.mark.parametrize("rows,C", SHAPES)
+def test_mask_words_give_the_bits_of_the_pass_over_y(jz, rows, C):  # noqa: F811
+    gen = torch.Generator(device="cuda").manual_seed(rows + C)
+    rnd = lambda *s: torch.randn(*s, generator=gen, device="cuda")
+    x, dy, y = rnd(rows, C).half(), rnd(rows, C).half(), rnd(rows, C).half()
+    y.view(-1)[::7] = 0.0
+    y.view(-1)[3::11] = float("nan")
+    gamma, mean, invstd = rnd(C), rnd(C), rnd(C).abs() + 0.1
+    full = jz.jz_bn_workspace_bytes(rows, C)
+    res = []
+    for n in (full, full - rows * C // 8):  # without room for the bits
+        dx = torch.full((rows, C), 7.0, device="cuda", dtype=torch.float16)
+        dg, db = torch.zeros(C, device="cuda", dtype=torch.float16), torch.zeros(C, device="cuda", dtype=torch.float16)
+        ws = torch.full((n + 256,), 0xA5, dtype=torch.uint8, device="cuda")
+        jz.jz_bn_relu_bwd(rows, C, x, y, dy, gamma, mean, invstd, True, dx, dg, db, ws[:n])
+        assert bool((ws[n:] == 0xA5).all())
+        res.append([jzt.bits(t.cpu().numpy()) for t in (dx, dg, db)])
+    for a, b in zip(*res):
+        assert np.array_equal(a, b)
+
+
+# sizes on either side of the limits of the shared-slab plan, channel counts that are not multiples of its 64
+@pytest.mark.parametrize("rows,C", [(8191, 256), (8192, 256), (12545, 256), (3136, 2048), (29128, 72), (2100, 1000), (16385, 136)])
+@pytest.mark.parametrize("relu", [True, False])
+def test_forward_and_backward_against_the_oracle(jz, rows, C, relu):  # noqa: F811
+    _run(jz, *_inputs((rows, C, 9), rows, C), 1e-5, relu)
