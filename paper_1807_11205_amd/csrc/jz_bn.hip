@@ -96,7 +96,8 @@ int make_bn_plan(int64_t rows, int channels, bool forward, BnPlan* p) {
   p->off_coef = up256((size_t)p->slabs * 2 * channels * sizeof(float));
   p->total = p->off_coef + up256((size_t)4 * channels * sizeof(float));
   p->mask_iters = (int)((p->rows_per_slab + BN_BWD_ROWS * (int64_t)p->rpp - 1) / (BN_BWD_ROWS * (int64_t)p->rpp));
-  p->mask_bytes = (size_t)p->slabs * p->csplit * p->mask_iters * BN_THREADS * 4;
+  if (p->slabs > BN_MERGE_SLABS)  // an apply pass that finishes the statistics itself reads y
+    p->mask_bytes = (size_t)p->slabs * p->csplit * p->mask_iters * BN_THREADS * 4;
   return JZ_OK;
 }
 
@@ -788,7 +789,7 @@ extern "C" int jz_bn_relu_bwd(int64_t rows, int channels, const void* x16, const
   if (!jz::aligned16(x16) || !jz::aligned16(dy16) || !jz::aligned16(dx16) || !jz::aligned16(ws) || (relu && !jz::aligned16(y16)) ||
       !jz::aligned16(gamma) || !jz::aligned16(save_mean) || !jz::aligned16(save_invstd))
     return JZ_ERR_ALIGN;
-  const bool keep_mask = relu && p.slabs > BN_MERGE_SLABS && ws_bytes >= p.total + p.mask_bytes;
+  const bool keep_mask = relu && p.mask_bytes > 0 && ws_bytes >= p.total + p.mask_bytes;
   if (keep_mask) p.total += p.mask_bytes;
   const size_t nb = (size_t)rows * channels * 2, nh = (size_t)channels * 2;
   if (jz::overlaps(dx16, nb, x16, nb) || jz::overlaps(dx16, nb, dy16, nb) || (relu && jz::overlaps(dx16, nb, y16, nb)) ||
