@@ -588,7 +588,8 @@ def chain_workload(args):
     gpu_ms = float(np.mean([e[0].elapsed_time(e[3]) for e in ev]))
     tflops = net.flops_per_step() / (gpu_ms * 1e-3) / 1e12
     kinds = {}
-    for op in net.trace:
+    calls = net.fwd_ops + net.bwd_schedule + net.trace[-1:]
+    for op in calls:
         kinds[op.kind] = kinds.get(op.kind, 0) + 1
     print(json.dumps({
         "metric": "ResNet-50 N=%d chained training step images/s" % args.batch, "value": args.batch / (ms * 1e-3), "unit": "images/s",
@@ -596,7 +597,7 @@ def chain_workload(args):
         "vs_baseline": None, "dtype": "f16 storage, f32 accumulate, f32 master weights", "data": "synthetic",
         "config": {"workload": "ResNet-50 v1 chained step: conv + batch norm + ReLU + pooling + residual adds + classifier + "
                                "softmax loss gradient, backward, LARS with dynamic loss scale", "batch": args.batch, "image": args.image,
-                   "launch": "eager", "streams": 1 + (len(side) if side else 0), "launches_per_step": len(net.trace), "launches_by_kind": kinds,
+                   "launch": "eager", "streams": 1 + (len(side) if side else 0), "launches_per_step": len(calls), "launches_by_kind": kinds,
                    "conv_bn_forward": "one call, statistics in the convolution epilogue" if net.fused else "two calls",
                    "loss_scale": api.loss_scale_state(net.ls_state)[0], "steps_skipped_while_the_scale_settled": skipped,
                    "mean_loss": net.mean_loss()},

@@ -18,11 +18,12 @@ JZ_ERR_NULL, JZ_ERR_SHAPE, JZ_ERR_UNSUPPORTED, JZ_ERR_WORKSPACE = -1, -2, -3, -4
 JZ_ERR_ALIGN, JZ_ERR_ALIAS, JZ_ERR_LAUNCH, JZ_ERR_NOT_PREPARED = -5, -6, -7, -8
 JZ_FWD, JZ_BWD_DATA, JZ_BWD_WEIGHT = 0, 1, 2
 JZ_BESIDE = 16
+JZ_SET_MAX = 11
 JZ_PARAM_WEIGHT_DECAY, JZ_PARAM_LARS, JZ_PARAM_GRAD_PRESUMMED = 1, 2, 4
 
 EXPORTS = [
     "jz_conv2d_workspace_bytes", "jz_conv2d_describe_plan", "jz_conv2d_tune_set", "jz_conv2d_tune_use_table", "jz_conv2d_tune_clear", "jz_conv2d_fwd", "jz_conv2d_bwd_data", "jz_conv2d_bwd_weight", "jz_conv2d_bwd_weight_static",
-    "jz_conv2d_bwd_weight_sumsq", "jz_conv2d_bwd_weight_beside", "jz_gemm_fc_workspace_bytes", "jz_gemm_fc", "jz_gemm_fc_bwd_weight_sumsq",
+    "jz_conv2d_bwd_weight_sumsq", "jz_conv2d_bwd_weight_beside", "jz_conv2d_bwd_weight_set_workspace_bytes", "jz_conv2d_bwd_weight_set", "jz_gemm_fc_workspace_bytes", "jz_gemm_fc", "jz_gemm_fc_bwd_weight_sumsq",
     "jz_conv2d_f32_workspace_bytes", "jz_conv2d_fwd_f32", "jz_conv2d_bwd_data_f32", "jz_conv2d_bwd_weight_f32",
     "jz_gemm_fc_f32_workspace_bytes", "jz_gemm_fc_f32",
     "jz_lars_workspace_bytes", "jz_lars_prepare", "jz_lars_mp_update", "jz_loss_scale_init", "jz_lars_mp_update_dyn",
@@ -104,6 +105,9 @@ def lib() -> ctypes.CDLL:
         sk = ctypes.POINTER(jz_sumsq_sink)
         L.jz_conv2d_bwd_weight_sumsq.argtypes = [dp, vp, vp, vp, vp, sz, sk, vp]
         L.jz_conv2d_bwd_weight_beside.argtypes = [dp, vp, vp, vp, vp, sz, sk, vp]
+        pv = ctypes.POINTER(vp)
+        L.jz_conv2d_bwd_weight_set_workspace_bytes.argtypes = [ci, dp, ctypes.POINTER(sz)]
+        L.jz_conv2d_bwd_weight_set.argtypes = [ci, dp, pv, pv, pv, vp, sz, vp]
         L.jz_gemm_fc_bwd_weight_sumsq.argtypes = [ci, ci, ci, vp, vp, vp, vp, sz, sk, vp]
         L.jz_conv2d_f32_workspace_bytes.argtypes = [ci, dp, ctypes.POINTER(sz)]
         for name in ("jz_conv2d_fwd_f32", "jz_conv2d_bwd_data_f32", "jz_conv2d_bwd_weight_f32"):
@@ -393,6 +397,33 @@ def bind_conv2d(op: int, desc, a16, b16, out16, ws=None) -> BoundCall:
     args = (ctypes.byref(d), _dev_ptr(a16, h, na, "first operand"), _dev_ptr(b16, h, nb, "second operand"),
             _dev_ptr(out16, h, no, "output"), wp, wn)
     return BoundCall(getattr(lib(), name), args, name, (d, a16, b16, out16, ws))
+
+
+def _desc_array(descs):
+    return (jz_conv_desc * len(descs))(*descs)
+
+
+def jz_conv2d_bwd_weight_set_workspace_bytes(descs) -> int:
+    n = ctypes.c_size_t(0)
+    _check(lib().jz_conv2d_bwd_weight_set_workspace_bytes(len(descs), _desc_array(descs), ctypes.byref(n)), "jz_conv2d_bwd_weight_set_workspace_bytes")
+    return int(n.value)
+
+
+def bind_conv2d_bwd_weight_set(descs, x16, dy16, dw16, ws=None) -> BoundCall:
+    """Pre-marshalled jz_conv2d_bwd_weight_set: lists of descriptors and tensors, one entry a layer."""
+    h, n = torch.float16, len(descs)
+    if not len(x16) == len(dy16) == len(dw16) == n:
+        raise ValueError("one x, dy and dw for each descriptor")
+    arr = ctypes.c_void_p * n
+    px = arr(*(_dev_ptr(t, h, d.N * d.H * d.W * d.C, "x16") for d, t in zip(descs, x16)))
+    py = arr(*(_dev_ptr(t, h, d.N * d.P * d.Q * d.K, "dy16") for d, t in zip(descs, dy16)))
+    pw = arr(*(_dev_ptr(t, h, d.K * d.R * d.S * d.C, "dw16") for d, t in zip(descs, dw16)))
+    da, (wp, wn) = _desc_array(descs), _ws(ws)
+    return BoundCall(lib().jz_conv2d_bwd_weight_set, (n, da, px, py, pw, wp, wn), "jz_conv2d_bwd_weight_set", (da, x16, dy16, dw16, ws))
+
+
+def jz_conv2d_bwd_weight_set(descs, x16, dy16, dw16, ws=None, stream=None):
+    bind_conv2d_bwd_weight_set(descs, x16, dy16, dw16, ws)(stream)
 
 
 def bind_gemm_fc(mode, batch, in_features, out_features, a16, b16, out16, ws=None) -> BoundCall:

@@ -168,12 +168,12 @@ __global__ __launch_bounds__(256) void unpack_filter_c4(const unsigned short* __
 // for the small outputs that need many splits: with one thread per output group those launches were latency-bound.
 // KT4 > 0 (small-channel backward-weight): the sums are dw'[K][R][4 KT4] of the padded 4-channel problem; group
 // (kr, s) of four goes to dw[kr][s][0..C) when s < S and nowhere otherwise, which saves the separate unpacking launch.
-__global__ __launch_bounds__(256) void splitk_reduce(const float* __restrict__ part, unsigned short* __restrict__ out,
-                                                     long long MN, int splits, int lg, int KT4, int S, int C) {
+__device__ __forceinline__ void splitk_reduce_body(const float* __restrict__ part, unsigned short* __restrict__ out, long long MN, int splits,
+                                                   int lg, int KT4, int S, int C, unsigned block) {
   __shared__ float4 red[256];
   const int G = 1 << lg, Q = 256 >> lg;
   const int q = threadIdx.x & (Q - 1), g = threadIdx.x >> (8 - lg);
-  const long long i = ((long long)blockIdx.x * Q + q) * 4;
+  const long long i = ((long long)block * Q + q) * 4;
   // 16-byte loads need every split's slab to start on a 16-byte boundary: MN a multiple of 4
   const bool full = i + 3 < MN && (MN & 3) == 0;
   float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -236,6 +236,26 @@ __global__ __launch_bounds__(256) void splitk_reduce(const float* __restrict__ p
       out[i + e] = bts;
     }
   }
+}
+
+__global__ __launch_bounds__(256) void splitk_reduce(const float* __restrict__ part, unsigned short* __restrict__ out,
+                                                     long long MN, int splits, int lg, int KT4, int S, int C) {
+  splitk_reduce_body(part, out, MN, splits, lg, KT4, S, C, blockIdx.x);
+}
+
+// The same for several weight gradients in one launch.
+struct ReduceSet {
+  const float* part[kWgradSet];
+  unsigned short* out[kWgradSet];
+  long long MN[kWgradSet];
+  int splits[kWgradSet], lg[kWgradSet];
+  unsigned first[kWgradSet + 1];
+};
+__global__ __launch_bounds__(256) void splitk_reduce_set(ReduceSet s) {
+  int k = 0;
+#pragma unroll
+  for (int j = 1; j < kWgradSet; ++j) k += blockIdx.x >= s.first[j] ? 1 : 0;
+  splitk_reduce_body(s.part[k], s.out[k], s.MN[k], s.splits[k], s.lg[k], 0, 0, 0, blockIdx.x - s.first[k]);
 }
 
 // splitk_reduce that also leaves the sum of squares of the FP16 values it writes (and whether any of them is Inf / NaN)
@@ -971,6 +991,13 @@ bool plan_leaves_bwd_stats(const Plan& pl) {
 // row groups of those sums: row tiles, or slabs of the reduction
 int stats_groups(const Plan& pl) { return pl.args.splits > 1 ? reduce_slabs(pl.args) : pl.args.tiles_m; }
 
+// log2 of the split lanes per output group: enough workgroups to cover the chip first, then shorten each thread's chain
+int reduce_lanes(long long MN, int splits) {
+  int lg = 0;
+  while (splits > 1 && lg < 5 && (2 << lg) <= splits && ((MN + 3) / 4 + (256 >> lg) - 1) / (256 >> lg) < 1024) ++lg;
+  return lg;
+}
+
 int run_widened(int op, const jz_conv_desc* d, const Plan& pl, const void* A, const void* B, void* D, void* ws, size_t ws_bytes,
                 void* stream, const jz::SumsqSink* sink);
 
@@ -1106,11 +1133,7 @@ int run(int op, const jz_conv_desc* d, const void* A, const void* B, void* D, vo
   else if (op == JZ_BWD_DATA) rc = !epilogue_stats ? launch_bwd_data(pl, st) : bn->block_end ? launch_bwd_data_block_end(pl, st) : launch_bwd_data_stats(pl, st);
   else rc = launch_bwd_weight(pl, st);
   if (rc != JZ_OK) return rc;
-  int lg = 0;
-  if (a.splits > 1) {  // split lanes per output group: enough workgroups to cover the chip first, then shorten each thread's chain
-    const long long MN = (long long)a.M * a.N;
-    while (lg < 5 && (2 << lg) <= a.splits && ((MN + 3) / 4 + (256 >> lg) - 1) / (256 >> lg) < 1024) ++lg;
-  }
+  const int lg = reduce_lanes((long long)a.M * a.N, a.splits);
   if (a.splits > 1 && stats) {
     const dim3 grid((unsigned)((a.N + RS_COLS - 1) / RS_COLS), (unsigned)reduce_slabs(a));
     const int mode = op == JZ_FWD ? 0 : bn->block_end ? 2 : 1;
@@ -1389,6 +1412,176 @@ extern "C" int jz_conv2d_bwd_weight_beside(const jz_conv_desc* desc, const void*
   jz::SumsqSink sk;
   if ((rc = check_sink(sink, dw16, pl.bytesD, ws, ws_bytes < pl.ws_bytes ? ws_bytes : pl.ws_bytes, &sk)) != JZ_OK) return rc;
   return run(op, desc, dy16, x16, dw16, ws, ws_bytes, hip_stream, nullptr, 0, &sk);
+}
+
+// ---- weight gradients of several layers -----------------------------------------------------------------------------------------
+namespace {
+
+bool joins_set(const Plan& pl) { return pl.fast && !pl.packed && !pl.widen; }
+
+struct SetPlan {
+  Plan m[kWgradSet];  // the members, longest reductions first, all of one variant
+  int index[kWgradSet];
+  int n = 0;
+  size_t part_bytes = 0;
+};
+
+// One variant for all members and the most k tiles a workgroup walks through (longer reductions are split), by the cost model
+// of choose_tiling with all members' workgroups together.  `in`: the members' own plans.
+void choose_set(const Plan* in, int n, size_t limit, SetPlan* sp) {
+  // offered: what the model chooses for sets of ResNet-50's layers, 8 to 64 images of 64 to 224 pixels
+  static const int offered[][5] = {{128, 128, 32, 8, 4}, {64, 64, 64, 4, 4}, {64, 64, 32, 4, 4}};
+  static const int caps[] = {4, 6, 8, 12, 16, 24, 32, 48, 64, 96, 128, 192, 256, 512, 1 << 30};
+  const CostGlobals& cg = kCost[2];
+  auto p4 = [](double x) { return (x * x) * (x * x); };
+  double best = 1e30;
+  const Variant* bv = nullptr;
+  int bcap = 1 << 30;
+  for (const Variant& v : kVariants) {
+    bool ok = false;
+    for (const auto& o : offered) ok |= v.BM == o[0] && v.BN == o[1] && v.bk == o[2] && v.waves == o[3] && v.nst == o[4];
+    if (!ok) continue;
+    for (int cap : caps) {
+      double lat = 0, thr = 0, longest = 0, mem = 0, part = 0;
+      for (int i = 0; i < n; ++i) {
+        const GemmArgs& a = in[i].args;
+        const int nkt = (a.Kred + v.bk - 1) / v.bk, s = (nkt - 1) / cap + 1, kps = (nkt + s - 1) / s, real = (nkt + kps - 1) / kps;
+        const double blocks = (double)((a.M + v.BM - 1) / v.BM) * ((a.N + v.BN - 1) / v.BN) * real;
+        const double loop = kps * (a.g.R * a.g.S > 1 ? cg.taps : 1.0), out = 1e-6 * (double)a.M * a.N;
+        lat += blocks * (v.prologue[2] + v.lat[2] * loop);
+        thr += blocks * (v.own[2] + v.thr[2] * loop);
+        longest = std::max(longest, v.prologue[2] + v.lat[2] * loop);
+        mem += 1e-6 * ((double)std::min<long long>(in[i].bytesA, 2ll * a.M * a.Kred) + (double)std::min<long long>(in[i].bytesB, 2ll * a.N * a.Kred)) + 2.0 * out;
+        if (real > 1) part += 4.0 * real * out;
+      }
+      if (1e6 * part > (double)limit) continue;
+      const double t_lat = std::max(longest, lat / (kUnits * v.resident) + 0.5 * longest);
+      double t = cg.fixed + std::sqrt(std::sqrt(p4(t_lat) + p4(thr / kUnits) + p4(cg.byte * (mem + part))));
+      if (part > 0) t += cg.reduce_launch + cg.reduce_byte * part;
+      if (t < best) { best = t; bv = &v; bcap = cap; }
+    }
+  }
+  sp->n = n;
+  for (int i = 0; i < n; ++i) sp->index[i] = i;
+  std::stable_sort(sp->index, sp->index + n, [&](int x, int y) {
+    auto kps = [&](int i) { const int nkt = (in[i].args.Kred + bv->bk - 1) / bv->bk, s = (nkt - 1) / bcap + 1; return (nkt + s - 1) / s; };
+    return kps(x) > kps(y);
+  });
+  sp->part_bytes = 0;
+  for (int i = 0; i < n; ++i) {
+    Plan& m = sp->m[i];
+    m = in[sp->index[i]];
+    m.BM = bv->BM; m.BN = bv->BN; m.bk = bv->bk; m.waves = bv->waves; m.nst = bv->nst;
+    set_tiles(&m, ((m.args.Kred + m.bk - 1) / m.bk - 1) / bcap + 1);
+    m.part_offset = sp->part_bytes;
+    if (m.args.splits > 1) sp->part_bytes += up256((size_t)m.args.splits * m.args.M * m.args.N * sizeof(float));
+  }
+}
+
+int run_set(const SetPlan& sp, const void* const* x16, const void* const* dy16, void* const* dw16, void* ws, hipStream_t st) {
+  WgradSet set;
+  ReduceSet red{};
+  int r = 0;
+  set.first[0] = 0;
+  for (int i = 0; i < kWgradSet; ++i) {
+    if (i >= sp.n) {
+      set.first[i + 1] = set.first[i];
+      continue;
+    }
+    const Plan& m = sp.m[i];
+    GemmArgs& a = set.g[i];
+    a = m.args;
+    a.A = static_cast<const unsigned short*>(dy16[sp.index[i]]);
+    a.B = static_cast<const unsigned short*>(x16[sp.index[i]]);
+    a.D16 = static_cast<unsigned short*>(dw16[sp.index[i]]);
+    a.bytesA = (unsigned)m.bytesA;
+    a.bytesB = (unsigned)m.bytesB;
+    a.Dpart = reinterpret_cast<float*>(static_cast<char*>(ws) + m.part_offset);
+    a.stats = nullptr;
+    a.st_y = a.st_c = a.st_add = nullptr;
+    a.st_mean = a.st_invstd = nullptr;
+    set.first[i + 1] = set.first[i] + (unsigned)a.tiles_m * (unsigned)a.tiles_n * (unsigned)a.splits;
+    if (a.splits > 1) {
+      const long long MN = (long long)a.M * a.N;
+      red.part[r] = a.Dpart;
+      red.out[r] = a.D16;
+      red.MN[r] = MN;
+      red.splits[r] = a.splits;
+      red.lg[r] = reduce_lanes(MN, a.splits);
+      const long long per_block = 256 >> red.lg[r];
+      red.first[r + 1] = red.first[r] + (unsigned)(((MN + 3) / 4 + per_block - 1) / per_block);
+      ++r;
+    }
+  }
+  int rc = launch_bwd_weight_set(sp.m[0], set, st);
+  if (rc != JZ_OK || r == 0) return rc;
+  for (int i = r; i < kWgradSet; ++i) red.first[i + 1] = red.first[i];
+  hipLaunchKernelGGL(splitk_reduce_set, dim3(red.first[kWgradSet]), dim3(256), 0, st, red);
+  return jz::launch_status();
+}
+
+}  // namespace
+
+extern "C" int jz_conv2d_bwd_weight_set_workspace_bytes(int n, const jz_conv_desc* descs, size_t* bytes) {
+  if (!descs || !bytes) return JZ_ERR_NULL;
+  if (n < 1 || n > JZ_SET_MAX) return JZ_ERR_SHAPE;
+  Plan set[JZ_SET_MAX];
+  int k = 0;
+  size_t need = 0;
+  for (int i = 0; i < n; ++i) {
+    const int rc = make_plan(JZ_BWD_WEIGHT, descs + i, &set[k]);
+    if (rc != JZ_OK) return rc;
+    if (joins_set(set[k])) ++k;
+    else need = std::max(need, set[k].ws_bytes);
+  }
+  if (k > 0) {
+    SetPlan sp;
+    choose_set(set, k, kPartialSumLimit, &sp);
+    need = std::max(need, sp.part_bytes);
+  }
+  *bytes = need;
+  return JZ_OK;
+}
+
+extern "C" int jz_conv2d_bwd_weight_set(int n, const jz_conv_desc* descs, const void* const* x16, const void* const* dy16, void* const* dw16,
+                                        void* ws, size_t ws_bytes, void* hip_stream) {
+  if (!descs || !x16 || !dy16 || !dw16) return JZ_ERR_NULL;
+  if (n < 1 || n > JZ_SET_MAX) return JZ_ERR_SHAPE;
+  if (ws && !aligned16(ws)) return JZ_ERR_ALIGN;
+  Plan set[JZ_SET_MAX], own;
+  const void *x[JZ_SET_MAX], *dy[JZ_SET_MAX];
+  void* dw[JZ_SET_MAX];
+  int alone[JZ_SET_MAX], k = 0, m = 0;
+  for (int i = 0; i < n; ++i) {
+    const int rc = make_plan(JZ_BWD_WEIGHT, descs + i, &own);
+    if (rc != JZ_OK) return rc;
+    if (!x16[i] || !dy16[i] || !dw16[i]) return JZ_ERR_NULL;
+    if (!aligned16(x16[i]) || !aligned16(dy16[i]) || !aligned16(dw16[i])) return JZ_ERR_ALIGN;
+    if (!joins_set(own)) {
+      alone[m++] = i;
+      continue;
+    }
+    set[k] = own;
+    x[k] = x16[i];
+    dy[k] = dy16[i];
+    dw[k++] = dw16[i];
+  }
+  SetPlan sp;
+  if (k > 0) choose_set(set, k, std::min(kPartialSumLimit, ws ? ws_bytes : 0), &sp);
+  // a result overlaps no operand and no other result of the launch, nothing overlaps the partial sums
+  for (int i = 0; i < k; ++i) {
+    for (int j = 0; j < k; ++j)
+      if (overlaps(dw[i], set[i].bytesD, dy[j], set[j].bytesA) || overlaps(dw[i], set[i].bytesD, x[j], set[j].bytesB) ||
+          (i < j && overlaps(dw[i], set[i].bytesD, dw[j], set[j].bytesD)))
+        return JZ_ERR_ALIAS;
+    if (sp.part_bytes > 0 && (overlaps(ws, sp.part_bytes, dy[i], set[i].bytesA) || overlaps(ws, sp.part_bytes, x[i], set[i].bytesB) ||
+                              overlaps(ws, sp.part_bytes, dw[i], set[i].bytesD)))
+      return JZ_ERR_ALIAS;
+  }
+  int rc = k > 0 ? run_set(sp, x, dy, dw, ws, static_cast<hipStream_t>(hip_stream)) : JZ_OK;
+  for (int i = 0; i < m && rc == JZ_OK; ++i)
+    rc = run(JZ_BWD_WEIGHT, descs + alone[i], dy16[alone[i]], x16[alone[i]], dw16[alone[i]], ws, ws_bytes, hip_stream);
+  return rc;
 }
 
 // ---- backward-weight without a caller workspace ---------------------------------------------------------------

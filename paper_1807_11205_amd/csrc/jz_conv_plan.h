@@ -1,6 +1,6 @@
 // What the planner hands to the kernel launchers of the implicit-GEMM family: the GEMM view of one convolution /
 // fully connected operation with the kernel variant chosen for it.  The launchers live in one translation unit per
-// operation (jz_conv_fwd.hip, jz_conv_fwd_stats.hip, jz_conv_bwd_data.hip, jz_conv_bwd_data_stats.hip, jz_conv_bwd_data_block_end.hip, jz_conv_bwd_weight.hip) so that they
+// operation (jz_conv_fwd.hip, jz_conv_fwd_stats.hip, jz_conv_bwd_data.hip, jz_conv_bwd_data_stats.hip, jz_conv_bwd_data_block_end.hip, jz_conv_bwd_weight.hip, jz_conv_bwd_weight_set.hip) so that they
 // compile in parallel; the planner and the entry points are in jz_conv.hip.
 #pragma once
 #include "jz_igemm.h"
@@ -63,5 +63,6 @@ int launch_bwd_data_stats(const Plan& pl, hipStream_t st);  // backward-data tha
 int launch_bwd_data_block_end(const Plan& pl, hipStream_t st);  // ... of the block-end gradient it forms from its tile
 int launch_bwd_data(const Plan& pl, hipStream_t st, const GemmSet* set = nullptr);  // set: these GEMMs instead of the plan's own
 int launch_bwd_weight(const Plan& pl, hipStream_t st);
+int launch_bwd_weight_set(const Plan& variant, const WgradSet& set, hipStream_t st);  // one of the variants choose_set offers
 
 }  // namespace jz

@@ -97,4 +97,12 @@ struct GemmSet {
   unsigned first[kGemmSet + 1];  // workgroup numbers of member k: first[k] .. first[k + 1] - 1
 };
 
+// Weight gradients of several layers in one launch (kernel arguments hold 4 KB).
+constexpr int kWgradSet = 11;
+struct WgradSet {
+  GemmArgs g[kWgradSet];
+  unsigned first[kWgradSet + 1];
+};
+static_assert(sizeof(WgradSet) <= 4096, "kernel arguments");
+
 }  // namespace jz

@@ -7,9 +7,9 @@ the residual adds, the global average pool and the classifier; softmax cross-ent
 LARS update with the device-resident dynamic loss scale.  The network is the stock ResNet-50 the paper trains
 (Table 3); gamma, beta and the bias are exempt from weight decay (Section 4.2) through the parameter flags.
 
-Every intermediate tensor has a buffer of its own and every launch is recorded in `self.trace` with the tensors it
-read and wrote, so that a test can check each launch against an independent implementation on the inputs that launch
-actually saw.
+Every intermediate tensor has a buffer of its own and every operation is recorded in `self.trace` with the tensors it
+read and wrote, so that a test can check each one against an independent implementation on the inputs that it
+actually saw.  The backward pass launches `self.bwd_schedule`: the same operations with short weight gradients in sets.
 """
 from typing import List
 
@@ -19,6 +19,7 @@ import torch
 from . import api, inputs, shapes
 
 BN_EPS = 1e-5
+SET_PIXELS, SET_FLOPS = 65536, 20e9     # weight gradients that are launched together, see ResNet50Chain._group_weight_gradients
 
 
 class Op:
@@ -91,13 +92,14 @@ class ResNet50Chain:
             self.bwd_ops.append(Op("lars_grad_sumsq", "rest", {}, [self.grad], [],
                                    lambda stream=None: api.jz_lars_grad_sumsq(self.ps, 0, self.ps.T, self.lars_ws, stream)))
             self.bwd_ops[-1].joins_side = True
+        self.bwd_schedule = self._group_weight_gradients(self.bwd_ops)
         self.ws = torch.zeros(self._ws_bytes, dtype=torch.uint8, device=dev)
         self.side_ws = []               # one workspace per side stream, made on first use
         self._side_calls = {}
         self._events = {}
         # the launches' arguments are checked and marshalled once, here: doing that on every call was most of the host time of
         # a step whose layers are short
-        for op in self.fwd_ops + self.bwd_ops:
+        for op in self.fwd_ops + self.bwd_ops + [o for o in self.bwd_schedule if o.kind == "bwd_weight_set"]:
             if op.bind is not None:
                 op.call = op.bind(self.ws)
         self.trace = self.fwd_ops + self.bwd_ops + [self._lars_op()]
@@ -208,6 +210,45 @@ class ResNet50Chain:
             else:
                 out.append(a)
                 i += 1
+        return out
+
+    def _group_weight_gradients(self, ops):
+        """The backward ops as a step launches them: runs of weight gradients, which nothing before the gradients' norms waits
+        for, become one call where the last of them stands (jz_conv2d_bwd_weight_set).  Only layers of at most SET_PIXELS
+        output pixels: the others fill the chip alone (batch 64: the 56 x 56 layers, 6.27 ms a step either way with a side
+        stream).  A set is closed at SET_FLOPS: with a side stream longer ones hold compute units that the chain of activation
+        gradients wants (batch 64: 6.27 ms at 20 GFLOP, 6.30 at 40, 6.34 at 120; on one stream, batch 55: 6.02, 5.97, 5.88)."""
+        out, group, flops = [], [], 0.0
+
+        def close():
+            if len(group) < 2:
+                out.extend(group)
+            else:
+                conv = lambda o: "desc" in o.params
+                descs = [o.params["desc"] if conv(o) else api.conv_desc(o.params["B"], 1, 1, o.params["I"], o.params["O"], 1, 1, 1, 0) for o in group]
+                x, dy = [o.ins[0 if conv(o) else 1] for o in group], [o.ins[1 if conv(o) else 0] for o in group]
+                dw = [o.outs[0] for o in group]
+                self._ws_bytes = max(self._ws_bytes, api.jz_conv2d_bwd_weight_set_workspace_bytes(descs))
+                op = Op("bwd_weight_set", " + ".join(o.name for o in group), dict(descs=descs), x + dy, dw,
+                        bind=lambda ws: api.bind_conv2d_bwd_weight_set(descs, x, dy, dw, ws))
+                # a projection branch's operands may come from the first side stream: such a set stays in order there
+                op.lane = "proj" if any(o.lane == "proj" for o in group) else group[0].lane
+                out.append(op)
+            group.clear()
+
+        for op in ops:
+            d = op.params.get("desc")
+            if op.kind in ("conv_bwd_weight", "fc_bwd_weight") and (d is None or (d.C % 8 == 0 and d.N * d.P * d.Q <= SET_PIXELS)):
+                flops = 0.0 if not group else flops
+                group.append(op)
+                flops += 2.0 * op.outs[0].numel() * (op.params["B"] if d is None else d.N * d.P * d.Q)
+                if len(group) == api.JZ_SET_MAX or flops >= SET_FLOPS:
+                    close()
+                continue
+            if op.kind == "lars_grad_sumsq":
+                close()
+            out.append(op)
+        close()
         return out
 
     # ---- the network -------------------------------------------------------------------------------------------------
@@ -417,7 +458,7 @@ class ResNet50Chain:
     def backward(self, stream=None, side=None):
         """With side streams the weight-gradient GEMMs (which nothing in the backward pass waits for) and the backward
         of the projection-shortcut branches run there, beside the chain of activation gradients."""
-        self._run(self.bwd_ops, stream, side, "bwd")
+        self._run(self.bwd_schedule, stream, side, "bwd")
 
     def update(self, stream=None):
         self.trace[-1].call(stream)
