@@ -19,8 +19,9 @@
 //                  which the next update's reduce pass then need not read w for.
 //
 // A set of at most LARS_SMALL_CHUNKS chunks is one launch of one workgroup (lars_small): three launches are 13 us of
-// latency whatever they do.  Up to LARS_MERGED_CHUNKS chunks there are two: every workgroup of the update adds up its tensor's
-// chunk sums itself (lars_update<LARS_MERGED>), which costs it less than the finalize launch costs the stream.
+// latency whatever they do.  Other small sets, and those with very large tensors, take two: a workgroup of the reduce pass takes
+// a group of chunks of one tensor (lars_reduce_groups), so few that every workgroup of the update adds up its tensor's group sums
+// itself while its chunk is on its way (lars_update<LARS_GROUPS>).
 //
 // When the kernels that produce the gradients also leave each tensor's sum of squares (jz_sumsq.h), the first two
 // launches have nothing left to do at update time and the update is one launch ("presummed"):
@@ -50,10 +51,14 @@ constexpr int LARS_WAVES = LARS_THREADS / 64;
 constexpr int LARS_FIN_BATCH = 10;       // chunk sums a thread of the finalize kernel requests together
 constexpr int LARS_SMALL_CHUNKS = 4;     // largest set lars_small takes: one chunk per group of threads (18 chunks: 37 us) ...
 constexpr int LARS_SMALL_T = 64;         // ... and this many tensors
-// Largest set whose update works out its rates itself: a chunk's sums for every thread.  Saves the finalize launch (3.0-4.6 us)
-// where a launch costs as much as the work: the three passes and the update of one 3x3 layer 32.7 -> 30.9 us, of a block 181 -> 176.
-constexpr int LARS_MERGED_CHUNKS = LARS_THREADS;
-enum { LARS_PLAIN = 0, LARS_PRE = 1, LARS_MERGED = 2 };  // where lars_update takes a tensor's rate from
+// Sets whose update works out its rates itself, which saves the finalize launch: at most LARS_MAX_GROUPS groups of chunks, two
+// for every thread, and either few chunks in all or more in one tensor than the finalize kernel takes in one round of 256 threads.
+// Updates in a row: 505 chunks 17.5 -> 15.3 us, 1075 chunks 25.3 -> 24.6, AlexNet's 15230 (9216 in one tensor, 11 us of the
+// finalize launch) 259 -> 253; between those fewer, longer workgroups cost the reduce pass what the launch costs (1954 chunks 36.9
+// and 37.4 us, ResNet-50's 6334 109.3 and 110.6).
+constexpr int LARS_MAX_GROUPS = 2 * LARS_THREADS;
+constexpr int64_t LARS_GROUPED_CHUNKS = 1536;
+enum { LARS_PLAIN = 0, LARS_PRE = 1, LARS_GROUPS = 2 };  // where lars_update takes a tensor's rate from
 constexpr uint64_t LARS_MAGIC = 0x4a5a4c4152533031ull;  // "JZLARS01"
 
 // Everything a workgroup needs to know about its chunk in one 16-byte record: a kernel's first loads then depend on
@@ -64,14 +69,21 @@ struct ChunkRec {
   int tensor;
 };
 
+// Chunks chunk0, chunk0 + stride, ... of a tensor: the groups of a tensor interleave, so that workgroups side by side read side by side.
+struct GroupRec {
+  int chunk0, chunks, tensor, stride;
+  int64_t start, end;  // of the first chunk, of the tensor
+};
+
 struct Layout {
   int64_t T = 0, P = 0, n_chunks = 0;
+  int64_t group_chunks = 1, n_groups = 0;  // chunks of a group at most; 0 groups: the update takes the rates from lars_finalize
   int64_t most_chunks = 0;  // of one tensor
-  size_t off_header = 0, off_offsets = 0, off_chunk_begin = 0, off_flags = 0, off_chunk_tensor = 0, off_chunk_rec = 0;
+  size_t off_header = 0, off_offsets = 0, off_chunk_begin = 0, off_flags = 0, off_chunk_tensor = 0, off_chunk_rec = 0, off_group_rec = 0;
   size_t off_state = 0;
   size_t static_bytes = 0;  // everything up to here is written by prepare
   size_t off_psum_w = 0, off_psum_g = 0, off_coef = 0, off_tflag = 0;
-  size_t off_gsum = 0, off_gflag = 0, off_wsum = 0, off_psum_w_before = 0, total = 0;  // presummed path: gradient sinks, their flags, sum of w^2
+  size_t off_gsum = 0, off_gflag = 0, off_wsum = 0, off_group_sum = 0, total = 0;  // presummed path: gradient sinks, their flags, sum of w^2
 };
 
 size_t up256(size_t x) { return (x + 255) & ~size_t(255); }
@@ -96,6 +108,16 @@ int make_layout(const jz_param_set* ps, Layout* L) {
   }
   if (L->T >= (int64_t(1) << 24) || chunks >= (int64_t(1) << 30)) return JZ_ERR_UNSUPPORTED;
   L->n_chunks = chunks;
+  for (L->group_chunks = 1;; L->group_chunks = L->group_chunks < 4 ? 2 * L->group_chunks : L->group_chunks + 4) {
+    int64_t groups = 0, most = 0;
+    for (int64_t t = 0; t < L->T; ++t) {
+      const int64_t nc = (ps->offsets[t + 1] - ps->offsets[t] + LARS_CH - 1) / LARS_CH;
+      groups += (nc + L->group_chunks - 1) / L->group_chunks;
+      if (nc > most) most = nc;
+    }
+    if (groups <= LARS_MAX_GROUPS && (chunks <= LARS_GROUPED_CHUNKS || most > 256 * LARS_FIN_BATCH)) L->n_groups = groups;
+    if (groups <= LARS_MAX_GROUPS || most <= L->group_chunks) break;
+  }
   size_t o = 0;
   L->off_header = o;        o = up256(o + 64);
   L->off_offsets = o;       o = up256(o + sizeof(int64_t) * (L->T + 1));
@@ -103,6 +125,7 @@ int make_layout(const jz_param_set* ps, Layout* L) {
   L->off_flags = o;         o = up256(o + sizeof(int) * (L->T ? L->T : 1));
   L->off_chunk_tensor = o;  o = up256(o + sizeof(int) * (chunks ? chunks : 1));
   L->off_chunk_rec = o;     o = up256(o + sizeof(ChunkRec) * (chunks ? chunks : 1));
+  L->off_group_rec = o;     o = up256(o + sizeof(GroupRec) * L->n_groups);
   L->off_state = o;         o = up256(o + 64);
   L->static_bytes = o;
   const size_t parts = (size_t)(chunks ? chunks : 1);
@@ -113,7 +136,7 @@ int make_layout(const jz_param_set* ps, Layout* L) {
   L->off_gsum = o;          o = up256(o + jz::kSumsqSinkBytes * (L->T ? L->T : 1));
   L->off_gflag = o;         o = up256(o + sizeof(int) * (L->T ? L->T : 1));
   L->off_wsum = o;          o = up256(o + sizeof(double) * (L->T ? L->T : 1));
-  L->off_psum_w_before = o; o = up256(o + (L->n_chunks <= LARS_MERGED_CHUNKS ? sizeof(double) * LARS_WAVES * L->n_chunks : 0));
+  L->off_group_sum = o;     o = up256(o + sizeof(double2) * L->n_groups);
   L->total = o;
   return JZ_OK;
 }
@@ -184,8 +207,9 @@ struct Tables {
   unsigned long long* gsum;  // [T][kSumsqSubs * kSumsqSubStride]: gradient sum-of-squares sinks
   int* gflag;                // [T]: non-finite gradient reported to the sink
   double* wsum;              // [T]: sum of squares of the master weights, written by lars_begin
-  double* psum_w_before;     // psum_w as the update found it (sets of at most LARS_MERGED_CHUNKS chunks)
-  int T, n_chunks;
+  const GroupRec* group_rec;
+  double2* group_sum;        // [n_groups] sums of w^2 and of g16^2
+  int T, n_chunks, n_groups;
   uint64_t checksum;
 };
 
@@ -340,32 +364,108 @@ __device__ __forceinline__ double chunk_thread_sumsq_g(const ChunkGrads& r) {
 }
 __device__ __forceinline__ bool sum_overflowed(double sg) { return !(sg <= 1.7e308); }  // Inf or NaN
 
-// MERGED: the update works out the rates itself (lars_update<LARS_MERGED>): it also finds the weights' sums where it does not
-// overwrite them, and the device-resident loss scale where it does not adjust it.
-template <bool MERGED>
-__global__ __launch_bounds__(LARS_THREADS) void lars_reduce(Tables tb, const float* __restrict__ w,
-                                                            const unsigned short* __restrict__ g16, const float* __restrict__ scale_dev) {
+__global__ __launch_bounds__(LARS_THREADS) void lars_reduce(Tables tb, const float* __restrict__ w, const unsigned short* __restrict__ g16) {
   __shared__ double red[LARS_WAVES];
   const int c = blockIdx.x;
   const ChunkRec rec = tb.chunk_rec[c];  // requested together with the header: garbage if the header is, but then unused
   const bool have_w = tb.state[0] != 0;  // written by the previous update, i.e. by an earlier launch
   if (!table_ok(tb)) return;
   const double sg = wave_sum(chunk_thread_sumsq_g(load_chunk_grads(rec, g16, threadIdx.x)));
-  double sw = have_w ? 0.0 : wave_sum(chunk_thread_sumsq_w(rec, w, threadIdx.x));
+  const double sw = have_w ? 0.0 : wave_sum(chunk_thread_sumsq_w(rec, w, threadIdx.x));
   if ((threadIdx.x & 63) == 0) {
     red[threadIdx.x >> 6] = sg;
-    double* const pw = tb.psum_w + (size_t)c * LARS_WAVES + (threadIdx.x >> 6);
-    if (!have_w) *pw = sw;
-    else if (MERGED) sw = *pw;
-    if (MERGED) tb.psum_w_before[(size_t)c * LARS_WAVES + (threadIdx.x >> 6)] = sw;
+    if (!have_w) tb.psum_w[(size_t)c * LARS_WAVES + (threadIdx.x >> 6)] = sw;
   }
-  if (MERGED && scale_dev && c == 0 && threadIdx.x == 0) {
+  lds_barrier();
+  if (threadIdx.x == 0) tb.psum_g[c] = ((red[0] + red[1]) + red[2]) + red[3];
+}
+
+// The sums of a group of chunks for an update that works out the rates itself: it also finds the device-resident loss scale where
+// it does not adjust it.
+template <int T>
+__global__ __launch_bounds__(T) void lars_reduce_groups(Tables tb, const float* __restrict__ w, const unsigned short* __restrict__ g16,
+                                                       const float* __restrict__ scale_dev) {
+  __shared__ double red[2][T / 64];
+  constexpr int U = 4, PIECES = LARS_CH / 8;     // 16-byte loads of a thread requested together; of a whole chunk
+  const GroupRec gr = tb.group_rec[blockIdx.x];  // requested together with the header: garbage if the header is, but then unused
+  const bool have_w = tb.state[0] != 0;          // written by the previous update, i.e. by an earlier launch
+  if (!table_ok(tb)) return;
+  const bool aligned = (gr.start & 7) == 0;
+  double sw = 0.0, sg = 0.0;
+  uint4 q[U];
+  auto fetch = [&](int i) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int p = i + u * T;
+      const int64_t at = gr.start + (int64_t)(p / PIECES * gr.stride) * LARS_CH + p % PIECES * 8;
+      q[u] = make_uint4(0, 0, 0, 0);
+      if (p < gr.chunks * PIECES && at + 8 <= gr.end) q[u] = *reinterpret_cast<const uint4*>(g16 + at);
+    }
+  };
+  if (aligned) fetch(threadIdx.x);
+  if (!have_w) {  // a fresh workspace: what the previous update would have left, chunk by chunk
+    for (int j = (int)(threadIdx.x / LARS_THREADS); j < gr.chunks; j += T / LARS_THREADS) {
+      const int c = gr.chunk0 + j * gr.stride;
+      const double p = wave_sum(chunk_thread_sumsq_w(tb.chunk_rec[c], w, threadIdx.x % LARS_THREADS));
+      if ((threadIdx.x & 63) == 0) tb.psum_w[(size_t)c * LARS_WAVES + (threadIdx.x % LARS_THREADS >> 6)] = p;
+    }
+    __threadfence_block();
+    __syncthreads();
+  }
+  for (int i = threadIdx.x; i < gr.chunks * LARS_WAVES; i += T) {
+    const double* const p = tb.psum_w + (size_t)(gr.chunk0 + i / LARS_WAVES * gr.stride) * LARS_WAVES + i % LARS_WAVES;
+    // a fresh one's sums may share a line with a neighbour's that this compute unit has pulled in before they were written
+    sw += have_w ? *p
+                 : __longlong_as_double((long long)__hip_atomic_load(reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED,
+                                                                     __HIP_MEMORY_SCOPE_AGENT));
+  }
+  if (aligned) {
+    const int64_t end = gr.end & ~int64_t(7);  // the elements behind it belong to the tensor's last chunk
+    if ((int)threadIdx.x < (int)(gr.end - end) && gr.end - gr.start <= ((int64_t)(gr.chunks - 1) * gr.stride + 1) * LARS_CH) {
+      const float g = half_bits_to_float(g16[end + threadIdx.x]);
+      sg = (double)(g * g);
+    }
+    for (int i = threadIdx.x; i < gr.chunks * PIECES; i += U * T) {
+      uint4 now[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) now[u] = q[u];
+      fetch(i + U * T);  // on its way while these squares are added
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const unsigned gw[4] = {now[u].x, now[u].y, now[u].z, now[u].w};
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const float g = half_bits_to_float((unsigned short)(gw[j >> 1] >> ((j & 1) * 16)));
+          sg += (double)(g * g);
+        }
+      }
+    }
+  } else {
+    for (int j = (int)(threadIdx.x / LARS_THREADS); j < gr.chunks; j += T / LARS_THREADS)
+      sg += chunk_thread_sumsq_g(load_chunk_grads(tb.chunk_rec[gr.chunk0 + j * gr.stride], g16, threadIdx.x % LARS_THREADS));
+  }
+  sw = wave_sum(sw);
+  sg = wave_sum(sg);
+  if ((threadIdx.x & 63) == 0) {
+    red[0][threadIdx.x >> 6] = sw;
+    red[1][threadIdx.x >> 6] = sg;
+  }
+  if (scale_dev && blockIdx.x == 0 && threadIdx.x == 0) {
     const float scale = *scale_dev;
     tb.state[1] = __float_as_int(1.0f / scale);
     tb.state[2] = __float_as_int(scale);
   }
   lds_barrier();
-  if (threadIdx.x == 0) tb.psum_g[c] = ((red[0] + red[1]) + red[2]) + red[3];
+  if (threadIdx.x == 0) {
+    sw = red[0][0];
+    sg = red[1][0];
+#pragma unroll
+    for (int i = 1; i < T / 64; ++i) {
+      sw += red[0][i];
+      sg += red[1][i];
+    }
+    tb.group_sum[blockIdx.x] = make_double2(sw, sg);
+  }
 }
 
 // gamma rho_t of Eq. 1 on the un-scaled gradient
@@ -527,36 +627,49 @@ __device__ __forceinline__ void lars_step(float& w, float& v, unsigned short gbi
   w16 = float_to_half_bits(wn);                 // cast back for the next forward pass
 }
 
-// One thread's share (tid of LARS_THREADS) of a chunk's update; returns its share of the sum of squares of the new weights.
+// One thread's share (tid of LARS_THREADS) of a chunk's state and gradients: every load is in flight before the first use.
+struct ChunkState {
+  float4 w0[LARS_IT], w1[LARS_IT], v0[LARS_IT], v1[LARS_IT];
+  uint4 gq[LARS_IT];
+};
 template <bool STREAM>
-__device__ __forceinline__ double update_chunk(const ChunkRec& rec, int tid, float* __restrict__ w, float* __restrict__ v,
+__device__ __forceinline__ ChunkState load_chunk_state(const ChunkRec& rec, int tid, const float* __restrict__ w, const float* __restrict__ v,
+                                                       const unsigned short* __restrict__ g16) {
+  ChunkState r;
+  int t;
+  int64_t s, e, b0, b1;
+  chunk_range(rec, &t, &s, &e);
+  chunk_body(s, e, &b0, &b1);
+#pragma unroll
+  for (int k = 0; k < LARS_IT; ++k) {
+    int64_t i = b0 + (int64_t)(k * LARS_THREADS + tid) * 8;
+    if (i < b1) {
+      r.gq[k] = *reinterpret_cast<const uint4*>(g16 + i);
+      r.w0[k] = load_state_f4<STREAM>(w + i);
+      r.w1[k] = load_state_f4<STREAM>(w + i + 4);
+      r.v0[k] = load_state_f4<STREAM>(v + i);
+      r.v1[k] = load_state_f4<STREAM>(v + i + 4);
+    }
+  }
+  return r;
+}
+
+// Its update; returns its share of the sum of squares of the new weights.
+__device__ __forceinline__ double update_chunk(const ChunkState& q, const ChunkRec& rec, int tid, float* __restrict__ w, float* __restrict__ v,
                                                const unsigned short* __restrict__ g16, unsigned short* __restrict__ w16, float coef,
                                                float lam, float m, float inv_s) {
   int t;
   int64_t s, e, b0, b1;
   chunk_range(rec, &t, &s, &e);
   chunk_body(s, e, &b0, &b1);
-  float4 w0[LARS_IT], w1[LARS_IT], v0[LARS_IT], v1[LARS_IT];
-  uint4 gq[LARS_IT];
-#pragma unroll
-  for (int k = 0; k < LARS_IT; ++k) {  // every load of the chunk is in flight before the first use
-    int64_t i = b0 + (int64_t)(k * LARS_THREADS + tid) * 8;
-    if (i < b1) {
-      gq[k] = *reinterpret_cast<const uint4*>(g16 + i);
-      w0[k] = load_state_f4<STREAM>(w + i);
-      w1[k] = load_state_f4<STREAM>(w + i + 4);
-      v0[k] = load_state_f4<STREAM>(v + i);
-      v1[k] = load_state_f4<STREAM>(v + i + 4);
-    }
-  }
   double sw = 0.0;  // sum of squares of the new weights, in the order lars_reduce would add them
 #pragma unroll
   for (int k = 0; k < LARS_IT; ++k) {
     int64_t i = b0 + (int64_t)(k * LARS_THREADS + tid) * 8;
     if (i < b1) {
-      float wv[8] = {w0[k].x, w0[k].y, w0[k].z, w0[k].w, w1[k].x, w1[k].y, w1[k].z, w1[k].w};
-      float vv[8] = {v0[k].x, v0[k].y, v0[k].z, v0[k].w, v1[k].x, v1[k].y, v1[k].z, v1[k].w};
-      unsigned gw[4] = {gq[k].x, gq[k].y, gq[k].z, gq[k].w};
+      float wv[8] = {q.w0[k].x, q.w0[k].y, q.w0[k].z, q.w0[k].w, q.w1[k].x, q.w1[k].y, q.w1[k].z, q.w1[k].w};
+      float vv[8] = {q.v0[k].x, q.v0[k].y, q.v0[k].z, q.v0[k].w, q.v1[k].x, q.v1[k].y, q.v1[k].z, q.v1[k].w};
+      unsigned gw[4] = {q.gq[k].x, q.gq[k].y, q.gq[k].z, q.gq[k].w};
       unsigned ow[4];
 #pragma unroll
       for (int j = 0; j < 8; j += 2) {
@@ -600,7 +713,7 @@ __global__ __launch_bounds__(LARS_THREADS) void lars_update(Tables tb, float* __
                                                             float inv_s, int* __restrict__ found_inf, DynScale dyn,
                                                             float lr, float eta, float loss_scale) {
   constexpr bool PRE = MODE == LARS_PRE;
-  if (dyn.st) {  // written by lars_finalize / lars_begin / lars_reduce (not used when there is no tensor)
+  if (dyn.st) {  // written by lars_finalize / lars_begin / lars_reduce_groups (not used when there is no tensor)
     inv_s = __int_as_float(tb.state[1]);
     if (MODE != LARS_PLAIN) loss_scale = __int_as_float(tb.state[2]);
   }
@@ -608,18 +721,22 @@ __global__ __launch_bounds__(LARS_THREADS) void lars_update(Tables tb, float* __
   // tables is used before the header has been checked
   const int cidx = (int)blockIdx.x < tb.n_chunks ? tb.n_chunks - 1 - (int)blockIdx.x : 0;
   const ChunkRec rec = tb.n_chunks > 0 ? tb.chunk_rec[cidx] : ChunkRec{0, 0, 0};
-  int f = 0;  // every wavefront looks at all tensor flags itself
+  int f = 0;  // every wavefront looks at all tensor flags (or group sums) itself
   double mw = 0.0, mg = 0.0;
-  __shared__ double red[LARS_WAVES];
-  if constexpr (MODE == LARS_MERGED) {  // a chunk per thread: is any gradient not finite, and what the chunk adds to its tensor's sums
-    const int i = threadIdx.x;
-    if (i < tb.n_chunks) {
-      const double g = tb.psum_g[i];
-      const int ti = tb.chunk_tensor[i];
-      f = sum_overflowed(g) ? 1 : 0;
-      if (ti == rec.tensor) { mg = g; mw = chunk_sumsq_w(tb.psum_w_before, i); }
+  __shared__ double red[2][LARS_WAVES];
+  __shared__ int red_f[LARS_WAVES];
+  double2 gs[LARS_MAX_GROUPS / LARS_THREADS];
+  int gt[LARS_MAX_GROUPS / LARS_THREADS];
+  if constexpr (MODE == LARS_GROUPS) {  // is any gradient not finite, and what do this tensor's groups add up to
+#pragma unroll
+    for (int k = 0; k < LARS_MAX_GROUPS / LARS_THREADS; ++k) {
+      const int i = k * LARS_THREADS + (int)threadIdx.x;
+      gt[k] = -1;
+      if (i < tb.n_groups) {
+        gs[k] = tb.group_sum[i];
+        gt[k] = tb.group_rec[i].tensor;
+      }
     }
-    f = __syncthreads_or(f);
   } else {
     for (int t = threadIdx.x & 63; t < tb.T; t += 64) f |= PRE ? tb.gflag[t] : tb.tflag[t];
   }
@@ -642,7 +759,33 @@ __global__ __launch_bounds__(LARS_THREADS) void lars_update(Tables tb, float* __
     if (blockIdx.x == 0 && threadIdx.x == 0) *found_inf = -1;
     return;
   }
-  f = __any(f);
+  ChunkState q;
+  if constexpr (MODE == LARS_GROUPS) {
+    q = load_chunk_state<STREAM>(rec, threadIdx.x, w, v, g16);  // on its way while the sums are added
+#pragma unroll
+    for (int k = 0; k < LARS_MAX_GROUPS / LARS_THREADS; ++k)
+      if (gt[k] >= 0) {
+        f |= sum_overflowed(gs[k].y) ? 1 : 0;
+        if (gt[k] == rec.tensor) {
+          mw += gs[k].x;
+          mg += gs[k].y;
+        }
+      }
+    mw = wave_sum(mw);
+    mg = wave_sum(mg);
+    f = __any(f);
+    if ((threadIdx.x & 63) == 0) {
+      red[0][threadIdx.x >> 6] = mw;
+      red[1][threadIdx.x >> 6] = mg;
+      red_f[threadIdx.x >> 6] = f;
+    }
+    lds_barrier();
+    mw = ((red[0][0] + red[0][1]) + red[0][2]) + red[0][3];
+    mg = ((red[1][0] + red[1][1]) + red[1][2]) + red[1][3];
+    f = red_f[0] | red_f[1] | red_f[2] | red_f[3];
+  } else {
+    f = __any(f);
+  }
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     *found_inf = f ? 1 : 0;
     // skipped or not, psum_w describes the master weights as this launch leaves them: lars_reduce / lars_begin filled it in
@@ -664,15 +807,14 @@ __global__ __launch_bounds__(LARS_THREADS) void lars_update(Tables tb, float* __
     }
     __syncthreads();  // every wavefront of the workgroup is here: the returns above depend on nothing wave-specific
     coef = lars_rate(tb.flags[t], sw_t, sg_shared, lr, eta, loss_scale);
-  } else if (MODE == LARS_MERGED) {
-    mw = block_sum<LARS_WAVES>(mw, red);
-    mg = block_sum<LARS_WAVES>(mg, red);
+  } else if (MODE == LARS_GROUPS) {
     coef = lars_rate(tb.flags[t], mw, mg, lr, eta, loss_scale);
   } else {
     coef = tb.coef[t];
   }
   const float lam = (tb.flags[t] & JZ_PARAM_WEIGHT_DECAY) ? wd : 0.0f;
-  const double sw = wave_sum(update_chunk<STREAM>(rec, threadIdx.x, w, v, g16, w16, coef, lam, m, inv_s));
+  if constexpr (MODE != LARS_GROUPS) q = load_chunk_state<STREAM>(rec, threadIdx.x, w, v, g16);
+  const double sw = wave_sum(update_chunk(q, rec, threadIdx.x, w, v, g16, w16, coef, lam, m, inv_s));
   if ((threadIdx.x & 63) == 0) tb.psum_w[(size_t)c * LARS_WAVES + (threadIdx.x >> 6)] = sw;
 }
 
@@ -732,7 +874,7 @@ __global__ __launch_bounds__(1024) void lars_small(Tables tb, float* __restrict_
   for (int c = group; c < tb.n_chunks; c += 1024 / LARS_THREADS) {
     const ChunkRec rec = tb.chunk_rec[c];
     const float lam = (tb.flags[rec.tensor] & JZ_PARAM_WEIGHT_DECAY) ? wd : 0.0f;
-    const double sw = wave_sum(update_chunk<false>(rec, tid, w, v, g16, w16, coef[rec.tensor], lam, m, inv_s));
+    const double sw = wave_sum(update_chunk(load_chunk_state<false>(rec, tid, w, v, g16), rec, tid, w, v, g16, w16, coef[rec.tensor], lam, m, inv_s));
     if ((tid & 63) == 0) tb.psum_w[(size_t)c * LARS_WAVES + (tid >> 6)] = sw;
   }
 }
@@ -761,7 +903,9 @@ Tables make_tables(const Layout& L, void* ws, uint64_t sum) {
   tb.gsum = reinterpret_cast<unsigned long long*>(b + L.off_gsum);
   tb.gflag = reinterpret_cast<int*>(b + L.off_gflag);
   tb.wsum = reinterpret_cast<double*>(b + L.off_wsum);
-  tb.psum_w_before = reinterpret_cast<double*>(b + L.off_psum_w_before);
+  tb.group_rec = reinterpret_cast<const GroupRec*>(b + L.off_group_rec);
+  tb.group_sum = reinterpret_cast<double2*>(b + L.off_group_sum);
+  tb.n_groups = (int)L.n_groups;
   tb.T = (int)L.T;
   tb.n_chunks = (int)L.n_chunks;
   tb.checksum = sum;
@@ -798,6 +942,7 @@ extern "C" int jz_lars_prepare(const jz_param_set* ps, void* ws, size_t ws_bytes
   int* fl = reinterpret_cast<int*>(host.data() + L.off_flags);
   int* ct = reinterpret_cast<int*>(host.data() + L.off_chunk_tensor);
   ChunkRec* cr = reinterpret_cast<ChunkRec*>(host.data() + L.off_chunk_rec);
+  GroupRec* gr = reinterpret_cast<GroupRec*>(host.data() + L.off_group_rec);
   int c = 0;
   off[0] = 0;
   cb[0] = 0;
@@ -813,6 +958,8 @@ extern "C" int jz_lars_prepare(const jz_param_set* ps, void* ws, size_t ws_bytes
       const int64_t en = st0 + LARS_CH < ps->offsets[t + 1] ? st0 + LARS_CH : ps->offsets[t + 1];
       cr[c + k] = ChunkRec{st0, (int)(en - st0), (int)t};
     }
+    const int ng = (int)((nc + L.group_chunks - 1) / L.group_chunks);
+    for (int k = 0; L.n_groups > 0 && k < ng; ++k) *gr++ = GroupRec{c + k, (nc - k + ng - 1) / ng, (int)t, ng, ps->offsets[t] + (int64_t)k * LARS_CH, ps->offsets[t + 1]};
     c += nc;
     cb[t + 1] = c;
   }
@@ -887,15 +1034,18 @@ int lars_run(const jz_param_set* ps, const jz_lars_hparams* hp, const jz_loss_sc
                        found_inf_dev, dyn, hp->lr, hp->trust_coef, state ? 1.0f : hp->loss_scale);
     return jz::launch_status();
   }
-  if (L.n_chunks > 0 && L.n_chunks <= LARS_MERGED_CHUNKS) {
-    hipLaunchKernelGGL(lars_reduce<true>, dim3((unsigned)L.n_chunks), dim3(LARS_THREADS), 0, st, tb, ps->master_w, g16, scale_dev);
-    hipLaunchKernelGGL((lars_update<LARS_MERGED, false>), dim3((unsigned)L.n_chunks), dim3(LARS_THREADS), 0, st, tb, ps->master_w,
-                       ps->momentum, g16, static_cast<unsigned short*>(ps->weight16), hp->momentum, hp->weight_decay,
-                       state ? 1.0f : 1.0f / hp->loss_scale, found_inf_dev, dyn, hp->lr, hp->trust_coef, state ? 1.0f : hp->loss_scale);
+  if (L.n_groups > 0) {
+    const dim3 groups((unsigned)L.n_groups);
+    if (L.group_chunks == 1) hipLaunchKernelGGL(lars_reduce_groups<LARS_THREADS>, groups, dim3(LARS_THREADS), 0, st, tb, ps->master_w, g16, scale_dev);
+    else hipLaunchKernelGGL(lars_reduce_groups<1024>, groups, dim3(1024), 0, st, tb, ps->master_w, g16, scale_dev);
+    if ((rc = jz::launch_status()) != JZ_OK) return rc;
+    hipLaunchKernelGGL((L.P > LARS_STREAM_ELEMENTS ? lars_update<LARS_GROUPS, true> : lars_update<LARS_GROUPS, false>), dim3((unsigned)L.n_chunks),
+                       dim3(LARS_THREADS), 0, st, tb, ps->master_w, ps->momentum, g16, static_cast<unsigned short*>(ps->weight16), hp->momentum,
+                       hp->weight_decay, state ? 1.0f : 1.0f / hp->loss_scale, found_inf_dev, dyn, hp->lr, hp->trust_coef,
+                       state ? 1.0f : hp->loss_scale);
     return jz::launch_status();
   }
-  if (L.n_chunks > 0)
-    hipLaunchKernelGGL(lars_reduce<false>, dim3((unsigned)L.n_chunks), dim3(LARS_THREADS), 0, st, tb, ps->master_w, g16, nullptr);
+  if (L.n_chunks > 0) hipLaunchKernelGGL(lars_reduce, dim3((unsigned)L.n_chunks), dim3(LARS_THREADS), 0, st, tb, ps->master_w, g16);
   if (L.T > 0 && L.most_chunks <= 256 * LARS_FIN_BATCH)
     hipLaunchKernelGGL(lars_finalize<256>, dim3((unsigned)L.T), dim3(256), 0, st, tb, hp->lr, hp->trust_coef,
                        state ? 1.0f : hp->loss_scale, scale_dev);
