@@ -2,11 +2,12 @@
 // gfx950: the single-precision side of the paper's FP32-versus-mixed-precision throughput comparison (Jia et al. 2018,
 // Section 5.4, Table 9).  Same operations, layouts and GEMM view as the FP16 path (jz_igemm.h):
 //
-//   D[m][n] = sum_k A(m,k) * B(n,k), every product and sum in FP32 on the FP32 matrix instructions.
+//   D[m][n] = sum_k A(m,k) * B(n,k), 24-bit operands, sums in FP32.
 //
-// Channel counts that are multiples of 4 run on the LDS-direct kernel of jz_f32_dma.h (strided multi-tap backward-data as one
-// unit-stride launch per residue of the stride, strided 1x1 backward-data with a scattering epilogue); other counts run on
-// it through copies with the channels rounded up to 4, where that adds at most half to the work (3-channel stems).
+// Channel counts that are multiples of 4 run on the kernels of jz_f32_split.h (products of bfloat16 parts with the accuracy of FP32)
+// and jz_f32_dma.h (FP32 matrix instructions), whichever choose_tiling_f32 expects to be faster (strided multi-tap backward-data as
+// one unit-stride launch per residue of the stride, strided 1x1 backward-data with a scattering epilogue); other counts run on them
+// through copies with the channels rounded up to 4, where that adds at most half to the work (3-channel stems).
 //
 // What is left (a filter smaller than its stride in backward-data; 1 or 2 channels; callers without room for the copies) runs on
 // igemm_f32_kernel below: a workgroup of 4 wavefronts (2 x 2) owns a BM x BN output tile, walks the reduction in
@@ -47,7 +48,7 @@ struct F32Args {
   int M, N, Kred;
   int nkt, kt_per_split, splits, tiles_m, tiles_n;
   ConvGeom g;
-  // the LDS-direct kernel's: descriptor bounds, tile decomposition, where tap (r, s) of the launch sits among the w_taps taps
+  // those kernels': descriptor bounds, tile decomposition, where tap (r, s) of the launch sits among the w_taps taps
   // of a filter (backward-data), and the scatter of strided backward-data as in GemmArgs
   unsigned bytesA, bytesB;
   int full_rows;  // rows of tiles whose reduction is not split (all of them: splits == 1)
@@ -60,6 +61,7 @@ struct F32Args {
 
 #include "jz_lds_dma.h"
 #include "jz_f32_dma.h"
+#include "jz_f32_split.h"
 
 // Address of the gathered tensor's element for pixel `pix` of the (n, OH, OW) grid at filter tap `tap`, channel c, or
 // nullptr when the tap falls outside the image (or, backward-data, when no output pixel reads the input pixel through it).
@@ -328,8 +330,9 @@ __global__ __launch_bounds__(256) void narrow_channels_f32(const float* __restri
 struct PlanF32 {
   int op = 0;
   bool vec = false;
-  bool dma = false;      // the LDS-direct kernel
+  bool dma = false;      // a kernel of jz_f32_split.h or jz_f32_dma.h
   bool gen = false;      // ... with per-lane tap arithmetic
+  bool parts = false;    // ... its operands taken apart for the bfloat16 matrix instructions (jz_f32_split.h)
   bool classes = false;  // strided multi-tap backward-data: one launch per residue of the stride (class_args_f32)
   bool widen = false;    // channels rounded up to 4 on copies: `wide` is the layer that runs
   int BM = 128, BN = 128;
@@ -364,60 +367,74 @@ bool needs_gen_f32(const PlanF32& pl) {
   return g.IC % FD_BK != 0 || g.R * g.S > 32 || (long long)pl.bytesA + margin >= 0xfffffff0ll;
 }
 
-// Tile and split of the LDS-direct kernel, by a cost model in microseconds.  A compute unit works through its share of the
-// workgroups, `resident` of them at a time; the vector ALU (which the FP32 matrix instructions share) bounds it at `thr` a k
-// tile, a workgroup whose waits nothing covers takes `lat`, and the operands have to come from memory once: the launch takes
-// the fourth-power norm of the three.  A split adds a second launch and re-reading the partial sums.
+// Form, tile and split of a launch, by a cost model in microseconds.  Forms: operands in three bfloat16 parts (jz_f32_split.h), or
+// the FP32 matrix instructions (jz_f32_dma.h), which are ahead in launches of a few microseconds and for reductions of one k tile
+// only.  A compute unit works through its share of the workgroups, `resident` of them at a time; its vector or matrix pipes bound it
+// at `thr` a k tile, a workgroup whose waits nothing covers takes `lat`, and the operands have to come from memory once: the launch
+// takes the fourth-power norm of the three.  A split adds a second launch and re-reading the partial sums.
 // Which part of the reduction is split: all of it, or only the rows of tiles that would start the last, unfilled round of
 // workgroups (full_rows rows of tiles are then computed whole).  Batch 64 makes 98 * 2^n tiles, 784 for most layers of
-// ResNet-50: four rounds of 256 instead of 3.06 (14 x 14, 256 -> 256, 3x3: 135 -> 118 us forward, 139 -> 124 backward-data).
+// ResNet-50: four rounds of 256 instead of 3.06 (14 x 14, 256 -> 256, 3x3 with FP32 instructions: 135 -> 118 us forward, 139 -> 124
+// backward-data).
 // The constants (forward, backward-data, backward-weight with plain and with gathered x) are least-squares fits to timings of
-// every tile and split on 660 operations: ResNet-50 of both kinds and AlexNet at batch sizes from 2 to 64, random layers.  On a
-// quarter of them left out of the fit the choices were 0.7-1.9 % slower than the best.  limit: bytes of partial sums.
-void choose_tiling_f32(PlanF32* pl, bool may_split, bool fixed_tile = false, size_t limit = 0) {
-  struct Tile { int bm, bn, resident; double lat[4], thr[4], prologue[4], own[4]; };
+// both forms, every tile and up to six splits of each on 3100 operations: ResNet-50 of both kinds and AlexNet at batch sizes from 2
+// to 128, random layers.  On a quarter of them left out of the fit the choices were 0.8-1.2 % slower than the best.  parts_ahead:
+// by how much the first form has to be faster to be taken, about what the model is wrong by on launches of 6-8 us, where it gains
+// nothing and its choices were up to 0.6 us slower without.  limit: bytes of partial sums.
+void choose_tiling_f32(PlanF32* pl, bool may_split, bool fixed_tile = false, size_t limit = 0, bool may_parts = true) {
+  struct Tile { bool parts; int bm, bn, resident; double lat[4], thr[4], prologue[4], own[4]; };
   static const Tile tiles[] = {
-      {128, 128, 2, {0.935, 1.023, 1.020, 1.181}, {0.889, 0.919, 0.907, 1.065}, {1.798, 1.665, 2.516, 2.486}, {2.607, 2.429, 2.484, 0.813}},
-      {128, 64, 3, {0.513, 0.615, 0.604, 0.685}, {0.461, 0.464, 0.488, 0.532}, {0.137, 0.147, 0.335, 0.128}, {1.206, 1.280, 0.974, 0.474}},
-      {64, 128, 3, {0.489, 0.579, 0.630, 0.800}, {0.456, 0.476, 0.494, 0.565}, {0.159, 0.239, 0.687, 0.228}, {1.199, 1.092, 0.988, 0.657}},
-      {64, 64, 5, {0.283, 0.342, 0.352, 0.421}, {0.235, 0.246, 0.255, 0.288}, {0.037, 0.039, 0.043, 0.030}, {0.512, 0.548, 0.429, 0.187}}};
-  static const double fixed[] = {4.76, 4.82, 5.10, 5.64}, reduce_launch[] = {3.38, 3.81, 3.59, 4.01}, reduce_byte[] = {0.187, 0.169, 0.160, 0.208},
-                      byte[] = {0.135, 0.127, 0.135, 0.230};  // per megabyte
+      {true, 128, 128, 2, {0.427, 0.537, 0.629, 0.756}, {0.572, 0.567, 0.533, 0.612}, {3.458, 2.504, 3.066, 2.014}, {0.883, 0.888, 2.248, 0.346}},
+      {true, 128, 64, 3, {0.324, 0.382, 0.463, 0.489}, {0.323, 0.327, 0.340, 0.359}, {1.365, 1.111, 1.112, 0.101}, {0.622, 0.637, 0.989, 0.079}},
+      {true, 64, 128, 3, {0.329, 0.395, 0.476, 0.560}, {0.328, 0.332, 0.349, 0.381}, {1.581, 1.099, 1.412, 1.033}, {0.456, 0.442, 1.133, 0.316}},
+      {true, 64, 64, 5, {0.254, 0.303, 0.309, 0.333}, {0.188, 0.191, 0.206, 0.215}, {0.000, 0.000, 0.000, 0.000}, {0.303, 0.312, 0.439, 0.000}},
+      {false, 128, 128, 2, {0.935, 1.023, 1.020, 1.181}, {0.889, 0.919, 0.907, 1.065}, {1.798, 1.665, 2.516, 2.486}, {2.607, 2.429, 2.484, 0.813}},
+      {false, 128, 64, 3, {0.513, 0.615, 0.604, 0.685}, {0.461, 0.464, 0.488, 0.532}, {0.137, 0.147, 0.335, 0.128}, {1.206, 1.280, 0.974, 0.474}},
+      {false, 64, 128, 3, {0.489, 0.579, 0.630, 0.800}, {0.456, 0.476, 0.494, 0.565}, {0.159, 0.239, 0.687, 0.228}, {1.199, 1.092, 0.988, 0.657}},
+      {false, 64, 64, 5, {0.283, 0.342, 0.352, 0.421}, {0.235, 0.246, 0.255, 0.288}, {0.037, 0.039, 0.043, 0.030}, {0.512, 0.548, 0.429, 0.187}}};
+  const double parts_ahead = 0.3;
+  // FP32 instructions, parts; the last two per megabyte
+  static const double fixed[2][4] = {{4.76, 4.82, 5.10, 5.64}, {4.347, 5.147, 4.159, 5.374}},
+                      reduce_launch[2][4] = {{3.38, 3.81, 3.59, 4.01}, {3.094, 3.142, 3.543, 4.043}},
+                      reduce_byte[2][4] = {{0.187, 0.169, 0.160, 0.208}, {0.244, 0.234, 0.218, 0.285}},
+                      byte[2][4] = {{0.135, 0.127, 0.135, 0.230}, {0.120, 0.088, 0.120, 0.185}};
   F32Args& a = pl->args;
   a.nkt = (a.Kred + FD_BK - 1) / FD_BK;
   const int c = pl->op == JZ_FWD ? 0 : pl->op == JZ_BWD_DATA ? 1 : a.bw_linear ? 2 : 3;
   const double in = 1e-6 * ((double)std::min<long long>(pl->bytesA, 4ll * a.M * a.Kred) + (double)std::min<long long>(pl->bytesB, 4ll * a.N * a.Kred));
+  auto even = [](bool parts, int k) { return parts ? k + (k & 1) : k; };  // operands in parts: two k tiles at a time
   auto p4 = [](double x) { return (x * x) * (x * x); };
   auto rounds = [](double w) { return w <= 4.0 ? ceil(w) : w + 0.5; };  // many small rounds even out
   double best = 1e30;
   int bsp = 1, bfull = 0;
   for (const Tile& t : tiles) {
-    if (fixed_tile && (t.bm != pl->BM || t.bn != pl->BN)) continue;
+    if (fixed_tile && (t.parts != pl->parts || t.bm != pl->BM || t.bn != pl->BN)) continue;
+    if (t.parts && (!may_parts || a.nkt == 1)) continue;  // half of its work would be done on zeros
     const long long tm = (a.M + t.bm - 1) / t.bm, tn = (a.N + t.bn - 1) / t.bn, slots = 256 * t.resident;
     for (int sp = 1; sp <= 512; sp = sp < 8 ? sp + 1 : sp + sp / 4) {
       if (sp > 1 && (!may_split || a.nkt / sp < 8)) break;
-      const int kps = (a.nkt + sp - 1) / sp, real = (a.nkt + kps - 1) / kps;
+      const int kps = even(t.parts, (a.nkt + sp - 1) / sp), real = (a.nkt + kps - 1) / kps;
       // full rows of tiles: none (all of them without a split), or as many as fill whole rounds
       const long long round_rows = tm * tn / 256 * 256 / tn;
       for (int tail = 0; tail < 2; ++tail) {
         if (tail && (sp == 1 || round_rows == 0 || round_rows >= tm)) break;
         const long long full = sp == 1 ? tm : tail ? round_rows : 0, wf = full * tn, ws = (tm - full) * tn * real;
         const double n1 = tail ? ceil(wf / 256.0) : rounds(wf / 256.0), n2 = tail ? ceil(ws / 256.0) : rounds(ws / 256.0);
-        const double t_thr = n1 * (t.own[c] + t.thr[c] * a.nkt) + n2 * (t.own[c] + t.thr[c] * kps);
+        const double t_thr = n1 * (t.own[c] + t.thr[c] * even(t.parts, a.nkt)) + n2 * (t.own[c] + t.thr[c] * kps);
         const long long l1 = (wf + slots - 1) / slots, l2 = wf > 0 ? (wf + ws + slots - 1) / slots - l1 : (ws + slots - 1) / slots;
-        const double t_lat = l1 * (t.prologue[c] + t.lat[c] * a.nkt) + l2 * (t.prologue[c] + t.lat[c] * kps);
+        const double t_lat = l1 * (t.prologue[c] + t.lat[c] * even(t.parts, a.nkt)) + l2 * (t.prologue[c] + t.lat[c] * kps);
         const double out = 4e-6 * a.M * a.N, part = sp > 1 ? 4e-6 * real * (double)(a.M - full * t.bm) * a.N : 0.0;
         if (1e6 * part > (double)limit) continue;
-        const double t_mem = byte[c] * (in + part + (full > 0 ? out : 0.0));
-        double time = fixed[c] + sqrt(sqrt(p4(t_thr) + p4(t_lat) + p4(t_mem)));
-        if (sp > 1) time += reduce_launch[c] + reduce_byte[c] * part;
-        if (time < best) { best = time; pl->BM = t.bm; pl->BN = t.bn; bsp = sp; bfull = (int)full; }
+        const double t_mem = byte[t.parts][c] * (in + part + (full > 0 ? out : 0.0));
+        double time = fixed[t.parts][c] + (t.parts ? parts_ahead : 0.0) + sqrt(sqrt(p4(t_thr) + p4(t_lat) + p4(t_mem)));
+        if (sp > 1) time += reduce_launch[t.parts][c] + reduce_byte[t.parts][c] * part;
+        if (time < best) { best = time; pl->parts = t.parts; pl->BM = t.bm; pl->BN = t.bn; bsp = sp; bfull = (int)full; }
       }
     }
   }
   a.tiles_m = (a.M + pl->BM - 1) / pl->BM;
   a.tiles_n = (a.N + pl->BN - 1) / pl->BN;
-  a.kt_per_split = (a.nkt + bsp - 1) / bsp;
+  a.kt_per_split = even(pl->parts, (a.nkt + bsp - 1) / bsp);
   a.splits = (a.nkt + a.kt_per_split - 1) / a.kt_per_split;
   a.full_rows = a.splits > 1 ? bfull : a.tiles_m;
   const int tail_tiles = (a.tiles_m - a.full_rows) * a.tiles_n;
@@ -449,7 +466,7 @@ bool class_args_f32(const jz_conv_desc* d, const PlanF32& base, int ca, int cb, 
   return true;
 }
 
-int compute_plan_f32(int op, const jz_conv_desc* d, PlanF32* pl, size_t limit);
+int compute_plan_f32(int op, const jz_conv_desc* d, PlanF32* pl, size_t limit, bool may_parts = true);
 
 // Channels rounded up to 4 on copies, when that adds at most half to the multiply-adds.
 void plan_widened_f32(int op, const jz_conv_desc* d, PlanF32* pl) {
@@ -473,7 +490,7 @@ void plan_widened_f32(int op, const jz_conv_desc* d, PlanF32* pl) {
 
 int out_dim(int in, int pad, int f, int st) { return (in + 2 * pad - f) / st + 1; }
 
-int compute_plan_f32(int op, const jz_conv_desc* d, PlanF32* pl, size_t limit) {
+int compute_plan_f32(int op, const jz_conv_desc* d, PlanF32* pl, size_t limit, bool may_parts) {
   if (!d) return JZ_ERR_NULL;
   if (op != JZ_FWD && op != JZ_BWD_DATA && op != JZ_BWD_WEIGHT) return JZ_ERR_UNSUPPORTED;
   if (d->N <= 0 || d->H <= 0 || d->W <= 0 || d->C <= 0 || d->K <= 0 || d->R <= 0 || d->S <= 0 || d->stride_h <= 0 ||
@@ -534,11 +551,11 @@ int compute_plan_f32(int op, const jz_conv_desc* d, PlanF32* pl, size_t limit) {
     if (pl->classes) {  // every input pixel meets one residue's taps only
       const int all = a.Kred;
       a.Kred = all / (d->stride_h * d->stride_w) + 1;
-      choose_tiling_f32(pl, false);
+      choose_tiling_f32(pl, false, false, 0, may_parts);
       a.Kred = all;
       a.splits = 1;
     } else {
-      choose_tiling_f32(pl, !a.sc_on, false, limit);
+      choose_tiling_f32(pl, !a.sc_on, false, limit, may_parts);
     }
     pl->ws_bytes = a.splits > 1 ? (size_t)a.splits * (a.M - a.full_rows * pl->BM) * a.N * sizeof(float) : 0;
     pl->plain_ws_bytes = pl->ws_bytes;
@@ -565,9 +582,20 @@ int compute_plan_f32(int op, const jz_conv_desc* d, PlanF32* pl, size_t limit) {
   return JZ_OK;
 }
 
-int make_plan_f32(int op, const jz_conv_desc* d, PlanF32* pl, size_t limit = kPartialSumLimit) {
+int make_plan_f32(int op, const jz_conv_desc* d, PlanF32* pl, size_t limit = kPartialSumLimit, bool may_parts = true) {
   if (!d) return JZ_ERR_NULL;
-  return cached_plan(1, PlanKey{op, -1, -1, limit, *d}, pl, [&](PlanF32* p) { return compute_plan_f32(op, d, p, limit); });
+  constexpr int kNoParts = 16;
+  return cached_plan(1, PlanKey{may_parts ? op : op + kNoParts, -1, -1, limit, *d}, pl,
+                     [&](PlanF32* p) { return compute_plan_f32(op, d, p, limit, may_parts); });
+}
+// Whether a layer runs in less room than its plan asks for (runs_with_fewer_splits): as the plan of the FP32 instructions has it,
+// so that which calls are taken does not depend on which form is faster.
+bool runs_in_f32(int op, const jz_conv_desc* d, size_t room) {
+  PlanF32 pl;
+  if (make_plan_f32(op, d, &pl, kPartialSumLimit, false) != JZ_OK) return false;
+  if (room >= pl.plain_ws_bytes) return true;
+  return make_plan_f32(op, d, &pl, room, false) == JZ_OK && room >= pl.plain_ws_bytes &&
+         runs_with_fewer_splits(op, pl.args.M, pl.args.N, pl.args.splits);
 }
 // residues of larger strides are planned anew by every call: they would fill the table
 constexpr int kKeptResidues = 16;
@@ -576,22 +604,40 @@ bool make_class_plan_f32(const jz_conv_desc* d, const PlanF32& base, int ca, int
   return cached_plan(1, PlanKey{JZ_BWD_DATA, ca, cb, 0, *d}, pl, [&](PlanF32* p) { return class_args_f32(d, base, ca, cb, p) ? 1 : 0; }) != 0;
 }
 
-template <int OP, int BM, int BN, bool GEN>
-int launch_f32_dma(const F32Args& a, hipStream_t st) {
-  constexpr size_t smem = (size_t)FD_NST * (BM + BN) * FD_BK * 4;
+template <int BM, int BN, bool PARTS>
+constexpr size_t lds_bytes_f32 = PARTS ? F32Split<BM, BN>::LDS_BYTES : (size_t)FD_NST * (BM + BN) * FD_BK * 4;
+
+template <int OP, int BM, int BN, bool GEN, bool PARTS>
+int launch_f32_tile(const F32Args& a, hipStream_t st) {
+  constexpr size_t smem = lds_bytes_f32<BM, BN, PARTS>;
   static std::atomic<bool> lds_set{false};
-  if (!allow_lds(reinterpret_cast<const void*>(&f32_dma_kernel<OP, BM, BN, GEN>), smem, lds_set)) return JZ_ERR_LAUNCH;
-  hipLaunchKernelGGL((f32_dma_kernel<OP, BM, BN, GEN>), dim3((unsigned)(a.full_rows + (a.tiles_m - a.full_rows) * a.splits) * (unsigned)a.tiles_n), dim3(256), smem, st, a);
+  if (!allow_lds(reinterpret_cast<const void*>(&f32_kernel<OP, BM, BN, GEN, PARTS>), smem, lds_set)) return JZ_ERR_LAUNCH;
+  hipLaunchKernelGGL((f32_kernel<OP, BM, BN, GEN, PARTS>), dim3((unsigned)(a.full_rows + (a.tiles_m - a.full_rows) * a.splits) * (unsigned)a.tiles_n),
+                     dim3(256), smem, st, a);
+  return jz::launch_status();
+}
+template <int BM, int BN, bool GEN, bool PARTS>
+int launch_f32_set_tile(const F32Set& set, hipStream_t st) {
+  constexpr size_t smem = lds_bytes_f32<BM, BN, PARTS>;
+  static std::atomic<bool> lds_set{false};
+  if (!allow_lds(reinterpret_cast<const void*>(&f32_set_kernel<BM, BN, GEN, PARTS>), smem, lds_set)) return JZ_ERR_LAUNCH;
+  hipLaunchKernelGGL((f32_set_kernel<BM, BN, GEN, PARTS>), dim3(set.first[FD_MAX_SET]), dim3(256), smem, st, set);
   return jz::launch_status();
 }
 
-template <int BM, int BN, bool GEN>
-int launch_f32_set(const F32Set& set, hipStream_t st) {
-  constexpr size_t smem = (size_t)FD_NST * (BM + BN) * FD_BK * 4;
-  static std::atomic<bool> lds_set{false};
-  if (!allow_lds(reinterpret_cast<const void*>(&f32_dma_set_kernel<BM, BN, GEN>), smem, lds_set)) return JZ_ERR_LAUNCH;
-  hipLaunchKernelGGL((f32_dma_set_kernel<BM, BN, GEN>), dim3(set.first[FD_MAX_SET]), dim3(256), smem, st, set);
-  return jz::launch_status();
+template <int OP, bool GEN, bool PARTS>
+int launch_f32_form(const PlanF32& pl, hipStream_t st) {
+  if (pl.BM == 128 && pl.BN == 128) return launch_f32_tile<OP, 128, 128, GEN, PARTS>(pl.args, st);
+  if (pl.BM == 128) return launch_f32_tile<OP, 128, 64, GEN, PARTS>(pl.args, st);
+  if (pl.BN == 128) return launch_f32_tile<OP, 64, 128, GEN, PARTS>(pl.args, st);
+  return launch_f32_tile<OP, 64, 64, GEN, PARTS>(pl.args, st);
+}
+template <bool GEN, bool PARTS>
+int launch_f32_set(const PlanF32& pl, const F32Set& set, hipStream_t st) {
+  if (pl.BM == 128 && pl.BN == 128) return launch_f32_set_tile<128, 128, GEN, PARTS>(set, st);
+  if (pl.BM == 128) return launch_f32_set_tile<128, 64, GEN, PARTS>(set, st);
+  if (pl.BN == 128) return launch_f32_set_tile<64, 128, GEN, PARTS>(set, st);
+  return launch_f32_set_tile<64, 64, GEN, PARTS>(set, st);
 }
 
 template <int OP>
@@ -599,16 +645,8 @@ int launch_f32(const PlanF32& pl, hipStream_t st) {
   const F32Args& a = pl.args;
   if (pl.dma) {
     if constexpr (OP != OP_BWD_WEIGHT)
-      if (pl.gen) {
-        if (pl.BM == 128 && pl.BN == 128) return launch_f32_dma<OP, 128, 128, true>(a, st);
-        if (pl.BM == 128) return launch_f32_dma<OP, 128, 64, true>(a, st);
-        if (pl.BN == 128) return launch_f32_dma<OP, 64, 128, true>(a, st);
-        return launch_f32_dma<OP, 64, 64, true>(a, st);
-      }
-    if (pl.BM == 128 && pl.BN == 128) return launch_f32_dma<OP, 128, 128, false>(a, st);
-    if (pl.BM == 128) return launch_f32_dma<OP, 128, 64, false>(a, st);
-    if (pl.BN == 128) return launch_f32_dma<OP, 64, 128, false>(a, st);
-    return launch_f32_dma<OP, 64, 64, false>(a, st);
+      if (pl.gen) return pl.parts ? launch_f32_form<OP, true, true>(pl, st) : launch_f32_form<OP, true, false>(pl, st);
+    return pl.parts ? launch_f32_form<OP, false, true>(pl, st) : launch_f32_form<OP, false, false>(pl, st);
   }
   const dim3 grid((unsigned)a.tiles_m * (unsigned)a.tiles_n * (unsigned)a.splits), block(F_THREADS);
   if constexpr (OP == OP_BWD_DATA)
@@ -643,7 +681,7 @@ int run_f32(int op, const jz_conv_desc* d, const void* A, const void* B, void* D
       pl.widen = false;
       pl.ws_bytes = pl.plain_ws_bytes;
     }
-    if (room < pl.ws_bytes || !runs_with_fewer_splits(op, pl.args.M, pl.args.N, pl.args.splits)) return JZ_ERR_WORKSPACE;
+    if (room < pl.ws_bytes || !runs_in_f32(op, d, room)) return JZ_ERR_WORKSPACE;
   }
   if (pl.ws_bytes > 0 && (overlaps(ws, pl.ws_bytes, A, pl.bytesA) || overlaps(ws, pl.ws_bytes, B, pl.bytesB) ||
                           overlaps(ws, pl.ws_bytes, D, pl.bytesD)))
@@ -666,11 +704,8 @@ int run_f32(int op, const jz_conv_desc* d, const void* A, const void* B, void* D
         set.first[j + 1] = set.first[j];
       }
       k = 0;
-      const int v = (pl.gen ? 4 : 0) + (pl.BM == 128 ? 2 : 0) + (pl.BN == 128 ? 1 : 0);
-      return v == 0 ? launch_f32_set<64, 64, false>(set, st) : v == 1 ? launch_f32_set<64, 128, false>(set, st)
-           : v == 2 ? launch_f32_set<128, 64, false>(set, st) : v == 3 ? launch_f32_set<128, 128, false>(set, st)
-           : v == 4 ? launch_f32_set<64, 64, true>(set, st) : v == 5 ? launch_f32_set<64, 128, true>(set, st)
-           : v == 6 ? launch_f32_set<128, 64, true>(set, st) : launch_f32_set<128, 128, true>(set, st);
+      if (pl.gen) return pl.parts ? launch_f32_set<true, true>(pl, set, st) : launch_f32_set<true, false>(pl, set, st);
+      return pl.parts ? launch_f32_set<false, true>(pl, set, st) : launch_f32_set<false, false>(pl, set, st);
     };
     const int Rm = (d->R + d->stride_h - 1) / d->stride_h, Sm = (d->S + d->stride_w - 1) / d->stride_w;
     const bool rows_first = (Rm - 1) * Sm >= Rm * (Sm - 1);

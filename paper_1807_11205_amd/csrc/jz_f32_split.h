@@ -1,0 +1,272 @@
+// FP32 implicit GEMM on the bfloat16 matrix instructions (included by jz_conv_f32.hip behind jz_f32_dma.h, whose F32Tile says what
+// a workgroup loads and stores).
+//
+// An FP32 value is the sum of three bfloat16 values of eight significant bits each: p0 = a rounded to bfloat16, p1 = a - p0
+// rounded, p2 = a - p0 - p1 (both differences and the last part are exact, the parts cover the 24 bits).  Of the nine products of
+// two such sums the six of order 2^0 .. 2^-16 are added up, each exact in the FP32 accumulators; what is left out is at most
+// 2^-25 of a product, half of what rounding the product to FP32 would lose, and of either sign.  The five smaller products have
+// accumulators of their own: their sums are 2^-8 of the result, so their roundings do not count, and the large sums are rounded
+// once in 16 k steps where the FP32 instructions round once in 4.  Errors against 64 bits are a third to two thirds of those of
+// the FP32 instructions over the layers of ResNet-50 (one common set of accumulators would make them up to twice as large).
+//
+// Infinities, NaN and values that round to an infinite p0 end in a result that is not finite: a workgroup that finds one in its
+// tile computes the tile again with the FP32 instructions (f32_dma_body).  Operands below 2^-109 lose their last bits, an
+// absolute error below 2^-133.
+//
+// Why: the FP32 matrix instructions reach 154 TFLOP/s and leave no issue slots beside them, the bfloat16 ones 1.9 PFLOP/s, 317 for
+// six products.  Measured, FP32 instructions and parts: 3x3, 512 channels, 28x28, N = 64 1650 -> 1206 us (144 -> 197 TFLOP/s);
+// 256 channels, 14x14 135 -> 101 us; 64 channels, 56x56 132 -> 96; 1x1 512 -> 128 on 28x28 68 -> 45; ResNet-50's operations at N = 64
+// 13.94 -> 11.36 ms.
+// What bounds it: issue slots, then power.  A 32x32x16 product holds the matrix pipe for 32 cycles, eight issue slots of its SIMD;
+// a loop of products with four vector instructions behind each runs at 95 % of the pipe, with four times as many behind every
+// fourth at 68 %.  Taking the parts apart is 5.5 vector instructions a value.  A wavefront that did that for its own 64 + 64
+// operand rows needed 7.3 of them per product (14x14 layer 129 us; v_dot2_f32_bf16 for the differences: 146).  So values are taken
+// apart once per workgroup, on their way through registers into LDS, two instructions at a time between the products, and the
+// operands are read from LDS as bfloat16: 4 instructions per product for 128x128 tiles.  The pipes are then busy for 65 % of the
+// cycles, without bank conflicts, at a clock that power holds at 1.5-1.7 GHz.
+//
+// A tile's loads are requested two tiles ahead; the parts of tile i + 1 are made and written to the other of two stages between
+// the products of tile i; one barrier a tile, behind five of the six groups of products; the sixth covers the first operand reads of the
+// next tile.  LDS layouts of a part ("KC", "MC" as in jz_f32_dma.h): KC rows of 16 bfloat16, 16-byte half c of row r at place
+// c ^ ((r >> 3) & 1); MC [16 k][rows], chunk c of eight at place c ^ 4 (k & 3) (64 rows: c ^ 2 (k & 3)), read with the transposing
+// ds_read_b64_tr_b16.
+#pragma once
+
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+
+template <int BM, int BN>
+struct F32Split {
+  static constexpr int STAGE = 3 * (BM + BN) * FD_BK * 2;
+  static constexpr int RING = FD_NST * (BM + BN) * FD_BK * 4;  // of f32_dma_body, in the same LDS
+  static constexpr int LDS_BYTES = 2 * STAGE > RING ? 2 * STAGE : RING;
+};
+
+template <int OP, int BM, int BN, bool GEN>
+__device__ __forceinline__ void f32_split_body(const F32Args& a, unsigned block, unsigned blocks) {
+  using Tile = F32Tile<OP, BM, BN, GEN, false>;
+  using Lds = F32Split<BM, BN>;
+  constexpr bool A_KC = Tile::A_KC, B_KC = Tile::B_KC;
+  constexpr int TM = BM / 64, TN = BN / 64, TT = TM * TN;  // 32x32 MFMA tiles per wavefront
+  constexpr int LA = Tile::LA, LPT = Tile::LPT;
+  constexpr int A_PART = BM * FD_BK * 2, B_PART = BN * FD_BK * 2, B0 = 3 * A_PART, STAGE = Lds::STAGE;
+  extern __shared__ __align__(16) float lds_f[];
+  lds_byte* const ldsb = (lds_byte*)lds_f;
+  Tile t(a, block, blocks);
+  const int nk = t.nk, lane = t.lane, wave = t.wave, wm = t.wm, wn = t.wn;
+
+  f32x4 raw[2][LPT];  // tiles on their way in
+  // A tile that does not exist is requested too, out of range (zeros, nothing is fetched): a request under a condition would make
+  // the compiler wait for all of them where one is used.
+  struct Next {
+    typename Tile::TileCtx c;
+    unsigned none;
+  };
+  auto next = [&](int i) { return Next{t.tile_ctx(t.kt_begin + i), i < nk ? 0u : Tile::OOB}; };
+  auto request = [&](const Next& n, auto set_tag, auto l_tag) {
+    constexpr int SET = decltype(set_tag)::value, Lx = decltype(l_tag)::value;
+    t.template load<Lx>(n.c, [&](__amdgpu_buffer_rsrc_t rsrc, unsigned voff, unsigned soff) {
+      raw[SET][Lx] = __builtin_bit_cast(f32x4, (u32x4)__builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)(voff | n.none), (int)soff, 0));
+    });
+  };
+  static_for<0, 2>([&](auto s_tag) {
+    const Next n = next(decltype(s_tag)::value);
+    static_for<0, LPT>([&](auto l_tag) { request(n, s_tag, l_tag); });
+  });
+  sched_fence();
+
+  // ---- where a load's four values go in a part, where the operands are read ---------------------------
+  // KC: four k of row 64 ii + kc_row.  MC: four rows of k-row mc_k.
+  unsigned wr[LPT];
+#pragma unroll
+  for (int l = 0; l < LPT; ++l) {
+    const bool isA = l < LA;
+    const int ii = isA ? l : l - LA, rows = isA ? BM : BN;
+    if (isA ? A_KC : B_KC) {
+      const int row = 64 * ii + t.kc_row, q = lane & 3;
+      wr[l] = (unsigned)(row * 32 + (((q >> 1) ^ ((row >> 3) & 1)) * 16) + (q & 1) * 8);
+    } else {
+      const int k = t.mc_k(rows, ii), q = lane % (rows / 4);
+      wr[l] = (unsigned)(k * rows * 2 + (((q >> 1) ^ ((rows >= 128 ? 4 : 2) * (k & 3))) * 16) + (q & 1) * 8);
+    }
+    if (!isA) wr[l] += (unsigned)B0;
+  }
+  const int r31 = lane & 31, h = lane >> 5;
+  // KC: row r31, k 8 h .. 8 h + 7.  MC: 16-lane group gi = lane / 16 reads half gi % 2 of the 32 rows and k block gi / 2; lane
+  // 4 j + c4 of the group addresses k-row j, the 8-byte piece c4 of those 16 rows.
+  unsigned rdA[A_KC ? 1 : 2 * TM], rdB[B_KC ? 1 : 2 * TN];
+  auto read_addr = [&](unsigned* rd, bool kc, int row0, int rows, int tiles, int base) {
+    if (kc) {
+      rd[0] = (unsigned)(base + (row0 + r31) * 32 + ((h ^ ((r31 >> 3) & 1)) * 16));
+    } else {
+      const int gi = lane >> 4, j = (lane >> 2) & 3, c4 = lane & 3;
+#pragma unroll
+      for (int x = 0; x < tiles; ++x)
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf) {
+          const int k = 8 * (gi >> 1) + 4 * hf + j, c = (row0 + 32 * x + 16 * (gi & 1) + 4 * c4) / 8;
+          rd[2 * x + hf] = (unsigned)(base + k * rows * 2 + ((c ^ ((rows >= 128 ? 4 : 2) * (k & 3))) * 16) + (c4 & 1) * 8);
+        }
+    }
+  };
+  read_addr(rdA, A_KC, wm * (BM / 2), BM, TM, 0);
+  read_addr(rdB, B_KC, wn * (BN / 2), BN, TN, B0);
+
+  bf16x8 fa[3][TM], fb[3][TN];
+  auto read_operand = [&](bool kc, const unsigned* rd, int x, int off) {
+    if (kc) return *(const __attribute__((address_space(3))) bf16x8*)(ldsb + rd[0] + (off + x * 1024));
+    typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+    struct { s16x4 lo, hi; } v;
+    v.lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(ldsb + rd[2 * x] + off));
+    v.hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(ldsb + rd[2 * x + 1] + off));
+    return __builtin_bit_cast(bf16x8, v);
+  };
+  auto read_part = [&](int st, int k) {
+#pragma unroll
+    for (int x = 0; x < TM; ++x) fa[k][x] = read_operand(A_KC, rdA, x, st * STAGE + k * A_PART);
+#pragma unroll
+    for (int y = 0; y < TN; ++y) fb[k][y] = read_operand(B_KC, rdB, y, st * STAGE + k * B_PART);
+  };
+
+  // Taking load l of register set SET apart, in kSteps steps of two vector instructions (the products hide four behind each of
+  // them): the next eight bits of its values go to LDS as part k and, where another part follows, are taken off value by value
+  // (exact).
+  constexpr int kSteps = 11;
+  u32x2 part[LPT];
+  auto split_step = [&](auto set_tag, auto l_tag, auto step_tag, int st) {
+    constexpr int SET = decltype(set_tag)::value, Lx = decltype(l_tag)::value, K = decltype(step_tag)::value / 5, E = decltype(step_tag)::value % 5 - 1;
+    f32x4& v = raw[SET][Lx];
+    if constexpr (E < 0) {
+      part[Lx] = u32x2{__builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{v[0], v[1]}, bf16x2)),
+                       __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{v[2], v[3]}, bf16x2))};
+      *(__attribute__((address_space(3))) u32x2*)(ldsb + wr[Lx] + (st * STAGE + K * (Lx < LA ? A_PART : B_PART))) = part[Lx];
+    } else {
+      v[E] -= __builtin_bit_cast(float, E % 2 == 0 ? part[Lx][E / 2] << 16 : part[Lx][E / 2] & 0xffff0000u);
+    }
+  };
+
+  f32x16 acc[TM][TN], low[TM][TN];
+#pragma unroll
+  for (int x = 0; x < TM; ++x)
+#pragma unroll
+    for (int y = 0; y < TN; ++y)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[x][y][r] = low[x][y][r] = 0.0f;
+
+  auto barrier = [&] {  // this wavefront's LDS writes have landed, and everyone else's; loads stay in flight
+    lds_wait<0>();
+    __builtin_amdgcn_s_barrier();
+  };
+  // Tile i out of stage PAR = i & 1.
+  auto tile = [&](int i, auto par_tag) {
+    constexpr int PAR = decltype(par_tag)::value, NEXT = 1 - PAR;
+    constexpr int kA[6] = {0, 0, 1, 0, 2, 1}, kB[6] = {0, 1, 0, 2, 0, 1};
+    const Next n = next(i + 3);
+    read_part(PAR, 1);
+    read_part(PAR, 2);
+    sched_fence();
+    static_for<0, 6 * TT>([&](auto s_tag) {
+      constexpr int S = decltype(s_tag)::value, P = S / TT, X = S % TT / TN, Y = S % TN;
+      if constexpr (S == 5 * TT) {
+        barrier();
+        read_part(NEXT, 0);
+        sched_fence();
+      }
+      f32x16& d = P == 0 ? acc[X][Y] : low[X][Y];
+      // n operand in the first slot: each lane then owns 4 consecutive n for one m (row = lane % 32)
+      d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[kB[P]][Y], fa[kA[P]][X], d, 0, 0, 0);
+      if constexpr (S < 5 * TT) {
+        static_for<0, kSteps * LPT>([&](auto u_tag) {
+          constexpr int U = decltype(u_tag)::value, Lx = U / kSteps, K = U % kSteps;
+          if constexpr (U * 5 * TT / (kSteps * LPT) == S) {
+            split_step(std::integral_constant<int, NEXT>{}, std::integral_constant<int, Lx>{}, std::integral_constant<int, K>{}, NEXT);
+            if constexpr (K + 1 == kSteps) request(n, std::integral_constant<int, NEXT>{}, std::integral_constant<int, Lx>{});
+          }
+        });
+      }
+      sched_fence();
+    });
+  };
+  constexpr std::integral_constant<int, 0> EVEN{};
+  constexpr std::integral_constant<int, 1> ODD{};
+  if (nk > 0) {
+    const Next n = next(2);
+    static_for<0, LPT>([&](auto l_tag) {
+      static_for<0, kSteps>([&](auto k_tag) { split_step(EVEN, l_tag, k_tag, 0); });
+      request(n, EVEN, l_tag);
+    });
+    barrier();
+    read_part(0, 0);
+    sched_fence();
+    // Behind an odd number of tiles there is one of zeros: with a condition around it the waits would count for a path without
+    // it, an exit in front of it doubles the accumulators' registers.
+    for (int i = 0; i < nk; i += 2) {
+      tile(i, EVEN);
+      tile(i + 1, ODD);
+    }
+  }
+
+  float odd = 0.f;  // 0 or, from a result that is not finite, NaN
+#pragma unroll
+  for (int x = 0; x < TM; ++x)
+#pragma unroll
+    for (int y = 0; y < TN; ++y)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        acc[x][y][r] += low[x][y][r];
+        odd = fmaf(acc[x][y][r], 0.f, odd);
+      }
+  __shared__ int not_finite[4];
+  const bool any = __ballot(odd != 0.f) != 0;
+  if (lane == 0) not_finite[wave] = any;
+  __syncthreads();  // and the tile is staged where the operands were
+  if (__builtin_amdgcn_readfirstlane(not_finite[0] | not_finite[1] | not_finite[2] | not_finite[3])) {
+    f32_dma_body<OP, BM, BN, GEN>(a, block, blocks);
+    return;
+  }
+  // accumulator register r of tile (x,y): m = wrow + 32 x + lane % 32, n = wcol + 32 y + 8 (r / 4) + 4 (lane / 32) + r % 4
+  t.template store<Lds::LDS_BYTES>(lds_f, [&](float* rows) {
+#pragma unroll
+    for (int x = 0; x < TM; ++x)
+#pragma unroll
+      for (int y = 0; y < TN; ++y)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          *reinterpret_cast<float4*>(rows + (32 * x + r31) * Tile::LDF + 32 * y + 8 * q + 4 * h) =
+              make_float4(acc[x][y][4 * q], acc[x][y][4 * q + 1], acc[x][y][4 * q + 2], acc[x][y][4 * q + 3]);
+  });
+}
+
+template <int OP, int BM, int BN, bool GEN, bool PARTS>
+__device__ __forceinline__ void f32_body(const F32Args& a, unsigned block, unsigned blocks) {
+  if constexpr (PARTS) f32_split_body<OP, BM, BN, GEN>(a, block, blocks);
+  else f32_dma_body<OP, BM, BN, GEN>(a, block, blocks);
+}
+template <int OP, int BM, int BN, bool GEN, bool PARTS>
+__global__ __launch_bounds__(256, PARTS ? 2 : 1) void f32_kernel(F32Args a) {
+  f32_body<OP, BM, BN, GEN, PARTS>(a, blockIdx.x, gridDim.x);
+}
+
+// Several launches in one: the residues of the stride of a strided backward-data layer, each of which alone fills a part of
+// the chip (ResNet-50 v1.5 at batch 20, 3x3 512 -> 512 on 14x14: 128 workgroups each).
+constexpr int FD_MAX_SET = 4;
+struct F32Set {
+  F32Args c[FD_MAX_SET];
+  unsigned first[FD_MAX_SET + 1];  // workgroup numbers of member k: first[k] .. first[k + 1] - 1
+};
+template <int BM, int BN, bool GEN, bool PARTS>
+__global__ __launch_bounds__(256, PARTS ? 2 : 1) void f32_set_kernel(F32Set s) {
+  int k = 0;
+  while (k + 1 < FD_MAX_SET && blockIdx.x >= s.first[k + 1]) ++k;
+#if defined(__HIP_DEVICE_COMPILE__)
+  // the member where it lies among the kernel's arguments: indexing the argument copies all of it to scratch memory first
+  const F32Set& set = *(const F32Set*)(const __attribute__((address_space(4))) F32Set*)__builtin_amdgcn_kernarg_segment_ptr();
+#else
+  const F32Set& set = s;
+#endif
+  f32_body<OP_BWD_DATA, BM, BN, GEN, PARTS>(set.c[k], blockIdx.x - s.first[k], s.first[k + 1] - s.first[k]);
+}
