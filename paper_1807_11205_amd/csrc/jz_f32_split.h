@@ -26,8 +26,7 @@
 // cycles, without bank conflicts, at a clock that power holds at 1.5-1.7 GHz.
 //
 // A tile's loads are requested two tiles ahead; the parts of tile i + 1 are made and written to the other of two stages between
-// the products of tile i; one barrier a tile, behind five of the six groups of products; the sixth covers the first operand reads of the
-// next tile.  LDS layouts of a part ("KC", "MC" as in jz_f32_dma.h): KC rows of 16 bfloat16, 16-byte half c of row r at place
+// the products of tile i; one barrier a tile, in the last of the six groups of products.  LDS layouts of a part ("KC", "MC" as in jz_f32_dma.h): KC rows of 16 bfloat16, 16-byte half c of row r at place
 // c ^ ((r >> 3) & 1); MC [16 k][rows], chunk c of eight at place c ^ 4 (k & 3) (64 rows: c ^ 2 (k & 3)), read with the transposing
 // ds_read_b64_tr_b16.
 #pragma once
@@ -125,11 +124,19 @@ __device__ __forceinline__ void f32_split_body(const F32Args& a, unsigned block,
     v.hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(ldsb + rd[2 * x + 1] + off));
     return __builtin_bit_cast(bf16x8, v);
   };
-  auto read_part = [&](int st, int k) {
+  auto read_a = [&](int st, int k) {
 #pragma unroll
     for (int x = 0; x < TM; ++x) fa[k][x] = read_operand(A_KC, rdA, x, st * STAGE + k * A_PART);
+  };
+  auto read_b = [&](int st, int k) {
 #pragma unroll
     for (int y = 0; y < TN; ++y) fb[k][y] = read_operand(B_KC, rdB, y, st * STAGE + k * B_PART);
+  };
+  // what the first two groups of products need, and what the last group leaves free
+  auto read_first = [&](int st) {
+    read_a(st, 1);
+    read_b(st, 1);
+    read_a(st, 0);
   };
 
   // Taking load l of register set SET apart, in kSteps steps of two vector instructions (the products hide four behind each of
@@ -161,28 +168,33 @@ __device__ __forceinline__ void f32_split_body(const F32Args& a, unsigned block,
     lds_wait<0>();
     __builtin_amdgcn_s_barrier();
   };
+  // The parts of the next tile are written behind kWritten of the 6 TT products, the barrier that waits for them is kMeet products
+  // in: 18 and 22 of 24, with the reads of read_first behind it, and 20 and 20, with part 0 of both operands behind it: 14x14 layer
+  // of 256 channels, 196 workgroups, 97 against 103 us; the same where two workgroups share a compute unit.
+  constexpr int kWritten = TT == 1 ? 5 : 9 * TT / 2, kMeet = 11 * TT / 2;
   // Tile i out of stage PAR = i & 1.
   auto tile = [&](int i, auto par_tag) {
     constexpr int PAR = decltype(par_tag)::value, NEXT = 1 - PAR;
-    constexpr int kA[6] = {0, 0, 1, 0, 2, 1}, kB[6] = {0, 1, 0, 2, 0, 1};
+    constexpr int kA[6] = {1, 0, 0, 1, 0, 2}, kB[6] = {1, 1, 0, 0, 2, 0};
     const Next n = next(i + 3);
-    read_part(PAR, 1);
-    read_part(PAR, 2);
+    read_b(PAR, 0);
+    read_b(PAR, 2);
+    read_a(PAR, 2);
     sched_fence();
     static_for<0, 6 * TT>([&](auto s_tag) {
       constexpr int S = decltype(s_tag)::value, P = S / TT, X = S % TT / TN, Y = S % TN;
-      if constexpr (S == 5 * TT) {
+      if constexpr (S == kMeet) {
         barrier();
-        read_part(NEXT, 0);
+        read_first(NEXT);
         sched_fence();
       }
-      f32x16& d = P == 0 ? acc[X][Y] : low[X][Y];
+      f32x16& d = kA[P] + kB[P] == 0 ? acc[X][Y] : low[X][Y];
       // n operand in the first slot: each lane then owns 4 consecutive n for one m (row = lane % 32)
       d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[kB[P]][Y], fa[kA[P]][X], d, 0, 0, 0);
-      if constexpr (S < 5 * TT) {
+      if constexpr (S < kWritten) {
         static_for<0, kSteps * LPT>([&](auto u_tag) {
           constexpr int U = decltype(u_tag)::value, Lx = U / kSteps, K = U % kSteps;
-          if constexpr (U * 5 * TT / (kSteps * LPT) == S) {
+          if constexpr (U * kWritten / (kSteps * LPT) == S) {
             split_step(std::integral_constant<int, NEXT>{}, std::integral_constant<int, Lx>{}, std::integral_constant<int, K>{}, NEXT);
             if constexpr (K + 1 == kSteps) request(n, std::integral_constant<int, NEXT>{}, std::integral_constant<int, Lx>{});
           }
@@ -200,7 +212,7 @@ __device__ __forceinline__ void f32_split_body(const F32Args& a, unsigned block,
       request(n, EVEN, l_tag);
     });
     barrier();
-    read_part(0, 0);
+    read_first(0);
     sched_fence();
     // Behind an odd number of tiles there is one of zeros: with a condition around it the waits would count for a path without
     // it, an exit in front of it doubles the accumulators' registers.
