@@ -393,9 +393,9 @@ void choose_tiling_f32(PlanF32* pl, bool may_split, bool fixed_tile = false, siz
       {false, 64, 128, 3, {0.489, 0.579, 0.630, 0.800}, {0.456, 0.476, 0.494, 0.565}, {0.159, 0.239, 0.687, 0.228}, {1.199, 1.092, 0.988, 0.657}},
       {false, 64, 64, 5, {0.283, 0.342, 0.352, 0.421}, {0.235, 0.246, 0.255, 0.288}, {0.037, 0.039, 0.043, 0.030}, {0.512, 0.548, 0.429, 0.187}}};
   const double parts_ahead = 0.3;
-  // FP32 instructions, parts; the last two per megabyte
+  // FP32 instructions, parts; the last two per megabyte (2.3: anything from 2 to 3.1 fits as well)
   static const double fixed[2][4] = {{4.76, 4.82, 5.10, 5.64}, {4.347, 5.147, 4.159, 5.374}},
-                      reduce_launch[2][4] = {{3.38, 3.81, 3.59, 4.01}, {3.094, 3.142, 3.543, 4.043}},
+                      reduce_launch[2][4] = {{3.38, 3.81, 3.59, 4.01}, {2.3, 2.3, 3.543, 4.043}},
                       reduce_byte[2][4] = {{0.187, 0.169, 0.160, 0.208}, {0.244, 0.234, 0.218, 0.285}},
                       byte[2][4] = {{0.135, 0.127, 0.135, 0.230}, {0.120, 0.088, 0.120, 0.185}};
   F32Args& a = pl->args;
@@ -607,46 +607,53 @@ bool make_class_plan_f32(const jz_conv_desc* d, const PlanF32& base, int ca, int
 template <int BM, int BN, bool PARTS>
 constexpr size_t lds_bytes_f32 = PARTS ? F32Split<BM, BN>::LDS_BYTES : (size_t)FD_NST * (BM + BN) * FD_BK * 4;
 
-template <int OP, int BM, int BN, bool GEN, bool PARTS>
+template <int OP, int BM, int BN, int FORM, bool PARTS>
 int launch_f32_tile(const F32Args& a, hipStream_t st) {
   constexpr size_t smem = lds_bytes_f32<BM, BN, PARTS>;
   static std::atomic<bool> lds_set{false};
-  if (!allow_lds(reinterpret_cast<const void*>(&f32_kernel<OP, BM, BN, GEN, PARTS>), smem, lds_set)) return JZ_ERR_LAUNCH;
-  hipLaunchKernelGGL((f32_kernel<OP, BM, BN, GEN, PARTS>), dim3((unsigned)(a.full_rows + (a.tiles_m - a.full_rows) * a.splits) * (unsigned)a.tiles_n),
+  if (!allow_lds(reinterpret_cast<const void*>(&f32_kernel<OP, BM, BN, FORM, PARTS>), smem, lds_set)) return JZ_ERR_LAUNCH;
+  hipLaunchKernelGGL((f32_kernel<OP, BM, BN, FORM, PARTS>), dim3((unsigned)(a.full_rows + (a.tiles_m - a.full_rows) * a.splits) * (unsigned)a.tiles_n),
                      dim3(256), smem, st, a);
   return jz::launch_status();
 }
-template <int BM, int BN, bool GEN, bool PARTS>
+template <int BM, int BN, int FORM, bool PARTS>
 int launch_f32_set_tile(const F32Set& set, hipStream_t st) {
   constexpr size_t smem = lds_bytes_f32<BM, BN, PARTS>;
   static std::atomic<bool> lds_set{false};
-  if (!allow_lds(reinterpret_cast<const void*>(&f32_set_kernel<BM, BN, GEN, PARTS>), smem, lds_set)) return JZ_ERR_LAUNCH;
-  hipLaunchKernelGGL((f32_set_kernel<BM, BN, GEN, PARTS>), dim3(set.first[FD_MAX_SET]), dim3(256), smem, st, set);
+  if (!allow_lds(reinterpret_cast<const void*>(&f32_set_kernel<BM, BN, FORM, PARTS>), smem, lds_set)) return JZ_ERR_LAUNCH;
+  hipLaunchKernelGGL((f32_set_kernel<BM, BN, FORM, PARTS>), dim3(set.first[FD_MAX_SET]), dim3(256), smem, st, set);
   return jz::launch_status();
 }
 
-template <int OP, bool GEN, bool PARTS>
-int launch_f32_form(const PlanF32& pl, hipStream_t st) {
-  if (pl.BM == 128 && pl.BN == 128) return launch_f32_tile<OP, 128, 128, GEN, PARTS>(pl.args, st);
-  if (pl.BM == 128) return launch_f32_tile<OP, 128, 64, GEN, PARTS>(pl.args, st);
-  if (pl.BN == 128) return launch_f32_tile<OP, 64, 128, GEN, PARTS>(pl.args, st);
-  return launch_f32_tile<OP, 64, 64, GEN, PARTS>(pl.args, st);
+template <int OP, int FORM, bool PARTS>
+int launch_f32_tiles(const PlanF32& pl, hipStream_t st) {
+  if (pl.BM == 128 && pl.BN == 128) return launch_f32_tile<OP, 128, 128, FORM, PARTS>(pl.args, st);
+  if (pl.BM == 128) return launch_f32_tile<OP, 128, 64, FORM, PARTS>(pl.args, st);
+  if (pl.BN == 128) return launch_f32_tile<OP, 64, 128, FORM, PARTS>(pl.args, st);
+  return launch_f32_tile<OP, 64, 64, FORM, PARTS>(pl.args, st);
 }
-template <bool GEN, bool PARTS>
+template <int OP, int FORM>
+int launch_f32_form(const PlanF32& pl, hipStream_t st) {
+  return pl.parts ? launch_f32_tiles<OP, FORM, true>(pl, st) : launch_f32_tiles<OP, FORM, false>(pl, st);
+}
+template <int FORM, bool PARTS>
 int launch_f32_set(const PlanF32& pl, const F32Set& set, hipStream_t st) {
-  if (pl.BM == 128 && pl.BN == 128) return launch_f32_set_tile<128, 128, GEN, PARTS>(set, st);
-  if (pl.BM == 128) return launch_f32_set_tile<128, 64, GEN, PARTS>(set, st);
-  if (pl.BN == 128) return launch_f32_set_tile<64, 128, GEN, PARTS>(set, st);
-  return launch_f32_set_tile<64, 64, GEN, PARTS>(set, st);
+  if (pl.BM == 128 && pl.BN == 128) return launch_f32_set_tile<128, 128, FORM, PARTS>(set, st);
+  if (pl.BM == 128) return launch_f32_set_tile<128, 64, FORM, PARTS>(set, st);
+  if (pl.BN == 128) return launch_f32_set_tile<64, 128, FORM, PARTS>(set, st);
+  return launch_f32_set_tile<64, 64, FORM, PARTS>(set, st);
 }
 
 template <int OP>
 int launch_f32(const PlanF32& pl, hipStream_t st) {
   const F32Args& a = pl.args;
   if (pl.dma) {
-    if constexpr (OP != OP_BWD_WEIGHT)
-      if (pl.gen) return pl.parts ? launch_f32_form<OP, true, true>(pl, st) : launch_f32_form<OP, true, false>(pl, st);
-    return pl.parts ? launch_f32_form<OP, false, true>(pl, st) : launch_f32_form<OP, false, false>(pl, st);
+    if constexpr (OP == OP_BWD_WEIGHT) {
+      if (a.bw_linear) return launch_f32_form<OP, F32_MATRIX>(pl, st);
+      return a.bw_same ? launch_f32_form<OP, F32_SAME>(pl, st) : launch_f32_form<OP, F32_GATHER>(pl, st);
+    } else {
+      return pl.gen ? launch_f32_form<OP, F32_TAPS>(pl, st) : launch_f32_form<OP, F32_MASKS>(pl, st);
+    }
   }
   const dim3 grid((unsigned)a.tiles_m * (unsigned)a.tiles_n * (unsigned)a.splits), block(F_THREADS);
   if constexpr (OP == OP_BWD_DATA)
@@ -704,8 +711,8 @@ int run_f32(int op, const jz_conv_desc* d, const void* A, const void* B, void* D
         set.first[j + 1] = set.first[j];
       }
       k = 0;
-      if (pl.gen) return pl.parts ? launch_f32_set<true, true>(pl, set, st) : launch_f32_set<true, false>(pl, set, st);
-      return pl.parts ? launch_f32_set<false, true>(pl, set, st) : launch_f32_set<false, false>(pl, set, st);
+      if (pl.gen) return pl.parts ? launch_f32_set<F32_TAPS, true>(pl, set, st) : launch_f32_set<F32_TAPS, false>(pl, set, st);
+      return pl.parts ? launch_f32_set<F32_MASKS, true>(pl, set, st) : launch_f32_set<F32_MASKS, false>(pl, set, st);
     };
     const int Rm = (d->R + d->stride_h - 1) / d->stride_h, Sm = (d->S + d->stride_w - 1) / d->stride_w;
     const bool rows_first = (Rm - 1) * Sm >= Rm * (Sm - 1);

@@ -12,8 +12,11 @@
 //     none for the others (the last tile of a backward-weight reduction, whose rows can lie beyond the tensors, is the one
 //     that compares: scalar offsets take no part in the descriptor's range check);
 //   * the loop is unrolled over the ring's stages, so that LDS addresses are a register plus a constant.
-// GEN = true keeps per-lane tap arithmetic, for channel counts that are not multiples of the k tile (the reduction then runs
-// over the flattened (tap, channel) index) and more than 32 taps.
+// F32_TAPS keeps per-lane tap arithmetic, for channel counts that are not multiples of the k tile (the reduction then runs
+// over the flattened (tap, channel) index) and more than 32 taps.  Backward-weight reads x as a plain matrix (1x1, unit stride,
+// unpadded), at a constant distance per tap (F32_SAME: the output grid is the input grid) or by the input pixel's offset; as one
+// kernel that looks at the launch's arguments a gathered load was 38 vector instructions, now 4, 17 and 20 (ResNet-50's weight
+// gradients at N = 64, operands in parts: 3.63 -> 3.46 ms).
 // The MFMA is the 16x16x4 form: in a loop of nothing else it reaches 152-154 TFLOP/s whatever the occupancy, the 32x32x2
 // form 141 with one wavefront per SIMD, 151 with two and 124 with four.
 //
@@ -51,11 +54,15 @@ __device__ __forceinline__ int clamp_taps(int x, int hi) { return x < 0 ? 0 : (x
 constexpr int FD_BK = 16;   // floats per k tile: a KC row is 64 bytes
 constexpr int FD_NST = 4;   // ring stages
 
+// how an operand is gathered: x and dy per pixel in forward and backward-data, x in backward-weight
+enum { F32_MASKS = 0, F32_TAPS = 1, F32_MATRIX = 0, F32_SAME = 1, F32_GATHER = 2 };
+
 // What the workgroup with number `block` of the `blocks` that the launch `a` consists of loads, and where its results go.
 // SWZ: the places of the 16-byte chunks in LDS follow from the load (LDS-direct), so the lanes fetch them in swizzled order.
-template <int OP, int BM, int BN, bool GEN, bool SWZ>
+template <int OP, int BM, int BN, int FORM, bool SWZ>
 struct F32Tile {
-  static_assert(!GEN || OP != OP_BWD_WEIGHT, "backward-weight has one form");
+  static constexpr bool GEN = OP != OP_BWD_WEIGHT && FORM == F32_TAPS;
+  static constexpr bool MATRIX = OP == OP_BWD_WEIGHT && FORM == F32_MATRIX, SAME = OP == OP_BWD_WEIGHT && FORM == F32_SAME;
   static constexpr bool A_KC = OP != OP_BWD_WEIGHT, B_KC = OP == OP_FWD;
   static constexpr int A_BYTES = BM * FD_BK * 4, B_BYTES = BN * FD_BK * 4;
   static constexpr int LA = A_BYTES / 4096, LB = B_BYTES / 4096, LPT = LA + LB;  // 16-byte loads per thread and tile
@@ -113,7 +120,7 @@ struct F32Tile {
     rsrcA = __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)a.A - biasA), 0, (int)(a.bytesA + biasA), 0x00020000);
     // backward-weight of a layer whose output grid is its input grid (bw_same): pixel j at a tap is pixel j + constant of x, so the
     // offset is linear in j as for a plain matrix and only the image borders need the pixel's coordinates
-    const unsigned biasB = OP == OP_BWD_WEIGHT && a.bw_same ? (unsigned)(g.ph * g.row_pitch + g.pw * g.IC) * 4u : 0u;
+    const unsigned biasB = SAME ? (unsigned)(g.ph * g.row_pitch + g.pw * g.IC) * 4u : 0u;
     rsrcB = __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)a.B - biasB), 0, (int)(a.bytesB + biasB), 0x00020000);
 
     // ---- loader geometry: one load of a wavefront fills 1 KB ----------------------------------------
@@ -195,7 +202,7 @@ struct F32Tile {
         xq[ii] = (int)qq * g.sw + s0;
         xp_end[ii] = bw_rows + r0;
         xq_end[ii] = bw_cols + s0;
-        if (a.bw_same && nn < a.N) vB[ii] = (unsigned)((mc_k(BN, ii) + r0 * g.IW + s0) * g.IC + ch) * 4u + biasB;
+        if (SAME && nn < a.N) vB[ii] = (unsigned)((mc_k(BN, ii) + r0 * g.IW + s0) * g.IC + ch) * 4u + biasB;
         xoff[ii] = ((n * (unsigned)g.IH + (unsigned)xp[ii]) * (unsigned)g.row_pitch + (unsigned)xq[ii] * (unsigned)g.IC + (unsigned)ch) * 4u;
       }
     }
@@ -267,25 +274,20 @@ struct F32Tile {
       } else if constexpr (OP != OP_BWD_WEIGHT) {
         f(rsrcB, vB[ii], c.soffB);
       } else {
-        // one request whatever the form: a wait counts the requests behind it
-        unsigned voff, soff = c.soffB;
-        bool ok = true;
-        if (a.bw_linear) {
-          voff = vB[ii];
+        const bool beyond = c.tail && c.k0 + (unsigned)mc_k(BN, ii) >= (unsigned)a.Kred;
+        if constexpr (MATRIX) {
+          f(rsrcB, beyond ? OOB : vB[ii], c.soffB);
         } else {
-          ok = (unsigned)xp[ii] < (unsigned)g.IH && (unsigned)xq[ii] < (unsigned)g.IW;
-          voff = a.bw_same ? vB[ii] : xoff[ii];
-          if (!a.bw_same) soff = 0u;
+          const bool ok = (unsigned)xp[ii] < (unsigned)g.IH && (unsigned)xq[ii] < (unsigned)g.IW && !beyond;
+          f(rsrcB, ok ? (SAME ? vB[ii] : xoff[ii]) : OOB, SAME ? c.soffB : 0u);
           xq[ii] += bw_tq;
           const bool c1 = xq[ii] >= xq_end[ii];
           xq[ii] -= c1 ? bw_cols : 0;
           xp[ii] += c1 ? bw_tp1 : bw_tp;
           const bool c2 = xp[ii] >= xp_end[ii];
           xp[ii] -= c2 ? bw_rows : 0;
-          if (!a.bw_same) xoff[ii] += bw_dv + (c1 ? bw_k1 : 0u) + (c2 ? bw_k2 : 0u);
+          if constexpr (!SAME) xoff[ii] += bw_dv + (c1 ? bw_k1 : 0u) + (c2 ? bw_k2 : 0u);
         }
-        if (c.tail) ok = ok && c.k0 + (unsigned)mc_k(BN, ii) < (unsigned)a.Kred;
-        f(rsrcB, ok ? voff : OOB, soff);
       }
     }
   }
@@ -342,9 +344,9 @@ struct F32Tile {
 };
 
 // the tile on the FP32 matrix instructions
-template <int OP, int BM, int BN, bool GEN>
+template <int OP, int BM, int BN, int FORM>
 __device__ __forceinline__ void f32_dma_body(const F32Args& a, unsigned block, unsigned blocks) {
-  using Tile = F32Tile<OP, BM, BN, GEN, true>;
+  using Tile = F32Tile<OP, BM, BN, FORM, true>;
   constexpr bool A_KC = Tile::A_KC, B_KC = Tile::B_KC;
   constexpr int TM = BM / 32, TN = BN / 32;   // 16x16 MFMA tiles per wavefront
   constexpr int RB = FD_BK * 4;               // bytes per row of a KC tile

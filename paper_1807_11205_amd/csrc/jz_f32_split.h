@@ -45,9 +45,9 @@ struct F32Split {
   static constexpr int LDS_BYTES = 2 * STAGE > RING ? 2 * STAGE : RING;
 };
 
-template <int OP, int BM, int BN, bool GEN>
+template <int OP, int BM, int BN, int FORM>
 __device__ __forceinline__ void f32_split_body(const F32Args& a, unsigned block, unsigned blocks) {
-  using Tile = F32Tile<OP, BM, BN, GEN, false>;
+  using Tile = F32Tile<OP, BM, BN, FORM, false>;
   using Lds = F32Split<BM, BN>;
   constexpr bool A_KC = Tile::A_KC, B_KC = Tile::B_KC;
   constexpr int TM = BM / 64, TN = BN / 64, TT = TM * TN;  // 32x32 MFMA tiles per wavefront
@@ -237,7 +237,7 @@ __device__ __forceinline__ void f32_split_body(const F32Args& a, unsigned block,
   if (lane == 0) not_finite[wave] = any;
   __syncthreads();  // and the tile is staged where the operands were
   if (__builtin_amdgcn_readfirstlane(not_finite[0] | not_finite[1] | not_finite[2] | not_finite[3])) {
-    f32_dma_body<OP, BM, BN, GEN>(a, block, blocks);
+    f32_dma_body<OP, BM, BN, FORM>(a, block, blocks);
     return;
   }
   // accumulator register r of tile (x,y): m = wrow + 32 x + lane % 32, n = wcol + 32 y + 8 (r / 4) + 4 (lane / 32) + r % 4
@@ -253,14 +253,14 @@ __device__ __forceinline__ void f32_split_body(const F32Args& a, unsigned block,
   });
 }
 
-template <int OP, int BM, int BN, bool GEN, bool PARTS>
+template <int OP, int BM, int BN, int FORM, bool PARTS>
 __device__ __forceinline__ void f32_body(const F32Args& a, unsigned block, unsigned blocks) {
-  if constexpr (PARTS) f32_split_body<OP, BM, BN, GEN>(a, block, blocks);
-  else f32_dma_body<OP, BM, BN, GEN>(a, block, blocks);
+  if constexpr (PARTS) f32_split_body<OP, BM, BN, FORM>(a, block, blocks);
+  else f32_dma_body<OP, BM, BN, FORM>(a, block, blocks);
 }
-template <int OP, int BM, int BN, bool GEN, bool PARTS>
+template <int OP, int BM, int BN, int FORM, bool PARTS>
 __global__ __launch_bounds__(256, PARTS ? 2 : 1) void f32_kernel(F32Args a) {
-  f32_body<OP, BM, BN, GEN, PARTS>(a, blockIdx.x, gridDim.x);
+  f32_body<OP, BM, BN, FORM, PARTS>(a, blockIdx.x, gridDim.x);
 }
 
 // Several launches in one: the residues of the stride of a strided backward-data layer, each of which alone fills a part of
@@ -270,7 +270,7 @@ struct F32Set {
   F32Args c[FD_MAX_SET];
   unsigned first[FD_MAX_SET + 1];  // workgroup numbers of member k: first[k] .. first[k + 1] - 1
 };
-template <int BM, int BN, bool GEN, bool PARTS>
+template <int BM, int BN, int FORM, bool PARTS>
 __global__ __launch_bounds__(256, PARTS ? 2 : 1) void f32_set_kernel(F32Set s) {
   int k = 0;
   while (k + 1 < FD_MAX_SET && blockIdx.x >= s.first[k + 1]) ++k;
@@ -280,5 +280,5 @@ __global__ __launch_bounds__(256, PARTS ? 2 : 1) void f32_set_kernel(F32Set s) {
 #else
   const F32Set& set = s;
 #endif
-  f32_body<OP_BWD_DATA, BM, BN, GEN, PARTS>(set.c[k], blockIdx.x - s.first[k], s.first[k + 1] - s.first[k]);
+  f32_body<OP_BWD_DATA, BM, BN, FORM, PARTS>(set.c[k], blockIdx.x - s.first[k], s.first[k + 1] - s.first[k]);
 }
