@@ -804,8 +804,13 @@ int compute_plan(int op, const jz_conv_desc* d, Plan* pl, size_t limit = kPartia
   a.sc_on = 0; a.sc_H = a.sc_W = 0; a.sc_sh = a.sc_sw = 1; a.sc_oh = a.sc_ow = 0; a.sc_fill = 0;
   a.w_taps = d->R * d->S; a.w_tap0 = 0; a.w_tap_r = d->S; a.w_tap_s = 1;
   g.always_mask = 0;
-  a.bw_linear = (op == JZ_BWD_WEIGHT && d->R == 1 && d->S == 1 && d->stride_h == 1 && d->stride_w == 1 && d->pad_h == 0 &&
-                 d->pad_w == 0) ? 1 : 0;
+  a.bw_x = BW_GATHER;
+  if (op == JZ_BWD_WEIGHT && d->stride_h == 1 && d->stride_w == 1) {
+    if (d->R == 1 && d->S == 1 && d->pad_h == 0 && d->pad_w == 0) a.bw_x = BW_MATRIX;
+    else if (pl->fast && P == d->H && Q == d->W && (long long)d->R * d->W < (1ll << 30) &&
+             (long long)pl->bytesB + 2ll * d->C * ((long long)d->pad_h * d->W + d->pad_w) < 0xfffffff0ll)
+      a.bw_x = BW_SAME;
+  }
   if (op == JZ_BWD_DATA && pl->fast && d->R == 1 && d->S == 1 && d->pad_h == 0 && d->pad_w == 0 &&
       (d->stride_h > 1 || d->stride_w > 1)) {
     // strided 1x1 layer (the ResNet downsampling convs): only input pixels (p*sh, q*sw) receive gradient, so the GEMM
@@ -940,7 +945,7 @@ bool compute_class_plan(const jz_conv_desc* d, const Plan& base, int ca, int cb,
   g.always_mask = 1;   // the class grid and the dy grid are not tied by the usual size formula
   a.w_tap0 = r0 * d->S + s0; a.w_tap_r = sh * d->S; a.w_tap_s = sw;   // its taps among the filter's
   a.sc_on = 1; a.sc_H = d->H; a.sc_W = d->W; a.sc_sh = sh; a.sc_sw = sw; a.sc_oh = ca; a.sc_ow = cb; a.sc_fill = 0;
-  a.bw_linear = 0;
+  a.bw_x = BW_GATHER;
   finish_geometry(g);
   pl->bk = 32;
   choose_tiling(pl, d->K % 64 == 0, 0);

@@ -14,7 +14,10 @@ __global__ __launch_bounds__(64 * WGM * WGN) void igemm_wgrad_set_kernel(WgradSe
   int k = 0;
 #pragma unroll
   for (int j = 1; j < kWgradSet; ++j) k += blockIdx.x >= s.first[j] ? 1 : 0;  // behind the last member: first[j] is the grid size
-  igemm_dma_body<OP_BWD_WEIGHT, BM, BN, TBK, NST, false, WGM, WGN, false, false>(s.g[k], blockIdx.x - s.first[k], s.first[k + 1] - s.first[k]);
+  const unsigned block = blockIdx.x - s.first[k], blocks = s.first[k + 1] - s.first[k];
+  if (s.g[k].bw_x == BW_MATRIX) igemm_dma_body<OP_BWD_WEIGHT, BM, BN, TBK, NST, false, WGM, WGN, false, false, BW_MATRIX>(s.g[k], block, blocks);
+  else if (s.g[k].bw_x == BW_SAME) igemm_dma_body<OP_BWD_WEIGHT, BM, BN, TBK, NST, false, WGM, WGN, false, false, BW_SAME>(s.g[k], block, blocks);
+  else igemm_dma_body<OP_BWD_WEIGHT, BM, BN, TBK, NST, false, WGM, WGN, false, false, BW_GATHER>(s.g[k], block, blocks);
 }
 
 template <int BM, int BN, int TBK, int NST, int WGM, int WGN>

@@ -55,6 +55,15 @@ struct ConvGeom {
   FastDiv d_ohow, d_ow, d_ic, d_s, d_sh, d_sw;
 };
 
+// How the gathered x of a weight gradient is read.  BW_MATRIX: a 1x1 unit-stride unpadded layer, reduction row j (a pixel) starts
+// at j * IC.  BW_SAME: unit stride, output grid = input grid: pixel j at a tap is pixel j + constant of x, so the offset is linear in j
+// and only the image borders need j's place in its image.  BW_GATHER: by the input pixel's coordinates and offset.
+// A kernel for each: as one that looked at its arguments a gathered load was 24 vector instructions and two branches between two
+// products (four are free behind a product, eight leave the matrix pipe two thirds busy), now 12 and 17 over two of them.  3x3 weight
+// gradients, N = 64: 64 channels, 56x56 42 -> 34 us; 128, 28x28 30.5 -> 28.3; 256, 14x14 31 -> 29; AlexNet's 5x5 141 -> 134; with the
+// same instructions saved but a branch per form kept in the loop they were 3-25 % slower than before.
+enum { BW_GATHER = 0, BW_MATRIX = 1, BW_SAME = 2 };
+
 struct GemmArgs {
   const unsigned short* A;
   const unsigned short* B;
@@ -83,8 +92,7 @@ struct GemmArgs {
   // sc_H x sc_W image; sc_fill: the other pixels of each sc_sh x sc_sw cell receive zeros (strided 1x1 layers, where no
   // output pixel reads them); without it the launch is one of sc_sh * sc_sw that cover the image between them
   int sc_on, sc_H, sc_W, sc_sh, sc_sw, sc_oh, sc_ow, sc_fill;
-  // backward-weight of a 1x1 unit-stride unpadded layer: reduction row j (a pixel) of x starts at j * IC, no gather
-  int bw_linear;
+  int bw_x;  // backward-weight: how x is read (BW_MATRIX ...)
   // backward-data: tap (r, s) of the launch is tap w_tap0 + r w_tap_r + s w_tap_s of the w_taps taps of a filter (a parity
   // class of a stride has a subset of them)
   int w_taps, w_tap0, w_tap_r, w_tap_s;

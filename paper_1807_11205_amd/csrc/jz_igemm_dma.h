@@ -78,7 +78,7 @@ constexpr int dma_epass(int bm, int bn) { return bm * (bn + 8) * 2 > 128 * 1024 
 __device__ __forceinline__ unsigned low_bits(int k) { return k >= 32 ? 0xffffffffu : (1u << k) - 1u; }
 __device__ __forceinline__ int clamp_to(int x, int hi) { return x < 0 ? 0 : (x > hi ? hi : x); }
 
-template <int OP_ARG, int BM, int BN, int TBK, int NST, bool MASKA = false, int WGM = 2, int WGN = 2, bool GEN = false, bool FLAT = false>
+template <int OP_ARG, int BM, int BN, int TBK, int NST, bool MASKA = false, int WGM = 2, int WGN = 2, bool GEN = false, bool FLAT = false, int BWX = BW_GATHER>
 __device__ __forceinline__ void igemm_dma_body(const GemmArgs& a, unsigned block, unsigned blocks) {
   // the forward kernel with column sums in its epilogue (1), the backward-data kernel with batch-norm backward sums (2),
   // the same with the gradient of a residual block's end formed from the tile first (3)
@@ -134,7 +134,9 @@ __device__ __forceinline__ void igemm_dma_body(const GemmArgs& a, unsigned block
   }
   const __amdgpu_buffer_rsrc_t rsrcA =
       __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)a.A - biasA), 0, (int)(a.bytesA + biasA), 0x00020000);
-  const __amdgpu_buffer_rsrc_t rsrcB = __builtin_amdgcn_make_buffer_rsrc((void*)a.B, 0, (int)a.bytesB, 0x00020000);
+  const unsigned biasB = OP == OP_BWD_WEIGHT && BWX == BW_SAME ? (unsigned)(g.ph * g.row_pitch + g.pw * g.IC) * 2u : 0u;
+  const __amdgpu_buffer_rsrc_t rsrcB =
+      __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)a.B - biasB), 0, (int)(a.bytesB + biasB), 0x00020000);
 
   // ---- loader geometry ---------------------------------------------------------------------
   // KC tile: one load covers 64 / CR rows; load ii of wave w covers rows (NW ii + w) * (64 / CR) + lane / CR and the
@@ -252,11 +254,13 @@ __device__ __forceinline__ void igemm_dma_body(const GemmArgs& a, unsigned block
   }
   // backward-weight, gathered x: per load the row, the column and the byte offset of the input pixel at this lane's tap,
   // advanced per tile; the digits are input coordinates (times the stride, plus the tap), which wrap at xp_end, xq_end: no
-  // multiplication in the k loop, exact for every size
+  // multiplication in the k loop, exact for every size.  BW_SAME: xp is the output pixel's index in its image, xq its column, advanced
+  // without a carry between them: tap row r of pixel i is inside where i + (r - ph) OW is an index of the image.
   int xp[LB], xq[LB], xp_end = 0, xq_end = 0, bw_tp = 0, bw_tp1 = 0, bw_tq = 0;
+  const unsigned bw_img = (unsigned)(g.OH * g.OW);
   const int bw_rows = g.OH * g.sh, bw_cols = g.OW * g.sw;
   unsigned xoff[LB], bw_dv = 0, bw_k1 = 0, bw_k2 = 0;
-  (void)xp; (void)xq; (void)xp_end; (void)xq_end; (void)xoff; (void)bw_tp; (void)bw_tp1; (void)bw_tq; (void)bw_dv; (void)bw_k1; (void)bw_k2;
+  (void)xp; (void)xq; (void)xp_end; (void)xq_end; (void)xoff; (void)bw_img; (void)bw_tp; (void)bw_tp1; (void)bw_tq; (void)bw_dv; (void)bw_k1; (void)bw_k2;
   if (OP == OP_FWD) {
 #pragma unroll
     for (int ii = 0; ii < LB; ++ii) {
@@ -285,12 +289,29 @@ __device__ __forceinline__ void igemm_dma_body(const GemmArgs& a, unsigned block
     // 1x1, unit stride, no padding: pixel j of x is row j of a plain [Kred][IC] matrix, so the load needs no pixel
     // arithmetic at all (per-lane offset fixed, per-tile offset scalar)
 #pragma unroll
-    for (int ii = 0; ii < LB; ++ii) vB[ii] = (a.bw_linear && nn < a.N) ? (unsigned)(mc_k(BN, ii) * g.IC + nn) * 2u : OOB;
+    for (int ii = 0; ii < LB; ++ii) {
+      vB[ii] = BWX == BW_MATRIX ? (unsigned)(mc_k(BN, ii) * g.IC + nn) * 2u
+                                   : (unsigned)((mc_k(BN, ii) + sb1 * g.IW + sb2) * g.IC + sbc) * 2u + biasB;  // used by BW_SAME
+      if (nn >= a.N) vB[ii] = OOB;
+    }
     // Any other layer: load ii of k tile kt reads, for output pixel j = kt TBK + k-row, the input pixel at this lane's
     // tap.  The pixel of the first tile is decomposed by division here; from tile to tile j grows by TBK, so its
     // (image, row, column) digits and the byte offset advance by TBK's own digits with one carry each (as the rows
     // of the gathered operand do in the other two passes): no division and no slow multiplication inside the k loop.
-    if (!a.bw_linear) {
+    if (BWX == BW_SAME) {
+      const unsigned dj = (unsigned)TBK;
+      bw_tp = (int)(dj - fd_div(dj, g.d_ohow) * bw_img);
+      bw_tq = (int)(dj - fd_div(dj, g.d_ow) * (unsigned)g.OW);
+      xp_end = sb1 * g.OW;  // what the lane's tap adds to index and column; a column that does not exist has vB out of range
+      xq_end = sb2;
+#pragma unroll
+      for (int ii = 0; ii < LB; ++ii) {
+        const unsigned j = (unsigned)(kt_begin * TBK + mc_k(BN, ii));
+        const unsigned rem = j - fd_div(j, g.d_ohow) * bw_img;
+        xp[ii] = (int)rem;
+        xq[ii] = (int)(rem - fd_div(rem, g.d_ow) * (unsigned)g.OW);
+      }
+    } else if (BWX == BW_GATHER) {
       const unsigned ta = fd_div((unsigned)TBK, g.d_ohow);
       const unsigned trem = (unsigned)TBK - ta * (unsigned)(g.OH * g.OW);
       const unsigned tp = fd_div(trem, g.d_ow), tq = trem - tp * (unsigned)g.OW;
@@ -363,7 +384,7 @@ __device__ __forceinline__ void igemm_dma_body(const GemmArgs& a, unsigned block
       c.rag = c.c0 + kc_chunk * 8 < g.IC ? 0u : OOB;
     } else {
       c.soffA = (unsigned)(c.k0 * a.M) * 2u;
-      c.soffB = (unsigned)(c.k0 * g.IC) * 2u;  // used by the plain-matrix case only
+      c.soffB = (unsigned)(c.k0 * g.IC) * 2u;  // not used by BW_GATHER
     }
     return c;
   };
@@ -414,28 +435,46 @@ __device__ __forceinline__ void igemm_dma_body(const GemmArgs& a, unsigned block
         } else if constexpr (OP == OP_BWD_DATA) {
           const bool ok = c.c0 + mc_k(BN, ii) < g.IC;
           jz_dma16s(rsrcB, dst, ok ? vB[ii] : OOB, c.soffB);
-        } else if (a.bw_linear) {  // x rows j = k0 + k of a plain matrix
+        } else if (BWX == BW_MATRIX) {  // x rows j = k0 + k of a plain matrix
           const bool ok = c.k0 + mc_k(BN, ii) < a.Kred;
+          jz_dma16s(rsrcB, dst, ok ? vB[ii] : OOB, c.soffB);
+        } else if (BWX == BW_SAME) {
+          const bool ok = c.k0 + mc_k(BN, ii) < a.Kred && (unsigned)(xp[ii] + xp_end) < bw_img && (unsigned)(xq[ii] + xq_end) < (unsigned)g.OW;
           jz_dma16s(rsrcB, dst, ok ? vB[ii] : OOB, c.soffB);
         } else {  // x at this lane's tap for output pixel j = k0 + k-row
           const bool ok = c.k0 + mc_k(BN, ii) < a.Kred && (unsigned)xp[ii] < (unsigned)g.IH && (unsigned)xq[ii] < (unsigned)g.IW;
           jz_dma16(rsrcB, dst, ok ? xoff[ii] : OOB);
-          // on to the pixel of the next tile
-          xq[ii] += bw_tq;
-          const bool c1 = xq[ii] >= xq_end;
-          xq[ii] -= c1 ? bw_cols : 0;
-          xp[ii] += c1 ? bw_tp1 : bw_tp;
-          const bool c2 = xp[ii] >= xp_end;
-          xp[ii] -= c2 ? bw_rows : 0;
-          xoff[ii] += bw_dv + (c1 ? bw_k1 : 0u) + (c2 ? bw_k2 : 0u);
         }
+      }
+    }
+  };
+  // ... and on to the pixel of the next tile: a product later, so that neither has more vector instructions behind it than it hides
+  auto advance_load = [&](auto l_tag) {
+    constexpr int Lidx = decltype(l_tag)::value;
+    if constexpr (OP == OP_BWD_WEIGHT && Lidx >= LA && Lidx < LPT) {
+      constexpr int ii = Lidx - LA;
+      if (BWX == BW_SAME) {
+        const unsigned i = (unsigned)(xp[ii] + bw_tp), q = (unsigned)(xq[ii] + bw_tq), i1 = i - bw_img, q1 = q - (unsigned)g.OW;
+        xp[ii] = (int)(i < i1 ? i : i1);  // unsigned: a difference below zero is the larger one
+        xq[ii] = (int)(q < q1 ? q : q1);
+      } else if (BWX == BW_GATHER) {
+        xq[ii] += bw_tq;
+        const bool c1 = xq[ii] >= xq_end;
+        xq[ii] -= c1 ? bw_cols : 0;
+        xp[ii] += c1 ? bw_tp1 : bw_tp;
+        const bool c2 = xp[ii] >= xp_end;
+        xp[ii] -= c2 ? bw_rows : 0;
+        xoff[ii] += bw_dv + (c1 ? bw_k1 : 0u) + (c2 ? bw_k2 : 0u);
       }
     }
   };
   static_assert(NST >= 3 && NST <= 8 && (NST - 2) * LPT <= 63, "ring depth: vmcnt is a 6-bit counter");
   auto issue = [&](int kt, int st) {  // all loads of a tile at once (prologue)
     TileCtx c = tile_ctx(kt);
-    static_for<0, LPT>([&](auto l) { issue_load(c, st, l); });
+    static_for<0, LPT>([&](auto l) {
+      issue_load(c, st, l);
+      advance_load(l);
+    });
   };
 
   // the first NST-1 tiles are requested before anything else is set up: their round trip to memory is the longest
@@ -611,10 +650,17 @@ __device__ __forceinline__ void igemm_dma_body(const GemmArgs& a, unsigned block
         // n operand in the first slot: each lane then owns 4 consecutive n for one m (row = lane % 32)
         acc[I][J] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fb[J], fa[I], acc[I][J], 0, 0, 0);
         sched_fence();
-        if constexpr (ISSUE && (Q < G - 1 || G == 1)) {
+        if constexpr (ISSUE) {
           static_for<0, LPT>([&](auto l_tag) {
-            constexpr int Lx = decltype(l_tag)::value;
-            if constexpr ((Lx * NSL / LPT) / SPG == KS && (Lx * NSL / LPT) % SPG == Q) issue_load(c, ist, l_tag);
+            constexpr int Lx = decltype(l_tag)::value, SLOT = Lx * NSL / LPT;
+            if constexpr (G > 1 && SLOT / SPG == KS && SLOT % SPG + 1 == Q) advance_load(l_tag);
+          });
+          static_for<0, LPT>([&](auto l_tag) {
+            constexpr int Lx = decltype(l_tag)::value, SLOT = Lx * NSL / LPT;
+            if constexpr ((Q < G - 1 || G == 1) && SLOT / SPG == KS && SLOT % SPG == Q) {
+              issue_load(c, ist, l_tag);
+              if constexpr (G == 1) advance_load(l_tag);
+            }
           });
           sched_fence();
         }
@@ -658,9 +704,9 @@ __device__ __forceinline__ void igemm_dma_body(const GemmArgs& a, unsigned block
       a, acc, lds, m0, n0, split, tid, lane, wm * WTM, wn * WTN);
 }
 
-template <int OP, int BM, int BN, int TBK, int NST, bool MASKA = false, int WGM = 2, int WGN = 2, bool GEN = false, bool FLAT = false>
+template <int OP, int BM, int BN, int TBK, int NST, bool MASKA = false, int WGM = 2, int WGN = 2, bool GEN = false, bool FLAT = false, int BWX = BW_GATHER>
 __global__ __launch_bounds__(64 * WGM * WGN) void igemm_dma_kernel(GemmArgs a) {
-  igemm_dma_body<OP, BM, BN, TBK, NST, MASKA, WGM, WGN, GEN, FLAT>(a, blockIdx.x, gridDim.x);
+  igemm_dma_body<OP, BM, BN, TBK, NST, MASKA, WGM, WGN, GEN, FLAT, BWX>(a, blockIdx.x, gridDim.x);
 }
 
 // Several GEMMs of one variant in one launch: the parity classes of a strided backward-data layer, each of which alone is a

@@ -459,14 +459,14 @@ int launch_one(const GemmArgs& a, hipStream_t st) {
   return jz::launch_status();
 }
 
-template <int OP, int BM, int BN, int TBK, int NST, bool MASKA = false, int WGM = 2, int WGN = 2, bool GEN = false, bool FLAT = false>
-int launch_dma(const GemmArgs& a, hipStream_t st, const GemmSet* set = nullptr) {
+template <int OP, int BM, int BN, int TBK, int NST, bool MASKA, int WGM, int WGN, bool GEN, bool FLAT, int BWX>
+int launch_dma_x(const GemmArgs& a, hipStream_t st, const GemmSet* set) {
   constexpr size_t ring_bytes = (size_t)NST * (BM + BN) * 2 * TBK;
   constexpr size_t epi_bytes = (size_t)BM / dma_epass(BM, BN) * (BN + 8) * sizeof(unsigned short);
   constexpr size_t smem = ring_bytes > epi_bytes ? ring_bytes : epi_bytes;
   static_assert(smem <= 160 * 1024, "more LDS than a compute unit has");
   static std::atomic<bool> lds_set{false};
-  if (!jz::allow_lds(reinterpret_cast<const void*>(&igemm_dma_kernel<OP, BM, BN, TBK, NST, MASKA, WGM, WGN, GEN, FLAT>), smem, lds_set)) return JZ_ERR_LAUNCH;
+  if (!jz::allow_lds(reinterpret_cast<const void*>(&igemm_dma_kernel<OP, BM, BN, TBK, NST, MASKA, WGM, WGN, GEN, FLAT, BWX>), smem, lds_set)) return JZ_ERR_LAUNCH;
   if constexpr (OP == OP_BWD_DATA && !GEN && !MASKA) {
     if (set) {
       static std::atomic<bool> set_lds_set{false};
@@ -476,8 +476,16 @@ int launch_dma(const GemmArgs& a, hipStream_t st, const GemmSet* set = nullptr) 
     }
   }
   unsigned grid = (unsigned)a.tiles_m * (unsigned)a.tiles_n * (unsigned)a.splits;
-  hipLaunchKernelGGL((igemm_dma_kernel<OP, BM, BN, TBK, NST, MASKA, WGM, WGN, GEN, FLAT>), dim3(grid), dim3(64 * WGM * WGN), smem, st, a);
+  hipLaunchKernelGGL((igemm_dma_kernel<OP, BM, BN, TBK, NST, MASKA, WGM, WGN, GEN, FLAT, BWX>), dim3(grid), dim3(64 * WGM * WGN), smem, st, a);
   return jz::launch_status();
+}
+template <int OP, int BM, int BN, int TBK, int NST, bool MASKA = false, int WGM = 2, int WGN = 2, bool GEN = false, bool FLAT = false>
+int launch_dma(const GemmArgs& a, hipStream_t st, const GemmSet* set = nullptr) {
+  if constexpr (OP == OP_BWD_WEIGHT) {
+    if (a.bw_x == BW_MATRIX) return launch_dma_x<OP, BM, BN, TBK, NST, MASKA, WGM, WGN, GEN, FLAT, BW_MATRIX>(a, st, set);
+    if (a.bw_x == BW_SAME) return launch_dma_x<OP, BM, BN, TBK, NST, MASKA, WGM, WGN, GEN, FLAT, BW_SAME>(a, st, set);
+  }
+  return launch_dma_x<OP, BM, BN, TBK, NST, MASKA, WGM, WGN, GEN, FLAT, BW_GATHER>(a, st, set);
 }
 
 template <int OP>
