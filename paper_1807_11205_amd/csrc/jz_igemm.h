@@ -36,7 +36,9 @@ inline FastDiv make_fastdiv(unsigned d) {
   return f;
 }
 __device__ __forceinline__ unsigned fd_div(unsigned n, const FastDiv& f) {
-  return f.d <= 1 ? n : (__umulhi(n, f.mult) >> f.shift);
+  // both values, then a choice: the k loops divide per tile by scalars, and a branch there stands between the products
+  const unsigned q = __umulhi(n, f.mult) >> f.shift;
+  return f.d <= 1 ? n : q;
 }
 
 struct ConvGeom {
