@@ -166,7 +166,8 @@ int jz_gemm_fc_bwd_weight_sumsq(int batch, int in_features, int out_features, co
 
 /* ---- the same four operations in single precision (Section 5.4, Table 9: the FP32 side of the paper's FP32 versus
  * mixed-precision throughput comparison) --------------------------------------------------------------------------
- * FP32 storage, FP32 products and sums (v_mfma_f32_16x16x4_f32), no rounding to FP16 anywhere: same definitions, same
+ * FP32 storage, 24-bit operands and FP32 sums (six products of bfloat16 parts a multiply-add, no further from 64 bits than the
+ * FP32 matrix instructions, which short launches take), no rounding to FP16 anywhere: same definitions, same
  * layouts (NHWC / KRSC / NPQK), same GEMM view, same conventions and status codes as the FP16 entry points above, with
  * float tensors (DEVICE, 16-byte aligned).  Split reductions leave FP32 partial sums in `ws` that are added in a fixed
  * order (deterministic); they take at most 256 MiB.  With less workspace than reported a call runs with fewer splits: forward
