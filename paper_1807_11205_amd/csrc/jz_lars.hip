@@ -88,12 +88,40 @@ struct Layout {
 
 size_t up256(size_t x) { return (x + 255) & ~size_t(255); }
 
+// The smallest of the group sizes 1, 2, 4, 8, 12, 16 ... that leaves at most LARS_MAX_GROUPS groups, for a set with no more tensors
+// than that.  The layout is worked out by every call, so the sizes are not tried one after the other: size s leaves at least
+// chunks / s groups and fewer than chunks / s + filled, and between those bounds the search halves (a set that takes groups costs one
+// or two passes over its tensors, up to ten where nearly every tensor is a group of its own; the others none).
+void choose_groups(const jz_param_set* ps, int64_t filled, Layout* L) {
+  auto size = [](int64_t i) { return i < 2 ? i + 1 : 4 * (i - 1); };             // candidate i
+  auto first_from = [](int64_t s) { return s <= 2 ? s - 1 : (s + 3) / 4 + 1; };  // the first candidate of at least s >= 1
+  auto groups = [&](int64_t s) {
+    int64_t n = 0;
+    for (int64_t t = 0; t < L->T; ++t) {
+      const unsigned nc = (unsigned)((ps->offsets[t + 1] - ps->offsets[t] + LARS_CH - 1) / LARS_CH);
+      n += (nc + (unsigned)s - 1) / (unsigned)s;
+    }
+    return n;
+  };
+  const int64_t spare = LARS_MAX_GROUPS - filled, least = (L->n_chunks + LARS_MAX_GROUPS - 1) / LARS_MAX_GROUPS;
+  int64_t enough = L->most_chunks;
+  if (spare > 0 && (L->n_chunks + spare - 1) / spare < enough) enough = (L->n_chunks + spare - 1) / spare;
+  int64_t lo = first_from(least < 1 ? 1 : least), hi = first_from(enough < 1 ? 1 : enough);
+  while (lo < hi) {
+    const int64_t mid = (lo + hi) / 2;
+    if (groups(size(mid)) <= LARS_MAX_GROUPS) hi = mid;
+    else lo = mid + 1;
+  }
+  L->group_chunks = size(hi);
+  L->n_groups = groups(L->group_chunks);
+}
+
 int make_layout(const jz_param_set* ps, Layout* L) {
   if (!ps) return JZ_ERR_NULL;
   if (ps->num_tensors < 0) return JZ_ERR_SHAPE;
   if (ps->num_tensors > 0 && (!ps->offsets || !ps->flags)) return JZ_ERR_NULL;
   L->T = ps->num_tensors;
-  int64_t chunks = 0;
+  int64_t chunks = 0, filled = 0;  // tensors that have elements
   if (L->T > 0) {
     if (ps->offsets[0] != 0) return JZ_ERR_SHAPE;
     for (int64_t t = 0; t < L->T; ++t) {
@@ -102,22 +130,14 @@ int make_layout(const jz_param_set* ps, Layout* L) {
       if (n >= (int64_t(1) << 31)) return JZ_ERR_UNSUPPORTED;
       const int64_t nc = (n + LARS_CH - 1) / LARS_CH;
       chunks += nc;
+      filled += nc > 0 ? 1 : 0;
       if (nc > L->most_chunks) L->most_chunks = nc;
     }
     L->P = ps->offsets[L->T];
   }
   if (L->T >= (int64_t(1) << 24) || chunks >= (int64_t(1) << 30)) return JZ_ERR_UNSUPPORTED;
   L->n_chunks = chunks;
-  for (L->group_chunks = 1;; L->group_chunks = L->group_chunks < 4 ? 2 * L->group_chunks : L->group_chunks + 4) {
-    int64_t groups = 0, most = 0;
-    for (int64_t t = 0; t < L->T; ++t) {
-      const int64_t nc = (ps->offsets[t + 1] - ps->offsets[t] + LARS_CH - 1) / LARS_CH;
-      groups += (nc + L->group_chunks - 1) / L->group_chunks;
-      if (nc > most) most = nc;
-    }
-    if (groups <= LARS_MAX_GROUPS && (chunks <= LARS_GROUPED_CHUNKS || most > 256 * LARS_FIN_BATCH)) L->n_groups = groups;
-    if (groups <= LARS_MAX_GROUPS || most <= L->group_chunks) break;
-  }
+  if (filled <= LARS_MAX_GROUPS && (chunks <= LARS_GROUPED_CHUNKS || L->most_chunks > 256 * LARS_FIN_BATCH)) choose_groups(ps, filled, L);
   size_t o = 0;
   L->off_header = o;        o = up256(o + 64);
   L->off_offsets = o;       o = up256(o + sizeof(int64_t) * (L->T + 1));
