@@ -9,20 +9,23 @@
 // once in 16 k steps where the FP32 instructions round once in 4.  Errors against 64 bits are a third to two thirds of those of
 // the FP32 instructions over the layers of ResNet-50 (one common set of accumulators would make them up to twice as large).
 //
-// Infinities, NaN and values that round to an infinite p0 end in a result that is not finite: a workgroup that finds one in its
-// tile computes the tile again with the FP32 instructions (f32_dma_body).  Operands below 2^-109 lose their last bits, an
-// absolute error below 2^-133.
+// Bfloat16 has FP32's exponents, so the last parts of a small value would fall below its normal range or out of it (unscaled, values
+// below 2^-110 lost bits and subnormal ones all of them).  Every value is therefore multiplied by 2^24 on its way in and the sums by
+// 2^-48: the last bit of the smallest FP32 value is then 2^-125, and no part of any value is subnormal.  It costs four vector
+// instructions a load, 1.9 % of ResNet-50's operations at N = 64 (11.24 -> 11.45 ms).  Infinities, NaN, values of 2^104 and more (an
+// infinite p0) and sums of 2^80 and more end in a result that is not finite: a workgroup that finds one in its tile computes the tile
+// again with the FP32 instructions (f32_dma_body).
 //
 // Why: the FP32 matrix instructions reach 154 TFLOP/s and leave no issue slots beside them, the bfloat16 ones 1.9 PFLOP/s, 317 for
-// six products.  Measured, FP32 instructions and parts: 3x3, 512 channels, 28x28, N = 64 1650 -> 1206 us (144 -> 197 TFLOP/s);
-// 256 channels, 14x14 135 -> 101 us; 64 channels, 56x56 132 -> 96; 1x1 512 -> 128 on 28x28 68 -> 45; ResNet-50's operations at N = 64
-// 13.94 -> 11.36 ms.
+// six products.  Measured, FP32 instructions and parts: 3x3, 512 channels, 28x28, N = 64 1650 -> 1137 us (144 -> 208 TFLOP/s);
+// 256 channels, 14x14 135 -> 96 us; 64 channels, 56x56 132 -> 94; 1x1 512 -> 128 on 28x28 68 -> 43; ResNet-50's operations at N = 64
+// 13.94 -> 11.45 ms.
 // What bounds it: issue slots, then power.  A 32x32x16 product holds the matrix pipe for 32 cycles, eight issue slots of its SIMD;
 // a loop of products with four vector instructions behind each runs at 95 % of the pipe, with four times as many behind every
-// fourth at 68 %.  Taking the parts apart is 5.5 vector instructions a value.  A wavefront that did that for its own 64 + 64
+// fourth at 68 %.  Taking the parts apart is 6.5 vector instructions a value.  A wavefront that did that for its own 64 + 64
 // operand rows needed 7.3 of them per product (14x14 layer 129 us; v_dot2_f32_bf16 for the differences: 146).  So values are taken
 // apart once per workgroup, on their way through registers into LDS, two instructions at a time between the products, and the
-// operands are read from LDS as bfloat16: 4 instructions per product for 128x128 tiles.  The pipes are then busy for 65 % of the
+// operands are read from LDS as bfloat16: 4 to 5 instructions per product for 128x128 tiles.  The pipes are then busy for 65 % of the
 // cycles, without bank conflicts, at a clock that power holds at 1.5-1.7 GHz.
 //
 // A tile's loads are requested two tiles ahead; the parts of tile i + 1 are made and written to the other of two stages between
@@ -140,14 +143,18 @@ __device__ __forceinline__ void f32_split_body(const F32Args& a, unsigned block,
   };
 
   // Taking load l of register set SET apart, in kSteps steps of two vector instructions (the products hide four behind each of
-  // them): the next eight bits of its values go to LDS as part k and, where another part follows, are taken off value by value
-  // (exact).
-  constexpr int kSteps = 11;
+  // them): its values are scaled, then the next eight bits of them go to LDS as part k and, where another part follows, are taken off
+  // value by value (exact).
+  constexpr int kScale = 2, kSteps = kScale + 11;
   u32x2 part[LPT];
   auto split_step = [&](auto set_tag, auto l_tag, auto step_tag, int st) {
-    constexpr int SET = decltype(set_tag)::value, Lx = decltype(l_tag)::value, K = decltype(step_tag)::value / 5, E = decltype(step_tag)::value % 5 - 1;
+    constexpr int SET = decltype(set_tag)::value, Lx = decltype(l_tag)::value, STEP = decltype(step_tag)::value - kScale;
+    constexpr int K = STEP / 5, E = STEP % 5 - 1;
     f32x4& v = raw[SET][Lx];
-    if constexpr (E < 0) {
+    if constexpr (STEP < 0) {
+      v[2 * (STEP + kScale)] *= 0x1p24f;
+      v[2 * (STEP + kScale) + 1] *= 0x1p24f;
+    } else if constexpr (E < 0) {
       part[Lx] = u32x2{__builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{v[0], v[1]}, bf16x2)),
                        __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{v[2], v[3]}, bf16x2))};
       *(__attribute__((address_space(3))) u32x2*)(ldsb + wr[Lx] + (st * STAGE + K * (Lx < LA ? A_PART : B_PART))) = part[Lx];
@@ -169,9 +176,9 @@ __device__ __forceinline__ void f32_split_body(const F32Args& a, unsigned block,
     __builtin_amdgcn_s_barrier();
   };
   // The parts of the next tile are written behind kWritten of the 6 TT products, the barrier that waits for them is kMeet products
-  // in: 18 and 22 of 24, with the reads of read_first behind it, and 20 and 20, with part 0 of both operands behind it: 14x14 layer
-  // of 256 channels, 196 workgroups, 97 against 103 us; the same where two workgroups share a compute unit.
-  constexpr int kWritten = TT == 1 ? 5 : 9 * TT / 2, kMeet = 11 * TT / 2;
+  // in, with the reads of read_first behind it.  20 and 22 of 24; ResNet-50's operations at N = 64 with 18 and 22 11.50 ms, 20 and 22
+  // 11.39, 21 and 22 11.43, 20 and 23 11.43.
+  constexpr int kWritten = TT == 1 ? 5 : 5 * TT, kMeet = 11 * TT / 2;
   // Tile i out of stage PAR = i & 1.
   auto tile = [&](int i, auto par_tag) {
     constexpr int PAR = decltype(par_tag)::value, NEXT = 1 - PAR;
@@ -229,7 +236,7 @@ __device__ __forceinline__ void f32_split_body(const F32Args& a, unsigned block,
     for (int y = 0; y < TN; ++y)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        acc[x][y][r] += low[x][y][r];
+        acc[x][y][r] = (acc[x][y][r] + low[x][y][r]) * 0x1p-48f;
         odd = fmaf(acc[x][y][r], 0.f, odd);
       }
   __shared__ int not_finite[4];

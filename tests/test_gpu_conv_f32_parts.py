@@ -65,6 +65,22 @@ def test_magnitudes(jz, scale):
         check_f32(run_f32(jz, op, d, a, b, shape), fn(od, a, b), fn(od, np.abs(a), np.abs(b)), "op %d" % op)
 
 
+# Operands whose third part, second part, and whole value would be too small for a bfloat16 (2^-126, subnormal down to 2^-133), the
+# other operand such that results are ordinary numbers; the last two hold the values of a subnormal operand (eight bits and one).
+@pytest.mark.parametrize("small", [2.0 ** -104, 2.0 ** -109, 2.0 ** -113, 1e-35, 2.0 ** -120, 1e-37, 2.0 ** -141, 2.0 ** -148])
+@pytest.mark.parametrize("cfg", [SHAPES[0], SHAPES[5], (24, 28, 28, 128, 128, 3, 3, 1, 1)], ids=["64", "residues", "128"])
+def test_small_operands_keep_their_bits(jz, cfg, small):
+    other = min(1.0 / small, 1e30)
+    for key, scale in ((70, (small, other)), (71, (other, small))):
+        od, x, w, dy = operands(cfg, key, scale)
+        d = jz.conv_desc(*cfg)
+        ops = calls(jz, od, x, w, dy)
+        for op in (jz.JZ_FWD, jz.JZ_BWD_DATA):
+            a, b, shape, fn, red = ops[op]
+            err, _ = check_f32(run_f32(jz, op, d, a, b, shape), fn(od, a, b), fn(od, np.abs(a), np.abs(b)), "op %d" % op)
+            assert err <= 2.0 ** -24 * (2 + 2 * (red / 16) ** 0.5), (op, scale, err)  # as in test_accuracy
+
+
 @pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan, 3.4e38, -3.4e38])
 @pytest.mark.parametrize("cfg", [SHAPES[0], SHAPES[5], (24, 28, 28, 128, 128, 3, 3, 1, 1)], ids=["64", "residues", "128"])
 def test_values_that_parts_cannot_hold(jz, cfg, value):
