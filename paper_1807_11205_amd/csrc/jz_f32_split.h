@@ -171,9 +171,12 @@ __device__ __forceinline__ void f32_split_body(const F32Args& a, unsigned block,
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[x][y][r] = low[x][y][r] = 0.0f;
 
-  auto barrier = [&] {  // this wavefront's LDS writes have landed, and everyone else's; loads stay in flight
-    lds_wait<0>();
+  // This wavefront's LDS writes have landed, and everyone else's; loads stay in flight.  Both sides of it are ordinary accesses,
+  // which the compiler may move across the barrier itself: the fences, of LDS alone, are what keeps them in place.
+  auto barrier = [&] {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
     __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
   };
   // The parts of the next tile are written behind kWritten of the 6 TT products, the barrier that waits for them is kMeet products
   // in, with the reads of read_first behind it.  20 and 22 of 24; ResNet-50's operations at N = 64 with 18 and 22 11.50 ms, 20 and 22
