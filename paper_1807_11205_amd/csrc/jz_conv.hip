@@ -1006,15 +1006,15 @@ int reduce_lanes(long long MN, int splits) {
 int run_widened(int op, const jz_conv_desc* d, const Plan& pl, const void* A, const void* B, void* D, void* ws, size_t ws_bytes,
                 void* stream, const jz::SumsqSink* sink);
 
+// The plan that a call runs in the workspace it was given, or why it is refused; what run() checks before its first launch.
 // A, B in the kernel's order: FWD (x, w), BWD_DATA (dy, w), BWD_WEIGHT (dy, x)
-// op may be JZ_BWD_WEIGHT | JZ_BESIDE
-int run(int op, const jz_conv_desc* d, const void* A, const void* B, void* D, void* ws, size_t ws_bytes, void* stream,
-        float* stats = nullptr, int stats_tiles_m = 0, const jz::SumsqSink* sink = nullptr, const jz::BnBwdOperands* bn = nullptr) {
-  Plan pl;
-  const int plan_op = op;
+// plan_op may be JZ_BWD_WEIGHT | JZ_BESIDE
+int admit(int plan_op, const jz_conv_desc* d, const void* A, const void* B, const void* D, const void* ws, size_t ws_bytes, Plan* out,
+          bool stats = false, int stats_tiles_m = 0, const jz::BnBwdOperands* bn = nullptr) {
+  Plan& pl = *out;
   int rc = make_plan(plan_op, d, &pl);
   if (rc != JZ_OK) return rc;
-  op = pl.op;
+  const int op = pl.op;
   // the caller sized the buffer of the column sums from an earlier plan: it has to be this plan (the run-time tuning table
   // may have been changed in between)
   if (stats && !(op == JZ_BWD_DATA ? plan_leaves_bwd_stats(pl) && bn != nullptr : plan_leaves_stats(pl))) return JZ_ERR_UNSUPPORTED;
@@ -1039,6 +1039,15 @@ int run(int op, const jz_conv_desc* d, const void* A, const void* B, void* D, vo
   if (pl.ws_bytes > 0 && (overlaps(ws, pl.ws_bytes, A, pl.bytesA) || overlaps(ws, pl.ws_bytes, B, pl.bytesB) ||
                           overlaps(ws, pl.ws_bytes, D, pl.bytesD)))
     return JZ_ERR_ALIAS;
+  return JZ_OK;
+}
+
+int run(int op, const jz_conv_desc* d, const void* A, const void* B, void* D, void* ws, size_t ws_bytes, void* stream,
+        float* stats = nullptr, int stats_tiles_m = 0, const jz::SumsqSink* sink = nullptr, const jz::BnBwdOperands* bn = nullptr) {
+  Plan pl;
+  int rc = admit(op, d, A, B, D, ws, ws_bytes, &pl, stats != nullptr, stats_tiles_m, bn);
+  if (rc != JZ_OK) return rc;
+  op = pl.op;
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (pl.widen) return run_widened(op, d, pl, A, B, D, ws, ws_bytes, stream, sink);
   if (pl.classes) {
@@ -1553,16 +1562,22 @@ extern "C" int jz_conv2d_bwd_weight_set(int n, const jz_conv_desc* descs, const 
   if (!descs || !x16 || !dy16 || !dw16) return JZ_ERR_NULL;
   if (n < 1 || n > JZ_SET_MAX) return JZ_ERR_SHAPE;
   if (ws && !aligned16(ws)) return JZ_ERR_ALIGN;
+  // Everything is settled before the first launch: a call that is refused has written nothing.
   Plan set[JZ_SET_MAX], own;
   const void *x[JZ_SET_MAX], *dy[JZ_SET_MAX];
   void* dw[JZ_SET_MAX];
+  struct { size_t x, dy, dw; } bytes[JZ_SET_MAX];
   int alone[JZ_SET_MAX], k = 0, m = 0;
+  size_t ws_used = 0;
   for (int i = 0; i < n; ++i) {
-    const int rc = make_plan(JZ_BWD_WEIGHT, descs + i, &own);
+    int rc = make_plan(JZ_BWD_WEIGHT, descs + i, &own);
     if (rc != JZ_OK) return rc;
     if (!x16[i] || !dy16[i] || !dw16[i]) return JZ_ERR_NULL;
     if (!aligned16(x16[i]) || !aligned16(dy16[i]) || !aligned16(dw16[i])) return JZ_ERR_ALIGN;
+    bytes[i] = {(size_t)own.bytesB, (size_t)own.bytesA, (size_t)own.bytesD};
     if (!joins_set(own)) {
+      if ((rc = admit(JZ_BWD_WEIGHT, descs + i, dy16[i], x16[i], dw16[i], ws, ws_bytes, &own)) != JZ_OK) return rc;
+      ws_used = std::max(ws_used, own.ws_bytes);
       alone[m++] = i;
       continue;
     }
@@ -1573,14 +1588,15 @@ extern "C" int jz_conv2d_bwd_weight_set(int n, const jz_conv_desc* descs, const 
   }
   SetPlan sp;
   if (k > 0) choose_set(set, k, std::min(kPartialSumLimit, ws ? ws_bytes : 0), &sp);
-  // a result overlaps no operand and no other result of the launch, nothing overlaps the partial sums
-  for (int i = 0; i < k; ++i) {
-    for (int j = 0; j < k; ++j)
-      if (overlaps(dw[i], set[i].bytesD, dy[j], set[j].bytesA) || overlaps(dw[i], set[i].bytesD, x[j], set[j].bytesB) ||
-          (i < j && overlaps(dw[i], set[i].bytesD, dw[j], set[j].bytesD)))
+  ws_used = std::max(ws_used, sp.part_bytes);
+  // a result overlaps no operand and no other result of the call, the workspace that it uses none of them
+  for (int i = 0; i < n; ++i) {
+    for (int j = 0; j < n; ++j)
+      if (overlaps(dw16[i], bytes[i].dw, dy16[j], bytes[j].dy) || overlaps(dw16[i], bytes[i].dw, x16[j], bytes[j].x) ||
+          (i < j && overlaps(dw16[i], bytes[i].dw, dw16[j], bytes[j].dw)))
         return JZ_ERR_ALIAS;
-    if (sp.part_bytes > 0 && (overlaps(ws, sp.part_bytes, dy[i], set[i].bytesA) || overlaps(ws, sp.part_bytes, x[i], set[i].bytesB) ||
-                              overlaps(ws, sp.part_bytes, dw[i], set[i].bytesD)))
+    if (ws_used > 0 && (overlaps(ws, ws_used, dy16[i], bytes[i].dy) || overlaps(ws, ws_used, x16[i], bytes[i].x) ||
+                        overlaps(ws, ws_used, dw16[i], bytes[i].dw)))
       return JZ_ERR_ALIAS;
   }
   int rc = k > 0 ? run_set(sp, x, dy, dw, ws, static_cast<hipStream_t>(hip_stream)) : JZ_OK;
