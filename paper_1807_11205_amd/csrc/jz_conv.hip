@@ -1456,7 +1456,8 @@ void choose_set(const Plan* in, int n, size_t limit, SetPlan* sp) {
     for (const auto& o : offered) ok |= v.BM == o[0] && v.BN == o[1] && v.bk == o[2] && v.waves == o[3] && v.nst == o[4];
     if (!ok) continue;
     for (int cap : caps) {
-      double lat = 0, thr = 0, longest = 0, mem = 0, part = 0;
+      double lat = 0, thr = 0, longest = 0, mem = 0;
+      size_t part_bytes = 0;
       for (int i = 0; i < n; ++i) {
         const GemmArgs& a = in[i].args;
         const int nkt = (a.Kred + v.bk - 1) / v.bk, s = (nkt - 1) / cap + 1, kps = (nkt + s - 1) / s, real = (nkt + kps - 1) / kps;
@@ -1466,9 +1467,11 @@ void choose_set(const Plan* in, int n, size_t limit, SetPlan* sp) {
         thr += blocks * (v.own[2] + v.thr[2] * loop);
         longest = std::max(longest, v.prologue[2] + v.lat[2] * loop);
         mem += 1e-6 * ((double)std::min<long long>(in[i].bytesA, 2ll * a.M * a.Kred) + (double)std::min<long long>(in[i].bytesB, 2ll * a.N * a.Kred)) + 2.0 * out;
-        if (real > 1) part += 4.0 * real * out;
+        if (real > 1) part_bytes += up256((size_t)real * a.M * a.N * sizeof(float));
       }
-      if (1e6 * part > (double)limit) continue;
+      // whole bytes, as below: the workspace that the query reports has to hold what it was reported for
+      if (part_bytes > limit) continue;
+      const double part = 1e-6 * (double)part_bytes;
       const double t_lat = std::max(longest, lat / (kUnits * v.resident) + 0.5 * longest);
       double t = cg.fixed + std::sqrt(std::sqrt(p4(t_lat) + p4(thr / kUnits) + p4(cg.byte * (mem + part))));
       if (part > 0) t += cg.reduce_launch + cg.reduce_byte * part;

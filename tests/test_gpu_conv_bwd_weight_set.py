@@ -47,6 +47,27 @@ def test_set_against_the_oracle(name):
         assert all(np.array_equal(jzt.bits(a), jzt.bits(t.cpu().numpy())) for a, t in zip(first, dw))
 
 
+# sets whose partial sums, added up in megabytes as floating-point numbers, come to more than the bytes that they are
+ROUNDED = [[(13, 7, 136, 16, 3, 1, 1), (13, 7, 288, 216, 3, 1, 1), (23, 30, 8, 232, 1, 1, 0)], [(13, 30, 296, 112, 1, 1, 0)], [(19, 30, 192, 248, 3, 1, 1)],
+           [(8, 28, 144, 112, 1, 1, 0), (15, 13, 176, 96, 3, 1, 1), (21, 7, 184, 96, 1, 1, 0), (6, 13, 184, 312, 3, 1, 1)]]
+
+
+@pytest.mark.parametrize("layers", ROUNDED + [SETS["mixed"]], ids=lambda c: str(len(c)))
+def test_the_reported_workspace_is_enough_for_the_reported_plan(layers):
+    from paper_1807_11205_amd import api as jz
+    descs = [jz.conv_desc(n, h, h, c, k, r, r, st, pad) for n, h, c, k, r, st, pad in layers]
+    gen = torch.Generator(device="cuda").manual_seed(len(layers))
+    rnd = lambda n: torch.randn(n, generator=gen, device="cuda").half()
+    x, dy = [rnd(d.N * d.H * d.W * d.C) for d in descs], [rnd(d.N * d.P * d.Q * d.K) for d in descs]
+    need, res = jz.jz_conv2d_bwd_weight_set_workspace_bytes(descs), []
+    for more in (0, 1 << 20):                                   # with fewer splits the sums have another order
+        dw = [torch.zeros(d.K * d.R * d.S * d.C, dtype=torch.float16, device="cuda") for d in descs]
+        jz.jz_conv2d_bwd_weight_set(descs, x, dy, dw, torch.zeros(need + more, dtype=torch.uint8, device="cuda"))
+        torch.cuda.synchronize()
+        res.append(torch.cat(dw).view(torch.int16))
+    assert torch.equal(*res)
+
+
 def test_argument_errors():
     from paper_1807_11205_amd import api as jz
     d = jz.conv_desc(4, 8, 8, 16, 16, 3, 3, 1, 1)
