@@ -789,9 +789,7 @@ extern "C" int jz_bn_relu_bwd(int64_t rows, int channels, const void* x16, const
   if (!jz::aligned16(x16) || !jz::aligned16(dy16) || !jz::aligned16(dx16) || !jz::aligned16(ws) || (relu && !jz::aligned16(y16)) ||
       !jz::aligned16(gamma) || !jz::aligned16(save_mean) || !jz::aligned16(save_invstd))
     return JZ_ERR_ALIGN;
-  const bool keep_mask = relu && p.mask_bytes > 0 && ws_bytes >= p.total + p.mask_bytes;
-  if (keep_mask) p.total += p.mask_bytes;
-  const size_t nb = (size_t)rows * channels * 2, nh = (size_t)channels * 2;
+  const size_t nb = (size_t)rows * channels * 2, nh = (size_t)channels * 2, nf = (size_t)channels * 4;
   if (jz::overlaps(dx16, nb, x16, nb) || jz::overlaps(dx16, nb, dy16, nb) || (relu && jz::overlaps(dx16, nb, y16, nb)) ||
       jz::overlaps(ws, p.total, x16, nb) || jz::overlaps(ws, p.total, dy16, nb) || jz::overlaps(ws, p.total, dx16, nb) ||
       (relu && jz::overlaps(ws, p.total, y16, nb)) || jz::overlaps(dgamma16, nh, dbeta16, nh) || jz::overlaps(dgamma16, nh, dx16, nb) ||
@@ -801,7 +799,16 @@ extern "C" int jz_bn_relu_bwd(int64_t rows, int channels, const void* x16, const
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   float* part = reinterpret_cast<float*>(static_cast<char*>(ws) + p.off_part);
   float* coef = reinterpret_cast<float*>(static_cast<char*>(ws) + p.off_coef);
-  unsigned* mask = keep_mask ? reinterpret_cast<unsigned*>(static_cast<char*>(ws) + p.total - p.mask_bytes) : nullptr;
+  // the mask's bits are optional: they go where the workspace has room behind what the call cannot do without, and none of its
+  // tensors lies there (a workspace that is the head of a larger piece of memory)
+  unsigned* mask = nullptr;
+  if (relu && p.mask_bytes > 0 && ws_bytes >= p.total + p.mask_bytes) {
+    char* const bits = static_cast<char*>(ws) + p.total;
+    auto there = [&](const void* t, size_t n) { return jz::overlaps(bits, p.mask_bytes, t, n); };
+    if (!there(x16, nb) && !there(y16, nb) && !there(dy16, nb) && !there(dx16, nb) && !there(gamma, nf) && !there(save_mean, nf) &&
+        !there(save_invstd, nf) && !there(dgamma16, nh) && !there(dbeta16, nh))
+      mask = reinterpret_cast<unsigned*>(bits);
+  }
   const uint4* x = static_cast<const uint4*>(x16);
   const uint4* y = static_cast<const uint4*>(y16);
   const uint4* dy = static_cast<const uint4*>(dy16);

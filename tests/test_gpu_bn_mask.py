@@ -34,6 +34,33 @@ def test_mask_words_give_the_bits_of_the_pass_over_y(jz, rows, C):  # noqa: F811
         assert np.array_equal(a, b)
 
 
+@pytest.mark.parametrize("tail", ["x", "y", "dy", "dx", "gamma", "mean", "invstd", "dg", "db"])
+def test_a_tensor_of_the_call_behind_the_workspace_it_needs(jz, tail):  # noqa: F811
+    """One piece of memory is passed as the workspace, and where the mask's bits would go lies a tensor of the call."""
+    rows, C = 4160, 256                                 # 130 slabs: a workspace of 266240 + 4096 bytes and 133120 of bits
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    rnd = lambda *s: torch.randn(*s, generator=gen, device="cuda")
+    half, zero = torch.float16, lambda dt: torch.zeros(C, device="cuda", dtype=dt)
+    t = dict(x=rnd(rows, C).half(), y=rnd(rows, C).half(), dy=rnd(rows, C).half(), dx=torch.zeros(rows, C, device="cuda", dtype=half),
+             gamma=rnd(C), mean=rnd(C), invstd=rnd(C).abs() + 0.1, dg=zero(half), db=zero(half))
+    full = jz.jz_bn_workspace_bytes(rows, C)
+    need = 266240 + 4096
+    assert full == need + 133120
+
+    def call(ws, **o):
+        a = dict(t, **o)
+        jz.jz_bn_relu_bwd(rows, C, a["x"], a["y"], a["dy"], a["gamma"], a["mean"], a["invstd"], True, a["dx"], a["dg"], a["db"], ws)
+        return [jzt.bits(a[k].cpu().numpy()) for k in ("dx", "dg", "db")]
+
+    want = call(torch.zeros(full, dtype=torch.uint8, device="cuda"))
+    n = t[tail].numel() * t[tail].element_size()
+    memory = torch.zeros(max(full, need + n), dtype=torch.uint8, device="cuda")
+    there = memory[need:need + n].view(t[tail].dtype).view(t[tail].shape)
+    there.copy_(t[tail])
+    for a, b in zip(call(memory, **{tail: there}), want):
+        assert np.array_equal(a, b)
+
+
 # sizes on either side of the limits of the shared-slab plan, channel counts that are not multiples of its 64
 @pytest.mark.parametrize("rows,C", [(8191, 256), (8192, 256), (12545, 256), (3136, 2048), (29128, 72), (2100, 1000), (16385, 136)])
 @pytest.mark.parametrize("relu", [True, False])
