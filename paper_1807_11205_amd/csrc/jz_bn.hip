@@ -257,10 +257,13 @@ __global__ __launch_bounds__(BN_THREADS) void bn_stats(BnStatsArgs a) {
   }
   if (MODE == ST_MASK && word) __builtin_nontemporal_store(held, word);
   // the rows' sums are added by all threads: each takes a channel's sum, of a part of the rows where there are fewer sums than
-  // threads (the lanes of one row adding up the others': 8.7 instead of 7.5 us for 200704 x 64)
+  // threads (the lanes of one row adding up the others': 8.7 instead of 7.5 us for 200704 x 64).  The forward sums in FP64: a slab has
+  // up to 400 rows where rows are shared by workgroups, and FP32 would make the variance of channels far from zero less exact than
+  // slabs of 32 rows do (12544 x 256, mean 10 std: relative error 5.3e-7, so 3.2e-7, with slabs of 32 rows 3.2e-7).
+  using Acc = std::conditional_t<GRAD, float, double>;
   const int ch = 8 * cpr_l, sums = 2 * ch;  // red[0] and red[1] are [rows of a pass][ch]
-  float* const r0s = &red[0][0][0];
-  float* const r1s = &red[1][0][0];
+  const float* const r0s = &red[0][0][0];
+  const float* const r1s = &red[1][0][0];
 #pragma unroll
   for (int e = 0; e < 8; e += 4) {
     *reinterpret_cast<float4*>(&red[0][tid][e]) = make_float4(s0[e], s0[e + 1], s0[e + 2], s0[e + 3]);
@@ -271,25 +274,26 @@ __global__ __launch_bounds__(BN_THREADS) void bn_stats(BnStatsArgs a) {
   if (sums >= BN_THREADS) {
     for (int i = tid; i < sums; i += BN_THREADS) {
       const float* p = i < ch ? r0s + i : r1s + (i - ch);
-      float t = 0.f;
+      Acc t = 0;
       for (int j = 0; j < rpp; ++j) t += p[j * ch];
-      out[i < ch ? i : C + i - ch] = t;
+      out[i < ch ? i : C + i - ch] = (float)t;
     }
     return;
   }
   const int parts = BN_THREADS / sums, i = tid % sums, first = tid / sums;
-  float t = 0.f;
+  Acc t = 0;
   if (first < parts) {
     const float* p = i < ch ? r0s + i : r1s + (i - ch);
     for (int j = first; j < rpp; j += parts) t += p[j * ch];
   }
   __syncthreads();
-  if (first < parts) r0s[first * sums + i] = t;
+  Acc* const part_sums = reinterpret_cast<Acc*>(&red[0][0][0]);
+  if (first < parts) part_sums[first * sums + i] = t;
   __syncthreads();
   if (tid < sums) {
-    t = 0.f;
-    for (int k = 0; k < parts; ++k) t += r0s[k * sums + tid];
-    out[tid < ch ? tid : C + tid - ch] = t;
+    t = 0;
+    for (int k = 0; k < parts; ++k) t += part_sums[k * sums + tid];
+    out[tid < ch ? tid : C + tid - ch] = (float)t;
   }
 }
 

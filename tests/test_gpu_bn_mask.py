@@ -6,6 +6,7 @@ import pytest
 import torch
 
 import jzt
+from paper_1807_11205_amd import inputs
 from test_gpu_bn import _inputs, _run, jz  # noqa: F401
 
 pytestmark = pytest.mark.gpu
@@ -66,3 +67,18 @@ def test_a_tensor_of_the_call_behind_the_workspace_it_needs(jz, tail):  # noqa: 
 @pytest.mark.parametrize("relu", [True, False])
 def test_forward_and_backward_against_the_oracle(jz, rows, C, relu):  # noqa: F811
     _run(jz, *_inputs((rows, C, 9), rows, C), 1e-5, relu)
+
+
+def test_variance_of_channels_far_from_zero(jz):  # noqa: F811
+    """Slabs of 128 rows shared by workgroups: the sums of squares are rounded to FP32 once a slab, 98 times in all, each time by
+    at most 2^-24 (root mean square 3^-0.5 of that) of 101 variances, and invstd, whose relative error is half the variance's, once.  The
+    factor allows for the spread of 256 channels."""
+    rows, C = 12544, 256
+    x = (inputs.rng_for(95, 1).standard_normal((rows, C), dtype=np.float32) + np.float32(10)).astype(np.float16)
+    X = torch.from_numpy(x).cuda()
+    one, y = torch.ones(C, device="cuda"), torch.empty_like(X)
+    mean, invstd = torch.empty_like(one), torch.empty_like(one)
+    jz.jz_bn_relu_fwd(rows, C, X, one, one, 0.0, False, y, mean, invstd, torch.zeros(jz.jz_bn_workspace_bytes(rows, C), dtype=torch.uint8, device="cuda"))
+    want = 1.0 / x.astype(np.float64).std(0)
+    err = float(np.sqrt(np.mean((invstd.cpu().numpy().astype(np.float64) / want - 1) ** 2)))
+    assert err <= 1.2 * 2.0 ** -24 / 3 ** 0.5 * ((0.5 * 101 / 98 ** 0.5) ** 2 + 1) ** 0.5, err
