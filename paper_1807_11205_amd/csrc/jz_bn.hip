@@ -257,9 +257,9 @@ __global__ __launch_bounds__(BN_THREADS) void bn_stats(BnStatsArgs a) {
   }
   if (MODE == ST_MASK && word) __builtin_nontemporal_store(held, word);
   // the rows' sums are added by all threads: each takes a channel's sum, of a part of the rows where there are fewer sums than
-  // threads (the lanes of one row adding up the others': 8.7 instead of 7.5 us for 200704 x 64).  The forward sums in FP64: a slab has
-  // up to 400 rows where rows are shared by workgroups, and FP32 would make the variance of channels far from zero less exact than
-  // slabs of 32 rows do (12544 x 256, mean 10 std: relative error 5.3e-7, so 3.2e-7, with slabs of 32 rows 3.2e-7).
+  // threads (the lanes of one row adding up the others': 8.7 instead of 7.5 us for 200704 x 64).  The forward sums in FP64: where
+  // rows are shared by workgroups a slab has four times as many, and FP32 would make the variance of channels far from zero less exact
+  // than with small slabs (12544 x 256, mean 10 std: relative error 5.3e-7, in FP64 3.2e-7; FP32 and slabs of 32 rows: 3.2e-7).
   using Acc = std::conditional_t<GRAD, float, double>;
   const int ch = 8 * cpr_l, sums = 2 * ch;  // red[0] and red[1] are [rows of a pass][ch]
   const float* const r0s = &red[0][0][0];
@@ -747,24 +747,24 @@ int launch_bwd_rest(const float* part, int slabs, float* coef, int64_t rows, int
 
 extern "C" int jz_bn_workspace_bytes(int64_t rows, int channels, size_t* bytes) {
   if (!bytes) return JZ_ERR_NULL;
-  BnPlan f, b;
-  int rc = make_bn_plan(rows, channels, true, &f);
+  BnPlan p;
+  int rc = make_bn_plan(rows, channels, false, &p);  // the forward plan fits where the backward one does
   if (rc != JZ_OK) return rc;
-  make_bn_plan(rows, channels, false, &b);
-  *bytes = f.total > b.total + b.mask_bytes ? f.total : b.total + b.mask_bytes;
+  *bytes = p.total + p.mask_bytes;
   return JZ_OK;
 }
 
 extern "C" int jz_bn_relu_fwd(int64_t rows, int channels, const void* x16, const float* gamma, const float* beta, float eps,
                               int relu, void* y16, float* save_mean, float* save_invstd, void* ws, size_t ws_bytes,
                               void* hip_stream) {
-  BnPlan p;
+  BnPlan p, b;
   int rc = make_bn_plan(rows, channels, true, &p);
-  if (rc == JZ_OK && ws_bytes < p.total) rc = make_bn_plan(rows, channels, false, &p);
   if (rc != JZ_OK) return rc;
+  make_bn_plan(rows, channels, false, &b);  // one size for both directions
+  if (p.total > b.total) p = b;             // it has no more slabs, for any size looked at
   if (!(eps >= 0.f)) return JZ_ERR_SHAPE;
   if (!x16 || !gamma || !beta || !y16 || !save_mean || !save_invstd) return JZ_ERR_NULL;
-  if (!ws || ws_bytes < p.total) return JZ_ERR_WORKSPACE;
+  if (!ws || ws_bytes < b.total) return JZ_ERR_WORKSPACE;
   if (!jz::aligned16(x16) || !jz::aligned16(y16) || !jz::aligned16(ws) || !jz::aligned16(gamma) || !jz::aligned16(beta) ||
       !jz::aligned16(save_mean) || !jz::aligned16(save_invstd))
     return JZ_ERR_ALIGN;

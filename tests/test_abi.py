@@ -235,6 +235,15 @@ def test_layer_entry_points_validate_on_the_host_before_any_launch(jzlib):
     assert be(g=D[2]) == E.JZ_ERR_ALIAS and be(dx=D[7]) == E.JZ_ERR_ALIAS and be(g=D[0]) == E.JZ_ERR_ALIAS
     assert L.jz_bn_bwd_block_end(64, 12, D[0], D[1], D[2], None, D[4], D[5], D[6], D[7], D[8], D[9], D[9] + 0x1000, D[10], n.value,
                                  None) == E.JZ_ERR_UNSUPPORTED
+    # one workspace size for both directions, also where the forward pass has a plan with fewer partial sums
+    for rows, C in ((12544, 256), (50176, 512), (64, 16)):
+        b = lambda n: L.jz_bn_relu_bwd(rows, C, D[0], D[1], D[2], D[4], D[5], D[6], 1, D[0], D[9], D[9] + 0x1000, 0x90000000, n, None)
+        fw = lambda n: L.jz_bn_relu_fwd(rows, C, D[0], D[4], D[5], f(0.0), 1, D[0], D[6], D[7], 0x90000000, n, None)
+        lo, hi = 0, 1 << 28                                # the smallest size that gets as far as the overlap of an output with x
+        while lo < hi:
+            mid = (lo + hi) // 2
+            lo, hi = (mid + 1, hi) if b(mid) == E.JZ_ERR_WORKSPACE else (lo, mid)
+        assert b(lo) == E.JZ_ERR_ALIAS and fw(lo) == E.JZ_ERR_ALIAS and fw(lo - 1) == E.JZ_ERR_WORKSPACE, (rows, C, lo)
     assert L.jz_loss_scale_init(None, f(1.0), None) == E.JZ_ERR_NULL
     assert L.jz_loss_scale_init(A, f(0.0), None) == E.JZ_ERR_SHAPE
     assert L.jz_loss_scale_init(A + 4, f(1.0), None) == E.JZ_ERR_ALIGN
