@@ -419,7 +419,8 @@ def bind_conv2d_bwd_weight_set(descs, x16, dy16, dw16, ws=None) -> BoundCall:
     py = arr(*(_dev_ptr(t, h, d.N * d.P * d.Q * d.K, "dy16") for d, t in zip(descs, dy16)))
     pw = arr(*(_dev_ptr(t, h, d.K * d.R * d.S * d.C, "dw16") for d, t in zip(descs, dw16)))
     da, (wp, wn) = _desc_array(descs), _ws(ws)
-    return BoundCall(lib().jz_conv2d_bwd_weight_set, (n, da, px, py, pw, wp, wn), "jz_conv2d_bwd_weight_set", (da, x16, dy16, dw16, ws))
+    return BoundCall(lib().jz_conv2d_bwd_weight_set, (n, da, px, py, pw, wp, wn), "jz_conv2d_bwd_weight_set",
+                     (da, *x16, *dy16, *dw16, ws))   # the tensors: the lists are the caller's, who may change them
 
 
 def jz_conv2d_bwd_weight_set(descs, x16, dy16, dw16, ws=None, stream=None):

@@ -1,8 +1,10 @@
 """jz_conv2d_bwd_weight_set refuses a call before its first launch, whichever member is at fault: those that share a launch and
 those that run alone (channel counts that are not multiples of 8, 3-channel stems).  Host only: addresses are never used."""
 import ctypes
+import weakref
 
 import pytest
+import torch
 
 from paper_1807_11205_amd import api
 
@@ -40,3 +42,24 @@ def test_workspace_over_another_member(layers):
     for i in range(len(layers)):
         for j in range(3):                                     # the stem's copy is 160 KB and more
             assert call(layers, ws=A + (3 * i + j) * STEP) == api.JZ_ERR_ALIAS
+
+
+class _Tensor:                                                 # what binding looks at
+    is_cuda, dtype = True, torch.float16
+    is_contiguous = lambda self: True
+    data_ptr = lambda self: A
+
+    def __init__(self, n):
+        self.numel = lambda: n
+
+
+def test_bound_call_keeps_the_tensors_of_lists_that_change():
+    d = api.conv_desc(*FAST)
+    x, dy, dw = ([_Tensor(n)] for n in (d.N * d.H * d.W * d.C, d.N * d.P * d.Q * d.K, d.K * d.R * d.S * d.C))
+    refs = [weakref.ref(t[0]) for t in (x, dy, dw)]
+    bound = api.bind_conv2d_bwd_weight_set([d], x, dy, dw)
+    for t in (x, dy, dw):
+        t.clear()
+    assert all(r() is not None for r in refs)                  # the call has their addresses
+    del bound
+    assert all(r() is None for r in refs)
