@@ -3,11 +3,12 @@
 //
 // An FP32 value is the sum of three bfloat16 values of eight significant bits each: p0 = a rounded to bfloat16, p1 = a - p0
 // rounded, p2 = a - p0 - p1 (both differences and the last part are exact, the parts cover the 24 bits).  Of the nine products of
-// two such sums the six of order 2^0 .. 2^-16 are added up, each exact in the FP32 accumulators; what is left out is at most
-// 2^-25 of a product, half of what rounding the product to FP32 would lose, and of either sign.  The five smaller products have
-// accumulators of their own: their sums are 2^-8 of the result, so their roundings do not count, and the large sums are rounded
-// once in 16 k steps where the FP32 instructions round once in 4.  Errors against 64 bits are a third to two thirds of those of
-// the FP32 instructions over the layers of ResNet-50 (one common set of accumulators would make them up to twice as large).
+// two such sums the six of order 2^0 .. 2^-16 are added up, each exact in the FP32 accumulators; what is left out (two products of up
+// to 2^-25 each, one of 2^-34) is at most 2^-24 of a product, what rounding the product to FP32 would lose, and of either sign.  The
+// five smaller products have accumulators of their own: their sums are 2^-8 of the result, so their roundings do not count, and the
+// large sums are rounded once in 16 k steps where the FP32 instructions round once in 4.  Errors measured against 64 bits are a third
+// to two thirds of those of the FP32 instructions over the layers of ResNet-50 (one common set of accumulators would make them up to
+// twice as large).
 //
 // Bfloat16 has FP32's exponents, so the last parts of a small value would fall below its normal range or out of it (unscaled, values
 // below 2^-110 lost bits and subnormal ones all of them).  Every value is therefore multiplied by 2^24 on its way in and the sums by

@@ -1,6 +1,6 @@
 """Batch normalization, the routes that depend on the workspace and on the tensor's size: the ReLU mask kept as bits between the
-backward passes against the pass that reads y again, and forward statistics with few, shared slabs against those of a
-workspace that holds the other plan only."""
+backward passes against the pass that reads y again, forward statistics with few, shared slabs against the oracle and in
+their accuracy."""
 import numpy as np
 import pytest
 import torch

@@ -48,9 +48,10 @@ def test_accuracy(jz, cfg):
     d = jz.conv_desc(*cfg)
     for op, (a, b, shape, fn, red) in calls(jz, od, x, w, dy).items():
         err, _ = check_f32(run_f32(jz, op, d, a, b, shape), fn(od, a, b), fn(od, np.abs(a), np.abs(b)), "op %d" % op)
-        # the products are exact to 2^-25 and the large sums rounded once in 16 steps, each time by at most 2^-24 of the sum, which
-        # grows as sqrt(k): sqrt(k / 16) 2^-24, and an ulp for adding the small sums and the rounding of the result.  The FP32 form,
-        # which short launches may take, rounds four times as often: twice that.
+        # what is left out of a product is at most 2^-24 of it, of either sign: 2^-24 of the result.  The large sums are rounded once
+        # in 16 steps, each time by at most 2^-24 of the sum, which grows as sqrt(k): sqrt(k / 16) 2^-24.  Adding the small sums rounds
+        # by half an ulp, the result by another: 2^-24 together.  The FP32 form, which short launches may take, rounds four times as
+        # often: twice the second.
         assert err <= 2.0 ** -24 * (2 + 2 * (red / 16) ** 0.5), (op, err)
 
 
