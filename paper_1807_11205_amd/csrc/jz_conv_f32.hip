@@ -28,7 +28,7 @@
 #include <algorithm>
 #include <type_traits>
 
-#include "jz_igemm.h"
+#include "jz_f32_plan.h"
 #include "jz_internal.h"
 #include "jz_plan_cache.h"
 
@@ -40,28 +40,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 constexpr int F_THREADS = 256;
 constexpr int F_BK = 16;  // reduction elements per tile
 
-struct F32Args {
-  const float* A;
-  const float* B;
-  float* D;      // [M][N], written where the reduction is not split
-  float* Dpart;  // [splits][rows][N], the rows whose reduction is split
-  int M, N, Kred;
-  int nkt, kt_per_split, splits, tiles_m, tiles_n;
-  ConvGeom g;
-  // those kernels': descriptor bounds, tile decomposition, where tap (r, s) of the launch sits among the w_taps taps
-  // of a filter (backward-data), and the scatter of strided backward-data as in GemmArgs
-  unsigned bytesA, bytesB;
-  int full_rows;  // rows of tiles whose reduction is not split (all of them: splits == 1)
-  FastDiv d_tiles_mn, d_tiles_n;  // d_tiles_mn: the tiles of the other rows
-  int w_taps, w_tap0, w_tap_r, w_tap_s;
-  int bw_same;    // backward-weight, unit stride, output grid = input grid: x is read at a constant pixel distance per tap
-  int bw_linear;  // backward-weight of a 1x1 unit-stride unpadded layer: x is a plain [Kred][IC] matrix
-  int sc_on, sc_H, sc_W, sc_sh, sc_sw, sc_oh, sc_ow, sc_fill;
-};
-
 #include "jz_lds_dma.h"
-#include "jz_f32_dma.h"
-#include "jz_f32_split.h"
 
 // Address of the gathered tensor's element for pixel `pix` of the (n, OH, OW) grid at filter tap `tap`, channel c, or
 // nullptr when the tap falls outside the image (or, backward-data, when no output pixel reads the input pixel through it).
@@ -327,22 +306,6 @@ __global__ __launch_bounds__(256) void narrow_channels_f32(const float* __restri
   }
 }
 
-struct PlanF32 {
-  int op = 0;
-  bool vec = false;
-  bool dma = false;      // a kernel of jz_f32_split.h or jz_f32_dma.h
-  bool gen = false;      // ... with per-lane tap arithmetic
-  bool parts = false;    // ... its operands taken apart for the bfloat16 matrix instructions (jz_f32_split.h)
-  bool classes = false;  // strided multi-tap backward-data: one launch per residue of the stride (class_args_f32)
-  bool widen = false;    // channels rounded up to 4 on copies: `wide` is the layer that runs
-  int BM = 128, BN = 128;
-  F32Args args{};
-  size_t ws_bytes = 0, bytesA = 0, bytesB = 0, bytesD = 0;
-  jz_conv_desc wide{};
-  size_t wide_a = 0, wide_b = 0, wide_d = 0;  // bytes of the copies (0: that operand is used where it is)
-  size_t plain_ws_bytes = 0;                  // what the same layer needs without them
-};
-
 size_t up256f(size_t x) { return (x + 255) & ~size_t(255); }
 
 void finish_geometry_f32(ConvGeom& g) {
@@ -604,57 +567,10 @@ bool make_class_plan_f32(const jz_conv_desc* d, const PlanF32& base, int ca, int
   return cached_plan(1, PlanKey{JZ_BWD_DATA, ca, cb, 0, *d}, pl, [&](PlanF32* p) { return class_args_f32(d, base, ca, cb, p) ? 1 : 0; }) != 0;
 }
 
-template <int BM, int BN, bool PARTS>
-constexpr size_t lds_bytes_f32 = PARTS ? F32Split<BM, BN>::LDS_BYTES : (size_t)FD_NST * (BM + BN) * FD_BK * 4;
-
-template <int OP, int BM, int BN, int FORM, bool PARTS>
-int launch_f32_tile(const F32Args& a, hipStream_t st) {
-  constexpr size_t smem = lds_bytes_f32<BM, BN, PARTS>;
-  static std::atomic<bool> lds_set{false};
-  if (!allow_lds(reinterpret_cast<const void*>(&f32_kernel<OP, BM, BN, FORM, PARTS>), smem, lds_set)) return JZ_ERR_LAUNCH;
-  hipLaunchKernelGGL((f32_kernel<OP, BM, BN, FORM, PARTS>), dim3((unsigned)(a.full_rows + (a.tiles_m - a.full_rows) * a.splits) * (unsigned)a.tiles_n),
-                     dim3(256), smem, st, a);
-  return jz::launch_status();
-}
-template <int BM, int BN, int FORM, bool PARTS>
-int launch_f32_set_tile(const F32Set& set, hipStream_t st) {
-  constexpr size_t smem = lds_bytes_f32<BM, BN, PARTS>;
-  static std::atomic<bool> lds_set{false};
-  if (!allow_lds(reinterpret_cast<const void*>(&f32_set_kernel<BM, BN, FORM, PARTS>), smem, lds_set)) return JZ_ERR_LAUNCH;
-  hipLaunchKernelGGL((f32_set_kernel<BM, BN, FORM, PARTS>), dim3(set.first[FD_MAX_SET]), dim3(256), smem, st, set);
-  return jz::launch_status();
-}
-
-template <int OP, int FORM, bool PARTS>
-int launch_f32_tiles(const PlanF32& pl, hipStream_t st) {
-  if (pl.BM == 128 && pl.BN == 128) return launch_f32_tile<OP, 128, 128, FORM, PARTS>(pl.args, st);
-  if (pl.BM == 128) return launch_f32_tile<OP, 128, 64, FORM, PARTS>(pl.args, st);
-  if (pl.BN == 128) return launch_f32_tile<OP, 64, 128, FORM, PARTS>(pl.args, st);
-  return launch_f32_tile<OP, 64, 64, FORM, PARTS>(pl.args, st);
-}
-template <int OP, int FORM>
-int launch_f32_form(const PlanF32& pl, hipStream_t st) {
-  return pl.parts ? launch_f32_tiles<OP, FORM, true>(pl, st) : launch_f32_tiles<OP, FORM, false>(pl, st);
-}
-template <int FORM, bool PARTS>
-int launch_f32_set(const PlanF32& pl, const F32Set& set, hipStream_t st) {
-  if (pl.BM == 128 && pl.BN == 128) return launch_f32_set_tile<128, 128, FORM, PARTS>(set, st);
-  if (pl.BM == 128) return launch_f32_set_tile<128, 64, FORM, PARTS>(set, st);
-  if (pl.BN == 128) return launch_f32_set_tile<64, 128, FORM, PARTS>(set, st);
-  return launch_f32_set_tile<64, 64, FORM, PARTS>(set, st);
-}
-
 template <int OP>
 int launch_f32(const PlanF32& pl, hipStream_t st) {
   const F32Args& a = pl.args;
-  if (pl.dma) {
-    if constexpr (OP == OP_BWD_WEIGHT) {
-      if (a.bw_linear) return launch_f32_form<OP, F32_MATRIX>(pl, st);
-      return a.bw_same ? launch_f32_form<OP, F32_SAME>(pl, st) : launch_f32_form<OP, F32_GATHER>(pl, st);
-    } else {
-      return pl.gen ? launch_f32_form<OP, F32_TAPS>(pl, st) : launch_f32_form<OP, F32_MASKS>(pl, st);
-    }
-  }
+  if (pl.dma) return OP == OP_FWD ? launch_f32_fwd(pl, st) : OP == OP_BWD_DATA ? launch_f32_bwd_data(pl, st) : launch_f32_bwd_weight(pl, st);
   const dim3 grid((unsigned)a.tiles_m * (unsigned)a.tiles_n * (unsigned)a.splits), block(F_THREADS);
   if constexpr (OP == OP_BWD_DATA)
     if (pl.vec) {  // a filter smaller than its stride
@@ -711,8 +627,7 @@ int run_f32(int op, const jz_conv_desc* d, const void* A, const void* B, void* D
         set.first[j + 1] = set.first[j];
       }
       k = 0;
-      if (pl.gen) return pl.parts ? launch_f32_set<F32_TAPS, true>(pl, set, st) : launch_f32_set<F32_TAPS, false>(pl, set, st);
-      return pl.parts ? launch_f32_set<F32_MASKS, true>(pl, set, st) : launch_f32_set<F32_MASKS, false>(pl, set, st);
+      return launch_f32_bwd_data(pl, st, &set);
     };
     const int Rm = (d->R + d->stride_h - 1) / d->stride_h, Sm = (d->S + d->stride_w - 1) / d->stride_w;
     const bool rows_first = (Rm - 1) * Sm >= Rm * (Sm - 1);

@@ -1,4 +1,4 @@
-// FP32 implicit GEMM with LDS-direct loads for channel counts that are multiples of 4 (included by jz_conv_f32.hip inside its
+// FP32 implicit GEMM with LDS-direct loads for channel counts that are multiples of 4 (included by jz_f32_kernels.h inside its
 // anonymous namespace; the table in jz_igemm.h says what A, B, m, n, k are in each operation): what a workgroup of either form loads
 // and stores (F32Tile), and the form on the FP32 matrix instructions, which short launches take (choose_tiling_f32) and tiles with
 // results that are not finite (jz_f32_split.h).
@@ -50,12 +50,6 @@ __device__ __forceinline__ float lds_read_f1(unsigned addr) {
 // the k lowest bits, k in [0, 32]
 __device__ __forceinline__ unsigned low_taps(int k) { return k >= 32 ? 0xffffffffu : (1u << k) - 1u; }
 __device__ __forceinline__ int clamp_taps(int x, int hi) { return x < 0 ? 0 : (x > hi ? hi : x); }
-
-constexpr int FD_BK = 16;   // floats per k tile: a KC row is 64 bytes
-constexpr int FD_NST = 4;   // ring stages
-
-// how an operand is gathered: x and dy per pixel in forward and backward-data, x in backward-weight
-enum { F32_MASKS = 0, F32_TAPS = 1, F32_MATRIX = 0, F32_SAME = 1, F32_GATHER = 2 };
 
 // What the workgroup with number `block` of the `blocks` that the launch `a` consists of loads, and where its results go.
 // SWZ: the places of the 16-byte chunks in LDS follow from the load (LDS-direct), so the lanes fetch them in swizzled order.

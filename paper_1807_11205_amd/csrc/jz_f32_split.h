@@ -1,4 +1,4 @@
-// FP32 implicit GEMM on the bfloat16 matrix instructions (included by jz_conv_f32.hip behind jz_f32_dma.h, whose F32Tile says what
+// FP32 implicit GEMM on the bfloat16 matrix instructions (included by jz_f32_kernels.h behind jz_f32_dma.h, whose F32Tile says what
 // a workgroup loads and stores).
 //
 // An FP32 value is the sum of three bfloat16 values of eight significant bits each: p0 = a rounded to bfloat16, p1 = a - p0
@@ -274,13 +274,6 @@ __global__ __launch_bounds__(256, PARTS ? 2 : 1) void f32_kernel(F32Args a) {
   f32_body<OP, BM, BN, FORM, PARTS>(a, blockIdx.x, gridDim.x);
 }
 
-// Several launches in one: the residues of the stride of a strided backward-data layer, each of which alone fills a part of
-// the chip (ResNet-50 v1.5 at batch 20, 3x3 512 -> 512 on 14x14: 128 workgroups each).
-constexpr int FD_MAX_SET = 4;
-struct F32Set {
-  F32Args c[FD_MAX_SET];
-  unsigned first[FD_MAX_SET + 1];  // workgroup numbers of member k: first[k] .. first[k + 1] - 1
-};
 template <int BM, int BN, int FORM, bool PARTS>
 __global__ __launch_bounds__(256, PARTS ? 2 : 1) void f32_set_kernel(F32Set s) {
   int k = 0;
