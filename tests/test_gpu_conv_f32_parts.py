@@ -55,7 +55,8 @@ def test_accuracy(jz, cfg):
         assert err <= 2.0 ** -24 * (2 + 2 * (red / 16) ** 0.5), (op, err)
 
 
-@pytest.mark.parametrize("scale", [(1e-20, 1e15), (1e25, 1e-20), (1e-30, 1.0)])
+# the last four: sums that are too large for the loop once scaled, operands that are (some, all), and sums on either side of that
+@pytest.mark.parametrize("scale", [(1e-20, 1e15), (1e25, 1e-20), (1e-30, 1.0), (1e18, 1e18), (2.0 ** 104, 1e-20), (1e-20, 2.0 ** 110), (2.0 ** 50, 2.0 ** 22)])
 def test_magnitudes(jz, scale):
     cfg = SHAPES[0]
     od, x, w, dy = operands(cfg, 50, scale)
