@@ -1443,7 +1443,8 @@ struct SetPlan {
 // One variant for all members and the most k tiles a workgroup walks through (longer reductions are split), by the cost model
 // of choose_tiling with all members' workgroups together.  `in`: the members' own plans.
 void choose_set(const Plan* in, int n, size_t limit, SetPlan* sp) {
-  // offered: what the model chooses for sets of ResNet-50's layers, 8 to 64 images of 64 to 224 pixels
+  // offered: what the model chooses for sets of ResNet-50's layers, 8 to 64 images of 64 to 224 pixels; sets of other networks are held
+  // to these (a variant is a kernel of three forms of reading x)
   static const int offered[][5] = {{128, 128, 32, 8, 4}, {64, 64, 64, 4, 4}, {64, 64, 32, 4, 4}};
   static const int caps[] = {4, 6, 8, 12, 16, 24, 32, 48, 64, 96, 128, 192, 256, 512, 1 << 30};
   const CostGlobals& cg = kCost[2];

@@ -26,8 +26,8 @@
 // fourth at 68 %.  Taking the parts apart is 6.5 vector instructions a value.  A wavefront that did that for its own 64 + 64
 // operand rows needed 7.3 of them per product (14x14 layer 129 us; v_dot2_f32_bf16 for the differences: 146).  So values are taken
 // apart once per workgroup, on their way through registers into LDS, two instructions at a time between the products, and the
-// operands are read from LDS as bfloat16: 4 to 5 instructions per product for 128x128 tiles.  The pipes are then busy for 65 % of the
-// cycles, without bank conflicts, at a clock that power holds at 1.5-1.7 GHz.
+// operands are read from LDS as bfloat16: 4 to 5 instructions per product for 128x128 tiles.  The pipes are then busy for 81 % of the
+// compute units' busy cycles, without bank conflicts, at a clock that power holds at 1.4-1.5 GHz.
 //
 // A tile's loads are requested two tiles ahead; the parts of tile i + 1 are made and written to the other of two stages between
 // the products of tile i; one barrier a tile, in the last of the six groups of products.  LDS layouts of a part ("KC", "MC" as in jz_f32_dma.h): KC rows of 16 bfloat16, 16-byte half c of row r at place
