@@ -130,10 +130,11 @@ int jz_conv2d_bwd_weight_beside(const jz_conv_desc* desc, const void* x16, const
 
 /* The weight gradients of up to JZ_SET_MAX layers, as jz_conv2d_bwd_weight for each but in one launch where their channel counts
  * are multiples of 8 (others follow one by one): together they fill the chip with few splits of their reductions or none, where
- * every one alone pays for partial sums and two launches.  x16, dy16, dw16: HOST arrays of n DEVICE pointers.  No result may
- * overlap an operand or result of any member, nor the workspace any of them; a call that is refused has launched nothing.
- * Workspace: with less than jz_conv2d_bwd_weight_set_workspace_bytes fewer reductions are split (for members that follow one by
- * one: as in jz_conv2d_bwd_weight).  The bits of a member's result depend on the set it is in (the order of its sums). */
+ * every one alone pays for partial sums and two launches.  The launch has one of three tile shapes, those that sets of ResNet-50's
+ * layers of up to 65536 output pixels want; longer layers fill the chip alone.  x16, dy16, dw16: HOST arrays of n DEVICE pointers.
+ * No result may overlap an operand or result of any member, nor the workspace any of them; a call that is refused has launched
+ * nothing.  Workspace: with less than jz_conv2d_bwd_weight_set_workspace_bytes fewer reductions are split (for members that follow
+ * one by one: as in jz_conv2d_bwd_weight).  The bits of a member's result depend on the set it is in (the order of its sums). */
 enum { JZ_SET_MAX = 11 };
 int jz_conv2d_bwd_weight_set_workspace_bytes(int n, const jz_conv_desc* descs, size_t* bytes);
 int jz_conv2d_bwd_weight_set(int n, const jz_conv_desc* descs, const void* const* x16, const void* const* dy16, void* const* dw16,
