@@ -31,7 +31,7 @@ EXPORTS = [
     "jz_add_fwd", "jz_relu_bwd", "jz_relu_bwd_sum", "jz_maxpool_fwd", "jz_maxpool_bwd", "jz_avgpool_fwd", "jz_avgpool_bwd", "jz_bias_add",
     "jz_bias_grad", "jz_softmax_xent_bwd", "jz_conv2d_bn_relu_fwd_workspace_bytes", "jz_conv2d_bn_relu_fwd",
     "jz_conv2d_bwd_data_bn_relu_bwd_workspace_bytes", "jz_conv2d_bwd_data_bn_relu_bwd", "jz_conv2d_bwd_data_block_end_bwd",
-    "jz_bn_workspace_bytes", "jz_bn_relu_fwd", "jz_bn_relu_bwd", "jz_bn_bwd_block_end",
+    "jz_bn_workspace_bytes", "jz_bn_relu_fwd", "jz_bn_relu_bwd", "jz_bn_bwd_block_end", "jz_bn_tune_wait",
     "jz_status_string", "jz_version",
 ]
 
@@ -99,6 +99,7 @@ def lib() -> ctypes.CDLL:
         L.jz_conv2d_tune_set.argtypes = [ci, dp, ci, ci, ci, ci, ci, ci]
         L.jz_conv2d_tune_use_table.argtypes = [ci]
         L.jz_conv2d_tune_clear.argtypes = []
+        L.jz_bn_tune_wait.argtypes = [ci]
         for name in ("jz_conv2d_fwd", "jz_conv2d_bwd_data", "jz_conv2d_bwd_weight"):
             getattr(L, name).argtypes = [dp, vp, vp, vp, vp, sz, vp]
         L.jz_conv2d_bwd_weight_static.argtypes = [dp, vp, vp, vp, vp]
@@ -286,6 +287,11 @@ def jz_conv2d_tune_use_table(on: bool):
 
 def jz_conv2d_tune_clear():
     _check(lib().jz_conv2d_tune_clear(), "jz_conv2d_tune_clear")
+
+
+def jz_bn_tune_wait(microseconds: int):
+    """How long a workgroup of the one-launch batch normalization waits for the others, for calls of this thread (a test's hook)."""
+    _check(lib().jz_bn_tune_wait(microseconds), "jz_bn_tune_wait")
 
 
 def jz_conv2d_fwd(desc, x16, w16, y16, ws=None, stream=None):

@@ -12,6 +12,9 @@
 //             bn_bwd_final  dbeta = sum g, dgamma = sum g x^ (FP16 copies for the optimizer's gradient buffer)
 //             bn_bwd_apply  dx = gamma invstd (g - dbeta/M - x^ dgamma/M), evaluated as a g + P x + Q per channel
 //
+// Channel counts that are multiples of 64 go through one launch a direction instead, which reads every tensor once (jz_bn_whole.h,
+// and launch_whole below for where it may run); the passes above are for the others, and with its slabs for what it may not take.
+//
 // Where there is room in the workspace the backward statistics leave the ReLU's mask as bits for the apply pass, which then
 // reads x, dy and 1/16 of y's bytes instead of y (bn_bwd_apply_masked).  Where the partial sums are few the apply pass adds them
 // up itself (*_merged).
@@ -21,7 +24,11 @@
 // (rows, C).
 #include <hip/hip_runtime.h>
 
+#include <atomic>
+#include <chrono>
+#include <initializer_list>
 #include <type_traits>
+#include <utility>
 
 #include "jz_internal.h"
 
@@ -42,7 +49,7 @@ constexpr int BN_MERGE_SLABS = 64;     // most partial sums per channel that an 
 constexpr int BN_MERGE_SLABS_WIDE = 128;
 constexpr int64_t BN_WIDE_BYTES = 4 << 20, BN_FEW_SLABS_BYTES = 64 << 20;
 constexpr int BN_FIN_C = 8;            // channels a finalize workgroup handles (32 contiguous bytes of every slab's sums);
-                                       // its 256 / 8 = 32 lanes per channel share the slabs
+constexpr int BN_FIN_LANES = BN_THREADS / BN_FIN_C;  // its 32 lanes per channel share the slabs
 
 size_t up256(size_t x) { return (x + 255) & ~size_t(255); }
 
@@ -50,10 +57,12 @@ struct BnPlan {
   int64_t rows = 0;
   int C = 0, cpr = 0;        // 16-byte chunks per row
   int csplit = 1;            // workgroups that share a slab of rows, each with cpr / csplit of the chunks (wide, short tensors)
-  int rpp = 0;               // rows one pass of a workgroup covers (BN_THREADS / (cpr / csplit); lanes beyond that idle)
+  int threads = BN_THREADS;  // of the statistics pass
+  int rpp = 0;               // rows one pass of a workgroup covers (threads / (cpr / csplit); lanes beyond that idle)
   int64_t rows_per_slab = 0; // a multiple of rpp
   int slabs = 0;
   size_t off_part = 0, off_coef = 0, total = 0;  // workspace: [slabs][2][C] float partial sums, [4][C] float coefficients
+  size_t off_flags = 0;      // between them, for bn_whole: a word a workgroup
   int mask_iters = 0;        // words of it a lane of the statistics pass has
   size_t mask_bytes = 0;     // behind them, if there is room: one bit per element, the backward pass's ReLU mask
 };
@@ -132,6 +141,10 @@ __device__ __forceinline__ uint4 pack8(const float (&f)[8]) {
   return make_uint4(w[0], w[1], w[2], w[3]);
 }
 
+// One element of dx.  Written out where kernels share a formula: left to the compiler, products and sums are contracted one way here
+// and another way there, and the bits differ.
+__device__ __forceinline__ float bn_dx(float a, float g, float p, float x, float q) { return fmaf(a, g, fmaf(p, x, q)); }
+
 // A result of the passes over large tensors goes out with the non-temporal hint: written back while the pass that makes it
 // reads out of the last-level cache and memory is idle, instead of during the next pass, which does read from memory and
 // slowed down to 3.3-4.3 TB/s beside the write-back.  ResNet-50's 53 layers forward and backward, batch 64: 3.52 -> 3.17 ms
@@ -159,9 +172,9 @@ struct BnStatsArgs {
   int64_t rows, rows_per_slab;
   int C, cpr, rpp, csplit, mask_iters;
 };
-template <int MODE>
-__global__ __launch_bounds__(BN_THREADS) void bn_stats(BnStatsArgs a) {
-  __shared__ __align__(16) float red[2][BN_THREADS][8];
+template <int MODE, int T>
+__global__ __launch_bounds__(T) void bn_stats(BnStatsArgs a) {
+  __shared__ __align__(16) float red[2][T][8];
   constexpr bool GRAD = MODE != ST_SUM, NEEDS_Y = MODE == ST_RELU || MODE == ST_MASK || MODE == ST_END;
   const int tid = threadIdx.x, cpr = a.cpr, rpp = a.rpp, C = a.C;
   const int cpr_l = cpr / a.csplit;  // chunks of a row this workgroup handles: [cfirst, cfirst + cpr_l)
@@ -180,7 +193,7 @@ __global__ __launch_bounds__(BN_THREADS) void bn_stats(BnStatsArgs a) {
     load8(a.invstd + chunk * 8, is);
   }
   unsigned held = 0, *word = nullptr;  // ST_MASK: the bits of the rows before, and where they go
-  unsigned* next_word = MODE == ST_MASK ? a.mask + (size_t)blockIdx.x * a.mask_iters * BN_THREADS + tid : nullptr;
+  unsigned* next_word = MODE == ST_MASK ? a.mask + (size_t)blockIdx.x * a.mask_iters * T + tid : nullptr;
   // U rows of a lane are requested together (the loop is bound by memory latency otherwise); rows beyond the slab add nothing
   // (x = 0 and g = 0 contribute zero to every sum)
   constexpr int U = MODE == ST_SUM ? 8 : BN_BWD_ROWS;
@@ -204,7 +217,7 @@ __global__ __launch_bounds__(BN_THREADS) void bn_stats(BnStatsArgs a) {
       // the word of the group before goes out behind this group's loads: a wait for loads behind it would wait for the store too
       if (word) __builtin_nontemporal_store(held, word);
       word = next_word;
-      next_word += BN_THREADS;
+      next_word += T;
       held = 0;
     }
 #pragma unroll
@@ -215,7 +228,7 @@ __global__ __launch_bounds__(BN_THREADS) void bn_stats(BnStatsArgs a) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
           s0[e] += xv[e];
-          s1[e] += xv[e] * xv[e];
+          s1[e] = fmaf(xv[e], xv[e], s1[e]);
         }
         continue;
       }
@@ -246,7 +259,7 @@ __global__ __launch_bounds__(BN_THREADS) void bn_stats(BnStatsArgs a) {
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         s0[e] += gv[e];
-        s1[e] += gv[e] * ((xv[e] - mu[e]) * is[e]);
+        s1[e] = fmaf(gv[e], (xv[e] - mu[e]) * is[e], s1[e]);
       }
     }
   };
@@ -271,8 +284,8 @@ __global__ __launch_bounds__(BN_THREADS) void bn_stats(BnStatsArgs a) {
   }
   __syncthreads();
   float* const out = a.part + (size_t)slab * 2 * C + cfirst * 8;
-  if (sums >= BN_THREADS) {
-    for (int i = tid; i < sums; i += BN_THREADS) {
+  if (sums >= T) {
+    for (int i = tid; i < sums; i += T) {
       const float* p = i < ch ? r0s + i : r1s + (i - ch);
       Acc t = 0;
       for (int j = 0; j < rpp; ++j) t += p[j * ch];
@@ -280,7 +293,7 @@ __global__ __launch_bounds__(BN_THREADS) void bn_stats(BnStatsArgs a) {
     }
     return;
   }
-  const int parts = BN_THREADS / sums, i = tid % sums, first = tid / sums;
+  const int parts = T / sums, i = tid % sums, first = tid / sums;
   Acc t = 0;
   if (first < parts) {
     const float* p = i < ch ? r0s + i : r1s + (i - ch);
@@ -297,11 +310,14 @@ __global__ __launch_bounds__(BN_THREADS) void bn_stats(BnStatsArgs a) {
   }
 }
 
+// lanes of a channel that have a slab to add
+__device__ __forceinline__ int bn_lanes(int slabs) { return slabs < BN_FIN_LANES ? slabs : BN_FIN_LANES; }
+
 // The two sums of channel c over all slabs, FP64: lane js of the channel's 32 lanes adds slabs js, js + 32, ... in that order,
 // then lane 0 adds the 32 lane sums in lane order (deterministic).  Returns true on the lane that holds the totals.
 __device__ __forceinline__ bool bn_slab_totals(const float* __restrict__ part, int slabs, int C, int c, double& s, double& q) {
   __shared__ double red[2][BN_THREADS];
-  constexpr int LANES = BN_THREADS / BN_FIN_C;
+  constexpr int LANES = BN_FIN_LANES;
   const int js = threadIdx.x / BN_FIN_C;
   s = 0.0;
   q = 0.0;
@@ -342,7 +358,7 @@ __device__ __forceinline__ bool bn_slab_totals(const float* __restrict__ part, i
 __device__ __forceinline__ void bn_fwd_coef(double s, double q, double inv_rows, float eps, float gamma, float beta, float* save_mean,
                                             float* save_invstd, float* coef, int pitch) {
   const double m = s * inv_rows;
-  double var = q * inv_rows - m * m;
+  double var = fma(-m, m, q * inv_rows);
   if (var < 0.0) var = 0.0;
   const double is = 1.0 / sqrt(var + (double)eps);
   const float mf = (float)m, isf = (float)is;
@@ -350,7 +366,7 @@ __device__ __forceinline__ void bn_fwd_coef(double s, double q, double inv_rows,
   if (save_invstd) *save_invstd = isf;
   const float a = gamma * isf;
   coef[0] = a;
-  coef[pitch] = beta - mf * a;
+  coef[pitch] = fmaf(-mf, a, beta);
 }
 
 __global__ __launch_bounds__(BN_THREADS) void bn_fwd_final(const float* __restrict__ part, int slabs, int C, double inv_rows,
@@ -382,7 +398,7 @@ __global__ __launch_bounds__(BN_THREADS) void bn_apply(const uint4* __restrict__
     if (RES) unpack8(res[i], rv);
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      float z = v[e] * a[e] + b[e];
+      float z = fmaf(v[e], a[e], b[e]);
       if (RES) z += rv[e];
       v[e] = (relu && !(z > 0.f)) ? 0.f : z;
     }
@@ -401,7 +417,7 @@ __device__ __forceinline__ void bn_bwd_coef(double sb, double sg, double inv_row
   const double t = a * (sg * inv_rows) * (double)invstd;
   coef[0] = (float)a;
   coef[pitch] = (float)(-t);
-  coef[2 * pitch] = (float)(t * (double)mean - a * (sb * inv_rows));
+  coef[2 * pitch] = (float)fma(t, (double)mean, -(a * (sb * inv_rows)));
 }
 
 __global__ __launch_bounds__(BN_THREADS) void bn_bwd_final(const float* __restrict__ part, int slabs, int C, double inv_rows,
@@ -435,7 +451,7 @@ __global__ __launch_bounds__(BN_THREADS) void bn_bwd_apply(const uint4* __restri
       for (int e = 0; e < 8; ++e) gv[e] = yv[e] > 0.f ? gv[e] : 0.f;
     }
 #pragma unroll
-    for (int e = 0; e < 8; ++e) out[e] = a[e] * gv[e] + (pc[e] * xv[e] + qc[e]);
+    for (int e = 0; e < 8; ++e) out[e] = bn_dx(a[e], gv[e], pc[e], xv[e], qc[e]);
     store_streaming(dx + i, pack8(out));
   }
 }
@@ -444,7 +460,8 @@ __global__ __launch_bounds__(BN_THREADS) void bn_bwd_apply(const uint4* __restri
 // a quarter of the reads less.  802816 x 64 (103 MB a tensor): statistics 56 -> 63 us for writing the words, apply pass 63 -> 52;
 // ResNet-50's 53 layers at batch 64: 920 -> 970 and 888 -> 710 us.  A byte per 16 bytes of y at its place in the tensor, which any
 // mapping could read, cost the statistics 145 us; the words with the non-temporal hint cost the apply passes 50.
-__global__ __launch_bounds__(BN_THREADS) void bn_bwd_apply_masked(const uint4* __restrict__ x, const uint4* __restrict__ dy, uint4* __restrict__ dx,
+template <int T>
+__global__ __launch_bounds__(T) void bn_bwd_apply_masked(const uint4* __restrict__ x, const uint4* __restrict__ dy, uint4* __restrict__ dx,
                                                                  const float* __restrict__ coef, const unsigned* __restrict__ mask,
                                                                  int64_t rows, int C, int cpr, int rpp, int64_t rows_per_slab, int csplit) {
   constexpr int U = BN_BWD_ROWS;
@@ -452,7 +469,7 @@ __global__ __launch_bounds__(BN_THREADS) void bn_bwd_apply_masked(const uint4* _
   const int chunk = (blockIdx.x % csplit) * cpr_l + threadIdx.x % cpr_l;
   const int64_t r0 = (int64_t)slab * rows_per_slab, r1 = r0 + rows_per_slab < rows ? r0 + rows_per_slab : rows;
   if (rsub >= rpp) return;
-  mask += (size_t)blockIdx.x * ((rows_per_slab + U * rpp - 1) / (U * rpp)) * BN_THREADS + threadIdx.x;
+  mask += (size_t)blockIdx.x * ((rows_per_slab + U * rpp - 1) / (U * rpp)) * T + threadIdx.x;
   float a[8], pc[8], qc[8];
   load8(coef + chunk * 8, a);
   load8(coef + C + chunk * 8, pc);
@@ -462,7 +479,7 @@ __global__ __launch_bounds__(BN_THREADS) void bn_bwd_apply_masked(const uint4* _
   auto fetch = [&](int64_t r) {
     if (r < r1) {
       w = *mask;
-      mask += BN_THREADS;
+      mask += T;
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -484,7 +501,7 @@ __global__ __launch_bounds__(BN_THREADS) void bn_bwd_apply_masked(const uint4* _
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         const float g = (w >> (8 * u + e)) & 1u ? gv[e] : 0.f;
-        out[e] = a[e] * g + (pc[e] * xv[e] + qc[e]);
+        out[e] = bn_dx(a[e], g, pc[e], xv[e], qc[e]);
       }
       o[u] = pack8(out);
     }
@@ -541,7 +558,58 @@ __device__ __forceinline__ bool bn_merged_totals(const float* __restrict__ part,
   return true;
 }
 
-template <int RES, int T>
+// The same in bn_slab_totals' order, which is bn_whole's: for tensors that it takes where it may run.  A thread stands for 32 / (T / 64) of
+// the channel's 32 lanes.  (For all tensors it made the 8 x 64 x 64 training step 1.6 % slower.)
+template <int T>
+__device__ __forceinline__ bool bn_merged_totals_32(const float* __restrict__ part, int slabs, int C, int first, double& s, double& q) {
+  constexpr int THREADS = T / BM_CH, OWN = BN_FIN_LANES / THREADS;
+  __shared__ double red[2][BN_FIN_LANES][BM_CH];
+  const int cl = threadIdx.x & (BM_CH - 1), c = first + cl, j = __builtin_amdgcn_readfirstlane(threadIdx.x / BM_CH);
+  double ts[OWN], tq[OWN];
+#pragma unroll
+  for (int o = 0; o < OWN; ++o) ts[o] = tq[o] = 0.0;
+  if (c < C)
+    for (int k = j; k < slabs; k += BN_FIN_LANES) {  // OWN slabs' sums requested together
+      float a[OWN], b[OWN];
+#pragma unroll
+      for (int o = 0; o < OWN; ++o) {
+        a[o] = b[o] = 0.f;
+        if (k + THREADS * o < slabs) {
+          a[o] = part[((size_t)(k + THREADS * o) * 2) * C + c];
+          b[o] = part[((size_t)(k + THREADS * o) * 2 + 1) * C + c];
+        }
+      }
+#pragma unroll
+      for (int o = 0; o < OWN; ++o) {
+        ts[o] += (double)a[o];
+        tq[o] += (double)b[o];
+      }
+    }
+#pragma unroll
+  for (int o = 0; o < OWN; ++o) {
+    red[0][j + THREADS * o][cl] = ts[o];
+    red[1][j + THREADS * o][cl] = tq[o];
+  }
+  __syncthreads();
+  if (j < 2) {  // the first 64 threads add the lanes' first sums, the next 64 their second ones
+    double t = 0.0;
+    for (int l0 = 0; l0 < bn_lanes(slabs); l0 += 8) {  // eight read together; lanes beyond the slabs hold zeros
+      double v[8];
+#pragma unroll
+      for (int l = 0; l < 8; ++l) v[l] = red[j][l0 + l][cl];
+#pragma unroll
+      for (int l = 0; l < 8; ++l) t += v[l];
+    }
+    red[j][0][cl] = t;
+  }
+  __syncthreads();
+  if (j != 0 || c >= C) return false;
+  s = red[0][0][cl];
+  q = red[1][0][cl];
+  return true;
+}
+
+template <int RES, int T, bool WHOLE = false>
 __global__ __launch_bounds__(T) void bn_apply_merged(const uint4* __restrict__ x, const uint4* __restrict__ res, uint4* __restrict__ y,
                                                              int64_t rows, int rows_per_wg, int C, const float* __restrict__ part, int slabs,
                                                              double inv_rows, float eps, int relu, const float* __restrict__ gamma,
@@ -566,7 +634,7 @@ __global__ __launch_bounds__(T) void bn_apply_merged(const uint4* __restrict__ x
   };
   fetch(r0 + rsub);
   double s, sq;
-  if (bn_merged_totals<T>(part, slabs, C, first, s, sq)) {
+  if (WHOLE ? bn_merged_totals_32<T>(part, slabs, C, first, s, sq) : bn_merged_totals<T>(part, slabs, C, first, s, sq)) {
     const int c = first + threadIdx.x;
     const bool writer = blockIdx.y == 0;
     bn_fwd_coef(s, sq, inv_rows, eps, gamma[c], beta[c], writer ? save_mean + c : nullptr, writer ? save_invstd + c : nullptr,
@@ -585,7 +653,7 @@ __global__ __launch_bounds__(T) void bn_apply_merged(const uint4* __restrict__ x
       if (RES) unpack8(e[u], rv);
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
-        float z = v[k] * a[k] + b[k];
+        float z = fmaf(v[k], a[k], b[k]);
         if (RES) z += rv[k];
         v[k] = (relu && !(z > 0.f)) ? 0.f : z;
       }
@@ -602,6 +670,7 @@ __global__ __launch_bounds__(T) void bn_apply_merged(const uint4* __restrict__ x
   }
 }
 
+template <bool WHOLE>
 __global__ __launch_bounds__(BN_THREADS) void bn_bwd_apply_merged(const uint4* __restrict__ x, const uint4* __restrict__ y,
                                                                  const uint4* __restrict__ dy, uint4* __restrict__ dx, int64_t rows,
                                                                  int rows_per_wg, int C, const float* __restrict__ part, int slabs,
@@ -628,7 +697,7 @@ __global__ __launch_bounds__(BN_THREADS) void bn_bwd_apply_merged(const uint4* _
   };
   fetch(r0 + rsub);
   double sb, sg;
-  if (bn_merged_totals<BN_THREADS>(part, slabs, C, first, sb, sg)) {
+  if (WHOLE ? bn_merged_totals_32<BN_THREADS>(part, slabs, C, first, sb, sg) : bn_merged_totals<BN_THREADS>(part, slabs, C, first, sb, sg)) {
     const int c = first + threadIdx.x;
     const bool writer = blockIdx.y == 0;
     bn_bwd_coef(sb, sg, inv_rows, gamma[c], mean[c], invstd[c], writer ? dgamma16 + c : nullptr, writer ? dbeta16 + c : nullptr,
@@ -653,7 +722,7 @@ __global__ __launch_bounds__(BN_THREADS) void bn_bwd_apply_merged(const uint4* _
         for (int k = 0; k < 8; ++k) gv[k] = yv[k] > 0.f ? gv[k] : 0.f;
       }
 #pragma unroll
-      for (int k = 0; k < 8; ++k) out[k] = a[k] * gv[k] + (pc[k] * xv[k] + qc[k]);
+      for (int k = 0; k < 8; ++k) out[k] = bn_dx(a[k], gv[k], pc[k], xv[k], qc[k]);
       o[u] = pack8(out);
     }
     fetch(r + BM_U * BM_ROWS);
@@ -663,6 +732,119 @@ __global__ __launch_bounds__(BN_THREADS) void bn_bwd_apply_merged(const uint4* _
       if (live && ru < r1) dx[(size_t)ru * cpr + chunk] = o[u];
     }
   }
+}
+
+#include "jz_bn_whole.h"
+
+// One launch for all (bn_whole): channel counts that are multiples of 64.  The plan is the statistics passes' with slabs for one workgroup
+// per compute unit, so that the launches apart leave the same bits.  room: what the call has of workspace.
+// Backward up to 128 passes of 64 rows a workgroup: beyond, most rows are read twice either way and the launches apart have more loads in
+// flight (401408 x 256, 98 passes: 252 us apart, 217 in one; 200704 x 1024, 196 passes: 497 and 529).  Forward it is never slower (802816 x 256: 226
+// and 218).
+constexpr int64_t BW_MOST_PASSES_BWD = 128;
+// launches apart, backward: large slabs are few, and the pass over y that the mask's bits save is worth a finalize launch earlier
+constexpr int BW_MERGE_SLABS_BWD = 16;
+bool make_whole_plan(int64_t rows, int C, bool forward, size_t room, BnPlan* p) {
+  if (C % BW_CH != 0) return false;
+  const int groups = C / BW_CH;
+  int64_t per = (rows + BW_WGS / groups - 1) / (BW_WGS / groups);
+  if (per < BW_ROWS) per = BW_ROWS;
+  p->rows = rows;
+  p->C = C;
+  p->cpr = C / 8;
+  p->csplit = groups;
+  p->threads = BW_THREADS;
+  p->rpp = BW_ROWS;
+  p->off_part = 0;
+  for (;; per += BW_ROWS) {  // fewer workgroups where there is no room for the sums of more
+    p->slabs = (int)((rows + per - 1) / per);
+    p->off_flags = up256((size_t)p->slabs * 2 * C * sizeof(float));
+    p->off_coef = up256(p->off_flags + (size_t)p->slabs * groups * sizeof(unsigned long long));
+    p->total = p->off_coef + up256((size_t)4 * C * sizeof(float));
+    if (p->total <= room) break;
+    if (p->slabs == 1) return false;
+  }
+  p->rows_per_slab = per;
+  p->mask_iters = (int)((per + BN_BWD_ROWS * BW_ROWS - 1) / (BN_BWD_ROWS * BW_ROWS));
+  p->mask_bytes = p->slabs > BW_MERGE_SLABS_BWD ? (size_t)p->slabs * groups * p->mask_iters * BW_THREADS * 4 : 0;
+  return per * C * 2 < (int64_t(1) << 31) && (forward || per <= BW_MOST_PASSES_BWD * BW_ROWS);
+}
+
+// the sums lie elsewhere in the workspace than the other plan's: a tensor that this one leaves alone and that one does not keeps the call where it was
+bool clear_of(const void* ws, size_t n, std::initializer_list<std::pair<const void*, size_t>> tensors) {
+  for (const auto& t : tensors)
+    if (jz::overlaps(ws, n, t.first, t.second)) return false;
+  return true;
+}
+
+thread_local int t_bn_wait_us = 100;
+// 62 bits of a counter that starts where the clock stood, mixed: no launch of this process has had them, and sums that an earlier call left in
+// the workspace do not look like them
+unsigned long long bw_tag() {
+  static std::atomic<unsigned long long> launches{(unsigned long long)std::chrono::steady_clock::now().time_since_epoch().count()};
+  unsigned long long z = 0x9e3779b97f4a7c15ull * launches.fetch_add(1, std::memory_order_relaxed);
+  z = (z ^ (z >> 30)) * 0xbf58476d1ce4e5b9ull;
+  z = (z ^ (z >> 27)) * 0x94d049bb133111ebull;
+  return (z ^ (z >> 31)) & ~3ull;
+}
+
+// Whether a call on this stream may take bn_whole: it wants the chip to itself, and several of them from different streams would
+// get in each other's way (four streams with 200704 x 64 each: 100 us a call instead of 21).  So one stream a device has it; another one
+// gets it after 64 calls without one of the first.  Never while the stream is captured.
+bool bw_has_chip(hipStream_t st) {
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &capture) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  int dev = 0, cus = 0;
+  if (capture != hipStreamCaptureStatusNone || hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return false;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < BW_WGS) return false;
+  struct Owner {
+    std::atomic<uintptr_t> stream{1};  // no stream's handle
+    std::atomic<int> others{64};
+  };
+  static Owner owners[64];
+  Owner& o = owners[dev];
+  const uintptr_t me = reinterpret_cast<uintptr_t>(st);
+  if (o.stream.load(std::memory_order_relaxed) != me) {
+    if (o.others.fetch_add(1, std::memory_order_relaxed) < 64) return false;
+    o.stream.store(me, std::memory_order_relaxed);
+  }
+  o.others.store(0, std::memory_order_relaxed);
+  return true;
+}
+
+template <int MODE>
+int launch_whole(const BnPlan& p, BnWholeArgs a, void* ws, hipStream_t st) {
+  a.rows = p.rows;
+  a.C = p.C;
+  a.groups = p.csplit;
+  a.wgs = p.slabs;
+  a.rows_per_wg = (int)p.rows_per_slab;
+  a.part = reinterpret_cast<float*>(static_cast<char*>(ws) + p.off_part);
+  a.flags = reinterpret_cast<unsigned long long*>(static_cast<char*>(ws) + p.off_flags);
+  a.tag = bw_tag();
+  a.wait_ticks = (long long)t_bn_wait_us * 100;
+  a.inv_rows = 1.0 / (double)p.rows;
+  const int passes = (int)((p.rows_per_slab + BW_ROWS - 1) / BW_ROWS);
+  auto go = [&](auto k_tag, auto l_tag, auto m_tag) {
+    constexpr int K = decltype(k_tag)::value, KL = decltype(l_tag)::value, MASKS = decltype(m_tag)::value;
+    constexpr size_t lds = ((size_t)KL * (MODE == BW_FWD ? 1 : 2) * 16 + MASKS) * BW_THREADS;
+    static std::atomic<bool> lds_set{false};
+    if (lds > 0 && !jz::allow_lds(reinterpret_cast<const void*>(bn_whole<MODE, K, KL, MASKS>), lds, lds_set)) return (int)JZ_ERR_LAUNCH;
+    hipLaunchKernelGGL((bn_whole<MODE, K, KL, MASKS>), dim3((unsigned)(p.slabs * p.csplit)), dim3(BW_THREADS), lds, st, a);
+    return jz::launch_status();
+  };
+  // the smallest kernel that keeps all passes, else the one that keeps the most: in registers as many as do not spill, then LDS (forward
+  // LDS did not pay: 44 + 14 passes 41.7 us at 200704 x 256, 46 alone 39.3)
+#define JZ_BW(K, KL, MASKS) go(std::integral_constant<int, K>{}, std::integral_constant<int, KL>{}, std::integral_constant<int, MASKS>{})
+  if (passes <= 4) return JZ_BW(4, 0, 0);
+  if (passes <= 8) return JZ_BW(8, 0, 0);
+  if constexpr (MODE == BW_FWD) return passes <= 16 ? JZ_BW(16, 0, 0) : passes <= 32 ? JZ_BW(32, 0, 0) : JZ_BW(44, 0, 0);
+  else if constexpr (MODE == BW_RELU) return passes <= 14 ? JZ_BW(14, 0, 0) : passes <= 25 ? JZ_BW(18, 7, 0) : JZ_BW(18, 6, 56);
+  else return passes <= 12 ? JZ_BW(8, 4, 0) : JZ_BW(10, 6, 0);
+#undef JZ_BW
 }
 
 // grid of a merged apply pass: about `wgs` workgroups, at least one pass of `pass` rows each
@@ -685,13 +867,15 @@ int launch_stats(const BnPlan& p, float* part, BnStatsArgs a, hipStream_t st) {
   a.part = part;
   a.rows = p.rows; a.rows_per_slab = p.rows_per_slab;
   a.C = p.C; a.cpr = p.cpr; a.rpp = p.rpp; a.csplit = p.csplit; a.mask_iters = p.mask_iters;
-  hipLaunchKernelGGL(bn_stats<MODE>, dim3((unsigned)(p.slabs * p.csplit)), dim3(BN_THREADS), 0, st, a);
+  const dim3 grid((unsigned)(p.slabs * p.csplit));
+  if (p.threads == BN_THREADS) hipLaunchKernelGGL((bn_stats<MODE, BN_THREADS>), grid, dim3(BN_THREADS), 0, st, a);
+  else hipLaunchKernelGGL((bn_stats<MODE, BW_THREADS>), grid, dim3(BW_THREADS), 0, st, a);
   return jz::launch_status();
 }
 
 // what follows the partial sums of the forward pass: totals, saved statistics, y = [relu](a x + b [+ res])
 int launch_fwd_rest(const float* part, int slabs, float* coef, int64_t rows, int C, float eps, int relu, const float* gamma, const float* beta,
-                    const uint4* x, const uint4* res, uint4* y, float* save_mean, float* save_invstd, hipStream_t st) {
+                    const uint4* x, const uint4* res, uint4* y, float* save_mean, float* save_invstd, hipStream_t st, bool whole = false) {
   const double inv_rows = 1.0 / (double)rows;
   auto merged = [&](auto kernel, int threads, int wgs) {
     int per;
@@ -702,7 +886,8 @@ int launch_fwd_rest(const float* part, int slabs, float* coef, int64_t rows, int
   };
   const int64_t nb = rows * C * 2;
   if (slabs <= BN_MERGE_SLABS_WIDE && nb >= BN_WIDE_BYTES && nb <= BN_FEW_SLABS_BYTES)
-    return res ? merged(bn_apply_merged<1, 512>, 512, 512) : merged(bn_apply_merged<0, 512>, 512, 512);
+    return whole ? merged(bn_apply_merged<0, 512, true>, 512, 512) : res ? merged(bn_apply_merged<1, 512>, 512, 512) : merged(bn_apply_merged<0, 512>, 512, 512);
+  if (slabs <= BN_MERGE_SLABS && whole) return merged(bn_apply_merged<0, BN_THREADS, true>, BN_THREADS, 2048);
   if (slabs <= BN_MERGE_SLABS) return res ? merged(bn_apply_merged<1, BN_THREADS>, BN_THREADS, 2048) : merged(bn_apply_merged<0, BN_THREADS>, BN_THREADS, 2048);
   hipLaunchKernelGGL(bn_fwd_final, dim3((unsigned)((C + BN_FIN_C - 1) / BN_FIN_C)), dim3(BN_THREADS), 0, st, part, slabs, C, inv_rows, eps, gamma,
                      beta, save_mean, save_invstd, coef);
@@ -723,11 +908,12 @@ int launch_bwd_rest(const float* part, int slabs, float* coef, int64_t rows, int
   const double inv_rows = 1.0 / (double)rows;
   unsigned short* dg = static_cast<unsigned short*>(dgamma16);
   unsigned short* db = static_cast<unsigned short*>(dbeta16);
-  if (slabs <= BN_MERGE_SLABS) {
+  const bool whole = p && p->threads == BW_THREADS;
+  if (slabs <= (whole ? BW_MERGE_SLABS_BWD : BN_MERGE_SLABS)) {
     int per;
     const dim3 grid = merged_grid(rows, C, BM_ROWS, 2048, &per);
-    hipLaunchKernelGGL(bn_bwd_apply_merged, grid, dim3(BN_THREADS), 0, st, x, y, dy, dx, rows, per, C, part, slabs, inv_rows, relu, gamma, mean,
-                       invstd, dg, db);
+    auto kernel = whole ? bn_bwd_apply_merged<true> : bn_bwd_apply_merged<false>;
+    hipLaunchKernelGGL(kernel, grid, dim3(BN_THREADS), 0, st, x, y, dy, dx, rows, per, C, part, slabs, inv_rows, relu, gamma, mean, invstd, dg, db);
     return jz::launch_status();
   }
   hipLaunchKernelGGL(bn_bwd_final, dim3((unsigned)((C + BN_FIN_C - 1) / BN_FIN_C)), dim3(BN_THREADS), 0, st, part, slabs, C, inv_rows, gamma, mean,
@@ -735,15 +921,25 @@ int launch_bwd_rest(const float* part, int slabs, float* coef, int64_t rows, int
   int rc = jz::launch_status();
   if (rc != JZ_OK) return rc;
   const int64_t n_chunks = rows * (C / 8);
-  if (mask)
-    hipLaunchKernelGGL(bn_bwd_apply_masked, dim3((unsigned)(p->slabs * p->csplit)), dim3(BN_THREADS), 0, st, x, dy, dx, coef, mask, rows, C, p->cpr,
-                       p->rpp, p->rows_per_slab, p->csplit);
+  const dim3 grid(mask ? (unsigned)(p->slabs * p->csplit) : apply_grid(n_chunks));
+  if (mask && p->threads == BN_THREADS)
+    hipLaunchKernelGGL(bn_bwd_apply_masked<BN_THREADS>, grid, dim3(BN_THREADS), 0, st, x, dy, dx, coef, mask, rows, C, p->cpr, p->rpp, p->rows_per_slab,
+                       p->csplit);
+  else if (mask)
+    hipLaunchKernelGGL(bn_bwd_apply_masked<BW_THREADS>, grid, dim3(BW_THREADS), 0, st, x, dy, dx, coef, mask, rows, C, p->cpr, p->rpp, p->rows_per_slab,
+                       p->csplit);
   else
-    hipLaunchKernelGGL(bn_bwd_apply, dim3(apply_grid(n_chunks)), dim3(BN_THREADS), 0, st, x, y, dy, dx, coef, n_chunks, C, C / 8, relu);
+    hipLaunchKernelGGL(bn_bwd_apply, grid, dim3(BN_THREADS), 0, st, x, y, dy, dx, coef, n_chunks, C, C / 8, relu);
   return jz::launch_status();
 }
 
 }  // namespace
+
+extern "C" int jz_bn_tune_wait(int microseconds) {
+  if (microseconds < 0 || microseconds > 1000000) return JZ_ERR_SHAPE;
+  t_bn_wait_us = microseconds;
+  return JZ_OK;
+}
 
 extern "C" int jz_bn_workspace_bytes(int64_t rows, int channels, size_t* bytes) {
   if (!bytes) return JZ_ERR_NULL;
@@ -773,13 +969,22 @@ extern "C" int jz_bn_relu_fwd(int64_t rows, int channels, const void* x16, const
       jz::overlaps(save_mean, nc, x16, nb) || jz::overlaps(save_invstd, nc, x16, nb) || jz::overlaps(save_mean, nc, save_invstd, nc) ||
       jz::overlaps(save_mean, nc, y16, nb) || jz::overlaps(save_invstd, nc, y16, nb))
     return JZ_ERR_ALIAS;
+  BnPlan wp;
+  const bool whole = make_whole_plan(rows, channels, true, b.total, &wp) &&
+                     clear_of(ws, wp.total, {{x16, nb}, {y16, nb}, {gamma, nc}, {beta, nc}, {save_mean, nc}, {save_invstd, nc}});
+  if (whole) p = wp;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   float* part = reinterpret_cast<float*>(static_cast<char*>(ws) + p.off_part);
   float* coef = reinterpret_cast<float*>(static_cast<char*>(ws) + p.off_coef);
   const uint4* x = static_cast<const uint4*>(x16);
+  BnWholeArgs w;
+  w.x = x; w.out = static_cast<uint4*>(y16);
+  w.gamma = gamma; w.beta = beta; w.save_mean = save_mean; w.save_invstd = save_invstd;
+  w.eps = eps; w.relu = relu ? 1 : 0;
+  if (whole && bw_has_chip(st)) return launch_whole<BW_FWD>(p, w, ws, st);
   if ((rc = launch_stats<ST_SUM>(p, part, {.x = x}, st)) != JZ_OK) return rc;
   return launch_fwd_rest(part, p.slabs, coef, rows, channels, eps, relu ? 1 : 0, gamma, beta, x, nullptr, static_cast<uint4*>(y16), save_mean,
-                         save_invstd, st);
+                         save_invstd, st, whole);
 }
 
 extern "C" int jz_bn_relu_bwd(int64_t rows, int channels, const void* x16, const void* y16, const void* dy16,
@@ -800,6 +1005,10 @@ extern "C" int jz_bn_relu_bwd(int64_t rows, int channels, const void* x16, const
       jz::overlaps(dbeta16, nh, dx16, nb) || jz::overlaps(dgamma16, nh, x16, nb) || jz::overlaps(dbeta16, nh, x16, nb) ||
       jz::overlaps(dgamma16, nh, dy16, nb) || jz::overlaps(dbeta16, nh, dy16, nb))
     return JZ_ERR_ALIAS;
+  BnPlan wp;  // its tensors are clear of the workspace (checked above)
+  const bool whole = make_whole_plan(rows, channels, false, p.total, &wp) &&
+                     clear_of(ws, wp.total, {{gamma, nf}, {save_mean, nf}, {save_invstd, nf}, {dgamma16, nh}, {dbeta16, nh}});
+  if (whole) p = wp;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   float* part = reinterpret_cast<float*>(static_cast<char*>(ws) + p.off_part);
   float* coef = reinterpret_cast<float*>(static_cast<char*>(ws) + p.off_coef);
@@ -816,6 +1025,11 @@ extern "C" int jz_bn_relu_bwd(int64_t rows, int channels, const void* x16, const
   const uint4* x = static_cast<const uint4*>(x16);
   const uint4* y = static_cast<const uint4*>(y16);
   const uint4* dy = static_cast<const uint4*>(dy16);
+  BnWholeArgs w;
+  w.x = x; w.y = y; w.dy = dy; w.out = static_cast<uint4*>(dx16);
+  w.gamma = gamma; w.mean = save_mean; w.invstd = save_invstd;
+  w.dgamma = static_cast<unsigned short*>(dgamma16); w.dbeta = static_cast<unsigned short*>(dbeta16);
+  if (whole && bw_has_chip(st)) return relu ? launch_whole<BW_RELU>(p, w, ws, st) : launch_whole<BW_GRAD>(p, w, ws, st);
   const BnStatsArgs in{.x = x, .y = y, .dy = dy, .mask = mask, .mean = save_mean, .invstd = save_invstd};
   rc = !relu ? launch_stats<ST_GRAD>(p, part, in, st) : mask ? launch_stats<ST_MASK>(p, part, in, st) : launch_stats<ST_RELU>(p, part, in, st);
   if (rc != JZ_OK) return rc;
@@ -845,16 +1059,27 @@ extern "C" int jz_bn_bwd_block_end(int64_t rows, int channels, const void* x16, 
   if (jz::overlaps(g16, nb, dx16, nb) || jz::overlaps(dgamma16, nh, dbeta16, nh)) return JZ_ERR_ALIAS;
   for (const void* i : ins)
     if (jz::overlaps(i, nb, ws, p.total) || jz::overlaps(i, nb, dgamma16, nh) || jz::overlaps(i, nb, dbeta16, nh)) return JZ_ERR_ALIAS;
+  const size_t nf = (size_t)channels * 4;
+  BnPlan wp;
+  const bool whole = make_whole_plan(rows, channels, false, p.total, &wp) &&
+                     clear_of(ws, wp.total, {{gamma, nf}, {save_mean, nf}, {save_invstd, nf}, {dgamma16, nh}, {dbeta16, nh}});
+  if (whole) p = wp;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   float* part = reinterpret_cast<float*>(static_cast<char*>(ws) + p.off_part);
   float* coef = reinterpret_cast<float*>(static_cast<char*>(ws) + p.off_coef);
   const uint4* x = static_cast<const uint4*>(x16);
+  BnWholeArgs w;
+  w.x = x; w.y = static_cast<const uint4*>(y_out16); w.dy = static_cast<const uint4*>(dya16); w.dy2 = static_cast<const uint4*>(dyb16);
+  w.g_out = static_cast<uint4*>(g16); w.out = static_cast<uint4*>(dx16);
+  w.gamma = gamma; w.mean = save_mean; w.invstd = save_invstd;
+  w.dgamma = static_cast<unsigned short*>(dgamma16); w.dbeta = static_cast<unsigned short*>(dbeta16);
+  if (whole && bw_has_chip(st)) return launch_whole<BW_END>(p, w, ws, st);
   rc = launch_stats<ST_END>(p, part, {.x = x, .y = static_cast<const uint4*>(y_out16), .dy = static_cast<const uint4*>(dya16),
                                       .dy2 = static_cast<const uint4*>(dyb16), .g_out = static_cast<uint4*>(g16), .mean = save_mean,
                                       .invstd = save_invstd}, st);
   if (rc != JZ_OK) return rc;
   return launch_bwd_rest(part, p.slabs, coef, rows, channels, 0, gamma, save_mean, save_invstd, x, nullptr, static_cast<const uint4*>(g16),
-                         static_cast<uint4*>(dx16), dgamma16, dbeta16, st);
+                         static_cast<uint4*>(dx16), dgamma16, dbeta16, st, nullptr, &p);
 }
 
 // ---- convolution + batch normalization (+ ReLU), forward, with the statistics taken in the convolution's epilogue ----
