@@ -34,6 +34,8 @@
 
 namespace {
 
+#include "jz_bn_math.h"
+
 constexpr int BN_THREADS = 256;
 constexpr int BN_BWD_ROWS = 4;         // rows of a lane whose loads are in flight together in the backward passes
 constexpr int BN_MAX_C = 2048;       // C / 8 lanes of a row have to fit one workgroup
@@ -140,10 +142,6 @@ __device__ __forceinline__ uint4 pack8(const float (&f)[8]) {
   }
   return make_uint4(w[0], w[1], w[2], w[3]);
 }
-
-// One element of dx.  Written out where kernels share a formula: left to the compiler, products and sums are contracted one way here
-// and another way there, and the bits differ.
-__device__ __forceinline__ float bn_dx(float a, float g, float p, float x, float q) { return fmaf(a, g, fmaf(p, x, q)); }
 
 // A result of the passes over large tensors goes out with the non-temporal hint: written back while the pass that makes it
 // reads out of the last-level cache and memory is idle, instead of during the next pass, which does read from memory and
@@ -354,21 +352,6 @@ __device__ __forceinline__ bool bn_slab_totals(const float* __restrict__ part, i
   return true;
 }
 
-// mean and 1 / sqrt(var + eps) of one channel (written where the pointers are not null) and y = a x + b
-__device__ __forceinline__ void bn_fwd_coef(double s, double q, double inv_rows, float eps, float gamma, float beta, float* save_mean,
-                                            float* save_invstd, float* coef, int pitch) {
-  const double m = s * inv_rows;
-  double var = fma(-m, m, q * inv_rows);
-  if (var < 0.0) var = 0.0;
-  const double is = 1.0 / sqrt(var + (double)eps);
-  const float mf = (float)m, isf = (float)is;
-  if (save_mean) *save_mean = mf;
-  if (save_invstd) *save_invstd = isf;
-  const float a = gamma * isf;
-  coef[0] = a;
-  coef[pitch] = fmaf(-mf, a, beta);
-}
-
 __global__ __launch_bounds__(BN_THREADS) void bn_fwd_final(const float* __restrict__ part, int slabs, int C, double inv_rows,
                                                           float eps, const float* __restrict__ gamma,
                                                           const float* __restrict__ beta, float* __restrict__ save_mean,
@@ -404,20 +387,6 @@ __global__ __launch_bounds__(BN_THREADS) void bn_apply(const uint4* __restrict__
     }
     store_streaming(y + i, pack8(v));
   }
-}
-
-// the parameter gradients of one channel (written where the pointers are not null) and its dx = a (g - dbeta/M - x^ dgamma/M),
-// x^ = (x - mean) invstd, as a g + P x + Q
-__device__ __forceinline__ void bn_bwd_coef(double sb, double sg, double inv_rows, float gamma, float mean, float invstd,
-                                            unsigned short* dgamma16, unsigned short* dbeta16, float* coef, int pitch) {
-  _Float16 hg = (_Float16)(float)sg, hb = (_Float16)(float)sb;
-  if (dgamma16) __builtin_memcpy(dgamma16, &hg, 2);
-  if (dbeta16) __builtin_memcpy(dbeta16, &hb, 2);
-  const double a = (double)gamma * (double)invstd;
-  const double t = a * (sg * inv_rows) * (double)invstd;
-  coef[0] = (float)a;
-  coef[pitch] = (float)(-t);
-  coef[2 * pitch] = (float)fma(t, (double)mean, -(a * (sb * inv_rows)));
 }
 
 __global__ __launch_bounds__(BN_THREADS) void bn_bwd_final(const float* __restrict__ part, int slabs, int C, double inv_rows,
@@ -1148,8 +1117,10 @@ extern "C" int jz_conv2d_bn_relu_fwd(const jz_conv_desc* desc, const void* x16, 
   float* part = reinterpret_cast<float*>(bws + p.bn.off_part);
   float* coef = reinterpret_cast<float*>(bws + p.bn.off_coef);
   // the convolution (its own checks cover x, w, conv_out and its part of the workspace)
-  rc = jz::conv_fwd_run(desc, x16, w16, conv_out16, ws, p.conv_ws, p.tiles_m > 0 ? part : nullptr, p.tiles_m, hip_stream);
-  if (rc != JZ_OK) return rc;
+  jz::BnTail tail{.gamma = gamma, .beta = beta, .eps = eps, .relu = relu ? 1 : 0, .residual16 = residual16, .y16 = y16, .save_mean = save_mean,
+                  .save_invstd = save_invstd};
+  rc = jz::conv_fwd_run(desc, x16, w16, conv_out16, ws, p.conv_ws, p.tiles_m > 0 ? part : nullptr, p.tiles_m, &tail, hip_stream);
+  if (rc != JZ_OK || tail.done) return rc;
   const uint4* c = static_cast<const uint4*>(conv_out16);
   int slabs = p.tiles_m;
   if (slabs == 0) {  // this convolution kernel cannot leave the sums: one more pass over its output
@@ -1239,8 +1210,9 @@ static int conv_bwd_data_bn_bwd(const jz_conv_desc* desc, const void* dy16, cons
   jz::BnBwdOperands bn{bn_x16, bn_y16, save_mean, save_invstd};
   bn.block_end = block_end;
   bn.add16 = add16;
-  rc = jz::conv_bwd_data_run(desc, dy16, w16, out16, ws, p.conv_ws, p.tiles_m > 0 ? part : nullptr, p.tiles_m, &bn, hip_stream);
-  if (rc != JZ_OK) return rc;
+  jz::BnTail tail{.gamma = gamma, .dx16 = bn_dx16, .dgamma16 = dgamma16, .dbeta16 = dbeta16};
+  rc = jz::conv_bwd_data_run(desc, dy16, w16, out16, ws, p.conv_ws, p.tiles_m > 0 ? part : nullptr, p.tiles_m, &bn, &tail, hip_stream);
+  if (rc != JZ_OK || tail.done) return rc;
   const uint4* x = static_cast<const uint4*>(bn_x16);
   const uint4* y = static_cast<const uint4*>(bn_y16);
   const uint4* dz = static_cast<const uint4*>(out16);

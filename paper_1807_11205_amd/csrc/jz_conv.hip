@@ -25,6 +25,8 @@ using namespace jz;
 
 constexpr int BK = 64;  // k tile depth of the element-wise kernel
 
+#include "jz_bn_math.h"
+
 // ---------------------------------------------------------------------------------------------
 // small-channel layers (C <= 4: the 3-channel stems of ResNet-50 and AlexNet)
 // ---------------------------------------------------------------------------------------------
@@ -353,6 +355,33 @@ __global__ __launch_bounds__(256) void splitk_reduce_sumsq(const float* __restri
 // 1.66 ms (45 launches fewer).  A workgroup owns 64 columns; a thread 4 of them (one 16-byte load per split, eight in
 // flight) in every 16th row.
 constexpr int RS_COLS = 64, RS_ROWS = 16;
+// four columns of a row: splitk_reduce's order, hence its bits: splits g, g + G, g + 2G, ... for lane g, then the lanes; eight loads in flight
+__device__ __forceinline__ float4 split_sum(const float* __restrict__ p, size_t MN, int splits, int G) {
+  float v[4] = {0.f, 0.f, 0.f, 0.f}, lane[4] = {0.f, 0.f, 0.f, 0.f};
+  for (int k = 0, g = 0; g < G;) {
+    float4 t[8];
+    int ends = 0;  // bit u: load u is its lane's last
+    int n8 = 0;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      t[u] = *reinterpret_cast<const float4*>(p + (size_t)(g < G ? k : 0) * MN);
+      if (g < G) {
+        ++n8;
+        k += G;
+        if (k >= splits) { ends |= 1 << u; k = ++g; }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (u < n8) {
+        lane[0] += t[u].x; lane[1] += t[u].y; lane[2] += t[u].z; lane[3] += t[u].w;
+        if (ends >> u & 1)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) { v[e] += lane[e]; lane[e] = 0.f; }
+      }
+  }
+  return make_float4(v[0], v[1], v[2], v[3]);
+}
 template <int MODE>
 __global__ __launch_bounds__(256) void splitk_reduce_stats(const float* __restrict__ part, unsigned short* __restrict__ out, int M, int N,
                                                            int splits, int G, int rows_per_slab, const unsigned short* __restrict__ y,
@@ -386,30 +415,8 @@ __global__ __launch_bounds__(256) void splitk_reduce_stats(const float* __restri
       cq = *reinterpret_cast<const uint2*>(c + i);
       if (MODE == 2 && add) aq = *reinterpret_cast<const uint2*>(add + i);
     }
-    float v[4] = {0.f, 0.f, 0.f, 0.f}, lane[4] = {0.f, 0.f, 0.f, 0.f};
-    // splitk_reduce's order, hence its bits: splits g, g + G, g + 2G, ... for lane g, then the lanes
-    for (int k = 0, g = 0; g < G;) {
-      float4 t[8];
-      int ends = 0;  // bit u: load u is its lane's last
-      int n8 = 0;
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        t[u] = *reinterpret_cast<const float4*>(part + (size_t)(g < G ? k : 0) * MN + i);
-        if (g < G) {
-          ++n8;
-          k += G;
-          if (k >= splits) { ends |= 1 << u; k = ++g; }
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u)
-        if (u < n8) {
-          lane[0] += t[u].x; lane[1] += t[u].y; lane[2] += t[u].z; lane[3] += t[u].w;
-          if (ends >> u & 1)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) { v[e] += lane[e]; lane[e] = 0.f; }
-        }
-    }
+    const float4 v4 = split_sum(part + i, MN, splits, G);
+    const float v[4] = {v4.x, v4.y, v4.z, v4.w};
     _Float16 h[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -436,6 +443,147 @@ __global__ __launch_bounds__(256) void splitk_reduce_stats(const float* __restri
 #pragma unroll
     for (int r = 0; r < RS_ROWS; ++r) t += src[r * RS_COLS];
     if (blockIdx.x * RS_COLS + col < (unsigned)N) stats[((size_t)blockIdx.y * 2 + kind) * N + blockIdx.x * RS_COLS + col] = t;
+  }
+}
+
+// splitk_reduce_stats and the normalization behind it in one launch, for reductions of few rows: a workgroup owns 16 columns of all
+// rows, so that their statistics need no other workgroup, and what it has summed is still in its registers when they are there.
+// MODE as above; out2 is y (MODE 0: [relu](a c + b [+ add])) or the gradient of the normalization's input.
+// What bounds it is a chain of latencies: the loads of the splits, two barriers' worth of sums, the coefficients.  5.1-5.7 us a launch where the
+// two it replaces took 3.1-3.6 and 3.7; ResNet-50's step at 8 images of 64 x 64 (35 of them) 1.383 -> 1.342 ms.  Up to 256 rows: with
+// 512 the few workgroups read too much each (8 of them 256 KB: the same step 1.371 ms).
+constexpr int RN_THREADS = 512, RN_COLS = 16, RN_LANES = RN_COLS / 4, RN_ROWS = RN_THREADS / RN_LANES, RN_PASSES = 2;
+constexpr int RN_MAX_ROWS = RN_ROWS * RN_PASSES;
+struct NormArgs {
+  const float* part;
+  unsigned short* out;
+  int M, N, splits, G;
+  const unsigned short *y, *c, *add;
+  const float *mean, *invstd;
+  const float *gamma, *beta;
+  float eps;
+  int relu;
+  double inv_rows;
+  unsigned short* out2;
+  float *save_mean, *save_invstd;
+  unsigned short *dgamma, *dbeta;
+};
+template <int MODE>
+__global__ __launch_bounds__(RN_THREADS) void splitk_reduce_norm(NormArgs a) {
+  __shared__ float red[2][RN_ROWS][RN_COLS];
+  __shared__ double parts[RN_THREADS / (2 * RN_COLS)][2 * RN_COLS];
+  __shared__ float coef[3][RN_COLS];
+  const int tid = threadIdx.x, q = tid % RN_LANES, rsub = tid / RN_LANES;
+  const int first = blockIdx.x * RN_COLS, n = first + q * 4;
+  const bool live = n < a.N;  // N is a multiple of 8
+  const size_t MN = (size_t)a.M * a.N;
+  float mu[4] = {0.f, 0.f, 0.f, 0.f}, is[4] = {0.f, 0.f, 0.f, 0.f};
+  if (MODE >= 1 && live) {
+    const float4 m4 = *reinterpret_cast<const float4*>(a.mean + n), i4 = *reinterpret_cast<const float4*>(a.invstd + n);
+    mu[0] = m4.x; mu[1] = m4.y; mu[2] = m4.z; mu[3] = m4.w;
+    is[0] = i4.x; is[1] = i4.y; is[2] = i4.z; is[3] = i4.w;
+  }
+  auto half_at = [](const uint2& v, int e) {
+    const unsigned short b = (unsigned short)((e < 2 ? v.x : v.y) >> ((e & 1) * 16));
+    _Float16 h;
+    __builtin_memcpy(&h, &b, 2);
+    return (float)h;
+  };
+  uint2 cq[RN_PASSES], aq[RN_PASSES], kept[RN_PASSES];  // kept: what is normalized, or the gradient behind the ReLU
+  float s0[4] = {0.f, 0.f, 0.f, 0.f}, s1[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int p = 0; p < RN_PASSES; ++p) {
+    const int r = p * RN_ROWS + rsub;
+    cq[p] = aq[p] = kept[p] = make_uint2(0u, 0u);
+    if (!live || r >= a.M) continue;
+    const size_t i = (size_t)r * a.N + n;
+    uint2 yq = make_uint2(0u, 0u);
+    if (MODE >= 1) {
+      yq = *reinterpret_cast<const uint2*>(a.y + i);
+      cq[p] = *reinterpret_cast<const uint2*>(a.c + i);
+    }
+    if (MODE != 1 && a.add) aq[p] = *reinterpret_cast<const uint2*>(a.add + i);
+    _Float16 h[4];
+    const float4 v = split_sum(a.part + i, MN, a.splits, a.G);
+    h[0] = (_Float16)v.x; h[1] = (_Float16)v.y; h[2] = (_Float16)v.z; h[3] = (_Float16)v.w;
+    if (MODE == 2) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        h[e] = (_Float16)((float)h[e] + half_at(aq[p], e));  // exact in FP32, rounded once
+        if (!(half_at(yq, e) > 0.f)) h[e] = (_Float16)0.f;
+      }
+    }
+    uint2 pk;
+    __builtin_memcpy(&pk, h, 8);
+    *reinterpret_cast<uint2*>(a.out + i) = pk;
+    if (MODE == 1) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (!(half_at(yq, e) > 0.f)) h[e] = (_Float16)0.f;
+      __builtin_memcpy(&pk, h, 8);
+    }
+    kept[p] = pk;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float g = (float)h[e];
+      s0[e] += g;
+      s1[e] = fmaf(g, MODE == 0 ? g : (half_at(cq[p], e) - mu[e]) * is[e], s1[e]);
+    }
+  }
+  // at most RN_PASSES rows a thread in FP32, everything else in FP64
+  *reinterpret_cast<float4*>(&red[0][rsub][q * 4]) = make_float4(s0[0], s0[1], s0[2], s0[3]);
+  *reinterpret_cast<float4*>(&red[1][rsub][q * 4]) = make_float4(s1[0], s1[1], s1[2], s1[3]);
+  __syncthreads();
+  {
+    constexpr int PARTS = RN_THREADS / (2 * RN_COLS), PER = RN_ROWS / PARTS;
+    const int i = tid % (2 * RN_COLS), j = tid / (2 * RN_COLS);
+    double t = 0.0;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) t += (double)red[i / RN_COLS][j + k * PARTS][i % RN_COLS];
+    parts[j][i] = t;
+    __syncthreads();
+    if (tid < 2 * RN_COLS) {
+      t = 0.0;
+#pragma unroll
+      for (int k = 0; k < PARTS; ++k) t += parts[k][tid];
+      parts[0][tid] = t;
+    }
+    __syncthreads();
+    if (tid < RN_COLS && first + tid < a.N) {
+      const int c = first + tid;
+      if (MODE == 0)
+        bn_fwd_coef(parts[0][tid], parts[0][RN_COLS + tid], a.inv_rows, a.eps, a.gamma[c], a.beta[c], a.save_mean + c, a.save_invstd + c, &coef[0][tid], RN_COLS);
+      else
+        bn_bwd_coef(parts[0][tid], parts[0][RN_COLS + tid], a.inv_rows, a.gamma[c], a.mean[c], a.invstd[c], a.dgamma + c, a.dbeta + c, &coef[0][tid],
+                    RN_COLS);
+    }
+    __syncthreads();
+  }
+  float ca[4], cb[4], cc[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    ca[e] = coef[0][q * 4 + e];
+    cb[e] = coef[1][q * 4 + e];
+    cc[e] = MODE == 0 ? 0.f : coef[2][q * 4 + e];
+  }
+#pragma unroll
+  for (int p = 0; p < RN_PASSES; ++p) {
+    const int r = p * RN_ROWS + rsub;
+    if (!live || r >= a.M) continue;
+    _Float16 h[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (MODE == 0) {
+        float z = fmaf(half_at(kept[p], e), ca[e], cb[e]);
+        if (a.add) z += half_at(aq[p], e);
+        h[e] = (_Float16)(a.relu && !(z > 0.f) ? 0.f : z);
+      } else {
+        h[e] = (_Float16)bn_dx(ca[e], half_at(kept[p], e), cb[e], half_at(cq[p], e), cc[e]);
+      }
+    }
+    uint2 pk;
+    __builtin_memcpy(&pk, h, 8);
+    *reinterpret_cast<uint2*>(a.out2 + (size_t)r * a.N + n) = pk;
   }
 }
 
@@ -1043,7 +1191,8 @@ int admit(int plan_op, const jz_conv_desc* d, const void* A, const void* B, cons
 }
 
 int run(int op, const jz_conv_desc* d, const void* A, const void* B, void* D, void* ws, size_t ws_bytes, void* stream,
-        float* stats = nullptr, int stats_tiles_m = 0, const jz::SumsqSink* sink = nullptr, const jz::BnBwdOperands* bn = nullptr) {
+        float* stats = nullptr, int stats_tiles_m = 0, const jz::SumsqSink* sink = nullptr, const jz::BnBwdOperands* bn = nullptr,
+        jz::BnTail* tail = nullptr) {
   Plan pl;
   int rc = admit(op, d, A, B, D, ws, ws_bytes, &pl, stats != nullptr, stats_tiles_m, bn);
   if (rc != JZ_OK) return rc;
@@ -1148,6 +1297,18 @@ int run(int op, const jz_conv_desc* d, const void* A, const void* B, void* D, vo
   else rc = launch_bwd_weight(pl, st);
   if (rc != JZ_OK) return rc;
   const int lg = reduce_lanes((long long)a.M * a.N, a.splits);
+  if (a.splits > 1 && stats && tail && a.M <= RN_MAX_ROWS) {
+    NormArgs n{a.Dpart, a.D16, a.M, a.N, a.splits, 1 << lg, a.st_y, a.st_c, op == JZ_FWD ? static_cast<const unsigned short*>(tail->residual16) : a.st_add,
+               a.st_mean, a.st_invstd, tail->gamma, tail->beta, tail->eps, tail->relu, 1.0 / (double)a.M,
+               static_cast<unsigned short*>(op == JZ_FWD ? tail->y16 : tail->dx16), tail->save_mean, tail->save_invstd,
+               static_cast<unsigned short*>(tail->dgamma16), static_cast<unsigned short*>(tail->dbeta16)};
+    const dim3 grid((unsigned)((a.N + RN_COLS - 1) / RN_COLS));
+    if (op == JZ_FWD) hipLaunchKernelGGL(splitk_reduce_norm<0>, grid, dim3(RN_THREADS), 0, st, n);
+    else if (!bn->block_end) hipLaunchKernelGGL(splitk_reduce_norm<1>, grid, dim3(RN_THREADS), 0, st, n);
+    else hipLaunchKernelGGL(splitk_reduce_norm<2>, grid, dim3(RN_THREADS), 0, st, n);
+    tail->done = true;
+    return jz::launch_status();
+  }
   if (a.splits > 1 && stats) {
     const dim3 grid((unsigned)((a.N + RS_COLS - 1) / RS_COLS), (unsigned)reduce_slabs(a));
     const int mode = op == JZ_FWD ? 0 : bn->block_end ? 2 : 1;
@@ -1262,8 +1423,8 @@ int jz::conv_fwd_stats_plan(const jz_conv_desc* d, size_t* conv_ws_bytes, int* t
   return JZ_OK;
 }
 int jz::conv_fwd_run(const jz_conv_desc* d, const void* x, const void* w, void* y, void* ws, size_t ws_bytes, float* stats,
-                     int stats_tiles_m, void* stream) {
-  return run(JZ_FWD, d, x, w, y, ws, ws_bytes, stream, stats, stats_tiles_m);
+                     int stats_tiles_m, BnTail* tail, void* stream) {
+  return run(JZ_FWD, d, x, w, y, ws, ws_bytes, stream, stats, stats_tiles_m, nullptr, nullptr, tail);
 }
 int jz::conv_bwd_data_stats_plan(const jz_conv_desc* d, size_t* conv_ws_bytes, int* tiles_m) {
   Plan pl;
@@ -1274,8 +1435,8 @@ int jz::conv_bwd_data_stats_plan(const jz_conv_desc* d, size_t* conv_ws_bytes, i
   return JZ_OK;
 }
 int jz::conv_bwd_data_run(const jz_conv_desc* d, const void* dy, const void* w, void* dx, void* ws, size_t ws_bytes, float* stats,
-                          int stats_tiles_m, const BnBwdOperands* bn, void* stream) {
-  return run(JZ_BWD_DATA, d, dy, w, dx, ws, ws_bytes, stream, stats, stats_tiles_m, nullptr, bn);
+                          int stats_tiles_m, const BnBwdOperands* bn, BnTail* tail, void* stream) {
+  return run(JZ_BWD_DATA, d, dy, w, dx, ws, ws_bytes, stream, stats, stats_tiles_m, nullptr, bn, tail);
 }
 
 extern "C" int jz_conv2d_workspace_bytes(int op, const jz_conv_desc* desc, size_t* bytes) {

@@ -22,9 +22,21 @@ inline bool overlaps(const void* a, size_t na, const void* b, size_t nb) {
 // the convolution needs and, when its kernel (or its split reduction) can leave column sums of y and y^2 over groups of
 // rows (its row tiles, or slabs of the reduction), the number of groups (else 0).  conv_fwd_run with stats != nullptr (only after a plan that said so) writes them as [tiles_m][2][K] floats; it
 // returns JZ_ERR_UNSUPPORTED, before anything is launched, if the plan no longer has stats_tiles_m row tiles.
+// BnTail: the normalization itself, for a split reduction that can do it all; `done` says that it did.
+struct BnTail {
+  const float* gamma;
+  const float* beta = nullptr;         // forward
+  float eps = 0.f;
+  int relu = 0;
+  const void* residual16 = nullptr;
+  void* y16 = nullptr;
+  float *save_mean = nullptr, *save_invstd = nullptr;
+  void *dx16 = nullptr, *dgamma16 = nullptr, *dbeta16 = nullptr;  // backward
+  bool done = false;
+};
 int conv_fwd_stats_plan(const jz_conv_desc* d, size_t* conv_ws_bytes, int* tiles_m);
 int conv_fwd_run(const jz_conv_desc* d, const void* x, const void* w, void* y, void* ws, size_t ws_bytes, float* stats,
-                 int stats_tiles_m, void* stream);
+                 int stats_tiles_m, BnTail* tail, void* stream);
 
 // Backward-data convolution for the fused "backward-data + batch-norm backward" entry point (jz_bn.hip): the layer whose
 // output (after batch normalization + ReLU) was this convolution's input.  conv_bwd_data_stats_plan: the convolution's
@@ -42,7 +54,7 @@ struct BnBwdOperands {
 };
 int conv_bwd_data_stats_plan(const jz_conv_desc* d, size_t* conv_ws_bytes, int* tiles_m);
 int conv_bwd_data_run(const jz_conv_desc* d, const void* dy, const void* w, void* dx, void* ws, size_t ws_bytes, float* stats,
-                      int stats_tiles_m, const BnBwdOperands* bn, void* stream);
+                      int stats_tiles_m, const BnBwdOperands* bn, BnTail* tail, void* stream);
 
 // Splitting a reduction is a matter of speed.  A plan's partial sums take at most kPartialSumLimit bytes, the size of the
 // last-level cache: more of them would be written to memory and read back, and lie outside what the cost models were fitted to
