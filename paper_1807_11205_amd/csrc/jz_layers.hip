@@ -107,46 +107,60 @@ struct PoolGeom {
   int N, H, W, C8, P, Q, window, stride, pad;
 };
 
+// Grids of the pooling kernels: (row of positions x 8 channels, rows, images), so that a position needs one 32-bit division; a flat index
+// took three of 64 bits, which bound them.  112 x 112 x 64 -> 56 x 56, 64 images: forward 46.7 -> 36.3 us (142 MB; the comparisons of a
+// window's 9 x 8 elements are 16 of it), backward from the saved winners 55 -> 36 (141 MB).  Strips of 4 to 16 rows a workgroup, for the
+// rows that windows share, were slower the longer they were (48 to 67, 39 to 46 us): too few loads in flight.
+dim3 pool_grid(int64_t row, int rows, int images) {
+  constexpr int MOST = 65535;
+  return dim3((unsigned)((row + LY_THREADS - 1) / LY_THREADS), (unsigned)(rows < MOST ? rows : MOST), (unsigned)(images < MOST ? images : MOST));
+}
+
+// column and channel group of a thread
+__device__ __forceinline__ void pool_place(int C8, int& col, int& c) {
+  const uint64_t i = (uint64_t)blockIdx.x * LY_THREADS + threadIdx.x;
+  col = (i >> 32) == 0 ? (int)((unsigned)i / (unsigned)C8) : (int)(i / (unsigned)C8);
+  c = (int)(i - (uint64_t)(unsigned)col * (unsigned)C8);
+}
+
 // WIN > 0: window size known at compile time (loops unrolled, the window's loads in flight together); 0: g.window
 template <int WIN>
 __global__ __launch_bounds__(LY_THREADS) void maxpool_fwd_kernel(const uint4* __restrict__ x, uint4* __restrict__ y,
                                                                  uint2* __restrict__ arg, PoolGeom g) {
   const int window = WIN > 0 ? WIN : g.window;
-  const int64_t total = (int64_t)g.N * g.P * g.Q * g.C8;
-  for (int64_t i = (int64_t)blockIdx.x * LY_THREADS + threadIdx.x; i < total; i += (int64_t)gridDim.x * LY_THREADS) {
-    const int c = (int)(i % g.C8);
-    int64_t t = i / g.C8;
-    const int q = (int)(t % g.Q);
-    t /= g.Q;
-    const int p = (int)(t % g.P);
-    const int n = (int)(t / g.P);
-    float best[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    unsigned win[8] = {0, 0, 0, 0, 0, 0, 0, 0};  // position r * window + s of the first maximum
-    bool have = false;
+  int q, c;
+  pool_place(g.C8, q, c);
+  if (q >= g.Q) return;
+  for (int n = blockIdx.z; n < g.N; n += gridDim.z)
+    for (int p = blockIdx.y; p < g.P; p += gridDim.y) {
+      // A position outside the image is read at the nearest inside, which the window has too, and counted as that one: no branch around the
+      // load, and the first maximum stays the first (its row and column are the first or the last inside).
+      float best[8];
+      unsigned win[8];  // position r * window + s of the first maximum
+      const int top = p * g.stride - g.pad, left = q * g.stride - g.pad;
 #pragma unroll(WIN > 0 ? WIN : 1)
-    for (int r = 0; r < window; ++r) {
-      const int h = p * g.stride - g.pad + r;
+      for (int r = 0; r < window; ++r) {
+        const int h = top + r, hc = h < 0 ? 0 : (h >= g.H ? g.H - 1 : h);
+        const uint4* const row = x + ((int64_t)n * g.H + hc) * g.W * g.C8 + c;
 #pragma unroll(WIN > 0 ? WIN : 1)
-      for (int s = 0; s < window; ++s) {
-        const int w = q * g.stride - g.pad + s;
-        // a position outside the image is read at the nearest inside one and ignored: no branch around the load
-        const bool ok = h >= 0 && h < g.H && w >= 0 && w < g.W;
-        const int hc = h < 0 ? 0 : (h >= g.H ? g.H - 1 : h), wc = w < 0 ? 0 : (w >= g.W ? g.W - 1 : w);
-        float v[8];
-        unpack8(x[(((int64_t)n * g.H + hc) * g.W + wc) * g.C8 + c], v);
+        for (int s = 0; s < window; ++s) {
+          const int w = left + s, wc = w < 0 ? 0 : (w >= g.W ? g.W - 1 : w);
+          const unsigned at = (unsigned)((hc - top) * window + wc - left);
+          float v[8];
+          unpack8(row[(int64_t)wc * g.C8], v);
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          const bool better = ok && (!have || v[k] > best[k]);
-          best[k] = better ? v[k] : best[k];
-          win[k] = better ? (unsigned)(r * window + s) : win[k];
+          for (int k = 0; k < 8; ++k) {
+            const bool better = (r == 0 && s == 0) || v[k] > best[k];
+            best[k] = better ? v[k] : best[k];
+            win[k] = better ? at : win[k];
+          }
         }
-        have = have || ok;
       }
+      const int64_t i = (((int64_t)n * g.P + p) * g.Q + q) * g.C8 + c;
+      y[i] = pack8(best);
+      if (arg)
+        arg[i] = make_uint2(win[0] | (win[1] << 8) | (win[2] << 16) | (win[3] << 24), win[4] | (win[5] << 8) | (win[6] << 16) | (win[7] << 24));
     }
-    y[i] = pack8(best);
-    if (arg)
-      arg[i] = make_uint2(win[0] | (win[1] << 8) | (win[2] << 16) | (win[3] << 24), win[4] | (win[5] << 8) | (win[6] << 16) | (win[7] << 24));
-  }
 }
 
 // one thread per input position and 8 channels: it looks at every window that contains the position, finds that
@@ -212,55 +226,119 @@ __global__ __launch_bounds__(LY_THREADS) void maxpool_bwd_kernel(const uint4* __
 // the same gather from the winners the forward pass saved: nothing is re-derived, x is not read
 __global__ __launch_bounds__(LY_THREADS) void maxpool_bwd_arg_kernel(const uint2* __restrict__ arg, const uint4* __restrict__ dy,
                                                                      uint4* __restrict__ dx, PoolGeom g) {
-  const int64_t total = (int64_t)g.N * g.H * g.W * g.C8;
-  for (int64_t i = (int64_t)blockIdx.x * LY_THREADS + threadIdx.x; i < total; i += (int64_t)gridDim.x * LY_THREADS) {
-    const int c = (int)(i % g.C8);
-    int64_t t = i / g.C8;
-    const int w0 = (int)(t % g.W);
-    t /= g.W;
-    const int h0 = (int)(t % g.H);
-    const int n = (int)(t / g.H);
-    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    int p_lo = h0 + g.pad - g.window + 1;
-    p_lo = p_lo <= 0 ? 0 : (p_lo + g.stride - 1) / g.stride;
-    int p_hi = (h0 + g.pad) / g.stride;
-    if (p_hi > g.P - 1) p_hi = g.P - 1;
-    int q_lo = w0 + g.pad - g.window + 1;
-    q_lo = q_lo <= 0 ? 0 : (q_lo + g.stride - 1) / g.stride;
-    int q_hi = (w0 + g.pad) / g.stride;
-    if (q_hi > g.Q - 1) q_hi = g.Q - 1;
-    for (int p = p_lo; p <= p_hi; ++p)
-      for (int q = q_lo; q <= q_hi; ++q) {
-        const unsigned me = (unsigned)((h0 - (p * g.stride - g.pad)) * g.window + (w0 - (q * g.stride - g.pad)));
-        const int64_t o = (((int64_t)n * g.P + p) * g.Q + q) * g.C8 + c;
-        const uint2 a = arg[o];
-        float gy[8];
-        unpack8(dy[o], gy);
+  int w0, c;
+  pool_place(g.C8, w0, c);
+  if (w0 >= g.W) return;
+  int q_lo = w0 + g.pad - g.window + 1;
+  q_lo = q_lo <= 0 ? 0 : (q_lo + g.stride - 1) / g.stride;
+  int q_hi = (w0 + g.pad) / g.stride;
+  if (q_hi > g.Q - 1) q_hi = g.Q - 1;
+  for (int n = blockIdx.z; n < g.N; n += gridDim.z)
+    for (int h0 = blockIdx.y; h0 < g.H; h0 += gridDim.y) {
+      float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      int p_lo = h0 + g.pad - g.window + 1;
+      p_lo = p_lo <= 0 ? 0 : (p_lo + g.stride - 1) / g.stride;
+      int p_hi = (h0 + g.pad) / g.stride;
+      if (p_hi > g.P - 1) p_hi = g.P - 1;
+      for (int p = p_lo; p <= p_hi; ++p)
+        for (int q = q_lo; q <= q_hi; ++q) {
+          const unsigned me = (unsigned)((h0 - (p * g.stride - g.pad)) * g.window + (w0 - (q * g.stride - g.pad)));
+          const int64_t o = (((int64_t)n * g.P + p) * g.Q + q) * g.C8 + c;
+          const uint2 a = arg[o];
+          float gy[8];
+          unpack8(dy[o], gy);
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          const unsigned wk = ((k < 4 ? a.x : a.y) >> (8 * (k & 3))) & 0xffu;
-          acc[k] += wk == me ? gy[k] : 0.f;
+          for (int k = 0; k < 8; ++k) {
+            const unsigned wk = ((k < 4 ? a.x : a.y) >> (8 * (k & 3))) & 0xffu;
+            acc[k] += wk == me ? gy[k] : 0.f;
+          }
         }
-      }
-    dx[i] = pack8(acc);
-  }
+      dx[(((int64_t)n * g.H + h0) * g.W + w0) * g.C8 + c] = pack8(acc);
+    }
+}
+
+// ... for 3 x 3 windows with stride 2: positions 2 a + 1 and 2 a + 2 of the padded image meet windows a and a + 1, so a thread takes a 2 x 2
+// cell and requests its 2 x 2 windows at once (position by position they are nine).  The general kernel's order of sums.
+__global__ __launch_bounds__(LY_THREADS) void maxpool_bwd_arg_3x3s2_kernel(const uint2* __restrict__ arg, const uint4* __restrict__ dy,
+                                                                           uint4* __restrict__ dx, PoolGeom g, int first, int rows, int cols) {
+  int bi, c;
+  pool_place(g.C8, bi, c);
+  const int b = first + bi;
+  if (bi >= cols) return;
+  for (int n = blockIdx.z; n < g.N; n += gridDim.z)
+    for (int ai = blockIdx.y; ai < rows; ai += gridDim.y) {
+      const int a = first + ai;
+      uint2 win[2][2];
+      uint4 gq[2][2];
+#pragma unroll
+      for (int dp = 0; dp < 2; ++dp)
+#pragma unroll
+        for (int dq = 0; dq < 2; ++dq) {
+          const int p = a + dp, q = b + dq;
+          win[dp][dq] = make_uint2(~0u, ~0u);  // no position's number
+          gq[dp][dq] = make_uint4(0u, 0u, 0u, 0u);
+          if (p >= 0 && p < g.P && q >= 0 && q < g.Q) {
+            const int64_t o = (((int64_t)n * g.P + p) * g.Q + q) * g.C8 + c;
+            win[dp][dq] = arg[o];
+            gq[dp][dq] = dy[o];
+          }
+        }
+      float acc[2][2][8];
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int k = 0; k < 8; ++k) acc[i][j][k] = 0.f;
+#pragma unroll
+      for (int dp = 0; dp < 2; ++dp)
+#pragma unroll
+        for (int dq = 0; dq < 2; ++dq) {
+          float gy[8];
+          unpack8(gq[dp][dq], gy);
+#pragma unroll
+          for (int k = 0; k < 8; ++k) {
+            const unsigned wk = ((k < 4 ? win[dp][dq].x : win[dp][dq].y) >> (8 * (k & 3))) & 0xffu;
+#pragma unroll
+            for (int i = dp; i < 2; ++i)
+#pragma unroll
+              for (int j = dq; j < 2; ++j) acc[i][j][k] += wk == (unsigned)((1 + i - 2 * dp) * 3 + 1 + j - 2 * dq) ? gy[k] : 0.f;
+          }
+        }
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const int h = 2 * a + 1 + i - g.pad, w = 2 * b + 1 + j - g.pad;
+          if (h >= 0 && h < g.H && w >= 0 && w < g.W) dx[(((int64_t)n * g.H + h) * g.W + w) * g.C8 + c] = pack8(acc[i][j]);
+        }
+    }
 }
 
 // ---- global average pooling ----------------------------------------------------------------------------------------
-__global__ __launch_bounds__(LY_THREADS) void avgpool_fwd_kernel(const uint4* __restrict__ x, uint4* __restrict__ y, int N, int HW,
-                                                                 int C8) {
+// Sixteen positions requested together, added in order; small workgroups, for as many compute units as there are (64 images of 7 x 7 x 2048: 26.2 -> 9.0 us).
+constexpr int AVG_THREADS = 64;
+__global__ __launch_bounds__(AVG_THREADS) void avgpool_fwd_kernel(const uint4* __restrict__ x, uint4* __restrict__ y, int N, int HW,
+                                                                  int C8) {
+  constexpr int U = 16;
   const int64_t total = (int64_t)N * C8;
-  for (int64_t i = (int64_t)blockIdx.x * LY_THREADS + threadIdx.x; i < total; i += (int64_t)gridDim.x * LY_THREADS) {
-    const int c = (int)(i % C8);
+  for (int64_t i = (int64_t)blockIdx.x * AVG_THREADS + threadIdx.x; i < total; i += (int64_t)gridDim.x * AVG_THREADS) {
     const int64_t n = i / C8;
+    const uint4* const p = x + n * HW * C8 + (i - n * C8);
     float acc[8];
 #pragma unroll
     for (int k = 0; k < 8; ++k) acc[k] = 0.f;
-    for (int j = 0; j < HW; ++j) {
-      float v[8];
-      unpack8(x[(n * HW + j) * C8 + c], v);
+    for (int j = 0; j < HW; j += U) {
+      uint4 q[U];
 #pragma unroll
-      for (int k = 0; k < 8; ++k) acc[k] += v[k];
+      for (int u = 0; u < U; ++u) q[u] = j + u < HW ? p[(int64_t)(j + u) * C8] : make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        float v[8];
+        unpack8(q[u], v);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) acc[k] = j + u < HW ? acc[k] + v[k] : acc[k];
+      }
     }
     const float d = (float)HW;
 #pragma unroll
@@ -446,7 +524,7 @@ extern "C" int jz_maxpool_fwd(int N, int H, int W, int C, int window, int stride
   if (!jz::aligned16(x16) || !jz::aligned16(y16) || (reinterpret_cast<uintptr_t>(arg8) & 7u)) return JZ_ERR_ALIGN;
   const size_t nx = (size_t)N * H * W * C * 2, ny = (size_t)N * g.P * g.Q * C * 2;
   if (jz::overlaps(x16, nx, y16, ny) || jz::overlaps(arg8, ny / 2, x16, nx) || jz::overlaps(arg8, ny / 2, y16, ny)) return JZ_ERR_ALIAS;
-  const dim3 grid(grid_for((int64_t)N * g.P * g.Q * g.C8));
+  const dim3 grid = pool_grid((int64_t)g.Q * g.C8, g.P, N);
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   const uint4* x = static_cast<const uint4*>(x16);
   uint4* y = static_cast<uint4*>(y16);
@@ -474,8 +552,12 @@ extern "C" int jz_maxpool_bwd(int N, int H, int W, int C, int window, int stride
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   const uint4 *x = static_cast<const uint4*>(x16), *dy = static_cast<const uint4*>(dy16);
   uint4* dx = static_cast<uint4*>(dx16);
-  if (arg8)  // the winners are known: x is not needed
-    hipLaunchKernelGGL(maxpool_bwd_arg_kernel, grid, dim3(LY_THREADS), 0, st, static_cast<const uint2*>(arg8), dy, dx, g);
+  if (arg8 && window == 3 && stride == 2) {  // the winners are known: x is not needed
+    const int first = pad > 0 ? 0 : -1, rows = (H + pad - 2 - first * 2) / 2 + 1, cols = (W + pad - 2 - first * 2) / 2 + 1;
+    hipLaunchKernelGGL(maxpool_bwd_arg_3x3s2_kernel, pool_grid((int64_t)cols * g.C8, rows, N), dim3(LY_THREADS), 0, st, static_cast<const uint2*>(arg8), dy,
+                       dx, g, first, rows, cols);
+  } else if (arg8)
+    hipLaunchKernelGGL(maxpool_bwd_arg_kernel, pool_grid((int64_t)W * g.C8, H, N), dim3(LY_THREADS), 0, st, static_cast<const uint2*>(arg8), dy, dx, g);
   else if (window == 3)
     hipLaunchKernelGGL(maxpool_bwd_kernel<3>, grid, dim3(LY_THREADS), 0, st, x, dy, dx, g);
   else if (window == 2)
@@ -491,7 +573,8 @@ extern "C" int jz_avgpool_fwd(int N, int HW, int C, const void* x16, void* y16, 
   if (!x16 || !y16) return JZ_ERR_NULL;
   if (!jz::aligned16(x16) || !jz::aligned16(y16)) return JZ_ERR_ALIGN;
   if (jz::overlaps(x16, (size_t)N * HW * C * 2, y16, (size_t)N * C * 2)) return JZ_ERR_ALIAS;
-  hipLaunchKernelGGL(avgpool_fwd_kernel, dim3(grid_for((int64_t)N * (C / 8))), dim3(LY_THREADS), 0,
+  const int64_t blocks = ((int64_t)N * (C / 8) + AVG_THREADS - 1) / AVG_THREADS;
+  hipLaunchKernelGGL(avgpool_fwd_kernel, dim3((unsigned)(blocks < 65536 ? blocks : 65536)), dim3(AVG_THREADS), 0,
                      static_cast<hipStream_t>(hip_stream), static_cast<const uint4*>(x16), static_cast<uint4*>(y16), N, HW, C / 8);
   return jz::launch_status();
 }
