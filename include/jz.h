@@ -310,7 +310,7 @@ int jz_lars_mp_update_presummed_dyn(const jz_param_set* ps, const jz_lars_hparam
  *   dc, dgamma, dbeta = jz_bn_relu_bwd(rows = N*H*W, C, x = bn_x16 (= c), y = bn_y16, dy = dz, relu = 1)
  * with the statistics of the normalization's backward (sum g, sum g x^ over g = dz where y > 0) taken in the
  * convolution's epilogue, while the dz tile is on chip, when the convolution's kernel allows it (not split, unit stride
- * or no scatter form, C a multiple of 8); otherwise the statistics pass runs as in jz_bn_relu_bwd.  dz16 holds the same
+ * or no scatter form, C a multiple of 8); otherwise the normalization runs as in jz_bn_relu_bwd.  dz16 holds the same
  * bits as from jz_conv2d_bwd_data; bn_dx16 / dgamma16 / dbeta16 meet jz_bn_relu_bwd's within the rounding of FP32 sums
  * taken in another (fixed, deterministic) order.  bn_y16 is the tensor the forward pass fed to this convolution; bn_x16
  * the normalization's input; gamma, save_mean, save_invstd as for jz_bn_relu_bwd.  Outputs must not overlap anything.

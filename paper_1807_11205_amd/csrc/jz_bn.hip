@@ -1216,17 +1216,33 @@ static int conv_bwd_data_bn_bwd(const jz_conv_desc* desc, const void* dy16, cons
   const uint4* x = static_cast<const uint4*>(bn_x16);
   const uint4* y = static_cast<const uint4*>(bn_y16);
   const uint4* dz = static_cast<const uint4*>(out16);
-  int slabs = p.tiles_m;
-  if (slabs == 0) {  // this convolution kernel cannot leave the sums: the statistics pass, which then also forms g in place
-    slabs = p.bn.slabs;
-    BnStatsArgs in{.x = x, .y = y, .dy = dz, .mean = save_mean, .invstd = save_invstd};
-    in.dy2 = static_cast<const uint4*>(add16);
-    in.g_out = static_cast<uint4*>(out16);
-    rc = block_end ? launch_stats<ST_END>(p.bn, part, in, st) : launch_stats<ST_RELU>(p.bn, part, in, st);
-    if (rc != JZ_OK) return rc;
+  if (p.tiles_m > 0)
+    return launch_bwd_rest(part, p.tiles_m, coef, rows, C, block_end ? 0 : 1, gamma, save_mean, save_invstd, x, block_end ? nullptr : y, dz,
+                           static_cast<uint4*>(bn_dx16), dgamma16, dbeta16, st);
+  // This convolution kernel cannot leave the sums: the normalization as its own call takes it, a block end with g in place.  In one launch
+  // 83 us at the block ends of ResNet-50's strided layers (batch 64, 200704 x 256 to 12544 x 1024, mean), as statistics and the rest 102.
+  BnPlan wp;  // all tensors are clear of the workspace (checked above)
+  const bool whole = make_whole_plan(rows, C, false, p.bn.total, &wp);
+  if (whole) {
+    p.bn = wp;
+    part = reinterpret_cast<float*>(bws + wp.off_part);
+    coef = reinterpret_cast<float*>(bws + wp.off_coef);
   }
-  return launch_bwd_rest(part, slabs, coef, rows, C, block_end ? 0 : 1, gamma, save_mean, save_invstd, x, block_end ? nullptr : y, dz,
-                         static_cast<uint4*>(bn_dx16), dgamma16, dbeta16, st);
+  uint4* const g = static_cast<uint4*>(out16);
+  const uint4* const add = static_cast<const uint4*>(add16);
+  if (whole && bw_has_chip(st)) {
+    BnWholeArgs w;
+    w.x = x; w.y = y; w.dy = dz; w.dy2 = add;
+    w.g_out = g; w.out = static_cast<uint4*>(bn_dx16);
+    w.gamma = gamma; w.mean = save_mean; w.invstd = save_invstd;
+    w.dgamma = static_cast<unsigned short*>(dgamma16); w.dbeta = static_cast<unsigned short*>(dbeta16);
+    return block_end ? launch_whole<BW_END>(wp, w, bws, st) : launch_whole<BW_RELU>(wp, w, bws, st);
+  }
+  const BnStatsArgs in{.x = x, .y = y, .dy = dz, .dy2 = add, .g_out = g, .mean = save_mean, .invstd = save_invstd};
+  rc = block_end ? launch_stats<ST_END>(p.bn, part, in, st) : launch_stats<ST_RELU>(p.bn, part, in, st);
+  if (rc != JZ_OK) return rc;
+  return launch_bwd_rest(part, p.bn.slabs, coef, rows, C, block_end ? 0 : 1, gamma, save_mean, save_invstd, x, block_end ? nullptr : y, dz,
+                         static_cast<uint4*>(bn_dx16), dgamma16, dbeta16, st, nullptr, &p.bn);
 }
 
 extern "C" int jz_conv2d_bwd_data_bn_relu_bwd(const jz_conv_desc* desc, const void* dy16, const void* w16, const void* bn_x16,

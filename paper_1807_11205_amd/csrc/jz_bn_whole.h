@@ -298,6 +298,7 @@ __global__ __launch_bounds__(BW_THREADS) void bn_whole(BnWholeArgs a) {
   // ---- the exchange -----------------------------------------------------------------------------------------------------
   unsigned long long* const flags = a.flags + (size_t)group * a.wgs;
   if (a.wgs > 1) {
+    if constexpr (MODE == BW_END) bw_performed();  // g_out too: if this workgroup leaves, another reads it
     __syncthreads();
     if (tid < 64) {  // the first wavefront looks, each lane at up to four flags
       constexpr int F = BW_WGS / 64;
@@ -324,6 +325,7 @@ __global__ __launch_bounds__(BW_THREADS) void bn_whole(BnWholeArgs a) {
         __builtin_amdgcn_s_sleep(1);
       }
       if (!done) {
+        if constexpr (MODE == BW_END) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
         if (tid == 0) __hip_atomic_store(flags + slab, a.tag | BW_LEFT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         bw_performed();
         if (complete()) {
@@ -430,31 +432,31 @@ __global__ __launch_bounds__(BW_THREADS) void bn_whole(BnWholeArgs a) {
     }
     return pack8(o);
   };
-  // passes from p on of a workgroup's rows out of memory.  Its own are masked already: by bits, or in g_out
+  // passes from p on of a workgroup's rows out of memory.  Its own are masked already, by bits; a block end's are in g_out, also those of a
+  // workgroup that left (g_out may be dy, which is gone then)
   auto stream = [&](const Rows& r, int p, auto own_tag) {
     constexpr bool OWN = decltype(own_tag)::value;
     const int n = (r.n + BW_ROWS - 1) / BW_ROWS;
     for (; p < n; p += BW_U) {
-      uint4 x8[BW_U], g8[BW_U], y8[BW_U], e8[BW_U];
+      uint4 x8[BW_U], g8[BW_U], y8[BW_U];
       const bool bits = OWN && MASKS > 0 && p + BW_U - 1 - K - KL < MASKS;
 #pragma unroll
       for (int u = 0; u < BW_U; ++u) {
         const unsigned o = voff + (unsigned)(p + u) * step;
         x8[u] = get(r.x, o);
-        if constexpr (OWN && MODE == BW_END) {
+        if constexpr (MODE == BW_END) {
           g8[u] = get(r.g, o);
         } else {
           if constexpr (GRAD) g8[u] = get(r.dy, o);
           if constexpr (NEEDS_Y)
             if (!bits) y8[u] = get(r.y, o);
-          if constexpr (MODE == BW_END) e8[u] = get(r.dy2, o);
         }
       }
 #pragma unroll
       for (int u = 0; u < BW_U; ++u) {
-        if constexpr (!OWN || MODE != BW_END) {
+        if constexpr (MODE != BW_END) {
           if (bits) g8[u] = masked_by(g8[u], mask[(p + u - K - KL) * BW_THREADS + tid]);
-          else g8[u] = masked(g8[u], y8[u], e8[u]);
+          else g8[u] = masked(g8[u], y8[u], g8[u]);
         }
         put(r.out, voff + (unsigned)(p + u) * step, result(x8[u], g8[u]));
       }
@@ -487,6 +489,7 @@ __global__ __launch_bounds__(BW_THREADS) void bn_whole(BnWholeArgs a) {
       }
       __syncthreads();
       if (!state) continue;
+      if constexpr (MODE == BW_END) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
       if (s == 0) finish(true);
       stream(rows_of(s), 0, std::false_type{});
     }

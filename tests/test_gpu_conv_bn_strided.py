@@ -1,0 +1,68 @@
+"""The normalization behind a strided backward-data product that scatters its rows and so leaves no sums: one launch, with a block end's g formed
+in place.  The same bits as the two calls it replaces, as the launches apart (which a captured graph takes), and when workgroups end without
+their rows written, which others then take from g."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+# N, H, channels of the normalization (the convolution's input), output channels: rows of one workgroup, a ragged last one, kept and read again
+SIZES = [(1, 7, 64, 64), (3, 15, 128, 64), (32, 28, 192, 64), (41, 56, 256, 128), (5, 9, 96, 64)]  # 96 channels: the launches apart
+
+
+@pytest.mark.parametrize("N,H,C,K", SIZES)
+def test_strided_pointwise(N, H, C, K):
+    from paper_1807_11205_amd import api as jz
+    d = jz.conv_desc(N, H, H, C, K, 1, 1, 2, 0)
+    rows = N * H * H
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(rows + C)
+    rn = lambda n, std, dt=torch.float16, mean=0.0: (torch.randn(n, generator=gen, device=DEV) * std + mean).to(dt)
+    x, dyb, w, dy = rn(rows * C, 1.5), rn(rows * C, 1.0), rn(K * C, 0.1), rn(N * d.P * d.Q * K, 1.0)
+    y = torch.relu(rn(rows * C, 1.0))
+    gamma, mean, invstd = rn(C, 0.1, torch.float32, 1.0), rn(C, 0.1, torch.float32), rn(C, 0.05, torch.float32, 0.7)
+    ws = torch.full((jz.jz_conv2d_bwd_data_bn_relu_bwd_workspace_bytes(d),), 0xCD, dtype=torch.uint8, device=DEV)
+    bws = torch.empty(jz.jz_bn_workspace_bytes(rows, C), dtype=torch.uint8, device=DEV)
+    cws = torch.empty(max(jz.jz_conv2d_workspace_bytes(jz.JZ_BWD_DATA, d), 16), dtype=torch.uint8, device=DEV)
+    h = lambda n: torch.full((n,), 7.0, dtype=torch.float16, device=DEV)
+    outputs = lambda: [[h(rows * C), h(rows * C), h(C), h(C)] for _ in range(3)]
+
+    def fused(o):
+        jz.jz_conv2d_bwd_data_bn_relu_bwd(d, dy, w, x, y, gamma, mean, invstd, *o[0], ws)
+        jz.jz_conv2d_bwd_data_block_end_bwd(d, dy, w, dyb, x, y, gamma, mean, invstd, *o[1], ws)
+        jz.jz_conv2d_bwd_data_block_end_bwd(d, dy, w, None, x, y, gamma, mean, invstd, *o[2], ws)
+
+    def apart(o):
+        jz.bind_conv2d(jz.JZ_BWD_DATA, d, dy, w, o[0][0], cws)()
+        jz.jz_bn_relu_bwd(rows, C, x, y, o[0][0], gamma, mean, invstd, True, *o[0][1:], bws)
+        for i, second in ((1, dyb), (2, None)):
+            jz.jz_bn_bwd_block_end(rows, C, x, y, o[0][0], second, gamma, mean, invstd, *o[i], bws)
+
+    def differ(a, b):
+        return [(i, k) for i in range(3) for k in range(4) if not torch.equal(a[i][k].view(torch.int16), b[i][k].view(torch.int16))]
+
+    for _ in range(70):            # one stream a device runs it in one launch: the one that called last, and often
+        apart(want := outputs())
+    fused(o := outputs())
+    torch.cuda.synchronize()
+    assert differ(want, o) == []
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    g, o = torch.cuda.CUDAGraph(), outputs()
+    with torch.cuda.graph(g, stream=s):
+        fused(o)
+    for _ in range(3):
+        for t in o[0] + o[1] + o[2]:
+            t.fill_(-3.0)
+        g.replay()
+        torch.cuda.synchronize()
+        assert differ(want, o) == []
+    jz.jz_bn_tune_wait(0)          # nobody waits: the last workgroup to arrive finds most others gone
+    try:
+        for _ in range(3):
+            fused(o := outputs())
+            torch.cuda.synchronize()
+            assert differ(want, o) == []
+    finally:
+        jz.jz_bn_tune_wait(100)
