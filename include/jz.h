@@ -436,7 +436,9 @@ int jz_conv2d_describe_plan(int op, const jz_conv_desc* desc, char* text, size_t
  * shorter than four k tiles).  Later calls for that shape use it in place of the built-in table of measured
  * choices and of the cost model; nothing else overrides the planner (the library reads no environment variables).
  * The variant must be one the library has (jz_conv2d_describe_plan shows the names: e.g. 128x128 tile, k tile 64,
- * 8 wavefronts, ring 4), else JZ_ERR_UNSUPPORTED; shapes that gather with per-load tap arithmetic take the four
+ * 8 wavefronts, ring 4), else JZ_ERR_UNSUPPORTED (a ring of 16 and more names a variant of the window kernel, which takes layers of unit
+ * stride whose output grid is their input grid, 9 to 25 taps, and keeps a tile's pixels and what their taps reach in LDS; unless a variant is
+ * recorded here it stands in for the planner's choice where it is faster); shapes that gather with per-load tap arithmetic take the four
  * 4-wavefront tiles, 32 deep, ring 4; a strided multi-tap backward-data layer, whose parity classes (the residues of its
  * stride) run side by side in one launch, takes the variant for every one of them (never split); shapes on the
  * element-wise kernel cannot be tuned (JZ_ERR_UNSUPPORTED).

@@ -708,9 +708,42 @@ void set_tiles(Plan* pl, int splits) {
   a.tiles_m = (a.M + pl->BM - 1) / pl->BM;
   a.tiles_n = (a.N + pl->BN - 1) / pl->BN;
   a.kt_per_split = (a.nkt + splits - 1) / splits;
+  if (pl->window) {  // whole blocks of channels
+    const int taps = a.g.R * a.g.S, blocks = a.nkt / taps;
+    a.kt_per_split = (blocks + splits - 1) / splits * taps;
+  }
   a.splits = (a.nkt + a.kt_per_split - 1) / a.kt_per_split;  // drop empty splits
   a.d_tiles_mn = make_fastdiv((unsigned)(a.tiles_m * a.tiles_n));
   a.d_tiles_n = make_fastdiv((unsigned)a.tiles_n);
+}
+
+// Whether the window kernel's variant v takes this problem: unit stride, output grid = input grid, whole blocks of channels, and a
+// window that holds the tile's pixels and what their taps reach.
+bool window_fits(const Plan& pl, const WindowVariant& v) {
+  const GemmArgs& a = pl.args;
+  const ConvGeom& g = a.g;
+  return (pl.op == JZ_FWD || pl.op == JZ_BWD_DATA) && pl.fast && !pl.packed && !pl.gen && !pl.flat && !a.sc_on && g.sh == 1 && g.sw == 1 &&
+         g.IH == g.OH && g.IW == g.OW && 2 * g.ph + 1 == g.R && 2 * g.pw + 1 == g.S && g.R * g.S >= 9 && g.R * g.S <= 32 && g.IC % v.ck == 0 &&
+         (v.windows > 1 || g.IC == v.ck) && (long long)v.BM + (long long)(g.R - 1) * g.IW + g.S - 1 <= v.rows;
+}
+
+// The window kernel's entry (+ 1) for a plan that the tables or the cost model have made for the ring kernels, or 0.  From 90 random layers (3x3 and
+// 5x5, 64 ... 512 channels, images of 7 ... 63 pixels, 5 ... 3300 tiles), both directions, time against the ring kernel's:
+//   more than 64 channels in, the plan is 256x128 tiles: 0.76 ... 1.006, median 0.95 (fewer bytes into LDS at the same tile);
+//   ... is 128x128 tiles on 4 wavefronts: 0.83 ... 0.99 where 256x128 tiles leave at most 30 % of their last round of workgroups empty,
+//   up to 1.11 where they leave more; eight wavefronts, 256x256 tiles or 64 columns: mostly slower, up to 1.1 and 1.4;
+//   64 channels in and at most 64 out: 0.66 ... 0.96 from 155 tiles of 256x64 on, slower from 93 down (1.2); more columns bring the
+//   window in several times: 0.76 ... 1.014, median 0.92, where the last round is 80 % full, up to 1.08 elsewhere.
+int choose_window(const Plan& pl) {
+  const GemmArgs& a = pl.args;
+  auto tiles = [&](const WindowVariant& v) { return (long long)((a.M + v.BM - 1) / v.BM) * ((a.N + v.BN - 1) / v.BN); };
+  auto full = [&](long long t) { return (double)t / (double)((t + kUnits - 1) / kUnits * kUnits); };
+  if (window_fits(pl, kWindows[1])) {
+    const long long t = tiles(kWindows[1]);
+    return (a.N <= 64 ? t >= 150 : t >= kUnits && full(t) >= 0.8) ? 2 : 0;
+  }
+  if (!window_fits(pl, kWindows[0]) || a.g.IC <= 64 || a.N <= 64 || pl.BN != 128) return 0;
+  return pl.BM == 256 || (pl.BM == 128 && pl.waves == 4 && pl.bk == 32 && full(tiles(kWindows[0])) >= 0.7) ? 1 : 0;
 }
 
 void choose_tiling(Plan* pl, bool bk64_ok, int forced_bk, bool tables = true) {
@@ -778,6 +811,13 @@ void choose_tiling(Plan* pl, bool bk64_ok, int forced_bk, bool tables = true) {
   if (hit) {
     pl->BM = hit->BM; pl->BN = hit->BN; pl->bk = hit->bk; pl->waves = hit->waves;
     pl->nst = hit->nst;
+    if (hit->nst > kWindowRing) {
+      pl->nst -= kWindowRing;
+      for (int i = 0; i < kNumWindows; ++i) {
+        const WindowVariant& v = kWindows[i];
+        if (v.BM == pl->BM && v.BN == pl->BN && v.ck == pl->bk && v.waves == pl->waves && v.nst == pl->nst && window_fits(*pl, v)) pl->window = i + 1;
+      }
+    }
     bS = hit->splits;
     const int nkt_h = (a.Kred + hit->bk - 1) / hit->bk;
     if (bS > 1 && (nkt_h / bS < 4 || a.sc_on)) bS = 1;  // the same admissibility rules as the search below
@@ -807,6 +847,16 @@ void choose_tiling(Plan* pl, bool bk64_ok, int forced_bk, bool tables = true) {
   }
   pl->tuned = hit != nullptr;
   set_tiles(pl, bS);
+  if (!pl->rt_forced && a.splits == 1) {
+    const int w = choose_window(*pl);
+    if (w != 0) {
+      const WindowVariant& v = kWindows[w - 1];
+      pl->window = w;
+      pl->replaced = {pl->BM, pl->BN, pl->bk, pl->waves, pl->nst, a.tiles_m, a.tiles_n, a.nkt};
+      pl->BM = v.BM; pl->BN = v.BN; pl->bk = v.ck; pl->waves = v.waves; pl->nst = v.nst;
+      set_tiles(pl, 1);
+    }
+  }
 }
 
 void finish_geometry(ConvGeom& g) {
@@ -870,9 +920,16 @@ void plan_text(const Plan& pl, char* buf, size_t n) {
              "4 wavefronts, 4-channel padded copy", pl.op, a.M, a.N, a.Kred, mb, a.N, (a.g.OH * a.g.OW + mb - 1) / mb);
     return;
   }
+  if (pl.window && !pl.rt_forced) {
+    const auto& r = pl.replaced;
+    snprintf(buf, n, "op %d M %d N %d K %d: vector tile %dx%dx%d, %d wavefronts, ring %d, %d x %d tiles, 1 splits of %d k tiles%s; "
+             "replaced by window tile %dx%dx%d, %d wavefronts, ring %d, %d x %d tiles", pl.op, a.M, a.N, a.Kred, r.BM, r.BN, r.bk, r.waves, r.nst,
+             r.tiles_m, r.tiles_n, r.nkt, pl.tuned ? ", recorded choice" : "", pl.BM, pl.BN, pl.bk, pl.waves, pl.nst + kWindowRing, a.tiles_m, a.tiles_n);
+    return;
+  }
   snprintf(buf, n, "op %d M %d N %d K %d: %s tile %dx%dx%d, %d wavefronts, ring %d, %d x %d tiles, %d splits of %d k tiles%s%s%s", pl.op, a.M,
-           a.N, a.Kred, pl.fast ? "vector" : "element-wise", pl.BM, pl.BN, pl.bk, pl.fast ? pl.waves : 4,
-           pl.fast ? pl.nst : 2, a.tiles_m, a.tiles_n,
+           a.N, a.Kred, pl.window ? "window" : pl.fast ? "vector" : "element-wise", pl.BM, pl.BN, pl.bk, pl.fast ? pl.waves : 4,
+           pl.window ? pl.nst + kWindowRing : pl.fast ? pl.nst : 2, a.tiles_m, a.tiles_n,
            a.splits, a.kt_per_split, pl.packed ? ", 4-channel padded copy" : "",
            pl.flat ? (pl.classes ? ", flattened taps, the residues of the stride in one launch" : ", flattened taps")
            : a.sc_on ? ", scatter epilogue" : pl.classes ? ", the parity classes of the stride in one launch" : pl.gen ? ", per-load tap arithmetic" : "",
@@ -1292,7 +1349,10 @@ int run(int op, const jz_conv_desc* d, const void* A, const void* B, void* D, vo
     if ((rc = jz::launch_status()) != JZ_OK) return rc;
   }
   const bool epilogue_stats = stats && a.splits == 1;
-  if (op == JZ_FWD) rc = epilogue_stats ? launch_fwd_stats(pl, st) : launch_fwd(pl, st);
+  if (pl.window) {
+    if (op == JZ_FWD) rc = epilogue_stats ? launch_window_fwd_stats(pl, st) : launch_window_fwd(pl, st);
+    else rc = !epilogue_stats ? launch_window_bwd_data(pl, st) : bn->block_end ? launch_window_bwd_data_block_end(pl, st) : launch_window_bwd_data_stats(pl, st);
+  } else if (op == JZ_FWD) rc = epilogue_stats ? launch_fwd_stats(pl, st) : launch_fwd(pl, st);
   else if (op == JZ_BWD_DATA) rc = !epilogue_stats ? launch_bwd_data(pl, st) : bn->block_end ? launch_bwd_data_block_end(pl, st) : launch_bwd_data_stats(pl, st);
   else rc = launch_bwd_weight(pl, st);
   if (rc != JZ_OK) return rc;
@@ -1476,6 +1536,12 @@ extern "C" int jz_conv2d_tune_set(int op, const jz_conv_desc* desc, int tile_m, 
   const Variant* v = nullptr;
   for (const Variant& c : kVariants)
     if (c.BM == tile_m && c.BN == tile_n && c.bk == k_tile && c.waves == wavefronts && c.nst == ring) v = &c;
+  Variant window{};
+  for (const WindowVariant& c : kWindows)
+    if (c.BM == tile_m && c.BN == tile_n && c.ck == k_tile && c.waves == wavefronts && c.nst + kWindowRing == ring && window_fits(pl, c)) {
+      window.BM = c.BM; window.BN = c.BN; window.bk = c.ck; window.waves = c.waves; window.nst = ring;
+      v = &window;
+    }
   if (!v) return JZ_ERR_UNSUPPORTED;
   if (pl.classes) {  // the variant goes to every parity class's launch (their reductions are never split)
     std::vector<Tuned> keys;

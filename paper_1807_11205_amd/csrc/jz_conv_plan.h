@@ -28,6 +28,10 @@ struct Plan {
   int BM = 128, BN = 128;
   int bk = 64;  // k tile depth of the kernel that will run
   int waves = 4, nst = 4;  // wavefronts per workgroup and ring depth (large tiles come in several variants)
+  int window = 0;          // entry of kWindows + 1: runs on the window kernel (jz_window.h)
+  struct {
+    int BM, BN, bk, waves, nst, tiles_m, tiles_n, nkt;
+  } replaced{};            // the ring kernel's variant that it stands in for, unless chosen by hand
   GemmArgs args{};
   size_t ws_bytes = 0;       // total workspace
   size_t part_offset = 0;    // where the split-K partial sums start inside it
@@ -38,6 +42,17 @@ struct Plan {
   int Hp = 0, Wp = 0, KT = 0;
   size_t xp_bytes = 0, wp_bytes = 0;
 };
+
+// Variants of the window kernel: tile, channels of a window (the k tile), wavefronts, filter ring, rows and number of windows
+struct WindowVariant {
+  int BM, BN, ck, waves, nst, rows, windows;
+};
+constexpr WindowVariant kWindows[] = {
+    {256, 128, 64, 8, 3, 384, 2},
+    {256, 64, 64, 4, 3, 384, 1},
+};
+constexpr int kNumWindows = sizeof(kWindows) / sizeof(kWindows[0]);
+constexpr int kWindowRing = 16;  // added to the ring depth where a window variant is named (jz_conv2d_tune_set)
 
 // Small-channel forward layer on the patch kernel: the padded 4-channel copy, the filter repacked as
 // wq[R][NKS * 2][K][8 halves], blocks of 128 * TM consecutive output pixels of one image.
@@ -62,6 +77,12 @@ int launch_fwd_stats(const Plan& pl, hipStream_t st);  // forward that also leav
 int launch_bwd_data_stats(const Plan& pl, hipStream_t st);  // backward-data that also leaves batch-norm backward sums
 int launch_bwd_data_block_end(const Plan& pl, hipStream_t st);  // ... of the block-end gradient it forms from its tile
 int launch_bwd_data(const Plan& pl, hipStream_t st, const GemmSet* set = nullptr);  // set: these GEMMs instead of the plan's own
+// the same on the window kernel
+int launch_window_fwd(const Plan& pl, hipStream_t st);
+int launch_window_fwd_stats(const Plan& pl, hipStream_t st);
+int launch_window_bwd_data(const Plan& pl, hipStream_t st);
+int launch_window_bwd_data_stats(const Plan& pl, hipStream_t st);
+int launch_window_bwd_data_block_end(const Plan& pl, hipStream_t st);
 int launch_bwd_weight(const Plan& pl, hipStream_t st);
 int launch_bwd_weight_set(const Plan& variant, const WgradSet& set, hipStream_t st);  // one of the variants choose_set offers
 
