@@ -10,6 +10,8 @@ from typing import Optional, Sequence
 import numpy as np
 import torch
 
+from . import _jz_host as _host      # built beside libjz.so; there is no fallback here either
+
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.environ.get("JZ_LIB_PATH", os.path.join(_PKG, "libjz.so"))
 
@@ -178,6 +180,9 @@ def conv_desc(N, H, W, C, K, R, S, stride=1, pad=0) -> jz_conv_desc:
 def _dev_ptr(t: Optional[torch.Tensor], dtype, numel=None, what="tensor") -> Optional[int]:
     if t is None:
         return None
+    p = _host.ptr(t, dtype, numel)
+    if p is not None:
+        return p
     if not t.is_cuda or t.dtype != dtype or not t.is_contiguous():
         raise TypeError("%s must be a contiguous %s tensor on the GPU" % (what, dtype))
     if numel is not None and t.numel() != numel:
@@ -188,6 +193,9 @@ def _dev_ptr(t: Optional[torch.Tensor], dtype, numel=None, what="tensor") -> Opt
 def _ws(ws: Optional[torch.Tensor]):
     if ws is None:
         return None, 0
+    p = _host.ws(ws)
+    if p is not None:
+        return p
     if not ws.is_cuda or not ws.is_contiguous():
         raise TypeError("workspace must be a contiguous GPU tensor")
     return ws.data_ptr(), ws.numel() * ws.element_size()
@@ -294,7 +302,31 @@ def jz_bn_tune_wait(microseconds: int):
     _check(lib().jz_bn_tune_wait(microseconds), "jz_bn_tune_wait")
 
 
+def _address(name: str) -> int:
+    """Where an entry point is."""
+    a = _addresses.get(name)
+    if a is None:
+        a = _addresses[name] = ctypes.cast(getattr(lib(), name), ctypes.c_void_p).value
+    return a
+
+
+_addresses = {}
+_F32_CONV = {JZ_FWD: "jz_conv2d_fwd_f32", JZ_BWD_DATA: "jz_conv2d_bwd_data_f32", JZ_BWD_WEIGHT: "jz_conv2d_bwd_weight_f32"}
+
+
+def _conv(name, op, desc, a, b, out, ws, dtype, stream) -> bool:
+    """The call, in one step where its arguments are plainly in order.  False: nothing was called, the caller looks closer."""
+    st = _host.conv(_address(name), op, desc, a, b, out, ws, dtype, stream, _stream)
+    if st == JZ_OK:
+        return True
+    if st == _host.LOOK:
+        return False
+    raise JzError(st, "jz_conv2d_f32" if dtype is torch.float32 else name)
+
+
 def jz_conv2d_fwd(desc, x16, w16, y16, ws=None, stream=None):
+    if _conv("jz_conv2d_fwd", JZ_FWD, desc, x16, w16, y16, ws, torch.float16, stream):
+        return
     d, h = desc, torch.float16
     wp, wn = _ws(ws)
     _check(lib().jz_conv2d_fwd(ctypes.byref(d), _dev_ptr(x16, h, d.N * d.H * d.W * d.C, "x16"),
@@ -303,6 +335,8 @@ def jz_conv2d_fwd(desc, x16, w16, y16, ws=None, stream=None):
 
 
 def jz_conv2d_bwd_data(desc, dy16, w16, dx16, ws=None, stream=None):
+    if _conv("jz_conv2d_bwd_data", JZ_BWD_DATA, desc, dy16, w16, dx16, ws, torch.float16, stream):
+        return
     d, h = desc, torch.float16
     wp, wn = _ws(ws)
     _check(lib().jz_conv2d_bwd_data(ctypes.byref(d), _dev_ptr(dy16, h, d.N * d.P * d.Q * d.K, "dy16"),
@@ -312,6 +346,8 @@ def jz_conv2d_bwd_data(desc, dy16, w16, dx16, ws=None, stream=None):
 
 
 def jz_conv2d_bwd_weight(desc, x16, dy16, dw16, ws=None, stream=None):
+    if _conv("jz_conv2d_bwd_weight", JZ_BWD_WEIGHT, desc, x16, dy16, dw16, ws, torch.float16, stream):
+        return
     d, h = desc, torch.float16
     wp, wn = _ws(ws)
     _check(lib().jz_conv2d_bwd_weight(ctypes.byref(d), _dev_ptr(x16, h, d.N * d.H * d.W * d.C, "x16"),
@@ -329,6 +365,9 @@ def jz_conv2d_f32_workspace_bytes(op: int, desc: jz_conv_desc) -> int:
 
 def jz_conv2d_f32(op: int, desc: jz_conv_desc, a32, b32, out32, ws=None, stream=None):
     """op JZ_FWD: (x, w) -> y; JZ_BWD_DATA: (dy, w) -> dx; JZ_BWD_WEIGHT: (x, dy) -> dw; float32 GPU tensors."""
+    name = _F32_CONV.get(op)
+    if name and _conv(name, op, desc, a32, b32, out32, ws, torch.float32, stream):
+        return
     d, f = desc, torch.float32
     nx, ny, nw = d.N * d.H * d.W * d.C, d.N * d.P * d.Q * d.K, d.K * d.R * d.S * d.C
     na, nb, no = {JZ_FWD: (nx, nw, ny), JZ_BWD_DATA: (ny, nw, nx), JZ_BWD_WEIGHT: (nx, ny, nw)}[op]
@@ -378,17 +417,38 @@ def jz_conv2d_bwd_weight_static(desc, x16, dy16, dw16, stream=None):
            "jz_conv2d_bwd_weight_static")
 
 
+def _words(args):
+    """The arguments as integers and addresses (args keeps what they point to), None where one of them is neither."""
+    w = []
+    for a in args:
+        if a is None:
+            w.append(0)
+        elif isinstance(a, int):
+            w.append(a)
+        elif isinstance(a, ctypes.Array):
+            w.append(ctypes.addressof(a))
+        elif hasattr(a, "_obj"):                # ctypes.byref
+            w.append(ctypes.addressof(a._obj))
+        else:
+            return None
+    return tuple(w) if len(w) <= 24 else None
+
+
 class BoundCall:
     """One entry-point call with its arguments already marshalled: `call(stream)` enqueues it again without
     re-validating the tensors (they are kept alive here).  For launch loops that repeat the same calls every step."""
 
-    __slots__ = ("fn", "args", "where", "keep")
+    __slots__ = ("fn", "args", "where", "keep", "address", "words")
 
     def __init__(self, fn, args, where, keep):
         self.fn, self.args, self.where, self.keep = fn, args, where, keep
+        self.address, self.words = ctypes.cast(fn, ctypes.c_void_p).value, _words(args)
 
     def __call__(self, stream=None):
-        st = self.fn(*self.args, _stream(stream))
+        if self.words is not None:
+            st = _host.invoke(self.address, self.words, _stream(stream))
+        else:
+            st = self.fn(*self.args, _stream(stream))
         if st:      # JZ_OK is 0
             raise JzError(st, self.where)
 
@@ -488,12 +548,22 @@ def jz_lars_prepare(ps: ParamSet, ws: torch.Tensor, stream=None):
     _check(lib().jz_lars_prepare(ctypes.byref(ps.c), wp, wn, _stream(stream)), "jz_lars_prepare")
 
 
-def jz_lars_mp_update(ps: ParamSet, hp: jz_lars_hparams, found_inf: torch.Tensor, ws: torch.Tensor, stream=None):
+def _flag(found_inf: torch.Tensor) -> int:
+    p = _host.ptr(found_inf, torch.int32, 1)
+    if p is not None:
+        return p
     if not found_inf.is_cuda or found_inf.dtype != torch.int32 or found_inf.numel() != 1:
         raise TypeError("found_inf must be a one-element int32 GPU tensor")
+    return found_inf.data_ptr()
+
+
+def jz_lars_mp_update(ps: ParamSet, hp: jz_lars_hparams, found_inf: torch.Tensor, ws: torch.Tensor, stream=None):
+    flag = _flag(found_inf)
     wp, wn = _ws(ws)
-    _check(lib().jz_lars_mp_update(ctypes.byref(ps.c), ctypes.byref(hp), found_inf.data_ptr(), wp, wn, _stream(stream)),
-           "jz_lars_mp_update")
+    if isinstance(hp, jz_lars_hparams):
+        words = (ctypes.addressof(ps.c), ctypes.addressof(hp), flag, wp or 0, wn)
+        return _check(_host.invoke(_address("jz_lars_mp_update"), words, _stream(stream)), "jz_lars_mp_update")
+    _check(lib().jz_lars_mp_update(ctypes.byref(ps.c), ctypes.byref(hp), flag, wp, wn, _stream(stream)), "jz_lars_mp_update")
 
 
 def _ls_state(state: torch.Tensor) -> int:

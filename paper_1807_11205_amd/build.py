@@ -1,4 +1,4 @@
-"""Build libjz.so (HIP kernels + C ABI) for gfx950 in-tree: python -m paper_1807_11205_amd.build
+"""Build libjz.so (HIP kernels + C ABI) for gfx950 and the binding's native part in-tree: python -m paper_1807_11205_amd.build
 
 Every csrc/*.hip is compiled to an object of its own, in parallel, then linked; objects go to a scratch directory
 outside the source tree."""
@@ -6,6 +6,7 @@ import glob
 import os
 import subprocess
 import sys
+import sysconfig
 import tempfile
 from concurrent.futures import ThreadPoolExecutor
 
@@ -13,6 +14,7 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 OUT = os.path.join(PKG, "libjz.so")
+HOST_OUT = os.path.join(PKG, "_jz_host.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -22,6 +24,20 @@ FLAGS = [
     "-Wall", "-Wno-unused-function", "-Wno-cuda-compat",
     "-I", os.path.join(ROOT, "include"), "-I", CSRC,
 ]
+
+
+def build_host(verbose: bool = False) -> str:
+    """csrc/jz_host.cpp, the CPython module the binding imports."""
+    import torch
+    t = os.path.dirname(os.path.abspath(torch.__file__))
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-I", os.path.join(ROOT, "include"),
+           "-I", sysconfig.get_paths()["include"], "-isystem", os.path.join(t, "include"),
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), "-o", HOST_OUT, os.path.join(CSRC, "jz_host.cpp"),
+           "-L", os.path.join(t, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    return HOST_OUT
 
 
 def build(verbose: bool = False, extra=()) -> str:
@@ -36,8 +52,10 @@ def build(verbose: bool = False, extra=()) -> str:
             subprocess.run(cmd, check=True)
             return obj
 
-        with ThreadPoolExecutor(jobs) as pool:
+        with ThreadPoolExecutor(jobs + 1) as pool:
+            host = pool.submit(build_host, verbose)
             objs = list(pool.map(compile_one, srcs))
+            host.result()
         link = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-fno-gpu-rdc", "-o", OUT, *objs]
         if verbose:
             print(" ".join(link), flush=True)
