@@ -316,6 +316,8 @@ _F32_CONV = {JZ_FWD: "jz_conv2d_fwd_f32", JZ_BWD_DATA: "jz_conv2d_bwd_data_f32",
 
 def _conv(name, op, desc, a, b, out, ws, dtype, stream) -> bool:
     """The call, in one step where its arguments are plainly in order.  False: nothing was called, the caller looks closer."""
+    if type(desc) is not jz_conv_desc:          # native code takes any buffer of its size
+        return False
     st = _host.conv(_address(name), op, desc, a, b, out, ws, dtype, stream, _stream)
     if st == JZ_OK:
         return True

@@ -27,6 +27,8 @@ def test_tensors_that_are_not_plainly_in_order_are_left_alone():
     for call, a in ((api.jz_conv2d_fwd, (x, w, x)), (api.jz_conv2d_bwd_data, (x, w, x)), (api.jz_conv2d_bwd_weight, (x, x, w))):
         with pytest.raises(TypeError, match="must be a contiguous"):
             call(d, *a)
+        with pytest.raises(TypeError, match="ctypes instance"):     # the descriptor's bytes are not a descriptor
+            call(bytes(d), *a)
 
 
 def test_bound_calls_pass_every_kind_of_argument():
