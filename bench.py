@@ -543,11 +543,11 @@ def bn_workload(args):
         "dtype": "f16 storage, f32 statistics (f64 across slabs)", "data": "synthetic",
         "config": {"workload": "the 53 batch-normalization + ReLU layers of ResNet-50 v1 (training mode), forward then backward, "
                                "independent seeded inputs", "batch": B, "elements_per_pass": elems, "launch": "eager", "streams": 1},
-        "roofline": {"kernel": "bn_stats / bn_apply / bn_bwd_apply (6 launches per layer)", "bound": "hbm", "achieved": gbps,
+        "roofline": {"kernel": "bn_whole (a launch for each direction of a layer)", "bound": "hbm", "achieved": gbps,
                      "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": gbps / HBM_PEAK_GBPS,
                      "traffic": None,
                      "traffic_note": "not measured in this run; profiles/bench_bn_resnet50_n64_kernel_stats.txt holds the HBM-counter "
-                                     "summary of this workload (20.9 bytes per element moved against 12 algorithmic when it was taken)",
+                                     "summary of this workload (12.9 bytes per element moved against 12 algorithmic when it was taken)",
                      "bytes_per_element": 12}}))
 
 
