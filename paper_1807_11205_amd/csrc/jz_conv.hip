@@ -727,6 +727,16 @@ bool window_fits(const Plan& pl, const WindowVariant& v) {
          (v.windows > 1 || g.IC == v.ck) && (long long)v.BM + (long long)(g.R - 1) * g.IW + g.S - 1 <= v.rows;
 }
 
+// The entry (+ 1) that a recorded window variant names, 0 where it does not take this problem.  A key does not hold the image's width, the stride
+// or the padding, which decide that: layers share keys that the variant takes and that it does not.
+int recorded_window(const Plan& pl, const Tuned& t) {
+  for (int i = 0; i < kNumWindows; ++i) {
+    const WindowVariant& v = kWindows[i];
+    if (v.BM == t.BM && v.BN == t.BN && v.ck == t.bk && v.waves == t.waves && v.nst + kWindowRing == t.nst && window_fits(pl, v)) return i + 1;
+  }
+  return 0;
+}
+
 // The window kernel's entry (+ 1) for a plan that the tables or the cost model have made for the ring kernels, or 0.  From 90 random layers (3x3 and
 // 5x5, 64 ... 512 channels, images of 7 ... 63 pixels, 5 ... 3300 tiles), both directions, time against the ring kernel's:
 //   more than 64 channels in, the plan is 256x128 tiles: 0.76 ... 1.006, median 0.95 (fewer bytes into LDS at the same tile);
@@ -760,6 +770,7 @@ void choose_tiling(Plan* pl, bool bk64_ok, int forced_bk, bool tables = true) {
     const Tuned key{oi, a.M, a.N, a.Kred, a.g.R * a.g.S, a.sc_on, 0, 0, 0, 0, 0, 0};
     auto usable = [&](const Tuned& t) {
       if ((pl->gen || pl->flat) && (t.waves != 4 || t.bk != 32 || t.nst != 4 || t.BM > 128 || t.BN > 128)) return false;  // the only kernels of those modes
+      if (t.nst > kWindowRing && recorded_window(*pl, t) == 0) return false;
       return same_key(t, key) && (forced_bk ? t.bk == forced_bk : (t.bk == 32 || bk64_ok));
     };
     bool use_table;
@@ -813,10 +824,7 @@ void choose_tiling(Plan* pl, bool bk64_ok, int forced_bk, bool tables = true) {
     pl->nst = hit->nst;
     if (hit->nst > kWindowRing) {
       pl->nst -= kWindowRing;
-      for (int i = 0; i < kNumWindows; ++i) {
-        const WindowVariant& v = kWindows[i];
-        if (v.BM == pl->BM && v.BN == pl->BN && v.ck == pl->bk && v.waves == pl->waves && v.nst == pl->nst && window_fits(*pl, v)) pl->window = i + 1;
-      }
+      pl->window = recorded_window(*pl, *hit);
     }
     bS = hit->splits;
     const int nkt_h = (a.Kred + hit->bk - 1) / hit->bk;

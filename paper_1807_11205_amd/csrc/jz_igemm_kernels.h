@@ -523,7 +523,8 @@ int launch_op(const Plan& pl, hipStream_t st, const GemmSet* set = nullptr) {
       if (pl.BM == 128 && pl.BN == 128) return launch_dma<OP, 128, 128, 32, 4, false, 2, 2, true>(a, st);
       if (pl.BM == 128 && pl.BN == 64) return launch_dma<OP, 128, 64, 32, 4, false, 2, 2, true>(a, st);
       if (pl.BM == 64 && pl.BN == 128) return launch_dma<OP, 64, 128, 32, 4, false, 2, 2, true>(a, st);
-      return launch_dma<OP, 64, 64, 32, 4, false, 2, 2, true>(a, st);
+      if (pl.BM == 64 && pl.BN == 64) return launch_dma<OP, 64, 64, 32, 4, false, 2, 2, true>(a, st);
+      return JZ_ERR_UNSUPPORTED;
     }
   }
   if constexpr (OP == OP_FWD || OP == OP_BWD_DATA) {
@@ -531,7 +532,8 @@ int launch_op(const Plan& pl, hipStream_t st, const GemmSet* set = nullptr) {
       if (pl.BM == 128 && pl.BN == 128) return launch_dma<OP, 128, 128, 32, 4, false, 2, 2, false, true>(a, st, set);
       if (pl.BM == 128 && pl.BN == 64) return launch_dma<OP, 128, 64, 32, 4, false, 2, 2, false, true>(a, st, set);
       if (pl.BM == 64 && pl.BN == 128) return launch_dma<OP, 64, 128, 32, 4, false, 2, 2, false, true>(a, st, set);
-      return launch_dma<OP, 64, 64, 32, 4, false, 2, 2, false, true>(a, st, set);
+      if (pl.BM == 64 && pl.BN == 64) return launch_dma<OP, 64, 64, 32, 4, false, 2, 2, false, true>(a, st, set);
+      return JZ_ERR_UNSUPPORTED;
     }
   }
   // large tiles, one workgroup of 8 wavefronts per compute unit with (nearly) the whole LDS as its ring
@@ -546,18 +548,21 @@ int launch_op(const Plan& pl, hipStream_t st, const GemmSet* set = nullptr) {
     if (pl.BM == 128 && pl.BN == 128) return launch_dma<OP, 128, 128, 64, 4>(a, st, set);
     if (pl.BM == 128 && pl.BN == 64) return launch_dma<OP, 128, 64, 64, 4>(a, st, set);
     if (pl.BM == 64 && pl.BN == 128) return launch_dma<OP, 64, 128, 64, 4>(a, st, set);
-    return launch_dma<OP, 64, 64, 64, 4>(a, st, set);
+    if (pl.BM == 64 && pl.BN == 64) return launch_dma<OP, 64, 64, 64, 4>(a, st, set);
+    return JZ_ERR_UNSUPPORTED;
   }
   if (pl.nst == 3) {
     if (pl.BM == 128 && pl.BN == 128) return launch_dma<OP, 128, 128, 32, 3>(a, st, set);
     if (pl.BM == 128 && pl.BN == 64) return launch_dma<OP, 128, 64, 32, 3>(a, st, set);
     if (pl.BM == 64 && pl.BN == 128) return launch_dma<OP, 64, 128, 32, 3>(a, st, set);
-    return launch_dma<OP, 64, 64, 32, 3>(a, st, set);
+    if (pl.BM == 64 && pl.BN == 64) return launch_dma<OP, 64, 64, 32, 3>(a, st, set);
+    return JZ_ERR_UNSUPPORTED;
   }
   if (pl.BM == 128 && pl.BN == 128) return launch_dma<OP, 128, 128, 32, 4>(a, st, set);
   if (pl.BM == 128 && pl.BN == 64) return launch_dma<OP, 128, 64, 32, 4>(a, st, set);
   if (pl.BM == 64 && pl.BN == 128) return launch_dma<OP, 64, 128, 32, 4>(a, st, set);
-  return launch_dma<OP, 64, 64, 32, 4>(a, st, set);
+  if (pl.BM == 64 && pl.BN == 64) return launch_dma<OP, 64, 64, 32, 4>(a, st, set);
+  return JZ_ERR_UNSUPPORTED;
 }
 
 }  // namespace

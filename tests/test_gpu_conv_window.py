@@ -25,6 +25,26 @@ def test_which_layers_run_on_it():
     assert "window" not in plan(api.JZ_BWD_WEIGHT, 64, 56, 56, 64, 64, 3, 3, 1, 1)
 
 
+@pytest.mark.parametrize("variant,fits,others", [
+    (NARROW, (64, 56, 56, 64, 64, 3, 3, 1, 1), [(16, 112, 112, 64, 64, 3, 3, 1, 1), (64, 112, 112, 64, 64, 3, 3, 2, 1), (64, 58, 58, 64, 64, 3, 3, 1, 0)]),
+    (WIDE, (16, 28, 28, 128, 128, 3, 3, 1, 1), [(1, 112, 112, 128, 128, 3, 3, 1, 1), (16, 30, 30, 128, 128, 3, 3, 1, 0)]),
+])
+def test_a_recorded_variant_is_for_layers_that_it_takes(variant, fits, others):
+    """Layers of the same pixels, channels and taps share a recorded choice; those whose width, stride or padding the window kernel
+    does not take have the plan that they have without it."""
+    for op in (api.JZ_FWD, api.JZ_BWD_DATA):
+        ones = [o for o in others if op == api.JZ_FWD or o[8] == fits[8] and o[7] == 1]     # backward-data: the pixels of the input count
+        before = [plan(op, *o) for o in ones]
+        try:
+            api.jz_conv2d_tune_set(op, api.conv_desc(*fits), *variant, 1)
+            assert ": window tile %dx%dx%d, %d wavefronts, ring %d" % variant in plan(op, *fits)
+            for o, b in zip(ones, before):
+                assert plan(op, *o).split(":")[0] == plan(op, *fits).split(":")[0], "another key"
+                assert plan(op, *o) == b, o
+        finally:
+            api.jz_conv2d_tune_clear()
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("variant,N,H,W,C,K,R", [
     (NARROW, 1, 4, 3, 64, 64, 3),        # 12 pixels: less than a fragment; the filter covers the image
