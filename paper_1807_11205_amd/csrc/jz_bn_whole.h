@@ -297,9 +297,9 @@ __global__ __launch_bounds__(BW_THREADS) void bn_whole(BnWholeArgs a) {
 
   // ---- the exchange -----------------------------------------------------------------------------------------------------
   unsigned long long* const flags = a.flags + (size_t)group * a.wgs;
+  if constexpr (MODE == BW_END) bw_performed();  // g_out too: if this workgroup leaves, another reads it
+  __syncthreads();  // also where no other workgroup has rows: two wavefronts have left the sums that any of them reads
   if (a.wgs > 1) {
-    if constexpr (MODE == BW_END) bw_performed();  // g_out too: if this workgroup leaves, another reads it
-    __syncthreads();
     if (tid < 64) {  // the first wavefront looks, each lane at up to four flags
       constexpr int F = BW_WGS / 64;
       unsigned long long v[F];

@@ -101,7 +101,9 @@ def _graph_run(c, o):
 
 # 256 workgroups of 64 channels each, a pass of 64 rows: rows = passes * 64 * 256 / (C / 64) fill the chip
 FULL = [(p * 64 * (256 // (C // 64)), C) for p, C in ((4, 2048), (8, 1024), (14, 512), (25, 256))]
-SIZES = [(1, 64), (63, 64), (64, 128), (65, 64), (129, 2048), (1000, 192), (777, 320), (4099, 1984)] + [(r + d, C) for r, C in FULL for d in (0, 1)]
+SIZES = [(1, 64), (63, 64), (64, 128), (65, 64), (129, 2048), (1000, 192), (777, 320), (4099, 1984),
+         (49, 2048), (64, 1024), (37, 512)]   # one workgroup has all rows of its channels: its wavefronts wait for each other's sums
+SIZES += [(r + d, C) for r, C in FULL for d in (0, 1)]
 
 
 @pytest.mark.parametrize("rows,C", SIZES)
