@@ -412,7 +412,8 @@ int jz_softmax_xent_bwd(int rows, int classes, const void* z16, const int* label
  *       reads y16 twice); contents need not survive between the forward and the backward call
  * jz_bn_relu_fwd: y = gamma * (x - mean) * invstd + beta, then max(., 0) when relu != 0, rounded once to FP16; writes the
  *   statistics it used (invstd = 1 / sqrt(var + eps)) to save_mean / save_invstd.  Sums run over at
- *   most 512 slabs of rows: FP32 within a lane, FP64 between lanes, rounded to FP32 once a slab, FP64 across slabs, in an order that
+ *   most 512 slabs of rows: FP32 within a lane, FP64 between lanes, rounded to FP32 once a slab (never where channels is a multiple of 64 and
+ *   one launch can do it all; backward FP32 between the lanes of the other slabs), FP64 across slabs, in an order that
  *   depends only on (rows, channels): results are deterministic.
  * jz_bn_relu_bwd: with g = dy (relu == 0) or dy where y16 > 0 and 0 elsewhere (relu != 0; y16 is the forward output):
  *   dbeta = sum g, dgamma = sum g * x^, dx = gamma * invstd * (g - dbeta / rows - x^ * dgamma / rows).  y16 may be NULL

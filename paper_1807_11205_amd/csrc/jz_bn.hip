@@ -1,8 +1,8 @@
 // Training-mode batch normalization with an optional ReLU, forward and backward, for gfx950 (Jia et al. 2018,
 // Section 4.2: x^ = (x - mean_B) / sqrt(var_B + eps), y = gamma x^ + beta, statistics per channel over the mini-batch).
 //
-// Activations are FP16 [rows][C] (NHWC with rows = N*H*W), gamma / beta / the saved statistics FP32, all sums FP32 per
-// workgroup slab and FP64 across slabs.  Every pass is bound by HBM, so each direction is three stream-ordered launches:
+// Activations are FP16 [rows][C] (NHWC with rows = N*H*W), gamma / beta / the saved statistics FP32, sums FP32 per
+// workgroup slab (FP64 for bn_whole's slabs, which are longer) and FP64 across slabs.  Every pass is bound by HBM, so each direction is three stream-ordered launches:
 //
 //   forward   bn_stats      a workgroup owns a slab of rows: per channel sum(x) and sum(x^2) of the slab (no atomics)
 //             bn_fwd_final  per channel: the slabs' sums added in a fixed order in FP64 -> mean, 1/sqrt(var + eps), and the
@@ -63,8 +63,7 @@ struct BnPlan {
   int rpp = 0;               // rows one pass of a workgroup covers (threads / (cpr / csplit); lanes beyond that idle)
   int64_t rows_per_slab = 0; // a multiple of rpp
   int slabs = 0;
-  size_t off_part = 0, off_coef = 0, total = 0;  // workspace: [slabs][2][C] float partial sums, [4][C] float coefficients
-  size_t off_flags = 0;      // between them, for bn_whole: a word a workgroup
+  size_t off_part = 0, off_coef = 0, total = 0;  // workspace: [slabs][2][C] partial sums, [4][C] float coefficients (bn_whole: its flags, a word a workgroup)
   int mask_iters = 0;        // words of it a lane of the statistics pass has
   size_t mask_bytes = 0;     // behind them, if there is room: one bit per element, the backward pass's ReLU mask
 };
@@ -166,10 +165,14 @@ struct BnStatsArgs {
   uint4* g_out;
   unsigned* mask;
   const float *mean, *invstd;
-  float* part;
+  void* part;  // BnSum
   int64_t rows, rows_per_slab;
   int C, cpr, rpp, csplit, mask_iters;
 };
+// What a slab's sums are stored as.  bn_whole's slabs are up to 16 times as long as the others: in FP32 they would be less exact
+// (mean over 12544 x 1024, deviations from FP64 in standard deviations: 3.2e-10, in FP64 2.4e-10, FP32 and the other slabs 2.5e-10).
+template <bool WHOLE>
+using BnSum = std::conditional_t<WHOLE, double, float>;
 template <int MODE, int T>
 __global__ __launch_bounds__(T) void bn_stats(BnStatsArgs a) {
   __shared__ __align__(16) float red[2][T][8];
@@ -271,7 +274,9 @@ __global__ __launch_bounds__(T) void bn_stats(BnStatsArgs a) {
   // threads (the lanes of one row adding up the others': 8.7 instead of 7.5 us for 200704 x 64).  The forward sums in FP64: where
   // rows are shared by workgroups a slab has four times as many, and FP32 would make the variance of channels far from zero less exact
   // than with small slabs (12544 x 256, mean 10 std: relative error 5.3e-7, in FP64 3.2e-7; FP32 and slabs of 32 rows: 3.2e-7).
-  using Acc = std::conditional_t<GRAD, float, double>;
+  // The gradients' too where bn_whole's slabs are summed.
+  using Part = BnSum<T != BN_THREADS>;
+  using Acc = std::conditional_t<GRAD, Part, double>;
   const int ch = 8 * cpr_l, sums = 2 * ch;  // red[0] and red[1] are [rows of a pass][ch]
   const float* const r0s = &red[0][0][0];
   const float* const r1s = &red[1][0][0];
@@ -281,13 +286,13 @@ __global__ __launch_bounds__(T) void bn_stats(BnStatsArgs a) {
     *reinterpret_cast<float4*>(&red[1][tid][e]) = make_float4(s1[e], s1[e + 1], s1[e + 2], s1[e + 3]);
   }
   __syncthreads();
-  float* const out = a.part + (size_t)slab * 2 * C + cfirst * 8;
+  Part* const out = static_cast<Part*>(a.part) + (size_t)slab * 2 * C + cfirst * 8;
   if (sums >= T) {
     for (int i = tid; i < sums; i += T) {
       const float* p = i < ch ? r0s + i : r1s + (i - ch);
       Acc t = 0;
       for (int j = 0; j < rpp; ++j) t += p[j * ch];
-      out[i < ch ? i : C + i - ch] = (float)t;
+      out[i < ch ? i : C + i - ch] = (Part)t;
     }
     return;
   }
@@ -304,7 +309,7 @@ __global__ __launch_bounds__(T) void bn_stats(BnStatsArgs a) {
   if (tid < sums) {
     t = 0;
     for (int k = 0; k < parts; ++k) t += part_sums[k * sums + tid];
-    out[tid < ch ? tid : C + tid - ch] = (float)t;
+    out[tid < ch ? tid : C + tid - ch] = (Part)t;
   }
 }
 
@@ -313,7 +318,8 @@ __device__ __forceinline__ int bn_lanes(int slabs) { return slabs < BN_FIN_LANES
 
 // The two sums of channel c over all slabs, FP64: lane js of the channel's 32 lanes adds slabs js, js + 32, ... in that order,
 // then lane 0 adds the 32 lane sums in lane order (deterministic).  Returns true on the lane that holds the totals.
-__device__ __forceinline__ bool bn_slab_totals(const float* __restrict__ part, int slabs, int C, int c, double& s, double& q) {
+template <class P>
+__device__ __forceinline__ bool bn_slab_totals(const P* __restrict__ part, int slabs, int C, int c, double& s, double& q) {
   __shared__ double red[2][BN_THREADS];
   constexpr int LANES = BN_FIN_LANES;
   const int js = threadIdx.x / BN_FIN_C;
@@ -321,7 +327,7 @@ __device__ __forceinline__ bool bn_slab_totals(const float* __restrict__ part, i
   q = 0.0;
   if (c < C)
     for (int k = js; k < slabs; k += 8 * LANES) {  // eight slabs' sums requested together, added in slab order
-      float a[8], b[8];
+      P a[8], b[8];
 #pragma unroll
       for (int u = 0; u < 8; ++u) {  // all sixteen loads first (clamped index), the selection afterwards
         const int ku = k + u * LANES;
@@ -332,8 +338,8 @@ __device__ __forceinline__ bool bn_slab_totals(const float* __restrict__ part, i
 #pragma unroll
       for (int u = 0; u < 8; ++u)
         if (k + u * LANES >= slabs) {
-          a[u] = 0.f;
-          b[u] = 0.f;
+          a[u] = 0;
+          b[u] = 0;
         }
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
@@ -352,7 +358,8 @@ __device__ __forceinline__ bool bn_slab_totals(const float* __restrict__ part, i
   return true;
 }
 
-__global__ __launch_bounds__(BN_THREADS) void bn_fwd_final(const float* __restrict__ part, int slabs, int C, double inv_rows,
+template <class P>
+__global__ __launch_bounds__(BN_THREADS) void bn_fwd_final(const P* __restrict__ part, int slabs, int C, double inv_rows,
                                                           float eps, const float* __restrict__ gamma,
                                                           const float* __restrict__ beta, float* __restrict__ save_mean,
                                                           float* __restrict__ save_invstd, float* __restrict__ coef) {
@@ -389,7 +396,8 @@ __global__ __launch_bounds__(BN_THREADS) void bn_apply(const uint4* __restrict__
   }
 }
 
-__global__ __launch_bounds__(BN_THREADS) void bn_bwd_final(const float* __restrict__ part, int slabs, int C, double inv_rows,
+template <class P>
+__global__ __launch_bounds__(BN_THREADS) void bn_bwd_final(const P* __restrict__ part, int slabs, int C, double inv_rows,
                                                           const float* __restrict__ gamma, const float* __restrict__ mean,
                                                           const float* __restrict__ invstd, unsigned short* __restrict__ dgamma16,
                                                           unsigned short* __restrict__ dbeta16, float* __restrict__ coef) {
@@ -530,7 +538,7 @@ __device__ __forceinline__ bool bn_merged_totals(const float* __restrict__ part,
 // The same in bn_slab_totals' order, which is bn_whole's: for tensors that it takes where it may run.  A thread stands for 32 / (T / 64) of
 // the channel's 32 lanes.  (For all tensors it made the 8 x 64 x 64 training step 1.6 % slower.)
 template <int T>
-__device__ __forceinline__ bool bn_merged_totals_32(const float* __restrict__ part, int slabs, int C, int first, double& s, double& q) {
+__device__ __forceinline__ bool bn_merged_totals_32(const double* __restrict__ part, int slabs, int C, int first, double& s, double& q) {
   constexpr int THREADS = T / BM_CH, OWN = BN_FIN_LANES / THREADS;
   __shared__ double red[2][BN_FIN_LANES][BM_CH];
   const int cl = threadIdx.x & (BM_CH - 1), c = first + cl, j = __builtin_amdgcn_readfirstlane(threadIdx.x / BM_CH);
@@ -539,10 +547,10 @@ __device__ __forceinline__ bool bn_merged_totals_32(const float* __restrict__ pa
   for (int o = 0; o < OWN; ++o) ts[o] = tq[o] = 0.0;
   if (c < C)
     for (int k = j; k < slabs; k += BN_FIN_LANES) {  // OWN slabs' sums requested together
-      float a[OWN], b[OWN];
+      double a[OWN], b[OWN];
 #pragma unroll
       for (int o = 0; o < OWN; ++o) {
-        a[o] = b[o] = 0.f;
+        a[o] = b[o] = 0.0;
         if (k + THREADS * o < slabs) {
           a[o] = part[((size_t)(k + THREADS * o) * 2) * C + c];
           b[o] = part[((size_t)(k + THREADS * o) * 2 + 1) * C + c];
@@ -550,8 +558,8 @@ __device__ __forceinline__ bool bn_merged_totals_32(const float* __restrict__ pa
       }
 #pragma unroll
       for (int o = 0; o < OWN; ++o) {
-        ts[o] += (double)a[o];
-        tq[o] += (double)b[o];
+        ts[o] += a[o];
+        tq[o] += b[o];
       }
     }
 #pragma unroll
@@ -580,7 +588,7 @@ __device__ __forceinline__ bool bn_merged_totals_32(const float* __restrict__ pa
 
 template <int RES, int T, bool WHOLE = false>
 __global__ __launch_bounds__(T) void bn_apply_merged(const uint4* __restrict__ x, const uint4* __restrict__ res, uint4* __restrict__ y,
-                                                             int64_t rows, int rows_per_wg, int C, const float* __restrict__ part, int slabs,
+                                                             int64_t rows, int rows_per_wg, int C, const BnSum<WHOLE>* __restrict__ part, int slabs,
                                                              double inv_rows, float eps, int relu, const float* __restrict__ gamma,
                                                              const float* __restrict__ beta, float* __restrict__ save_mean,
                                                              float* __restrict__ save_invstd) {
@@ -603,7 +611,10 @@ __global__ __launch_bounds__(T) void bn_apply_merged(const uint4* __restrict__ x
   };
   fetch(r0 + rsub);
   double s, sq;
-  if (WHOLE ? bn_merged_totals_32<T>(part, slabs, C, first, s, sq) : bn_merged_totals<T>(part, slabs, C, first, s, sq)) {
+  bool has;
+  if constexpr (WHOLE) has = bn_merged_totals_32<T>(part, slabs, C, first, s, sq);
+  else has = bn_merged_totals<T>(part, slabs, C, first, s, sq);
+  if (has) {
     const int c = first + threadIdx.x;
     const bool writer = blockIdx.y == 0;
     bn_fwd_coef(s, sq, inv_rows, eps, gamma[c], beta[c], writer ? save_mean + c : nullptr, writer ? save_invstd + c : nullptr,
@@ -642,7 +653,7 @@ __global__ __launch_bounds__(T) void bn_apply_merged(const uint4* __restrict__ x
 template <bool WHOLE>
 __global__ __launch_bounds__(BN_THREADS) void bn_bwd_apply_merged(const uint4* __restrict__ x, const uint4* __restrict__ y,
                                                                  const uint4* __restrict__ dy, uint4* __restrict__ dx, int64_t rows,
-                                                                 int rows_per_wg, int C, const float* __restrict__ part, int slabs,
+                                                                 int rows_per_wg, int C, const BnSum<WHOLE>* __restrict__ part, int slabs,
                                                                  double inv_rows, int relu, const float* __restrict__ gamma,
                                                                  const float* __restrict__ mean, const float* __restrict__ invstd,
                                                                  unsigned short* __restrict__ dgamma16, unsigned short* __restrict__ dbeta16) {
@@ -666,7 +677,10 @@ __global__ __launch_bounds__(BN_THREADS) void bn_bwd_apply_merged(const uint4* _
   };
   fetch(r0 + rsub);
   double sb, sg;
-  if (WHOLE ? bn_merged_totals_32<BN_THREADS>(part, slabs, C, first, sb, sg) : bn_merged_totals<BN_THREADS>(part, slabs, C, first, sb, sg)) {
+  bool has;
+  if constexpr (WHOLE) has = bn_merged_totals_32<BN_THREADS>(part, slabs, C, first, sb, sg);
+  else has = bn_merged_totals<BN_THREADS>(part, slabs, C, first, sb, sg);
+  if (has) {
     const int c = first + threadIdx.x;
     const bool writer = blockIdx.y == 0;
     bn_bwd_coef(sb, sg, inv_rows, gamma[c], mean[c], invstd[c], writer ? dgamma16 + c : nullptr, writer ? dbeta16 + c : nullptr,
@@ -727,9 +741,9 @@ bool make_whole_plan(int64_t rows, int C, bool forward, size_t room, BnPlan* p) 
   p->off_part = 0;
   for (;; per += BW_ROWS) {  // fewer workgroups where there is no room for the sums of more
     p->slabs = (int)((rows + per - 1) / per);
-    p->off_flags = up256((size_t)p->slabs * 2 * C * sizeof(float));
-    p->off_coef = up256(p->off_flags + (size_t)p->slabs * groups * sizeof(unsigned long long));
-    p->total = p->off_coef + up256((size_t)4 * C * sizeof(float));
+    p->off_coef = up256((size_t)p->slabs * 2 * C * sizeof(BnSum<true>));
+    const size_t coef = (size_t)4 * C * sizeof(float), flags = (size_t)p->slabs * groups * sizeof(unsigned long long);
+    p->total = p->off_coef + up256(coef > flags ? coef : flags);
     if (p->total <= room) break;
     if (p->slabs == 1) return false;
   }
@@ -791,8 +805,8 @@ int launch_whole(const BnPlan& p, BnWholeArgs a, void* ws, hipStream_t st) {
   a.groups = p.csplit;
   a.wgs = p.slabs;
   a.rows_per_wg = (int)p.rows_per_slab;
-  a.part = reinterpret_cast<float*>(static_cast<char*>(ws) + p.off_part);
-  a.flags = reinterpret_cast<unsigned long long*>(static_cast<char*>(ws) + p.off_flags);
+  a.part = reinterpret_cast<double*>(static_cast<char*>(ws) + p.off_part);
+  a.flags = reinterpret_cast<unsigned long long*>(static_cast<char*>(ws) + p.off_coef);
   a.tag = bw_tag();
   a.wait_ticks = (long long)t_bn_wait_us * 100;
   a.inv_rows = 1.0 / (double)p.rows;
@@ -832,7 +846,7 @@ unsigned apply_grid(int64_t n_chunks) {
 }
 
 template <int MODE>
-int launch_stats(const BnPlan& p, float* part, BnStatsArgs a, hipStream_t st) {
+int launch_stats(const BnPlan& p, void* part, BnStatsArgs a, hipStream_t st) {
   a.part = part;
   a.rows = p.rows; a.rows_per_slab = p.rows_per_slab;
   a.C = p.C; a.cpr = p.cpr; a.rpp = p.rpp; a.csplit = p.csplit; a.mask_iters = p.mask_iters;
@@ -843,23 +857,30 @@ int launch_stats(const BnPlan& p, float* part, BnStatsArgs a, hipStream_t st) {
 }
 
 // what follows the partial sums of the forward pass: totals, saved statistics, y = [relu](a x + b [+ res])
-int launch_fwd_rest(const float* part, int slabs, float* coef, int64_t rows, int C, float eps, int relu, const float* gamma, const float* beta,
+int launch_fwd_rest(const void* part, int slabs, float* coef, int64_t rows, int C, float eps, int relu, const float* gamma, const float* beta,
                     const uint4* x, const uint4* res, uint4* y, float* save_mean, float* save_invstd, hipStream_t st, bool whole = false) {
   const double inv_rows = 1.0 / (double)rows;
-  auto merged = [&](auto kernel, int threads, int wgs) {
+  const float* const part32 = static_cast<const float*>(part);
+  const double* const part64 = static_cast<const double*>(part);
+  auto merged = [&](auto kernel, auto* sums, int threads, int wgs) {
     int per;
     const dim3 grid = merged_grid(rows, C, threads / (BM_CH / 8), wgs, &per);
-    hipLaunchKernelGGL(kernel, grid, dim3((unsigned)threads), 0, st, x, res, y, rows, per, C, part, slabs, inv_rows, eps, relu, gamma, beta, save_mean,
+    hipLaunchKernelGGL(kernel, grid, dim3((unsigned)threads), 0, st, x, res, y, rows, per, C, sums, slabs, inv_rows, eps, relu, gamma, beta, save_mean,
                        save_invstd);
     return jz::launch_status();
   };
   const int64_t nb = rows * C * 2;
   if (slabs <= BN_MERGE_SLABS_WIDE && nb >= BN_WIDE_BYTES && nb <= BN_FEW_SLABS_BYTES)
-    return whole ? merged(bn_apply_merged<0, 512, true>, 512, 512) : res ? merged(bn_apply_merged<1, 512>, 512, 512) : merged(bn_apply_merged<0, 512>, 512, 512);
-  if (slabs <= BN_MERGE_SLABS && whole) return merged(bn_apply_merged<0, BN_THREADS, true>, BN_THREADS, 2048);
-  if (slabs <= BN_MERGE_SLABS) return res ? merged(bn_apply_merged<1, BN_THREADS>, BN_THREADS, 2048) : merged(bn_apply_merged<0, BN_THREADS>, BN_THREADS, 2048);
-  hipLaunchKernelGGL(bn_fwd_final, dim3((unsigned)((C + BN_FIN_C - 1) / BN_FIN_C)), dim3(BN_THREADS), 0, st, part, slabs, C, inv_rows, eps, gamma,
-                     beta, save_mean, save_invstd, coef);
+    return whole ? merged(bn_apply_merged<0, 512, true>, part64, 512, 512)
+           : res ? merged(bn_apply_merged<1, 512>, part32, 512, 512)
+                 : merged(bn_apply_merged<0, 512>, part32, 512, 512);
+  if (slabs <= BN_MERGE_SLABS)
+    return whole ? merged(bn_apply_merged<0, BN_THREADS, true>, part64, BN_THREADS, 2048)
+           : res ? merged(bn_apply_merged<1, BN_THREADS>, part32, BN_THREADS, 2048)
+                 : merged(bn_apply_merged<0, BN_THREADS>, part32, BN_THREADS, 2048);
+  const dim3 fin((unsigned)((C + BN_FIN_C - 1) / BN_FIN_C));
+  if (whole) hipLaunchKernelGGL(bn_fwd_final<double>, fin, dim3(BN_THREADS), 0, st, part64, slabs, C, inv_rows, eps, gamma, beta, save_mean, save_invstd, coef);
+  else hipLaunchKernelGGL(bn_fwd_final<float>, fin, dim3(BN_THREADS), 0, st, part32, slabs, C, inv_rows, eps, gamma, beta, save_mean, save_invstd, coef);
   int rc = jz::launch_status();
   if (rc != JZ_OK) return rc;
   const int64_t n_chunks = rows * (C / 8);
@@ -871,22 +892,29 @@ int launch_fwd_rest(const float* part, int slabs, float* coef, int64_t rows, int
 }
 
 // the same for the backward pass: parameter gradients, dx from g = dy (masked by y > 0 when relu)
-int launch_bwd_rest(const float* part, int slabs, float* coef, int64_t rows, int C, int relu, const float* gamma, const float* mean,
+int launch_bwd_rest(const void* part, int slabs, float* coef, int64_t rows, int C, int relu, const float* gamma, const float* mean,
                     const float* invstd, const uint4* x, const uint4* y, const uint4* dy, uint4* dx, void* dgamma16, void* dbeta16, hipStream_t st,
                     const unsigned* mask = nullptr, const BnPlan* p = nullptr) {
   const double inv_rows = 1.0 / (double)rows;
   unsigned short* dg = static_cast<unsigned short*>(dgamma16);
   unsigned short* db = static_cast<unsigned short*>(dbeta16);
   const bool whole = p && p->threads == BW_THREADS;
+  const float* const part32 = static_cast<const float*>(part);
+  const double* const part64 = static_cast<const double*>(part);
   if (slabs <= (whole ? BW_MERGE_SLABS_BWD : BN_MERGE_SLABS)) {
     int per;
     const dim3 grid = merged_grid(rows, C, BM_ROWS, 2048, &per);
-    auto kernel = whole ? bn_bwd_apply_merged<true> : bn_bwd_apply_merged<false>;
-    hipLaunchKernelGGL(kernel, grid, dim3(BN_THREADS), 0, st, x, y, dy, dx, rows, per, C, part, slabs, inv_rows, relu, gamma, mean, invstd, dg, db);
+    if (whole)
+      hipLaunchKernelGGL(bn_bwd_apply_merged<true>, grid, dim3(BN_THREADS), 0, st, x, y, dy, dx, rows, per, C, part64, slabs, inv_rows, relu, gamma, mean,
+                         invstd, dg, db);
+    else
+      hipLaunchKernelGGL(bn_bwd_apply_merged<false>, grid, dim3(BN_THREADS), 0, st, x, y, dy, dx, rows, per, C, part32, slabs, inv_rows, relu, gamma, mean,
+                         invstd, dg, db);
     return jz::launch_status();
   }
-  hipLaunchKernelGGL(bn_bwd_final, dim3((unsigned)((C + BN_FIN_C - 1) / BN_FIN_C)), dim3(BN_THREADS), 0, st, part, slabs, C, inv_rows, gamma, mean,
-                     invstd, dg, db, coef);
+  const dim3 fin((unsigned)((C + BN_FIN_C - 1) / BN_FIN_C));
+  if (whole) hipLaunchKernelGGL(bn_bwd_final<double>, fin, dim3(BN_THREADS), 0, st, part64, slabs, C, inv_rows, gamma, mean, invstd, dg, db, coef);
+  else hipLaunchKernelGGL(bn_bwd_final<float>, fin, dim3(BN_THREADS), 0, st, part32, slabs, C, inv_rows, gamma, mean, invstd, dg, db, coef);
   int rc = jz::launch_status();
   if (rc != JZ_OK) return rc;
   const int64_t n_chunks = rows * (C / 8);

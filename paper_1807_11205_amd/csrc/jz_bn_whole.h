@@ -29,7 +29,7 @@ struct BnWholeArgs {
   const float *gamma = nullptr, *beta = nullptr, *mean = nullptr, *invstd = nullptr;
   float *save_mean = nullptr, *save_invstd = nullptr;
   unsigned short *dgamma = nullptr, *dbeta = nullptr;
-  float* part = nullptr;                 // [slabs][2][C] sums
+  double* part = nullptr;                // [slabs][2][C] sums
   unsigned long long* flags = nullptr;   // one a workgroup
   unsigned long long tag = 0;            // this launch's, two low bits clear
   long long wait_ticks = 0;              // of the 100 MHz clock: the longest wait
@@ -268,8 +268,7 @@ __global__ __launch_bounds__(BW_THREADS) void bn_whole(BnWholeArgs a) {
     if constexpr (KL % BW_UL != 0) add_passes(std::integral_constant<int, 1>{}, std::true_type{}, K + KL - 1);
   }
   for (int p = K + KL; p < passes; p += BW_U) add_passes(std::integral_constant<int, BW_U>{}, std::false_type{}, p);
-  // forward sums between lanes in FP64, as in bn_stats
-  using Acc = std::conditional_t<GRAD, float, double>;
+  // A lane's sums, of one in 64 of the workgroup's rows, are FP32; everything behind them is FP64, as in bn_stats for this plan's slabs.
 #pragma unroll
   for (int e = 0; e < 8; e += 4) {
     *reinterpret_cast<float4*>(&red[0][tid][e]) = make_float4(s0[e], s0[e + 1], s0[e + 2], s0[e + 3]);
@@ -280,17 +279,17 @@ __global__ __launch_bounds__(BW_THREADS) void bn_whole(BnWholeArgs a) {
     constexpr int SUMS = 2 * BW_CH, PARTS = BW_THREADS / SUMS;
     const int i = tid % SUMS, first = tid / SUMS;
     const float* p = &red[0][0][0] + (i < BW_CH ? i : BW_THREADS * 8 + i - BW_CH);  // [row of a pass][BW_CH]
-    Acc t = 0;
+    double t = 0;
     for (int j = first; j < BW_ROWS; j += PARTS) t += p[j * BW_CH];
     __syncthreads();
-    Acc* const sums = reinterpret_cast<Acc*>(&red[0][0][0]);
+    double* const sums = reinterpret_cast<double*>(&red[0][0][0]);
     sums[first * SUMS + i] = t;
     __syncthreads();
     if (tid < SUMS) {
       t = 0;
 #pragma unroll
       for (int k = 0; k < PARTS; ++k) t += sums[k * SUMS + tid];
-      __hip_atomic_store(a.part + ((size_t)slab * 2 + tid / BW_CH) * a.C + group * BW_CH + tid % BW_CH, (float)t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(a.part + ((size_t)slab * 2 + tid / BW_CH) * a.C + group * BW_CH + tid % BW_CH, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       bw_performed();
     }
   }
@@ -353,35 +352,30 @@ __global__ __launch_bounds__(BW_THREADS) void bn_whole(BnWholeArgs a) {
   // ---- the channels' totals, FP64, in bn_slab_totals' order -----------------------------------------------------------
   double* const tot = reinterpret_cast<double*>(&red[0][0][0]);  // [lane][2 * BW_CH]
   {
-    constexpr int Q = 2 * BW_CH / 4, OWN = BN_FIN_LANES / (BW_THREADS / Q), IN_FLIGHT = 2;
-    const int q = tid % Q, j = tid / Q;  // four channels' first or second sums, lanes j and j + 16 of them
-    const unsigned long long* const p = reinterpret_cast<const unsigned long long*>(a.part + (size_t)(q / (Q / 2)) * a.C + group * BW_CH + q % (Q / 2) * 4);
-    double t[OWN][4];
+    constexpr int Q = 2 * BW_CH / 2, OWN = BN_FIN_LANES / (BW_THREADS / Q), IN_FLIGHT = 2, LANES = BN_FIN_LANES / OWN;
+    const int q = tid % Q, j = tid / Q;  // two channels' first or second sums, lanes j, j + 8, j + 16 and j + 24 of them
+    // past the last workgroup's sums the loads return zeros; device scope, like the stores: they pass by the caches that are not shared
+    constexpr int DEVICE_SCOPE = 16;
+    const __amdgpu_buffer_rsrc_t sums = __builtin_amdgcn_make_buffer_rsrc((void*)a.part, 0, (int)((unsigned)a.wgs * (unsigned)a.C * 16u), 0x00020000);
+    const unsigned slab_bytes = (unsigned)a.C * 16u, at = (unsigned)(q / (Q / 2)) * ((unsigned)a.C * 8u) + (unsigned)(group * BW_CH + q % (Q / 2) * 2) * 8u;
+    double t[OWN][2];
 #pragma unroll
-    for (int o = 0; o < OWN; ++o)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) t[o][e] = 0.0;
+    for (int o = 0; o < OWN; ++o) t[o][0] = t[o][1] = 0.0;
     for (int k = j; k < a.wgs; k += BN_FIN_LANES * IN_FLIGHT) {
-      unsigned long long v[IN_FLIGHT * OWN][2];
+      u32x4_bw v[IN_FLIGHT * OWN];
+#pragma unroll
+      for (int u = 0; u < IN_FLIGHT * OWN; ++u) v[u] = __builtin_amdgcn_raw_buffer_load_b128(sums, (int)(at + (unsigned)(k + u * LANES) * slab_bytes), 0, DEVICE_SCOPE);
 #pragma unroll
       for (int u = 0; u < IN_FLIGHT * OWN; ++u) {
-        v[u][0] = v[u][1] = 0;
-        if (k + u * (BN_FIN_LANES / OWN) < a.wgs) {
-#pragma unroll
-          for (int h = 0; h < 2; ++h)
-            v[u][h] = __hip_atomic_load(p + (size_t)(k + u * (BN_FIN_LANES / OWN)) * a.C + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
+        t[u % OWN][0] += __hiloint2double((int)v[u].y, (int)v[u].x);
+        t[u % OWN][1] += __hiloint2double((int)v[u].w, (int)v[u].z);
       }
-#pragma unroll
-      for (int u = 0; u < IN_FLIGHT * OWN; ++u)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) t[u % OWN][e] += (double)__uint_as_float((unsigned)(v[u][e / 2] >> (32 * (e % 2))));
     }
     __syncthreads();
 #pragma unroll
     for (int o = 0; o < OWN; ++o)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) tot[(j + o * (BN_FIN_LANES / OWN)) * (2 * BW_CH) + q * 4 + e] = t[o][e];
+      for (int e = 0; e < 2; ++e) tot[(j + o * LANES) * (2 * BW_CH) + q * 2 + e] = t[o][e];
     __syncthreads();
     if (tid < 2 * BW_CH) {
       double sum = 0.0;

@@ -147,6 +147,37 @@ def test_more_rows_than_are_kept(jz, passes):
         jz.jz_bn_tune_wait(100)
 
 
+@pytest.mark.parametrize("rows,C", [(784, 512), (3136, 256), (12544, 64)])
+def test_sums_between_lanes_and_workgroups_are_fp64(jz, rows, C):
+    """Large terms that cancel, in different workgroups, in lanes (a lane has every 64th row) that hold nothing else; the other terms are 2^-16.  Every
+    lane's FP32 sum is exact and so is every FP64 sum of them, while FP32 sums at the size of the large terms (ulp 2^-9) lose the small ones."""
+    t = torch.full((rows, C), 2.0 ** -16, device=DEV)
+    t[0::64], t[1::64] = 0.0, 0.0
+    t[0], t[1 + rows // 128 * 64] = 30000.0, -30000.0
+    total = int((t == 2.0 ** -16).sum()) // C * 2.0 ** -16
+    t = t.half().view(-1)
+    c = Case(jz, rows, C)
+    one, zero = torch.ones(C, device=DEV), torch.zeros(C, device=DEV)
+    x = torch.ones(rows * C, dtype=torch.float16, device=DEV)
+
+    def run(o):
+        jz.jz_bn_relu_fwd(rows, C, t, one, zero, 1e-5, False, o["y"], o["mean"], o["invstd"], c.ws)
+        jz.jz_bn_relu_bwd(rows, C, x, x, t, one, zero, one, True, o["dx"], o["dg"], o["db"], c.ws)
+        jz.jz_bn_relu_bwd(rows, C, x, None, t, one, zero, one, False, o["dx0"], o["dg0"], o["db0"], c.ws)
+        jz.jz_bn_bwd_block_end(rows, C, x, x, t, None, one, zero, one, o["g"], o["dxe"], o["dge"], o["dbe"], c.ws)
+
+    c.run = run
+    o, b = c.outputs(), c.outputs()
+    run(o)
+    torch.cuda.synchronize()
+    mean = torch.tensor(total * (1.0 / rows), dtype=torch.float64)
+    assert float((o["mean"].double().cpu() / mean - 1).abs().max()) <= 2.0 ** -24
+    for k in ("dg", "db", "dg0", "db0", "dge", "dbe"):
+        assert torch.equal(o[k], torch.full_like(o[k], total)), (k, o[k][:2], total)
+    _graph_run(c, b)
+    assert _same(o, b) == {}
+
+
 def test_several_streams_at_once(jz):
     cases = [Case(jz, 20000 + 64 * i, 128, seed=i) for i in range(5)]
     want = [c.outputs() for c in cases]
