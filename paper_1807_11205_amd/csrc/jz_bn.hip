@@ -720,18 +720,22 @@ __global__ __launch_bounds__(BN_THREADS) void bn_bwd_apply_merged(const uint4* _
 #include "jz_bn_whole.h"
 
 // One launch for all (bn_whole): channel counts that are multiples of 64.  The plan is the statistics passes' with slabs for one workgroup
-// per compute unit, so that the launches apart leave the same bits.  room: what the call has of workspace.
+// per compute unit, so that the launches apart leave the same bits.
 // Backward up to 128 passes of 64 rows a workgroup: beyond, most rows are read twice either way and the launches apart have more loads in
 // flight (401408 x 256, 98 passes: 252 us apart, 217 in one; 200704 x 1024, 196 passes: 497 and 529).  Forward it is never slower (802816 x 256: 226
 // and 218).
 constexpr int64_t BW_MOST_PASSES_BWD = 128;
+// Fewest rows of a workgroup.  A workgroup more is a slab more that all others read, and a flag more to wait for.  16384 x 64 forward / backward with
+// ReLU, microseconds, with 64, 128 and 256 rows each: 9.8 / 10.7, 8.3 / 9.2, 7.8 / 8.6; 6272 x 64: 7.7 / 8.9, 7.1 / 8.0, 7.1 / 8.1; 392 x 2048: 6.7 / 7.9,
+// 6.5 / 7.8, 6.7 / 8.2.  Up to 256 rows one workgroup has all and waits for nobody: 196 x 1024 5.6 / 6.5 instead of 6.4 / 7.4.
+int64_t whole_min_rows(int64_t rows) { return rows <= 256 || rows >= 8192 ? 4 * BW_ROWS : 2 * BW_ROWS; }
 // launches apart, backward: large slabs are few, and the pass over y that the mask's bits save is worth a finalize launch earlier
 constexpr int BW_MERGE_SLABS_BWD = 16;
-bool make_whole_plan(int64_t rows, int C, bool forward, size_t room, BnPlan* p) {
+bool make_whole_plan(int64_t rows, int C, bool forward, BnPlan* p) {
   if (C % BW_CH != 0) return false;
   const int groups = C / BW_CH;
   int64_t per = (rows + BW_WGS / groups - 1) / (BW_WGS / groups);
-  if (per < BW_ROWS) per = BW_ROWS;
+  if (per < whole_min_rows(rows)) per = whole_min_rows(rows);
   p->rows = rows;
   p->C = C;
   p->cpr = C / 8;
@@ -739,21 +743,18 @@ bool make_whole_plan(int64_t rows, int C, bool forward, size_t room, BnPlan* p) 
   p->threads = BW_THREADS;
   p->rpp = BW_ROWS;
   p->off_part = 0;
-  for (;; per += BW_ROWS) {  // fewer workgroups where there is no room for the sums of more
-    p->slabs = (int)((rows + per - 1) / per);
-    p->off_coef = up256((size_t)p->slabs * 2 * C * sizeof(BnSum<true>));
-    const size_t coef = (size_t)4 * C * sizeof(float), flags = (size_t)p->slabs * groups * sizeof(unsigned long long);
-    p->total = p->off_coef + up256(coef > flags ? coef : flags);
-    if (p->total <= room) break;
-    if (p->slabs == 1) return false;
-  }
+  p->slabs = (int)((rows + per - 1) / per);
+  p->off_coef = up256((size_t)p->slabs * 2 * C * sizeof(BnSum<true>));
+  const size_t coef = (size_t)4 * C * sizeof(float), flags = (size_t)p->slabs * groups * sizeof(unsigned long long);
+  p->total = p->off_coef + up256(coef > flags ? coef : flags);
   p->rows_per_slab = per;
   p->mask_iters = (int)((per + BN_BWD_ROWS * BW_ROWS - 1) / (BN_BWD_ROWS * BW_ROWS));
   p->mask_bytes = p->slabs > BW_MERGE_SLABS_BWD ? (size_t)p->slabs * groups * p->mask_iters * BW_THREADS * 4 : 0;
   return per * C * 2 < (int64_t(1) << 31) && (forward || per <= BW_MOST_PASSES_BWD * BW_ROWS);
 }
 
-// the sums lie elsewhere in the workspace than the other plan's: a tensor that this one leaves alone and that one does not keeps the call where it was
+// This plan may take more of the workspace than the other one, which is all that a call has to have.  A workspace of the reported size has room for
+// either; with less, or with a tensor of the call where only this plan writes, the call has the other plan.
 bool clear_of(const void* ws, size_t n, std::initializer_list<std::pair<const void*, size_t>> tensors) {
   for (const auto& t : tensors)
     if (jz::overlaps(ws, n, t.first, t.second)) return false;
@@ -943,7 +944,9 @@ extern "C" int jz_bn_workspace_bytes(int64_t rows, int channels, size_t* bytes) 
   BnPlan p;
   int rc = make_bn_plan(rows, channels, false, &p);  // the forward plan fits where the backward one does
   if (rc != JZ_OK) return rc;
-  *bytes = p.total + p.mask_bytes;
+  // room for the plan that takes more, and behind it for the mask's bits (the whole plan's, where there is room for those)
+  BnPlan w;
+  *bytes = (make_whole_plan(rows, channels, true, &w) && w.total > p.total ? w.total : p.total) + p.mask_bytes;
   return JZ_OK;
 }
 
@@ -967,7 +970,7 @@ extern "C" int jz_bn_relu_fwd(int64_t rows, int channels, const void* x16, const
       jz::overlaps(save_mean, nc, y16, nb) || jz::overlaps(save_invstd, nc, y16, nb))
     return JZ_ERR_ALIAS;
   BnPlan wp;
-  const bool whole = make_whole_plan(rows, channels, true, b.total, &wp) &&
+  const bool whole = make_whole_plan(rows, channels, true, &wp) && ws_bytes >= wp.total &&
                      clear_of(ws, wp.total, {{x16, nb}, {y16, nb}, {gamma, nc}, {beta, nc}, {save_mean, nc}, {save_invstd, nc}});
   if (whole) p = wp;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
@@ -1002,9 +1005,10 @@ extern "C" int jz_bn_relu_bwd(int64_t rows, int channels, const void* x16, const
       jz::overlaps(dbeta16, nh, dx16, nb) || jz::overlaps(dgamma16, nh, x16, nb) || jz::overlaps(dbeta16, nh, x16, nb) ||
       jz::overlaps(dgamma16, nh, dy16, nb) || jz::overlaps(dbeta16, nh, dy16, nb))
     return JZ_ERR_ALIAS;
-  BnPlan wp;  // its tensors are clear of the workspace (checked above)
-  const bool whole = make_whole_plan(rows, channels, false, p.total, &wp) &&
-                     clear_of(ws, wp.total, {{gamma, nf}, {save_mean, nf}, {save_invstd, nf}, {dgamma16, nh}, {dbeta16, nh}});
+  BnPlan wp;
+  const bool whole = make_whole_plan(rows, channels, false, &wp) && ws_bytes >= wp.total &&
+                     clear_of(ws, wp.total, {{x16, nb}, {relu ? y16 : nullptr, nb}, {dy16, nb}, {dx16, nb}, {gamma, nf}, {save_mean, nf}, {save_invstd, nf},
+                                             {dgamma16, nh}, {dbeta16, nh}});
   if (whole) p = wp;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   float* part = reinterpret_cast<float*>(static_cast<char*>(ws) + p.off_part);
@@ -1058,8 +1062,9 @@ extern "C" int jz_bn_bwd_block_end(int64_t rows, int channels, const void* x16, 
     if (jz::overlaps(i, nb, ws, p.total) || jz::overlaps(i, nb, dgamma16, nh) || jz::overlaps(i, nb, dbeta16, nh)) return JZ_ERR_ALIAS;
   const size_t nf = (size_t)channels * 4;
   BnPlan wp;
-  const bool whole = make_whole_plan(rows, channels, false, p.total, &wp) &&
-                     clear_of(ws, wp.total, {{gamma, nf}, {save_mean, nf}, {save_invstd, nf}, {dgamma16, nh}, {dbeta16, nh}});
+  const bool whole = make_whole_plan(rows, channels, false, &wp) && ws_bytes >= wp.total &&
+                     clear_of(ws, wp.total, {{x16, nb}, {y_out16, nb}, {dya16, nb}, {dyb16, nb}, {g16, nb}, {dx16, nb}, {gamma, nf}, {save_mean, nf},
+                                             {save_invstd, nf}, {dgamma16, nh}, {dbeta16, nh}});
   if (whole) p = wp;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   float* part = reinterpret_cast<float*>(static_cast<char*>(ws) + p.off_part);
@@ -1170,6 +1175,9 @@ struct ConvBnBwdPlan {
   size_t conv_ws = 0;
   int tiles_m = 0;      // > 0: the convolution kernel leaves [tiles_m][2][C] sums; 0: the statistics pass runs
   size_t off_bn = 0, total = 0;
+  bool whole = false;   // bn_whole takes the normalization where there is room for `whole_bn`
+  BnPlan whole_bn;
+  size_t reported = 0;
 };
 
 int make_conv_bn_bwd_plan(const jz_conv_desc* d, ConvBnBwdPlan* p) {
@@ -1182,7 +1190,9 @@ int make_conv_bn_bwd_plan(const jz_conv_desc* d, ConvBnBwdPlan* p) {
   p->bn.off_part = 0;
   p->bn.off_coef = up256((size_t)slabs * 2 * d->C * sizeof(float));
   p->bn.total = p->bn.off_coef + up256((size_t)4 * d->C * sizeof(float));
-  p->total = p->off_bn + p->bn.total;
+  p->total = p->reported = p->off_bn + p->bn.total;
+  p->whole = p->tiles_m == 0 && make_whole_plan(p->bn.rows, d->C, false, &p->whole_bn);
+  if (p->whole && p->whole_bn.total > p->bn.total) p->reported = p->off_bn + p->whole_bn.total;
   return JZ_OK;
 }
 
@@ -1193,7 +1203,7 @@ extern "C" int jz_conv2d_bwd_data_bn_relu_bwd_workspace_bytes(const jz_conv_desc
   ConvBnBwdPlan p;
   int rc = make_conv_bn_bwd_plan(desc, &p);
   if (rc != JZ_OK) return rc;
-  *bytes = p.total;
+  *bytes = p.reported;
   return JZ_OK;
 }
 
@@ -1249,12 +1259,13 @@ static int conv_bwd_data_bn_bwd(const jz_conv_desc* desc, const void* dy16, cons
                            static_cast<uint4*>(bn_dx16), dgamma16, dbeta16, st);
   // This convolution kernel cannot leave the sums: the normalization as its own call takes it, a block end with g in place.  In one launch
   // 83 us at the block ends of ResNet-50's strided layers (batch 64, 200704 x 256 to 12544 x 1024, mean), as statistics and the rest 102.
-  BnPlan wp;  // all tensors are clear of the workspace (checked above)
-  const bool whole = make_whole_plan(rows, C, false, p.bn.total, &wp);
+  bool whole = p.whole && ws_bytes >= p.off_bn + p.whole_bn.total;
+  for (int i = 0; i < 4; ++i) whole = whole && !jz::overlaps(bws, p.whole_bn.total, outs[i], outn[i]);
+  for (int j = 0; j < 8; ++j) whole = whole && !jz::overlaps(bws, p.whole_bn.total, ins[j], inn[j]);
   if (whole) {
-    p.bn = wp;
-    part = reinterpret_cast<float*>(bws + wp.off_part);
-    coef = reinterpret_cast<float*>(bws + wp.off_coef);
+    p.bn = p.whole_bn;
+    part = reinterpret_cast<float*>(bws + p.bn.off_part);
+    coef = reinterpret_cast<float*>(bws + p.bn.off_coef);
   }
   uint4* const g = static_cast<uint4*>(out16);
   const uint4* const add = static_cast<const uint4*>(add16);
@@ -1264,7 +1275,7 @@ static int conv_bwd_data_bn_bwd(const jz_conv_desc* desc, const void* dy16, cons
     w.g_out = g; w.out = static_cast<uint4*>(bn_dx16);
     w.gamma = gamma; w.mean = save_mean; w.invstd = save_invstd;
     w.dgamma = static_cast<unsigned short*>(dgamma16); w.dbeta = static_cast<unsigned short*>(dbeta16);
-    return block_end ? launch_whole<BW_END>(wp, w, bws, st) : launch_whole<BW_RELU>(wp, w, bws, st);
+    return block_end ? launch_whole<BW_END>(p.bn, w, bws, st) : launch_whole<BW_RELU>(p.bn, w, bws, st);
   }
   const BnStatsArgs in{.x = x, .y = y, .dy = dz, .dy2 = add, .g_out = g, .mean = save_mean, .invstd = save_invstd};
   rc = block_end ? launch_stats<ST_END>(p.bn, part, in, st) : launch_stats<ST_RELU>(p.bn, part, in, st);

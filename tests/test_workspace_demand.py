@@ -44,3 +44,21 @@ def test_partial_sums_of_half_precision_layers_are_bounded(jz):
 def test_strided_backward_data_of_ragged_channels_asks_for_no_workspace(jz):
     for N, H, W, C, K, R, S, st, pad in ((2, 16, 15, 40, 24, 3, 3, 2, 1), (1, 20, 20, 8, 200, 7, 4, (3, 2), (2, 1))):
         assert jz.jz_conv2d_workspace_bytes(jz.JZ_BWD_DATA, jz.conv_desc(N, H, W, C, K, R, S, st, pad)) == 0
+
+
+def whole_plan(rows, C):
+    """Slabs of batch normalization in one launch: 64 channels a workgroup, at most 256 of them, and the fewest rows that pay for one more."""
+    least = 256 if rows <= 256 or rows >= 8192 else 128
+    return -(-rows // max(least, -(-rows // (256 // (C // 64)))))
+
+
+def test_batch_normalization_in_one_launch_has_room_for_all_its_workgroups(jz):
+    """Two FP64 sums a channel of every slab, and behind them a flag a workgroup or the coefficients of the launches apart."""
+    for rows, C in ((1, 64), (63, 64), (64, 128), (257, 64), (2048, 64), (6272, 64), (16384, 64), (25088, 64), (49, 2048), (12545, 128), (4099, 1984),
+                    (100352, 64), (200704, 64), (802816, 64)):
+        slabs = whole_plan(rows, C)
+        assert jz.jz_bn_workspace_bytes(rows, C) >= slabs * 2 * C * 8 + max(16 * C, slabs * C // 8), (rows, C)
+    for N, H, C, K in ((1, 7, 64, 64), (1, 14, 64, 128), (2, 28, 128, 128), (64, 56, 64, 64)):
+        d, rows = jz.conv_desc(N, H, H, C, K, 1, 1, 2, 0), N * H * H
+        need = jz.jz_conv2d_workspace_bytes(jz.JZ_BWD_DATA, d) + whole_plan(rows, C) * (2 * C * 8) + 16 * C
+        assert jz.jz_conv2d_bwd_data_bn_relu_bwd_workspace_bytes(d) >= need, (N, H, C, K)
