@@ -53,6 +53,11 @@ constexpr int64_t BN_WIDE_BYTES = 4 << 20, BN_FEW_SLABS_BYTES = 64 << 20;
 constexpr int BN_FIN_C = 8;            // channels a finalize workgroup handles (32 contiguous bytes of every slab's sums);
 constexpr int BN_FIN_LANES = BN_THREADS / BN_FIN_C;  // its 32 lanes per channel share the slabs
 
+// bn_whole (jz_bn_whole.h)
+constexpr int BW_THREADS = 512;                  // one workgroup per compute unit: 2 wavefronts per SIMD, 256 registers a lane
+constexpr int BW_CH = 64;                        // channels of a workgroup: one 128-byte line of every row
+constexpr int BW_ROWS = BW_THREADS / (BW_CH / 8);  // rows one pass of a workgroup covers
+
 size_t up256(size_t x) { return (x + 255) & ~size_t(255); }
 
 struct BnPlan {
@@ -177,8 +182,9 @@ template <int MODE, int T>
 __global__ __launch_bounds__(T) void bn_stats(BnStatsArgs a) {
   __shared__ __align__(16) float red[2][T][8];
   constexpr bool GRAD = MODE != ST_SUM, NEEDS_Y = MODE == ST_RELU || MODE == ST_MASK || MODE == ST_END;
-  const int tid = threadIdx.x, cpr = a.cpr, rpp = a.rpp, C = a.C;
-  const int cpr_l = cpr / a.csplit;  // chunks of a row this workgroup handles: [cfirst, cfirst + cpr_l)
+  constexpr bool WHOLE_PLAN = T != BN_THREADS;  // bn_whole's, for calls that may not take it: what is known is constant
+  const int tid = threadIdx.x, cpr = a.cpr, rpp = WHOLE_PLAN ? BW_ROWS : a.rpp, C = a.C;
+  const int cpr_l = WHOLE_PLAN ? BW_CH / 8 : cpr / a.csplit;  // chunks of a row this workgroup handles: [cfirst, cfirst + cpr_l)
   const int slab = blockIdx.x / a.csplit, cfirst = (blockIdx.x % a.csplit) * cpr_l;
   const int chunk_l = tid % cpr_l, rsub = tid / cpr_l;
   const int chunk = cfirst + chunk_l;
@@ -275,7 +281,7 @@ __global__ __launch_bounds__(T) void bn_stats(BnStatsArgs a) {
   // rows are shared by workgroups a slab has four times as many, and FP32 would make the variance of channels far from zero less exact
   // than with small slabs (12544 x 256, mean 10 std: relative error 5.3e-7, in FP64 3.2e-7; FP32 and slabs of 32 rows: 3.2e-7).
   // The gradients' too where bn_whole's slabs are summed.
-  using Part = BnSum<T != BN_THREADS>;
+  using Part = BnSum<WHOLE_PLAN>;
   using Acc = std::conditional_t<GRAD, Part, double>;
   const int ch = 8 * cpr_l, sums = 2 * ch;  // red[0] and red[1] are [rows of a pass][ch]
   const float* const r0s = &red[0][0][0];
@@ -542,6 +548,28 @@ __device__ __forceinline__ bool bn_merged_totals_32(const double* __restrict__ p
   constexpr int THREADS = T / BM_CH, OWN = BN_FIN_LANES / THREADS;
   __shared__ double red[2][BN_FIN_LANES][BM_CH];
   const int cl = threadIdx.x & (BM_CH - 1), c = first + cl, j = __builtin_amdgcn_readfirstlane(threadIdx.x / BM_CH);
+  if (slabs <= BN_FIN_LANES) {  // a lane has one slab at most: one thread adds them, without the detour through LDS
+    if (j != 0 || c >= C) return false;
+    constexpr int U = 16;
+    s = q = 0.0;
+    for (int k = 0; k < slabs; k += U) {
+      double a[U], b[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        a[u] = b[u] = 0.0;
+        if (k + u < slabs) {
+          a[u] = part[((size_t)(k + u) * 2) * C + c];
+          b[u] = part[((size_t)(k + u) * 2 + 1) * C + c];
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        s += a[u];
+        q += b[u];
+      }
+    }
+    return true;
+  }
   double ts[OWN], tq[OWN];
 #pragma unroll
   for (int o = 0; o < OWN; ++o) ts[o] = tq[o] = 0.0;
@@ -728,9 +756,10 @@ constexpr int64_t BW_MOST_PASSES_BWD = 128;
 // Fewest rows of a workgroup.  A workgroup more is a slab more that all others read, and a flag more to wait for.  16384 x 64 forward / backward with
 // ReLU, microseconds, with 64, 128 and 256 rows each: 9.8 / 10.7, 8.3 / 9.2, 7.8 / 8.6; 6272 x 64: 7.7 / 8.9, 7.1 / 8.0, 7.1 / 8.1; 392 x 2048: 6.7 / 7.9,
 // 6.5 / 7.8, 6.7 / 8.2.  Up to 256 rows one workgroup has all and waits for nobody: 196 x 1024 5.6 / 6.5 instead of 6.4 / 7.4.
-int64_t whole_min_rows(int64_t rows) { return rows <= 256 || rows >= 8192 ? 4 * BW_ROWS : 2 * BW_ROWS; }
-// launches apart, backward: large slabs are few, and the pass over y that the mask's bits save is worth a finalize launch earlier
-constexpr int BW_MERGE_SLABS_BWD = 16;
+int64_t whole_min_rows(int64_t rows) { return rows <= 256 || rows >= 4096 ? 4 * BW_ROWS : 2 * BW_ROWS; }
+// Launches apart on this plan, backward: whether the apply pass adds up the slabs itself.  Its slabs are few, so size decides: the pass over y that the
+// mask's bits save is worth a finalize launch from some MB up (12544 x 1024, 16 slabs: 41.4 us merged, 38.5 with both; 1568 x 1024, 16 slabs: 11.7 and 12.1).
+bool whole_merges_bwd(const BnPlan& p) { return p.slabs <= BN_MERGE_SLABS && p.rows * p.C * 2 <= BN_WIDE_BYTES; }
 bool make_whole_plan(int64_t rows, int C, bool forward, BnPlan* p) {
   if (C % BW_CH != 0) return false;
   const int groups = C / BW_CH;
@@ -749,7 +778,7 @@ bool make_whole_plan(int64_t rows, int C, bool forward, BnPlan* p) {
   p->total = p->off_coef + up256(coef > flags ? coef : flags);
   p->rows_per_slab = per;
   p->mask_iters = (int)((per + BN_BWD_ROWS * BW_ROWS - 1) / (BN_BWD_ROWS * BW_ROWS));
-  p->mask_bytes = p->slabs > BW_MERGE_SLABS_BWD ? (size_t)p->slabs * groups * p->mask_iters * BW_THREADS * 4 : 0;
+  p->mask_bytes = whole_merges_bwd(*p) ? 0 : (size_t)p->slabs * groups * p->mask_iters * BW_THREADS * 4;
   return per * C * 2 < (int64_t(1) << 31) && (forward || per <= BW_MOST_PASSES_BWD * BW_ROWS);
 }
 
@@ -774,8 +803,17 @@ unsigned long long bw_tag() {
 
 // Whether a call on this stream may take bn_whole: it wants the chip to itself, and several of them from different streams would
 // get in each other's way (four streams with 200704 x 64 each: 100 us a call instead of 21).  So one stream a device has it; another one
-// gets it after 64 calls without one of the first.  Never while the stream is captured.
-bool bw_has_chip(hipStream_t st) {
+// gets it after 64 calls without one of the first.  Never while the stream is captured.  Those calls run the passes apart on the same plan, for the
+// same bits.  Captured, microseconds, forward / backward with ReLU / block end, on the plan that other channel counts have and on this one:
+//   196 x 1024   6.5 /  7.4 /  7.8    5.4 /  6.5 /  7.1      3136 x 2048   13.6 / 22.7 / 28.5    10.8 / 22.4 / 29.5
+//   2048 x 128   6.4 /  7.6 /  7.8    6.9 /  7.7 /  8.6      12544 x 1024  17.2 / 39.2 / 46.8    14.3 / 38.5 / 48.5
+//   3136 x 256   9.3 / 11.2 / 11.3    7.7 /  9.5 / 10.1      50176 x 512   29.4 / 65.7 / 88.7    28.2 / 67.1 / 92.2
+//   6272 x 64    7.4 /  9.0 /  9.0    7.6 /  9.3 / 10.1      200704 x 256  54.6 / 120 / 163      54.2 / 121 / 164
+//   25088 x 64  10.3 / 12.1 / 13.3   10.4 / 12.9 / 13.3      802816 x 64   54.1 / 120 / 162      53.5 / 118 / 165
+// A block end loses up to 5 % where its rows are read in 128-byte pieces (an XCD for each range of whole rows: worse, 69.6 us backward at 50176 x 512).
+// A call whose workgroups have all rows of their channels has nothing to wait for and always may.
+bool bw_has_chip(const BnPlan& p, hipStream_t st) {
+  if (p.slabs == 1) return true;
   hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(st, &capture) != hipSuccess) {
     (void)hipGetLastError();
@@ -871,11 +909,11 @@ int launch_fwd_rest(const void* part, int slabs, float* coef, int64_t rows, int 
     return jz::launch_status();
   };
   const int64_t nb = rows * C * 2;
-  if (slabs <= BN_MERGE_SLABS_WIDE && nb >= BN_WIDE_BYTES && nb <= BN_FEW_SLABS_BYTES)
+  if (slabs <= (whole ? BN_MERGE_SLABS : BN_MERGE_SLABS_WIDE) && nb >= BN_WIDE_BYTES && nb <= BN_FEW_SLABS_BYTES)
     return whole ? merged(bn_apply_merged<0, 512, true>, part64, 512, 512)
            : res ? merged(bn_apply_merged<1, 512>, part32, 512, 512)
                  : merged(bn_apply_merged<0, 512>, part32, 512, 512);
-  if (slabs <= BN_MERGE_SLABS)
+  if (slabs <= BN_MERGE_SLABS && !(whole && nb > BN_FEW_SLABS_BYTES))
     return whole ? merged(bn_apply_merged<0, BN_THREADS, true>, part64, BN_THREADS, 2048)
            : res ? merged(bn_apply_merged<1, BN_THREADS>, part32, BN_THREADS, 2048)
                  : merged(bn_apply_merged<0, BN_THREADS>, part32, BN_THREADS, 2048);
@@ -902,7 +940,7 @@ int launch_bwd_rest(const void* part, int slabs, float* coef, int64_t rows, int 
   const bool whole = p && p->threads == BW_THREADS;
   const float* const part32 = static_cast<const float*>(part);
   const double* const part64 = static_cast<const double*>(part);
-  if (slabs <= (whole ? BW_MERGE_SLABS_BWD : BN_MERGE_SLABS)) {
+  if (whole ? whole_merges_bwd(*p) : slabs <= BN_MERGE_SLABS) {
     int per;
     const dim3 grid = merged_grid(rows, C, BM_ROWS, 2048, &per);
     if (whole)
@@ -981,7 +1019,7 @@ extern "C" int jz_bn_relu_fwd(int64_t rows, int channels, const void* x16, const
   w.x = x; w.out = static_cast<uint4*>(y16);
   w.gamma = gamma; w.beta = beta; w.save_mean = save_mean; w.save_invstd = save_invstd;
   w.eps = eps; w.relu = relu ? 1 : 0;
-  if (whole && bw_has_chip(st)) return launch_whole<BW_FWD>(p, w, ws, st);
+  if (whole && bw_has_chip(p, st)) return launch_whole<BW_FWD>(p, w, ws, st);
   if ((rc = launch_stats<ST_SUM>(p, part, {.x = x}, st)) != JZ_OK) return rc;
   return launch_fwd_rest(part, p.slabs, coef, rows, channels, eps, relu ? 1 : 0, gamma, beta, x, nullptr, static_cast<uint4*>(y16), save_mean,
                          save_invstd, st, whole);
@@ -1030,7 +1068,7 @@ extern "C" int jz_bn_relu_bwd(int64_t rows, int channels, const void* x16, const
   w.x = x; w.y = y; w.dy = dy; w.out = static_cast<uint4*>(dx16);
   w.gamma = gamma; w.mean = save_mean; w.invstd = save_invstd;
   w.dgamma = static_cast<unsigned short*>(dgamma16); w.dbeta = static_cast<unsigned short*>(dbeta16);
-  if (whole && bw_has_chip(st)) return relu ? launch_whole<BW_RELU>(p, w, ws, st) : launch_whole<BW_GRAD>(p, w, ws, st);
+  if (whole && bw_has_chip(p, st)) return relu ? launch_whole<BW_RELU>(p, w, ws, st) : launch_whole<BW_GRAD>(p, w, ws, st);
   const BnStatsArgs in{.x = x, .y = y, .dy = dy, .mask = mask, .mean = save_mean, .invstd = save_invstd};
   rc = !relu ? launch_stats<ST_GRAD>(p, part, in, st) : mask ? launch_stats<ST_MASK>(p, part, in, st) : launch_stats<ST_RELU>(p, part, in, st);
   if (rc != JZ_OK) return rc;
@@ -1075,7 +1113,7 @@ extern "C" int jz_bn_bwd_block_end(int64_t rows, int channels, const void* x16, 
   w.g_out = static_cast<uint4*>(g16); w.out = static_cast<uint4*>(dx16);
   w.gamma = gamma; w.mean = save_mean; w.invstd = save_invstd;
   w.dgamma = static_cast<unsigned short*>(dgamma16); w.dbeta = static_cast<unsigned short*>(dbeta16);
-  if (whole && bw_has_chip(st)) return launch_whole<BW_END>(p, w, ws, st);
+  if (whole && bw_has_chip(p, st)) return launch_whole<BW_END>(p, w, ws, st);
   rc = launch_stats<ST_END>(p, part, {.x = x, .y = static_cast<const uint4*>(y_out16), .dy = static_cast<const uint4*>(dya16),
                                       .dy2 = static_cast<const uint4*>(dyb16), .g_out = static_cast<uint4*>(g16), .mean = save_mean,
                                       .invstd = save_invstd}, st);
@@ -1269,7 +1307,7 @@ static int conv_bwd_data_bn_bwd(const jz_conv_desc* desc, const void* dy16, cons
   }
   uint4* const g = static_cast<uint4*>(out16);
   const uint4* const add = static_cast<const uint4*>(add16);
-  if (whole && bw_has_chip(st)) {
+  if (whole && bw_has_chip(p.bn, st)) {
     BnWholeArgs w;
     w.x = x; w.y = y; w.dy = dz; w.dy2 = add;
     w.g_out = g; w.out = static_cast<uint4*>(bn_dx16);

@@ -13,9 +13,6 @@
 // 64 channels are one 128-byte line of a row, the least that costs memory nothing; 512 threads are the fewest that can hold the register file.
 #pragma once
 
-constexpr int BW_THREADS = 512;                  // one workgroup per compute unit: 2 wavefronts per SIMD, 256 registers a lane
-constexpr int BW_CH = 64;                        // channels of a workgroup: one 128-byte line of every row
-constexpr int BW_ROWS = BW_THREADS / (BW_CH / 8);  // rows one pass of a workgroup covers
 constexpr int BW_WGS = 256;                      // workgroups at most: all of them run at the same time
 constexpr int BW_U = 4;                          // passes beyond the kept ones whose loads are in flight together
 constexpr int BW_UL = 2;                         // ... of the passes kept in LDS

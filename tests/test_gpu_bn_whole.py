@@ -102,7 +102,9 @@ def _graph_run(c, o):
 # 256 workgroups of 64 channels each, a pass of 64 rows: rows = passes * 64 * 256 / (C / 64) fill the chip
 FULL = [(p * 64 * (256 // (C // 64)), C) for p, C in ((4, 2048), (8, 1024), (14, 512), (25, 256))]
 SIZES = [(1, 64), (63, 64), (64, 128), (65, 64), (129, 2048), (1000, 192), (777, 320), (4099, 1984),
-         (49, 2048), (64, 1024), (37, 512)]   # one workgroup has all rows of its channels: its wavefronts wait for each other's sums
+         (49, 2048), (64, 1024), (256, 64),     # one workgroup has all rows of its channels: its wavefronts wait for each other's sums
+         (257, 64), (4095, 64), (4097, 64),     # two of 128 rows, 32, 17 of 256
+         (8193, 64), (16384, 64), (16385, 64)]  # 33 slabs: more than one for a lane; 64: the launches apart merge them, 65: they do not
 SIZES += [(r + d, C) for r, C in FULL for d in (0, 1)]
 
 

@@ -48,7 +48,7 @@ def test_strided_backward_data_of_ragged_channels_asks_for_no_workspace(jz):
 
 def whole_plan(rows, C):
     """Slabs of batch normalization in one launch: 64 channels a workgroup, at most 256 of them, and the fewest rows that pay for one more."""
-    least = 256 if rows <= 256 or rows >= 8192 else 128
+    least = 256 if rows <= 256 or rows >= 4096 else 128
     return -(-rows // max(least, -(-rows // (256 // (C // 64)))))
 
 
