@@ -453,8 +453,8 @@ int jz_conv2d_tune_use_table(int on);
 int jz_conv2d_tune_clear(void);
 
 /* A tuning hook like the above, of the calling HOST thread only: where a batch normalization runs in one launch, how many microseconds (0 to
- * 1000000, JZ_ERR_SHAPE beyond; 100 unless set) a workgroup waits for the others' sums before it leaves its rows to those that come
- * later.  Results have the same bits whatever it is; the tests set 0. */
+ * 1000000, JZ_ERR_SHAPE beyond; 10 unless set) beyond the time that its own rows took a workgroup waits for the others' sums before it takes over
+ * rows of workgroups that have not started (0: at once).  Results have the same bits whatever it is; the tests set 0. */
 int jz_bn_tune_wait(int microseconds);
 
 /* Human-readable name of a status code; static storage. */

@@ -298,7 +298,8 @@ def jz_conv2d_tune_clear():
 
 
 def jz_bn_tune_wait(microseconds: int):
-    """How long a workgroup of the one-launch batch normalization waits for the others, for calls of this thread (a test's hook)."""
+    """How long a workgroup of the one-launch batch normalization waits for those that have not started before it takes their rows over, for calls
+    of this thread (a test's hook)."""
     _check(lib().jz_bn_tune_wait(microseconds), "jz_bn_tune_wait")
 
 

@@ -790,7 +790,7 @@ bool clear_of(const void* ws, size_t n, std::initializer_list<std::pair<const vo
   return true;
 }
 
-thread_local int t_bn_wait_us = 100;
+thread_local int t_bn_wait_us = 10;
 // 62 bits of a counter that starts where the clock stood, mixed: no launch of this process has had them, and sums that an earlier call left in
 // the workspace do not look like them
 unsigned long long bw_tag() {
@@ -849,6 +849,7 @@ int launch_whole(const BnPlan& p, BnWholeArgs a, void* ws, hipStream_t st) {
   a.tag = bw_tag();
   a.wait_ticks = (long long)t_bn_wait_us * 100;
   a.inv_rows = 1.0 / (double)p.rows;
+  a.in_place = a.g_out != nullptr && (const void*)a.g_out == (const void*)a.dy;
   const int passes = (int)((p.rows_per_slab + BW_ROWS - 1) / BW_ROWS);
   auto go = [&](auto k_tag, auto l_tag, auto m_tag) {
     constexpr int K = decltype(k_tag)::value, KL = decltype(l_tag)::value, MASKS = decltype(m_tag)::value;
@@ -863,7 +864,7 @@ int launch_whole(const BnPlan& p, BnWholeArgs a, void* ws, hipStream_t st) {
 #define JZ_BW(K, KL, MASKS) go(std::integral_constant<int, K>{}, std::integral_constant<int, KL>{}, std::integral_constant<int, MASKS>{})
   if (passes <= 4) return JZ_BW(4, 0, 0);
   if (passes <= 8) return JZ_BW(8, 0, 0);
-  if constexpr (MODE == BW_FWD) return passes <= 16 ? JZ_BW(16, 0, 0) : passes <= 32 ? JZ_BW(32, 0, 0) : JZ_BW(44, 0, 0);
+  if constexpr (MODE == BW_FWD) return passes <= 16 ? JZ_BW(16, 0, 0) : passes <= 32 ? JZ_BW(32, 0, 0) : JZ_BW(43, 0, 0);
   else if constexpr (MODE == BW_RELU) return passes <= 14 ? JZ_BW(14, 0, 0) : passes <= 25 ? JZ_BW(18, 7, 0) : JZ_BW(18, 6, 56);
   else return passes <= 12 ? JZ_BW(8, 4, 0) : JZ_BW(10, 6, 0);
 #undef JZ_BW

@@ -15,7 +15,7 @@
 
 constexpr int BW_WGS = 256;                      // workgroups at most: all of them run at the same time
 constexpr int BW_U = 4;                          // passes beyond the kept ones whose loads are in flight together
-constexpr int BW_UL = 2;                         // ... of the passes kept in LDS
+constexpr int BW_UL = 2;                         // ... of the passes kept in LDS, and of rows taken over
 constexpr int BW_Y = 2;                          // passes ahead of which y is requested: registers are what there is least of
 
 typedef unsigned u32x4_bw __attribute__((ext_vector_type(4)));
@@ -29,16 +29,17 @@ struct BnWholeArgs {
   double* part = nullptr;                // [slabs][2][C] sums
   unsigned long long* flags = nullptr;   // one a workgroup
   unsigned long long tag = 0;            // this launch's, two low bits clear
-  long long wait_ticks = 0;              // of the 100 MHz clock: the longest wait
+  long long wait_ticks = 0;              // of the 100 MHz clock: see look()
   int64_t rows = 0;
   int rows_per_wg = 0, C = 0, groups = 0, wgs = 0;  // groups of BW_CH channels, workgroups a group
-  int relu = 0;
+  int relu = 0, in_place = 0;  // in_place: g_out is dy
   double inv_rows = 0;
   float eps = 0;
 };
 
-// what a workgroup's flag says in its two low bits, beside the launch's tag
-enum { BW_ARRIVED = 1, BW_LEFT = 2, BW_TAKEN = 3 };
+// what the flag of a workgroup's rows says in its two low bits, beside the launch's tag: someone has them in hand; their sums are there
+enum { BW_CLAIMED = 1, BW_ARRIVED = 2 };
+enum { BW_ALL_THERE = -1, BW_LOST = -2 };  // ends of the exchange, beside the rows to take over next
 enum { BW_FWD, BW_GRAD, BW_RELU, BW_END };  // forward; backward of dy, of dy where y > 0, of RNE16(dy [+ dy2]) where y > 0
 
 // Ties a value to its registers here.  The kept rows stay packed and their offsets are worked out again: left alone the compiler
@@ -69,13 +70,24 @@ __device__ __forceinline__ void bw_performed() {
 #endif
 }
 
-// How the exchange ends.  A workgroup leaves its sums and a flag, then waits until all flags of its channels are there.  All
-// workgroups fit the chip together, so on a chip of their own they do arrive.  Beside other streams some may not have started:
-// a convolution there ends, but two launches of this kernel could hold half of the chip each.  So the wait is bounded: a workgroup whose
-// time is up marks its flag BW_LEFT, looks once more, and if a flag is still missing it ends, which frees its compute unit.
-// Whoever arrives later sees the mark (each side has written its flag before it reads the other's), and the workgroups that find
-// the exchange complete take the rows of those that left, reading them again.  Each mark is taken by one compare-and-swap, so
-// every row is written once, with the same bits either way.
+__device__ __forceinline__ void bw_barrier() {  // orders accesses to LDS, waits for nothing else
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+#endif
+}
+
+// How the exchange ends.  A workgroup leaves its sums and its flag, then waits until all flags of its channels are there.  All
+// workgroups fit the chip together, so on a chip of their own they do arrive.  Beside other streams some may not have started, and may not for
+// as long as a kernel there holds a compute unit (a collective, another launch of this kernel).  So nobody waits for those: a workgroup whose time is
+// up claims the rows of one that has not started, by one compare-and-swap on its flag, sums them out of memory in the order that their own
+// workgroup would have, and looks again; when all sums are there it writes those rows' results too.  A workgroup that finds its flag claimed
+// ends.  What is waited for is in the hands of a running workgroup, so every wait ends, and the bits do not depend on who did what.  Where
+// the own workgroup is slow rather than absent both may sum the same rows, into the same bits, and the flag says who writes the results; only a block end
+// in place, whose sums write g_out over dy, claims its rows before it starts (1 us more for short tensors).  So that slow ones are left alone the time to
+// wait is what the own rows took, and 10 us.  Microseconds while another kernel holds one compute unit, forward / backward with ReLU: launches apart;
+// waiting 100 us and leaving the rows of all to whoever comes last; this.
+//   802816 x 64    55 / 103    3640 / 6770    84 / 164        50176 x 512    31 / 59    26 / 391    26 / 81
+//   200704 x 256   55 / 103    1004 / 1210    78 / 150        12544 x 1024   19 / 38    13 / 199    14 / 56
 // The flags need no clearing: they count only with the tag of this launch, 62 bits that no launch of the process had before.
 // A captured graph would run the same tag again, so a capture takes the kernels in two launches.
 template <int MODE, int K, int KL, int MASKS>
@@ -83,8 +95,8 @@ __global__ __launch_bounds__(BW_THREADS) void bn_whole(BnWholeArgs a) {
   constexpr bool GRAD = MODE != BW_FWD, NEEDS_Y = MODE == BW_RELU || MODE == BW_END;
   __shared__ __align__(16) float red[2][BW_THREADS][8];  // 32 KB: the lanes' sums, then the workgroups'
   __shared__ __align__(16) float coef[3][BW_CH];
-  __shared__ unsigned long long seen[BW_WGS];
-  __shared__ int state, left_rows;
+  __shared__ unsigned short taken[BW_WGS];  // rows taken over
+  __shared__ int next, owner;
   extern __shared__ __align__(16) uint4 kept[];  // [KL][x, and backward the gradient][lane]
   constexpr int TENSORS = GRAD ? 2 : 1;
   unsigned char* const mask = reinterpret_cast<unsigned char*>(kept + KL * TENSORS * BW_THREADS);  // [MASKS][lane]: y > 0 of a pass that is read again
@@ -157,6 +169,15 @@ __global__ __launch_bounds__(BW_THREADS) void bn_whole(BnWholeArgs a) {
     return make_uint4(o[0], o[1], o[2], o[3]);
   };
 
+  unsigned long long* const flags = a.flags + (size_t)group * a.wgs;
+  const unsigned started = (unsigned)wall_clock64();
+  unsigned long long stale = 0;  // what lies in the own flag: from before this launch, unless the rows have been claimed
+  if (a.wgs > 1 && tid == 0) stale = __hip_atomic_load(flags + slab, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  auto claim = [&](int s, unsigned long long from, int as) {
+    if ((from & ~3ull) == a.tag) return false;
+    return __hip_atomic_compare_exchange_strong(flags + s, &from, a.tag | (unsigned long long)as, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
+
   // ---- the workgroup's rows and their sums ---------------------------------------------------------------------------
   const Rows own = rows_of(slab);
   const unsigned voff = (unsigned)rsub * pitch + (unsigned)c0 * 2u;
@@ -210,6 +231,12 @@ __global__ __launch_bounds__(BW_THREADS) void bn_whole(BnWholeArgs a) {
       }
     };
     request(0);
+    if constexpr (MODE == BW_END)
+      if (a.in_place && a.wgs > 1) {
+        if (tid == 0) owner = claim(slab, stale, BW_CLAIMED);
+        bw_barrier();  // the loads stay in flight
+        if (!owner) return;
+      }
 #pragma unroll
     for (int k = 0; k < K; k += BW_Y) {
       const int b = k / BW_Y % 2;
@@ -233,27 +260,27 @@ __global__ __launch_bounds__(BW_THREADS) void bn_whole(BnWholeArgs a) {
       keep(k);
     }
   }
-  auto add_passes = [&](auto u_tag, auto lds_tag, int p) {  // U passes from p on: the loads of all of them first
-    constexpr int U = decltype(u_tag)::value;
-    constexpr bool LDS = decltype(lds_tag)::value;
+  enum { OWN, OWN_LDS, TAKEN };
+  auto add_passes = [&](auto u_tag, auto whose_tag, const Rows& r, int p) {  // U passes from p on: the loads of all of them first
+    constexpr int U = decltype(u_tag)::value, WHOSE = decltype(whose_tag)::value;
     uint4 x8[U], g8[U], y8[U], e8[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const unsigned o = voff + (unsigned)(p + u) * step;
-      x8[u] = get(own.x, o);
-      if constexpr (GRAD) g8[u] = get(own.dy, o);
-      if constexpr (NEEDS_Y) y8[u] = get(own.y, o);
-      if constexpr (MODE == BW_END) e8[u] = get(own.dy2, o);
+      x8[u] = get(r.x, o);
+      if constexpr (GRAD) g8[u] = get(r.dy, o);
+      if constexpr (NEEDS_Y) y8[u] = get(r.y, o);
+      if constexpr (MODE == BW_END) e8[u] = get(r.dy2, o);
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       g8[u] = masked(g8[u], y8[u], e8[u]);
-      if constexpr (MODE == BW_END) put(own.g, voff + (unsigned)(p + u) * step, g8[u]);
-      if constexpr (LDS) {
+      if constexpr (MODE == BW_END) put(r.g, voff + (unsigned)(p + u) * step, g8[u]);
+      if constexpr (WHOSE == OWN_LDS) {
         uint4* const slot = kept + (size_t)(p + u - K) * TENSORS * BW_THREADS + tid;
         slot[0] = x8[u];
         if constexpr (GRAD) slot[BW_THREADS] = g8[u];
-      } else if constexpr (MASKS > 0) {
+      } else if constexpr (WHOSE == OWN && MASKS > 0) {
         if (p + u - K - KL < MASKS) mask[(p + u - K - KL) * BW_THREADS + tid] = positive(y8[u]);
       }
       add(x8[u], g8[u]);
@@ -261,18 +288,18 @@ __global__ __launch_bounds__(BW_THREADS) void bn_whole(BnWholeArgs a) {
   };
   if constexpr (KL > 0) {
 #pragma unroll 1
-    for (int l = 0; l + BW_UL <= KL; l += BW_UL) add_passes(std::integral_constant<int, BW_UL>{}, std::true_type{}, K + l);
-    if constexpr (KL % BW_UL != 0) add_passes(std::integral_constant<int, 1>{}, std::true_type{}, K + KL - 1);
+    for (int l = 0; l + BW_UL <= KL; l += BW_UL) add_passes(std::integral_constant<int, BW_UL>{}, std::integral_constant<int, OWN_LDS>{}, own, K + l);
+    if constexpr (KL % BW_UL != 0) add_passes(std::integral_constant<int, 1>{}, std::integral_constant<int, OWN_LDS>{}, own, K + KL - 1);
   }
-  for (int p = K + KL; p < passes; p += BW_U) add_passes(std::integral_constant<int, BW_U>{}, std::false_type{}, p);
+  for (int p = K + KL; p < passes; p += BW_U) add_passes(std::integral_constant<int, BW_U>{}, std::integral_constant<int, OWN>{}, own, p);
   // A lane's sums, of one in 64 of the workgroup's rows, are FP32; everything behind them is FP64, as in bn_stats for this plan's slabs.
+  auto leave_sums = [&](int to) {
 #pragma unroll
-  for (int e = 0; e < 8; e += 4) {
-    *reinterpret_cast<float4*>(&red[0][tid][e]) = make_float4(s0[e], s0[e + 1], s0[e + 2], s0[e + 3]);
-    *reinterpret_cast<float4*>(&red[1][tid][e]) = make_float4(s1[e], s1[e + 1], s1[e + 2], s1[e + 3]);
-  }
-  __syncthreads();
-  {
+    for (int e = 0; e < 8; e += 4) {
+      *reinterpret_cast<float4*>(&red[0][tid][e]) = make_float4(s0[e], s0[e + 1], s0[e + 2], s0[e + 3]);
+      *reinterpret_cast<float4*>(&red[1][tid][e]) = make_float4(s1[e], s1[e + 1], s1[e + 2], s1[e + 3]);
+    }
+    __syncthreads();
     constexpr int SUMS = 2 * BW_CH, PARTS = BW_THREADS / SUMS;
     const int i = tid % SUMS, first = tid / SUMS;
     const float* p = &red[0][0][0] + (i < BW_CH ? i : BW_THREADS * 8 + i - BW_CH);  // [row of a pass][BW_CH]
@@ -286,64 +313,87 @@ __global__ __launch_bounds__(BW_THREADS) void bn_whole(BnWholeArgs a) {
       t = 0;
 #pragma unroll
       for (int k = 0; k < PARTS; ++k) t += sums[k * SUMS + tid];
-      __hip_atomic_store(a.part + ((size_t)slab * 2 + tid / BW_CH) * a.C + group * BW_CH + tid % BW_CH, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(a.part + ((size_t)to * 2 + tid / BW_CH) * a.C + group * BW_CH + tid % BW_CH, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       bw_performed();
     }
-  }
+    __syncthreads();  // also where no other workgroup has rows: two wavefronts have left the sums that any of them reads
+  };
+  leave_sums(slab);
 
   // ---- the exchange -----------------------------------------------------------------------------------------------------
-  unsigned long long* const flags = a.flags + (size_t)group * a.wgs;
-  if constexpr (MODE == BW_END) bw_performed();  // g_out too: if this workgroup leaves, another reads it
-  __syncthreads();  // also where no other workgroup has rows: two wavefronts have left the sums that any of them reads
+  int n_taken = 0;
+  bool first_rows = slab == 0;  // whoever has them writes what the call returns beside the tensor
   if (a.wgs > 1) {
-    if (tid < 64) {  // the first wavefront looks, each lane at up to four flags
+    // the first wavefront looks, each lane at up to four flags: BW_ALL_THERE, or rows that it has claimed
+    auto look = [&](unsigned since, unsigned patience) -> int {
       constexpr int F = BW_WGS / 64;
-      unsigned long long v[F];
-      auto complete = [&] {
+      for (;;) {
+        unsigned long long v[F];
         bool all = true;
 #pragma unroll
         for (int f = 0; f < F; ++f) {
           v[f] = a.tag | BW_ARRIVED;
           if (tid + 64 * f < a.wgs) v[f] = __hip_atomic_load(flags + tid + 64 * f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          all &= (v[f] & ~3ull) == a.tag && (v[f] & 3ull) != 0;
+          all &= v[f] == (a.tag | BW_ARRIVED);
         }
-        return __all(all) != 0;
-      };
-      auto swap = [](unsigned long long* p, unsigned long long from, unsigned long long to) {
-        return __hip_atomic_compare_exchange_strong(p, &from, to, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      };
-      if (tid == 0) __hip_atomic_store(flags + slab, a.tag | BW_ARRIVED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      bw_performed();
-      const long long t_arrived = wall_clock64();
-      bool done;
-      while (!(done = complete())) {
-        if (wall_clock64() - t_arrived >= a.wait_ticks) break;
+        if (__all(all)) return BW_ALL_THERE;
+        if ((unsigned)wall_clock64() - since >= patience) {
+          unsigned long long absent[F];
+          int n = 0;
+#pragma unroll
+          for (int f = 0; f < F; ++f) {
+            absent[f] = __ballot((v[f] & ~3ull) != a.tag);
+            n += __popcll(absent[f]);
+          }
+          if (n > 0) {  // one of them, another one for every workgroup that looks
+            int rank = -(slab % n), won = 0;
+#pragma unroll
+            for (int f = 0; f < F; ++f) {
+              const bool mine = rank + __popcll(absent[f] & ((1ull << tid) - 1ull)) == 0 && (absent[f] >> tid & 1ull) != 0;
+              rank += __popcll(absent[f]);
+              if (mine && claim(tid + 64 * f, v[f], BW_CLAIMED)) won = tid + 64 * f + 1;
+            }
+            const unsigned long long who = __ballot(won != 0);
+            if (who != 0) return __shfl(won, __ffsll(who) - 1) - 1;
+            continue;
+          }
+        }
         __builtin_amdgcn_s_sleep(1);
       }
-      if (!done) {
-        if constexpr (MODE == BW_END) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-        if (tid == 0) __hip_atomic_store(flags + slab, a.tag | BW_LEFT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        bw_performed();
-        if (complete()) {
-          int mine = 0;  // unless another workgroup has taken the rows meanwhile
-          if (tid == 0) mine = swap(flags + slab, a.tag | BW_LEFT, a.tag | BW_TAKEN);
-          done = __shfl(mine, 0) != 0;
-        }
-      }
-      bool left = false;
-#pragma unroll
-      for (int f = 0; f < F; ++f) {
-        left |= tid + 64 * f != slab && (v[f] & 3ull) == BW_LEFT;
-        seen[tid + 64 * f] = v[f];
-      }
-      left = __any(left) != 0;
+    };
+    unsigned since = 0, patience = 0;
+    if (tid < 64) {
+      int has = 1;
       if (tid == 0) {
-        state = done;
-        left_rows = left;
+        if (MODE == BW_END && a.in_place) __hip_atomic_store(flags + slab, a.tag | BW_ARRIVED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        else has = claim(slab, stale, BW_ARRIVED);
       }
+      has = __shfl(has, 0);
+      since = (unsigned)wall_clock64();
+      patience = a.wait_ticks > 0 ? (unsigned)a.wait_ticks + (since - started) : 0u;
+      const int l = has ? look(since, patience) : (int)BW_LOST;
+      if (tid == 0) next = l;
     }
     __syncthreads();
-    if (!state) return;
+    int s;
+    while ((s = next) >= 0) {
+      if (tid == 0) taken[n_taken] = (unsigned short)s;
+      ++n_taken;
+      first_rows |= s == 0;
+      const Rows r = rows_of(s);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) s0[e] = s1[e] = 0.f;
+      const int n = (r.n + BW_ROWS - 1) / BW_ROWS;
+      for (int p = 0; p < n; p += BW_UL) add_passes(std::integral_constant<int, BW_UL>{}, std::integral_constant<int, TAKEN>{}, r, p);
+      leave_sums(s);
+      if (tid < 64) {
+        if (tid == 0) __hip_atomic_store(flags + s, a.tag | BW_ARRIVED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const int l = look(since, patience);
+        if (tid == 0) next = l;
+      }
+      __syncthreads();
+    }
+    if (s == BW_LOST) return;
   }
 
   // ---- the channels' totals, FP64, in bn_slab_totals' order -----------------------------------------------------------
@@ -399,7 +449,7 @@ __global__ __launch_bounds__(BW_THREADS) void bn_whole(BnWholeArgs a) {
     }
     __syncthreads();
   };
-  finish(slab == 0);
+  finish(first_rows);
 
   // ---- the results ------------------------------------------------------------------------------------------------------
   float ca[8], cb[8], cq[8];
@@ -423,14 +473,14 @@ __global__ __launch_bounds__(BW_THREADS) void bn_whole(BnWholeArgs a) {
     }
     return pack8(o);
   };
-  // passes from p on of a workgroup's rows out of memory.  Its own are masked already, by bits; a block end's are in g_out, also those of a
-  // workgroup that left (g_out may be dy, which is gone then)
+  // passes from p on of a workgroup's rows out of memory.  Its own are masked already, by bits; a block end's are in g_out, also those taken
+  // over (g_out may be dy, which is gone then)
   auto stream = [&](const Rows& r, int p, auto own_tag) {
-    constexpr bool OWN = decltype(own_tag)::value;
+    constexpr bool IS_OWN = decltype(own_tag)::value;
     const int n = (r.n + BW_ROWS - 1) / BW_ROWS;
     for (; p < n; p += BW_U) {
       uint4 x8[BW_U], g8[BW_U], y8[BW_U];
-      const bool bits = OWN && MASKS > 0 && p + BW_U - 1 - K - KL < MASKS;
+      const bool bits = IS_OWN && MASKS > 0 && p + BW_U - 1 - K - KL < MASKS;
 #pragma unroll
       for (int u = 0; u < BW_U; ++u) {
         const unsigned o = voff + (unsigned)(p + u) * step;
@@ -468,21 +518,5 @@ __global__ __launch_bounds__(BW_THREADS) void bn_whole(BnWholeArgs a) {
     put(own.out, off, result(qx[k], qg[GRAD ? k : 0]));
     bw_fence();
   }
-  if (a.wgs > 1 && left_rows) {  // rows of workgroups that left: each is taken once
-    for (int d = 1; d < a.wgs; ++d) {
-      const int s = slab + d < a.wgs ? slab + d : slab + d - a.wgs;
-      if ((seen[s] & 3ull) != BW_LEFT) continue;
-      __syncthreads();
-      if (tid == 0) {
-        unsigned long long expected = a.tag | BW_LEFT;
-        state = __hip_atomic_compare_exchange_strong(flags + s, &expected, a.tag | BW_TAKEN, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                     __HIP_MEMORY_SCOPE_AGENT);
-      }
-      __syncthreads();
-      if (!state) continue;
-      if constexpr (MODE == BW_END) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-      if (s == 0) finish(true);
-      stream(rows_of(s), 0, std::false_type{});
-    }
-  }
+  for (int i = 0; i < n_taken; ++i) stream(rows_of(taken[i]), 0, std::false_type{});
 }

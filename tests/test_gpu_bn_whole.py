@@ -180,6 +180,37 @@ def test_sums_between_lanes_and_workgroups_are_fp64(jz, rows, C):
     assert _same(o, b) == {}
 
 
+@pytest.mark.parametrize("rows,C", [(802816, 64), (200704 - 37, 256), (50176, 512)])
+def test_beside_a_kernel_that_holds_a_compute_unit(jz, rows, C):
+    """Tensors that need all compute units, while another stream's kernel has one for 20 ms: the rows of the workgroup that cannot start are taken over, with
+    the same bits, and long before that kernel ends.  The bound is ten times the slowest of these calls; waiting for the absent workgroup or leaving it the
+    others' rows took 1 to 20 ms."""
+    c = Case(jz, rows, C)
+    a, b = c.outputs(), c.outputs()
+    c.run(a)
+    side, ev = torch.cuda.Stream(), lambda: torch.cuda.Event(enable_timing=True)
+    torch.cuda._sleep(1000)
+    torch.cuda.synchronize()
+    t = ev(), ev()
+    t[0].record()
+    torch.cuda._sleep(2000000)
+    t[1].record()
+    torch.cuda.synchronize()
+    per_ms = 2000000 / t[0].elapsed_time(t[1])
+    with torch.cuda.stream(side):
+        torch.cuda._sleep(int(20 * per_ms))
+    torch.cuda._sleep(int(0.1 * per_ms))          # the other one has started
+    t = ev(), ev()
+    t[0].record()
+    c.run(b)
+    t[1].record()
+    t[1].synchronize()
+    held = not side.query()
+    torch.cuda.synchronize()
+    assert _same(a, b) == {}
+    assert held and t[0].elapsed_time(t[1]) <= 10 * 4 * 0.25, t[0].elapsed_time(t[1])
+
+
 def test_several_streams_at_once(jz):
     cases = [Case(jz, 20000 + 64 * i, 128, seed=i) for i in range(5)]
     want = [c.outputs() for c in cases]
