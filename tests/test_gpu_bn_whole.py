@@ -12,11 +12,11 @@ def jz():
     from paper_1807_11205_amd import api
     api.lib()
     assert torch.cuda.is_available()
-    c = Case(api, 64, 64)
+    c = Case(api, 512, 64)
     o = c.outputs()
     for _ in range(66):            # one stream a device runs it in one launch: the one that called last, and often
         c.forward(o)
-    torch.cuda.synchronize()
+    assert _in_one_launch(c, lambda: c.forward(o))
     yield api
     api.jz_bn_tune_wait(100)
 
@@ -48,6 +48,25 @@ class Case:
         jz.jz_bn_relu_bwd(r, c, self.x, o["y"], self.dy, self.gamma, o["mean"], o["invstd"], True, o["dx"], o["dg"], o["db"], self.ws)
         jz.jz_bn_relu_bwd(r, c, self.x, None, self.dy, self.gamma, o["mean"], o["invstd"], False, o["dx0"], o["dg0"], o["db0"], self.ws)
         jz.jz_bn_bwd_block_end(r, c, self.x, o["y"], self.dy, self.dy2, self.gamma, o["mean"], o["invstd"], o["g"], o["dxe"], o["dge"], o["dbe"], self.ws)
+
+
+def _plan(rows, C):
+    """Slabs and groups of channels of the one launch."""
+    groups, least = C // 64, 256 if rows <= 256 or rows >= 4096 else 128
+    return -(-rows // max(least, -(-rows // (256 // groups)))), groups
+
+
+def _in_one_launch(c, call):
+    """Whether a call ran in one launch: it leaves the launch's tag and "sums are there" (2) in a word for every workgroup behind the slabs' FP64 sums."""
+    slabs, groups = _plan(c.rows, c.C)
+    assert slabs > 1, "workgroups that wait for nobody leave no flags"
+    at = (slabs * 2 * c.C * 8 + 255) // 256 * 256
+    c.ws.fill_(0xCD)
+    torch.cuda.synchronize()
+    call()
+    torch.cuda.synchronize()
+    words = c.ws[at:at + 8 * slabs * groups].view(torch.int64)
+    return bool((words == words[0]).all()) and int(words[0]) & 3 == 2
 
 
 def _same(a, b):
@@ -113,12 +132,15 @@ def test_edges(jz, rows, C):
     c = Case(jz, rows, C)
     a, b = c.outputs(), c.outputs()
     c.ws.fill_(0xCD)
-    c.run(a)
-    torch.cuda.synchronize()
+    if _plan(rows, C)[0] > 1:
+        assert _in_one_launch(c, lambda: c.run(a))
+    else:
+        c.run(a)
+        torch.cuda.synchronize()
     _check(c, a)
     _graph_run(c, b)
     assert _same(a, b) == {}
-    jz.jz_bn_tune_wait(0)          # nobody waits: the last workgroup to arrive finds most others gone
+    jz.jz_bn_tune_wait(0)          # nobody waits: whoever is first takes rows over
     try:
         for _ in range(3):
             b = c.outputs(fill=-3.0)
@@ -130,12 +152,11 @@ def test_edges(jz, rows, C):
         jz.jz_bn_tune_wait(100)
 
 
-@pytest.mark.parametrize("passes", [33, 46, 47, 82])
+@pytest.mark.parametrize("passes", [33, 43, 44, 46, 47, 80, 81, 82])   # forward keeps 43, backward 25, and the bits of 56 beyond 24
 def test_more_rows_than_are_kept(jz, passes):
     c = Case(jz, passes * 64 * 64 - 5, 256)
     a, b = c.outputs(), c.outputs()
-    c.run(a)
-    torch.cuda.synchronize()
+    assert _in_one_launch(c, lambda: c.run(a))
     _check(c, a)
     _graph_run(c, b)
     assert _same(a, b) == {}
@@ -221,13 +242,24 @@ def test_several_streams_at_once(jz):
     for _ in range(4):
         got = [c.outputs() for c in cases]
         torch.cuda.synchronize()
-        for _ in range(30):         # the right to the one launch moves between the streams meanwhile
+        for _ in range(30):         # one of the streams has the one launch
             for c, o, s in zip(cases, got, streams):
                 with torch.cuda.stream(s):
                     c.run(o)
         torch.cuda.synchronize()
         for a, b in zip(want, got):
             assert _same(a, b) == {}
+    got = [c.outputs() for c in cases]
+    torch.cuda.synchronize()
+    for c, o, s in zip(cases, got, streams):
+        with torch.cuda.stream(s):
+            for _ in range(18):     # 72 calls: it moves on to this stream while the work of the one before is on its way
+                c.run(o)
+    torch.cuda.synchronize()
+    for a, b in zip(want, got):
+        assert _same(a, b) == {}
+    with torch.cuda.stream(streams[-1]):
+        assert _in_one_launch(cases[-1], lambda: cases[-1].run(got[-1]))
 
 
 def test_infinities_and_nan_stay_in_their_channels(jz):
@@ -237,7 +269,7 @@ def test_infinities_and_nan_stay_in_their_channels(jz):
     x = c.x.view(5000, 128)
     x[17, 3], x[4000, 70] = float("inf"), float("nan")
     o, b = c.outputs(), c.outputs()
-    c.run(o)
+    assert _in_one_launch(c, lambda: c.run(o))
     _graph_run(c, b)
     ok = [i for i in range(128) if i not in (3, 70)]
     for k in ("y", "dx", "dx0"):
