@@ -791,19 +791,36 @@ bool clear_of(const void* ws, size_t n, std::initializer_list<std::pair<const vo
 }
 
 thread_local int t_bn_wait_us = 10;
-// 62 bits of a counter that starts where the clock stood, mixed: no launch of this process has had them, and sums that an earlier call left in
-// the workspace do not look like them
+// A counter that starts where the clock stood, of 62 bits, mixed by steps that keep different numbers different (odd factors, shifted xors): no launch of
+// this process has had the result, and sums that an earlier call left in the workspace do not look like it.
 unsigned long long bw_tag() {
   static std::atomic<unsigned long long> launches{(unsigned long long)std::chrono::steady_clock::now().time_since_epoch().count()};
-  unsigned long long z = 0x9e3779b97f4a7c15ull * launches.fetch_add(1, std::memory_order_relaxed);
-  z = (z ^ (z >> 30)) * 0xbf58476d1ce4e5b9ull;
-  z = (z ^ (z >> 27)) * 0x94d049bb133111ebull;
-  return (z ^ (z >> 31)) & ~3ull;
+  constexpr unsigned long long BITS = (1ull << 62) - 1;
+  unsigned long long z;
+  do {
+    z = 0x9e3779b97f4a7c15ull * launches.fetch_add(1, std::memory_order_relaxed) & BITS;
+    z = (z ^ (z >> 30)) * 0xbf58476d1ce4e5b9ull & BITS;
+    z = (z ^ (z >> 27)) * 0x94d049bb133111ebull & BITS;
+    z ^= z >> 31;
+  } while (z == 0);  // what cleared memory holds
+  return z << 2;
+}
+
+// Whether the stream's workgroups may run on all compute units.
+bool bw_all_units(hipStream_t st) {
+  uint32_t mask[BW_WGS / 32] = {};
+  if (hipExtStreamGetCUMask(st, BW_WGS / 32, mask) != hipSuccess) {
+    (void)hipGetLastError();
+    return true;
+  }
+  int n = 0;
+  for (uint32_t m : mask) n += __builtin_popcount(m);
+  return n >= BW_WGS;
 }
 
 // Whether a call on this stream may take bn_whole: it wants the chip to itself, and several of them from different streams would
 // get in each other's way (four streams with 200704 x 64 each: 100 us a call instead of 21).  So one stream a device has it; another one
-// gets it after 64 calls without one of the first.  Never while the stream is captured.  Those calls run the passes apart on the same plan, for the
+// gets it after 64 calls without one of the first, unless its workgroups are kept to a part of the chip.  Never while the stream is captured.  Those calls run the passes apart on the same plan, for the
 // same bits.  Captured, microseconds, forward / backward with ReLU / block end, on the plan that other channel counts have and on this one:
 //   196 x 1024   6.5 /  7.4 /  7.8    5.4 /  6.5 /  7.1      3136 x 2048   13.6 / 22.7 / 28.5    10.8 / 22.4 / 29.5
 //   2048 x 128   6.4 /  7.6 /  7.8    6.9 /  7.7 /  8.6      12544 x 1024  17.2 / 39.2 / 46.8    14.3 / 38.5 / 48.5
@@ -823,14 +840,19 @@ bool bw_has_chip(const BnPlan& p, hipStream_t st) {
   if (capture != hipStreamCaptureStatusNone || hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return false;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < BW_WGS) return false;
   struct Owner {
-    std::atomic<uintptr_t> stream{1};  // no stream's handle
+    std::atomic<uintptr_t> stream{~uintptr_t(0)};  // no stream's handle
     std::atomic<int> others{64};
   };
   static Owner owners[64];
   Owner& o = owners[dev];
-  const uintptr_t me = reinterpret_cast<uintptr_t>(st);
+  // each thread has its own stream of that name
+  const uintptr_t me = st == hipStreamPerThread ? reinterpret_cast<uintptr_t>(&t_bn_wait_us) : reinterpret_cast<uintptr_t>(st);
   if (o.stream.load(std::memory_order_relaxed) != me) {
     if (o.others.fetch_add(1, std::memory_order_relaxed) < 64) return false;
+    if (!bw_all_units(st)) {
+      o.others.store(0, std::memory_order_relaxed);
+      return false;
+    }
     o.stream.store(me, std::memory_order_relaxed);
   }
   o.others.store(0, std::memory_order_relaxed);

@@ -262,6 +262,22 @@ def test_several_streams_at_once(jz):
         assert _in_one_launch(cases[-1], lambda: cases[-1].run(got[-1]))
 
 
+def test_a_stream_that_is_kept_to_half_of_the_compute_units(jz):
+    """It never has the one launch, whose workgroups it could not run together."""
+    import ctypes
+    hip, stream = ctypes.CDLL("libamdhip64.so"), ctypes.c_void_p()
+    assert hip.hipExtStreamCreateWithCUMask(ctypes.byref(stream), 8, (ctypes.c_uint32 * 8)(*[0xffffffff] * 4, *[0] * 4)) == 0
+    c = Case(jz, 50176, 128)
+    a, b = c.outputs(), c.outputs()
+    assert _in_one_launch(c, lambda: c.run(a))
+    with torch.cuda.stream(torch.cuda.ExternalStream(stream.value)):
+        for _ in range(70):
+            c.run(b)
+        torch.cuda.synchronize()
+        assert not _in_one_launch(c, lambda: c.run(b))
+    assert _same(a, b) == {}
+
+
 def test_infinities_and_nan_stay_in_their_channels(jz):
     c = Case(jz, 5000, 128)
     clean = c.outputs()
