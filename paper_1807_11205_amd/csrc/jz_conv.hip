@@ -717,14 +717,15 @@ void set_tiles(Plan* pl, int splits) {
   a.d_tiles_n = make_fastdiv((unsigned)a.tiles_n);
 }
 
-// Whether the window kernel's variant v takes this problem: unit stride, output grid = input grid, whole blocks of channels, and a
-// window that holds the tile's pixels and what their taps reach.
+// Whether the window kernel's variant v takes this problem: unit stride, output grid = input grid, whole blocks of channels, a
+// window that holds the tile's pixels and what their taps reach, and window offsets within 31 bits.
 bool window_fits(const Plan& pl, const WindowVariant& v) {
   const GemmArgs& a = pl.args;
   const ConvGeom& g = a.g;
   return (pl.op == JZ_FWD || pl.op == JZ_BWD_DATA) && pl.fast && !pl.packed && !pl.gen && !pl.flat && !a.sc_on && g.sh == 1 && g.sw == 1 &&
          g.IH == g.OH && g.IW == g.OW && 2 * g.ph + 1 == g.R && 2 * g.pw + 1 == g.S && g.R * g.S >= 9 && g.R * g.S <= 32 && g.IC % v.ck == 0 &&
-         (v.windows > 1 || g.IC == v.ck) && (long long)v.BM + (long long)(g.R - 1) * g.IW + g.S - 1 <= v.rows;
+         (v.windows > 1 || g.IC == v.ck) && (long long)v.BM + (long long)(g.R - 1) * g.IW + g.S - 1 <= v.rows &&
+         2ll * v.rows * g.IC < (1ll << 31);
 }
 
 // The entry (+ 1) that a recorded window variant names, 0 where it does not take this problem.  A key does not hold the image's width, the stride

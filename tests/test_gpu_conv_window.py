@@ -25,6 +25,18 @@ def test_which_layers_run_on_it():
     assert "window" not in plan(api.JZ_BWD_WEIGHT, 64, 56, 56, 64, 64, 3, 3, 1, 1)
 
 
+def test_offsets_within_a_window_have_31_bits():
+    """384 rows of so many channels; the tensors themselves (3 x 3 pixels, eight filters) are below the 4 GB that a descriptor reaches."""
+    for op, at in ((api.JZ_FWD, 3), (api.JZ_BWD_DATA, 4)):
+        d = [1, 3, 3, 8, 8, 3, 3, 1, 1]
+        d[at] = (1 << 31) // 768 // 64 * 64
+        api.jz_conv2d_tune_set(op, api.conv_desc(*d), *WIDE, 1)
+        api.jz_conv2d_tune_clear()
+        d[at] += 64
+        with pytest.raises(RuntimeError):
+            api.jz_conv2d_tune_set(op, api.conv_desc(*d), *WIDE, 1)
+
+
 @pytest.mark.parametrize("variant,fits,others", [
     (NARROW, (64, 56, 56, 64, 64, 3, 3, 1, 1), [(16, 112, 112, 64, 64, 3, 3, 1, 1), (64, 112, 112, 64, 64, 3, 3, 2, 1), (64, 58, 58, 64, 64, 3, 3, 1, 0)]),
     (WIDE, (16, 28, 28, 128, 128, 3, 3, 1, 1), [(1, 112, 112, 128, 128, 3, 3, 1, 1), (16, 30, 30, 128, 128, 3, 3, 1, 0)]),
