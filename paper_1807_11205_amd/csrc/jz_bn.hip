@@ -1030,8 +1030,10 @@ extern "C" int jz_bn_relu_fwd(int64_t rows, int channels, const void* x16, const
       jz::overlaps(save_mean, nc, x16, nb) || jz::overlaps(save_invstd, nc, x16, nb) || jz::overlaps(save_mean, nc, save_invstd, nc) ||
       jz::overlaps(save_mean, nc, y16, nb) || jz::overlaps(save_invstd, nc, y16, nb))
     return JZ_ERR_ALIAS;
-  BnPlan wp;
-  const bool whole = make_whole_plan(rows, channels, true, &wp) && ws_bytes >= wp.total &&
+  BnPlan wp;  // there the first workgroup of a range of channels writes the statistics while others still read gamma and beta
+  const bool apart_only = jz::overlaps(save_mean, nc, gamma, nc) || jz::overlaps(save_mean, nc, beta, nc) || jz::overlaps(save_invstd, nc, gamma, nc) ||
+                          jz::overlaps(save_invstd, nc, beta, nc);
+  const bool whole = !apart_only && make_whole_plan(rows, channels, true, &wp) && ws_bytes >= wp.total &&
                      clear_of(ws, wp.total, {{x16, nb}, {y16, nb}, {gamma, nc}, {beta, nc}, {save_mean, nc}, {save_invstd, nc}});
   if (whole) p = wp;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
