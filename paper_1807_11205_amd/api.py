@@ -10,10 +10,21 @@ from typing import Optional, Sequence
 import numpy as np
 import torch
 
-from . import _jz_host as _host      # built beside libjz.so; there is no fallback here either
+
+class _NativePart:
+    """_jz_host, the binding's native part, built beside libjz.so: looked for when it is first used, as the library is.  There is no fallback."""
+
+    def __getattr__(self, name):
+        global _host
+        from . import _jz_host
+        _host = _jz_host
+        return getattr(_jz_host, name)
+
+
+_host = _NativePart()
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
-LIB_PATH = os.environ.get("JZ_LIB_PATH", os.path.join(_PKG, "libjz.so"))
+LIB_PATH = os.environ.get("JZ_LIB_PATH", os.path.join(_PKG, "libjz.so"))      # another build of the library; the binding's part stays
 
 JZ_OK = 0
 JZ_ERR_NULL, JZ_ERR_SHAPE, JZ_ERR_UNSUPPORTED, JZ_ERR_WORKSPACE = -1, -2, -3, -4

@@ -53,3 +53,17 @@ def test_bound_calls_pass_every_kind_of_argument():
     assert api._words((1, 0.5)) is None and api._words(tuple(range(25))) is None
     with pytest.raises(api.JzError):        # a null output, found by the library
         api.BoundCall(api.lib().jz_conv2d_fwd, (ctypes.byref(d), 16, 32, None, None, 0), "jz_conv2d_fwd", (d,))(0)
+
+
+def test_the_binding_can_be_imported_before_anything_is_built(tmp_path):
+    """Descriptors, status names and shapes need no native code; the first call that does says what is missing."""
+    import shutil
+    import subprocess
+    import sys
+    import paper_1807_11205_amd
+    src = paper_1807_11205_amd.__path__[0]
+    shutil.copytree(src, tmp_path / "paper_1807_11205_amd", ignore=shutil.ignore_patterns("*.so", "__pycache__", "csrc"))
+    code = ("import ctypes, torch\nfrom paper_1807_11205_amd import api, shapes, tune\nd = api.conv_desc(1, 8, 8, 16, 16, 3, 3, 1, 1)\n"
+            "assert d.P == 8 and shapes.resnet50_convs()\ntry:\n    api._dev_ptr(torch.zeros(1), torch.float32)\nexcept ImportError:\n    print('missing')\n")
+    out = subprocess.run([sys.executable, "-c", code], cwd=tmp_path, capture_output=True, text=True, timeout=120)
+    assert out.returncode == 0 and out.stdout.strip() == "missing", out.stderr
