@@ -111,56 +111,86 @@ struct PoolGeom {
 // took three of 64 bits, which bound them.  112 x 112 x 64 -> 56 x 56, 64 images: forward 46.7 -> 36.3 us (142 MB; the comparisons of a
 // window's 9 x 8 elements are 16 of it), backward from the saved winners 55 -> 36 (141 MB).  Strips of 4 to 16 rows a workgroup, for the
 // rows that windows share, were slower the longer they were (48 to 67, 39 to 46 us): too few loads in flight.
-dim3 pool_grid(int64_t row, int rows, int images) {
-  constexpr int MOST = 65535;
-  return dim3((unsigned)((row + LY_THREADS - 1) / LY_THREADS), (unsigned)(rows < MOST ? rows : MOST), (unsigned)(images < MOST ? images : MOST));
+// Rows of up to half a workgroup share one (SHORT), for two more divisions: 8 x 8 x 8, 4096 images, windows of 2 x 2: 10.0 -> 2.9 us forward, 17.5 -> 4.3
+// backward; 14 x 14 x 16, 512 images: 4.3 -> 2.9, 6.1 -> 4.1.
+struct PoolWalk {
+  int64_t row, rows;  // positions x 8 channels of a row; rows of an image, of all images (SHORT)
+  int images, k;      // k: rows of a workgroup
+  int64_t first = 0;  // of a row: a launch takes up to MOST_X workgroups of it, since the threads of a dimension are counted in 32 bits
+  static constexpr int64_t MOST_X = 1 << 23;
+};
+// launch(whether rows share a workgroup, grid, walk) as often as it takes
+template <class F>
+int pool_launch(int64_t row, int rows, int images, F launch) {
+  auto least = [](int64_t a, int64_t b) { return (unsigned)(a < b ? a : b); };
+  constexpr int64_t MOST = 65535;
+  if (row <= LY_THREADS / 2) {
+    const PoolWalk w{row, (int64_t)rows * images, 1, (int)(LY_THREADS / row)};
+    launch(std::true_type{}, dim3(1, least((w.rows + w.k - 1) / w.k, MOST)), w);
+    return jz::launch_status();
+  }
+  for (PoolWalk w{row, rows, images, 1}; w.first < row; w.first += PoolWalk::MOST_X * LY_THREADS) {
+    launch(std::false_type{}, dim3(least((row - w.first + LY_THREADS - 1) / LY_THREADS, PoolWalk::MOST_X), least(rows, MOST), least(images, MOST)), w);
+    const int rc = jz::launch_status();
+    if (rc != JZ_OK) return rc;
+  }
+  return JZ_OK;
 }
 
-// column and channel group of a thread
-__device__ __forceinline__ void pool_place(int C8, int& col, int& c) {
-  const uint64_t i = (uint64_t)blockIdx.x * LY_THREADS + threadIdx.x;
-  col = (i >> 32) == 0 ? (int)((unsigned)i / (unsigned)C8) : (int)(i / (unsigned)C8);
-  c = (int)(i - (uint64_t)(unsigned)col * (unsigned)C8);
+// f(image, row, column, channel group) for what falls to this thread; rows: of an image
+template <bool SHORT, class F>
+__device__ __forceinline__ void for_positions(const PoolWalk& w, int C8, int rows, F f) {
+  if constexpr (SHORT) {
+    const unsigned row = (unsigned)w.row, r = threadIdx.x / row, i = threadIdx.x - r * row, col = i / (unsigned)C8;
+    if (r >= (unsigned)w.k) return;
+    for (int64_t R = (int64_t)blockIdx.y * w.k + r; R < w.rows; R += (int64_t)gridDim.y * w.k) {
+      const int n = (R >> 32) == 0 ? (int)((unsigned)R / (unsigned)rows) : (int)(R / rows);
+      f(n, (int)(R - (int64_t)n * rows), (int)col, (int)(i - col * (unsigned)C8));
+    }
+  } else {
+    const int64_t i = w.first + (int64_t)blockIdx.x * LY_THREADS + threadIdx.x;
+    if (i >= w.row) return;
+    const int col = (i >> 32) == 0 ? (int)((unsigned)i / (unsigned)C8) : (int)(i / C8);
+    const int c = (int)(i - (int64_t)col * C8);
+    for (int n = blockIdx.z; n < w.images; n += gridDim.z)
+      for (int p = blockIdx.y; p < rows; p += gridDim.y) f(n, p, col, c);
+  }
 }
 
 // WIN > 0: window size known at compile time (loops unrolled, the window's loads in flight together); 0: g.window
-template <int WIN>
+template <int WIN, bool SHORT>
 __global__ __launch_bounds__(LY_THREADS) void maxpool_fwd_kernel(const uint4* __restrict__ x, uint4* __restrict__ y,
-                                                                 uint2* __restrict__ arg, PoolGeom g) {
+                                                                 uint2* __restrict__ arg, PoolGeom g, PoolWalk walk) {
   const int window = WIN > 0 ? WIN : g.window;
-  int q, c;
-  pool_place(g.C8, q, c);
-  if (q >= g.Q) return;
-  for (int n = blockIdx.z; n < g.N; n += gridDim.z)
-    for (int p = blockIdx.y; p < g.P; p += gridDim.y) {
-      // A position outside the image is read at the nearest inside, which the window has too, and counted as that one: no branch around the
-      // load, and the first maximum stays the first (its row and column are the first or the last inside).
-      float best[8];
-      unsigned win[8];  // position r * window + s of the first maximum
-      const int top = p * g.stride - g.pad, left = q * g.stride - g.pad;
+  for_positions<SHORT>(walk, g.C8, g.P, [&](int n, int p, int q, int c) {
+    // A position outside the image is read at the nearest inside, which the window has too, and counted as that one: no branch around the
+    // load, and the first maximum stays the first (its row and column are the first or the last inside).
+    float best[8];
+    unsigned win[8];  // position r * window + s of the first maximum
+    const int top = p * g.stride - g.pad, left = q * g.stride - g.pad;
 #pragma unroll(WIN > 0 ? WIN : 1)
-      for (int r = 0; r < window; ++r) {
-        const int h = top + r, hc = h < 0 ? 0 : (h >= g.H ? g.H - 1 : h);
-        const uint4* const row = x + ((int64_t)n * g.H + hc) * g.W * g.C8 + c;
+    for (int r = 0; r < window; ++r) {
+      const int h = top + r, hc = h < 0 ? 0 : (h >= g.H ? g.H - 1 : h);
+      const uint4* const row = x + ((int64_t)n * g.H + hc) * g.W * g.C8 + c;
 #pragma unroll(WIN > 0 ? WIN : 1)
-        for (int s = 0; s < window; ++s) {
-          const int w = left + s, wc = w < 0 ? 0 : (w >= g.W ? g.W - 1 : w);
-          const unsigned at = (unsigned)((hc - top) * window + wc - left);
-          float v[8];
-          unpack8(row[(int64_t)wc * g.C8], v);
+      for (int s = 0; s < window; ++s) {
+        const int w = left + s, wc = w < 0 ? 0 : (w >= g.W ? g.W - 1 : w);
+        const unsigned at = (unsigned)((hc - top) * window + wc - left);
+        float v[8];
+        unpack8(row[(int64_t)wc * g.C8], v);
 #pragma unroll
-          for (int k = 0; k < 8; ++k) {
-            const bool better = (r == 0 && s == 0) || v[k] > best[k];
-            best[k] = better ? v[k] : best[k];
-            win[k] = better ? at : win[k];
-          }
+        for (int k = 0; k < 8; ++k) {
+          const bool better = (r == 0 && s == 0) || v[k] > best[k];
+          best[k] = better ? v[k] : best[k];
+          win[k] = better ? at : win[k];
         }
       }
-      const int64_t i = (((int64_t)n * g.P + p) * g.Q + q) * g.C8 + c;
-      y[i] = pack8(best);
-      if (arg)
-        arg[i] = make_uint2(win[0] | (win[1] << 8) | (win[2] << 16) | (win[3] << 24), win[4] | (win[5] << 8) | (win[6] << 16) | (win[7] << 24));
     }
+    const int64_t i = (((int64_t)n * g.P + p) * g.Q + q) * g.C8 + c;
+    y[i] = pack8(best);
+    if (arg)
+      arg[i] = make_uint2(win[0] | (win[1] << 8) | (win[2] << 16) | (win[3] << 24), win[4] | (win[5] << 8) | (win[6] << 16) | (win[7] << 24));
+  });
 }
 
 // one thread per input position and 8 channels: it looks at every window that contains the position, finds that
@@ -224,103 +254,97 @@ __global__ __launch_bounds__(LY_THREADS) void maxpool_bwd_kernel(const uint4* __
 }
 
 // the same gather from the winners the forward pass saved: nothing is re-derived, x is not read
+template <bool SHORT>
 __global__ __launch_bounds__(LY_THREADS) void maxpool_bwd_arg_kernel(const uint2* __restrict__ arg, const uint4* __restrict__ dy,
-                                                                     uint4* __restrict__ dx, PoolGeom g) {
-  int w0, c;
-  pool_place(g.C8, w0, c);
-  if (w0 >= g.W) return;
-  int q_lo = w0 + g.pad - g.window + 1;
-  q_lo = q_lo <= 0 ? 0 : (q_lo + g.stride - 1) / g.stride;
-  int q_hi = (w0 + g.pad) / g.stride;
-  if (q_hi > g.Q - 1) q_hi = g.Q - 1;
-  for (int n = blockIdx.z; n < g.N; n += gridDim.z)
-    for (int h0 = blockIdx.y; h0 < g.H; h0 += gridDim.y) {
-      float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-      int p_lo = h0 + g.pad - g.window + 1;
-      p_lo = p_lo <= 0 ? 0 : (p_lo + g.stride - 1) / g.stride;
-      int p_hi = (h0 + g.pad) / g.stride;
-      if (p_hi > g.P - 1) p_hi = g.P - 1;
-      for (int p = p_lo; p <= p_hi; ++p)
-        for (int q = q_lo; q <= q_hi; ++q) {
-          const unsigned me = (unsigned)((h0 - (p * g.stride - g.pad)) * g.window + (w0 - (q * g.stride - g.pad)));
-          const int64_t o = (((int64_t)n * g.P + p) * g.Q + q) * g.C8 + c;
-          const uint2 a = arg[o];
-          float gy[8];
-          unpack8(dy[o], gy);
+                                                                     uint4* __restrict__ dx, PoolGeom g, PoolWalk walk) {
+  for_positions<SHORT>(walk, g.C8, g.H, [&](int n, int h0, int w0, int c) {
+    int q_lo = w0 + g.pad - g.window + 1;
+    q_lo = q_lo <= 0 ? 0 : (q_lo + g.stride - 1) / g.stride;
+    int q_hi = (w0 + g.pad) / g.stride;
+    if (q_hi > g.Q - 1) q_hi = g.Q - 1;
+    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    int p_lo = h0 + g.pad - g.window + 1;
+    p_lo = p_lo <= 0 ? 0 : (p_lo + g.stride - 1) / g.stride;
+    int p_hi = (h0 + g.pad) / g.stride;
+    if (p_hi > g.P - 1) p_hi = g.P - 1;
+    for (int p = p_lo; p <= p_hi; ++p)
+      for (int q = q_lo; q <= q_hi; ++q) {
+        const unsigned me = (unsigned)((h0 - (p * g.stride - g.pad)) * g.window + (w0 - (q * g.stride - g.pad)));
+        const int64_t o = (((int64_t)n * g.P + p) * g.Q + q) * g.C8 + c;
+        const uint2 a = arg[o];
+        float gy[8];
+        unpack8(dy[o], gy);
 #pragma unroll
-          for (int k = 0; k < 8; ++k) {
-            const unsigned wk = ((k < 4 ? a.x : a.y) >> (8 * (k & 3))) & 0xffu;
-            acc[k] += wk == me ? gy[k] : 0.f;
-          }
+        for (int k = 0; k < 8; ++k) {
+          const unsigned wk = ((k < 4 ? a.x : a.y) >> (8 * (k & 3))) & 0xffu;
+          acc[k] += wk == me ? gy[k] : 0.f;
         }
-      dx[(((int64_t)n * g.H + h0) * g.W + w0) * g.C8 + c] = pack8(acc);
-    }
+      }
+    dx[(((int64_t)n * g.H + h0) * g.W + w0) * g.C8 + c] = pack8(acc);
+  });
 }
 
 // ... for 3 x 3 windows with stride 2: positions 2 a + 1 and 2 a + 2 of the padded image meet windows a and a + 1, so a thread takes a 2 x 2
 // cell and requests its 2 x 2 windows at once (position by position they are nine).  The general kernel's order of sums.
+template <bool SHORT>
 __global__ __launch_bounds__(LY_THREADS) void maxpool_bwd_arg_3x3s2_kernel(const uint2* __restrict__ arg, const uint4* __restrict__ dy,
-                                                                           uint4* __restrict__ dx, PoolGeom g, int first, int rows, int cols) {
-  int bi, c;
-  pool_place(g.C8, bi, c);
-  const int b = first + bi;
-  if (bi >= cols) return;
-  for (int n = blockIdx.z; n < g.N; n += gridDim.z)
-    for (int ai = blockIdx.y; ai < rows; ai += gridDim.y) {
-      const int a = first + ai;
-      uint2 win[2][2];
-      uint4 gq[2][2];
+                                                                           uint4* __restrict__ dx, PoolGeom g, int first, int rows, PoolWalk walk) {
+  for_positions<SHORT>(walk, g.C8, rows, [&](int n, int ai, int bi, int c) {
+    const int a = first + ai, b = first + bi;
+    uint2 win[2][2];
+    uint4 gq[2][2];
 #pragma unroll
-      for (int dp = 0; dp < 2; ++dp)
+    for (int dp = 0; dp < 2; ++dp)
 #pragma unroll
-        for (int dq = 0; dq < 2; ++dq) {
-          const int p = a + dp, q = b + dq;
-          win[dp][dq] = make_uint2(~0u, ~0u);  // no position's number
-          gq[dp][dq] = make_uint4(0u, 0u, 0u, 0u);
-          if (p >= 0 && p < g.P && q >= 0 && q < g.Q) {
-            const int64_t o = (((int64_t)n * g.P + p) * g.Q + q) * g.C8 + c;
-            win[dp][dq] = arg[o];
-            gq[dp][dq] = dy[o];
-          }
+      for (int dq = 0; dq < 2; ++dq) {
+        const int p = a + dp, q = b + dq;
+        win[dp][dq] = make_uint2(~0u, ~0u);  // no position's number
+        gq[dp][dq] = make_uint4(0u, 0u, 0u, 0u);
+        if (p >= 0 && p < g.P && q >= 0 && q < g.Q) {
+          const int64_t o = (((int64_t)n * g.P + p) * g.Q + q) * g.C8 + c;
+          win[dp][dq] = arg[o];
+          gq[dp][dq] = dy[o];
         }
-      float acc[2][2][8];
+      }
+    float acc[2][2][8];
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+      for (int j = 0; j < 2; ++j)
 #pragma unroll
-          for (int k = 0; k < 8; ++k) acc[i][j][k] = 0.f;
+        for (int k = 0; k < 8; ++k) acc[i][j][k] = 0.f;
 #pragma unroll
-      for (int dp = 0; dp < 2; ++dp)
+    for (int dp = 0; dp < 2; ++dp)
 #pragma unroll
-        for (int dq = 0; dq < 2; ++dq) {
-          float gy[8];
-          unpack8(gq[dp][dq], gy);
+      for (int dq = 0; dq < 2; ++dq) {
+        float gy[8];
+        unpack8(gq[dp][dq], gy);
 #pragma unroll
-          for (int k = 0; k < 8; ++k) {
-            const unsigned wk = ((k < 4 ? win[dp][dq].x : win[dp][dq].y) >> (8 * (k & 3))) & 0xffu;
+        for (int k = 0; k < 8; ++k) {
+          const unsigned wk = ((k < 4 ? win[dp][dq].x : win[dp][dq].y) >> (8 * (k & 3))) & 0xffu;
 #pragma unroll
-            for (int i = dp; i < 2; ++i)
+          for (int i = dp; i < 2; ++i)
 #pragma unroll
-              for (int j = dq; j < 2; ++j) acc[i][j][k] += wk == (unsigned)((1 + i - 2 * dp) * 3 + 1 + j - 2 * dq) ? gy[k] : 0.f;
-          }
+            for (int j = dq; j < 2; ++j) acc[i][j][k] += wk == (unsigned)((1 + i - 2 * dp) * 3 + 1 + j - 2 * dq) ? gy[k] : 0.f;
         }
+      }
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          const int h = 2 * a + 1 + i - g.pad, w = 2 * b + 1 + j - g.pad;
-          if (h >= 0 && h < g.H && w >= 0 && w < g.W) dx[(((int64_t)n * g.H + h) * g.W + w) * g.C8 + c] = pack8(acc[i][j]);
-        }
-    }
+      for (int j = 0; j < 2; ++j) {
+        const int h = 2 * a + 1 + i - g.pad, w = 2 * b + 1 + j - g.pad;
+        if (h >= 0 && h < g.H && w >= 0 && w < g.W) dx[(((int64_t)n * g.H + h) * g.W + w) * g.C8 + c] = pack8(acc[i][j]);
+      }
+  });
 }
 
 // ---- global average pooling ----------------------------------------------------------------------------------------
-// Sixteen positions requested together, added in order; small workgroups, for as many compute units as there are (64 images of 7 x 7 x 2048: 26.2 -> 9.0 us).
+// U positions requested together, added in order; small workgroups, for as many compute units as there are (64 images of 7 x 7 x 2048, U = 16: 26.2 -> 9.0 us).
+// Images of fewer than 16 positions take four at a time: what is requested beyond them costs (one position of 2048 channels, 64 images: 3.3 us, 2.7).
 constexpr int AVG_THREADS = 64;
+template <int U>
 __global__ __launch_bounds__(AVG_THREADS) void avgpool_fwd_kernel(const uint4* __restrict__ x, uint4* __restrict__ y, int N, int HW,
                                                                   int C8) {
-  constexpr int U = 16;
   const int64_t total = (int64_t)N * C8;
   for (int64_t i = (int64_t)blockIdx.x * AVG_THREADS + threadIdx.x; i < total; i += (int64_t)gridDim.x * AVG_THREADS) {
     const int64_t n = i / C8;
@@ -524,18 +548,15 @@ extern "C" int jz_maxpool_fwd(int N, int H, int W, int C, int window, int stride
   if (!jz::aligned16(x16) || !jz::aligned16(y16) || (reinterpret_cast<uintptr_t>(arg8) & 7u)) return JZ_ERR_ALIGN;
   const size_t nx = (size_t)N * H * W * C * 2, ny = (size_t)N * g.P * g.Q * C * 2;
   if (jz::overlaps(x16, nx, y16, ny) || jz::overlaps(arg8, ny / 2, x16, nx) || jz::overlaps(arg8, ny / 2, y16, ny)) return JZ_ERR_ALIAS;
-  const dim3 grid = pool_grid((int64_t)g.Q * g.C8, g.P, N);
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   const uint4* x = static_cast<const uint4*>(x16);
   uint4* y = static_cast<uint4*>(y16);
   uint2* arg = static_cast<uint2*>(arg8);
-  if (window == 3)
-    hipLaunchKernelGGL(maxpool_fwd_kernel<3>, grid, dim3(LY_THREADS), 0, st, x, y, arg, g);
-  else if (window == 2)
-    hipLaunchKernelGGL(maxpool_fwd_kernel<2>, grid, dim3(LY_THREADS), 0, st, x, y, arg, g);
-  else
-    hipLaunchKernelGGL(maxpool_fwd_kernel<0>, grid, dim3(LY_THREADS), 0, st, x, y, arg, g);
-  return jz::launch_status();
+  return pool_launch((int64_t)g.Q * g.C8, g.P, N, [&](auto shared, dim3 grid, const PoolWalk& w) {
+    constexpr bool SHORT = decltype(shared)::value;
+    auto* const kernel = window == 3 ? maxpool_fwd_kernel<3, SHORT> : window == 2 ? maxpool_fwd_kernel<2, SHORT> : maxpool_fwd_kernel<0, SHORT>;
+    hipLaunchKernelGGL(kernel, grid, dim3(LY_THREADS), 0, st, x, y, arg, g, w);
+  });
 }
 
 extern "C" int jz_maxpool_bwd(int N, int H, int W, int C, int window, int stride, int pad, const void* x16, const void* arg8,
@@ -554,11 +575,16 @@ extern "C" int jz_maxpool_bwd(int N, int H, int W, int C, int window, int stride
   uint4* dx = static_cast<uint4*>(dx16);
   if (arg8 && window == 3 && stride == 2) {  // the winners are known: x is not needed
     const int first = pad > 0 ? 0 : -1, rows = (H + pad - 2 - first * 2) / 2 + 1, cols = (W + pad - 2 - first * 2) / 2 + 1;
-    hipLaunchKernelGGL(maxpool_bwd_arg_3x3s2_kernel, pool_grid((int64_t)cols * g.C8, rows, N), dim3(LY_THREADS), 0, st, static_cast<const uint2*>(arg8), dy,
-                       dx, g, first, rows, cols);
-  } else if (arg8)
-    hipLaunchKernelGGL(maxpool_bwd_arg_kernel, pool_grid((int64_t)W * g.C8, H, N), dim3(LY_THREADS), 0, st, static_cast<const uint2*>(arg8), dy, dx, g);
-  else if (window == 3)
+    return pool_launch((int64_t)cols * g.C8, rows, N, [&](auto shared, dim3 cells, const PoolWalk& w) {
+      hipLaunchKernelGGL(maxpool_bwd_arg_3x3s2_kernel<decltype(shared)::value>, cells, dim3(LY_THREADS), 0, st, static_cast<const uint2*>(arg8), dy, dx, g,
+                         first, rows, w);
+    });
+  }
+  if (arg8)
+    return pool_launch((int64_t)W * g.C8, H, N, [&](auto shared, dim3 positions, const PoolWalk& w) {
+      hipLaunchKernelGGL(maxpool_bwd_arg_kernel<decltype(shared)::value>, positions, dim3(LY_THREADS), 0, st, static_cast<const uint2*>(arg8), dy, dx, g, w);
+    });
+  if (window == 3)
     hipLaunchKernelGGL(maxpool_bwd_kernel<3>, grid, dim3(LY_THREADS), 0, st, x, dy, dx, g);
   else if (window == 2)
     hipLaunchKernelGGL(maxpool_bwd_kernel<2>, grid, dim3(LY_THREADS), 0, st, x, dy, dx, g);
@@ -574,7 +600,7 @@ extern "C" int jz_avgpool_fwd(int N, int HW, int C, const void* x16, void* y16, 
   if (!jz::aligned16(x16) || !jz::aligned16(y16)) return JZ_ERR_ALIGN;
   if (jz::overlaps(x16, (size_t)N * HW * C * 2, y16, (size_t)N * C * 2)) return JZ_ERR_ALIAS;
   const int64_t blocks = ((int64_t)N * (C / 8) + AVG_THREADS - 1) / AVG_THREADS;
-  hipLaunchKernelGGL(avgpool_fwd_kernel, dim3((unsigned)(blocks < 65536 ? blocks : 65536)), dim3(AVG_THREADS), 0,
+  hipLaunchKernelGGL(HW < 16 ? avgpool_fwd_kernel<4> : avgpool_fwd_kernel<16>, dim3((unsigned)(blocks < 65536 ? blocks : 65536)), dim3(AVG_THREADS), 0,
                      static_cast<hipStream_t>(hip_stream), static_cast<const uint4*>(x16), static_cast<uint4*>(y16), N, HW, C / 8);
   return jz::launch_status();
 }

@@ -9,9 +9,10 @@ from paper_1807_11205_amd import inputs
 pytestmark = pytest.mark.gpu
 
 # N, H, W, C, window, stride, pad: 3 x 3 with stride 2 goes by cells of 2 x 2 positions, which start before the image without padding and
-# end behind it for either parity of the size; the last two: the general gather, and more images than a grid dimension takes
+# end behind it for either parity of the size; then the general gather, more images than a grid dimension takes, and rows that share a workgroup (of
+# 4, 49 and 128 threads, forward, the last of them not all there) or just do not (129)
 POOLS = [(2, 3, 3, 8, 3, 2, 0), (3, 7, 10, 8, 3, 2, 1), (2, 6, 5, 24, 3, 2, 2), (1, 1, 2, 8, 3, 2, 1), (2, 8, 9, 16, 3, 2, 0), (2, 9, 8, 16, 3, 1, 1),
-         (65537, 3, 3, 8, 3, 2, 1)]
+         (65537, 3, 3, 8, 3, 2, 1), (4097, 4, 8, 8, 2, 2, 0), (301, 7, 7, 56, 3, 1, 1), (3, 30, 32, 64, 3, 2, 1), (2, 9, 86, 24, 2, 2, 0)]
 
 
 @pytest.mark.parametrize("N,H,W,C,window,stride,pad", POOLS)
@@ -39,7 +40,27 @@ def test_pool_edges(N, H, W, C, window, stride, pad):
         assert np.all(np.abs(got - np.asarray(r16, np.float64).reshape(got.shape)) <= 2.0 ** -10 * np.abs(got) + 2.0 ** -24)
 
 
-@pytest.mark.parametrize("N,HW,C", [(1, 1, 8), (3, 15, 24), (2, 16, 520), (5, 17, 8), (2, 49, 2048)])
+@pytest.mark.skipif(torch.cuda.is_available() and torch.cuda.mem_get_info()[0] < 100 << 30, reason="needs 70 GB of device memory")
+def test_a_row_of_more_than_32_bits():
+    """2^20 + 1 positions of 4096 x 8 channels: more threads than a dimension of a grid counts."""
+    from paper_1807_11205_amd import api
+    W, C, stride = (1 << 20) + 1, 32768, 64
+    Q = (W - 1) // stride + 1
+    dy = torch.randn(Q * C // 64, device="cuda").half().repeat(64)
+    arg = torch.zeros(Q * C, dtype=torch.uint8, device="cuda")
+    dx = torch.empty(W * C, dtype=torch.float16, device="cuda")
+    for w in (0, 1, W - 2, W - 1):
+        dx[w * C:(w + 1) * C] = 7.0
+    api.jz_maxpool_bwd(1, 1, W, C, 1, stride, 0, None, dy, dx, arg)
+    torch.cuda.synchronize()
+    for w in (0, 1, W - 2, W - 1):
+        want = dy[w // stride * C:(w // stride + 1) * C] if w % stride == 0 else torch.zeros(C, dtype=torch.float16, device="cuda")
+        assert torch.equal(dx[w * C:(w + 1) * C], want), w
+    del dx, dy, arg
+    torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("N,HW,C", [(1, 1, 8), (2, 5, 16), (3, 15, 24), (2, 16, 520), (5, 17, 8), (2, 49, 2048)])
 def test_average_pool_edges(N, HW, C):
     from paper_1807_11205_amd import api
     rng = inputs.rng_for(78, N, HW, C)
