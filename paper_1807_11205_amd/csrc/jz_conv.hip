@@ -450,10 +450,13 @@ __global__ __launch_bounds__(256) void splitk_reduce_stats(const float* __restri
 // rows, so that their statistics need no other workgroup, and what it has summed is still in its registers when they are there.
 // MODE as above; out2 is y (MODE 0: [relu](a c + b [+ add])) or the gradient of the normalization's input.
 // What bounds it is a chain of latencies: the loads of the splits, two barriers' worth of sums, the coefficients.  5.1-5.7 us a launch where the
-// two it replaces took 3.1-3.6 and 3.7; ResNet-50's step at 8 images of 64 x 64 (35 of them) 1.383 -> 1.342 ms.  Up to 256 rows: with
-// 512 the few workgroups read too much each (8 of them 256 KB: the same step 1.371 ms).
+// two it replaces took 3.1-3.6 and 3.7; ResNet-50's step at 8 images of 64 x 64 (35 of them) 1.383 -> 1.342 ms.
 constexpr int RN_THREADS = 512, RN_COLS = 16, RN_LANES = RN_COLS / 4, RN_ROWS = RN_THREADS / RN_LANES, RN_PASSES = 2;
 constexpr int RN_MAX_ROWS = RN_ROWS * RN_PASSES;
+// A workgroup reads rows x splits x 64 bytes, and the two launches share that among more of them the more rows there are.  Microseconds gained over the two
+// (mean over 64 ... 1024 columns, both directions): 16 rows 2.0 (8 ... 116 splits); 64 rows, 8 ... 16 splits 1.3, 29 ... 47 1.5, 80 0.8, 96 -0.9; 98 rows, 8 1.0,
+// 12 ... 16 0.6, 58 -0.3; 128 rows, 6 ... 8 0.5, 12 ... 16 -0.2, 58 -2.3; 144 rows, 4 ... 6 0.9, 8 -0.4, 24 -2.6; 196 rows, 4 ... 6 0, 8 -1.4, 48 -8.2.
+bool reduce_normalizes(int rows, int splits) { return rows <= RN_MAX_ROWS && (long long)rows * rows * splits <= 150000; }
 struct NormArgs {
   const float* part;
   unsigned short* out;
@@ -1366,7 +1369,7 @@ int run(int op, const jz_conv_desc* d, const void* A, const void* B, void* D, vo
   else rc = launch_bwd_weight(pl, st);
   if (rc != JZ_OK) return rc;
   const int lg = reduce_lanes((long long)a.M * a.N, a.splits);
-  if (a.splits > 1 && stats && tail && a.M <= RN_MAX_ROWS) {
+  if (a.splits > 1 && stats && tail && reduce_normalizes(a.M, a.splits)) {
     NormArgs n{a.Dpart, a.D16, a.M, a.N, a.splits, 1 << lg, a.st_y, a.st_c, op == JZ_FWD ? static_cast<const unsigned short*>(tail->residual16) : a.st_add,
                a.st_mean, a.st_invstd, tail->gamma, tail->beta, tail->eps, tail->relu, 1.0 / (double)a.M,
                static_cast<unsigned short*>(op == JZ_FWD ? tail->y16 : tail->dx16), tail->save_mean, tail->save_invstd,
