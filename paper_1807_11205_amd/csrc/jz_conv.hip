@@ -456,7 +456,11 @@ constexpr int RN_MAX_ROWS = RN_ROWS * RN_PASSES;
 // A workgroup reads rows x splits x 64 bytes, and the two launches share that among more of them the more rows there are.  Microseconds gained over the two
 // (mean over 64 ... 1024 columns, both directions): 16 rows 2.0 (8 ... 116 splits); 64 rows, 8 ... 16 splits 1.3, 29 ... 47 1.5, 80 0.8, 96 -0.9; 98 rows, 8 1.0,
 // 12 ... 16 0.6, 58 -0.3; 128 rows, 6 ... 8 0.5, 12 ... 16 -0.2, 58 -2.3; 144 rows, 4 ... 6 0.9, 8 -0.4, 24 -2.6; 196 rows, 4 ... 6 0, 8 -1.4, 48 -8.2.
-bool reduce_normalizes(int rows, int splits) { return rows <= RN_MAX_ROWS && (long long)rows * rows * splits <= 150000; }
+// Those are captured calls.  Launched one by one a launch less is worth more: the step above, whose 3x3 layers at 128 rows have 12 and 15 splits, is 0.4 % faster
+// with them merged.
+bool reduce_normalizes(int rows, int splits) {
+  return rows <= RN_MAX_ROWS && (long long)rows * rows * splits <= (rows <= RN_ROWS ? 250000 : 150000);
+}
 struct NormArgs {
   const float* part;
   unsigned short* out;

@@ -1,5 +1,5 @@
-"""A split reduction that also normalizes (splitk_reduce_norm, up to 256 rows and rows x rows x splits up to 150000) at the edges of its passes,
-columns and split lanes; more takes the reduction and the normalization apart."""
+"""A split reduction that also normalizes (splitk_reduce_norm: up to 256 rows, and rows x rows x splits up to 250000, from 129 rows on 150000) at
+the edges of its passes, columns and split lanes; more takes the reduction and the normalization apart."""
 import pytest
 
 import test_gpu_conv_bn as fwd
@@ -12,6 +12,7 @@ pytestmark = pytest.mark.gpu
 EDGES = [
     (2, 2, 512, 16, 1, 0, 8),       # 8 rows, one workgroup
     (2, 8, 256, 40, 3, 1, 9),       # 128 rows: exactly one pass; 40 columns: half a workgroup's at the end
+    (2, 8, 256, 40, 3, 1, 16),      # apart: more splits
     (129, 1, 1024, 24, 1, 0, 8),    # one row in the second pass
     (1, 16, 128, 1032, 3, 1, 2),    # 256 rows: the most, ragged columns
     (129, 1, 1024, 24, 1, 0, 16),   # apart: more splits
