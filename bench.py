@@ -547,7 +547,7 @@ def bn_workload(args):
                      "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": gbps / HBM_PEAK_GBPS,
                      "traffic": None,
                      "traffic_note": "not measured in this run; profiles/bench_bn_resnet50_n64_kernel_stats.txt holds the HBM-counter "
-                                     "summary of this workload (12.9 bytes per element moved against 12 algorithmic when it was taken)",
+                                     "summary of this workload (13.0 bytes per element moved against 12 algorithmic when it was taken)",
                      "bytes_per_element": 12}}))
 
 

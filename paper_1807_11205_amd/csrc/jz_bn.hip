@@ -825,9 +825,10 @@ bool bw_all_units(hipStream_t st) {
 //   196 x 1024   6.5 /  7.4 /  7.8    5.4 /  6.5 /  7.1      3136 x 2048   13.6 / 22.7 / 28.5    10.8 / 22.4 / 29.5
 //   2048 x 128   6.4 /  7.6 /  7.8    6.9 /  7.7 /  8.6      12544 x 1024  17.2 / 39.2 / 46.8    14.3 / 38.5 / 48.5
 //   3136 x 256   9.3 / 11.2 / 11.3    7.7 /  9.5 / 10.1      50176 x 512   29.4 / 65.7 / 88.7    28.2 / 67.1 / 92.2
+//   3136 x 512  10.2 / 12.0 / 13.5    8.9 / 12.8 / 13.8      12544 x 256   11.0 / 15.5 / 18.4    10.6 / 14.2 / 16.9
 //   6272 x 64    7.4 /  9.0 /  9.0    7.6 /  9.3 / 10.1      200704 x 256  54.6 / 120 / 163      54.2 / 121 / 164
 //   25088 x 64  10.3 / 12.1 / 13.3   10.4 / 12.9 / 13.3      802816 x 64   54.1 / 120 / 162      53.5 / 118 / 165
-// A block end loses up to 5 % where its rows are read in 128-byte pieces (an XCD for each range of whole rows: worse, 69.6 us backward at 50176 x 512).
+// A block end loses up to 5 %, short ones a microsecond, where its rows are read in 128-byte pieces (an XCD for each range of whole rows: worse, 69.6 us backward at 50176 x 512).
 // A call whose workgroups have all rows of their channels has nothing to wait for and always may.
 bool bw_has_chip(const BnPlan& p, hipStream_t st) {
   if (p.slabs == 1) return true;
@@ -882,7 +883,7 @@ int launch_whole(const BnPlan& p, BnWholeArgs a, void* ws, hipStream_t st) {
     return jz::launch_status();
   };
   // the smallest kernel that keeps all passes, else the one that keeps the most: in registers as many as do not spill, then LDS (forward
-  // LDS did not pay: 44 + 14 passes 41.7 us at 200704 x 256, 46 alone 39.3)
+  // LDS did not pay: 14 passes in LDS behind a full set of registers took 41.7 us at 200704 x 256, the registers alone 39.3)
 #define JZ_BW(K, KL, MASKS) go(std::integral_constant<int, K>{}, std::integral_constant<int, KL>{}, std::integral_constant<int, MASKS>{})
   if (passes <= 4) return JZ_BW(4, 0, 0);
   if (passes <= 8) return JZ_BW(8, 0, 0);

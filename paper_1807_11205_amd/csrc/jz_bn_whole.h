@@ -2,14 +2,15 @@
 //
 // The passes apart are bound by memory: forward they move 6 bytes an element, backward 12 (with the mask as bits), and the launch
 // between them waits for the last workgroup and fills the chip anew.  Here one workgroup a compute unit keeps its rows in registers (FP16,
-// 128 KB forward ... 400 KB) and LDS while the workgroups that share its 64 channels exchange their sums, so that a tensor of up to 103 MB
-// forward and 51 MB backward is read once: 4 and 8 bytes an element.  Rows beyond that are read again, with the mask's bits out of LDS.
-// Measured, launches apart and this, microseconds forward / backward with ReLU (one launch after another, different buffers):
-//   3136 x 512     9.3 / 10.8    7.3 /  8.9        802816 x 64    53.0 / 118    44.0 / 90
-//   12544 x 256   11.1 / 15.5    8.4 / 10.7        50176 x 512    29.1 / 63.5   23.6 / 41.6
-//   12544 x 1024  17.1 / 38.3   13.6 / 23.2        200704 x 256   53.6 / 118    40.1 / 86.5
-// ResNet-50's 53 layers at batch 64, both directions: 3.03 -> 2.23 ms.  What bounds it now: memory (5.0 TB/s read and written at
-// 200704 x 256 forward, 4.8 backward with 52 % of the rows kept) and, for short tensors, the launch and 3 us for the exchange.
+// 8 KB a pass) and LDS while the workgroups that share its 64 channels exchange their sums, so that a tensor of up to 43 passes = 90 MB
+// forward, 25 = 52 MB backward with ReLU and 16 = 33 MB backward without or at a block's end is read once: 4 and 8 bytes an element.
+// Rows beyond that are read again, with the mask's bits out of LDS.
+// Measured, launches apart with their own plan (make_plan) and this, microseconds forward / backward with ReLU, in turn, different buffers:
+//   3136 x 512    10.0 / 11.8    7.2 /  8.4        802816 x 64    53.0 / 119    43.8 / 93
+//   12544 x 256   10.7 / 15.1    7.9 /  9.9        50176 x 512    29.0 / 65.0   23.8 / 44.0
+//   12544 x 1024  16.9 / 38.6   13.4 / 24.8        200704 x 256   52.9 / 119    40.0 / 87.3
+// ResNet-50's 53 layers at batch 64, both directions: 3.04 -> 2.22 ms.  What bounds it now: memory (5.1 TB/s read and written at
+// 200704 x 256 forward, 4.7 backward with half of the rows kept) and, for short tensors, the launch and 3 us for the exchange.
 // 64 channels are one 128-byte line of a row, the least that costs memory nothing; 512 threads are the fewest that can hold the register file.
 #pragma once
 

@@ -21,13 +21,15 @@
 // six products.  Measured, FP32 instructions and parts: 3x3, 512 channels, 28x28, N = 64 1650 -> 1137 us (144 -> 208 TFLOP/s);
 // 256 channels, 14x14 135 -> 96 us; 64 channels, 56x56 132 -> 94; 1x1 512 -> 128 on 28x28 68 -> 43; ResNet-50's operations at N = 64
 // 13.94 -> 11.45 ms.
-// What bounds it: issue slots, then power.  A 32x32x16 product holds the matrix pipe for 32 cycles, eight issue slots of its SIMD;
+// What bounds it: issue slots, then, in long reductions, power.  A 32x32x16 product holds the matrix pipe for 32 cycles, eight issue slots of its SIMD;
 // a loop of products with four vector instructions behind each runs at 95 % of the pipe, with four times as many behind every
 // fourth at 68 %.  Taking the parts apart is 6.5 vector instructions a value.  A wavefront that did that for its own 64 + 64
 // operand rows needed 7.3 of them per product (14x14 layer 129 us; v_dot2_f32_bf16 for the differences: 146).  So values are taken
 // apart once per workgroup, on their way through registers into LDS, two instructions at a time between the products, and the
-// operands are read from LDS as bfloat16: 4 to 5 instructions per product for 128x128 tiles.  The pipes are then busy for 81 % of the
-// compute units' busy cycles, without bank conflicts, at a clock that power holds at 1.4-1.5 GHz.
+// operands are read from LDS as bfloat16: 4 to 5 instructions per product for 128x128 tiles.  On the 512-channel layer the pipes
+// are then busy for 81 % of the compute units' busy cycles, without bank conflicts, at a clock that power holds at 1.4-1.5 GHz.  ResNet-50's
+// own layers are not at that bound: 45-54 % in the main variants, 46 % over the stack, at 2.0-2.4 GHz under the profiler (short reductions:
+// each workgroup's first tiles and its epilogue; the values of a 3x3 layer are taken apart once per tap).
 //
 // A tile's loads are requested two tiles ahead; the parts of tile i + 1 are made and written to the other of two stages between
 // the products of tile i; one barrier a tile, in the last of the six groups of products.  LDS layouts of a part ("KC", "MC" as in jz_f32_dma.h): KC rows of 16 bfloat16, 16-byte half c of row r at place

@@ -1,5 +1,5 @@
 // Implicit GEMM of a convolution whose output grid is its input grid (unit stride, odd filter, "same" padding), forward and
-// backward-data, with the input window of a tile kept in LDS.  Included by jz_conv_window.hip behind jz_igemm_kernels.h.
+// backward-data, with the input window of a tile kept in LDS.  Included by jz_conv_window_fwd.hip and jz_conv_window_bwd_data.hip behind jz_igemm_kernels.h.
 //
 // igemm_dma_kernel brings the gathered operand in once per filter tap: nine times for a 3x3 layer, and the path from L2 into LDS is what
 // bounds those layers.  Here the BM pixels of a tile, which are consecutive in memory, and the pixels that their taps reach (a run of
@@ -15,12 +15,12 @@
 // The reduction runs channel blocks outside, taps inside (the ring kernel: taps outside), in FP32 as there.
 //
 // Measured, ring kernel and this, microseconds forward / backward-data (different buffers in turn):
-//   64 -> 64, 3x3, 64 x 56 x 56    31 / 30     23 / 24.5      128 -> 128, 3x3, 64 x 28 x 28     20.1 / 21.3   18.8 / 20.2
-//   64 -> 64, 3x3, 32 x 56 x 56    19.5 / 18.2 13.3 / 13.8    384 -> 384, 3x3, 128 x 13 x 13    54 / 60       51 / 53
-//   96 -> 256, 5x5, 128 x 27 x 27, backward-data   178   163 (256 channels read: the ring kernel's 128x128 tiles are 3 rounds of workgroups)
-// What bounds it now.  256x128 tiles: power.  384 channels, 128 x 13 x 13: 60 % of the compute units' busy cycles are products, as many as in the
-// ring kernel, at a clock of 1.69 GHz instead of 1.55, since less moves.  256x64 tiles: two workgroups a compute unit, 3.06 rounds
-// of work in four, and each waits for its window before its first product.
+//   64 -> 64, 3x3, 64 x 56 x 56    31.4 / 31.0 23.3 / 25.1    128 -> 128, 3x3, 64 x 28 x 28     20.5 / 22.1   19.6 / 21.0
+//   64 -> 64, 3x3, 32 x 56 x 56    19.5 / 18.2 13.0 / 13.9    384 -> 384, 3x3, 128 x 13 x 13    59.3 / 65.2   55.9 / 58.9
+//   96 -> 256, 5x5, 128 x 27 x 27, backward-data   179 ... 184   167 ... 171 (256 channels read: the ring kernel's 128x128 tiles are 3 rounds)
+// What bounds it now.  256x128 tiles: waits inside the loop, not the matrix pipes: over the 3x3 layers of 256 and 384 channels at 13 x 13 products
+// are 57 % (forward) and 55 % (backward-data) of the compute units' busy cycles by counters, 54 % in the ring kernel.  256x64 tiles: two workgroups a
+// compute unit, 3.06 rounds of work in four, and each waits for its window before its first product.
 // Tried: wavefronts in two groups that share the reduction, with 128x64 of the tile each (a quarter fewer LDS reads, and one exchange of sums):
 // 384 channels 51 -> 54 us, 128 channels 18.8 -> 22.5; 128x128 tiles (256 channels, 64 x 14 x 14: 20.1 us on eight wavefronts, 21.4 on four, the ring
 // kernel 19.5); 64x128 and 128x64 tiles for small layers (9 ... 30 % slower than the ring kernel); blocks of 32 channels (0.93 ... 1.4).
