@@ -790,6 +790,15 @@ bool clear_of(const void* ws, size_t n, std::initializer_list<std::pair<const vo
   return true;
 }
 
+// Whether a result of the call lies where its parameters do, which the library accepts: in one launch the first workgroups write results while others have
+// yet to read parameters; apart, a launch of its own reads them before the results are written.
+bool over_parameters(std::initializer_list<std::pair<const void*, size_t>> results, std::initializer_list<const float*> parameters, size_t bytes) {
+  for (const auto& r : results)
+    for (const float* p : parameters)
+      if (jz::overlaps(r.first, r.second, p, bytes)) return true;
+  return false;
+}
+
 thread_local int t_bn_wait_us = 10;
 // A counter that starts where the clock stood, of 62 bits, mixed by steps that keep different numbers different (odd factors, shifted xors): no launch of
 // this process has had the result, and sums that an earlier call left in the workspace do not look like it.
@@ -1031,10 +1040,9 @@ extern "C" int jz_bn_relu_fwd(int64_t rows, int channels, const void* x16, const
       jz::overlaps(save_mean, nc, x16, nb) || jz::overlaps(save_invstd, nc, x16, nb) || jz::overlaps(save_mean, nc, save_invstd, nc) ||
       jz::overlaps(save_mean, nc, y16, nb) || jz::overlaps(save_invstd, nc, y16, nb))
     return JZ_ERR_ALIAS;
-  BnPlan wp;  // there the first workgroup of a range of channels writes the statistics while others still read gamma and beta
-  const bool apart_only = jz::overlaps(save_mean, nc, gamma, nc) || jz::overlaps(save_mean, nc, beta, nc) || jz::overlaps(save_invstd, nc, gamma, nc) ||
-                          jz::overlaps(save_invstd, nc, beta, nc);
-  const bool whole = !apart_only && make_whole_plan(rows, channels, true, &wp) && ws_bytes >= wp.total &&
+  BnPlan wp;
+  const bool whole = make_whole_plan(rows, channels, true, &wp) && ws_bytes >= wp.total &&
+                     !over_parameters({{y16, nb}, {save_mean, nc}, {save_invstd, nc}}, {gamma, beta}, nc) &&
                      clear_of(ws, wp.total, {{x16, nb}, {y16, nb}, {gamma, nc}, {beta, nc}, {save_mean, nc}, {save_invstd, nc}});
   if (whole) p = wp;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
@@ -1071,6 +1079,7 @@ extern "C" int jz_bn_relu_bwd(int64_t rows, int channels, const void* x16, const
     return JZ_ERR_ALIAS;
   BnPlan wp;
   const bool whole = make_whole_plan(rows, channels, false, &wp) && ws_bytes >= wp.total &&
+                     !over_parameters({{dx16, nb}, {dgamma16, nh}, {dbeta16, nh}}, {gamma, save_mean, save_invstd}, nf) &&
                      clear_of(ws, wp.total, {{x16, nb}, {relu ? y16 : nullptr, nb}, {dy16, nb}, {dx16, nb}, {gamma, nf}, {save_mean, nf}, {save_invstd, nf},
                                              {dgamma16, nh}, {dbeta16, nh}});
   if (whole) p = wp;
@@ -1127,6 +1136,7 @@ extern "C" int jz_bn_bwd_block_end(int64_t rows, int channels, const void* x16, 
   const size_t nf = (size_t)channels * 4;
   BnPlan wp;
   const bool whole = make_whole_plan(rows, channels, false, &wp) && ws_bytes >= wp.total &&
+                     !over_parameters({{g16, nb}, {dx16, nb}, {dgamma16, nh}, {dbeta16, nh}}, {gamma, save_mean, save_invstd}, nf) &&
                      clear_of(ws, wp.total, {{x16, nb}, {y_out16, nb}, {dya16, nb}, {dyb16, nb}, {g16, nb}, {dx16, nb}, {gamma, nf}, {save_mean, nf},
                                              {save_invstd, nf}, {dgamma16, nh}, {dbeta16, nh}});
   if (whole) p = wp;

@@ -72,4 +72,4 @@ def test_strided_pointwise(N, H, C, K):
             torch.cuda.synchronize()
             assert differ(want, o) == []
     finally:
-        jz.jz_bn_tune_wait(100)
+        jz.jz_bn_tune_wait(10)
