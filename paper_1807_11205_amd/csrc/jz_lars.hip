@@ -283,7 +283,8 @@ __device__ __forceinline__ void chunk_range(const ChunkRec& r, int* t_out, int64
   *end = r.start + r.count;
 }
 
-constexpr int LARS_IT = LARS_CH / (LARS_THREADS * 8);  // 8-element groups per thread and chunk
+constexpr int LARS_IT = LARS_CH / (LARS_THREADS * 8);     // 8-element groups per thread and chunk: gradients where nothing else is read
+constexpr int LARS_QUADS = LARS_CH / (LARS_THREADS * 4);  // 4-element groups: weights, momentum and what goes with them
 
 // 16-byte accesses of the update pass.  What it writes (w, v, the FP16 copy: 20 of 28 bytes an element) goes out with the
 // non-temporal hint, or dirty lines of it are still being written back while the next pass reads: ResNet-50 113 -> 109 us,
@@ -292,7 +293,7 @@ constexpr int LARS_IT = LARS_CH / (LARS_THREADS * 8);  // 8-element groups per t
 // loads.  So is a part of the state when it fits there (204 MB for ResNet-50: 93 us for updates in a row, 108 with the hint);
 // state that does not fit only displaces the gradient and is read with the hint (STREAM; AlexNet 261 -> 253 us).
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
-typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
+typedef unsigned u32x2_t __attribute__((ext_vector_type(2)));
 constexpr int64_t LARS_STREAM_ELEMENTS = (256ll << 20) / 8;  // 8 bytes of state an element against 256 MiB of last-level cache
 template <bool STREAM>
 __device__ __forceinline__ float4 load_state_f4(const float* p) {
@@ -304,9 +305,9 @@ __device__ __forceinline__ void store_stream_f4(float* p, float a, float b, floa
   f32x4_t t = {a, b, c, d};
   __builtin_nontemporal_store(t, reinterpret_cast<f32x4_t*>(p));
 }
-__device__ __forceinline__ void store_stream_u4(unsigned short* p, unsigned a, unsigned b, unsigned c, unsigned d) {
-  u32x4_t t = {a, b, c, d};
-  __builtin_nontemporal_store(t, reinterpret_cast<u32x4_t*>(p));
+__device__ __forceinline__ void store_stream_u2(unsigned short* p, unsigned a, unsigned b) {
+  u32x2_t t = {a, b};
+  __builtin_nontemporal_store(t, reinterpret_cast<u32x2_t*>(p));
 }
 
 // the 8-aligned body [b0,b1) of a chunk [s,e); the rest is at most 7 head and 7 tail elements
@@ -317,7 +318,7 @@ __device__ __forceinline__ void chunk_body(int64_t s, int64_t e, int64_t* b0, in
   *b1 = a + ((e - a) & ~int64_t(7));
 }
 
-// One thread's share (tid of LARS_THREADS) of a chunk's sum of w^2, in the order lars_update adds it (the 8-element groups
+// One thread's share (tid of LARS_THREADS) of a chunk's sum of w^2, in the order lars_update adds it (the 4-element groups
 // in turn, then at most one head / tail element).
 __device__ __forceinline__ double chunk_thread_sumsq_w(const ChunkRec& rec, const float* __restrict__ w, int tid) {
   int t;
@@ -326,13 +327,13 @@ __device__ __forceinline__ double chunk_thread_sumsq_w(const ChunkRec& rec, cons
   chunk_body(s, e, &b0, &b1);
   double sw = 0.0;
 #pragma unroll
-  for (int k = 0; k < LARS_IT; ++k) {
-    int64_t i = b0 + (int64_t)(k * LARS_THREADS + tid) * 8;
+  for (int k = 0; k < LARS_QUADS; ++k) {
+    int64_t i = b0 + (int64_t)(k * LARS_THREADS + tid) * 4;
     if (i < b1) {
-      const float4 a = *reinterpret_cast<const float4*>(w + i), b = *reinterpret_cast<const float4*>(w + i + 4);
-      const float wv[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+      const float4 a = *reinterpret_cast<const float4*>(w + i);
+      const float wv[4] = {a.x, a.y, a.z, a.w};
 #pragma unroll
-      for (int j = 0; j < 8; ++j) sw = fma((double)wv[j], (double)wv[j], sw);
+      for (int j = 0; j < 4; ++j) sw = fma((double)wv[j], (double)wv[j], sw);
     }
   }
   int64_t nh = b0 - s, nt = e - b1;
@@ -648,9 +649,12 @@ __device__ __forceinline__ void lars_step(float& w, float& v, unsigned short gbi
 }
 
 // One thread's share (tid of LARS_THREADS) of a chunk's state and gradients: every load is in flight before the first use.
+// A lane takes four elements at a time, so that every access of a wavefront to weights or momentum is 1 KB without gaps.  With eight
+// (two 16-byte accesses 32 bytes apart, each of which touches every line of 2 KB) the same stream, 20 bytes an element, ran at 5.35
+// instead of 5.92 TB/s over 62 M elements.
 struct ChunkState {
-  float4 w0[LARS_IT], w1[LARS_IT], v0[LARS_IT], v1[LARS_IT];
-  uint4 gq[LARS_IT];
+  float4 w[LARS_QUADS], v[LARS_QUADS];
+  u32x2_t g[LARS_QUADS];
 };
 template <bool STREAM>
 __device__ __forceinline__ ChunkState load_chunk_state(const ChunkRec& rec, int tid, const float* __restrict__ w, const float* __restrict__ v,
@@ -661,14 +665,12 @@ __device__ __forceinline__ ChunkState load_chunk_state(const ChunkRec& rec, int 
   chunk_range(rec, &t, &s, &e);
   chunk_body(s, e, &b0, &b1);
 #pragma unroll
-  for (int k = 0; k < LARS_IT; ++k) {
-    int64_t i = b0 + (int64_t)(k * LARS_THREADS + tid) * 8;
+  for (int k = 0; k < LARS_QUADS; ++k) {
+    int64_t i = b0 + (int64_t)(k * LARS_THREADS + tid) * 4;
     if (i < b1) {
-      r.gq[k] = *reinterpret_cast<const uint4*>(g16 + i);
-      r.w0[k] = load_state_f4<STREAM>(w + i);
-      r.w1[k] = load_state_f4<STREAM>(w + i + 4);
-      r.v0[k] = load_state_f4<STREAM>(v + i);
-      r.v1[k] = load_state_f4<STREAM>(v + i + 4);
+      r.w[k] = load_state_f4<STREAM>(w + i);
+      r.v[k] = load_state_f4<STREAM>(v + i);
+      r.g[k] = *reinterpret_cast<const u32x2_t*>(g16 + i);
     }
   }
   return r;
@@ -684,27 +686,25 @@ __device__ __forceinline__ double update_chunk(const ChunkState& q, const ChunkR
   chunk_body(s, e, &b0, &b1);
   double sw = 0.0;  // sum of squares of the new weights, in the order lars_reduce would add them
 #pragma unroll
-  for (int k = 0; k < LARS_IT; ++k) {
-    int64_t i = b0 + (int64_t)(k * LARS_THREADS + tid) * 8;
+  for (int k = 0; k < LARS_QUADS; ++k) {
+    int64_t i = b0 + (int64_t)(k * LARS_THREADS + tid) * 4;
     if (i < b1) {
-      float wv[8] = {q.w0[k].x, q.w0[k].y, q.w0[k].z, q.w0[k].w, q.w1[k].x, q.w1[k].y, q.w1[k].z, q.w1[k].w};
-      float vv[8] = {q.v0[k].x, q.v0[k].y, q.v0[k].z, q.v0[k].w, q.v1[k].x, q.v1[k].y, q.v1[k].z, q.v1[k].w};
-      unsigned gw[4] = {q.gq[k].x, q.gq[k].y, q.gq[k].z, q.gq[k].w};
-      unsigned ow[4];
+      float wv[4] = {q.w[k].x, q.w[k].y, q.w[k].z, q.w[k].w};
+      float vv[4] = {q.v[k].x, q.v[k].y, q.v[k].z, q.v[k].w};
+      unsigned ow[2];
 #pragma unroll
-      for (int j = 0; j < 8; j += 2) {
+      for (int j = 0; j < 4; j += 2) {
+        const unsigned gw = q.g[k][j >> 1];
         unsigned short h0, h1;
-        lars_step(wv[j], vv[j], (unsigned short)(gw[j >> 1] & 0xffffu), coef, lam, m, inv_s, h0);
-        lars_step(wv[j + 1], vv[j + 1], (unsigned short)(gw[j >> 1] >> 16), coef, lam, m, inv_s, h1);
+        lars_step(wv[j], vv[j], (unsigned short)(gw & 0xffffu), coef, lam, m, inv_s, h0);
+        lars_step(wv[j + 1], vv[j + 1], (unsigned short)(gw >> 16), coef, lam, m, inv_s, h1);
         ow[j >> 1] = (unsigned)h0 | ((unsigned)h1 << 16);
       }
 #pragma unroll
-      for (int j = 0; j < 8; ++j) sw = fma((double)wv[j], (double)wv[j], sw);
+      for (int j = 0; j < 4; ++j) sw = fma((double)wv[j], (double)wv[j], sw);
       store_stream_f4(w + i, wv[0], wv[1], wv[2], wv[3]);
-      store_stream_f4(w + i + 4, wv[4], wv[5], wv[6], wv[7]);
       store_stream_f4(v + i, vv[0], vv[1], vv[2], vv[3]);
-      store_stream_f4(v + i + 4, vv[4], vv[5], vv[6], vv[7]);
-      store_stream_u4(w16 + i, ow[0], ow[1], ow[2], ow[3]);
+      store_stream_u2(w16 + i, ow[0], ow[1]);
     }
   }
   {
