@@ -344,17 +344,24 @@ bool needs_gen_f32(const PlanF32& pl) {
 // to 128, random layers.  On a quarter of them left out of the fit the choices were 0.8-1.2 % slower than the best.  parts_ahead:
 // by how much the first form has to be faster to be taken, about what the model is wrong by on launches of 6-8 us, where it gains
 // nothing and its choices were up to 0.6 us slower without.  limit: bytes of partial sums.
+// 3x3 layers on their own grid have a third form, the pixels of a tile taken apart once for all taps (jz_f32_window.h); its constants
+// are fits to ten layers in up to eleven splits each.  Over 40 random layers, both directions, its choices take 0.93 of the time of the
+// other forms' in the geometric mean, 0.77 ... 0.92 where the chip is full, and what they lose is within what two timings differ by.
+// 3x3, 64 images, forward / backward-data, without and with: 56x56x64 104 / 105 and 99 / 97 us, 28x28x128 101 / 102 and 86 / 84,
+// 14x14x256 105 / 106 and 89 / 89; 7x7x512 93 / 94 either way (100 tiles, and splits only in steps of 18 k tiles).
 void choose_tiling_f32(PlanF32* pl, bool may_split, bool fixed_tile = false, size_t limit = 0, bool may_parts = true) {
-  struct Tile { bool parts; int bm, bn, resident; double lat[4], thr[4], prologue[4], own[4]; };
+  struct Tile { bool parts, window; int bm, bn, resident; double lat[4], thr[4], prologue[4], own[4]; };
   static const Tile tiles[] = {
-      {true, 128, 128, 2, {0.427, 0.537, 0.629, 0.756}, {0.572, 0.567, 0.533, 0.612}, {3.458, 2.504, 3.066, 2.014}, {0.883, 0.888, 2.248, 0.346}},
-      {true, 128, 64, 3, {0.324, 0.382, 0.463, 0.489}, {0.323, 0.327, 0.340, 0.359}, {1.365, 1.111, 1.112, 0.101}, {0.622, 0.637, 0.989, 0.079}},
-      {true, 64, 128, 3, {0.329, 0.395, 0.476, 0.560}, {0.328, 0.332, 0.349, 0.381}, {1.581, 1.099, 1.412, 1.033}, {0.456, 0.442, 1.133, 0.316}},
-      {true, 64, 64, 5, {0.254, 0.303, 0.309, 0.333}, {0.188, 0.191, 0.206, 0.215}, {0.000, 0.000, 0.000, 0.000}, {0.303, 0.312, 0.439, 0.000}},
-      {false, 128, 128, 2, {0.935, 1.023, 1.020, 1.181}, {0.889, 0.919, 0.907, 1.065}, {1.798, 1.665, 2.516, 2.486}, {2.607, 2.429, 2.484, 0.813}},
-      {false, 128, 64, 3, {0.513, 0.615, 0.604, 0.685}, {0.461, 0.464, 0.488, 0.532}, {0.137, 0.147, 0.335, 0.128}, {1.206, 1.280, 0.974, 0.474}},
-      {false, 64, 128, 3, {0.489, 0.579, 0.630, 0.800}, {0.456, 0.476, 0.494, 0.565}, {0.159, 0.239, 0.687, 0.228}, {1.199, 1.092, 0.988, 0.657}},
-      {false, 64, 64, 5, {0.283, 0.342, 0.352, 0.421}, {0.235, 0.246, 0.255, 0.288}, {0.037, 0.039, 0.043, 0.030}, {0.512, 0.548, 0.429, 0.187}}};
+      {true, false, 128, 128, 2, {0.427, 0.537, 0.629, 0.756}, {0.572, 0.567, 0.533, 0.612}, {3.458, 2.504, 3.066, 2.014}, {0.883, 0.888, 2.248, 0.346}},
+      {true, false, 128, 64, 3, {0.324, 0.382, 0.463, 0.489}, {0.323, 0.327, 0.340, 0.359}, {1.365, 1.111, 1.112, 0.101}, {0.622, 0.637, 0.989, 0.079}},
+      {true, false, 64, 128, 3, {0.329, 0.395, 0.476, 0.560}, {0.328, 0.332, 0.349, 0.381}, {1.581, 1.099, 1.412, 1.033}, {0.456, 0.442, 1.133, 0.316}},
+      {true, false, 64, 64, 5, {0.254, 0.303, 0.309, 0.333}, {0.188, 0.191, 0.206, 0.215}, {0.000, 0.000, 0.000, 0.000}, {0.303, 0.312, 0.439, 0.000}},
+      {false, false, 128, 128, 2, {0.935, 1.023, 1.020, 1.181}, {0.889, 0.919, 0.907, 1.065}, {1.798, 1.665, 2.516, 2.486}, {2.607, 2.429, 2.484, 0.813}},
+      {false, false, 128, 64, 3, {0.513, 0.615, 0.604, 0.685}, {0.461, 0.464, 0.488, 0.532}, {0.137, 0.147, 0.335, 0.128}, {1.206, 1.280, 0.974, 0.474}},
+      {false, false, 64, 128, 3, {0.489, 0.579, 0.630, 0.800}, {0.456, 0.476, 0.494, 0.565}, {0.159, 0.239, 0.687, 0.228}, {1.199, 1.092, 0.988, 0.657}},
+      {false, false, 64, 64, 5, {0.283, 0.342, 0.352, 0.421}, {0.235, 0.246, 0.255, 0.288}, {0.037, 0.039, 0.043, 0.030}, {0.512, 0.548, 0.429, 0.187}},
+      {true, true, 128, 128, 2, {0.46, 0.48}, {0.50, 0.51}, {3.5, 3.5}, {1.5, 1.5}},
+      {true, true, 128, 64, 2, {0.31, 0.32}, {0.265, 0.267}, {1.4, 1.4}, {2.0, 2.0}}};
   const double parts_ahead = 0.3;
   // FP32 instructions, parts; the last two per megabyte (2.3: anything from 2 to 3.1 fits as well)
   static const double fixed[2][4] = {{4.76, 4.82, 5.10, 5.64}, {4.347, 5.147, 4.159, 5.374}},
@@ -364,40 +371,49 @@ void choose_tiling_f32(PlanF32* pl, bool may_split, bool fixed_tile = false, siz
   F32Args& a = pl->args;
   a.nkt = (a.Kred + FD_BK - 1) / FD_BK;
   const int c = pl->op == JZ_FWD ? 0 : pl->op == JZ_BWD_DATA ? 1 : a.bw_linear ? 2 : 3;
+  const ConvGeom& g = a.g;
+  const bool may_window = pl->op != JZ_BWD_WEIGHT && !pl->gen && !a.sc_on && g.R == 3 && g.S == 3 && g.ph == 1 && g.pw == 1 && g.sh == 1 && g.sw == 1 &&
+                          g.IH == g.OH && g.IW == g.OW && g.IW <= 63 && g.IC % (2 * FD_BK) == 0;
   const double in = 1e-6 * ((double)std::min<long long>(pl->bytesA, 4ll * a.M * a.Kred) + (double)std::min<long long>(pl->bytesB, 4ll * a.N * a.Kred));
-  auto even = [](bool parts, int k) { return parts ? k + (k & 1) : k; };  // operands in parts: two k tiles at a time
+  // k tiles that a workgroup takes: two at a time in parts, nine taps of twice 16 channels out of a window
+  auto even = [](const Tile& t, int k) { return t.window ? (k + 17) / 18 * 18 : t.parts ? k + (k & 1) : k; };
   auto p4 = [](double x) { return (x * x) * (x * x); };
   auto rounds = [](double w) { return w <= 4.0 ? ceil(w) : w + 0.5; };  // many small rounds even out
   double best = 1e30;
-  int bsp = 1, bfull = 0;
+  double most_part = 0.0;  // bytes of partial sums of the plan without a window: the workspace that a layer asks for does not grow with one,
+  int most_chain = 0;      // and no sum is rounded more often (64-wide tiles of the window kernel start a new one every 18 k tiles)
+  int bsp = 1, bfull = 0, kt_step = 1;
   for (const Tile& t : tiles) {
     if (fixed_tile && (t.parts != pl->parts || t.bm != pl->BM || t.bn != pl->BN)) continue;
+    if (t.window && !(may_window && may_split)) continue;
     if (t.parts && (!may_parts || a.nkt == 1)) continue;  // half of its work would be done on zeros
     const long long tm = (a.M + t.bm - 1) / t.bm, tn = (a.N + t.bn - 1) / t.bn, slots = 256 * t.resident;
     for (int sp = 1; sp <= 512; sp = sp < 8 ? sp + 1 : sp + sp / 4) {
       if (sp > 1 && (!may_split || a.nkt / sp < 8)) break;
-      const int kps = even(t.parts, (a.nkt + sp - 1) / sp), real = (a.nkt + kps - 1) / kps;
+      const int kps = even(t, (a.nkt + sp - 1) / sp), real = (a.nkt + kps - 1) / kps;
       // full rows of tiles: none (all of them without a split), or as many as fill whole rounds
       const long long round_rows = tm * tn / 256 * 256 / tn;
       for (int tail = 0; tail < 2; ++tail) {
         if (tail && (sp == 1 || round_rows == 0 || round_rows >= tm)) break;
         const long long full = sp == 1 ? tm : tail ? round_rows : 0, wf = full * tn, ws = (tm - full) * tn * real;
         const double n1 = tail ? ceil(wf / 256.0) : rounds(wf / 256.0), n2 = tail ? ceil(ws / 256.0) : rounds(ws / 256.0);
-        const double t_thr = n1 * (t.own[c] + t.thr[c] * even(t.parts, a.nkt)) + n2 * (t.own[c] + t.thr[c] * kps);
+        const double t_thr = n1 * (t.own[c] + t.thr[c] * even(t, a.nkt)) + n2 * (t.own[c] + t.thr[c] * kps);
         const long long l1 = (wf + slots - 1) / slots, l2 = wf > 0 ? (wf + ws + slots - 1) / slots - l1 : (ws + slots - 1) / slots;
-        const double t_lat = l1 * (t.prologue[c] + t.lat[c] * even(t.parts, a.nkt)) + l2 * (t.prologue[c] + t.lat[c] * kps);
+        const double t_lat = l1 * (t.prologue[c] + t.lat[c] * even(t, a.nkt)) + l2 * (t.prologue[c] + t.lat[c] * kps);
         const double out = 4e-6 * a.M * a.N, part = sp > 1 ? 4e-6 * real * (double)(a.M - full * t.bm) * a.N : 0.0;
-        if (1e6 * part > (double)limit) continue;
+        if (1e6 * part > (t.window ? most_part : (double)limit)) continue;
+        const int chain = full > 0 ? a.nkt : kps;  // k tiles that are added up one after the other
+        if (t.window && t.bn == 128 && chain > most_chain) continue;
         const double t_mem = byte[t.parts][c] * (in + part + (full > 0 ? out : 0.0));
         double time = fixed[t.parts][c] + (t.parts ? parts_ahead : 0.0) + sqrt(sqrt(p4(t_thr) + p4(t_lat) + p4(t_mem)));
         if (sp > 1) time += reduce_launch[t.parts][c] + reduce_byte[t.parts][c] * part;
-        if (time < best) { best = time; pl->parts = t.parts; pl->BM = t.bm; pl->BN = t.bn; bsp = sp; bfull = (int)full; }
+        if (time < best) { best = time; if (!t.window) { most_part = 1e6 * part; most_chain = chain; } pl->parts = t.parts; pl->window = t.window; kt_step = t.window ? 18 : t.parts ? 2 : 1; pl->BM = t.bm; pl->BN = t.bn; bsp = sp; bfull = (int)full; }
       }
     }
   }
   a.tiles_m = (a.M + pl->BM - 1) / pl->BM;
   a.tiles_n = (a.N + pl->BN - 1) / pl->BN;
-  a.kt_per_split = even(pl->parts, (a.nkt + bsp - 1) / bsp);
+  a.kt_per_split = ((a.nkt + bsp - 1) / bsp + kt_step - 1) / kt_step * kt_step;
   a.splits = (a.nkt + a.kt_per_split - 1) / a.kt_per_split;
   a.full_rows = a.splits > 1 ? bfull : a.tiles_m;
   const int tail_tiles = (a.tiles_m - a.full_rows) * a.tiles_n;

@@ -53,7 +53,8 @@ __device__ __forceinline__ int clamp_taps(int x, int hi) { return x < 0 ? 0 : (x
 
 // What the workgroup with number `block` of the `blocks` that the launch `a` consists of loads, and where its results go.
 // SWZ: the places of the 16-byte chunks in LDS follow from the load (LDS-direct), so the lanes fetch them in swizzled order.
-template <int OP, int BM, int BN, int FORM, bool SWZ>
+// TAPS_INSIDE: the k tiles go through the taps of 16 channels, then to the next channels (jz_f32_window.h: nine taps).
+template <int OP, int BM, int BN, int FORM, bool SWZ, bool TAPS_INSIDE = false>
 struct F32Tile {
   static constexpr bool GEN = OP != OP_BWD_WEIGHT && FORM == F32_TAPS;
   static constexpr bool MATRIX = OP == OP_BWD_WEIGHT && FORM == F32_MATRIX, SAME = OP == OP_BWD_WEIGHT && FORM == F32_SAME;
@@ -121,7 +122,6 @@ struct F32Tile {
     kc_row = wave * 16 + lane / 4;
     kc_chunk = SWZ ? (lane & 3) ^ ((kc_row >> 2) & 3) : lane & 3;
     if constexpr (A_KC) {
-      const unsigned row_taps = low_taps(g.S);
 #pragma unroll
       for (int ii = 0; ii < LA; ++ii) {
         const int m = m0 + 64 * ii + kc_row;
@@ -135,13 +135,7 @@ struct F32Tile {
           vA[ii] = (unsigned)(((int)n * g.IH + h0) * g.IW + w0) * (unsigned)g.IC;
           if constexpr (!GEN) {
             vA[ii] = (vA[ii] + (unsigned)kc_chunk * 4u) * 4u + (OP == OP_FWD ? biasA : 0u);
-            // along one axis the taps outside are a run at the start and a run at the end of the filter (backward-data: the
-            // other way round); the column mask is copied into every filter row's slot by one multiplication
-            const int lo_w = OP == OP_FWD ? -w0 : w0 - g.IW + 1, hi_w = OP == OP_FWD ? g.IW - w0 : w0 + 1;
-            const int lo_h = OP == OP_FWD ? -h0 : h0 - g.IH + 1, hi_h = OP == OP_FWD ? g.IH - h0 : h0 + 1;
-            const unsigned cm = low_taps(clamp_taps(lo_w, g.S)) | (row_taps & ~low_taps(clamp_taps(hi_w, g.S)));
-            invA[ii] = cm * g.tap_rep | low_taps(clamp_taps(lo_h, g.R) * g.S) |
-                       (low_taps(g.R * g.S) & ~low_taps(clamp_taps(hi_h, g.R) * g.S));
+            invA[ii] = taps_outside(h0, w0);
           }
         }
       }
@@ -202,6 +196,22 @@ struct F32Tile {
     }
   }
 
+  // The taps that read outside the image, for a row whose tap (0, 0) is at (h0, w0).  Along one axis they are a run at the start and a
+  // run at the end of the filter (backward-data: the other way round); the column mask is copied into every filter row's slot by one
+  // multiplication.
+  __device__ __forceinline__ unsigned taps_outside(int h0, int w0) const {
+    const int lo_w = OP == OP_FWD ? -w0 : w0 - g.IW + 1, hi_w = OP == OP_FWD ? g.IW - w0 : w0 + 1;
+    const int lo_h = OP == OP_FWD ? -h0 : h0 - g.IH + 1, hi_h = OP == OP_FWD ? g.IH - h0 : h0 + 1;
+    const unsigned cm = low_taps(clamp_taps(lo_w, g.S)) | (low_taps(g.S) & ~low_taps(clamp_taps(hi_w, g.S)));
+    return cm * g.tap_rep | low_taps(clamp_taps(lo_h, g.R) * g.S) | (low_taps(g.R * g.S) & ~low_taps(clamp_taps(hi_h, g.R) * g.S));
+  }
+  __device__ __forceinline__ unsigned taps_outside(int m) const {
+    if (m >= a.M) return OOB;
+    const unsigned n = fd_div((unsigned)m, g.d_ohow), rem = (unsigned)m - n * (unsigned)(g.OH * g.OW);
+    const int oh = (int)fd_div(rem, g.d_ow), ow = (int)rem - oh * g.OW;
+    return OP == OP_FWD ? taps_outside(oh * g.sh - g.ph, ow * g.sw - g.pw) : taps_outside(oh + g.ph, ow + g.pw);
+  }
+
   struct TileCtx {
     unsigned k0;
     unsigned tap, soffA, soffB;  // the same for the whole wavefront (the tile lies inside one tap)
@@ -213,6 +223,7 @@ struct F32Tile {
   __device__ __forceinline__ TileCtx tile_ctx(int kt) const {
     TileCtx c{};
     c.k0 = (unsigned)(kt * FD_BK);
+    if constexpr (TAPS_INSIDE) c.k0 = (unsigned)(kt % 9 * g.IC + kt / 9 * FD_BK);
     if constexpr (OP == OP_BWD_WEIGHT) {
       c.soffA = c.k0 * (unsigned)a.M * 4u;
       c.soffB = c.k0 * (unsigned)g.IC * 4u;
@@ -238,6 +249,12 @@ struct F32Tile {
       c.in = kq < (unsigned)a.Kred;
       c.soffB = c.k0 * 4u;
     }
+    return c;
+  }
+  // the filter's part of it for 16 channels of one of nine taps (jz_f32_window.h)
+  __device__ __forceinline__ TileCtx tile_at(int tap, int channel) const {
+    TileCtx c{};
+    c.soffB = OP == OP_FWD ? (unsigned)(tap * g.IC + channel) * 4u : (unsigned)(channel * 9 + tap) * (unsigned)a.N * 4u;
     return c;
   }
   // load Lx (A's, then B's) of the tile: f(descriptor, per-lane byte offset, scalar byte offset)
@@ -338,9 +355,9 @@ struct F32Tile {
 };
 
 // the tile on the FP32 matrix instructions
-template <int OP, int BM, int BN, int FORM>
+template <int OP, int BM, int BN, int FORM, bool TAPS_INSIDE = false>
 __device__ __forceinline__ void f32_dma_body(const F32Args& a, unsigned block, unsigned blocks) {
-  using Tile = F32Tile<OP, BM, BN, FORM, true>;
+  using Tile = F32Tile<OP, BM, BN, FORM, true, TAPS_INSIDE>;
   constexpr bool A_KC = Tile::A_KC, B_KC = Tile::B_KC;
   constexpr int TM = BM / 32, TN = BN / 32;   // 16x16 MFMA tiles per wavefront
   constexpr int RB = FD_BK * 4;               // bytes per row of a KC tile

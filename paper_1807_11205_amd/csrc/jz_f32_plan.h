@@ -40,6 +40,7 @@ struct PlanF32 {
   bool dma = false;      // a kernel of jz_f32_split.h or jz_f32_dma.h
   bool gen = false;      // ... with per-lane tap arithmetic
   bool parts = false;    // ... its operands taken apart for the bfloat16 matrix instructions (jz_f32_split.h)
+  bool window = false;   // ... and the pixels under a tile once for all taps (jz_f32_window.h)
   bool classes = false;  // strided multi-tap backward-data: one launch per residue of the stride (class_args_f32)
   bool widen = false;    // channels rounded up to 4 on copies: `wide` is the layer that runs
   int BM = 128, BN = 128;

@@ -51,6 +51,101 @@ struct F32Split {
   static constexpr int LDS_BYTES = 2 * STAGE > RING ? 2 * STAGE : RING;
 };
 
+// Taking four values apart, in kSplitSteps steps of two vector instructions (the products hide four behind each of them): they are
+// scaled, then the next eight bits of them go to LDS as part k at dst + k * part_bytes and, where another part follows, are taken
+// off value by value (exact).
+constexpr int kScaleSteps = 2, kSplitSteps = kScaleSteps + 11;
+template <int STEP0>
+__device__ __forceinline__ void f32_split_step(f32x4& v, u32x2& part, lds_byte* dst, int part_bytes) {
+  constexpr int STEP = STEP0 - kScaleSteps, K = STEP / 5, E = STEP % 5 - 1;
+  if constexpr (STEP < 0) {
+    v[2 * STEP0] *= 0x1p24f;
+    v[2 * STEP0 + 1] *= 0x1p24f;
+  } else if constexpr (E < 0) {
+    part = u32x2{__builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{v[0], v[1]}, bf16x2)),
+                 __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{v[2], v[3]}, bf16x2))};
+    *(__attribute__((address_space(3))) u32x2*)(dst + K * part_bytes) = part;
+  } else {
+    v[E] -= __builtin_bit_cast(float, E % 2 == 0 ? part[E / 2] << 16 : part[E / 2] & 0xffff0000u);
+  }
+}
+
+// LDS offset of value (row, k 4 q .. 4 q + 3) of a KC part, and of (k, rows 4 q .. 4 q + 3) of an MC part of `rows` rows
+__device__ __forceinline__ unsigned f32_kc_at(int row, int q) { return (unsigned)(row * 32 + (((q >> 1) ^ ((row >> 3) & 1)) * 16) + (q & 1) * 8); }
+__device__ __forceinline__ unsigned f32_mc_at(int rows, int k, int q) {
+  return (unsigned)(k * rows * 2 + (((q >> 1) ^ ((rows >= 128 ? 4 : 2) * (k & 3))) * 16) + (q & 1) * 8);
+}
+// Where a lane reads the operands of rows row0 .. of a part.  KC (one address): row r31, k 8 h .. 8 h + 7.  MC (two for each of the
+// 32-row tiles): 16-lane group gi = lane / 16 reads half gi % 2 of the 32 rows and k block gi / 2; lane 4 j + c4 of the group addresses
+// k-row j, the 8-byte piece c4 of those 16 rows.
+template <bool KC, int TILES>
+__device__ __forceinline__ void f32_read_addr(unsigned* rd, int lane, int row0, int rows, int base) {
+  if constexpr (KC) {
+    const int r31 = lane & 31, h = lane >> 5;
+    rd[0] = (unsigned)(base + (row0 + r31) * 32 + ((h ^ ((r31 >> 3) & 1)) * 16));
+  } else {
+    const int gi = lane >> 4, j = (lane >> 2) & 3, c4 = lane & 3;
+#pragma unroll
+    for (int x = 0; x < TILES; ++x)
+#pragma unroll
+      for (int hf = 0; hf < 2; ++hf) {
+        const int k = 8 * (gi >> 1) + 4 * hf + j, c = (row0 + 32 * x + 16 * (gi & 1) + 4 * c4) / 8;
+        rd[2 * x + hf] = (unsigned)(base + k * rows * 2 + ((c ^ ((rows >= 128 ? 4 : 2) * (k & 3))) * 16) + (c4 & 1) * 8);
+      }
+  }
+}
+template <bool KC>
+__device__ __forceinline__ bf16x8 f32_read_operand(lds_byte* ldsb, const unsigned* rd, int x, int off) {
+  if constexpr (KC) return *(const __attribute__((address_space(3))) bf16x8*)(ldsb + rd[0] + (off + x * 1024));
+  typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+  struct { s16x4 lo, hi; } v;
+  v.lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(ldsb + rd[KC ? 0 : 2 * x] + off));
+  v.hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(ldsb + rd[KC ? 0 : 2 * x + 1] + off));
+  return __builtin_bit_cast(bf16x8, v);
+}
+
+// This wavefront's LDS writes have landed, and everyone else's; loads stay in flight.  Both sides of it are ordinary accesses,
+// which the compiler may move across the barrier itself: the fences, of LDS alone, are what keeps them in place.
+__device__ __forceinline__ void f32_lds_meet() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// The two sums of every result added up and scaled back.  Whether all of the workgroup's are finite; every wavefront is past its
+// last operand read then.
+template <int TM, int TN>
+__device__ __forceinline__ bool f32_join_sums(f32x16 (&acc)[TM][TN], f32x16 (&low)[TM][TN], int lane, int wave) {
+  float odd = 0.f;  // 0 or, from a result that is not finite, NaN
+#pragma unroll
+  for (int x = 0; x < TM; ++x)
+#pragma unroll
+    for (int y = 0; y < TN; ++y)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        acc[x][y][r] = (acc[x][y][r] + low[x][y][r]) * 0x1p-48f;
+        odd = fmaf(acc[x][y][r], 0.f, odd);
+      }
+  __shared__ int not_finite[4];
+  const bool any = __ballot(odd != 0.f) != 0;
+  if (lane == 0) not_finite[wave] = any;
+  __syncthreads();  // and the tile is staged where the operands were
+  return __builtin_amdgcn_readfirstlane(not_finite[0] | not_finite[1] | not_finite[2] | not_finite[3]) == 0;
+}
+// accumulator register r of tile (x,y): m = wrow + 32 x + lane % 32, n = wcol + 32 y + 8 (r / 4) + 4 (lane / 32) + r % 4
+template <int LDF, int TM, int TN>
+__device__ __forceinline__ void f32_put_rows(float* rows, const f32x16 (&acc)[TM][TN], int lane) {
+  const int r31 = lane & 31, h = lane >> 5;
+#pragma unroll
+  for (int x = 0; x < TM; ++x)
+#pragma unroll
+    for (int y = 0; y < TN; ++y)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        *reinterpret_cast<float4*>(rows + (32 * x + r31) * LDF + 32 * y + 8 * q + 4 * h) =
+            make_float4(acc[x][y][4 * q], acc[x][y][4 * q + 1], acc[x][y][4 * q + 2], acc[x][y][4 * q + 3]);
+}
+
 template <int OP, int BM, int BN, int FORM>
 __device__ __forceinline__ void f32_split_body(const F32Args& a, unsigned block, unsigned blocks) {
   using Tile = F32Tile<OP, BM, BN, FORM, false>;
@@ -85,58 +180,27 @@ __device__ __forceinline__ void f32_split_body(const F32Args& a, unsigned block,
   sched_fence();
 
   // ---- where a load's four values go in a part, where the operands are read ---------------------------
-  // KC: four k of row 64 ii + kc_row.  MC: four rows of k-row mc_k.
   unsigned wr[LPT];
 #pragma unroll
   for (int l = 0; l < LPT; ++l) {
     const bool isA = l < LA;
     const int ii = isA ? l : l - LA, rows = isA ? BM : BN;
-    if (isA ? A_KC : B_KC) {
-      const int row = 64 * ii + t.kc_row, q = lane & 3;
-      wr[l] = (unsigned)(row * 32 + (((q >> 1) ^ ((row >> 3) & 1)) * 16) + (q & 1) * 8);
-    } else {
-      const int k = t.mc_k(rows, ii), q = lane % (rows / 4);
-      wr[l] = (unsigned)(k * rows * 2 + (((q >> 1) ^ ((rows >= 128 ? 4 : 2) * (k & 3))) * 16) + (q & 1) * 8);
-    }
+    if (isA ? A_KC : B_KC) wr[l] = f32_kc_at(64 * ii + t.kc_row, lane & 3);
+    else wr[l] = f32_mc_at(rows, t.mc_k(rows, ii), lane % (rows / 4));
     if (!isA) wr[l] += (unsigned)B0;
   }
-  const int r31 = lane & 31, h = lane >> 5;
-  // KC: row r31, k 8 h .. 8 h + 7.  MC: 16-lane group gi = lane / 16 reads half gi % 2 of the 32 rows and k block gi / 2; lane
-  // 4 j + c4 of the group addresses k-row j, the 8-byte piece c4 of those 16 rows.
   unsigned rdA[A_KC ? 1 : 2 * TM], rdB[B_KC ? 1 : 2 * TN];
-  auto read_addr = [&](unsigned* rd, bool kc, int row0, int rows, int tiles, int base) {
-    if (kc) {
-      rd[0] = (unsigned)(base + (row0 + r31) * 32 + ((h ^ ((r31 >> 3) & 1)) * 16));
-    } else {
-      const int gi = lane >> 4, j = (lane >> 2) & 3, c4 = lane & 3;
-#pragma unroll
-      for (int x = 0; x < tiles; ++x)
-#pragma unroll
-        for (int hf = 0; hf < 2; ++hf) {
-          const int k = 8 * (gi >> 1) + 4 * hf + j, c = (row0 + 32 * x + 16 * (gi & 1) + 4 * c4) / 8;
-          rd[2 * x + hf] = (unsigned)(base + k * rows * 2 + ((c ^ ((rows >= 128 ? 4 : 2) * (k & 3))) * 16) + (c4 & 1) * 8);
-        }
-    }
-  };
-  read_addr(rdA, A_KC, wm * (BM / 2), BM, TM, 0);
-  read_addr(rdB, B_KC, wn * (BN / 2), BN, TN, B0);
+  f32_read_addr<A_KC, TM>(rdA, lane, wm * (BM / 2), BM, 0);
+  f32_read_addr<B_KC, TN>(rdB, lane, wn * (BN / 2), BN, B0);
 
   bf16x8 fa[3][TM], fb[3][TN];
-  auto read_operand = [&](bool kc, const unsigned* rd, int x, int off) {
-    if (kc) return *(const __attribute__((address_space(3))) bf16x8*)(ldsb + rd[0] + (off + x * 1024));
-    typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-    struct { s16x4 lo, hi; } v;
-    v.lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(ldsb + rd[2 * x] + off));
-    v.hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(ldsb + rd[2 * x + 1] + off));
-    return __builtin_bit_cast(bf16x8, v);
-  };
   auto read_a = [&](int st, int k) {
 #pragma unroll
-    for (int x = 0; x < TM; ++x) fa[k][x] = read_operand(A_KC, rdA, x, st * STAGE + k * A_PART);
+    for (int x = 0; x < TM; ++x) fa[k][x] = f32_read_operand<A_KC>(ldsb, rdA, x, st * STAGE + k * A_PART);
   };
   auto read_b = [&](int st, int k) {
 #pragma unroll
-    for (int y = 0; y < TN; ++y) fb[k][y] = read_operand(B_KC, rdB, y, st * STAGE + k * B_PART);
+    for (int y = 0; y < TN; ++y) fb[k][y] = f32_read_operand<B_KC>(ldsb, rdB, y, st * STAGE + k * B_PART);
   };
   // what the first two groups of products need, and what the last group leaves free
   auto read_first = [&](int st) {
@@ -145,25 +209,12 @@ __device__ __forceinline__ void f32_split_body(const F32Args& a, unsigned block,
     read_a(st, 0);
   };
 
-  // Taking load l of register set SET apart, in kSteps steps of two vector instructions (the products hide four behind each of
-  // them): its values are scaled, then the next eight bits of them go to LDS as part k and, where another part follows, are taken off
-  // value by value (exact).
-  constexpr int kScale = 2, kSteps = kScale + 11;
+  // step K of taking load l of register set SET apart
+  constexpr int kSteps = kSplitSteps;
   u32x2 part[LPT];
   auto split_step = [&](auto set_tag, auto l_tag, auto step_tag, int st) {
-    constexpr int SET = decltype(set_tag)::value, Lx = decltype(l_tag)::value, STEP = decltype(step_tag)::value - kScale;
-    constexpr int K = STEP / 5, E = STEP % 5 - 1;
-    f32x4& v = raw[SET][Lx];
-    if constexpr (STEP < 0) {
-      v[2 * (STEP + kScale)] *= 0x1p24f;
-      v[2 * (STEP + kScale) + 1] *= 0x1p24f;
-    } else if constexpr (E < 0) {
-      part[Lx] = u32x2{__builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{v[0], v[1]}, bf16x2)),
-                       __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{v[2], v[3]}, bf16x2))};
-      *(__attribute__((address_space(3))) u32x2*)(ldsb + wr[Lx] + (st * STAGE + K * (Lx < LA ? A_PART : B_PART))) = part[Lx];
-    } else {
-      v[E] -= __builtin_bit_cast(float, E % 2 == 0 ? part[Lx][E / 2] << 16 : part[Lx][E / 2] & 0xffff0000u);
-    }
+    constexpr int Lx = decltype(l_tag)::value;
+    f32_split_step<decltype(step_tag)::value>(raw[decltype(set_tag)::value][Lx], part[Lx], ldsb + wr[Lx] + st * STAGE, Lx < LA ? A_PART : B_PART);
   };
 
   f32x16 acc[TM][TN], low[TM][TN];
@@ -174,13 +225,6 @@ __device__ __forceinline__ void f32_split_body(const F32Args& a, unsigned block,
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[x][y][r] = low[x][y][r] = 0.0f;
 
-  // This wavefront's LDS writes have landed, and everyone else's; loads stay in flight.  Both sides of it are ordinary accesses,
-  // which the compiler may move across the barrier itself: the fences, of LDS alone, are what keeps them in place.
-  auto barrier = [&] {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-  };
   // The parts of the next tile are written behind kWritten of the 6 TT products, the barrier that waits for them is kMeet products
   // in, with the reads of read_first behind it.  20 and 22 of 24; ResNet-50's operations at N = 64 with 18 and 22 11.50 ms, 20 and 22
   // 11.39, 21 and 22 11.43, 20 and 23 11.43.
@@ -197,7 +241,7 @@ __device__ __forceinline__ void f32_split_body(const F32Args& a, unsigned block,
     static_for<0, 6 * TT>([&](auto s_tag) {
       constexpr int S = decltype(s_tag)::value, P = S / TT, X = S % TT / TN, Y = S % TN;
       if constexpr (S == kMeet) {
-        barrier();
+        f32_lds_meet();
         read_first(NEXT);
         sched_fence();
       }
@@ -205,12 +249,11 @@ __device__ __forceinline__ void f32_split_body(const F32Args& a, unsigned block,
       // n operand in the first slot: each lane then owns 4 consecutive n for one m (row = lane % 32)
       d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[kB[P]][Y], fa[kA[P]][X], d, 0, 0, 0);
       if constexpr (S < kWritten) {
-        static_for<0, kSteps * LPT>([&](auto u_tag) {
+        constexpr int STEPS = kSteps * LPT;
+        static_for<(S * STEPS + kWritten - 1) / kWritten, ((S + 1) * STEPS + kWritten - 1) / kWritten>([&](auto u_tag) {
           constexpr int U = decltype(u_tag)::value, Lx = U / kSteps, K = U % kSteps;
-          if constexpr (U * kWritten / (kSteps * LPT) == S) {
-            split_step(std::integral_constant<int, NEXT>{}, std::integral_constant<int, Lx>{}, std::integral_constant<int, K>{}, NEXT);
-            if constexpr (K + 1 == kSteps) request(n, std::integral_constant<int, NEXT>{}, std::integral_constant<int, Lx>{});
-          }
+          split_step(std::integral_constant<int, NEXT>{}, std::integral_constant<int, Lx>{}, std::integral_constant<int, K>{}, NEXT);
+          if constexpr (K + 1 == kSteps) request(n, std::integral_constant<int, NEXT>{}, std::integral_constant<int, Lx>{});
         });
       }
       sched_fence();
@@ -224,7 +267,7 @@ __device__ __forceinline__ void f32_split_body(const F32Args& a, unsigned block,
       static_for<0, kSteps>([&](auto k_tag) { split_step(EVEN, l_tag, k_tag, 0); });
       request(n, EVEN, l_tag);
     });
-    barrier();
+    f32_lds_meet();
     read_first(0);
     sched_fence();
     // Behind an odd number of tiles there is one of zeros: with a condition around it the waits would count for a path without
@@ -235,35 +278,11 @@ __device__ __forceinline__ void f32_split_body(const F32Args& a, unsigned block,
     }
   }
 
-  float odd = 0.f;  // 0 or, from a result that is not finite, NaN
-#pragma unroll
-  for (int x = 0; x < TM; ++x)
-#pragma unroll
-    for (int y = 0; y < TN; ++y)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        acc[x][y][r] = (acc[x][y][r] + low[x][y][r]) * 0x1p-48f;
-        odd = fmaf(acc[x][y][r], 0.f, odd);
-      }
-  __shared__ int not_finite[4];
-  const bool any = __ballot(odd != 0.f) != 0;
-  if (lane == 0) not_finite[wave] = any;
-  __syncthreads();  // and the tile is staged where the operands were
-  if (__builtin_amdgcn_readfirstlane(not_finite[0] | not_finite[1] | not_finite[2] | not_finite[3])) {
+  if (!f32_join_sums(acc, low, lane, wave)) {
     f32_dma_body<OP, BM, BN, FORM>(a, block, blocks);
     return;
   }
-  // accumulator register r of tile (x,y): m = wrow + 32 x + lane % 32, n = wcol + 32 y + 8 (r / 4) + 4 (lane / 32) + r % 4
-  t.template store<Lds::LDS_BYTES>(lds_f, [&](float* rows) {
-#pragma unroll
-    for (int x = 0; x < TM; ++x)
-#pragma unroll
-      for (int y = 0; y < TN; ++y)
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          *reinterpret_cast<float4*>(rows + (32 * x + r31) * Tile::LDF + 32 * y + 8 * q + 4 * h) =
-              make_float4(acc[x][y][4 * q], acc[x][y][4 * q + 1], acc[x][y][4 * q + 2], acc[x][y][4 * q + 3]);
-  });
+  t.template store<Lds::LDS_BYTES>(lds_f, [&](float* rows) { f32_put_rows<Tile::LDF>(rows, acc, lane); });
 }
 
 template <int OP, int BM, int BN, int FORM, bool PARTS>

@@ -1,0 +1,54 @@
+"""Single-precision 3x3 layers whose output grid is their input grid: a tile's pixels taken apart once for all nine taps.  The sizes are
+such that the plan takes that kernel: the widest image that fits the window and both window lengths, narrow and single-row
+images, ragged pixels and columns, both tile widths, whole and split reductions."""
+import numpy as np
+import pytest
+
+from test_gpu_conv_f32 import check_f32, jz, run_f32  # noqa: F401  (jz is a fixture)
+from test_gpu_conv_f32_parts import calls, operands
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [
+    # N, H, W, C, K, R, S, stride, pad
+    (12, 43, 63, 64, 64, 3, 3, 1, 1),     # the widest image, 64-wide tiles
+    (32, 33, 31, 96, 64, 3, 3, 1, 1),     # the widest of the short window
+    (26, 39, 32, 64, 56, 3, 3, 1, 1),     # the narrowest of the long one, ragged columns (backward: not this kernel)
+    (728, 9, 5, 64, 64, 3, 3, 1, 1),      # several images under a tile
+    (818, 1, 40, 64, 64, 3, 3, 1, 1),     # one row: two thirds of the taps lie outside
+    (818, 40, 1, 64, 64, 3, 3, 1, 1),     # one column
+    (14, 61, 37, 32, 64, 3, 3, 1, 1),     # the shortest reduction: one pair of windows (backward: two)
+    (43, 28, 28, 128, 128, 3, 3, 1, 1),   # the last rows of tiles split
+    (60, 14, 14, 256, 256, 3, 3, 1, 1),   # 128-wide tiles
+]
+
+
+@pytest.mark.parametrize("cfg", SHAPES, ids=str)
+def test_accuracy(jz, cfg):  # noqa: F811
+    od, x, w, dy = operands(cfg, 200 + SHAPES.index(cfg))
+    d = jz.conv_desc(*cfg)
+    ops = calls(jz, od, x, w, dy)
+    for op in (jz.JZ_FWD, jz.JZ_BWD_DATA):
+        a, b, shape, fn, red = ops[op]
+        err, _ = check_f32(run_f32(jz, op, d, a, b, shape), fn(od, a, b), fn(od, np.abs(a), np.abs(b)), "op %d" % op)
+        # the bar of the kernel that takes every tap's values apart: the same products, the large sums rounded once in 16 steps
+        assert err <= 2.0 ** -24 * (2 + 2 * (red / 16) ** 0.5), (op, err)
+
+
+@pytest.mark.parametrize("cfg", [SHAPES[1], SHAPES[7], SHAPES[8]], ids=str)
+def test_values_that_parts_cannot_hold(jz, cfg):  # noqa: F811
+    """A tile with such a value is computed again with the FP32 instructions, its share of a split reduction too: in the window
+    kernel's order, channels outside and taps inside."""
+    for value in (3.4e38, np.inf, np.nan):
+        od, x, w, dy = operands(cfg, 230, (1.0, 0.01))
+        x[0, 3, 2, 7] = x[-1, -1, -1, -1] = value
+        dy[0, 2, 4, 9] = dy[-1, 0, 0, -1] = value
+        d = jz.conv_desc(*cfg)
+        ops = calls(jz, od, x, w, dy)
+        for op in (jz.JZ_FWD, jz.JZ_BWD_DATA):
+            a, b, shape, fn, red = ops[op]
+            got = run_f32(jz, op, d, a, b, shape)
+            ref, mag = fn(od, a, b), fn(od, np.abs(a), np.abs(b))
+            assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isinf(got), np.isinf(ref)), op
+            ok = np.isfinite(ref)
+            check_f32(got[ok], ref[ok], mag[ok], "op %d" % op)
