@@ -318,31 +318,44 @@ __device__ __forceinline__ void chunk_body(int64_t s, int64_t e, int64_t* b0, in
   *b1 = a + ((e - a) & ~int64_t(7));
 }
 
-// One thread's share (tid of LARS_THREADS) of a chunk's sum of w^2, in the order lars_update adds it (the 4-element groups
-// in turn, then at most one head / tail element).
-__device__ __forceinline__ double chunk_thread_sumsq_w(const ChunkRec& rec, const float* __restrict__ w, int tid) {
+// A thread's weights of one chunk: its 4-element groups (zero where the chunk has none) and at most one head / tail element.  Whole
+// chunks, nearly all, are loaded without conditions: behind a condition each, one group was waited for before the next was asked for.
+struct ChunkWeights {
+  float4 q[LARS_QUADS];
+  float edge;
+};
+__device__ __forceinline__ ChunkWeights load_chunk_weights(const ChunkRec& rec, const float* __restrict__ w, int tid) {
+  ChunkWeights r;
+  if (rec.count == LARS_CH && (rec.start & 7) == 0) {
+#pragma unroll
+    for (int k = 0; k < LARS_QUADS; ++k) r.q[k] = *reinterpret_cast<const float4*>(w + rec.start + (k * LARS_THREADS + tid) * 4);
+    r.edge = 0.f;
+    return r;
+  }
   int t;
   int64_t s, e, b0, b1;
   chunk_range(rec, &t, &s, &e);
   chunk_body(s, e, &b0, &b1);
+#pragma unroll
+  for (int k = 0; k < LARS_QUADS; ++k) {
+    const int64_t i = b0 + (int64_t)(k * LARS_THREADS + tid) * 4;
+    r.q[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (i < b1) r.q[k] = *reinterpret_cast<const float4*>(w + i);
+  }
+  const int64_t nh = b0 - s, nt = e - b1, k = tid;
+  r.edge = k < nh + nt ? w[k < nh ? s + k : b1 + (k - nh)] : 0.f;
+  return r;
+}
+// Its sum of squares, in the order lars_update adds it.
+__device__ __forceinline__ double chunk_thread_sumsq_w(const ChunkWeights& r) {
   double sw = 0.0;
 #pragma unroll
   for (int k = 0; k < LARS_QUADS; ++k) {
-    int64_t i = b0 + (int64_t)(k * LARS_THREADS + tid) * 4;
-    if (i < b1) {
-      const float4 a = *reinterpret_cast<const float4*>(w + i);
-      const float wv[4] = {a.x, a.y, a.z, a.w};
+    const float wv[4] = {r.q[k].x, r.q[k].y, r.q[k].z, r.q[k].w};
 #pragma unroll
-      for (int j = 0; j < 4; ++j) sw = fma((double)wv[j], (double)wv[j], sw);
-    }
+    for (int j = 0; j < 4; ++j) sw = fma((double)wv[j], (double)wv[j], sw);
   }
-  int64_t nh = b0 - s, nt = e - b1;
-  int64_t k = tid;
-  if (k < nh + nt) {
-    int64_t i = (k < nh) ? s + k : b1 + (k - nh);
-    sw = fma((double)w[i], (double)w[i], sw);
-  }
-  return sw;
+  return fma((double)r.edge, (double)r.edge, sw);
 }
 
 // A thread's gradients of one chunk: its 8-element groups (zero where the chunk has none) and at most one head / tail element.
@@ -392,7 +405,7 @@ __global__ __launch_bounds__(LARS_THREADS) void lars_reduce(Tables tb, const flo
   const bool have_w = tb.state[0] != 0;  // written by the previous update, i.e. by an earlier launch
   if (!table_ok(tb)) return;
   const double sg = wave_sum(chunk_thread_sumsq_g(load_chunk_grads(rec, g16, threadIdx.x)));
-  const double sw = have_w ? 0.0 : wave_sum(chunk_thread_sumsq_w(rec, w, threadIdx.x));
+  const double sw = have_w ? 0.0 : wave_sum(chunk_thread_sumsq_w(load_chunk_weights(rec, w, threadIdx.x)));
   if ((threadIdx.x & 63) == 0) {
     red[threadIdx.x >> 6] = sg;
     if (!have_w) tb.psum_w[(size_t)c * LARS_WAVES + (threadIdx.x >> 6)] = sw;
@@ -403,8 +416,9 @@ __global__ __launch_bounds__(LARS_THREADS) void lars_reduce(Tables tb, const flo
 
 // The sums of a group of chunks for an update that works out the rates itself: it also finds the device-resident loss scale where
 // it does not adjust it.
+// Eight wavefronts a SIMD: two workgroups of 1024 threads a compute unit (71 registers, room for one: AlexNet 221 -> 224 us).
 template <int T>
-__global__ __launch_bounds__(T) void lars_reduce_groups(Tables tb, const float* __restrict__ w, const unsigned short* __restrict__ g16,
+__global__ __launch_bounds__(T, 8) void lars_reduce_groups(Tables tb, const float* __restrict__ w, const unsigned short* __restrict__ g16,
                                                        const float* __restrict__ scale_dev) {
   __shared__ double red[2][T / 64];
   constexpr int U = 4, PIECES = LARS_CH / 8;     // 16-byte loads of a thread requested together; of a whole chunk
@@ -427,7 +441,7 @@ __global__ __launch_bounds__(T) void lars_reduce_groups(Tables tb, const float* 
   if (!have_w) {  // a fresh workspace: what the previous update would have left, chunk by chunk
     for (int j = (int)(threadIdx.x / LARS_THREADS); j < gr.chunks; j += T / LARS_THREADS) {
       const int c = gr.chunk0 + j * gr.stride;
-      const double p = wave_sum(chunk_thread_sumsq_w(tb.chunk_rec[c], w, threadIdx.x % LARS_THREADS));
+      const double p = wave_sum(chunk_thread_sumsq_w(load_chunk_weights(tb.chunk_rec[c], w, threadIdx.x % LARS_THREADS)));
       if ((threadIdx.x & 63) == 0) tb.psum_w[(size_t)c * LARS_WAVES + (threadIdx.x % LARS_THREADS >> 6)] = p;
     }
     __threadfence_block();
@@ -548,8 +562,12 @@ __global__ __launch_bounds__(LARS_THREADS) void lars_begin(Tables tb, const floa
     // Fresh workspace: leave in psum_w what lars_reduce would (same elements per thread, same order), chunk by chunk, so
     // that the sum below is the same bits whether the partial sums were carried or are recomputed here.  One workgroup
     // per tensor makes this slow for large tensors; it runs once per jz_lars_prepare.
+    ChunkWeights next{};
+    if (c0 < c1) next = load_chunk_weights(tb.chunk_rec[c0], w, threadIdx.x);
     for (int c = c0; c < c1; ++c) {
-      const double p = wave_sum(chunk_thread_sumsq_w(tb.chunk_rec[c], w, threadIdx.x));
+      const ChunkWeights now = next;
+      next = load_chunk_weights(tb.chunk_rec[c + 1 < c1 ? c + 1 : c], w, threadIdx.x);  // on its way while these are added
+      const double p = wave_sum(chunk_thread_sumsq_w(now));
       if ((threadIdx.x & 63) == 0) tb.psum_w[(size_t)c * LARS_WAVES + (threadIdx.x >> 6)] = p;
     }
     __threadfence_block();
@@ -862,7 +880,7 @@ __global__ __launch_bounds__(1024) void lars_small(Tables tb, float* __restrict_
   for (int c = group; c < tb.n_chunks; c += 1024 / LARS_THREADS) {
     const ChunkRec rec = tb.chunk_rec[c];
     const double sg = wave_sum(chunk_thread_sumsq_g(load_chunk_grads(rec, g16, tid)));
-    const double sw = have_w ? 0.0 : wave_sum(chunk_thread_sumsq_w(rec, w, tid));
+    const double sw = have_w ? 0.0 : wave_sum(chunk_thread_sumsq_w(load_chunk_weights(rec, w, tid)));
     if ((tid & 63) == 0) {
       pg[c][tid >> 6] = sg;
       pw[c][tid >> 6] = sw;
