@@ -29,7 +29,7 @@
 // operands are read from LDS as bfloat16: 4 to 5 instructions per product for 128x128 tiles.  On the 512-channel layer the pipes
 // are then busy for 81 % of the compute units' busy cycles, without bank conflicts, at a clock that power holds at 1.4-1.5 GHz.  ResNet-50's
 // own layers are not at that bound: 45-54 % in the main variants, 46 % over the stack, at 2.0-2.4 GHz under the profiler (short reductions:
-// each workgroup's first tiles and its epilogue; the values of a 3x3 layer are taken apart once per tap).
+// each workgroup's first tiles and its epilogue; the values of a 3x3 layer are taken apart once per tap, hence jz_f32_window.h).
 //
 // A tile's loads are requested two tiles ahead; the parts of tile i + 1 are made and written to the other of two stages between
 // the products of tile i; one barrier a tile, in the last of the six groups of products.  LDS layouts of a part ("KC", "MC" as in jz_f32_dma.h): KC rows of 16 bfloat16, 16-byte half c of row r at place

@@ -6,7 +6,8 @@
 // 128x64, and energy, which is what bounds long reductions.  Here the 128 pixels of a tile, which are consecutive in memory, and what their
 // taps reach (a run of 128 + 2 W + 2 pixels) are taken apart into LDS once per 16 channels, and each tap reads its rows out of that run at
 // its own distance; rows whose tap lies outside the image read a row of zeros (one bit per row and tap).  Only the filter still is taken apart
-// tile by tile.  That leaves 2.6 + 0.7 vector instructions per product for 128x128 tiles.
+// tile by tile.  That leaves about 3.2 vector instructions per product for 128x128 tiles: 2.2 for
+// the filter, 0.4 for the pixels, 0.6 for the taps' addresses.
 //
 //   LDS: two windows, each three parts of PR rows of 16 bfloat16 and 16 rows of zeros | two stages of the filter's parts, as in
 //   jz_f32_split.h.  Rows have the KC layout; its swizzle goes by the row's place in LDS, so any 16 consecutive rows read without conflicts.
