@@ -20,8 +20,8 @@
 // Relative errors against 64 bits over eight layers, both directions, are 0.3 ... 1.0 of those of the form before.
 //
 // The reduction runs blocks of 16 channels outside, taps inside.  The loop is unrolled over two blocks, 18 k tiles, so that the tap, both LDS
-// buffers and the register set of a load are constants: the window of the next block is requested during the first taps of one, a load a
-// tile, and taken apart during the last ones.
+// buffers and the register set of a load are constants: the window of the next block is requested behind the filter of one's second
+// tap and taken apart during the last taps (loads return in order: with one window load a tap every filter tile waited for one).
 #pragma once
 
 template <int BN, int LP>
