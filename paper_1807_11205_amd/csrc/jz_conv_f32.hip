@@ -402,7 +402,8 @@ void choose_tiling_f32(PlanF32* pl, bool may_split, bool fixed_tile = false, siz
         const double t_lat = l1 * (t.prologue[c] + t.lat[c] * even(t, a.nkt)) + l2 * (t.prologue[c] + t.lat[c] * kps);
         const double out = 4e-6 * a.M * a.N, part = sp > 1 ? 4e-6 * real * (double)(a.M - full * t.bm) * a.N : 0.0;
         if (1e6 * part > (t.window ? most_part : (double)limit)) continue;
-        const int chain = full > 0 ? a.nkt : kps;  // k tiles that are added up one after the other
+        // k tiles that are added up one after the other: at most in a plan with a window, at least in one without
+        const int chain = t.window && full > 0 ? a.nkt : kps;
         if (t.window && t.bn == 128 && chain > most_chain) continue;
         const double t_mem = byte[t.parts][c] * (in + part + (full > 0 ? out : 0.0));
         double time = fixed[t.parts][c] + (t.parts ? parts_ahead : 0.0) + sqrt(sqrt(p4(t_thr) + p4(t_lat) + p4(t_mem)));
