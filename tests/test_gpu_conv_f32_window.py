@@ -19,7 +19,11 @@ SHAPES = [
     (818, 40, 1, 64, 64, 3, 3, 1, 1),     # one column
     (14, 61, 37, 32, 64, 3, 3, 1, 1),     # the shortest reduction: one pair of windows (backward: two)
     (43, 28, 28, 128, 128, 3, 3, 1, 1),   # the last rows of tiles split
-    (60, 14, 14, 256, 256, 3, 3, 1, 1),   # 128-wide tiles
+    (60, 14, 14, 256, 256, 3, 3, 1, 1),
+    (12, 43, 63, 64, 128, 3, 3, 1, 1),    # 128-wide tiles forward, both window lengths
+    (32, 33, 31, 64, 128, 3, 3, 1, 1),
+    (24, 43, 63, 128, 64, 3, 3, 1, 1),    # and backward
+    (64, 33, 31, 128, 64, 3, 3, 1, 1),
 ]
 
 
