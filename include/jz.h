@@ -430,6 +430,7 @@ int jz_bn_relu_bwd(int64_t rows, int channels, const void* x16, const void* y16,
  * operation: GEMM dimensions, kernel variant (output tile, k tile depth, wavefronts), tiles, split of the reduction.
  * For tuning and bug reports; the wording is not part of the contract.  Same status codes as the workspace query. */
 int jz_conv2d_describe_plan(int op, const jz_conv_desc* desc, char* text, size_t text_bytes);
+int jz_conv2d_f32_describe_plan(int op, const jz_conv_desc* desc, char* text, size_t text_bytes);
 
 /* Planner tuning hook (HOST state, process-wide, guarded by a mutex).  jz_conv2d_tune_set records, for the GEMM that
  * `op` on `desc` maps to, which kernel variant to run: output tile tile_m x tile_n, k tile depth, wavefronts per

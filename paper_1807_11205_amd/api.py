@@ -37,7 +37,7 @@ JZ_PARAM_WEIGHT_DECAY, JZ_PARAM_LARS, JZ_PARAM_GRAD_PRESUMMED = 1, 2, 4
 EXPORTS = [
     "jz_conv2d_workspace_bytes", "jz_conv2d_describe_plan", "jz_conv2d_tune_set", "jz_conv2d_tune_use_table", "jz_conv2d_tune_clear", "jz_conv2d_fwd", "jz_conv2d_bwd_data", "jz_conv2d_bwd_weight", "jz_conv2d_bwd_weight_static",
     "jz_conv2d_bwd_weight_sumsq", "jz_conv2d_bwd_weight_beside", "jz_conv2d_bwd_weight_set_workspace_bytes", "jz_conv2d_bwd_weight_set", "jz_gemm_fc_workspace_bytes", "jz_gemm_fc", "jz_gemm_fc_bwd_weight_sumsq",
-    "jz_conv2d_f32_workspace_bytes", "jz_conv2d_fwd_f32", "jz_conv2d_bwd_data_f32", "jz_conv2d_bwd_weight_f32",
+    "jz_conv2d_f32_workspace_bytes", "jz_conv2d_f32_describe_plan", "jz_conv2d_fwd_f32", "jz_conv2d_bwd_data_f32", "jz_conv2d_bwd_weight_f32",
     "jz_gemm_fc_f32_workspace_bytes", "jz_gemm_fc_f32",
     "jz_lars_workspace_bytes", "jz_lars_prepare", "jz_lars_mp_update", "jz_loss_scale_init", "jz_lars_mp_update_dyn",
     "jz_lars_begin_step", "jz_lars_sumsq_sink", "jz_lars_grad_sumsq", "jz_lars_mp_update_presummed", "jz_lars_mp_update_presummed_dyn",
@@ -109,6 +109,7 @@ def lib() -> ctypes.CDLL:
         dp = ctypes.POINTER(jz_conv_desc)
         L.jz_conv2d_workspace_bytes.argtypes = [ci, dp, ctypes.POINTER(sz)]
         L.jz_conv2d_describe_plan.argtypes = [ci, dp, ctypes.c_char_p, sz]
+        L.jz_conv2d_f32_describe_plan.argtypes = [ci, dp, ctypes.c_char_p, sz]
         L.jz_conv2d_tune_set.argtypes = [ci, dp, ci, ci, ci, ci, ci, ci]
         L.jz_conv2d_tune_use_table.argtypes = [ci]
         L.jz_conv2d_tune_clear.argtypes = []
@@ -375,6 +376,12 @@ def jz_conv2d_f32_workspace_bytes(op: int, desc: jz_conv_desc) -> int:
     n = ctypes.c_size_t(0)
     _check(lib().jz_conv2d_f32_workspace_bytes(op, ctypes.byref(desc), ctypes.byref(n)), "jz_conv2d_f32_workspace_bytes")
     return n.value
+
+
+def jz_conv2d_f32_describe_plan(op: int, desc: jz_conv_desc) -> str:
+    buf = ctypes.create_string_buffer(256)
+    _check(lib().jz_conv2d_f32_describe_plan(op, ctypes.byref(desc), buf, 256), "jz_conv2d_f32_describe_plan")
+    return buf.value.decode()
 
 
 def jz_conv2d_f32(op: int, desc: jz_conv_desc, a32, b32, out32, ws=None, stream=None):

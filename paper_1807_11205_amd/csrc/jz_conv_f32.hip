@@ -24,6 +24,7 @@
 #include <hip/hip_runtime.h>
 
 #include <math.h>
+#include <stdio.h>
 
 #include <algorithm>
 #include <type_traits>
@@ -743,6 +744,27 @@ extern "C" int jz_conv2d_f32_workspace_bytes(int op, const jz_conv_desc* desc, s
   int rc = make_plan_f32(op, desc, &pl);
   if (rc != JZ_OK) return rc;
   *bytes = pl.ws_bytes;
+  return JZ_OK;
+}
+
+extern "C" int jz_conv2d_f32_describe_plan(int op, const jz_conv_desc* desc, char* text, size_t text_bytes) {
+  if (!text || text_bytes == 0) return JZ_ERR_NULL;
+  PlanF32 pl;
+  int rc = make_plan_f32(op, desc, &pl);
+  if (rc != JZ_OK) return rc;
+  const bool widen = pl.widen;
+  if (widen) {
+    const jz_conv_desc w = pl.wide;
+    pl = PlanF32{};
+    if ((rc = make_plan_f32(op, &w, &pl)) != JZ_OK) return rc;
+  }
+  const F32Args& a = pl.args;
+  char form[64];
+  if (pl.window) snprintf(form, sizeof form, "parts, window of %d rows", f32_window_rows(a.g));
+  else snprintf(form, sizeof form, "%s%s", !pl.dma ? "operands through registers" : pl.parts ? "parts" : "FP32 instructions", pl.gen ? ", per-lane taps" : "");
+  snprintf(text, text_bytes, "M %d N %d K %d: %s%s%s, tile %dx%d, %d x %d tiles, %d splits of %d k tiles, %d rows of tiles whole", a.M, a.N, a.Kred,
+           widen ? "copies of 4 n channels, " : "", form, pl.classes ? ", residues of the stride" : "", pl.BM, pl.BN, a.tiles_m, a.tiles_n, a.splits,
+           a.kt_per_split, a.full_rows);
   return JZ_OK;
 }
 

@@ -49,12 +49,12 @@ int launch_f32_window_tile(const F32Args& a, hipStream_t st) {
 template <int OP>
 int launch_f32_window(const PlanF32& pl, hipStream_t st) {
   const F32Args& a = pl.args;
-  const int rows = 128 + 2 * a.g.IW + 2;
   if (a.g.R != 3 || a.g.S != 3 || a.g.ph != 1 || a.g.pw != 1 || a.g.sh != 1 || a.g.sw != 1 || a.g.IH != a.g.OH || a.g.IW != a.g.OW || a.sc_on || pl.BM != 128 ||
-      rows > 256 || a.g.IC % (2 * FD_BK) != 0 || a.kt_per_split % 18 != 0 || a.nkt % 18 != 0)
+      a.g.IW > 63 || a.g.IC % (2 * FD_BK) != 0 || a.kt_per_split % 18 != 0 || a.nkt % 18 != 0)
     return JZ_ERR_UNSUPPORTED;
-  if (pl.BN == 128) return rows <= 192 ? launch_f32_window_tile<OP, 128, 3>(a, st) : launch_f32_window_tile<OP, 128, 4>(a, st);
-  return rows <= 192 ? launch_f32_window_tile<OP, 64, 3>(a, st) : launch_f32_window_tile<OP, 64, 4>(a, st);
+  const bool narrow = f32_window_rows(a.g) == 192;
+  if (pl.BN == 128) return narrow ? launch_f32_window_tile<OP, 128, 3>(a, st) : launch_f32_window_tile<OP, 128, 4>(a, st);
+  return narrow ? launch_f32_window_tile<OP, 64, 3>(a, st) : launch_f32_window_tile<OP, 64, 4>(a, st);
 }
 
 template <int OP, int FORM, bool PARTS>

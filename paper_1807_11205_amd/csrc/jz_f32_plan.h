@@ -59,6 +59,9 @@ struct F32Set {
   unsigned first[FD_MAX_SET + 1];  // workgroup numbers of member k: first[k] .. first[k + 1] - 1
 };
 
+// rows of window that a tile of a layer on jz_f32_window.h gets: its 128 pixels and what their taps reach
+inline int f32_window_rows(const ConvGeom& g) { return 128 + 2 * g.IW + 2 <= 192 ? 192 : 256; }
+
 int launch_f32_fwd(const PlanF32& pl, hipStream_t st);
 int launch_f32_bwd_data(const PlanF32& pl, hipStream_t st, const F32Set* set = nullptr);  // set: these problems instead of the plan's own
 int launch_f32_bwd_weight(const PlanF32& pl, hipStream_t st);

@@ -1,6 +1,8 @@
 """Single-precision 3x3 layers whose output grid is their input grid: a tile's pixels taken apart once for all nine taps.  The sizes are
-such that the plan takes that kernel: the widest image that fits the window and both window lengths, narrow and single-row
-images, ragged pixels and columns, both tile widths, whole and split reductions."""
+such that the plan takes that kernel, which the tests look up: the widest image that fits the window and both window lengths, narrow and
+single-row images, ragged pixels and columns, both tile widths, whole and split reductions.  test_plan_f32.py asks the plans on the CPU."""
+import re
+
 import numpy as np
 import pytest
 
@@ -17,14 +19,48 @@ SHAPES = [
     (728, 9, 5, 64, 64, 3, 3, 1, 1),      # several images under a tile
     (818, 1, 40, 64, 64, 3, 3, 1, 1),     # one row: two thirds of the taps lie outside
     (818, 40, 1, 64, 64, 3, 3, 1, 1),     # one column
-    (14, 61, 37, 32, 64, 3, 3, 1, 1),     # the shortest reduction: one pair of windows (backward: two)
+    (14, 61, 37, 32, 64, 3, 3, 1, 1),     # forward not this kernel; backward two pairs of windows
     (43, 28, 28, 128, 128, 3, 3, 1, 1),   # the last rows of tiles split
     (60, 14, 14, 256, 256, 3, 3, 1, 1),
     (12, 43, 63, 64, 128, 3, 3, 1, 1),    # 128-wide tiles forward, both window lengths
     (32, 33, 31, 64, 128, 3, 3, 1, 1),
     (24, 43, 63, 128, 64, 3, 3, 1, 1),    # and backward
     (64, 33, 31, 128, 64, 3, 3, 1, 1),
+    (40, 56, 22, 32, 96, 3, 3, 1, 1),     # the shortest reduction forward: one pair of windows
+    (30, 33, 11, 160, 96, 3, 3, 1, 1),    # 128-wide tiles, every row of tiles split
+    (8, 36, 38, 96, 160, 3, 3, 1, 1),
+    (49, 1, 45, 416, 32, 3, 3, 1, 1),     # a long reduction in many splits
 ]
+# columns of a tile, rows of its window and the rows of tiles whose reduction is split, forward and backward-data; None: another kernel
+FORMS = [
+    ((64, 256, "none"), (64, 256, "none")),
+    ((64, 192, "none"), (64, 192, "none")),
+    ((64, 256, "none"), None),
+    ((64, 192, "none"), (64, 192, "none")),
+    ((64, 256, "none"), (64, 256, "none")),
+    ((64, 192, "none"), (64, 192, "none")),
+    (None, (64, 256, "none")),
+    ((64, 192, "last"), (64, 192, "last")),
+    ((64, 192, "last"), (64, 192, "last")),
+    ((128, 256, "none"), (64, 256, "none")),
+    ((128, 192, "none"), (64, 192, "none")),
+    ((64, 256, "none"), (128, 256, "none")),
+    ((64, 192, "none"), (128, 192, "none")),
+    ((128, 192, "none"), (64, 192, "none")),
+    ((128, 192, "all"), None),
+    (None, (128, 256, "all")),
+    ((64, 256, "all"), None),
+]
+
+
+def window_form(jz, op, cfg):  # noqa: F811
+    """what FORMS has, as the library plans it"""
+    m = re.search(r"window of (\d+) rows, tile 128x(\d+), \d+ x \d+ tiles, (\d+) splits of \d+ k tiles, (\d+) rows",
+                  jz.jz_conv2d_f32_describe_plan(op, jz.conv_desc(*cfg)))
+    if not m:
+        return None
+    rows, bn, splits, full = (int(v) for v in m.groups())
+    return bn, rows, "none" if splits == 1 else "last" if full else "all"
 
 
 @pytest.mark.parametrize("cfg", SHAPES, ids=str)
@@ -33,13 +69,14 @@ def test_accuracy(jz, cfg):  # noqa: F811
     d = jz.conv_desc(*cfg)
     ops = calls(jz, od, x, w, dy)
     for op in (jz.JZ_FWD, jz.JZ_BWD_DATA):
+        assert window_form(jz, op, cfg) == FORMS[SHAPES.index(cfg)][op], op
         a, b, shape, fn, red = ops[op]
         err, _ = check_f32(run_f32(jz, op, d, a, b, shape), fn(od, a, b), fn(od, np.abs(a), np.abs(b)), "op %d" % op)
         # the bar of the kernel that takes every tap's values apart: the same products, the large sums rounded once in 16 steps
         assert err <= 2.0 ** -24 * (2 + 2 * (red / 16) ** 0.5), (op, err)
 
 
-@pytest.mark.parametrize("cfg", [SHAPES[1], SHAPES[7], SHAPES[8]], ids=str)
+@pytest.mark.parametrize("cfg", [SHAPES[1], SHAPES[7], SHAPES[8], SHAPES[9], SHAPES[11], SHAPES[14], SHAPES[15]], ids=str)
 def test_values_that_parts_cannot_hold(jz, cfg):  # noqa: F811
     """A tile with such a value is computed again with the FP32 instructions, its share of a split reduction too: in the window
     kernel's order, channels outside and taps inside."""
