@@ -331,6 +331,16 @@ bool needs_gen_f32(const PlanF32& pl) {
   return g.IC % FD_BK != 0 || g.R * g.S > 32 || (long long)pl.bytesA + margin >= 0xfffffff0ll;
 }
 
+// How often the large sums of a result are rounded: once per k tile of a run that is added up in the accumulators, once per such run where
+// there are several (window_run_f32), once per part of a split reduction.  A sum of n terms added one by one is off by sqrt(n / 2) roundings
+// of its final size, so is a sum of such sums, and variances add: plans compare by this number.  18x22x22 pixels, 128 -> 64, backward-data, 36
+// k tiles: three splits of 12 without a window 15 and a relative error of 8.46e-8; with one, whole, in runs of 18 20 and 9.66e-8, of 9 13 and
+// 7.85e-8.
+int roundings_f32(bool window, int bn, int k_tiles, int parts) {
+  const int run = window && bn == 64 ? window_run_f32(k_tiles) : k_tiles;
+  return run + (run < k_tiles ? k_tiles / run : 0) + (parts > 1 ? parts : 0);
+}
+
 // Form, tile and split of a launch, by a cost model in microseconds.  Forms: operands in three bfloat16 parts (jz_f32_split.h), or
 // the FP32 matrix instructions (jz_f32_dma.h), which are ahead in launches of a few microseconds and for reductions of one k tile
 // only.  A compute unit works through its share of the workgroups, `resident` of them at a time; its vector or matrix pipes bound it
@@ -382,7 +392,7 @@ void choose_tiling_f32(PlanF32* pl, bool may_split, bool fixed_tile = false, siz
   auto rounds = [](double w) { return w <= 4.0 ? ceil(w) : w + 0.5; };  // many small rounds even out
   double best = 1e30;
   double most_part = 0.0;  // bytes of partial sums of the plan without a window: the workspace that a layer asks for does not grow with one,
-  int most_chain = 0;      // and no sum is rounded more often (64-wide tiles of the window kernel start a new one every 18 k tiles)
+  int most_rounded = 0;    // and no sum is rounded more often
   int bsp = 1, bfull = 0, kt_step = 1;
   for (const Tile& t : tiles) {
     if (fixed_tile && (t.parts != pl->parts || t.bm != pl->BM || t.bn != pl->BN)) continue;
@@ -403,13 +413,24 @@ void choose_tiling_f32(PlanF32* pl, bool may_split, bool fixed_tile = false, siz
         const double t_lat = l1 * (t.prologue[c] + t.lat[c] * even(t, a.nkt)) + l2 * (t.prologue[c] + t.lat[c] * kps);
         const double out = 4e-6 * a.M * a.N, part = sp > 1 ? 4e-6 * real * (double)(a.M - full * t.bm) * a.N : 0.0;
         if (1e6 * part > (t.window ? most_part : (double)limit)) continue;
-        // k tiles that are added up one after the other: at most in a plan with a window, at least in one without
-        const int chain = t.window && full > 0 ? a.nkt : kps;
-        if (t.window && t.bn == 128 && chain > most_chain) continue;
+        // the rows that are rounded most often in a plan with a window, least often in one without
+        int rounded = sp > 1 ? roundings_f32(t.window, t.bn, kps, real) : roundings_f32(t.window, t.bn, a.nkt, 1);
+        if (sp > 1 && full > 0) {
+          const int whole = roundings_f32(t.window, t.bn, a.nkt, 1);
+          rounded = t.window ? std::max(rounded, whole) : std::min(rounded, whole);
+        }
+        if (t.window && rounded > most_rounded) continue;
         const double t_mem = byte[t.parts][c] * (in + part + (full > 0 ? out : 0.0));
         double time = fixed[t.parts][c] + (t.parts ? parts_ahead : 0.0) + sqrt(sqrt(p4(t_thr) + p4(t_lat) + p4(t_mem)));
         if (sp > 1) time += reduce_launch[t.parts][c] + reduce_byte[t.parts][c] * part;
-        if (time < best) { best = time; if (!t.window) { most_part = 1e6 * part; most_chain = chain; } pl->parts = t.parts; pl->window = t.window; kt_step = t.window ? 18 : t.parts ? 2 : 1; pl->BM = t.bm; pl->BN = t.bn; bsp = sp; bfull = (int)full; }
+        if (time < best) {
+          best = time;
+          if (!t.window) { most_part = 1e6 * part; most_rounded = rounded; }
+          pl->parts = t.parts; pl->window = t.window; pl->BM = t.bm; pl->BN = t.bn;
+          pl->rounded = rounded; pl->may_round = most_rounded;
+          kt_step = t.window ? 18 : t.parts ? 2 : 1;
+          bsp = sp; bfull = (int)full;
+        }
       }
     }
   }
@@ -759,8 +780,8 @@ extern "C" int jz_conv2d_f32_describe_plan(int op, const jz_conv_desc* desc, cha
     if ((rc = make_plan_f32(op, &w, &pl)) != JZ_OK) return rc;
   }
   const F32Args& a = pl.args;
-  char form[64];
-  if (pl.window) snprintf(form, sizeof form, "parts, window of %d rows", f32_window_rows(a.g));
+  char form[80];
+  if (pl.window) snprintf(form, sizeof form, "parts, window of %d rows, rounded %d times (%d without)", f32_window_rows(a.g), pl.rounded, pl.may_round);
   else snprintf(form, sizeof form, "%s%s", !pl.dma ? "operands through registers" : pl.parts ? "parts" : "FP32 instructions", pl.gen ? ", per-lane taps" : "");
   snprintf(text, text_bytes, "M %d N %d K %d: %s%s%s, tile %dx%d, %d x %d tiles, %d splits of %d k tiles, %d rows of tiles whole", a.M, a.N, a.Kred,
            widen ? "copies of 4 n channels, " : "", form, pl.classes ? ", residues of the stride" : "", pl.BM, pl.BN, a.tiles_m, a.tiles_n, a.splits,

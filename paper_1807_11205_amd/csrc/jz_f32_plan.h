@@ -44,6 +44,7 @@ struct PlanF32 {
   bool classes = false;  // strided multi-tap backward-data: one launch per residue of the stride (class_args_f32)
   bool widen = false;    // channels rounded up to 4 on copies: `wide` is the layer that runs
   int BM = 128, BN = 128;
+  int rounded = 0, may_round = 0;  // roundings of the large sums (roundings_f32): of this plan, and of the one without a window
   F32Args args{};
   size_t ws_bytes = 0, bytesA = 0, bytesB = 0, bytesD = 0;
   jz_conv_desc wide{};
@@ -59,6 +60,9 @@ struct F32Set {
   unsigned first[FD_MAX_SET + 1];  // workgroup numbers of member k: first[k] .. first[k + 1] - 1
 };
 
+// k tiles that a workgroup of jz_f32_window.h with 64-wide tiles adds up before it starts a new sum, of the k_tiles that it works through: one
+// window or two, whichever makes for fewer roundings (a run's, and one per run).
+__host__ __device__ inline int window_run_f32(int k_tiles) { return 9 + k_tiles / 9 <= 18 + k_tiles / 18 ? 9 : 18; }
 // rows of window that a tile of a layer on jz_f32_window.h gets: its 128 pixels and what their taps reach
 inline int f32_window_rows(const ConvGeom& g) { return 128 + 2 * g.IW + 2 <= 192 ? 192 : 256; }
 

@@ -17,7 +17,7 @@
 // 252 / 250.  What bounds it: with the chip full, power (384 channels: pipes busy 79 % of the compute units' busy cycles at 1.7 GHz, where a
 // loop of products alone has 1.74); with one or two workgroups a compute unit the waits of a tile (14x14: 62 % at 2.3 GHz).
 //
-// Relative errors against 64 bits over eight layers, both directions, are 0.3 ... 1.0 of those of the form before.
+// Relative errors against 64 bits, both directions of 21 layers, are 0.31 ... 1.00 of those of the form before.
 //
 // The reduction runs blocks of 16 channels outside, taps inside.  The loop is unrolled over two blocks, 18 k tiles, so that the tap, both LDS
 // buffers and the register set of a load are constants: the window of the next block is requested behind the filter of one's second
@@ -126,9 +126,9 @@ __device__ __forceinline__ void f32_window_body(const F32Args& a, unsigned block
     f32_split_step<decltype(step_tag)::value>(rawW[Lx], partW[Lx], ldsb + wrW + (win * WIN + Lx * 2048), PART);
   };
 
-  // 64-wide tiles have registers left: the large sums of every 18 k tiles are added up on their own.  A sum is then rounded 18 times and
-  // once more per 18 tiles, as in a reduction split into many parts, whose rounding errors are smaller (14x14, 256 channels: 1.3e-7 with
-  // five splits, 2.8e-7 whole).
+  // 64-wide tiles have registers left: the large sums of every nine or 18 k tiles are added up on their own (window_run_f32), so that they are
+  // rounded no more often than those of a reduction split into many parts (roundings_f32 in jz_conv_f32.hip; the planner sees to it).  Behind
+  // the products it costs at most 1 % over 35 layers (runs of 18 for every length: 28x28, 256 -> 512, backward-data 541 instead of 546 us).
   constexpr bool FOLD = BN == 64;
   f32x16 acc[TM][TN], low[TM][TN], sum[FOLD ? TM : 1][FOLD ? TN : 1];
 #pragma unroll
@@ -140,16 +140,19 @@ __device__ __forceinline__ void f32_window_body(const F32Args& a, unsigned block
         acc[x][y][r] = low[x][y][r] = 0.0f;
         if constexpr (FOLD) sum[x][y][r] = 0.0f;
       }
-  auto fold = [&] {
-#pragma unroll
-    for (int x = 0; x < TM; ++x)
-#pragma unroll
-      for (int y = 0; y < TN; ++y)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          sum[FOLD ? x : 0][FOLD ? y : 0][r] += acc[x][y][r];
-          acc[x][y][r] = 0.0f;
-        }
+  const float end_run = window_run_f32(nk) == 9 ? 1.0f : 0.0f, keep_run = 1.0f - end_run;
+  // The i-th of 16 TT sums, behind the second window (the products that follow start from the constant zero) or, where runs are nine k tiles,
+  // behind the first.  Both products are exact.
+  auto fold = [&](auto i_tag, auto window_tag) {
+    constexpr int I = decltype(i_tag)::value, X = I / 16 / TN, Y = I / 16 % TN;
+    f32x16& s = sum[FOLD ? X : 0][FOLD ? Y : 0];
+    if constexpr (decltype(window_tag)::value == 0) {
+      s[I % 16] = fmaf(acc[X][Y][I % 16], end_run, s[I % 16]);
+      acc[X][Y][I % 16] *= keep_run;
+    } else {
+      s[I % 16] += acc[X][Y][I % 16];
+      acc[X][Y][I % 16] = 0.0f;
+    }
   };
 
   // The parts of the next tile are written behind the first kWritten products, the barrier that waits for them is kMeet products in, the operands
@@ -196,6 +199,10 @@ __device__ __forceinline__ void f32_window_body(const F32Args& a, unsigned block
           }
         });
       }
+      if constexpr (FOLD && TAP + 1 == TAPS && S > 3 * TT) {  // behind the products that follow the last large one (the third group)
+        constexpr int FROM = S - 3 * TT - 1, OF = 3 * TT - 1;
+        static_for<16 * TT * FROM / OF, 16 * TT * (FROM + 1) / OF>([&](auto i) { fold(i, std::integral_constant<int, WINDOW>{}); });
+      }
       if constexpr (S >= 1 && S - 1 < TM) aim(S - 1, NEXT_WINDOW * WIN, dist[NEXT_TAP], NEXT_TAP);  // read_a(2) was the last of this tap
       sched_fence();
     });
@@ -216,7 +223,6 @@ __device__ __forceinline__ void f32_window_body(const F32Args& a, unsigned block
     sched_fence();
     for (int c = chunk0; c < chunk_end; c += 2) {
       static_for<0, 2 * TAPS>([&](auto k) { tile(c + decltype(k)::value / TAPS, k); });
-      if constexpr (FOLD) fold();
     }
     if constexpr (FOLD) {
 #pragma unroll

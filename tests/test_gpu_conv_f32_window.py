@@ -30,6 +30,8 @@ SHAPES = [
     (30, 33, 11, 160, 96, 3, 3, 1, 1),    # 128-wide tiles, every row of tiles split
     (8, 36, 38, 96, 160, 3, 3, 1, 1),
     (49, 1, 45, 416, 32, 3, 3, 1, 1),     # a long reduction in many splits
+    (18, 22, 22, 128, 64, 3, 3, 1, 1),    # backward whole where the plan without a window has three splits
+    (30, 16, 16, 384, 448, 3, 3, 1, 1),   # backward, 252 k tiles: runs of 18
 ]
 # columns of a tile, rows of its window and the rows of tiles whose reduction is split, forward and backward-data; None: another kernel
 FORMS = [
@@ -50,12 +52,14 @@ FORMS = [
     ((128, 192, "all"), None),
     (None, (128, 256, "all")),
     ((64, 256, "all"), None),
+    (None, (64, 192, "none")),
+    ((64, 192, "none"), (64, 192, "last")),
 ]
 
 
 def window_form(jz, op, cfg):  # noqa: F811
     """what FORMS has, as the library plans it"""
-    m = re.search(r"window of (\d+) rows, tile 128x(\d+), \d+ x \d+ tiles, (\d+) splits of \d+ k tiles, (\d+) rows",
+    m = re.search(r"window of (\d+) rows, rounded \d+ times \(\d+ without\), tile 128x(\d+), \d+ x \d+ tiles, (\d+) splits of \d+ k tiles, (\d+) rows",
                   jz.jz_conv2d_f32_describe_plan(op, jz.conv_desc(*cfg)))
     if not m:
         return None
@@ -74,6 +78,12 @@ def test_accuracy(jz, cfg):  # noqa: F811
         err, _ = check_f32(run_f32(jz, op, d, a, b, shape), fn(od, a, b), fn(od, np.abs(a), np.abs(b)), "op %d" % op)
         # the bar of the kernel that takes every tap's values apart: the same products, the large sums rounded once in 16 steps
         assert err <= 2.0 ** -24 * (2 + 2 * (red / 16) ** 0.5), (op, err)
+        if FORMS[SHAPES.index(cfg)][op]:
+            # A sum of n terms is off by n / 2 roundings of its final size, those of the plan's sums and of sums of sums together by
+            # half their number; joining the small sums and what is left out of the products count as two more.  A rounding is
+            # evenly spread over +- 2^-24: 2^-24 / sqrt(3) in the mean square.
+            times = int(re.search(r"rounded (\d+) times", jz.jz_conv2d_f32_describe_plan(op, d))[1])
+            assert err <= 2.0 ** -24 * ((times / 2 + 1) / 3) ** 0.5, (op, err, times)
 
 
 @pytest.mark.parametrize("cfg", [SHAPES[1], SHAPES[7], SHAPES[8], SHAPES[9], SHAPES[11], SHAPES[14], SHAPES[15]], ids=str)
