@@ -53,12 +53,15 @@ __device__ __forceinline__ void f32_window_body(const F32Args& a, unsigned block
   const unsigned vW = (unsigned)(t.m0 - g.IW - 1 + t.kc_row) * pitch + (unsigned)(lane & 3) * 16u, wrW = f32_kc_at(t.kc_row, lane & 3);
   const int chunk0 = t.kt_begin / TAPS, chunk_end = (t.kt_begin + nk) / TAPS;
   const auto rsrcW = __builtin_amdgcn_make_buffer_rsrc((void*)a.A, 0, (int)a.bytesA, 0x00020000);
-  f32x4 rawW[LP], rawB[SETS][LB];
-  auto request_window = [&](int chunk, auto l_tag) {  // one that does not exist is requested out of range, as in jz_f32_split.h
-    constexpr int Lx = decltype(l_tag)::value;
+  // A window comes in at once or, where its registers and those of 128-wide tiles are too many, in two halves.  At once, backward-data spilled 30
+  // registers and waited for all its loads seven times in the loop: 24 images of 43x63, 128 -> 64, 50.0 -> 48.2 us, 41x41, 384 -> 128, 171 -> 167.
+  constexpr int HALVES = BN == 128 && LP == 4 ? 2 : 1, LH = LP / HALVES;
+  f32x4 rawW[LP], rawB[SETS][LB];  // in the loop the second half takes the places of the first
+  auto request_window = [&](int chunk, auto l_tag, auto at_tag) {  // one that does not exist is requested out of range, as in jz_f32_split.h
+    constexpr int Lx = decltype(l_tag)::value, AT = decltype(at_tag)::value;
     const int rows = chunk < chunk_end ? BM + 2 * g.IW + 2 - 64 * Lx : 0;
     const unsigned at = t.kc_row < rows ? vW + (unsigned)(64 * Lx) * pitch : Tile::OOB;
-    rawW[Lx] = __builtin_bit_cast(f32x4, (u32x4)__builtin_amdgcn_raw_buffer_load_b128(rsrcW, (int)at, (int)((unsigned)chunk * FD_BK * 4u), 0));
+    rawW[AT] = __builtin_bit_cast(f32x4, (u32x4)__builtin_amdgcn_raw_buffer_load_b128(rsrcW, (int)at, (int)((unsigned)chunk * FD_BK * 4u), 0));
   };
   auto request_filter = [&](int chunk, int tap, auto set_tag, auto l_tag) {
     constexpr int SET = decltype(set_tag)::value, Lx = decltype(l_tag)::value;
@@ -67,7 +70,7 @@ __device__ __forceinline__ void f32_window_body(const F32Args& a, unsigned block
       rawB[SET][Lx] = __builtin_bit_cast(f32x4, (u32x4)__builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)(voff | none), (int)soff, 0));
     });
   };
-  static_for<0, LP>([&](auto l) { request_window(chunk0, l); });
+  static_for<0, LP>([&](auto l) { request_window(chunk0, l, l); });
   static_for<0, SETS>([&](auto s) { static_for<0, LB>([&](auto l) { request_filter(chunk0, decltype(s)::value, s, l); }); });
   sched_fence();
   // the zeros of both windows, 16 bytes a thread
@@ -116,14 +119,14 @@ __device__ __forceinline__ void f32_window_body(const F32Args& a, unsigned block
 #pragma unroll
     for (int y = 0; y < TN; ++y) fb[k][y] = f32_read_operand<B_KC>(ldsb, rdB, y, st * STAGE + k * B_PART);
   };
-  u32x2 partW[LP], partB[LB];
+  u32x2 partW, partB[LB];
   auto split_filter = [&](auto set_tag, auto l_tag, auto step_tag, int st) {
     constexpr int SET = decltype(set_tag)::value, Lx = decltype(l_tag)::value;
     f32_split_step<decltype(step_tag)::value>(rawB[SET][Lx], partB[Lx], ldsb + wrB[Lx] + st * STAGE, B_PART);
   };
-  auto split_window = [&](auto l_tag, auto step_tag, int win) {
+  auto split_window = [&](auto l_tag, auto at_tag, auto step_tag, int win) {
     constexpr int Lx = decltype(l_tag)::value;
-    f32_split_step<decltype(step_tag)::value>(rawW[Lx], partW[Lx], ldsb + wrW + (win * WIN + Lx * 2048), PART);
+    f32_split_step<decltype(step_tag)::value>(rawW[decltype(at_tag)::value], partW, ldsb + wrW + (win * WIN + Lx * 2048), PART);
   };
 
   // 64-wide tiles have registers left: the large sums of every nine or 18 k tiles are added up on their own (window_run_f32), so that they are
@@ -159,7 +162,8 @@ __device__ __forceinline__ void f32_window_body(const F32Args& a, unsigned block
   // of the next tile's first groups are read behind it.  A window is taken apart during
   // the last kWindowTiles taps.  Neither matters much: from 14 and 16 to 20 and 22 products, three or five taps, 2 % at most.
   constexpr int kWritten = 18 * TT / 4, kMeet = 5 * TT;
-  constexpr int kWindowTiles = 5, kWindowSteps = LP * kSplitSteps;
+  // Halves: the first during taps 3 and 4, then the other is requested, and taken apart during taps 7 and 8.
+  constexpr int kWindowTiles = HALVES == 2 ? 2 : 5, kWindowSteps = LH * kSplitSteps;
   static_assert(kMeet >= 5 * TT && kWritten <= kMeet, "parts 0 and 1 of the pixels are multiplied for the last time by the fifth group of products");
   // the T-th of 18 k tiles: a tap of `chunk`
   auto tile = [&](int chunk, auto t_tag) {
@@ -167,8 +171,9 @@ __device__ __forceinline__ void f32_window_body(const F32Args& a, unsigned block
     constexpr int NEXT_TAP = (TAP + 1) % TAPS, NEXT_WINDOW = TAP + 1 == TAPS ? 1 - WINDOW : WINDOW;
     constexpr int kA[6] = {1, 0, 0, 1, 0, 2}, kB[6] = {1, 1, 0, 0, 2, 0};
     // the steps of taking the next window apart that fall to this tile
-    constexpr int SHARE = TAP - (TAPS - kWindowTiles), W0 = SHARE < 0 ? 0 : SHARE * kWindowSteps / kWindowTiles;
-    constexpr int W1 = SHARE < 0 ? 0 : (SHARE + 1) * kWindowSteps / kWindowTiles, STEPS = kSplitSteps * LB + W1 - W0;
+    constexpr int HALF = HALVES == 2 && TAP > 4 ? 1 : 0, SHARE = TAP - (HALVES == 2 && TAP <= 4 ? 3 : TAPS - kWindowTiles);
+    constexpr int W0 = SHARE < 0 ? 0 : SHARE * kWindowSteps / kWindowTiles, W1 = SHARE < 0 ? 0 : (SHARE + 1) * kWindowSteps / kWindowTiles;
+    constexpr int STEPS = kSplitSteps * LB + W1 - W0;
     read_b(PAR, 0);
     read_b(PAR, 2);
     read_a(2);
@@ -187,15 +192,19 @@ __device__ __forceinline__ void f32_window_body(const F32Args& a, unsigned block
       d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[kB[P]][Y], fa[kA[P]][X], d, 0, 0, 0);
       if constexpr (S < kWritten) {
         static_for<(S * STEPS + kWritten - 1) / kWritten, ((S + 1) * STEPS + kWritten - 1) / kWritten>([&](auto u_tag) {
-          constexpr int U = decltype(u_tag)::value, W = W0 + U - kSplitSteps * LB, Lx = U / kSplitSteps, K = U % kSplitSteps;
+          constexpr int U = decltype(u_tag)::value, W = W0 + U - kSplitSteps * LB;
           if constexpr (W < W0) {
+            constexpr int Lx = U / kSplitSteps, K = U % kSplitSteps;
             constexpr std::integral_constant<int, (T + 1) % SETS> SET{};
             constexpr std::integral_constant<int, Lx> L{};
             split_filter(SET, L, std::integral_constant<int, K>{}, NEXT);
             if constexpr (K + 1 == kSplitSteps) request_filter(chunk + (TAP + 1 + SETS) / TAPS, (TAP + 1 + SETS) % TAPS, SET, L);
-            if constexpr (U + 1 == kSplitSteps * LB && TAP == 0) static_for<0, LP>([&](auto w) { request_window(chunk + 1, w); });
+            if constexpr (U + 1 == kSplitSteps * LB && TAP == 0) static_for<0, LH>([&](auto w) { request_window(chunk + 1, w, w); });
           } else {
-            split_window(std::integral_constant<int, W / kSplitSteps>{}, std::integral_constant<int, W % kSplitSteps>{}, 1 - WINDOW);
+            constexpr int AT = W / kSplitSteps, K = W % kSplitSteps;
+            constexpr std::integral_constant<int, AT> PLACE{};
+            split_window(std::integral_constant<int, HALF * LH + AT>{}, PLACE, std::integral_constant<int, K>{}, 1 - WINDOW);
+            if constexpr (HALVES == 2 && HALF == 0 && K + 1 == kSplitSteps) request_window(chunk + 1, std::integral_constant<int, LH + AT>{}, PLACE);
           }
         });
       }
@@ -208,7 +217,7 @@ __device__ __forceinline__ void f32_window_body(const F32Args& a, unsigned block
     });
   };
   if (nk > 0) {
-    static_for<0, LP>([&](auto l) { static_for<0, kSplitSteps>([&](auto k) { split_window(l, k, 0); }); });
+    static_for<0, LP>([&](auto l) { static_for<0, kSplitSteps>([&](auto k) { split_window(l, l, k, 0); }); });
     constexpr std::integral_constant<int, 0> FIRST{};
     static_for<0, LB>([&](auto l) {
       static_for<0, kSplitSteps>([&](auto k) { split_filter(FIRST, l, k, 0); });
