@@ -358,6 +358,9 @@ int roundings_f32(bool window, int bn, int k_tiles, int parts) {
 // 3x3 layers on their own grid have a third form, the pixels of a tile taken apart once for all taps (jz_f32_window.h); its constants
 // are fits to ten layers in up to eleven splits each.  Over 40 random layers, both directions, its choices take 0.93 of the time of the
 // other forms' in the geometric mean, 0.77 ... 0.92 where the chip is full, and what they lose is within what two timings differ by.
+// Its 128-wide tiles are not offered parts of 18 k tiles, whose first window nothing covers: 1.06 of the time without in the mean of 42 layers (1.00 ...
+// 1.12), where the model has them ahead.  Parts of 36 take 0.96 (107 layers; forward on no more workgroups than compute units 0.98, 0.93 ... 1.05
+// of which 0.04 are the difference of two timings), longer ones 0.91 (111).
 // 3x3, 64 images, forward / backward-data, without and with: 56x56x64 104 / 105 and 99 / 97 us, 28x28x128 101 / 102 and 86 / 84,
 // 14x14x256 105 / 106 and 89 / 89; 7x7x512 93 / 94 either way (100 tiles, and splits only in steps of 18 k tiles).
 void choose_tiling_f32(PlanF32* pl, bool may_split, bool fixed_tile = false, size_t limit = 0, bool may_parts = true) {
@@ -420,6 +423,7 @@ void choose_tiling_f32(PlanF32* pl, bool may_split, bool fixed_tile = false, siz
           rounded = t.window ? std::max(rounded, whole) : std::min(rounded, whole);
         }
         if (t.window && rounded > most_rounded) continue;
+        if (t.window && t.bn == 128 && sp > 1 && kps < 36) continue;
         const double t_mem = byte[t.parts][c] * (in + part + (full > 0 ? out : 0.0));
         double time = fixed[t.parts][c] + (t.parts ? parts_ahead : 0.0) + sqrt(sqrt(p4(t_thr) + p4(t_lat) + p4(t_mem)));
         if (sp > 1) time += reduce_launch[t.parts][c] + reduce_byte[t.parts][c] * part;

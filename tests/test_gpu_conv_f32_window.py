@@ -27,8 +27,8 @@ SHAPES = [
     (24, 43, 63, 128, 64, 3, 3, 1, 1),    # and backward
     (64, 33, 31, 128, 64, 3, 3, 1, 1),
     (40, 56, 22, 32, 96, 3, 3, 1, 1),     # the shortest reduction forward: one pair of windows
-    (30, 33, 11, 160, 96, 3, 3, 1, 1),    # 128-wide tiles, every row of tiles split
-    (8, 36, 38, 96, 160, 3, 3, 1, 1),
+    (15, 57, 11, 192, 96, 3, 3, 1, 1),    # 128-wide tiles, every row of tiles split
+    (27, 11, 44, 96, 256, 3, 3, 1, 1),
     (49, 1, 45, 416, 32, 3, 3, 1, 1),     # a long reduction in many splits
     (18, 22, 22, 128, 64, 3, 3, 1, 1),    # backward whole where the plan without a window has three splits
     (30, 16, 16, 384, 448, 3, 3, 1, 1),   # backward, 252 k tiles: runs of 18
@@ -49,8 +49,8 @@ FORMS = [
     ((64, 256, "none"), (128, 256, "none")),
     ((64, 192, "none"), (128, 192, "none")),
     ((128, 192, "none"), (64, 192, "none")),
-    ((128, 192, "all"), None),
-    (None, (128, 256, "all")),
+    ((128, 192, "all"), (64, 192, "none")),
+    ((64, 256, "none"), (128, 256, "all")),
     ((64, 256, "all"), None),
     (None, (64, 192, "none")),
     ((64, 192, "none"), (64, 192, "last")),

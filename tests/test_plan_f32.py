@@ -44,6 +44,16 @@ def test_no_sum_is_rounded_more_often_with_a_window_than_without(jz):  # noqa: F
     assert seen > 2000
 
 
+def test_128_wide_tiles_with_a_window_are_not_split_into_parts_of_18_k_tiles(jz):  # noqa: F811
+    """4 to 12 % slower than the plan without a window; 64-wide tiles gain with such parts."""
+    rng = random.Random(6)
+    layers = [((30, 33, 11, 160, 96), 0), ((8, 36, 38, 96, 160), 1), ((21, 6, 56, 288, 96), 0)]
+    layers += [((rng.randint(1, 40), rng.randint(1, 63), rng.randint(1, 63), 32 * rng.randint(1, 16), 32 * rng.randint(1, 16)), i % 2) for i in range(6000)]
+    for cfg, op in layers:
+        text = jz.jz_conv2d_f32_describe_plan(op, jz.conv_desc(*cfg, 3, 3, 1, 1))
+        assert not re.search(r"window .* tile 128x128, .* ([2-9]|[1-9]\d+) splits of 18 k tiles", text), (cfg, text)
+
+
 @pytest.mark.parametrize("cfg, op, words", [
     ((64, 7, 7, 512, 512, 3, 3, 1, 1), 2, ("M 512 N 4608 K 3136", "parts", "splits")),
     ((4, 9, 9, 64, 64, 3, 3, 2, 1), 1, ("residues of the stride",)),
