@@ -416,10 +416,12 @@ __global__ __launch_bounds__(LARS_THREADS) void lars_reduce(Tables tb, const flo
 
 // The sums of a group of chunks for an update that works out the rates itself: it also finds the device-resident loss scale where
 // it does not adjust it.
-// Eight wavefronts a SIMD: two workgroups of 1024 threads a compute unit (71 registers, room for one: AlexNet 221 -> 224 us).
+// 54 registers leave room for eight wavefronts a SIMD, two workgroups of 1024 threads a compute unit (with 71 and room for one AlexNet's update takes 224
+// instead of 221 us): the first gradients are requested behind the sums of a fresh workspace; kept across them
+// they spilled there (AlexNet's first call 74.9 us, 67.2 now).
 template <int T>
-__global__ __launch_bounds__(T, 8) void lars_reduce_groups(Tables tb, const float* __restrict__ w, const unsigned short* __restrict__ g16,
-                                                       const float* __restrict__ scale_dev) {
+__global__ __launch_bounds__(T) void lars_reduce_groups(Tables tb, const float* __restrict__ w, const unsigned short* __restrict__ g16,
+                                                        const float* __restrict__ scale_dev) {
   __shared__ double red[2][T / 64];
   constexpr int U = 4, PIECES = LARS_CH / 8;     // 16-byte loads of a thread requested together; of a whole chunk
   const GroupRec gr = tb.group_rec[blockIdx.x];  // requested together with the header: garbage if the header is, but then unused
@@ -437,7 +439,6 @@ __global__ __launch_bounds__(T, 8) void lars_reduce_groups(Tables tb, const floa
       if (p < gr.chunks * PIECES && at + 8 <= gr.end) q[u] = *reinterpret_cast<const uint4*>(g16 + at);
     }
   };
-  if (aligned) fetch(threadIdx.x);
   if (!have_w) {  // a fresh workspace: what the previous update would have left, chunk by chunk
     for (int j = (int)(threadIdx.x / LARS_THREADS); j < gr.chunks; j += T / LARS_THREADS) {
       const int c = gr.chunk0 + j * gr.stride;
@@ -447,6 +448,7 @@ __global__ __launch_bounds__(T, 8) void lars_reduce_groups(Tables tb, const floa
     __threadfence_block();
     __syncthreads();
   }
+  if (aligned) fetch(threadIdx.x);
   for (int i = threadIdx.x; i < gr.chunks * LARS_WAVES; i += T) {
     const double* const p = tb.psum_w + (size_t)(gr.chunk0 + i / LARS_WAVES * gr.stride) * LARS_WAVES + i % LARS_WAVES;
     // a fresh one's sums may share a line with a neighbour's that this compute unit has pulled in before they were written

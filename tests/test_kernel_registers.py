@@ -50,7 +50,7 @@ def notes():
     return found
 
 
-@pytest.mark.parametrize("kernel, variants", [("f32_window_kernel", 8)])
+@pytest.mark.parametrize("kernel, variants", [("f32_window_kernel", 8), ("lars_reduce_groups", 2), ("lars_update", 6), ("lars_begin", 1)])
 def test_vector_registers_are_not_spilled(notes, kernel, variants):
     of = {n: k for n, k in notes.items() if re.search(r"\d" + kernel + r"(I|E|P)", n)}
     assert len(of) == variants, sorted(of)
