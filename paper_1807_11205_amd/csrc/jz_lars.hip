@@ -568,7 +568,7 @@ __global__ __launch_bounds__(LARS_THREADS) void lars_begin(Tables tb, const floa
     if (c0 < c1) next = load_chunk_weights(tb.chunk_rec[c0], w, threadIdx.x);
     for (int c = c0; c < c1; ++c) {
       const ChunkWeights now = next;
-      next = load_chunk_weights(tb.chunk_rec[c + 1 < c1 ? c + 1 : c], w, threadIdx.x);  // on its way while these are added
+      if (c + 1 < c1) next = load_chunk_weights(tb.chunk_rec[c + 1], w, threadIdx.x);  // on its way while these are added
       const double p = wave_sum(chunk_thread_sumsq_w(now));
       if ((threadIdx.x & 63) == 0) tb.psum_w[(size_t)c * LARS_WAVES + (threadIdx.x >> 6)] = p;
     }
