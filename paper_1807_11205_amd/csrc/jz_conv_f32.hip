@@ -387,7 +387,9 @@ void choose_tiling_f32(PlanF32* pl, bool may_split, bool fixed_tile = false, siz
   const int c = pl->op == JZ_FWD ? 0 : pl->op == JZ_BWD_DATA ? 1 : a.bw_linear ? 2 : 3;
   const ConvGeom& g = a.g;
   const bool may_window = pl->op != JZ_BWD_WEIGHT && !pl->gen && !a.sc_on && g.R == 3 && g.S == 3 && g.ph == 1 && g.pw == 1 && g.sh == 1 && g.sw == 1 &&
-                          g.IH == g.OH && g.IW == g.OW && g.IW <= 63 && g.IC % (2 * FD_BK) == 0;
+                          g.IH == g.OH && g.IW == g.OW && g.IW <= 63 && g.IC % (2 * FD_BK) == 0 &&
+                          // offsets of the rows of a last tile's window that lie behind the tensor must not wrap into it
+                          (long long)pl->bytesA + 4ll * g.IC * (128 + g.IW + 1) < 0xfffffff0ll;
   const double in = 1e-6 * ((double)std::min<long long>(pl->bytesA, 4ll * a.M * a.Kred) + (double)std::min<long long>(pl->bytesB, 4ll * a.N * a.Kred));
   // k tiles that a workgroup takes: two at a time in parts, nine taps of twice 16 channels out of a window
   auto even = [](const Tile& t, int k) { return t.window ? (k + 17) / 18 * 18 : t.parts ? k + (k & 1) : k; };

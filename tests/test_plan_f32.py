@@ -54,6 +54,13 @@ def test_128_wide_tiles_with_a_window_are_not_split_into_parts_of_18_k_tiles(jz)
         assert not re.search(r"window .* tile 128x128, .* ([2-9]|[1-9]\d+) splits of 18 k tiles", text), (cfg, text)
 
 
+def test_no_window_reaches_past_32_bits(jz):  # noqa: F811
+    """Rows behind the tensor, up to 128 and a row of the image, are requested: their offsets have to stay out of the tensor's range."""
+    for N, H, W, C, K in ((3, 35, 3, 3047776, 28), (4, 36, 2, 3133216, 28), (1, 12, 13, 4062528, 8)):
+        assert "window" not in jz.jz_conv2d_f32_describe_plan(jz.JZ_FWD, jz.conv_desc(N, H, W, C, K, 3, 3, 1, 1))
+        assert "window" not in jz.jz_conv2d_f32_describe_plan(jz.JZ_BWD_DATA, jz.conv_desc(N, H, W, K, C, 3, 3, 1, 1))
+
+
 @pytest.mark.parametrize("cfg, op, words", [
     ((64, 7, 7, 512, 512, 3, 3, 1, 1), 2, ("M 512 N 4608 K 3136", "parts", "splits")),
     ((4, 9, 9, 64, 64, 3, 3, 2, 1), 1, ("residues of the stride",)),
