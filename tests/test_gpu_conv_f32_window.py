@@ -103,3 +103,19 @@ def test_values_that_parts_cannot_hold(jz, cfg):  # noqa: F811
             assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isinf(got), np.isinf(ref)), op
             ok = np.isfinite(ref)
             check_f32(got[ok], ref[ok], mag[ok], "op %d" % op)
+
+
+@pytest.mark.parametrize("part", [0.0, 0.5, 0.99])
+@pytest.mark.parametrize("cfg", [SHAPES[7], SHAPES[8], SHAPES[16]], ids=str)
+def test_less_workspace_than_reported(jz, cfg, part):  # noqa: F811
+    """Fewer splits or none: the plan for the room there is, on this kernel or another."""
+    from test_gpu_small_workspace import call_f32
+    od, x, w, dy = operands(cfg, 240)
+    d = jz.conv_desc(*cfg)
+    ops = calls(jz, od, x, w, dy)
+    for op in (jz.JZ_FWD, jz.JZ_BWD_DATA):
+        a, b, shape, fn, _ = ops[op]
+        need = jz.jz_conv2d_f32_workspace_bytes(op, d)
+        if FORMS[SHAPES.index(cfg)][op]:
+            assert need > 0, "the case has to split"
+            check_f32(call_f32(jz, op, d, a, b, shape, int(part * need) & ~15), fn(od, a, b), fn(od, np.abs(a), np.abs(b)), "op %d" % op)
