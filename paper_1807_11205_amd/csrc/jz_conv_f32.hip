@@ -355,14 +355,14 @@ int roundings_f32(bool window, int bn, int k_tiles, int parts) {
 // to 128, random layers.  On a quarter of them left out of the fit the choices were 0.8-1.2 % slower than the best.  parts_ahead:
 // by how much the first form has to be faster to be taken, about what the model is wrong by on launches of 6-8 us, where it gains
 // nothing and its choices were up to 0.6 us slower without.  limit: bytes of partial sums.
-// 3x3 layers on their own grid have a third form, the pixels of a tile taken apart once for all taps (jz_f32_window.h); its constants
-// are fits to ten layers in up to eleven splits each.  Over 40 random layers, both directions, its choices take 0.93 of the time of the
-// other forms' in the geometric mean, 0.77 ... 0.92 where the chip is full, and what they lose is within what two timings differ by.
+// 3x3 layers on their own grid have a third form, the pixels of a tile taken apart once for all taps (jz_f32_window.h, with timings); its constants
+// are fits to ten layers in up to eleven splits each: ResNet-50's four at batch 64 and 24, 13x13x384 at 128, 28x28x512 at 16.  They are on the
+// safe side: over 4343 forced plans of 270 random layers the model says 6 ... 10 % too much in the mean.  Over 500 random layers on a plan with a window the
+// choices take 0.87 of the time of the plan without in the geometric mean, 1.03 at worst.
 // Its 128-wide tiles are not offered parts of 18 k tiles, whose first window nothing covers: 1.06 of the time without in the mean of 42 layers (1.00 ...
 // 1.12), where the model has them ahead.  Parts of 36 take 0.96 (107 layers; forward on no more workgroups than compute units 0.98, 0.93 ... 1.05
 // of which 0.04 are the difference of two timings), longer ones 0.91 (111).
-// 3x3, 64 images, forward / backward-data, without and with: 56x56x64 104 / 105 and 99 / 97 us, 28x28x128 101 / 102 and 86 / 84,
-// 14x14x256 105 / 106 and 89 / 89; 7x7x512 93 / 94 either way (100 tiles, and splits only in steps of 18 k tiles).
+// 7x7x512 at batch 64 stays on the other forms (100 tiles, and splits only in steps of 18 k tiles).
 void choose_tiling_f32(PlanF32* pl, bool may_split, bool fixed_tile = false, size_t limit = 0, bool may_parts = true) {
   struct Tile { bool parts, window; int bm, bn, resident; double lat[4], thr[4], prologue[4], own[4]; };
   static const Tile tiles[] = {

@@ -12,10 +12,11 @@
 //   LDS: two windows, each three parts of PR rows of 16 bfloat16 and 16 rows of zeros | two stages of the filter's parts, as in
 //   jz_f32_split.h.  Rows have the KC layout; its swizzle goes by the row's place in LDS, so any 16 consecutive rows read without conflicts.
 //
-// Measured (3x3, 64 images, us forward / backward-data, every tap's values taken apart and this): 28x28, 128 channels 91 / 92 and
-// 77 / 78; 14x14, 256 channels 95 / 98 and 79 / 82; 56x56, 64 channels 97 / 96 and 87 / 87; 13x13, 384 channels, 128 images 291 / 281 and
-// 252 / 250.  What bounds it: with the chip full, power (384 channels: pipes busy 79 % of the compute units' busy cycles at 1.7 GHz, where a
-// loop of products alone has 1.74); with one or two workgroups a compute unit the waits of a tile (14x14: 62 % at 2.3 GHz).
+// Measured (3x3, 64 images, us of a call, split reductions included, calls in a row on other buffers each, one box, forward / backward-data, every
+// tap's values taken apart and this): 56x56, 64 channels 95 / 96 and 89 / 90; 28x28, 128 channels 92 / 93 and 79 / 79; 14x14, 256 channels
+// 95 / 99 and 83 / 85; 28x28, 256 -> 512 570 / 587 and 557 / 561.  What bounds it: with the chip full, power (13x13, 384 channels, 128 images: pipes
+// busy 82 % of the compute units' busy cycles at 1.7 GHz, where a loop of products alone has 1.74); with one or two workgroups a compute unit the
+// waits of a tile (14x14: 61 % at 2.0 GHz; bank conflicts 3-8 % of the busy cycles).
 //
 // Relative errors against 64 bits, both directions of 21 layers, are 0.31 ... 1.00 of those of the form before.
 //
@@ -159,8 +160,8 @@ __device__ __forceinline__ void f32_window_body(const F32Args& a, unsigned block
   };
 
   // The parts of the next tile are written behind the first kWritten products, the barrier that waits for them is kMeet products in, the operands
-  // of the next tile's first groups are read behind it.  A window is taken apart during
-  // the last kWindowTiles taps.  Neither matters much: from 14 and 16 to 20 and 22 products, three or five taps, 2 % at most.
+  // of the next tile's first groups are read behind it.  A window is taken apart during the last kWindowTiles taps.  Neither matters much: over 42
+  // layers, both directions, 14 products of 24 before the barrier 0.6 % slower (4 % at most), 20 and the barrier 22 in 1.0 % (4 %), three taps 0.1 % (1 %).
   constexpr int kWritten = 18 * TT / 4, kMeet = 5 * TT;
   // Halves: the first during taps 3 and 4, then the other is requested, and taken apart during taps 7 and 8.
   constexpr int kWindowTiles = HALVES == 2 ? 2 : 5, kWindowSteps = LH * kSplitSteps;
