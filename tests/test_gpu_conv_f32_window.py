@@ -32,6 +32,8 @@ SHAPES = [
     (49, 1, 45, 416, 32, 3, 3, 1, 1),     # a long reduction in many splits
     (18, 22, 22, 128, 64, 3, 3, 1, 1),    # backward whole where the plan without a window has three splits
     (30, 16, 16, 384, 448, 3, 3, 1, 1),   # backward, 252 k tiles: runs of 18
+    (26, 39, 32, 64, 62, 3, 3, 1, 1),     # results written one by one; backward on copies with 64 channels
+    (26, 39, 32, 62, 64, 3, 3, 1, 1),     # the other way round
 ]
 # columns of a tile, rows of its window and the rows of tiles whose reduction is split, forward and backward-data; None: another kernel
 FORMS = [
@@ -54,6 +56,8 @@ FORMS = [
     ((64, 256, "all"), None),
     (None, (64, 192, "none")),
     ((64, 192, "none"), (64, 192, "last")),
+    ((64, 256, "none"), (64, 256, "none")),
+    ((64, 256, "none"), (64, 256, "none")),
 ]
 
 
